@@ -13,14 +13,16 @@
  *     sum_{i < k*} t_i  +  N_b tau  +  sum_{i > k*} (2 t_i - tau)                       (N_b given)
  *     sum_{i < k*} (t_i + 4 tau)  +  4 tau  +  sum_{i > k*} (2 t_i + 3 tau)             (N_b = 4 S)
  * so for every stage that can be the slowest one, two dynamic programs -- before it with stage
- * times < tau, after it with stage times <= tau -- give the best pipeline around it.
+ * times < tau, after it with stage times <= tau -- give the best pipeline around it.  Stages whose
+ * lower bound (GPUs and stages priced by Lagrangian multipliers) exceeds what was found already are
+ * left out: the result is the minimum over all of them.
  *
  * Two entry points.  oob_exact_minimum keeps no stage count in its tables: it answers for the
  * templates whose stage-count limit S <= N_b cannot bind (microbatches = 0, the paper's planning-time
  * choice N_b = 4 S per pipeline, or microbatches >= min(L, n gpus_per_node)) and reports -2 for
  * the others.  oob_exact_minimum_staged carries the stage count as a third table index and answers
- * for every template and every N_b; its tables live in the workspace and its work grows with the
- * stage limit: for small and middle sizes.
+ * for every template and every N_b; its work grows with the stage limit and its tables live in LDS
+ * where they fit and in the workspace otherwise: for small and middle sizes.
  *
  * Conventions: as in oob_plan.h (DEVICE pointers, caller-owned, enqueued on `stream`, no
  * synchronisation, no allocation; host-visible argument errors are return codes).
@@ -40,12 +42,12 @@ extern "C" {
 #define OOB_EXACT_MAX_L 255      /* layers                                     */
 #define OOB_EXACT_MAX_GPUS 4096  /* n_max * gpus_per_node                      */
 
-/* Bytes of device workspace (256-byte aligned) of oob_exact_minimum: three tables of stage times
- * (the dynamic programs themselves run in LDS); for shapes whose tables exceed LDS also the tables
+/* Bytes of device workspace (256-byte aligned) of oob_exact_minimum: room for what lists of the possible
+ * slowest stages and their bounds take (the dynamic programs themselves run in LDS); for shapes whose tables exceed LDS also the tables
  * of the workgroups in flight.  0 if out of range. */
 size_t oob_exact_workspace_size(int L, int n_max, int gpus_per_node);
 
-/* Bytes of device workspace of oob_exact_minimum_staged: the stage-time tables and about a gigabyte
+/* Bytes of device workspace of oob_exact_minimum_staged: the lists and about a gigabyte
  * of tables (at least 16 workgroups' worth; the entry point uses as many as the workspace it is
  * given holds, at least 16).  0 if out of range. */
 size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per_node, int microbatches);

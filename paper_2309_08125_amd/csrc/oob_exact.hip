@@ -10,145 +10,313 @@
 // slowest stage's node covering [q, u), the stage itself, the remaining h = M - g - d GPUs of that
 // node covering [v, x), and b whole nodes covering [x, L); n = a + 1 + b.
 //
-// k_exact_lds (the fast path; everything in LDS, times as exact integers in doubles).  One
-// workgroup per slowest stage.  Phase 1, per wave and start layer q, no workgroup barrier: the
-// one-node table G_q[p][g] = least cost of covering [q, p) with stages on exactly the first g GPUs
-// of a node; it yields W[q][p] = G_q[p][M] (a whole node) and GU[q][g] = G_q[u][g].  Phase 2: the
-// node-level recurrence NP_a[p] = min_q NP_{a-1}[q] + W[q][p] and PreU[a][g] = min_q NP_a[q] +
-// GU[q][g], one barrier per node count.  The same two phases mirrored for the layers after v,
-// then every (template, a, g) combination.  Global memory is read for the stage times only (one
-// table for the whole call, resident in L2).
+// Branch and bound over the slowest stage.  Of the tens of thousands of possible slowest stages a
+// few hundred can be the slowest stage of a minimum: a stage much slower than the best pipeline's is
+// too dear, a much faster one leaves the other layers too few GPUs.  Four launches find them:
+//   k_exact_prep    validates the profile, forms the prefix sums and lists the possible slowest stages
+//                   in ascending order of their time (counting sort over the leading bits of the double);
+//   k_exact_bounds  per bucket of consecutive entries of that list and per template n a lower bound of
+//                   the cost around each of them: GPUs and stages are priced (Lagrangian multipliers
+//                   lambda per GPU, mu per stage where the stage limit binds) instead of counted, which
+//                   leaves two one-dimensional shortest paths per bucket, side and multiplier;
+//   k_exact_eval<kFirst>  evaluates the most promising slowest stages of every template exactly;
+//   k_exact_filter        keeps those whose bound does not exceed what was found;
+//   k_exact_eval<kRest>   evaluates these exactly, looking at the bounds again as the minima fall.
+// Small jobs (kDirectMax) skip the bounds and evaluate every stage but those too dear by their time alone.
+// Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.80 ms (1 400 of 17 524 slowest stages
+// evaluated); 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 69 us; 48 layers, 8 GPUs per node, N_b = 20 with
+// the limit binding 38.0 -> 2.7 ms (the evaluation of every stage in tables of the workspace before).
+//
+// k_exact_eval: one workgroup per slowest stage, everything in LDS, times as exact integers in doubles.
+// Phase 1, per wave, no workgroup barrier: the one-node table of start layer q, G_q[r][g] = least cost
+// of covering r layers from q on with stages on exactly g GPUs of one node; it yields W[r][q] =
+// G_q[r][M] (a whole node) and GU[r][g] = G_{u-r}[r][g].  Phase 2: the node-level recurrence
+// NP_{a+1}[p] = min_r NP_a[p-r] + W[r][p-r], one barrier per node count.  The same for the layers after v,
+// mirrored, side by side with it; then every (template, a, g) combination.  Stages slower than tau are
+// no use, so a node covers at most a few layers: all loops are bounded by that band.
+// With the stage count as a further index (oob_exact_minimum_staged where the limit S <= N_b can bind) the tables
+// hold plain sums of t per number of stages and the coefficient of tau follows from the counts at the end.
 //
 // k_exact_flat (tables in the caller's workspace, int64): the plain recurrence over (layer, GPUs
-// used [, stages used]).  It serves shapes whose tables exceed LDS and, with the stage count as a
-// third index (plain sums of t; the coefficient of tau follows from the counts at the end), the
-// limit S <= N_b: oob_exact_minimum_staged.
+// used [, stages used]).  It serves shapes whose tables exceed LDS and times beyond 2^52.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "oob_exact.h"
 
 namespace oob_exact {
 
-constexpr int kThreads = 256;       // k_exact_flat
-constexpr int kFlatSlots = 2048;    // its workgroups in flight at most, each with tables of its own
+constexpr int kThreads = 256;    // k_exact_flat
+constexpr int kFlatSlots = 2048; // its workgroups in flight at most, each with tables of its own
 constexpr long long kInf = 1ll << 61;
 constexpr long long kForbidden = 1ll << 62;
 constexpr long long kDoubleExact = 1ll << 52;
 constexpr double kNone = __builtin_huge_val();
+constexpr unsigned long long kNoneBits = 0x7FF0000000000000ull;
 constexpr size_t kLdsLimit = 160 * 1024;
 
+constexpr int kPrepThreads = 1024, kBins = 4096;
+constexpr int kEvalThreads = 512;    // two workgroups per compute unit where LDS allows
+constexpr int kStagedThreads = 1024; // with stage counts: one, it needs all the LDS
+constexpr int kBoundThreads = 576;   // eight waves for the paths, one for the fewest nodes
+// No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second
+// evaluation take 70 us or more whatever the job, what evaluating some thousand stages of a short model takes.
+constexpr int kDirectMax = 4096;
+constexpr int kMaxBuckets = 512, kBucket = 64; // entries per bucket: 64, more only where that would exceed kMaxBuckets
+constexpr int kMaxCount = 64;        // templates per job that the bounds are kept for
+constexpr int kLambdas = 8, kMus = 8;
+constexpr int kFirst = 1, kRest = 2, kAll = 0;
+
+struct Head { // first words of the workspace
+    unsigned ncand, bucket, nbuckets, alive, next, done, over, narrow;
+};
 struct Args {
     oob_profile prof;
-    int L, M, n_min, n_max, Nb, Dmax, Smax;
+    int L, M, n_min, n_max, Nb, Dmax, Smax, fast, staged, bounds;
     long long cap;
     long long limit;      // every cost must stay below this (2^52 for the LDS path, 2^61 otherwise)
-    long long *t;         // [(u (L+1) + v) M + d-1] stage times, -1: impossible
-    double *tds, *tdp;    // the same as doubles, laid out for the two walks of the fast path: tds[(u M + d-1)(L+1) + v]
-                          // (a stage out of u: v runs along a row), tdp[(v M + d-1)(L+1) + u] (a stage into v: u runs along a row)
+    Head *head;
+    long long *PT;        // [(L+1) M] prefix sums of F + B for d GPUs: entry l M + d-1, forbidden entries left out
+    unsigned char *flo;   // [(L+1) M] first layer u for which [u, v) may run on d GPUs of a node (memory, forbidden counts)
+    double *ctau;         // [ncand] possible slowest stages, ascending (by bins): time
+    unsigned *cuvd;       //         u | v << 8 | d << 16
+    float *lb;            // [ncand][count] lower bounds
+    float *blb;           // [nbuckets][count] smallest bound of a bucket
+    unsigned *barg;       // [nbuckets][count] and the entry it belongs to
+    unsigned *list;       // [ncand] entries left to evaluate
+    unsigned *over;       // [ncand] entries that k_exact_flat has to evaluate (tables beyond LDS)
     long long *slots;     // k_exact_flat: [slots][2][(L+1)][(Dmax+1)][J]
     unsigned long long *best; // per template: smallest cost so far
-    unsigned *counter;    // work counter of k_exact_lds
     int *status;
 };
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
-__host__ __device__ inline size_t table_entries(int L, int M) { return (size_t)(L + 1) * (L + 1) * M; }
-// the tables of doubles carry one more row, every entry "impossible", and a few entries of padding: the
-// walks of the fast path read up to three entries past their end, and idle lanes walk the extra row
-__host__ __device__ inline size_t dtable_entries(int L, int M) { return table_entries(L, M) + (size_t)(L + 1) + 8; }
-inline size_t head_bytes(int L, int M) { return 256 + align_up(8 * table_entries(L, M)) + 2 * align_up(8 * dtable_entries(L, M)); }
-constexpr int kGPad = 3; // rows of "impossible" in front of a one-node table
-
-// LDS of k_exact_lds for `nw` waves, in bytes (all arrays 8-byte entries; see the kernel).
 __host__ __device__ inline size_t tri(int L) { return (size_t)L * (L + 1) / 2; }
-inline size_t lds_bytes(int L, int M, int n_max, int count, int nw) {
-    const size_t n = tri(L) + (size_t)(L + 1) * M + 4 * (size_t)(L + 1) + 2 * (size_t)n_max * M +
-                     ((size_t)(L + 1) * M + 1) / 2 + (size_t)(L + 1) / 2 + 1 + L + count +
-                     (size_t)nw * (L + 1 + kGPad) * (M + 1);
-    return 8 * n + 64;
+__host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
+__host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
+
+// ---- what one workgroup's last act is: hand the minima to the caller ------------------------------
+// Results as int64: -1 where no pipeline exists, -2 (unstaged entry point) where the stage limit
+// can bind, so that the minimum without it is not the answer.
+__device__ void finish(const Args &a, bool from_double) {
+    for (int i = threadIdx.x; i <= a.n_max - a.n_min; i += blockDim.x) {
+        const int n = a.n_min + i;
+        const unsigned long long b = __hip_atomic_load(&a.best[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        long long out;
+        if (!a.staged && a.Nb > 0 && a.Nb < imin(a.L, n * a.M)) out = -2;
+        else if (from_double) { const double x = __longlong_as_double((long long)b); out = x < kNone ? (long long)x : -1; }
+        else out = (long long)b >= kInf / 2 ? -1 : (long long)b;
+        ((long long *)a.best)[i] = out;
+    }
 }
-inline int lds_waves(int L, int M, int n_max, int count) { // 0: does not fit
-    for (int nw : {16, 12, 8, 4, 2}) // the one-node phase is bound by the latency of a table row: as many waves as fit
-        if (lds_bytes(L, M, n_max, count, nw) <= kLdsLimit) return nw;
-    return 0;
+// True in every thread of the workgroup that finishes last of the grid's (which all call this once).  What the
+// others hand over are atomics on `best`, performed at the point where the last one reads them: waiting for the own ones
+// orders them, no cache has to be written back (a release at agent scope, once per workgroup, cost more than the work
+// of small jobs).
+__device__ bool last_workgroup(const Args &a) {
+    __shared__ unsigned s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_last = __hip_atomic_fetch_add(&a.head->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    return s_last != 0;
 }
 
-// Clears the result and validates the magnitudes: every cost is at most mult * w, w = the sum over
+// ---------------------------------------------------------------------------------------------
+// Preparation, one workgroup.  Validates the magnitudes: every cost is at most mult * w, w = the sum over
 // the layers of the slowest allowed F + B of the layer plus its boundary term (a bound on the sum
 // of all stage times of any pipeline), mult = N_b + 2 (4 S_max + 2 when N_b = 4 S).  status =
-// OOB_EOVERFLOW unless that stays below the limit of the path.  One workgroup; runs before
-// k_exact_stages, which only ever sets the status to OOB_EINVAL.
-__global__ void __launch_bounds__(kThreads) k_exact_init(Args a) {
-    __shared__ long long s_sum[kThreads];
-    const int count = a.n_max - a.n_min + 1;
-    for (int i = threadIdx.x; i < count; i += kThreads) a.best[i] = 0x7FF0000000000000ull; // +inf as a double, huge as an integer
-    if (threadIdx.x == 0) *a.counter = 0;
+// OOB_EOVERFLOW unless that stays below the limit of the path; OOB_EINVAL for a negative entry.
+// One launch in place of four (62 + 13 + 4 + 4 us at 98 layers x 8 GPUs): prefix sums instead of a table of all stage
+// times, 45 us there and 14 us at 26 x 4, most of it the two walks over the layer pairs with LDS atomics.
+// ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ unsigned long long scan_add(unsigned long long x, int lane) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned long long y = __shfl_up(x, d, 64);
+        if (lane >= d) x += y;
+    }
+    return x;
+}
+__device__ __forceinline__ int scan_max(int x, int lane) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(x, d, 64);
+        if (lane >= d) x = imax(x, y);
+    }
+    return x;
+}
+// Triple i -> (u, v, d), u < v, d fastest, then u.
+__device__ __forceinline__ void triple(int i, int M, int *u, int *v, int *d) {
+    const int p = i / M;
+    *d = i - p * M + 1;
+    int w = (int)((sqrtf(8.0f * (float)p + 1.0f) + 1.0f) * 0.5f);
+    while (w * (w - 1) / 2 > p) --w;
+    while (w * (w + 1) / 2 <= p) ++w;
+    *v = w;
+    *u = p - w * (w - 1) / 2;
+}
+
+__global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
+    HIP_DYNAMIC_SHARED(long long, s_prep) // [(L+1)] bytes, [(L+1) M] times where the fast path needs them, then bytes
+    __shared__ int s_hist[kBins];
+    __shared__ int s_bad, s_wave[kPrepThreads / 64];
+    __shared__ unsigned long long s_sum[kPrepThreads / 64], s_min;
+    const int L = a.L, M = a.M, W = L + 1, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
     const long long *fwd = (const long long *)a.prof.fwd_ns, *bwd = (const long long *)a.prof.bwd_ns;
-    const long long *bnd = (const long long *)a.prof.boundary_ns;
-    long long acc = 0;
-    for (int l = threadIdx.x; l < a.L; l += kThreads) {
+    const long long *mem = (const long long *)a.prof.mem_bytes, *bnd = (const long long *)a.prof.boundary_ns;
+    unsigned long long *s_pm = (unsigned long long *)s_prep;
+    long long *s_pt = s_prep + W;
+    unsigned char *s_lf = (unsigned char *)(s_pt + (a.fast ? (size_t)W * M : 0));
+    const int count = a.n_max - a.n_min + 1;
+    for (int i = tid; i < count; i += blockDim.x) a.best[i] = kNoneBits; // +inf as a double, huge as an integer
+    for (int i = tid; i < kBins; i += blockDim.x) s_hist[i] = 0;
+    if (tid == 0) { s_bad = 0; s_min = kNoneBits; }
+    __syncthreads();
+    // magnitudes and signs
+    unsigned long long acc = 0;
+    bool bad = false;
+    for (int l = tid; l < L; l += blockDim.x) {
         long long worst = 0;
-        for (int d = 1; d <= a.M; ++d) {
-            const long long f = fwd[(size_t)l * a.M + d - 1], b = bwd[(size_t)l * a.M + d - 1];
+        for (int d = 0; d < M; ++d) {
+            const long long f = fwd[(size_t)l * M + d], b = bwd[(size_t)l * M + d];
+            bad = bad || f < 0 || b < 0;
             if (f < 0 || b < 0 || f >= kForbidden || b >= kForbidden) continue;
             const long long fb = (f >= kInf || b >= kInf) ? kInf : f + b;
             worst = fb > worst ? fb : worst;
         }
         const long long x = bnd[l];
+        bad = bad || x < 0 || mem[l] < 0;
         if (x > 0) worst = (x >= kInf || worst >= kInf) ? kInf : worst + x;
-        acc = (acc + worst >= kInf || worst >= kInf) ? kInf : acc + worst;
+        acc = acc + (unsigned long long)worst;
+        if (acc > (unsigned long long)kInf) acc = (unsigned long long)kInf;
     }
-    s_sum[threadIdx.x] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long w = 0;
-        for (int i = 0; i < kThreads; ++i) w = (w + s_sum[i] >= kInf) ? kInf : w + s_sum[i];
-        const long long mult = (a.Nb > 0 ? (long long)a.Nb : 4ll * a.Smax) + 2;
-        *a.status = w >= a.limit / mult ? OOB_EOVERFLOW : OOB_OK;
+    if (bad) s_bad = 1;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        acc += __shfl_xor(acc, d, 64);
+        if (acc > (unsigned long long)kInf) acc = (unsigned long long)kInf;
     }
-}
-
-// Every entry of the two tables of doubles, the extra row and the padding included: "impossible".
-__global__ void k_exact_fill(Args a) {
-    const size_t n = dtable_entries(a.L, a.M);
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        a.tds[i] = kNone;
-        a.tdp[i] = kNone;
-    }
-}
-
-// Stage times of all (u, v, d): one thread per (u, d) walks v.  A negative profile entry sets the
-// status to OOB_EINVAL (every writer stores the same value, so the order does not matter).
-__global__ void k_exact_stages(Args a) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.L * a.M) return;
-    const int u = i / a.M, d = i % a.M + 1;
-    const long long *fwd = (const long long *)a.prof.fwd_ns, *bwd = (const long long *)a.prof.bwd_ns;
-    const long long *mem = (const long long *)a.prof.mem_bytes, *bnd = (const long long *)a.prof.boundary_ns;
-    long long time = 0, bytes = 0;
-    bool ok = true, bad = false;
-    for (int v = u + 1; v <= a.L; ++v) {
-        const long long f = fwd[(size_t)(v - 1) * a.M + d - 1], b = bwd[(size_t)(v - 1) * a.M + d - 1];
-        if (f < 0 || b < 0 || mem[v - 1] < 0 || bnd[v - 1] < 0) bad = true;
-        if (f >= kForbidden || b >= kForbidden) ok = false;
-        time += ok ? f + b : 0;
-        bytes += mem[v - 1];
-        long long val = -1;
-        if (ok && (bytes + d - 1) / d <= a.cap) val = time + (v < a.L ? bnd[v - 1] : 0);
-        const size_t o = ((size_t)u * (a.L + 1) + v) * a.M + d - 1;
-        a.t[o] = val;
-        if (val >= 0) { // an impossible stage keeps the fill value of the tables of doubles
-            a.tds[((size_t)u * a.M + d - 1) * (a.L + 1) + v] = (double)val;
-            a.tdp[((size_t)v * a.M + d - 1) * (a.L + 1) + u] = (double)val;
+    if (lane == 0) s_sum[wave] = acc;
+    // prefix sums, one wave per GPU count; wave nw - 1 also takes the bytes
+    for (int d = wave; d < M; d += nw) {
+        unsigned long long carry = 0;
+        int last = 0; // first layer after the last forbidden one so far
+        if (lane == 0) { a.PT[d] = 0; if (a.fast) s_pt[d] = 0; s_lf[d] = 0; }
+        for (int l0 = 0; l0 < L; l0 += 64) {
+            const int l = l0 + lane;
+            const long long f = l < L ? fwd[(size_t)l * M + d] : 0, b = l < L ? bwd[(size_t)l * M + d] : 0;
+            const bool forb = f >= kForbidden || b >= kForbidden;
+            const unsigned long long x = scan_add(forb ? 0ull : (unsigned long long)f + (unsigned long long)b, lane) + carry;
+            const int lf = imax(scan_max(forb ? l + 1 : 0, lane), last);
+            if (l < L) {
+                a.PT[(size_t)(l + 1) * M + d] = (long long)x;
+                if (a.fast) s_pt[(size_t)(l + 1) * M + d] = (long long)x;
+                s_lf[(size_t)(l + 1) * M + d] = (unsigned char)lf;
+            }
+            carry = __shfl(x, 63, 64);
+            last = __shfl(lf, 63, 64);
         }
     }
-    if (bad) atomicExch(a.status, OOB_EINVAL);
+    if (wave == nw - 1) {
+        unsigned long long carry = 0;
+        if (lane == 0) s_pm[0] = 0;
+        for (int l0 = 0; l0 < L; l0 += 64) {
+            const int l = l0 + lane;
+            const unsigned long long x = scan_add(l < L ? (unsigned long long)mem[l] : 0ull, lane) + carry;
+            if (l < L) s_pm[l + 1] = x;
+            carry = __shfl(x, 63, 64);
+        }
+    }
+    __syncthreads();
+    unsigned long long w = 0;
+    for (int i = 0; i < nw; ++i) { w += s_sum[i]; if (w > (unsigned long long)kInf) w = (unsigned long long)kInf; }
+    const long long mult = (a.Nb > 0 ? (long long)a.Nb : 4ll * a.Smax) + 2;
+    const int st = s_bad ? OOB_EINVAL : (long long)w >= a.limit / mult ? OOB_EOVERFLOW : OOB_OK;
+    const bool narrow = a.fast && (long long)w < kDoubleExact / mult; // every cost an exact integer in a double
+    // first layer a stage into v can start at
+    for (int i = tid; i < W * M; i += blockDim.x) {
+        const int v = i / M, d = i - v * M + 1;
+        const unsigned long long room = (unsigned long long)a.cap > 0x7FFFFFFFFFFFFFFFull / d ? 0x7FFFFFFFFFFFFFFFull
+                                                                                              : (unsigned long long)a.cap * d;
+        int lo = s_lf[i], hi = v; // ceil(bytes / d) <= cap; nothing fits: v
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (s_pm[v] - s_pm[mid] <= room) hi = mid; else lo = mid + 1;
+        }
+        a.flo[i] = (unsigned char)lo;
+        s_lf[i] = (unsigned char)lo; // (only this thread reads entry i before the barrier)
+    }
+    if (st == OOB_OK && narrow) // the fastest stage is one of a single layer
+        for (int i = tid; i < L * M; i += blockDim.x) {
+            const int l = i / M, d = i - l * M;
+            const long long t = s_pt[(size_t)(l + 1) * M + d] - s_pt[(size_t)l * M + d] + (l + 1 < L ? bnd[l] : 0);
+            if (t > 0) atomicMin(&s_min, (unsigned long long)__double_as_longlong((double)t));
+        }
+    __syncthreads();
+    int total = 0;
+    if (st == OOB_OK && narrow) { // list the possible slowest stages by time
+        const int kmin = (int)(s_min >> 44), inv = 65536 / M + 1;
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int v = 1 + wave; v <= L; v += nw) { // a wave takes the stages that end at layer v
+                const long long x = v < L ? bnd[v - 1] : 0;
+                for (int i0 = lane; i0 < v * M; i0 += 256) { // four entries of a lane in flight
+                    double tau[4];
+                    int pos[4], ud[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int i = i0 + 64 * q, ic = i < v * M ? i : 0;
+                        const int u = (int)((unsigned)(ic * inv) >> 16), d = ic - u * M; // i / M: exact below 2^14 for M <= 64
+                        const bool ok = (i < v * M) & (u >= s_lf[v * M + d]);
+                        tau[q] = (double)(s_pt[v * M + d] - s_pt[ic] + x);
+                        ud[q] = u | (d + 1) << 16;
+                        pos[q] = ok ? imax(0, imin((int)((unsigned long long)__double_as_longlong(tau[q]) >> 44) - kmin, kBins - 1)) : -1;
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) if (pos[q] >= 0) pos[q] = atomicAdd(&s_hist[pos[q]], 1);
+                    if (pass)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (pos[q] >= 0) { a.ctau[pos[q]] = tau[q]; a.cuvd[pos[q]] = (unsigned)(ud[q] | v << 8); }
+                }
+            }
+            __syncthreads();
+            if (pass) break;
+            // exclusive scan of the bins: kBins / kPrepThreads each
+            constexpr int per = kBins / kPrepThreads;
+            int h[per], sum = 0;
+#pragma unroll
+            for (int q = 0; q < per; ++q) { h[q] = s_hist[tid * per + q]; sum += h[q]; }
+            int incl = sum;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) { const int y = __shfl_up(incl, d, 64); if (lane >= d) incl += y; }
+            if (lane == 63) s_wave[wave] = incl;
+            __syncthreads();
+            int base = incl - sum;
+            for (int i = 0; i < nw; ++i) { if (i < wave) base += s_wave[i]; total += s_wave[i]; }
+#pragma unroll
+            for (int q = 0; q < per; ++q) { s_hist[tid * per + q] = base; base += h[q]; }
+            __syncthreads();
+        }
+    }
+    if (tid == 0) {
+        *a.status = st;
+        Head h;
+        h.ncand = (unsigned)total;
+        h.bucket = (unsigned)imax(kBucket, (total + kMaxBuckets - 1) / kMaxBuckets);
+        h.nbuckets = ((unsigned)total + h.bucket - 1) / h.bucket;
+        h.alive = h.next = h.done = h.over = 0;
+        h.narrow = narrow;
+        *a.head = h;
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
-// The fast path.
+// Shared pieces of the LDS kernels.
 // ---------------------------------------------------------------------------------------------
 // What one wave has written to LDS is read by its other lanes: program order of the LDS operations
 // of a wave is execution order, the fences keep the compiler from moving them.
@@ -157,9 +325,9 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-// Minimum over aligned groups of 4 / 8 consecutive lanes, in every lane of the group, with data-parallel
-// moves (quad permutations 1,0,3,2 and 2,3,0,1; then the mirror image within each half row, which
-// hands every lane a lane of the other quad of its group of eight).
+// Minimum over aligned groups of 4 / 16 consecutive lanes, in every lane of the group, with data-parallel
+// moves (quad permutations 1,0,3,2 and 2,3,0,1; then the mirror images within each half row and row,
+// which hand every lane a lane of the other half).
 template <int CTRL> __device__ __forceinline__ double dpp_f64(double x) {
     int lo = __double2loint(x), hi = __double2hiint(x);
     lo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false);
@@ -170,300 +338,795 @@ __device__ __forceinline__ double min4(double x) {
     x = fmin(x, dpp_f64<0xB1>(x));
     return fmin(x, dpp_f64<0x4E>(x));
 }
-__device__ __forceinline__ double min8(double x) {
+__device__ __forceinline__ double min16(double x) {
     x = min4(x);
-    return fmin(x, dpp_f64<0x141>(x));
+    x = fmin(x, dpp_f64<0x141>(x));
+    return fmin(x, dpp_f64<0x140>(x));
 }
 
-struct Lds {
-    double *W;    // [tri(L)]  one whole node covering [q, p), q < p: index q L - q (q-1)/2 + p - q - 1
-    double *GU;   // [(L+1)][M]  g GPUs (entry g, 1 <= g < M) of a node covering [q, u) / (mirrored) [v, x)
-    double *NP;   // [2][2][L+1]  per side: node-level tables of the previous and the current node count
-    double *PU;   // [n_max][M]  PreU[a][g]
-    double *SV;   // [n_max][M]  SufV[b][h]
-    int *lo;      // [(L+1)][M]  first (prefix) / last (suffix) layer a stage into / out of p can reach
-    int *lomin;   // [L+1]       the extreme of lo over the GPU counts
-    double *bnd;  // [L]
-    unsigned long long *best; // [count]
-    double *G;    // [waves][(L+1)][(M+1)]
-};
-__device__ __forceinline__ size_t widx(int q, int p, int L) { return (size_t)q * L - (size_t)q * (q - 1) / 2 + (p - q - 1); }
+// Lane 15 of the row below in rows 1 and 3 (rows 0 and 2: unchanged).
+__device__ __forceinline__ double row_below(double x) {
+    int lo = __double2loint(x), hi = __double2hiint(x);
+    lo = __builtin_amdgcn_update_dpp(lo, lo, 0x142, 0xA, 0xF, false);
+    hi = __builtin_amdgcn_update_dpp(hi, hi, 0x142, 0xA, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
 
-// The two sides of the slowest stage [u, v).  MIRROR = false: the layers [0, e) before it (e = u); a
-// one-node table starts at layer q and grows to the right, a stage [q', p) into p costs t + ptau * tau
-// and needs t < tau.  MIRROR = true: the layers [e, L) after it (e = v); a one-node table ends at
-// layer q and grows to the left, a stage [p, w) out of p costs 2 t + stau * tau and needs t <= tau.
-// Result per side: OUT[c][g] = least cost of covering the side with c whole nodes and g more GPUs
-// next to the slowest stage, g = 0 .. M-1.  The two sides use disjoint parts of every table that is
-// indexed by layers (W, GU, lo, lomin), so they run side by side.
-
-// Reach of a stage into / out of layer p on dd GPUs (entry i = p M + dd - 1), by bisection.
-template <bool MIRROR>
-__device__ __forceinline__ int side_reach(const Args &a, const Lds &s, int p, int dd, double tau) {
-    const int L = a.L, M = a.M;
-    if (!MIRROR) {
-        // [x, p) only gets slower and heavier as x goes down (impossible at the far end): the stages
-        // with t < tau are x = r .. p-1
-        int lo = 0, hi = p; // answer in [lo, hi]; hi = p: none
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            const double tt = a.tdp[((size_t)p * M + dd - 1) * (L + 1) + mid];
-            if (tt < tau) hi = mid; else lo = mid + 1;
-        }
-        return lo;
+// The profile in LDS: PT[l M + d-1] prefix sums, PX = PT plus the boundary term of a stage ending at layer l,
+// X the boundary terms, flo as in Args.
+struct Prof { double *PT, *PX, *X; unsigned char *flo; };
+__host__ __device__ inline size_t prof_doubles(int L, int M) { return 2 * (size_t)(L + 1) * M + (L + 1) + ((size_t)(L + 1) * M + 7) / 8; }
+__device__ __forceinline__ Prof load_prof(const Args &a, double *lds) {
+    const int W = a.L + 1, n = W * a.M;
+    Prof p;
+    p.PT = lds; p.PX = p.PT + n; p.X = p.PX + n; p.flo = (unsigned char *)(p.X + W);
+    const long long *bnd = (const long long *)a.prof.boundary_ns;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const int l = i / a.M;
+        const double pt = (double)a.PT[i];
+        p.PT[i] = pt;
+        p.PX[i] = pt + (l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0);
+        p.flo[i] = a.flo[i];
     }
-    // [p, w) as w goes up: impossible stays impossible and the time without the boundary term only
-    // grows: those stages are w = p+1 .. r
-    int lo = p, hi = L; // answer in [lo, hi]; lo = p: none
+    for (int l = threadIdx.x; l < W; l += blockDim.x) p.X[l] = l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0;
+    return p;
+}
+// Reach of a stage on dd GPUs into layer p (before the slowest stage: it starts at r .. p-1; p: none) that
+// takes less than tau (STRICT) or at most tau: it only gets slower and heavier as its start goes down.
+template <bool STRICT>
+__device__ __forceinline__ int reach_back(const Prof &s, int M, int p, int dd, double tau) {
+    const double end = s.PX[p * M + dd - 1];
+    int lo = s.flo[p * M + dd - 1], hi = p;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        const double t = end - s.PT[mid * M + dd - 1];
+        if (STRICT ? t < tau : t <= tau) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+// Reach of a stage on dd GPUs out of layer p (after the slowest stage: it ends at p+1 .. r; p: none).  Impossible
+// stays impossible and the time without the boundary term only grows as the end goes up.
+__device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int p, int dd, double tau) {
+    const double start = s.PT[p * M + dd - 1];
+    int lo = p, hi = L;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        const double tt = a.tds[((size_t)p * M + dd - 1) * (L + 1) + mid];
-        if (tt - (mid < L ? s.bnd[mid - 1] : 0.0) <= tau) lo = mid; else hi = mid - 1;
+        if (s.flo[mid * M + dd - 1] <= p && s.PT[mid * M + dd - 1] - start <= tau) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
 
-// One-node table of start layer q (one wave): rows, then its contribution to W and GU.
-template <bool MIRROR>
-__device__ void one_node_table(const Args &a, const Lds &s, int e, int q, double tau, double wt, double add, double *G) {
-    const int L = a.L, M = a.M, lane = threadIdx.x & 63, gi = lane >> 3, di = lane & 7;
-    // row r of G = layer q + r (prefix) / q - r (suffix); row 0: nothing covered
-    for (int g = lane; g <= M; g += 64) G[g] = g == 0 ? 0.0 : kNone;
+// ---------------------------------------------------------------------------------------------
+// Lower bounds.  For a bucket of slowest stages with times lo .. hi and multipliers lambda (per GPU) and
+// mu (per stage) the cost of any pipeline of n nodes around one of them is at least
+//     mid tau + P[u] + S[v] + lambda d + mu - lambda n M - mu S_max,
+// P[u] / S[v] = least sum over the stages of [0, u) / [v, L) of (weighted time + lambda GPUs + mu), stage times
+// at most hi, tau's share in a weight taken from the end of the bucket that makes it smaller: exactly n M
+// GPUs and at most S_max stages are used, whatever the prices.  The bound is the largest over the
+// multipliers.  Row after row of the two paths; a wave takes two lambdas, thirty-two lanes each share out the
+// starts of the last stage, eight GPU counts side by side.  Bound by the chain of rows (LDS read, reduction over the
+// lanes, LDS write per row) at one workgroup per bucket: 183 us at 98 layers x 8 GPUs, 274 buckets.
+// ---------------------------------------------------------------------------------------------
+__device__ const double kLambdaGiven[kLambdas] = {0, 0.04, 0.1, 0.2, 0.4, 0.8, 1.6, 3.5}; // more nodes pay (C falls with n) ...
+__device__ const double kLambda4S[kLambdas] = {0, -0.06, -0.14, -0.25, -0.43, -0.7, -1.3, -3.5}; // ... or cost
+__device__ const double kMuStep[kMus] = {0, 0.1, 0.2, 0.35, 0.5, 0.75, 1, 1.5};
+
+// Fewest nodes that can cover the layers at all with stages of at most the bucket's slowest time (boundary terms left
+// out of the test, so never too many).  One wave, lane = start layer: the farthest layer that g GPUs of a node
+// reach follows from the farthest that fewer do, because a stage that starts later also ends later; then node after
+// node from the farthest layer so far.
+constexpr int kCoverGpus = 8;
+__device__ int fewest_nodes(int L, int M, const unsigned char *reach, unsigned char *s_far) {
+    const int lane = threadIdx.x & 63;
+    int before = 0; // farthest of the start layers before this round's
+    for (int q0 = 0; q0 < L; q0 += 64) {
+        const int q = imin(q0 + lane, L - 1);
+        int far[kCoverGpus + 1];
+        far[0] = q;
+#pragma unroll
+        for (int g = 1; g <= kCoverGpus; ++g) far[g] = q;
+#pragma unroll
+        for (int g = 0; g < kCoverGpus; ++g)
+#pragma unroll
+            for (int dd = 1; dd <= kCoverGpus - g; ++dd)
+                if (g + dd <= M && far[g] < L) far[g + dd] = imax(far[g + dd], (int)reach[far[g] * M + dd - 1]);
+                else if (g + dd <= M) far[g + dd] = L;
+        int f = q;
+#pragma unroll
+        for (int g = 1; g <= kCoverGpus; ++g) if (g == M) f = far[g];
+        f = imax(scan_max(f, lane), before);
+        if (q0 + lane < L) s_far[q0 + lane] = (unsigned char)f;
+        before = __shfl(f, 63, 64);
+    }
     wave_sync();
-    const int rows = MIRROR ? q - e : e - q;
-    int lastfin = q; // the layer farthest from q that some number of GPUs can be made to reach
-    for (int r = 1; r <= rows; ++r) {
-        const int p = MIRROR ? q - r : q + r;
-        // farthest layer any stage of this row reaches (the same in every lane: say so, the loops below
-        // then count in scalar registers)
-        const int far = __builtin_amdgcn_readfirstlane(MIRROR ? min(q, s.lomin[p]) : max(q, s.lomin[p]));
-        if (MIRROR ? lastfin > far : lastfin < far) { // no stage of this row starts from a layer the table has reached
-            for (int g = lane; g <= M; g += 64) G[r * (M + 1) + g] = kNone;
-            wave_sync();
-            continue;
-        }
-        bool fin = false;
-        const int trips = MIRROR ? far - p : p - far; // stages [x, p), x = p-1 .. far / [p, x), x = p+1 .. far
-        for (int gt = 0; gt * 8 < M; ++gt) {
-            const int g = gt * 8 + gi + 1;
+    int n = 0, at = 0;
+    while (at < L && n <= L) { // (a node that covers nothing: never)
+        const int to = s_far[at];
+        if (to <= at) return L + 1;
+        at = to;
+        ++n;
+    }
+    return n;
+}
+
+__host__ __device__ inline size_t bound_doubles(int L, int M, int mus) {
+    return prof_doubles(L, M) + 2 * (((size_t)(L + 1) * M + 7) / 8) + (size_t)mus * kLambdas * 2 * (L + 1) +
+           kBucket * kMaxCount / 2 + 32;
+}
+template <int MT>
+__global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus) {
+    constexpr int CW = MT ? MT : 8;
+    HIP_DYNAMIC_SHARED(double, s_dyn)
+    __shared__ unsigned long long s_lo, s_hi;
+    __shared__ double s_lam[kLambdas], s_mu[kMus];
+    __shared__ int s_fewest;
+    if (*a.status != OOB_OK || !a.head->narrow) return;
+    const unsigned b = blockIdx.x, K = a.head->bucket;
+    if (b >= a.head->nbuckets) return;
+    const int L = a.L, M = MT ? MT : a.M, W = L + 1, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned c0 = b * K, c1 = min(a.head->ncand, c0 + K);
+    const Prof s = load_prof(a, s_dyn);
+    unsigned char *rb = (unsigned char *)(s_dyn + prof_doubles(L, M)), *rf = rb + ((size_t)W * M + 7) / 8 * 8;
+    double *PS = (double *)(rf + ((size_t)W * M + 7) / 8 * 8); // [mu][lambda][side][L+1]
+    float *s_lb = (float *)(PS + (size_t)mus * kLambdas * 2 * W); // [kBucket][kMaxCount]
+    unsigned char *s_far = (unsigned char *)(s_lb + kBucket * kMaxCount); // [256] for fewest_nodes()
+    if (threadIdx.x == 0) { s_lo = kNoneBits; s_hi = 0; s_fewest = 0; }
+    __syncthreads();
+    for (unsigned c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
+        atomicMin(&s_lo, (unsigned long long)__double_as_longlong(a.ctau[c]));
+        atomicMax(&s_hi, (unsigned long long)__double_as_longlong(a.ctau[c]));
+    }
+    __syncthreads();
+    const double lo = __longlong_as_double((long long)s_lo), hi = __longlong_as_double((long long)s_hi);
+    for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
+        const int p = i / M, dd = i - p * M + 1;
+        rb[i] = (unsigned char)reach_back<false>(s, M, p, dd, hi);
+        rf[i] = (unsigned char)reach_on(s, L, M, p, dd, hi);
+    }
+    const bool given = a.Nb > 0;
+    if (threadIdx.x < kLambdas) s_lam[threadIdx.x] = (given ? kLambdaGiven[threadIdx.x] : kLambda4S[threadIdx.x]) * lo;
+    else if (threadIdx.x - kLambdas < kMus) s_mu[threadIdx.x - kLambdas] = kMuStep[threadIdx.x - kLambdas] * lo;
+    __syncthreads();
+    const double pw = given ? 0.0 : 4.0 * lo, sw = given ? -hi : 3.0 * lo, mid = given ? (double)a.Nb : 4.0;
+    const int sub = lane & 31, nt = nw - 1; // the last wave: fewest nodes
+    if (wave == nt && M <= kCoverGpus) {
+        const int n = fewest_nodes(L, M, rf, s_far);
+        if (lane == 0) s_fewest = n;
+    }
+    for (int task = wave; wave < nt && task < mus * kLambdas; task += nt) { // two lambdas, one side
+        const int side = task & 1, lg = (task >> 1) % (kLambdas / 2), mi = (task >> 1) / (kLambdas / 2);
+        const int li = lg * 2 + (lane >> 5);
+        const double l = s_lam[li], mu = s_mu[mi];
+        double *P = PS + ((size_t)(mi * kLambdas + li) * 2 + side) * W;
+        for (int x = sub; x <= L; x += 32) P[x] = x == (side ? L : 0) ? 0.0 : kNone;
+        wave_sync();
+        auto rows = [&](auto side_c) {
+        constexpr bool side = decltype(side_c)::value;
+        for (int row = 1; row <= L; ++row) {
+            // stages [x, row) before, [p, x) after the slowest stage; a lane's share of the x, eight GPU counts side by side
+            const int p = side ? L - row : row;
+            const double *near = side ? s.PT : s.PX, *far = side ? s.PX : s.PT;
+            const unsigned char *reach = side ? rf : rb;
+            const double per = side ? 2.0 : -1.0;
             double acc = kNone;
-            for (int dt = 0; dt <= gt; ++dt) {
-                const int dd = dt * 8 + di + 1;
-                const bool on = g <= M && dd <= g;
-                // Every lane walks the row's whole reach (uniform trip count, loads without conditions),
-                // in groups of four trips: the four table entries and the four stage times are read
-                // before any of them is used (one wait per group instead of one per trip).
-                if (!MIRROR) {
-                    // a trip beyond the lane's own reach or GPU count reads a valid stage time and, from
-                    // the table, the entry (row 0, one GPU), which is "impossible" in every table
-                    const int reach = on ? s.lo[p * M + dd - 1] : p;
-                    const int mine = p - max(q, reach); // trips of this lane
-                    const int ddc = on ? dd : 1, gc = on ? g - dd : 0;
-                    int to = (p * M + ddc - 1) * (L + 1) + p - 1, go = (p - 1 - q) * (M + 1) + gc;
-                    for (int i = 0; i < trips; i += 4) { // stage [x, p), x = p - 1 - i; table row x - q
-                        double tt[4], gv[4];
+            for (int d0 = 0; d0 < M; d0 += CW) {
+                double cost[CW], edge[CW];
+                int lim[CW], most = 0; // layers of the longest stage per GPU count
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) tt[j] = a.tdp[to - j];
+                for (int j = 0; j < CW; ++j) {
+                    const int dc = MT ? j : imin(d0 + j, M - 1), rc = reach[p * M + dc];
+                    const double e = near[p * M + dc];
+                    lim[j] = d0 + j < M ? (side ? rc - p : p - rc) : 0;
+                    most = imax(most, lim[j]);
+                    cost[j] = (side ? sw + mu - 2.0 * e : pw + mu + e) + l * (dc + 1);
+                    edge[j] = side ? e + hi : kNone; // a later end than this is too slow by its boundary term
+                }
+                for (int k = sub; __any(k < most); k += 32) { // stage of k + 1 layers
+                    const int x = k < most ? (side ? p + 1 + k : p - 1 - k) : p;
+                    const double px = P[x];
+                    double f[CW], v[CW];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) gv[j] = G[i + j < mine ? go - j * (M + 1) : 1];
+                    for (int j = 0; j < CW; ++j) f[j] = far[x * M + (MT ? j : imin(d0 + j, M - 1))];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) acc = fmin(acc, gv[j] + (wt * tt[j] + add));
-                        to -= 4; go -= 4 * (M + 1);
+                    for (int j = 0; j < CW; ++j) {
+                        const bool ok = (k < lim[j]) & (!side | (f[j] <= edge[j]));
+                        const double c = fma(f[j], per, cost[j]);
+                        v[j] = ok ? c : kNone;
                     }
-                } else {
-                    // a lane without a pair walks the row of impossible stages; the others take every stage
-                    // with t <= tau (t is not monotone along the walk, so the test is on the value)
-                    const int row = on ? p * M + dd - 1 : (L + 1) * M, gc = on ? g - dd : 0;
-                    int to = row * (L + 1) + p + 1, go = (q - p - 1) * (M + 1) + gc;
-                    for (int i = 0; i < trips; i += 4) { // stage [p, x), x = p + 1 + i; table row q - x
-                        double tt[4], gv[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) tt[j] = a.tds[to + j];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) gv[j] = G[go - j * (M + 1)];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) acc = fmin(acc, gv[j] + (wt * (tt[j] <= tau ? tt[j] : kNone) + add));
-                        to += 4; go -= 4 * (M + 1);
-                    }
+                    for (int j = 1; j < CW; ++j) v[0] = fmin(v[0], v[j]);
+                    acc = fmin(acc, px + v[0]);
                 }
             }
-            acc = min8(acc);
-            if (di == 0 && g <= M) G[r * (M + 1) + g] = acc;
-            fin = fin || acc < kNone;
+            acc = min16(acc);
+            acc = fmin(acc, row_below(acc)); // the upper row of each half wave now holds the minimum of both
+            if (sub == 31) P[p] = acc;
+            wave_sync();
         }
-        if (lane == 0) G[r * (M + 1)] = kNone;
-        if (__any(fin)) lastfin = p; // the same in every lane
+        };
+        if (side) rows(std::true_type{}); else rows(std::false_type{});
+    }
+    __syncthreads();
+    // bounds of the bucket's entries, kBucket at a time; the smallest of every template
+    const int count = a.n_max - a.n_min + 1;
+    float mine = __builtin_huge_valf();
+    unsigned arg = c0;
+    for (unsigned m0 = c0; m0 < c1; m0 += kBucket) {
+        const int m = (int)min(c1 - m0, (unsigned)kBucket);
+        for (int i = threadIdx.x; i < m * count; i += blockDim.x) {
+            const int q = i / count, ni = i - q * count; // (n nodes that cannot cover the layers: never)
+            const unsigned uvd = a.cuvd[m0 + q];
+            const int u = uvd & 255, v = uvd >> 8 & 255, d = uvd >> 16, n = a.n_min + ni;
+            const double tau = a.ctau[m0 + q];
+            double bound = -kNone;
+            for (int k = 0; k < mus * kLambdas; ++k) {
+                const double l = s_lam[k % kLambdas], mu = s_mu[k / kLambdas];
+                const double base = mid * tau + PS[(size_t)k * 2 * W + u] + PS[((size_t)k * 2 + 1) * W + v] + l * d + mu;
+                const double spent = l * n * M + mu * a.Smax;
+                // lowered by far more than these few roundings are worth
+                bound = fmax(bound, base - spent - 1e-9 * (fabs(base) + mid * tau + s.PT[L * M] + fabs(l) * n * M + mu * a.Smax));
+            }
+            const float f = n >= s_fewest && n <= L ? __double2float_rd(bound) : __builtin_huge_valf();
+            s_lb[q * kMaxCount + ni] = f;
+            a.lb[(size_t)(m0 + q) * count + ni] = f;
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < count)
+            for (int q = 0; q < m; ++q) {
+                const float f = s_lb[q * kMaxCount + threadIdx.x];
+                if (f < mine) { mine = f; arg = m0 + q; }
+            }
+        __syncthreads();
+    }
+    if ((int)threadIdx.x < count) {
+        a.blb[(size_t)b * count + threadIdx.x] = mine;
+        a.barg[(size_t)b * count + threadIdx.x] = arg;
+    }
+}
+
+// Entries whose bound does not exceed the minimum found so far for some template: one wave each.
+__device__ __forceinline__ double best_now(const Args &a, int i) {
+    return __longlong_as_double((long long)__hip_atomic_load(&a.best[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// A wave looks through 64 consecutive entries, lanes = templates, and appends what is left with one atomic.
+__global__ void __launch_bounds__(256) k_exact_filter(Args a) {
+    if (*a.status != OOB_OK || !a.head->narrow) return;
+    const unsigned lane = threadIdx.x & 63, total = a.head->ncand, count = (unsigned)(a.n_max - a.n_min + 1);
+    const unsigned c0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
+    if (c0 >= total) return;
+    const double best = lane < count ? __longlong_as_double((long long)a.best[lane]) : -1.0;
+    unsigned long long keep = 0;
+    for (unsigned q0 = 0; q0 < 64; q0 += 16) {
+        float lb[16];
+#pragma unroll
+        for (unsigned q = 0; q < 16; ++q) lb[q] = a.lb[(size_t)min(c0 + q0 + q, total - 1) * count + min(lane, count - 1)];
+#pragma unroll
+        for (unsigned q = 0; q < 16; ++q)
+            if (c0 + q0 + q < total && __any(lane < count && lb[q] < __builtin_huge_valf() && (double)lb[q] <= best)) keep |= 1ull << (q0 + q);
+    }
+    unsigned at = 0;
+    if (lane == 0 && keep) at = atomicAdd(&a.head->alive, (unsigned)__popcll(keep));
+    at = __shfl(at, 0, 64);
+    if (keep >> lane & 1) a.list[at + __popcll(keep & ((1ull << lane) - 1))] = c0 + lane;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Exact evaluation.  Bound by the latency of dependent LDS reads on the rows of the one-node tables: 171 us for the
+// first picks and 446 us for the rest at 98 layers x 8 GPUs (the version before, without a band and evaluating
+// everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table entry: 1, or S_max + 1 (STAGED).
+// ---------------------------------------------------------------------------------------------
+struct Eval {
+    Prof pr;
+    unsigned char *reach; // [(L+1) M] of a stage into a layer p <= u / out of a layer p >= v
+    double *pool;         // GU, W, then the waves' one-node tables
+    size_t pool_n;
+    double *GU;           // [two sides][band][M, or staged_row(M)] covers next to the slowest stage, by the distance covered
+    double *NP;           // [2 buffers][len+1 of both sides][J]
+    double *OUT;          // [two sides][nodes][M][J] a whole nodes and g more GPUs
+    int *ints;            // [0..1] bands
+};
+// Column of (g GPUs, j stages), 1 <= j <= g, in a row of a table with stage counts; column 0: impossible.
+__host__ __device__ inline int staged_col(int g, int j) { return g * (g - 1) / 2 + j; }
+__host__ __device__ inline int staged_row(int M) { return M * (M + 1) / 2 + 1; }
+// Entry (r, j) of a band matrix with rows r = 1 .. and columns 0 .. len - r.
+__device__ __forceinline__ int band_index(int r, int j, int len) { return (r - 1) * len - (r - 1) * (r - 2) / 2 + j; }
+__host__ __device__ inline size_t band_size(int band, int len) { return (size_t)band * len - (size_t)band * (band - 1) / 2; }
+
+__host__ __device__ inline size_t eval_fixed(int L, int M, int n_max, int J) {
+    return prof_doubles(L, M) + ((size_t)(L + 1) * M + 7) / 8 + 2 * (size_t)(L + 2) * J + 2 * (size_t)n_max * M * J + 8;
+}
+// One-node tables of a side (this wave's share): start positions idx = first .. in side coordinates (layers
+// from the far end of the side), rows r = layers covered.  Lanes = (start, part of the walk, GPUs g); with stage
+// counts the lanes that would share a walk out hold the counts j = 1 .. M instead.  A row takes the stages that
+// cover its last k + 1 layers on CW GPU counts side by side: the CW table entries and the CW prefix sums of a
+// step are read before any of them is used.
+template <bool MIRROR, bool STAGED, int MT>
+__device__ void one_node_tables(const Args &a, const Eval &e, int len, int band, double tau, double wt, double add,
+                                double *Wm, double *GU, double *G, int first, int slots, int lgxs, int gbits) {
+    constexpr int CW = MT ? MT : 8;
+    const int L = a.L, M = MT ? MT : a.M, lane = threadIdx.x & 63;
+    const int gi = lane & ((1 << gbits) - 1), xs = (lane >> gbits) & ((1 << lgxs) - 1), slot = lane >> (gbits + lgxs);
+    const int idx = first + slot;
+    const bool live = idx < len && slot < slots && gi < M;
+    const int j = STAGED ? xs + 1 : 1;
+    const int XS = STAGED ? 1 : 1 << lgxs, x0 = STAGED ? 0 : xs;
+    const int row_n = STAGED ? staged_row(M) : M + 1;               // entries per row of a table
+    double *T = G + (size_t)slot * (band + 1) * row_n;
+    const int g = gi + 1, rows = live ? imin(band, len - idx) : 0;
+    const bool use = live && (!STAGED || j <= g);                   // this lane has an entry in every row
+    const int q = live ? (MIRROR ? L - idx : idx) : 0;                           // start layer
+    const double *far = MIRROR ? e.pr.PX : e.pr.PT;
+    const int top = g + 1 - (j - 1);
+    const int none = 0; // row 0 holds no cover (a node's first stage is taken on its own): always impossible
+    if (slot < slots && gi == 0 && xs == 0) T[none] = kNone;
+    wave_sync();
+    for (int r = 1; r <= band; ++r) {
+        double acc = kNone;
+        const bool on = use && r <= rows;
+        const int p = on ? (MIRROR ? q - r : q + r) : 0;
+        { // one stage on all g GPUs covers everything
+            const int gc = imin(gi, M - 1), rc = e.reach[p * M + gc];
+            const double here = MIRROR ? e.pr.PT[p * M + gc] : e.pr.PX[p * M + gc], all = far[q * M + gc];
+            const double tw = MIRROR ? all - here : here - all;
+            const bool one = on & (j == 1) & (x0 == 0) & ((MIRROR ? rc - p : p - rc) >= r) & (!MIRROR | (tw <= tau));
+            acc = one ? wt * tw + add : kNone;
+        }
+        for (int d0 = 0; d0 < M; d0 += CW) {
+            double near[CW], late[CW]; // weighted share of layer p, latest end fast enough with its boundary term
+            int lim[CW], off[CW]; // layers of the longest stage (the first layer of the node excluded), table column
+            int most = 0;
+#pragma unroll
+            for (int w = 0; w < CW; ++w) {
+                const int dc = MT ? w : imin(d0 + w, M - 1), rc = e.reach[p * M + dc];
+                near[w] = wt * (MIRROR ? -e.pr.PT[p * M + dc] : e.pr.PX[p * M + dc]) + add;
+                late[w] = MIRROR ? e.pr.PT[p * M + dc] + tau : 0.0;
+                lim[w] = on && d0 + w + 1 < top ? imin(MIRROR ? rc - p : p - rc, r - 1) : 0; // the other stages need a GPU each
+                most = imax(most, lim[w]);
+                const int left = g - dc - 1; // GPUs of the other stages
+                off[w] = (r - 1) * row_n + (STAGED ? (left > 0 && j > 1 ? staged_col(left, j - 1) : 0) : imax(left, 0));
+            }
+            for (int k = x0; __any(k < most); k += XS) { // stages of k + 1 layers
+                const int kk = imin(k, imax(most - 1, 0)), x = on ? (MIRROR ? p + 1 + kk : p - 1 - kk) : 0;
+                double tv[CW], gv[CW];
+#pragma unroll
+                for (int w = 0; w < CW; ++w) {
+                    tv[w] = far[x * M + (MT ? w : imin(d0 + w, M - 1))];
+                    gv[w] = T[k < lim[w] ? off[w] - kk * row_n : none]; // beyond the reach: an entry that is impossible
+                }
+#pragma unroll
+                for (int w = 0; w < CW; ++w) {
+                    const double c = gv[w] + (MIRROR ? fma(2.0, tv[w], near[w]) : near[w] - tv[w]); // (the weight is 2 after, 1 before)
+                    acc = fmin(acc, (!MIRROR | (tv[w] <= late[w])) ? c : kNone);
+                }
+            }
+        }
+        if (!STAGED)
+            for (int m = 1 << gbits; m < 1 << (gbits + lgxs); m <<= 1) acc = fmin(acc, __shfl_xor(acc, m, 64));
+        if (on && (STAGED || xs == 0)) { // (entry 0 of a row, no GPU used: impossible)
+            if (STAGED) {
+                double *row = T + (size_t)r * row_n;
+                row[staged_col(g, j)] = acc;
+                if (g == 1) row[0] = kNone;
+                if (g == M) Wm[(size_t)band_index(r, idx, len) * M + j - 1] = acc;
+                if (idx + r == len) GU[(size_t)(r - 1) * row_n + staged_col(g, j)] = acc;
+            } else {
+                T[r * row_n + g] = acc;
+                if (gi == 0) T[r * row_n] = kNone;
+                if (g == M) Wm[band_index(r, idx, len)] = acc;
+                else if (idx + r == len) GU[(r - 1) * M + g] = acc;
+            }
+        }
         wave_sync();
     }
-    // a whole node covering [q, p) (prefix) / [p, q) (suffix), and the partial covers next to the slowest stage
-    for (int r = 1 + lane; r <= rows; r += 64) {
-        const int p = MIRROR ? q - r : q + r;
-        s.W[MIRROR ? widx(p, q, L) : widx(q, p, L)] = G[r * (M + 1) + M];
-    }
-    for (int g = 1 + lane; g < M; g += 64) s.GU[q * M + g] = G[rows * (M + 1) + g];
-    wave_sync();
 }
 
-// Node after node, one step: OUT[c][g] from NP_c, and NP_{c+1} from NP_c (cur -> nxt).  NP_c[p]: c whole
-// nodes cover [0, p) (prefix) / [p, L) (suffix).  Called by `nth` threads (whole waves), th = 0 .. nth-1.
-template <bool MIRROR>
-__device__ void node_step(const Args &a, const Lds &s, int e, int c, int cend, const double *cur, double *nxt,
-                          double *OUT, int th, int nth) {
-    const int L = a.L, M = a.M, h4 = th & 3;
-    for (int i = th; i < M * 4; i += nth) { // four threads per g
-        const int g = i >> 2;
-        double m = kNone;
-        if (g == 0) { if (h4 == 0) m = cur[e]; }
-        else if (!MIRROR) for (int q = c + h4; q < e; q += 4) m = fmin(m, cur[q] + s.GU[q * M + g]); // c nodes cover at least c layers
-        else              for (int q = e + 1 + h4; q <= L - c; q += 4) m = fmin(m, cur[q] + s.GU[q * M + g]);
-        m = min4(m);
-        if (h4 == 0) OUT[c * M + g] = m;
-    }
-    if (c + 1 < cend) {
-        const int np = MIRROR ? L - e + 1 : e + 1; // layers of the side, origin included
-        for (int i = th; i < ((np * 4 + 63) & ~63); i += nth) { // whole waves
-            const int pi = i >> 2;
+// c -> c + 1 whole nodes: nxt[p] = min over r of cur[p - r] + W[r][p - r] for this side, by nth threads (whole waves).
+template <bool STAGED>
+__device__ void node_step(const Args &a, int len, int band, int c, const double *Wm, const double *cur, double *nxt, int th,
+                          int nth) {
+    const int lo = c + 1, hi = (int)imin(len, (c + 1) * band), np = hi - lo + 1;
+    if (!STAGED) {
+        const int h4 = th & 3;
+        for (int i = th; i < ((np * 4 + 63) & ~63); i += nth) { // whole waves, four threads per position
+            const int p = lo + (i >> 2), most = imin(band, p - c); // c nodes cover at least c layers
             double m = kNone;
-            if (pi < np) {
-                const int p = MIRROR ? L - pi : pi;
-                if (!MIRROR) for (int q = c + h4; q < p; q += 4) m = fmin(m, cur[q] + s.W[widx(q, p, L)]);
-                else         for (int q = p + 1 + h4; q <= L - c; q += 4) m = fmin(m, cur[q] + s.W[widx(p, q, L)]);
-            }
+            if (p <= hi)
+                for (int r = 1 + h4; r <= most; r += 4) m = fmin(m, cur[p - r] + Wm[band_index(r, p - r, len)]);
             m = min4(m);
-            if (h4 == 0 && pi < np) nxt[MIRROR ? L - pi : pi] = m;
+            if (h4 == 0 && p <= hi) nxt[p] = m;
+        }
+    } else {
+        const int J = a.Smax + 1, M = a.M;
+        for (int i = th; i < np * J; i += nth) {
+            const int p = lo + i / J, s = i % J, most = imin(band, p - c);
+            double m = kNone;
+            for (int r = 1; r <= most; ++r)
+                for (int j = 1; j <= imin(imin(M, r), s - c); ++j)
+                    m = fmin(m, cur[(size_t)(p - r) * J + s - j] + Wm[(size_t)band_index(r, p - r, len) * M + j - 1]);
+            nxt[(size_t)p * J + s] = m;
+        }
+    }
+}
+// OUT[c][g]: c whole nodes and g more GPUs next to the slowest stage cover the side.
+template <bool STAGED>
+__device__ void node_out(const Args &a, int len, int band, int c, const double *cur, const double *GU, double *OUT, int th, int nth) {
+    const int M = a.M, from = imax(1, len - c * band), to = imin(band, len - c); // distances left for the last node
+    const bool whole = len >= c && len <= c * band;
+    if (!STAGED) {
+        for (int i = th; i < ((M * 4 + 63) & ~63); i += nth) { // four threads per g
+            const int g = i >> 2, h4 = i & 3;
+            double m = kNone;
+            if (g == 0) { if (h4 == 0 && whole) m = cur[len]; }
+            else if (g < M) for (int r = from + h4; r <= to; r += 4) m = fmin(m, cur[len - r] + GU[(r - 1) * M + g]);
+            m = min4(m);
+            if (h4 == 0 && g < M) OUT[c * M + g] = m;
+        }
+    } else {
+        const int J = a.Smax + 1, row_n = staged_row(M);
+        for (int i = th; i < M * J; i += nth) {
+            const int g = i / J, s = i % J;
+            double m = kNone;
+            if (g == 0) { if (whole) m = cur[(size_t)len * J + s]; }
+            else
+                for (int r = from; r <= to; ++r)
+                    for (int j = 1; j <= imin(imin(g, r), s); ++j)
+                        m = fmin(m, cur[(size_t)(len - r) * J + s - j] + GU[(size_t)(r - 1) * row_n + staged_col(g, j)]);
+            OUT[((size_t)c * M + g) * J + s] = m;
         }
     }
 }
 
-__global__ void __launch_bounds__(1024) k_exact_lds(Args a) {
+// The node-level recurrence of one side by one wave, in registers: lane p (and p + 64) holds NP_c[p] and the
+// column W[1 .. B][p - r] it adds to; the wave shifts NP by a lane per r.  HIST[c][r] = NP_c[len - r], r = 0 .. band, is
+// what the last node's partial covers need.  No LDS read and no barrier on the chain of up to n_max steps.
+template <int B, bool TWO>
+__device__ __forceinline__ void node_chain(int len, int band, int cend, const double *Wm, double *HIST) {
+    const int lane = threadIdx.x & 63;
+    double w0[B], w1[TWO ? B : 1];
+#pragma unroll
+    for (int r = 1; r <= B; ++r) {
+        w0[r - 1] = r <= band && lane >= r && lane <= len ? Wm[band_index(r, lane - r, len)] : kNone;
+        if (TWO) w1[r - 1] = r <= band && lane + 64 <= len ? Wm[band_index(r, lane + 64 - r, len)] : kNone;
+    }
+    double c0 = lane == 0 ? 0.0 : kNone, c1 = kNone;
+    for (int c = 0; c < cend; ++c) {
+        if (lane <= len && len - lane <= band) HIST[c * (band + 1) + len - lane] = c0;
+        if (TWO && lane + 64 <= len && len - lane - 64 <= band) HIST[c * (band + 1) + len - lane - 64] = c1;
+        double n0 = kNone, n1 = kNone, s0 = c0, s1 = c1;
+#pragma unroll
+        for (int r = 1; r <= B; ++r) {
+            if (TWO) {
+                const int blo = __builtin_amdgcn_readlane(__double2loint(s0), 63), bhi = __builtin_amdgcn_readlane(__double2hiint(s0), 63);
+                const int lo = __builtin_amdgcn_update_dpp(blo, __double2loint(s1), 0x138, 0xF, 0xF, false);
+                const int hi = __builtin_amdgcn_update_dpp(bhi, __double2hiint(s1), 0x138, 0xF, 0xF, false);
+                s1 = __hiloint2double(hi, lo);
+                n1 = fmin(n1, s1 + w1[r - 1]);
+            }
+            const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(s0), 0x138, 0xF, 0xF, false);
+            const int hi = __builtin_amdgcn_update_dpp(0x7FF00000, __double2hiint(s0), 0x138, 0xF, 0xF, false);
+            s0 = __hiloint2double(hi, lo);
+            n0 = fmin(n0, s0 + w0[r - 1]);
+        }
+        c0 = n0;
+        c1 = n1;
+    }
+}
+constexpr int kChainBand = 16, kChainLen = 127;
+__device__ __forceinline__ void node_chain_any(int len, int band, int cend, const double *Wm, double *HIST) {
+    if (len < 64) {
+        if (band <= 4) node_chain<4, false>(len, band, cend, Wm, HIST);
+        else if (band <= 8) node_chain<8, false>(len, band, cend, Wm, HIST);
+        else node_chain<kChainBand, false>(len, band, cend, Wm, HIST);
+    } else {
+        if (band <= 8) node_chain<8, true>(len, band, cend, Wm, HIST);
+        else node_chain<kChainBand, true>(len, band, cend, Wm, HIST);
+    }
+}
+
+// The slowest stage at every place it fits: ca whole nodes and g GPUs before it, cb whole nodes and M - d - g
+// GPUs after it, n = ca + cb + 1, for every template whose stage limit cannot bind (or obeying it).
+template <bool STAGED>
+__device__ void combine(const Args &a, const Eval &e, int d, double tau, int nhi, int cendP, int cendS, double mid,
+                        unsigned long long *s_best) {
+    const int L = a.L, M = a.M, J = STAGED ? a.Smax + 1 : 1;
+    const int places = M - d + 1;
+    for (int i = threadIdx.x; i < cendP * cendS; i += blockDim.x) {
+        const int ca = i / cendS, cb = i - ca * cendS, n = ca + cb + 1;
+        if (n < a.n_min || n > nhi || (!STAGED && a.Nb > 0 && a.Nb < imin(L, n * M))) continue;
+        double m = kNone;
+        for (int g = 0; g < places; ++g) {
+            if (!STAGED) m = fmin(m, e.OUT[ca * M + g] + e.OUT[(a.n_max + cb) * M + (M - d - g)]);
+            else {
+                const double *p = e.OUT + (size_t)(ca * M + g) * J, *s = e.OUT + (size_t)((a.n_max + cb) * M + (M - d - g)) * J;
+                double pre = kNone; // least over the stages before, as many as the stages after leave room for
+                int j1 = 0;
+                for (int j2 = a.Smax - 1; j2 >= 0; --j2) {
+                    for (; j1 + 1 + j2 <= a.Smax; ++j1) pre = fmin(pre, p[j1]);
+                    m = fmin(m, pre + s[j2] - (double)j2 * tau);
+                }
+            }
+        }
+        m += mid * tau;
+        if (m < kNone) atomicMin(&s_best[n - a.n_min], (unsigned long long)__double_as_longlong(m));
+    }
+}
+
+// One row of the tables over (layers covered, GPUs used[, stages]) of a side: T[r][D][j], r layers from the far end of the
+// side on D GPUs, node after node.  Called by nth threads (whole waves); a thread has one (D, j) and a share of the walk.
+template <bool MIRROR, bool STAGED, int MT>
+__device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, double tau, double wt, double add, double *T, int th,
+                        int nth) {
+    constexpr int CW = MT ? MT : 8;
+    const int L = a.L, M = MT ? MT : a.M, row_n = nd * jd, p = MIRROR ? L - r : r;
+    const int items = STAGED ? nd * (jd - 1) : nd; // D = 0 .. nd - 1 (D = 0 covers nothing), j = 1 .. jd - 1
+    int lg = 0;
+    while (lg < 6 && items << (lg + 1) <= nth) ++lg;
+    const int XS = 1 << lg, x0 = th & (XS - 1);
+    const double *far = MIRROR ? e.pr.PX : e.pr.PT;
+    for (int i0 = 0; i0 < items; i0 += nth >> lg) {
+        const int i = i0 + (th >> lg), D = i % nd, j = STAGED ? i / nd + 1 : 1;
+        const bool on = i < items && D > 0 && j <= D;
+        const int gD = on ? (D - 1) % M + 1 : 0; // GPUs of D's last node
+        double acc = kNone;
+        for (int d0 = 0; d0 < M; d0 += CW) {
+            double near[CW];
+            int lim[CW], off[CW], most = 0;
+#pragma unroll
+            for (int w = 0; w < CW; ++w) {
+                const int dc = MT ? w : imin(d0 + w, M - 1), rc = e.reach[p * M + dc];
+                near[w] = MIRROR ? e.pr.PT[p * M + dc] : e.pr.PX[p * M + dc];
+                lim[w] = d0 + w < gD && (!STAGED || D - dc - 1 >= j - 1) ? imin(MIRROR ? rc - p : p - rc, r) : 0;
+                most = imax(most, lim[w]);
+                off[w] = (r - 1) * row_n + imax(D - dc - 1, 0) * jd + (STAGED ? j - 1 : 0);
+            }
+            for (int k = x0; __any(k < most); k += XS) { // stages of k + 1 layers
+                const int kk = imin(k, imax(most - 1, 0)), x = MIRROR ? p + 1 + kk : p - 1 - kk;
+                double tv[CW], gv[CW];
+#pragma unroll
+                for (int w = 0; w < CW; ++w) {
+                    tv[w] = far[x * M + (MT ? w : imin(d0 + w, M - 1))];
+                    gv[w] = T[off[w] - kk * row_n];
+                }
+#pragma unroll
+                for (int w = 0; w < CW; ++w) {
+                    const double t = MIRROR ? tv[w] - near[w] : near[w] - tv[w];
+                    const bool ok = (k < lim[w]) & (!MIRROR | (t <= tau));
+                    const double c = gv[w] + (wt * t + add);
+                    acc = fmin(acc, ok ? c : kNone);
+                }
+            }
+        }
+        for (int m = 1; m < XS; m <<= 1) acc = fmin(acc, __shfl_xor(acc, m, 64));
+        if (x0 == 0 && i < items) {
+            T[(size_t)r * row_n + D * jd + (STAGED ? j : 0)] = acc;
+            if (STAGED && j == 1) T[(size_t)r * row_n + D * jd] = kNone;
+        }
+    }
+}
+
+// The cost of the best pipelines around slowest stage (u, v, d) with n <= nhi nodes, merged into s_best.
+// Returns false (the same in every thread) if the tables do not fit the workgroup's LDS (STAGED only).
+template <bool STAGED, int MT>
+__device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int nhi, unsigned long long *s_best) {
+    const int L = a.L, M = MT ? MT : a.M, J = STAGED ? a.Smax + 1 : 1, nw = blockDim.x >> 6, W = L + 1;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int u = uvd & 255, v = uvd >> 8 & 255, d = uvd >> 16;
+    const int lenP = u, lenS = L - v;
+    // ---- reach of the stages, and the most layers a node can cover on either side: a stage on dd GPUs covers at
+    // most rho dd layers, rho the largest (layers / GPUs) of any stage, so a node at most floor(M rho)
+    if (threadIdx.x < 2) e.ints[threadIdx.x] = 0;
+    __syncthreads();
+    int mostP = 0, mostS = 0;
+    const int inv = 65536 / M + 1; // i / M = i inv >> 16, exact below 2^14
+    for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
+        const int p = (int)((unsigned)(i * inv) >> 16), dd = i - p * M + 1;
+        int r = p;
+        if (p >= 1 && p <= u) { r = reach_back<true>(e.pr, M, p, dd, tau); mostP = imax(mostP, (p - r) * M / dd); }
+        else if (p >= v && p < L) { r = reach_on(e.pr, L, M, p, dd, tau); mostS = imax(mostS, (r - p) * M / dd); }
+        e.reach[i] = (unsigned char)r;
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) { mostP = imax(mostP, __shfl_xor(mostP, m, 64)); mostS = imax(mostS, __shfl_xor(mostS, m, 64)); }
+    if ((threadIdx.x & 63) == 0) { atomicMax(&e.ints[0], mostP); atomicMax(&e.ints[1], mostS); }
+    __syncthreads();
+    const int bandP = imin(e.ints[0], lenP), bandS = imin(e.ints[1], lenS);
+    __syncthreads();
+    if ((lenP && !bandP) || (lenS && !bandS)) return true; // some layer fits no stage fast enough
+    const double mid = a.Nb > 0 ? (double)a.Nb : 4.0;
+    const double ptau = STAGED || a.Nb > 0 ? 0.0 : 4.0, stau = STAGED ? 0.0 : a.Nb > 0 ? -1.0 : 3.0;
+    const int cendP = imin(nhi, lenP + 1), cendS = imin(nhi, lenS + 1); // a node covers at least one layer
+    const int nwp = (nw + 1) >> 1, mir = wave >= nwp; // half of the waves per side
+    const int th = mir ? (int)threadIdx.x - nwp * 64 : (int)threadIdx.x, nth = (mir ? nw - nwp : nwp) * 64;
+    // ---- few nodes, each of many layers: tables over (layers covered, GPUs used) are smaller work than a table per
+    // start layer (nodes against layers per node), and the covers next to the slowest stage are their last rows
+    {
+        const int nd = imax(cendP, cendS) * M, jd = STAGED ? imin(J, nd + 1) : 1;
+        const size_t need = ((size_t)lenP + 1 + lenS + 1) * nd * jd;
+        if (nhi * 4 <= imax(bandP, bandS) && need <= e.pool_n) {
+            const int row_n = nd * jd;
+            const int second = (lenP + 1) * row_n; // the other side's table
+            for (int i = threadIdx.x; i < 2 * row_n; i += blockDim.x) {
+                const int side = i >= row_n, o = i - side * row_n;
+                e.pool[side * second + o] = o == 0 ? 0.0 : kNone;
+            }
+            __syncthreads();
+            for (int r = 1; r <= imax(lenP, lenS); ++r) {
+                if (!mir) { if (r <= lenP) gpu_row<false, STAGED, MT>(a, e, r, nd, jd, tau, 1.0, ptau * tau, e.pool, th, nth); }
+                else      { if (r <= lenS) gpu_row<true, STAGED, MT>(a, e, r, nd, jd, tau, 2.0, stau * tau, e.pool + second, th, nth); }
+                __syncthreads();
+            }
+            for (int i = threadIdx.x; i < (cendP + cendS) * M * J; i += blockDim.x) {
+                const bool after = i >= cendP * M * J;
+                const int o = after ? i - cendP * M * J : i, d0 = o / J, j = o - d0 * J;
+                e.OUT[(after ? a.n_max * M * J : 0) + o] =
+                    j < jd ? e.pool[(after ? second + lenS * row_n : lenP * row_n) + d0 * jd + j] : kNone;
+            }
+            __syncthreads();
+            combine<STAGED>(a, e, d, tau, nhi, cendP, cendS, mid, s_best);
+            return true;
+        }
+    }
+    // ---- layout of the pool: the two GU, the two W, then one-node tables
+    const int mult = STAGED ? M : 1, row_n = STAGED ? staged_row(M) : M + 1;
+    const size_t gu = STAGED ? row_n : M;
+    e.GU = e.pool;
+    double *WP = e.GU + (bandP + bandS) * gu, *WS = WP + band_size(bandP, lenP) * mult, *G = WS + band_size(bandS, lenS) * mult;
+    const size_t used = (size_t)(G - e.pool), table = (size_t)(imax(bandP, bandS) + 1) * row_n;
+    if (used + table > e.pool_n) return false;
+    const int fit = (int)((e.pool_n - used) / table); // one-node tables side by side
+    // ---- phase 1
+    {
+        int gbits = 0;
+        while (1 << gbits < M) ++gbits;
+        int lgxs = STAGED ? gbits : 0, slots = 64 >> (gbits + lgxs), waves = nw;
+        if (slots > fit) {
+            if (STAGED) slots = fit;
+            else while (slots > 1 && slots > fit) { slots >>= 1; ++lgxs; }
+        }
+        // long walks of few tables: more lanes per walk rather than idle waves
+        if (!STAGED) while (slots > 1 && slots * 4 > fit && imax(bandP, bandS) > 16) { slots >>= 1; ++lgxs; }
+        waves = imin(waves, imax(1, fit / slots));
+        if (wave < waves) {
+            double *mine = G + (size_t)wave * slots * table;
+            // (with a single node in all there is only the start at the far end)
+            const int nP = nhi == 1 ? (lenP > 0) : (lenP + slots - 1) / slots, nS = nhi == 1 ? (lenS > 0) : (lenS + slots - 1) / slots, both = 2 * imin(nP, nS);
+            for (int item = wave; item < nP + nS; item += waves) { // the two sides in turn
+                int side, i;
+                if (item < both) { side = item & 1; i = item >> 1; }
+                else { side = nS > nP; i = item - (both >> 1); }
+                if (!side) one_node_tables<false, STAGED, MT>(a, e, lenP, bandP, tau, 1.0, ptau * tau, WP, e.GU, mine, i * slots, slots, lgxs, gbits);
+                else       one_node_tables<true, STAGED, MT>(a, e, lenS, bandS, tau, 2.0, stau * tau, WS, e.GU + bandP * gu, mine, i * slots, slots, lgxs, gbits);
+            }
+        }
+    }
+    // ---- phase 2: node after node, both sides at once.  Narrow bands: one wave each
+    const size_t histP = (size_t)cendP * (bandP + 1), histS = (size_t)cendS * (bandS + 1);
+    if (!STAGED && imax(bandP, bandS) <= kChainBand && imax(lenP, lenS) <= kChainLen && used + histP + histS <= e.pool_n) {
+        double *HP = G; // (in place of the one-node tables)
+        __syncthreads();
+        if (wave == 0 || wave == nw - 1)
+            node_chain_any(mir ? lenS : lenP, mir ? bandS : bandP, mir ? cendS : cendP, WP + (mir ? WS - WP : 0), HP + (mir ? histP : 0));
+        __syncthreads();
+        for (int i = threadIdx.x; i < (cendP + cendS) * M; i += blockDim.x) {
+            const bool after = i >= cendP * M;
+            const int o = after ? i - cendP * M : i, c = o / M, g = o - c * M, band = after ? bandS : bandP;
+            const double *H = HP + (after ? histP : 0) + c * (band + 1), *cov = e.GU + (after ? bandP * M : 0) + g;
+            double m = g == 0 ? H[0] : kNone;
+            if (g > 0) for (int r = 1; r <= band; ++r) m = fmin(m, H[r] + cov[(r - 1) * M]);
+            e.OUT[(after ? a.n_max * M : 0) + o] = m;
+        }
+        __syncthreads();
+    } else {
+    // wide ones: half of the waves each, a barrier per node count
+    double *cur = e.NP + (mir ? (size_t)(lenP + 1) * J : 0), *nxt = cur + (size_t)(L + 2) * J;
+    const int len = mir ? lenS : lenP, band = mir ? bandS : bandP, cend = mir ? cendS : cendP;
+    for (int i = th; i < (len + 1) * J; i += nth) { cur[i] = i == 0 ? 0.0 : kNone; nxt[i] = kNone; }
+    __syncthreads();
+    for (int c = 0; c < imax(cendP, cendS); ++c) {
+        if (c < cend) {
+            node_out<STAGED>(a, len, band, c, cur, e.GU + (mir ? bandP * gu : 0), e.OUT + (mir ? (size_t)a.n_max * M * J : 0), th, nth);
+            if (c + 1 < cend) node_step<STAGED>(a, len, band, c, WP + (mir ? WS - WP : 0), cur, nxt, th, nth);
+        }
+        __syncthreads();
+        double *t = cur; cur = nxt; nxt = t;
+    }
+    }
+    combine<STAGED>(a, e, d, tau, nhi, cendP, cendS, mid, s_best);
+    return true;
+}
+
+template <bool STAGED, int MT>
+__global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_exact_eval(Args a, int mode, int lds_doubles, int picks) {
     HIP_DYNAMIC_SHARED(double, s_dyn)
     __shared__ unsigned s_next;
-    if (*a.status != OOB_OK) return; // the same for every thread: nothing is computed from a bad profile
-    const int L = a.L, M = a.M, count = a.n_max - a.n_min + 1, nw = blockDim.x >> 6;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    Lds s;
-    double *p = s_dyn;
-    s.W = p;    p += tri(L);
-    s.GU = p;   p += (size_t)(L + 1) * M;
-    s.NP = p;   p += 4 * (size_t)(L + 1);
-    s.PU = p;   p += (size_t)a.n_max * M;
-    s.SV = p;   p += (size_t)a.n_max * M;
-    s.lo = (int *)p;    p += ((size_t)(L + 1) * M + 1) / 2;
-    s.lomin = (int *)p; p += (size_t)(L + 1) / 2 + 1;
-    s.bnd = p;  p += L;
-    s.best = (unsigned long long *)p; p += count;
-    s.G = p;
-    // rows -kGPad .. -1 of a wave's one-node table stay "impossible": the walks run in groups of four
-    // and may pass the table's first row
-    double *G = s.G + (size_t)wave * (L + 1 + kGPad) * (M + 1) + kGPad * (M + 1);
-    for (int g = lane; g < kGPad * (M + 1); g += 64) G[g - kGPad * (M + 1)] = kNone;
-    const long long *bnd = (const long long *)a.prof.boundary_ns;
-    for (int i = threadIdx.x; i < L; i += blockDim.x) s.bnd[i] = (double)bnd[i];
-    for (int i = threadIdx.x; i < count; i += blockDim.x) s.best[i] = 0x7FF0000000000000ull;
-    // weights of a stage before / after the slowest one and of the slowest one, as (t, tau) coefficients
-    const double ptau = a.Nb > 0 ? 0.0 : 4.0, stau = a.Nb > 0 ? -1.0 : 3.0, mid = a.Nb > 0 ? (double)a.Nb : 4.0;
-    const unsigned ncand = (unsigned)((long long)L * (L + 1) / 2 * M);
-    // node-level phase: the first half of the waves takes the prefix side, the second half the suffix side
-    const int nwp = (nw + 1) >> 1, mir = wave >= nwp && nw > 1;
-    const int th = mir ? (int)threadIdx.x - nwp * 64 : (int)threadIdx.x, nth = nw > 1 ? (mir ? nw - nwp : nwp) * 64 : 64;
-    for (;;) {
-        __syncthreads(); // the previous candidate is done with LDS (and s_next has been read)
-        if (threadIdx.x == 0) s_next = atomicAdd(a.counter, 1u);
-        __syncthreads();
-        const unsigned c = s_next;
-        if (c >= ncand) break; // every wave of every workgroup gets here
-        // candidate c -> (u, v, d): pairs u < v in row order, d fastest
-        const int d = (int)(c % M) + 1;
-        unsigned pr = c / M;
-        int u = 0;
-        while (pr >= (unsigned)(L - u)) { pr -= L - u; ++u; }
-        const int v = u + 1 + (int)pr;
-        const double tau = a.tds[((size_t)u * M + d - 1) * (L + 1) + v];
-        if (!(tau < kNone)) continue; // the same for the whole workgroup
-        // ---- reach of a stage into every layer 1..u and out of every layer v..L-1, per GPU count ----
-        for (int i = threadIdx.x; i < (L + 1) * M; i += blockDim.x) {
-            const int pl = i / M, dd = i % M + 1;
-            int r = pl;
-            if (pl >= 1 && pl <= u) r = side_reach<false>(a, s, pl, dd, tau);
-            else if (pl >= v && pl < L) r = side_reach<true>(a, s, pl, dd, tau);
-            s.lo[i] = r;
-            s.GU[i] = kNone;
-        }
-        __syncthreads();
-        for (int pl = threadIdx.x; pl <= L; pl += blockDim.x) {
-            int m = s.lo[pl * M];
-            if (pl <= u) for (int dd = 2; dd <= M; ++dd) m = min(m, s.lo[pl * M + dd - 1]);
-            else         for (int dd = 2; dd <= M; ++dd) m = max(m, s.lo[pl * M + dd - 1]);
-            s.lomin[pl] = m;
-        }
-        __syncthreads();
-        // ---- phase 1: one-node tables, one start layer per wave at a time; the longest first, the two
-        // sides in turn (prefix starts 0 .. u-1 have u, u-1, .. rows, suffix starts L .. v+1 have L-v, .. rows)
-        {
-            const int nP = u, nS = L - v, both = 2 * min(nP, nS);
-            for (int item = wave; item < nP + nS; item += nw) {
-                int side, idx;
-                if (item < both) { side = item & 1; idx = item >> 1; }
-                else { side = nS > nP; idx = item - (both >> 1); }
-                if (!side) one_node_table<false>(a, s, u, idx, tau, 1.0, ptau * tau, G);
-                else       one_node_table<true>(a, s, v, L - idx, tau, 2.0, stau * tau, G);
-            }
-        }
-        __syncthreads();
-        // ---- phase 2: node after node, both sides at once -----------------------------------------
-        {
-            // a node covers at least one layer: more whole nodes than a side has layers cover nothing
-            const int cendP = min(a.n_max, u + 1), cendS = min(a.n_max, L - v + 1);
-            double *curP = s.NP, *nxtP = s.NP + (L + 1), *curS = s.NP + 2 * (L + 1), *nxtS = s.NP + 3 * (L + 1);
-            for (int pl = threadIdx.x; pl <= L; pl += blockDim.x) {
-                curP[pl] = pl == 0 ? 0.0 : kNone;
-                curS[pl] = pl == L ? 0.0 : kNone;
-            }
-            for (int i = threadIdx.x + cendP * M; i < a.n_max * M; i += blockDim.x) s.PU[i] = kNone;
-            for (int i = threadIdx.x + cendS * M; i < a.n_max * M; i += blockDim.x) s.SV[i] = kNone;
+    __shared__ int s_ints[4], s_nhi;
+    const bool idle = *a.status != OOB_OK || !a.head->narrow; // the same for every thread: nothing is computed from a bad profile
+    const int L = a.L, M = a.M, count = a.n_max - a.n_min + 1, J = STAGED ? a.Smax + 1 : 1, tid = threadIdx.x;
+    if (idle) return;
+    Eval e;
+    e.pr = load_prof(a, s_dyn);
+    double *p = s_dyn + prof_doubles(L, M);
+    e.reach = (unsigned char *)p; p += ((size_t)(L + 1) * M + 7) / 8;
+    e.NP = p;     p += 2 * (size_t)(L + 2) * J;
+    e.OUT = p; p += 2 * (size_t)a.n_max * M * J;
+    unsigned long long *s_best = (unsigned long long *)p; p += count;
+    e.pool = p; e.pool_n = (size_t)(lds_doubles - (p - s_dyn));
+    e.ints = s_ints;
+    for (int i = tid; i < count; i += blockDim.x) s_best[i] = kNoneBits;
+    const unsigned total = mode == kRest ? a.head->alive : a.head->ncand;
+    for (int turn = 0;; ++turn) {
+        __syncthreads(); // the previous entry is done with LDS (and s_next has been read)
+        unsigned c;
+        int nhi = a.n_max;
+        if (mode == kFirst) {
+            // workgroup (template, rank): the bucket with the rank-th smallest bound for that template, its best entry
+            if (turn) break;
+            const int ni = (int)blockIdx.x / picks, pick = (int)blockIdx.x % picks;
+            const int rank = pick * (pick + 1) / 2; // 0, 1, 3, 6, ...
+            nhi = a.n_min + ni;
+            const unsigned nb = a.head->nbuckets;
+            float *key = (float *)e.pool;
+            for (unsigned i = tid; i < nb; i += blockDim.x) key[i] = a.blb[(size_t)i * count + ni];
+            if (tid == 0) s_next = 0xffffffffu;
             __syncthreads();
-            const int cmax = max(cendP, cendS);
-            for (int cc = 0; cc < cmax; ++cc) {
-                if (nw > 1) {
-                    if (!mir) { if (cc < cendP) node_step<false>(a, s, u, cc, cendP, curP, nxtP, s.PU, th, nth); }
-                    else      { if (cc < cendS) node_step<true>(a, s, v, cc, cendS, curS, nxtS, s.SV, th, nth); }
-                } else {
-                    if (cc < cendP) node_step<false>(a, s, u, cc, cendP, curP, nxtP, s.PU, th, nth);
-                    if (cc < cendS) node_step<true>(a, s, v, cc, cendS, curS, nxtS, s.SV, th, nth);
+            for (unsigned i = tid; i < nb; i += blockDim.x) {
+                const float k = key[i];
+                int below = 0;
+                for (unsigned q = 0; q < nb; ++q) below += key[q] < k || (key[q] == k && q < i);
+                if (below == rank && k < __builtin_huge_valf()) s_next = a.barg[(size_t)i * count + ni];
+            }
+            __syncthreads();
+            c = s_next;
+            if (c == 0xffffffffu) break;
+        } else {
+            if (tid == 0) s_next = __hip_atomic_fetch_add(&a.head->next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 1) s_nhi = 0;
+            __syncthreads();
+            c = s_next;
+            if (c >= total) break; // every wave of every workgroup gets here
+            if (mode == kAll) {
+                // Without bounds of its own an entry is passed over if tau alone makes it too dear: of the j stages after it
+                // each takes back at most tau, j <= the layers and GPUs after it (N_b given), or n stages cost at least
+                // (3 n + 1) tau (N_b = 4 S).  The list ascends, so the first entries' minima meet the slow ones.
+                const unsigned uvd = a.cuvd[c];
+                const double tau = a.ctau[c];
+                if (tid < count) {
+                    const int n = a.n_min + tid, j = imin(L - (int)(uvd >> 8 & 255), n * M - (int)(uvd >> 16));
+                    const double least = a.Nb > 0 ? (double)imax(a.Nb - j, 0) * tau : (3.0 * n + 1.0) * tau;
+                    if (least <= best_now(a, tid)) atomicMax(&s_nhi, n);
+                }
+                if (count > (int)blockDim.x && tid == 0) s_nhi = a.n_max;
+                __syncthreads();
+                nhi = s_nhi;
+                if (nhi == 0) continue;
+            }
+            if (mode == kRest) {
+                c = a.list[c];
+                // the minima may have fallen below this entry's bounds by now; n beyond the last template left is no use
+                if (tid < count) {
+                    const float lb = a.lb[(size_t)c * count + tid];
+                    if (lb < __builtin_huge_valf() && (double)lb <= best_now(a, tid)) atomicMax(&s_nhi, a.n_min + tid);
                 }
                 __syncthreads();
-                double *tmp = curP; curP = nxtP; nxtP = tmp;
-                tmp = curS; curS = nxtS; nxtS = tmp;
+                nhi = s_nhi;
+                if (nhi == 0) continue;
             }
         }
-        // ---- the slowest stage at every place it fits, for every template whose stage limit cannot bind:
-        // ca whole nodes and g GPUs before it, cb whole nodes and M - d - g GPUs after it, n = ca + cb + 1
-        const int places = M - d + 1; // g = 0 .. M - d GPUs of its node before it
-        for (int i = threadIdx.x; i < a.n_max * a.n_max; i += blockDim.x) {
-            const int ca = i / a.n_max, cb = i % a.n_max, n = ca + cb + 1;
-            if (n < a.n_min || n > a.n_max || (a.Nb > 0 && a.Nb < min(L, n * M))) continue;
-            double m = kNone;
-            for (int g = 0; g < places; ++g) m = fmin(m, s.PU[ca * M + g] + s.SV[cb * M + (M - d - g)]);
-            m += mid * tau;
-            if (m < kNone) atomicMin(&s.best[n - a.n_min], (unsigned long long)__double_as_longlong(m));
+        if (!evaluate<STAGED, MT>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
+            if (tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
+            continue;
+        }
+        if (mode != kFirst) { // let the other workgroups know
+            __syncthreads();
+            for (int i = tid; i < count; i += blockDim.x)
+                if (s_best[i] < (unsigned long long)__double_as_longlong(best_now(a, i))) atomicMin(&a.best[i], s_best[i]);
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < count; i += blockDim.x)
-        if (s.best[i] != 0x7FF0000000000000ull) atomicMin(&a.best[i], s.best[i]);
-}
-
-// Results as int64: -1 where no pipeline exists, -2 (unstaged entry point) where the stage limit
-// can bind, so that the minimum without it is not the answer.
-__global__ void k_exact_finish(Args a, int from_double, int staged) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > a.n_max - a.n_min) return;
-    const int n = a.n_min + i;
-    long long out;
-    if (!staged && a.Nb > 0 && a.Nb < min(a.L, n * a.M)) out = -2;
-    else if (from_double) { const double x = __longlong_as_double((long long)a.best[i]); out = x < kNone ? (long long)x : -1; }
-    else out = (long long)a.best[i] >= kInf / 2 ? -1 : (long long)a.best[i];
-    ((long long *)a.best)[i] = out;
+    for (int i = tid; i < count; i += blockDim.x)
+        if (s_best[i] < (unsigned long long)__double_as_longlong(best_now(a, i))) atomicMin(&a.best[i], s_best[i]);
+    if (mode != kFirst && !a.staged && last_workgroup(a)) finish(a, true); // (the staged entry point: k_exact_flat follows)
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -472,6 +1135,7 @@ __global__ void k_exact_finish(Args a, int from_double, int staged) {
 //   Suf[p][E][j] = the same for [p, L) on exactly the last E GPUs, t <= tau
 // STAGED = false: J = 1, the sums carry the weights of the cost; STAGED = true: plain sums of t, the
 // stage counts choose the coefficient of tau at the end and obey j1 + 1 + j2 <= N_b.
+// After a fast path it takes the entries that path could not hold, and otherwise every stage.
 // One workgroup takes one candidate slowest stage at a time (a grid-stride loop), walks the layers
 // with two barriers per layer (the stage times into / out of the layer are staged in LDS), each
 // thread owning (GPUs, stages) positions.
@@ -485,24 +1149,32 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
     long long *Pre = a.slots + (size_t)blockIdx.x * 2 * (L + 1) * plane, *Suf = Pre + (size_t)(L + 1) * plane;
     const long long *bnd = (const long long *)a.prof.boundary_ns;
     if (*a.status != OOB_OK) return;
+    const bool narrow = a.head->narrow != 0; // a fast path has run: a.best holds doubles, and only its leftovers are to do
+    if (narrow && a.head->over == 0) {
+        if (blockIdx.x == 0) finish(a, true);
+        return;
+    }
+    // time of stage [q, p) on dd GPUs, -1: impossible
+    auto stage = [&](int q, int p, int dd) -> long long {
+        if (q < a.flo[(size_t)p * M + dd - 1]) return -1;
+        return a.PT[(size_t)p * M + dd - 1] - a.PT[(size_t)q * M + dd - 1] + (p < L ? bnd[p - 1] : 0);
+    };
     const long long ptau = STAGED ? 0 : (a.Nb > 0 ? 0 : 4), stau = STAGED ? 0 : (a.Nb > 0 ? -1 : 3);
     const long long wsuf = STAGED ? 1 : 2;
     for (int i = threadIdx.x; i < count; i += kThreads) s_best[i] = kInf;
-    const long long ncand = (long long)L * (L + 1) / 2 * M;
+    const long long ncand = narrow ? (long long)a.head->over : (long long)L * (L + 1) / 2 * M;
     for (long long c = blockIdx.x; c < ncand; c += gridDim.x) {
-        const int d = (int)(c % M) + 1;
-        long long pr = c / M;
-        int u = 0;
-        while (pr >= L - u) { pr -= L - u; ++u; }
-        const int v = u + 1 + (int)pr;
-        const long long tau = a.t[((size_t)u * (L + 1) + v) * M + d - 1];
+        int u, v, d;
+        if (narrow) { const unsigned x = a.cuvd[a.over[c]]; u = x & 255; v = x >> 8 & 255; d = x >> 16; }
+        else triple((int)c, M, &u, &v, &d);
+        const long long tau = stage(u, v, d);
         if (tau < 0) continue;
         __syncthreads(); // the tables of the previous candidate are no longer read
         for (size_t i = threadIdx.x; i < plane; i += kThreads) Pre[i] = i == 0 ? 0 : kInf;
         for (int p = 1; p <= u; ++p) {
             __syncthreads();
             for (int i = threadIdx.x; i < p * M; i += kThreads) // times of the stages [q, p) on dd GPUs
-                s_col[i] = a.t[((size_t)(i / M) * (L + 1) + p) * M + i % M];
+                s_col[i] = stage(i / M, p, i % M + 1);
             __syncthreads();
             for (size_t i = threadIdx.x; i < plane; i += kThreads) {
                 const int D = (int)(i / J), j = (int)(i % J);
@@ -527,7 +1199,7 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
         for (int p = L - 1; p >= v; --p) {
             __syncthreads();
             for (int i = threadIdx.x; i < (L - p) * M; i += kThreads) // times of the stages [p, p+1+i/M) on dd GPUs
-                s_col[i] = a.t[((size_t)p * (L + 1) + p + 1 + i / M) * M + i % M];
+                s_col[i] = stage(p, p + 1 + i / M, i % M + 1);
             __syncthreads();
             for (size_t i = threadIdx.x; i < plane; i += kThreads) {
                 const int E = (int)(i / J), j = (int)(i % J);
@@ -585,10 +1257,56 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
     }
     __syncthreads();
     for (int i = threadIdx.x; i < count; i += kThreads)
-        if (s_best[i] < kInf) atomicMin(&a.best[i], (unsigned long long)s_best[i]);
+        if (s_best[i] < kInf)
+            atomicMin(&a.best[i], narrow ? (unsigned long long)__double_as_longlong((double)s_best[i]) : (unsigned long long)s_best[i]);
+    if (last_workgroup(a)) finish(a, narrow);
 }
 
 inline size_t slot_bytes(int L, int Dmax, int J) { return align_up(sizeof(long long) * 2 * (size_t)(L + 1) * (Dmax + 1) * J); }
+
+// Threads of k_exact_eval: a wave takes 64 / M start layers at a time, two rounds of them.
+inline int eval_threads(int L, int M, bool staged) {
+    if (staged) return kStagedThreads;
+    int slots = 64, waves = 4;
+    while (slots > 1 && 64 / slots < M) slots >>= 1;
+    while (waves < kEvalThreads / 64 && waves * slots * 2 < L) waves *= 2;
+    return waves * 64;
+}
+// LDS of k_exact_eval in bytes: without stage counts the tables of any slowest stage fit (0: they do not, the
+// shape takes the general path); with stage counts whatever is left for them, entries beyond that take
+// the general path one by one.
+inline size_t eval_lds(int L, int M, int n_max, int J, bool staged) {
+    const size_t fixed = 8 * (eval_fixed(L, M, n_max, J) + n_max);
+    if (staged) return M <= 8 && fixed + 48 * 1024 <= kLdsLimit - 512 ? kLdsLimit - 512 : 0;
+    const size_t all = fixed + 8 * (tri(L) + (size_t)L * M + (size_t)(L + 1) * (M + 1));
+    if (all > kLdsLimit - 512) return 0;
+    // as many workgroups per compute unit as the registers allow (sixteen waves)
+    const size_t most = 1024 / eval_threads(L, M, false), k = (kLdsLimit - 512) / all;
+    return ((kLdsLimit / (k < most ? k : most) - 512) & ~(size_t)15);
+}
+inline int bound_mus(int L, int M, bool staged) {
+    int mus = staged ? kMus : 1;
+    while (mus > 1 && 8 * bound_doubles(L, M, mus) > kLdsLimit - 512) --mus;
+    return 8 * bound_doubles(L, M, mus) <= kLdsLimit - 512 ? mus : 0;
+}
+struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blb, barg, list, over, slots; };
+inline Layout layout(int L, int M, int n_max, bool fast) {
+    const size_t n = fast ? tri(L) * M : 0, cnt = (size_t)imin(n_max, kMaxCount);
+    Layout y;
+    size_t o = 0;
+    y.head = o; o = align_up(o + sizeof(Head));
+    y.PT = o;   o = align_up(o + 8 * (size_t)(L + 1) * M);
+    y.flo = o;  o = align_up(o + (size_t)(L + 1) * M);
+    y.ctau = o; o = align_up(o + 8 * n);
+    y.cuvd = o; o = align_up(o + 4 * n);
+    y.lb = o;   o = align_up(o + (n > kDirectMax ? 4 * n * cnt : 0));
+    y.blb = o;  o = align_up(o + 4 * (size_t)kMaxBuckets * cnt);
+    y.barg = o; o = align_up(o + 4 * (size_t)kMaxBuckets * cnt);
+    y.list = o; o = align_up(o + 4 * n);
+    y.over = o; o = align_up(o + 4 * n);
+    y.slots = o;
+    return y;
+}
 
 } // namespace oob_exact
 
@@ -601,12 +1319,21 @@ static int exact_smax(int L, int n_max, int M, int Nb) {
     return Nb > 0 && Nb < s ? Nb : s;
 }
 
+// The stage limit S <= N_b can bind for some template.
+static bool exact_limit_binds(int L, int n_max, int M, int Nb) { return Nb > 0 && Nb < (L < n_max * M ? L : n_max * M); }
+
+// LDS of the fast path, 0: none for this shape.
+static size_t exact_lds(int L, int M, int n_max, int Nb, bool staged) {
+    const bool counts = staged && exact_limit_binds(L, n_max, M, Nb);
+    return oob_exact::eval_lds(L, M, n_max, counts ? exact_smax(L, n_max, M, Nb) + 1 : 1, counts);
+}
+
 extern "C" size_t oob_exact_workspace_size(int L, int n_max, int gpus_per_node) {
     using namespace oob_exact;
     if (!exact_dims_ok(L, n_max, gpus_per_node)) return 0;
-    size_t n = head_bytes(L, gpus_per_node);
-    if (lds_waves(L, gpus_per_node, n_max, n_max) == 0) // tables beyond LDS: the general path
-        n += (size_t)kFlatSlots * slot_bytes(L, n_max * gpus_per_node, 1);
+    const bool fast = exact_lds(L, gpus_per_node, n_max, 0, false) != 0;
+    size_t n = layout(L, gpus_per_node, n_max, fast).slots;
+    if (!fast) n += (size_t)kFlatSlots * slot_bytes(L, n_max * gpus_per_node, 1); // tables beyond LDS: the general path
     return n;
 }
 
@@ -617,7 +1344,38 @@ extern "C" size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per
     const size_t want = (size_t)1 << 30; // about a gigabyte of tables, at least 16 and at most kFlatSlots workgroups in flight
     size_t slots = want / slot;
     slots = slots < 16 ? 16 : slots > (size_t)kFlatSlots ? (size_t)kFlatSlots : slots;
-    return head_bytes(L, gpus_per_node) + slots * slot;
+    return layout(L, gpus_per_node, n_max, exact_lds(L, gpus_per_node, n_max, microbatches, true) != 0).slots + slots * slot;
+}
+
+template <bool STAGED, int MT>
+static int eval_launch_m(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
+    using namespace oob_exact;
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return OOB_EHIP;
+    hipLaunchKernelGGL((k_exact_eval<STAGED, MT>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
+    return OOB_OK;
+}
+template <bool STAGED> // a kernel of its own for the usual numbers of GPUs per node, known to the compiler
+static int eval_launch(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
+    switch (a.M) {
+    case 1: return eval_launch_m<STAGED, 1>(a, mode, grid, threads, lds, picks, st);
+    case 2: return eval_launch_m<STAGED, 2>(a, mode, grid, threads, lds, picks, st);
+    case 4: return eval_launch_m<STAGED, 4>(a, mode, grid, threads, lds, picks, st);
+    case 8: return eval_launch_m<STAGED, 8>(a, mode, grid, threads, lds, picks, st);
+    default: return eval_launch_m<STAGED, 0>(a, mode, grid, threads, lds, picks, st);
+    }
+}
+
+template <int MT>
+static int bounds_launch(const oob_exact::Args &a, int mus, size_t lds, hipStream_t st) {
+    using namespace oob_exact;
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_bounds<MT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)lds) != hipSuccess)
+        return OOB_EHIP;
+    const unsigned nb = (unsigned)((tri(a.L) * a.M + kBucket - 1) / kBucket);
+    hipLaunchKernelGGL(k_exact_bounds<MT>, dim3(nb < (unsigned)kMaxBuckets ? nb : (unsigned)kMaxBuckets), dim3(kBoundThreads), lds, st, a, mus);
+    return OOB_OK;
 }
 
 static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max, int M, int microbatches, int64_t mem_cap,
@@ -632,41 +1390,70 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
     a.prof = *profile; a.L = L; a.M = M; a.n_min = n_min; a.n_max = n_max; a.Nb = microbatches; a.Dmax = Dmax;
     a.Smax = exact_smax(L, n_max, M, microbatches);
     a.cap = mem_cap;
+    // stage counts are only carried where the limit can bind
+    const bool counts = staged && exact_limit_binds(L, n_max, M, microbatches);
+    const int J = counts ? a.Smax + 1 : 1;
+    const size_t lds = exact_lds(L, M, n_max, microbatches, staged);
+    a.fast = lds != 0;
+    a.staged = staged;
+    const size_t ntri = tri(L) * M;
+    const int mus = bound_mus(L, M, counts);
+    a.bounds = a.fast && ntri > (size_t)kDirectMax && count <= kMaxCount && mus > 0;
     char *ws = (char *)dev_workspace;
-    a.counter = (unsigned *)ws;
-    a.t = (long long *)(ws + 256);
-    a.tds = (double *)(ws + 256 + align_up(8 * table_entries(L, M)));
-    a.tdp = (double *)(ws + 256 + align_up(8 * table_entries(L, M)) + align_up(8 * dtable_entries(L, M)));
-    a.slots = (long long *)(ws + head_bytes(L, M));
+    const Layout y = layout(L, M, n_max, a.fast);
+    a.head = (Head *)(ws + y.head); a.PT = (long long *)(ws + y.PT); a.flo = (unsigned char *)(ws + y.flo);
+    a.ctau = (double *)(ws + y.ctau); a.cuvd = (unsigned *)(ws + y.cuvd); a.lb = (float *)(ws + y.lb);
+    a.blb = (float *)(ws + y.blb); a.barg = (unsigned *)(ws + y.barg); a.list = (unsigned *)(ws + y.list);
+    a.over = (unsigned *)(ws + y.over); a.slots = (long long *)(ws + y.slots);
     a.best = (unsigned long long *)best; a.status = status;
     hipStream_t st = (hipStream_t)stream;
-    const int nw = staged ? 0 : lds_waves(L, M, n_max, count);
-    const int J = staged ? a.Smax + 1 : 1;
+    // the general path: shapes beyond LDS; with the staged entry point also times beyond 2^52 and entries beyond LDS
+    const bool general = staged || !a.fast;
     size_t slots = 0;
-    if (nw == 0) {
-        if (workspace_bytes < head_bytes(L, M) + 16 * slot_bytes(L, Dmax, J)) return OOB_ECAPACITY;
-        slots = (workspace_bytes - head_bytes(L, M)) / slot_bytes(L, Dmax, J);
+    if (general) {
+        const size_t slot = slot_bytes(L, Dmax, J);
+        if (workspace_bytes < y.slots + 16 * slot) return OOB_ECAPACITY;
+        slots = (workspace_bytes - y.slots) / slot;
         if (slots > (size_t)kFlatSlots) slots = kFlatSlots;
-    } else if (workspace_bytes < head_bytes(L, M)) return OOB_ECAPACITY;
-    a.limit = nw ? kDoubleExact : kInf;
-    hipLaunchKernelGGL(k_exact_init, dim3(1), dim3(kThreads), 0, st, a);
-    hipLaunchKernelGGL(k_exact_fill, dim3(64), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(k_exact_stages, dim3((L * M + 63) / 64), dim3(64), 0, st, a);
-    const long long ncand = (long long)L * (L + 1) / 2 * M;
-    if (nw) {
-        const size_t lds = lds_bytes(L, M, n_max, count, nw);
-        if (lds > 64 * 1024 &&
-            hipFuncSetAttribute((const void *)k_exact_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return OOB_EHIP;
-        const unsigned grid = (unsigned)(ncand < 512 ? ncand : 512); // two rounds of workgroups per compute unit; a counter hands out the work
-        hipLaunchKernelGGL(k_exact_lds, dim3(grid), dim3(nw * 64), lds, st, a);
-    } else {
-        const unsigned grid = (unsigned)(ncand < (long long)slots ? ncand : (long long)slots);
-        const size_t lds = sizeof(long long) * ((size_t)L * M + count);
-        if (staged) hipLaunchKernelGGL(k_exact_flat<true>, dim3(grid), dim3(kThreads), lds, st, a);
-        else        hipLaunchKernelGGL(k_exact_flat<false>, dim3(grid), dim3(kThreads), lds, st, a);
+    } else if (workspace_bytes < y.slots) return OOB_ECAPACITY;
+    a.limit = general ? kInf : kDoubleExact;
+    const size_t prep = 8 * ((size_t)(L + 1) + (a.fast ? (size_t)(L + 1) * M : 0)) + (size_t)(L + 1) * M;
+    if (prep > 48 * 1024 && hipFuncSetAttribute((const void *)k_exact_prep, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                (int)prep) != hipSuccess)
+        return OOB_EHIP;
+    hipLaunchKernelGGL(k_exact_prep, dim3(1), dim3(kPrepThreads), prep, st, a);
+    int rc = OOB_OK;
+    if (a.fast) {
+        const int threads = eval_threads(L, M, counts);
+        const unsigned fill = (unsigned)(256 * imax(1, imin((int)(kLdsLimit / lds), 1024 / threads))); // workgroups the GPU holds at once
+        if (a.bounds) {
+            const size_t bl = 8 * bound_doubles(L, M, mus);
+            switch (M) {
+            case 1: rc = bounds_launch<1>(a, mus, bl, st); break;
+            case 2: rc = bounds_launch<2>(a, mus, bl, st); break;
+            case 4: rc = bounds_launch<4>(a, mus, bl, st); break;
+            case 8: rc = bounds_launch<8>(a, mus, bl, st); break;
+            default: rc = bounds_launch<0>(a, mus, bl, st); break;
+            }
+            if (rc != OOB_OK) return rc;
+            const int picks = imax(1, imin(10, (int)(fill / count)));
+            rc = counts ? eval_launch<true>(a, kFirst, count * picks, threads, lds, picks, st)
+                        : eval_launch<false>(a, kFirst, count * picks, threads, lds, picks, st);
+            if (rc != OOB_OK) return rc;
+            hipLaunchKernelGGL(k_exact_filter, dim3((unsigned)((ntri + 255) / 256)), dim3(256), 0, st, a);
+            rc = counts ? eval_launch<true>(a, kRest, fill, threads, lds, 0, st) : eval_launch<false>(a, kRest, fill, threads, lds, 0, st);
+        } else {
+            const unsigned some = fill < 512 ? fill : 512, grid = ntri < some ? (unsigned)ntri : some; // few enough to learn from each other
+            rc = counts ? eval_launch<true>(a, kAll, grid, threads, lds, 0, st) : eval_launch<false>(a, kAll, grid, threads, lds, 0, st);
+        }
+        if (rc != OOB_OK) return rc;
     }
-    hipLaunchKernelGGL(k_exact_finish, dim3((count + 63) / 64), dim3(64), 0, st, a, nw ? 1 : 0, staged ? 1 : 0);
+    if (general) {
+        const unsigned grid = (unsigned)(ntri < slots ? ntri : slots);
+        const size_t fl = sizeof(long long) * ((size_t)L * M + count);
+        if (counts) hipLaunchKernelGGL(k_exact_flat<true>, dim3(grid), dim3(kThreads), fl, st, a);
+        else        hipLaunchKernelGGL(k_exact_flat<false>, dim3(grid), dim3(kThreads), fl, st, a);
+    }
     return hipGetLastError() == hipSuccess ? OOB_OK : OOB_EHIP;
 }
 

@@ -195,3 +195,30 @@ def test_many_random_shapes(P):
                                   forbid_some_d=(var == "forbid"), **kw)
         st, got = P.ExactMinimum(inp).run()
         assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (n, L, M, n_min, n_max, nb, var, kw)
+
+
+@pytest.mark.parametrize("shape", [(64, 3, 1, 5, 64), (92, 1, 1, 20, 92), (98, 8, 1, 2, 98), (75, 2, 3, 20, 75),
+                                   (72, 5, 2, 6, 0), (90, 2, 1, 30, 90), (64, 3, 1, 4, 12), (92, 1, 1, 9, 8), (70, 2, 1, 5, 9)])
+def test_jobs_large_enough_for_bounds(P, shape):
+    """More (layer pair, GPU count) triples than are evaluated without lower bounds: one GPU per node, GPU
+    counts that are no power of two, few nodes (long stages: wide bands, tables over layers and GPUs), many
+    nodes, a stage limit that binds; random times, equal layers (every stage time occurs many times, bounds
+    and minima tie) and one layer that dwarfs the others."""
+    import dataclasses
+
+    L, M, n_min, n_max, nb = shape
+    assert L * (L + 1) // 2 * M > 4096
+    for var in ("plain", "tight", "forbid", "equal", "dwarf"):
+        inp = inputs.random_small(11, L, M, n_min, n_max, nb, f=1, tight_mem=(var == "tight"),
+                                  forbid_some_d=(var == "forbid"))
+        if var == "equal":
+            inp = dataclasses.replace(inp, fwd_ns=inp.fwd_ns[:1].repeat(L, 0).copy(), bwd_ns=inp.bwd_ns[:1].repeat(L, 0).copy())
+        if var == "dwarf":
+            fwd = inp.fwd_ns.copy()
+            fwd[L // 3] = fwd.sum(0)
+            inp = dataclasses.replace(inp, fwd_ns=fwd)
+        print("case", shape, var, flush=True)
+        staged = 0 < nb < min(L, n_max * M)
+        st, got = P.ExactMinimum(inp, staged=staged).run()
+        want = E.exact_minimum_staged(inp) if staged else E.exact_minimum(inp)
+        assert st == P.OOB_OK and got == want, (shape, var)
