@@ -46,8 +46,11 @@
 #include <type_traits>
 
 #include "oob_exact.h"
+#include "oob_layout.h"
 
 namespace oob_exact {
+
+using oob::wg_sync;
 
 constexpr int kThreads = 256;    // k_exact_flat
 constexpr int kFlatSlots = 2048; // its workgroups in flight at most, each with tables of its own
@@ -83,9 +86,12 @@ struct Args {
     unsigned char *flo;   // [(L+1) M] first layer u for which [u, v) may run on d GPUs of a node (memory, forbidden counts)
     double *ctau;         // [ncand] possible slowest stages, ascending (by bins): time
     unsigned *cuvd;       //         u | v << 8 | d << 16
-    float *lb;            // [ncand][count] lower bounds
+    int nk;               // pairs of multipliers
+    float *lb;            // [ncand][nk] lower bounds but for the part that depends on the template
+    double *blo;          // [nbuckets] fastest stage of a bucket, the unit of its multipliers
+    int *bfew;            // [nbuckets] fewest nodes that can cover the layers
     float *blb;           // [nbuckets][count] smallest bound of a bucket
-    unsigned *barg;       // [nbuckets][count] and the entry it belongs to
+    unsigned short *barg; // [nbuckets][count] and the entry it belongs to, from the first of the bucket
     unsigned *list;       // [ncand] entries left to evaluate
     unsigned *over;       // [ncand] entries that k_exact_flat has to evaluate (tables beyond LDS)
     long long *slots;     // k_exact_flat: [slots][2][(L+1)][(Dmax+1)][J]
@@ -119,10 +125,10 @@ __device__ void finish(const Args &a, bool from_double) {
 __device__ bool last_workgroup(const Args &a) {
     __shared__ unsigned s_last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
+    wg_sync();
     if (threadIdx.x == 0)
         s_last = __hip_atomic_fetch_add(&a.head->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-    __syncthreads();
+    wg_sync();
     return s_last != 0;
 }
 
@@ -176,7 +182,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
     for (int i = tid; i < count; i += blockDim.x) a.best[i] = kNoneBits; // +inf as a double, huge as an integer
     for (int i = tid; i < kBins; i += blockDim.x) s_hist[i] = 0;
     if (tid == 0) { s_bad = 0; s_min = kNoneBits; }
-    __syncthreads();
+    wg_sync();
     // magnitudes and signs
     unsigned long long acc = 0;
     bool bad = false;
@@ -232,7 +238,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
             carry = __shfl(x, 63, 64);
         }
     }
-    __syncthreads();
+    wg_sync();
     unsigned long long w = 0;
     for (int i = 0; i < nw; ++i) { w += s_sum[i]; if (w > (unsigned long long)kInf) w = (unsigned long long)kInf; }
     const long long mult = (a.Nb > 0 ? (long long)a.Nb : 4ll * a.Smax) + 2;
@@ -257,7 +263,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
             const long long t = s_pt[(size_t)(l + 1) * M + d] - s_pt[(size_t)l * M + d] + (l + 1 < L ? bnd[l] : 0);
             if (t > 0) atomicMin(&s_min, (unsigned long long)__double_as_longlong((double)t));
         }
-    __syncthreads();
+    wg_sync();
     int total = 0;
     if (st == OOB_OK && narrow) { // list the possible slowest stages by time
         const int kmin = (int)(s_min >> 44), inv = 65536 / M + 1;
@@ -284,7 +290,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
                             if (pos[q] >= 0) { a.ctau[pos[q]] = tau[q]; a.cuvd[pos[q]] = (unsigned)(ud[q] | v << 8); }
                 }
             }
-            __syncthreads();
+            wg_sync();
             if (pass) break;
             // exclusive scan of the bins: kBins / kPrepThreads each
             constexpr int per = kBins / kPrepThreads;
@@ -295,12 +301,12 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) { const int y = __shfl_up(incl, d, 64); if (lane >= d) incl += y; }
             if (lane == 63) s_wave[wave] = incl;
-            __syncthreads();
+            wg_sync();
             int base = incl - sum;
             for (int i = 0; i < nw; ++i) { if (i < wave) base += s_wave[i]; total += s_wave[i]; }
 #pragma unroll
             for (int q = 0; q < per; ++q) { s_hist[tid * per + q] = base; base += h[q]; }
-            __syncthreads();
+            wg_sync();
         }
     }
     if (tid == 0) {
@@ -453,6 +459,17 @@ __host__ __device__ inline size_t bound_doubles(int L, int M, int mus) {
     return prof_doubles(L, M) + 2 * (((size_t)(L + 1) * M + 7) / 8) + (size_t)mus * kLambdas * 2 * (L + 1) +
            kBucket * kMaxCount / 2 + 32;
 }
+// What the multipliers k take off for a pipeline of n nodes, in units of the bucket's fastest stage.
+__device__ __forceinline__ double spent(const Args &a, int k, int n) {
+    return (a.Nb > 0 ? kLambdaGiven[k % kLambdas] : kLambda4S[k % kLambdas]) * (n * a.M) + kMuStep[k / kLambdas] * a.Smax;
+}
+// The bound of an entry (its values lb[0 .. nk-1]) of a bucket for n nodes; below all doubt where there is none.
+__device__ __forceinline__ double bound_of(const Args &a, const float *lb, double lo, int fewest, int n) {
+    if (n < fewest || n > a.L) return kNone;
+    double x = -kNone;
+    for (int k = 0; k < a.nk; ++k) x = fmax(x, (double)lb[k] - lo * spent(a, k, n));
+    return x;
+}
 template <int MT>
 __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus) {
     constexpr int CW = MT ? MT : 8;
@@ -472,12 +489,12 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
     float *s_lb = (float *)(PS + (size_t)mus * kLambdas * 2 * W); // [kBucket][kMaxCount]
     unsigned char *s_far = (unsigned char *)(s_lb + kBucket * kMaxCount); // [256] for fewest_nodes()
     if (threadIdx.x == 0) { s_lo = kNoneBits; s_hi = 0; s_fewest = 0; }
-    __syncthreads();
+    wg_sync();
     for (unsigned c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
         atomicMin(&s_lo, (unsigned long long)__double_as_longlong(a.ctau[c]));
         atomicMax(&s_hi, (unsigned long long)__double_as_longlong(a.ctau[c]));
     }
-    __syncthreads();
+    wg_sync();
     const double lo = __longlong_as_double((long long)s_lo), hi = __longlong_as_double((long long)s_hi);
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
         const int p = i / M, dd = i - p * M + 1;
@@ -487,7 +504,7 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
     const bool given = a.Nb > 0;
     if (threadIdx.x < kLambdas) s_lam[threadIdx.x] = (given ? kLambdaGiven[threadIdx.x] : kLambda4S[threadIdx.x]) * lo;
     else if (threadIdx.x - kLambdas < kMus) s_mu[threadIdx.x - kLambdas] = kMuStep[threadIdx.x - kLambdas] * lo;
-    __syncthreads();
+    wg_sync();
     const double pw = given ? 0.0 : 4.0 * lo, sw = given ? -hi : 3.0 * lo, mid = given ? (double)a.Nb : 4.0;
     const int sub = lane & 31, nt = nw - 1; // the last wave: fewest nodes
     if (wave == nt && M <= kCoverGpus) {
@@ -547,42 +564,45 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
         };
         if (side) rows(std::true_type{}); else rows(std::false_type{});
     }
-    __syncthreads();
+    wg_sync();
     // bounds of the bucket's entries, kBucket at a time; the smallest of every template
-    const int count = a.n_max - a.n_min + 1;
+    const int count = a.n_max - a.n_min + 1, nk = mus * kLambdas;
     float mine = __builtin_huge_valf();
     unsigned arg = c0;
     for (unsigned m0 = c0; m0 < c1; m0 += kBucket) {
         const int m = (int)min(c1 - m0, (unsigned)kBucket);
-        for (int i = threadIdx.x; i < m * count; i += blockDim.x) {
-            const int q = i / count, ni = i - q * count; // (n nodes that cannot cover the layers: never)
+        for (int i = threadIdx.x; i < m * nk; i += blockDim.x) {
+            const int q = i / nk, k = i - q * nk;
             const unsigned uvd = a.cuvd[m0 + q];
-            const int u = uvd & 255, v = uvd >> 8 & 255, d = uvd >> 16, n = a.n_min + ni;
-            const double tau = a.ctau[m0 + q];
-            double bound = -kNone;
-            for (int k = 0; k < mus * kLambdas; ++k) {
-                const double l = s_lam[k % kLambdas], mu = s_mu[k / kLambdas];
-                const double base = mid * tau + PS[(size_t)k * 2 * W + u] + PS[((size_t)k * 2 + 1) * W + v] + l * d + mu;
-                const double spent = l * n * M + mu * a.Smax;
-                // lowered by far more than these few roundings are worth
-                bound = fmax(bound, base - spent - 1e-9 * (fabs(base) + mid * tau + s.PT[L * M] + fabs(l) * n * M + mu * a.Smax));
-            }
-            const float f = n >= s_fewest && n <= L ? __double2float_rd(bound) : __builtin_huge_valf();
-            s_lb[q * kMaxCount + ni] = f;
-            a.lb[(size_t)(m0 + q) * count + ni] = f;
+            const int u = uvd & 255, v = uvd >> 8 & 255, d = uvd >> 16;
+            const double tau = a.ctau[m0 + q], l = s_lam[k % kLambdas], mu = s_mu[k / kLambdas];
+            const double base = mid * tau + PS[(size_t)k * 2 * W + u] + PS[((size_t)k * 2 + 1) * W + v] + l * d + mu;
+            // lowered by far more than a few roundings of sums of this size are worth
+            s_lb[i] = __double2float_rd(base - 1e-9 * (fabs(base) + mid * tau + s.PT[L * M] + fabs(l) * a.n_max * M + mu * a.Smax));
+            a.lb[(size_t)m0 * nk + i] = s_lb[i];
         }
-        __syncthreads();
-        if ((int)threadIdx.x < count)
-            for (int q = 0; q < m; ++q) {
-                const float f = s_lb[q * kMaxCount + threadIdx.x];
-                if (f < mine) { mine = f; arg = m0 + q; }
+        wg_sync();
+        // lanes: templates; the entries shared out among the waves
+        for (int ni = lane; ni < count; ni += 64)
+            for (int q = wave; q < m; q += nw) {
+                const double x = bound_of(a, s_lb + q * nk, lo, s_fewest, a.n_min + ni);
+                if (x < (double)mine) { mine = __double2float_rd(x); arg = m0 + q; }
             }
-        __syncthreads();
+        wg_sync();
     }
+    // (count <= kMaxCount = 64: a lane has one template)
+    s_lb[threadIdx.x] = mine;
+    ((unsigned *)s_lb)[kBoundThreads + threadIdx.x] = arg;
+    wg_sync();
     if ((int)threadIdx.x < count) {
+        for (int w = 1; w < nw; ++w) {
+            const float f = s_lb[w * 64 + threadIdx.x];
+            if (f < mine) { mine = f; arg = ((unsigned *)s_lb)[kBoundThreads + w * 64 + threadIdx.x]; }
+        }
         a.blb[(size_t)b * count + threadIdx.x] = mine;
-        a.barg[(size_t)b * count + threadIdx.x] = arg;
+        a.barg[(size_t)b * count + threadIdx.x] = (unsigned short)(arg - c0);
     }
+    if (threadIdx.x == 0) { a.blo[b] = lo; a.bfew[b] = s_fewest; }
 }
 
 // Entries whose bound does not exceed the minimum found so far for some template: one wave each.
@@ -597,13 +617,11 @@ __global__ void __launch_bounds__(256) k_exact_filter(Args a) {
     if (c0 >= total) return;
     const double best = lane < count ? __longlong_as_double((long long)a.best[lane]) : -1.0;
     unsigned long long keep = 0;
-    for (unsigned q0 = 0; q0 < 64; q0 += 16) {
-        float lb[16];
-#pragma unroll
-        for (unsigned q = 0; q < 16; ++q) lb[q] = a.lb[(size_t)min(c0 + q0 + q, total - 1) * count + min(lane, count - 1)];
-#pragma unroll
-        for (unsigned q = 0; q < 16; ++q)
-            if (c0 + q0 + q < total && __any(lane < count && lb[q] < __builtin_huge_valf() && (double)lb[q] <= best)) keep |= 1ull << (q0 + q);
+    const unsigned K = a.head->bucket;
+    for (unsigned q = 0; q < 64 && c0 + q < total; ++q) {
+        const unsigned c = c0 + q, bk = c / K;
+        const double x = lane < count ? bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + (int)lane) : kNone;
+        if (__any(x < kNone && x <= best)) keep |= 1ull << q;
     }
     unsigned at = 0;
     if (lane == 0 && keep) at = atomicAdd(&a.head->alive, (unsigned)__popcll(keep));
@@ -916,7 +934,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     // ---- reach of the stages, and the most layers a node can cover on either side: a stage on dd GPUs covers at
     // most rho dd layers, rho the largest (layers / GPUs) of any stage, so a node at most floor(M rho)
     if (threadIdx.x < 2) e.ints[threadIdx.x] = 0;
-    __syncthreads();
+    wg_sync();
     int mostP = 0, mostS = 0;
     const int inv = 65536 / M + 1; // i / M = i inv >> 16, exact below 2^14
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
@@ -929,9 +947,9 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) { mostP = imax(mostP, __shfl_xor(mostP, m, 64)); mostS = imax(mostS, __shfl_xor(mostS, m, 64)); }
     if ((threadIdx.x & 63) == 0) { atomicMax(&e.ints[0], mostP); atomicMax(&e.ints[1], mostS); }
-    __syncthreads();
+    wg_sync();
     const int bandP = imin(e.ints[0], lenP), bandS = imin(e.ints[1], lenS);
-    __syncthreads();
+    wg_sync();
     if ((lenP && !bandP) || (lenS && !bandS)) return true; // some layer fits no stage fast enough
     const double mid = a.Nb > 0 ? (double)a.Nb : 4.0;
     const double ptau = STAGED || a.Nb > 0 ? 0.0 : 4.0, stau = STAGED ? 0.0 : a.Nb > 0 ? -1.0 : 3.0;
@@ -950,11 +968,11 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
                 const int side = i >= row_n, o = i - side * row_n;
                 e.pool[side * second + o] = o == 0 ? 0.0 : kNone;
             }
-            __syncthreads();
+            wg_sync();
             for (int r = 1; r <= imax(lenP, lenS); ++r) {
                 if (!mir) { if (r <= lenP) gpu_row<false, STAGED, MT>(a, e, r, nd, jd, tau, 1.0, ptau * tau, e.pool, th, nth); }
                 else      { if (r <= lenS) gpu_row<true, STAGED, MT>(a, e, r, nd, jd, tau, 2.0, stau * tau, e.pool + second, th, nth); }
-                __syncthreads();
+                wg_sync();
             }
             for (int i = threadIdx.x; i < (cendP + cendS) * M * J; i += blockDim.x) {
                 const bool after = i >= cendP * M * J;
@@ -962,7 +980,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
                 e.OUT[(after ? a.n_max * M * J : 0) + o] =
                     j < jd ? e.pool[(after ? second + lenS * row_n : lenP * row_n) + d0 * jd + j] : kNone;
             }
-            __syncthreads();
+            wg_sync();
             combine<STAGED>(a, e, d, tau, nhi, cendP, cendS, mid, s_best);
             return true;
         }
@@ -1004,10 +1022,10 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     const size_t histP = (size_t)cendP * (bandP + 1), histS = (size_t)cendS * (bandS + 1);
     if (!STAGED && imax(bandP, bandS) <= kChainBand && imax(lenP, lenS) <= kChainLen && used + histP + histS <= e.pool_n) {
         double *HP = G; // (in place of the one-node tables)
-        __syncthreads();
+        wg_sync();
         if (wave == 0 || wave == nw - 1)
             node_chain_any(mir ? lenS : lenP, mir ? bandS : bandP, mir ? cendS : cendP, WP + (mir ? WS - WP : 0), HP + (mir ? histP : 0));
-        __syncthreads();
+        wg_sync();
         for (int i = threadIdx.x; i < (cendP + cendS) * M; i += blockDim.x) {
             const bool after = i >= cendP * M;
             const int o = after ? i - cendP * M : i, c = o / M, g = o - c * M, band = after ? bandS : bandP;
@@ -1016,19 +1034,19 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
             if (g > 0) for (int r = 1; r <= band; ++r) m = fmin(m, H[r] + cov[(r - 1) * M]);
             e.OUT[(after ? a.n_max * M : 0) + o] = m;
         }
-        __syncthreads();
+        wg_sync();
     } else {
     // wide ones: half of the waves each, a barrier per node count
     double *cur = e.NP + (mir ? (size_t)(lenP + 1) * J : 0), *nxt = cur + (size_t)(L + 2) * J;
     const int len = mir ? lenS : lenP, band = mir ? bandS : bandP, cend = mir ? cendS : cendP;
     for (int i = th; i < (len + 1) * J; i += nth) { cur[i] = i == 0 ? 0.0 : kNone; nxt[i] = kNone; }
-    __syncthreads();
+    wg_sync();
     for (int c = 0; c < imax(cendP, cendS); ++c) {
         if (c < cend) {
             node_out<STAGED>(a, len, band, c, cur, e.GU + (mir ? bandP * gu : 0), e.OUT + (mir ? (size_t)a.n_max * M * J : 0), th, nth);
             if (c + 1 < cend) node_step<STAGED>(a, len, band, c, WP + (mir ? WS - WP : 0), cur, nxt, th, nth);
         }
-        __syncthreads();
+        wg_sync();
         double *t = cur; cur = nxt; nxt = t;
     }
     }
@@ -1056,7 +1074,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     for (int i = tid; i < count; i += blockDim.x) s_best[i] = kNoneBits;
     const unsigned total = mode == kRest ? a.head->alive : a.head->ncand;
     for (int turn = 0;; ++turn) {
-        __syncthreads(); // the previous entry is done with LDS (and s_next has been read)
+        wg_sync(); // the previous entry is done with LDS (and s_next has been read)
         unsigned c;
         int nhi = a.n_max;
         if (mode == kFirst) {
@@ -1069,20 +1087,20 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
             float *key = (float *)e.pool;
             for (unsigned i = tid; i < nb; i += blockDim.x) key[i] = a.blb[(size_t)i * count + ni];
             if (tid == 0) s_next = 0xffffffffu;
-            __syncthreads();
+            wg_sync();
             for (unsigned i = tid; i < nb; i += blockDim.x) {
                 const float k = key[i];
                 int below = 0;
                 for (unsigned q = 0; q < nb; ++q) below += key[q] < k || (key[q] == k && q < i);
-                if (below == rank && k < __builtin_huge_valf()) s_next = a.barg[(size_t)i * count + ni];
+                if (below == rank && k < __builtin_huge_valf()) s_next = i * a.head->bucket + a.barg[(size_t)i * count + ni];
             }
-            __syncthreads();
+            wg_sync();
             c = s_next;
             if (c == 0xffffffffu) break;
         } else {
             if (tid == 0) s_next = __hip_atomic_fetch_add(&a.head->next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (tid == 1) s_nhi = 0;
-            __syncthreads();
+            wg_sync();
             c = s_next;
             if (c >= total) break; // every wave of every workgroup gets here
             if (mode == kAll) {
@@ -1097,7 +1115,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                     if (least <= best_now(a, tid)) atomicMax(&s_nhi, n);
                 }
                 if (count > (int)blockDim.x && tid == 0) s_nhi = a.n_max;
-                __syncthreads();
+                wg_sync();
                 nhi = s_nhi;
                 if (nhi == 0) continue;
             }
@@ -1105,10 +1123,11 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                 c = a.list[c];
                 // the minima may have fallen below this entry's bounds by now; n beyond the last template left is no use
                 if (tid < count) {
-                    const float lb = a.lb[(size_t)c * count + tid];
-                    if (lb < __builtin_huge_valf() && (double)lb <= best_now(a, tid)) atomicMax(&s_nhi, a.n_min + tid);
+                    const unsigned bk = c / a.head->bucket;
+                    const double x = bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + tid);
+                    if (x < kNone && x <= best_now(a, tid)) atomicMax(&s_nhi, a.n_min + tid);
                 }
-                __syncthreads();
+                wg_sync();
                 nhi = s_nhi;
                 if (nhi == 0) continue;
             }
@@ -1118,12 +1137,12 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
             continue;
         }
         if (mode != kFirst) { // let the other workgroups know
-            __syncthreads();
+            wg_sync();
             for (int i = tid; i < count; i += blockDim.x)
                 if (s_best[i] < (unsigned long long)__double_as_longlong(best_now(a, i))) atomicMin(&a.best[i], s_best[i]);
         }
     }
-    __syncthreads();
+    wg_sync();
     for (int i = tid; i < count; i += blockDim.x)
         if (s_best[i] < (unsigned long long)__double_as_longlong(best_now(a, i))) atomicMin(&a.best[i], s_best[i]);
     if (mode != kFirst && !a.staged && last_workgroup(a)) finish(a, true); // (the staged entry point: k_exact_flat follows)
@@ -1169,13 +1188,13 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
         else triple((int)c, M, &u, &v, &d);
         const long long tau = stage(u, v, d);
         if (tau < 0) continue;
-        __syncthreads(); // the tables of the previous candidate are no longer read
+        wg_sync(); // the tables of the previous candidate are no longer read
         for (size_t i = threadIdx.x; i < plane; i += kThreads) Pre[i] = i == 0 ? 0 : kInf;
         for (int p = 1; p <= u; ++p) {
-            __syncthreads();
+            wg_sync();
             for (int i = threadIdx.x; i < p * M; i += kThreads) // times of the stages [q, p) on dd GPUs
                 s_col[i] = stage(i / M, p, i % M + 1);
-            __syncthreads();
+            wg_sync();
             for (size_t i = threadIdx.x; i < plane; i += kThreads) {
                 const int D = (int)(i / J), j = (int)(i % J);
                 long long m = kInf;
@@ -1194,13 +1213,13 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
                 Pre[(size_t)p * plane + i] = m;
             }
         }
-        __syncthreads();
+        wg_sync();
         for (size_t i = threadIdx.x; i < plane; i += kThreads) Suf[(size_t)L * plane + i] = i == 0 ? 0 : kInf;
         for (int p = L - 1; p >= v; --p) {
-            __syncthreads();
+            wg_sync();
             for (int i = threadIdx.x; i < (L - p) * M; i += kThreads) // times of the stages [p, p+1+i/M) on dd GPUs
                 s_col[i] = stage(p, p + 1 + i / M, i % M + 1);
-            __syncthreads();
+            wg_sync();
             for (size_t i = threadIdx.x; i < plane; i += kThreads) {
                 const int E = (int)(i / J), j = (int)(i % J);
                 long long m = kInf;
@@ -1226,7 +1245,7 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
                 Suf[(size_t)p * plane + i] = m;
             }
         }
-        __syncthreads();
+        wg_sync();
         // the slowest stage at every place it fits, for every template
         for (size_t i = threadIdx.x; i < plane; i += kThreads) {
             const int D = (int)(i / J), j1 = (int)(i % J);
@@ -1255,7 +1274,7 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
             }
         }
     }
-    __syncthreads();
+    wg_sync();
     for (int i = threadIdx.x; i < count; i += kThreads)
         if (s_best[i] < kInf)
             atomicMin(&a.best[i], narrow ? (unsigned long long)__double_as_longlong((double)s_best[i]) : (unsigned long long)s_best[i]);
@@ -1289,8 +1308,8 @@ inline int bound_mus(int L, int M, bool staged) {
     while (mus > 1 && 8 * bound_doubles(L, M, mus) > kLdsLimit - 512) --mus;
     return 8 * bound_doubles(L, M, mus) <= kLdsLimit - 512 ? mus : 0;
 }
-struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blb, barg, list, over, slots; };
-inline Layout layout(int L, int M, int n_max, bool fast) {
+struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blo, bfew, blb, barg, list, over, slots; };
+inline Layout layout(int L, int M, int n_max, bool fast, int mus, bool staged) { // mus: of the stage limit, 0: no bounds
     const size_t n = fast ? tri(L) * M : 0, cnt = (size_t)imin(n_max, kMaxCount);
     Layout y;
     size_t o = 0;
@@ -1299,11 +1318,13 @@ inline Layout layout(int L, int M, int n_max, bool fast) {
     y.flo = o;  o = align_up(o + (size_t)(L + 1) * M);
     y.ctau = o; o = align_up(o + 8 * n);
     y.cuvd = o; o = align_up(o + 4 * n);
-    y.lb = o;   o = align_up(o + (n > kDirectMax ? 4 * n * cnt : 0));
+    y.lb = o;   o = align_up(o + (n > kDirectMax ? 4 * n * kLambdas * mus : 0));
+    y.blo = o;  o = align_up(o + 8 * (size_t)kMaxBuckets);
+    y.bfew = o; o = align_up(o + 4 * (size_t)kMaxBuckets);
     y.blb = o;  o = align_up(o + 4 * (size_t)kMaxBuckets * cnt);
-    y.barg = o; o = align_up(o + 4 * (size_t)kMaxBuckets * cnt);
+    y.barg = o; o = align_up(o + 2 * (size_t)kMaxBuckets * cnt);
     y.list = o; o = align_up(o + 4 * n);
-    y.over = o; o = align_up(o + 4 * n);
+    y.over = o; o = align_up(o + (staged ? 4 * n : 0));
     y.slots = o;
     return y;
 }
@@ -1332,7 +1353,7 @@ extern "C" size_t oob_exact_workspace_size(int L, int n_max, int gpus_per_node) 
     using namespace oob_exact;
     if (!exact_dims_ok(L, n_max, gpus_per_node)) return 0;
     const bool fast = exact_lds(L, gpus_per_node, n_max, 0, false) != 0;
-    size_t n = layout(L, gpus_per_node, n_max, fast).slots;
+    size_t n = layout(L, gpus_per_node, n_max, fast, bound_mus(L, gpus_per_node, false), false).slots;
     if (!fast) n += (size_t)kFlatSlots * slot_bytes(L, n_max * gpus_per_node, 1); // tables beyond LDS: the general path
     return n;
 }
@@ -1344,7 +1365,8 @@ extern "C" size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per
     const size_t want = (size_t)1 << 30; // about a gigabyte of tables, at least 16 and at most kFlatSlots workgroups in flight
     size_t slots = want / slot;
     slots = slots < 16 ? 16 : slots > (size_t)kFlatSlots ? (size_t)kFlatSlots : slots;
-    return layout(L, gpus_per_node, n_max, exact_lds(L, gpus_per_node, n_max, microbatches, true) != 0).slots + slots * slot;
+    const int mus = bound_mus(L, gpus_per_node, exact_limit_binds(L, n_max, gpus_per_node, microbatches));
+    return layout(L, gpus_per_node, n_max, exact_lds(L, gpus_per_node, n_max, microbatches, true) != 0, mus, true).slots + slots * slot;
 }
 
 template <bool STAGED, int MT>
@@ -1400,10 +1422,11 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
     const int mus = bound_mus(L, M, counts);
     a.bounds = a.fast && ntri > (size_t)kDirectMax && count <= kMaxCount && mus > 0;
     char *ws = (char *)dev_workspace;
-    const Layout y = layout(L, M, n_max, a.fast);
+    const Layout y = layout(L, M, n_max, a.fast, mus, staged);
     a.head = (Head *)(ws + y.head); a.PT = (long long *)(ws + y.PT); a.flo = (unsigned char *)(ws + y.flo);
     a.ctau = (double *)(ws + y.ctau); a.cuvd = (unsigned *)(ws + y.cuvd); a.lb = (float *)(ws + y.lb);
-    a.blb = (float *)(ws + y.blb); a.barg = (unsigned *)(ws + y.barg); a.list = (unsigned *)(ws + y.list);
+    a.blo = (double *)(ws + y.blo); a.bfew = (int *)(ws + y.bfew); a.nk = kLambdas * mus;
+    a.blb = (float *)(ws + y.blb); a.barg = (unsigned short *)(ws + y.barg); a.list = (unsigned *)(ws + y.list);
     a.over = (unsigned *)(ws + y.over); a.slots = (long long *)(ws + y.slots);
     a.best = (unsigned long long *)best; a.status = status;
     hipStream_t st = (hipStream_t)stream;

@@ -175,4 +175,12 @@ __host__ __device__ inline int seg_count_bound(int L) {
     return c;
 }
 
+// Workgroup barrier behind this wave's LDS operations.  The compiler leaves that wait out at the head of some loops
+// (a write from the end of the loop body is then still under way when the other waves read past the barrier).
+#ifdef __HIP_DEVICE_COMPILE__
+__device__ __forceinline__ void wg_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); __syncthreads(); }
+#else
+__device__ inline void wg_sync() {}
+#endif
+
 } // namespace oob
