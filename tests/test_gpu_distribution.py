@@ -160,6 +160,23 @@ def test_choice_of_the_plan_against_the_oracle(P):
     assert checked >= 15
 
 
+@pytest.mark.parametrize("groups", [[1], [0, 255, 256, 257, 0], [70000, 3, 65537], [5] * 300])
+def test_choice_in_groups_of_any_size(P, groups):
+    """Groups below, at and above the shares of a workgroup, empty ones, more groups than lanes; few distinct times, so
+    that the first of equals decides, and plans that cannot be distributed."""
+    rng = np.random.Generator(np.random.PCG64(len(groups)))
+    total = sum(groups)
+    vecs = rng.integers(0, 3, size=(total, 3))
+    tT = [40, 50, 50]
+    d = P.Distributor(vecs, total, tT, 5)
+    st, vx, slow, base, extra = d.solve()
+    off = np.concatenate([[0], np.cumsum(groups)])
+    best = d.choose(off)
+    for g in range(len(groups)):
+        ok = np.flatnonzero(st[off[g]:off[g + 1]] == P.OOB_DIST_OK) + off[g]
+        assert best[g] == (ok[np.argmin(slow[ok])] if len(ok) else -1), g
+
+
 def test_headline_node_specification_at_full_size(P):
     """All 1 343 380 plans of the headline workload's node specification (templates for 8..64 nodes,
     f = 8, 72..128 nodes), the planner's own T1 per template as the time per microbatch, 512
