@@ -1,8 +1,9 @@
 // Reconfiguration simulator (Section 5.1 and Appendix B of the Oobleck paper) for gfx950.
 //
 // One lane runs one failure sequence.  A trajectory's state is small (at most 64 pipeline sizes
-// and a 64-bit mask of the list positions still in use), but it is indexed by data: the sizes
-// live in LDS, one column per lane (sizes[position][lane], 16 bits, as many rows as there are
+// and a 64-bit mask of the list positions still in use), but it is indexed by data.  Up to 16 pipelines
+// and 128 nodes the sizes are bytes in registers and every search over the list works on whole
+// words (run_in_registers); beyond that (run_in_lds) the sizes live in LDS, one column per lane (sizes[position][lane], 16 bits, as many rows as there are
 // starting pipelines), so that the lanes of a wave never share a bank row for the same position,
 // and the mask lives in a register pair.  A list position whose pipeline was absorbed keeps size
 // 0, so the two loops that run at every step (which pipeline holds the failing node; who can
@@ -20,6 +21,7 @@
 namespace oob_reconf {
 
 constexpr int kLanes = 256; // trajectories per workgroup
+constexpr int kPackedNodes = 128, kPackedWords = 4;
 constexpr int kUnroll = 4;  // list positions per round of the two scans; the list is padded with empty ones
 
 struct Args {
@@ -32,26 +34,32 @@ struct Args {
     int *final_sizes, *summary, *status;
 };
 
-// Starting pipelines must be template sizes and few enough nodes for 16 bits.
-__device__ __forceinline__ bool start_ok(const Args &a) {
+// Nodes at the start; -1 where the starting pipelines are no template sizes or too many nodes for 16 bits.
+__device__ __forceinline__ long long start_nodes(const Args &a) {
     long long sum = 0;
     for (int i = 0; i < a.c0; ++i) {
         const int s = a.sizes0[i];
-        if (s < a.n0 || s > a.n_hi) return false;
+        if (s < a.n0 || s > a.n_hi) return -1;
         sum += s;
     }
-    return sum <= OOB_RECONF_MAX_NODES;
+    return sum <= OOB_RECONF_MAX_NODES ? sum : -1;
 }
 
-__global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
-    HIP_DYNAMIC_SHARED(unsigned short, sizes) // [rows][kLanes], rows = c0 rounded up to kUnroll
-    const int lane = threadIdx.x;
-    const long long t = (long long)blockIdx.x * kLanes + lane;
-    const bool ok = start_ok(a);
-    if (t == 0) *a.status = ok ? OOB_OK : OOB_EINVAL;
-    if (!ok || t >= a.T) return;
+__device__ __forceinline__ void write_summary(const Args &a, long long t, int survived, int reinst, int borrowed, int merges,
+                                              int alive, int nodes, int viol, int stop) {
+    int *sm = a.summary + t;
+    sm[OOB_RECONF_SURVIVED * a.T] = survived;
+    sm[OOB_RECONF_REINSTANTIATED * a.T] = reinst;
+    sm[OOB_RECONF_BORROWED * a.T] = borrowed;
+    sm[OOB_RECONF_MERGES * a.T] = merges;
+    sm[OOB_RECONF_ALIVE * a.T] = alive;
+    sm[OOB_RECONF_NODES * a.T] = nodes;
+    sm[OOB_RECONF_VIOLATIONS * a.T] = viol;
+    sm[OOB_RECONF_STOP * a.T] = stop;
+}
 
-    unsigned short *mine = sizes + lane; // position i at mine[i * kLanes]
+// One trajectory with its sizes in LDS: position i at mine[i * kLanes].
+__device__ void run_in_lds(const Args &a, long long t, unsigned short *mine) {
     const int rows = (a.c0 + kUnroll - 1) / kUnroll * kUnroll;
     unsigned total = 0;
     for (int i = 0; i < rows; ++i) {
@@ -148,15 +156,189 @@ __global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
 
     if (a.final_sizes)
         for (int i = 0; i < a.c0; ++i) a.final_sizes[(long long)i * a.T + t] = mine[i * kLanes];
-    int *sm = a.summary + t;
-    sm[OOB_RECONF_SURVIVED * a.T] = survived;
-    sm[OOB_RECONF_REINSTANTIATED * a.T] = sum_reinst;
-    sm[OOB_RECONF_BORROWED * a.T] = sum_borrowed;
-    sm[OOB_RECONF_MERGES * a.T] = sum_merges;
-    sm[OOB_RECONF_ALIVE * a.T] = __popcll(alive);
-    sm[OOB_RECONF_NODES * a.T] = (int)total;
-    sm[OOB_RECONF_VIOLATIONS * a.T] = viol;
-    sm[OOB_RECONF_STOP * a.T] = stop;
+    write_summary(a, t, survived, sum_reinst, sum_borrowed, sum_merges, __popcll(alive), (int)total, viol, stop);
+}
+
+// One trajectory with its sizes in registers: four list positions to a 32-bit word, one byte each, W words.  Needs at
+// most kPackedNodes = 128 nodes (a running sum of sizes then fits its byte, and (128 | r) - sum neither borrows
+// nor loses its top bit) and at most 4 W starting pipelines.
+//
+// What bounds it: the vector ALUs (about 200 instructions a step) at first, the 8 bytes a step moves next.  With the
+// sizes in LDS a step read every position twice from there and the merge, which some lane of a wave needs at almost
+// every step, walked the list position by position: 318 us for 2^20 sequences of 57 steps with 13 pipelines,
+// against 258 us here.
+constexpr unsigned kTops = 0x80808080u;
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned pk_max(unsigned x, unsigned y) {
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(u16x2, x), __builtin_bit_cast(u16x2, y)));
+}
+__device__ __forceinline__ unsigned pk_min(unsigned x, unsigned y) {
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(u16x2, x), __builtin_bit_cast(u16x2, y)));
+}
+// Bytes 0, 1 (or 2, 3) of `size` above those of `low` as two 16-bit keys.
+__device__ __forceinline__ unsigned keys01(unsigned size, unsigned low) { return __builtin_amdgcn_perm(size, low, 0x05010400u); }
+__device__ __forceinline__ unsigned keys23(unsigned size, unsigned low) { return __builtin_amdgcn_perm(size, low, 0x07030602u); }
+
+template <int W> struct Packed {
+    unsigned w[W];
+    __device__ __forceinline__ int get(int i) const {
+        unsigned v = 0; // an OR of masked words: a choice between words becomes a choice between addresses, in scratch memory
+#pragma unroll
+        for (int k = 0; k < W; ++k) v |= w[k] & (0u - (unsigned)((i >> 2) == k));
+        return (int)(v >> ((i & 3) * 8) & 255u);
+    }
+    __device__ __forceinline__ void set(int i, int value) {
+        const unsigned keep = ~(255u << ((i & 3) * 8)), put = (unsigned)value << ((i & 3) * 8);
+#pragma unroll
+        for (int k = 0; k < W; ++k) w[k] = (i >> 2) == k ? (w[k] & keep) | put : w[k];
+    }
+};
+
+template <int W> __device__ void run_in_registers(const Args &a, long long t) {
+    Packed<W> size, gone; // gone: 255 at positions that are absorbed or were never there, else 0
+    unsigned total = 0;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        size.w[k] = 0; gone.w[k] = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int i = 4 * k + b;
+            const unsigned s = i < a.c0 ? (unsigned)a.sizes0[i] : 0u;
+            size.w[k] |= s << (8 * b);
+            gone.w[k] |= i < a.c0 ? 0u : 255u << (8 * b);
+            total += s;
+        }
+    }
+    unsigned alive = (1u << a.c0) - 1; // c0 <= 16
+    const unsigned need = (unsigned)(a.f + 1) * (unsigned)a.n0; // fewer nodes: training stops
+    int stop = OOB_RECONF_STOP_NONE, viol = 0;
+    int survived = 0, sum_reinst = 0, sum_borrowed = 0, sum_merges = 0;
+    const unsigned *draw = a.draws + t;               // the draws of this trajectory, in order
+    // A step's trace word is stored and the next draw read at the head of the step that follows: the wait for the draw at its
+    // end covers the store too, and both have had a step's time by then.
+    unsigned *word = a.trace ? a.trace + t : nullptr; // where the last step's word goes
+    unsigned last = 0;
+    unsigned first = a.steps > 0 ? *draw : 0;         // this step's first draw, read a step ahead
+
+    for (int step = 0; step < a.steps; ++step) {
+        const unsigned *step_draw = draw;
+        draw += (long long)a.burst * a.T;
+        unsigned next = 0;
+        if (step + 1 < a.steps) next = *draw;
+        if (step > 0 && word) {
+            *word = last;
+            word += a.T;
+        }
+        int reinst = 0, borrowed = 0, merges = 0;
+        if (stop == OOB_RECONF_STOP_NONE) {
+            // the losses of this step
+            unsigned affected = 0;
+            for (int b = 0; b < a.burst && total > 0; ++b) {
+                const unsigned d = b ? step_draw[(long long)b * a.T] : first;
+                const unsigned r = __umulhi(d, total) | 128u; // floor(d * total / 2^32) < total, for the comparison below
+                const unsigned rs = __builtin_amdgcn_perm(r, r, 0u);
+                // The pipeline that holds node r is the first position whose running sum exceeds r: the lowest set
+                // top bit of `over`, words in order.
+                unsigned run = 0, below = 0; // running sum of the words before, in every byte; their last byte of `over`
+                int hit = 0;
+#pragma unroll
+                for (int k = 0; k < W; ++k) {
+                    unsigned p = size.w[k] + (size.w[k] << 8);
+                    p += (p << 16) + run;
+                    run = __builtin_amdgcn_perm(p, p, 0x03030303u);
+                    const unsigned over = ~(rs - p) & kTops;
+                    size.w[k] -= (over & ~(over << 8 | below >> 24)) >> 7;
+                    below = over;
+                    hit += __popc(over ^ kTops);
+                }
+                affected |= 1u << hit;
+                --total;
+            }
+            if (total < need) {
+                stop = OOB_RECONF_STOP_TOO_FEW_NODES;
+            } else {
+                // repairs, in list order
+                while (affected && stop == OOB_RECONF_STOP_NONE) {
+                    const int i = __ffs((int)affected) - 1;
+                    affected &= affected - 1;
+                    if (!((alive >> i) & 1)) continue; // absorbed by an earlier repair
+                    int si = size.get(i);
+                    if (si >= a.n0) { ++reinst; continue; }
+                    while (si < a.n0) { // borrow from the largest pipeline above n0, first of equals
+                        // one max over (size, 255 - position); position i itself is below n0 here
+                        unsigned best = 0;
+#pragma unroll
+                        for (int k = 0; k < W; ++k) {
+                            const unsigned low = 0xFCFDFEFFu - 0x04040404u * (unsigned)k;
+                            best = pk_max(best, pk_max(keys01(size.w[k], low), keys23(size.w[k], low)));
+                        }
+                        best = pk_max(best, best >> 16) & 0xFFFFu;
+                        if ((int)(best >> 8) <= a.n0) break;
+                        const int k = 255 - (int)(best & 255u);
+                        const unsigned one = 1u << ((k & 3) * 8);
+#pragma unroll
+                        for (int x = 0; x < W; ++x) size.w[x] -= (k >> 2) == x ? one : 0u;
+                        ++si;
+                        ++borrowed;
+                    }
+                    while (si < a.n0) { // absorb the smallest other pipeline, first of equals
+                        // one min over (size, position), 255 for the size of position i and of those that are gone
+                        gone.set(i, 255);
+                        unsigned best = 0xFFFFFFFFu;
+#pragma unroll
+                        for (int k = 0; k < W; ++k) {
+                            const unsigned low = 0x03020100u + 0x04040404u * (unsigned)k, s = size.w[k] | gone.w[k];
+                            best = pk_min(best, pk_min(keys01(s, low), keys23(s, low)));
+                        }
+                        best = pk_min(best, best >> 16) & 0xFFFFu;
+                        gone.set(i, 0);
+                        if ((best >> 8) == 255u) { stop = OOB_RECONF_STOP_NO_PARTNER; break; }
+                        const int j = (int)(best & 255u);
+                        si += (int)(best >> 8);
+                        size.set(j, 0);
+                        gone.set(j, 255);
+                        alive &= ~(1u << j);
+                        ++merges;
+                    }
+                    size.set(i, si);
+                    if (stop == OOB_RECONF_STOP_NONE && si > a.n_hi) viol |= 1;
+                }
+                if (stop == OOB_RECONF_STOP_NONE) {
+                    ++survived;
+                    if (__popc(alive) < a.f + 1) viol |= 2;
+                }
+            }
+            sum_reinst += reinst; sum_borrowed += borrowed; sum_merges += merges;
+        }
+        last = (unsigned)reinst | (unsigned)borrowed << 8 | (unsigned)merges << 16 |
+               (unsigned)__popc(alive) << 23 | (unsigned)stop << 30;
+        first = next;
+    }
+    if (a.steps > 0 && word) *word = last;
+
+    if (a.final_sizes)
+#pragma unroll
+        for (int i = 0; i < 4 * W; ++i)
+            if (i < a.c0) a.final_sizes[(long long)i * a.T + t] = (int)(size.w[i >> 2] >> (8 * (i & 3)) & 255u);
+    write_summary(a, t, survived, sum_reinst, sum_borrowed, sum_merges, __popc(alive), (int)total, viol, stop);
+}
+
+// W: words of packed sizes, 0 for more than 16 starting pipelines.  The number of nodes is in device memory: a list of
+// more than kPackedNodes takes the sizes in LDS, the same branch for every lane.
+template <int W> __global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
+    HIP_DYNAMIC_SHARED(unsigned short, sizes) // [rows][kLanes], rows = c0 rounded up to kUnroll
+    const long long t = (long long)blockIdx.x * kLanes + threadIdx.x;
+    const long long nodes = start_nodes(a);
+    const bool ok = nodes >= 0;
+    if (t == 0) *a.status = ok ? OOB_OK : OOB_EINVAL;
+    if (!ok || t >= a.T) return;
+    if constexpr (W > 0) {
+        if (nodes <= kPackedNodes) {
+            run_in_registers<W>(a, t);
+            return;
+        }
+    }
+    run_in_lds(a, t, sizes + threadIdx.x);
 }
 
 } // namespace oob_reconf
@@ -179,6 +361,9 @@ extern "C" int oob_reconf_simulate(const int32_t *sizes0, int c0, int n0, int n_
     a.draws = draws; a.steps = steps; a.burst = burst; a.T = T;
     a.trace = trace; a.final_sizes = final_sizes; a.summary = summary; a.status = status;
     const size_t lds = (size_t)((c0 + kUnroll - 1) / kUnroll * kUnroll) * kLanes * sizeof(unsigned short); // <= 32 KB
-    hipLaunchKernelGGL(k_reconf, dim3((unsigned)blocks), dim3(kLanes), lds, (hipStream_t)stream, a);
+    const int words = (c0 + 3) / 4;
+    const auto kernel = words == 1 ? k_reconf<1> : words == 2 ? k_reconf<2> : words == 3 ? k_reconf<3>
+                      : words == kPackedWords ? k_reconf<kPackedWords> : k_reconf<0>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kLanes), lds, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? OOB_OK : OOB_EHIP;
 }

@@ -94,6 +94,20 @@ def test_larger_specifications_every_trajectory(P):
         cases += 1
 
 
+@pytest.mark.parametrize("count", [1, 4, 5, 8, 9, 12, 13, 16, 17])
+@pytest.mark.parametrize("burst", [1, 3])
+def test_numbers_of_pipelines_and_nodes(P, count, burst):
+    """Every word count of the sizes held as bytes and one more pipeline than those hold; 128 nodes (the most they
+    take), 129 and few; the first and the last position of a word hit, lent from and absorbed."""
+    rng = np.random.Generator(np.random.PCG64(100 * count + burst))
+    for nodes in (128, 129, 3 * count):
+        n0 = max(1, nodes // count // 2)
+        sizes0 = rng.multinomial(nodes - n0 * count, np.full(count, 1 / count)) + n0
+        f = int(rng.integers(0, max(1, nodes // n0 - 1)))
+        print("case", sizes0.tolist(), n0, f, flush=True)
+        compare(P, sizes0.tolist(), n0, int(sizes0.max()), min(f, 8), inputs.failure_draws(count, nodes // burst + 1, burst, 130))
+
+
 def test_edge_cases(P):
     # no steps at all: the starting state comes back
     st, summary, final, trace = P.FailureSimulator([3, 4], 3, 5, 0, np.zeros((0, 1, 5), dtype=np.uint32)).run()
