@@ -150,7 +150,51 @@ def exact_relaxations(inp):
     reaches back over the layers whose stage time stays below tau (at most to the table's start layer q)
     and serves M - dd + 1 GPU counts -- plus the node-level recurrences.  The kernels leave out the slowest
     stages whose lower bound is above the minimum, so this is the size of the problem, not their work.
-    Returns (possible slowest stages, one-node relaxations, node-level relaxations)."""The exact minimum of the template cost for every template of the workload, under the workload's
+    Returns (possible slowest stages, one-node relaxations, node-level relaxations)."""
+    import numpy as np
+
+    L, M, n_max = inp.L, inp.gpus_per_node, inp.n_max
+    fb = (inp.fwd_ns + inp.bwd_ns).astype(np.float64)
+    forb = (inp.fwd_ns >= (1 << 62)) | (inp.bwd_ns >= (1 << 62))
+    fb[forb] = 0
+    PT = np.vstack([np.zeros((1, M)), np.cumsum(fb, axis=0)])
+    PF = np.vstack([np.zeros((1, M)), np.cumsum(forb, axis=0)])
+    PM = np.concatenate([[0], np.cumsum(inp.mem_bytes.astype(np.int64))])
+    d = np.arange(1, M + 1)
+    t0 = np.full((L + 1, L + 1, M), np.inf)  # stage time without the boundary term, inf = impossible
+    for u in range(L):
+        for v in range(u + 1, L + 1):
+            ok = (PF[v] - PF[u] == 0) & (-(-(PM[v] - PM[u]) // d) <= inp.mem_cap)
+            t0[u, v, ok] = (PT[v] - PT[u])[ok]
+    bnd = np.concatenate([[0], inp.boundary_ns.astype(np.float64)])
+    bnd[L] = 0
+    t = t0 + bnd[None, :, None]
+    uu, vv, dd = np.nonzero(np.isfinite(t))
+    taus = t[uu, vv, dd]
+    w = (M - d + 1).astype(np.float64)
+
+    def h(cnt, j):  # sum_{i=1..j} min(cnt, i): the table starts q = p-1 .. p-j against a reach of cnt layers
+        c = np.minimum(cnt, j)
+        return c * (c + 1) / 2 + c * (j - c)
+
+    pre_rows = np.zeros((len(taus), L + 1))
+    suf_rows = np.zeros((len(taus), L + 1))
+    for p in range(1, L + 1):
+        for k in range(M):
+            pre_rows[:, p] += w[k] * h(np.searchsorted(t[p - 1::-1, p, k], taus, side="left"), p)
+    for p in range(L):
+        for k in range(M):
+            suf_rows[:, p] += w[k] * h(np.searchsorted(t0[p, p + 1:, k], taus, side="right"), L - p)
+    pre = np.cumsum(pre_rows, axis=1)[np.arange(len(taus)), uu]
+    suf = np.cumsum(suf_rows[:, ::-1], axis=1)[:, ::-1][np.arange(len(taus)), vv]
+    lu, lv = uu.astype(np.float64), (L - vv).astype(np.float64)
+    node = (np.minimum(n_max, lu + 1) * (lu * (lu + 1) / 2 + (M - 1) * lu) +
+            np.minimum(n_max, lv + 1) * (lv * (lv + 1) / 2 + (M - 1) * lv))
+    return len(taus), float(pre.sum() + suf.sum()), float(node.sum())
+
+
+def bench_exact(P, planner, inp, res, reps=3):
+    """The exact minimum of the template cost for every template of the workload, under the workload's
     N_b and under N_b = 4 S (the paper's planning-time choice), and the gap of the recursion's result
     to each.  Timed with events on the stream the kernels are launched on; the oracle (all host cores)
     is timed on the same job when that takes seconds, else on a part of it."""
