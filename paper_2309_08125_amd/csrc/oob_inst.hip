@@ -50,7 +50,7 @@ __device__ __forceinline__ long long sat_add(long long a, long long b) {
 //     C(j, N', q) = sum_{i >= 0, i n <= N'} C(j-1, N' - i n, max(q - i, 0)),
 // so all entries of a plane are independent: one barrier per template size.  With IN_LDS the
 // previous and the current plane live in LDS (two planes of (N_hi+1)(Q+1) counts); otherwise
-// the previous plane is read back from the table.
+// the previous plane is read back from the table.  Used where k_inst_count_ring does not fit.
 template <bool IN_LDS>
 __global__ void __launch_bounds__(1024) k_inst_count(Spec s, long long *offsets, int *status, int keep_wide) {
     HIP_DYNAMIC_SHARED(long long, s_dyn) // IN_LDS: two planes; then reused for the prefix sum
@@ -122,6 +122,105 @@ __global__ void __launch_bounds__(1024) k_inst_count(Spec s, long long *offsets,
             s.cnt32[e] = v == 0x7FFFFFFFFFFFFFFFll ? 0xFFFFFFFFu : (unsigned)v;
         }
     if (threadIdx.x == 0) *s.narrow = narrow;
+}
+
+// The same counts where kGroup planes fit the LDS together (about 2 400 pairs (N', q); 1 290 at 128 nodes, f = 8).
+//
+// What bounds it: one workgroup's instructions and the lines that its stores touch.  Written plane by plane a count
+// is a line of its own, and the 32-bit copy was a further pass that waited for a read of memory per 1 024 counts; here
+// kGroup planes are kept and written as whole pieces of their rows, in both types at once.  The pair (N', q) of a
+// thread's entries comes from one division per thread instead of one per entry and plane.  Of the sum over i two
+// terms are added at a time (three numbers up to 2^62 stay below 2^64).
+// 56 sizes of 8..64 from a list, f = 8, up to 128 nodes: 59 us; counting and listing 217 -> 167 us as a caller sees them.
+// 29 sizes 4..32, f = 4: 21 us.
+constexpr size_t kRingLdsBytes = 152 * 1024; // beside 4 KB of sizes, of the 160 KB of a compute unit
+constexpr int kCountThreads = 1024;
+
+__global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long long *offsets, int *status, int keep_wide) {
+    HIP_DYNAMIC_SHARED(long long, s_ring) // [kGroup][plane]: plane j at slot j % kGroup
+    __shared__ int s_size[OOB_INST_MAX_P];
+    __shared__ int s_bad;
+    __shared__ unsigned long long s_max;
+    const int QQ = s.Q + 1, plane = (s.N_hi + 1) * QQ, len = s.N_hi - s.N_lo + 1;
+    if (threadIdx.x == 0) { s_bad = 0; s_max = 0; }
+    for (int j = threadIdx.x; j < s.p; j += kCountThreads) s_size[j] = size_of(s, j);
+    for (int e = threadIdx.x; e < plane; e += kCountThreads) s_ring[e] = e == 0 ? 1 : 0; // C(0, ., .)
+    __syncthreads();
+    for (int j = threadIdx.x; j < s.p; j += kCountThreads)
+        if (s_size[j] < 1 || (j > 0 && s_size[j] <= s_size[j - 1])) s_bad = 1;
+    __syncthreads();
+    if (s_bad) { // uniform: every thread leaves here
+        for (int i = threadIdx.x; i <= len; i += kCountThreads) offsets[i] = 0;
+        if (threadIdx.x == 0) { *status = OOB_EINVAL; *s.narrow = 0; }
+        return;
+    }
+    const int N0 = (int)threadIdx.x / QQ, q0 = (int)threadIdx.x - N0 * QQ;
+    const int dN = kCountThreads / QQ, dq = kCountThreads - dN * QQ; // from one entry of a thread to its next
+    unsigned long long mine = 0; // largest count of the last plane: no plane before holds a larger one
+    for (int j = 1; j <= s.p; ++j) {
+        const int n = s_size[j - 1], nq = n * QQ;
+        const long long *prev = s_ring + ((j - 1) & (kGroup - 1)) * plane;
+        long long *cur = s_ring + (j & (kGroup - 1)) * plane;
+        int N = N0, q = q0;
+        for (int e = threadIdx.x; e < plane; e += kCountThreads) {
+            unsigned long long sum = 0;
+            int Ni = N, qi = q, at = e; // at = Ni * QQ + qi
+            for (;;) {
+                const bool two = Ni >= n;
+                const int second = two ? at - nq - (qi > 0) : at;
+                const unsigned long long a = (unsigned long long)prev[at], b = (unsigned long long)prev[second];
+                sum += a + (two ? b : 0);
+                sum = sum > (unsigned long long)kSat ? (unsigned long long)kSat : sum;
+                if (Ni - n < n) break;
+                Ni -= 2 * n;
+                at = second - nq - (qi > 1);
+                qi = qi > 2 ? qi - 2 : 0;
+            }
+            cur[e] = (long long)sum;
+            if (j == s.p) mine = sum > mine ? sum : mine;
+            N += dN; q += dq;
+            if (q >= QQ) { q -= QQ; ++N; }
+        }
+        __syncthreads(); // plane j complete
+        if ((j & (kGroup - 1)) != kGroup - 1 && j != s.p) continue;
+        const int last = j & (kGroup - 1), base = j - last; // planes base..j; what follows in a row compares greater than any list position
+        for (int i = threadIdx.x; i < plane * (kGroup / 2); i += kCountThreads) {
+            const int e = i / (kGroup / 2), k = i % (kGroup / 2) * 2;
+            const bool in0 = k <= last, in1 = k + 1 <= last;
+            const long long c0 = s_ring[k * plane + e], c1 = s_ring[(k + 1) * plane + e]; // past `last`: older planes or nothing, not used
+            const long long row = (long long)e * s.R + base + k;
+            *reinterpret_cast<longlong2 *>(s.cnt + row) =
+                make_longlong2(in0 ? c0 : 0x7FFFFFFFFFFFFFFFll, in1 ? c1 : 0x7FFFFFFFFFFFFFFFll);
+            *reinterpret_cast<uint2 *>(s.cnt32 + row) = make_uint2(in0 ? (unsigned)c0 : 0xFFFFFFFFu, in1 ? (unsigned)c1 : 0xFFFFFFFFu);
+        }
+        __syncthreads(); // the next plane overwrites the first slot
+    }
+    atomicMax(&s_max, mine);
+    // exclusive prefix over N' = N_lo..N_hi of the filtered list lengths C(p, N', f+1), by the first wave
+    if (threadIdx.x < 64) {
+        const long long *whole = s_ring + (s.p & (kGroup - 1)) * plane;
+        const int lane = threadIdx.x;
+        long long run = 0;
+        for (int i0 = 0; i0 < len; i0 += 64) {
+            const int i = i0 + lane;
+            long long v = i < len ? whole[(s.N_lo + i) * QQ + s.Q] : 0;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const long long u = __shfl_up(v, d, 64);
+                v = lane >= d ? sat_add(v, u) : v;
+            }
+            const long long before = __shfl_up(v, 1, 64);
+            if (i < len) offsets[i] = lane ? sat_add(run, before) : run;
+            run = sat_add(run, __shfl(v, 63, 64));
+        }
+        if (lane == 0) {
+            offsets[len] = run;
+            *status = run >= kSat ? OOB_EOVERFLOW : OOB_OK;
+        }
+    }
+    __syncthreads();
+    // the 32-bit copy halves what a lane of the enumeration reads per comparison step
+    if (threadIdx.x == 0) *s.narrow = s_max < (1ull << 32) && !keep_wide;
 }
 
 // One lane per output vector (grid-stride).  A vector at position rho of the list of (N', q)
@@ -251,7 +350,15 @@ static int launch_count(const Spec &s, int64_t *offsets, int32_t *status, hipStr
     const int keep_wide = g_keep_wide.load();
     const size_t plane = (size_t)(s.N_hi + 1) * (s.Q + 1) * sizeof(long long);
     const size_t scan = (size_t)(s.N_hi - s.N_lo + 2) * sizeof(long long);
-    if (2 * plane <= 128 * 1024) {
+    if (kGroup * plane <= kRingLdsBytes) { // faster wherever it fits, see the kernel
+        const size_t lds = kGroup * plane;
+        if (lds > 48 * 1024 && // with the 4 KB of sizes above what a launch may ask for unannounced
+            hipFuncSetAttribute((const void *)k_inst_count_ring, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess)
+            return OOB_EHIP;
+        hipLaunchKernelGGL(k_inst_count_ring, dim3(1), dim3(kCountThreads), lds, stream, s, (long long *)offsets, status,
+                           keep_wide);
+    } else if (2 * plane <= 128 * 1024) {
         const size_t lds = 2 * plane > scan ? 2 * plane : scan;
         if (lds > 64 * 1024 &&
             hipFuncSetAttribute((const void *)k_inst_count<true>, hipFuncAttributeMaxDynamicSharedMemorySize,

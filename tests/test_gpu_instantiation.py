@@ -135,3 +135,31 @@ def test_capacity_larger_than_total_leaves_the_tail_untouched(P):
     assert int(inst.status.item()) == P.OOB_OK
     assert h[:, :5].T.tolist() == [[5, 1, 0], [2, 3, 0], [3, 1, 1], [0, 3, 1], [1, 1, 2]]
     assert (h[:, 5:] == 7777).all()
+
+
+@pytest.mark.parametrize("p,N_hi,f", [(1, 0, 0), (1, 1215, 0), (7, 1215, 0), (8, 1215, 0), (9, 1216, 0), (16, 242, 8), (15, 243, 8),
+                                      (23, 127, 17), (24, 128, 17)])
+def test_count_table_at_the_edges_of_its_lds(P, p, N_hi, f):
+    """8 planes of (N_hi + 1) (f + 2) counts fit 152 KB up to 2 432 of them; planes are written in groups of 8."""
+    step = max(1, N_hi // 40)
+    sizes = [3 + step * (j + 1) for j in range(p)]
+    print(f"p {p} N_hi {N_hi} f {f}", flush=True)
+    compare(P, sizes, max(0, N_hi - 70), N_hi, f)
+
+
+@pytest.mark.parametrize("N_hi,p,f", [(200, 200, 8), (300, 61, 3), (600, 600, 2), (1000, 40, 0)])
+def test_list_lengths_beyond_32_bits(P, N_hi, p, f):
+    """Lengths (no list is enumerated) against the recurrence of the count in Python integers."""
+    C = [[0] * (f + 2) for _ in range(N_hi + 1)]
+    C[0][0] = 1
+    for n in range(1, p + 1):
+        for x in range(n, N_hi + 1):
+            C[x] = [C[x][q] + C[x - n][max(q - 1, 0)] for q in range(f + 2)]
+    N_lo = max(0, N_hi - 150)
+    want = [0]
+    for x in range(N_lo, N_hi + 1):
+        want.append(want[-1] + C[x][f + 1])
+    assert want[-1] > 1 << 32
+    off, st = P.Instantiator(None, N_lo, N_hi, f, n0=1, p=p).count()
+    assert off.tolist() == [min(w, 1 << 62) for w in want]
+    assert st == (P.OOB_OK if want[-1] < 1 << 62 else P.OOB_EOVERFLOW)
