@@ -128,98 +128,143 @@ __global__ void __launch_bounds__(1024) k_inst_count(Spec s, long long *offsets,
 //
 // What bounds it: one workgroup's instructions and the lines that its stores touch.  Written plane by plane a count
 // is a line of its own, and the 32-bit copy was a further pass that waited for a read of memory per 1 024 counts; here
-// kGroup planes are kept and written as whole pieces of their rows, in both types at once.  The pair (N', q) of a
-// thread's entries comes from one division per thread instead of one per entry and plane.  Of the sum over i two
-// terms are added at a time (three numbers up to 2^62 stay below 2^64).
-// 56 sizes of 8..64 from a list, f = 8, up to 128 nodes: 59 us; counting and listing 217 -> 167 us as a caller sees them.
-// 29 sizes 4..32, f = 4: 21 us.
+// kGroup planes are kept and written as whole pieces of their rows.  The pair (N', q) of a thread's entries comes
+// from one division per thread instead of one per entry and plane.  The planes are counted in 32 bits with
+// saturating additions first; only where that saturates (or the 64-bit table is asked for) they are counted
+// again in 64 bits, which writes both tables.
+// 56 sizes of 8..64 from a list, f = 8, up to 128 nodes: 44 us, 59 us with 64 bits throughout; counting and listing
+// 217 -> 152 us as a caller sees them.  29 sizes 4..32, f = 4: 17 us, 21 us with 64 bits.
 constexpr size_t kRingLdsBytes = 152 * 1024; // beside 4 KB of sizes, of the 160 KB of a compute unit
 constexpr int kCountThreads = 1024;
+static_assert(kGroup == 8, "a row's piece is stored as two or four vectors");
 
-__global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long long *offsets, int *status, int keep_wide) {
-    HIP_DYNAMIC_SHARED(long long, s_ring) // [kGroup][plane]: plane j at slot j % kGroup
-    __shared__ int s_size[OOB_INST_MAX_P];
-    __shared__ int s_bad;
-    __shared__ unsigned long long s_max;
-    const int QQ = s.Q + 1, plane = (s.N_hi + 1) * QQ, len = s.N_hi - s.N_lo + 1;
-    if (threadIdx.x == 0) { s_bad = 0; s_max = 0; }
-    for (int j = threadIdx.x; j < s.p; j += kCountThreads) s_size[j] = size_of(s, j);
-    for (int e = threadIdx.x; e < plane; e += kCountThreads) s_ring[e] = e == 0 ? 1 : 0; // C(0, ., .)
-    __syncthreads();
-    for (int j = threadIdx.x; j < s.p; j += kCountThreads)
-        if (s_size[j] < 1 || (j > 0 && s_size[j] <= s_size[j - 1])) s_bad = 1;
-    __syncthreads();
-    if (s_bad) { // uniform: every thread leaves here
-        for (int i = threadIdx.x; i <= len; i += kCountThreads) offsets[i] = 0;
-        if (threadIdx.x == 0) { *status = OOB_EINVAL; *s.narrow = 0; }
-        return;
-    }
+// Two terms more, saturating: at 2^32 - 1, or at 2^62 (three numbers up to 2^62 stay below 2^64).
+__device__ __forceinline__ unsigned add_terms(unsigned sum, unsigned a, unsigned b) {
+    return __builtin_elementwise_add_sat(__builtin_elementwise_add_sat(sum, a), b);
+}
+__device__ __forceinline__ unsigned long long add_terms(unsigned long long sum, unsigned long long a, unsigned long long b) {
+    const unsigned long long c = sum + a + b;
+    return c > (unsigned long long)kSat ? (unsigned long long)kSat : c;
+}
+
+// All planes of the table in CT; the last one stays in the ring.  Returns the largest count of this thread's entries of
+// the last plane (no plane before holds a larger one).  Called and left by the whole workgroup.
+template <typename CT> __device__ CT count_planes(const Spec &s, CT *ring, const int *size) {
+    const int QQ = s.Q + 1, plane = (s.N_hi + 1) * QQ;
     const int N0 = (int)threadIdx.x / QQ, q0 = (int)threadIdx.x - N0 * QQ;
     const int dN = kCountThreads / QQ, dq = kCountThreads - dN * QQ; // from one entry of a thread to its next
-    unsigned long long mine = 0; // largest count of the last plane: no plane before holds a larger one
+    for (int e = threadIdx.x; e < plane; e += kCountThreads) ring[e] = e == 0 ? 1 : 0; // C(0, ., .)
+    __syncthreads();
+    CT mine = 0;
     for (int j = 1; j <= s.p; ++j) {
-        const int n = s_size[j - 1], nq = n * QQ;
-        const long long *prev = s_ring + ((j - 1) & (kGroup - 1)) * plane;
-        long long *cur = s_ring + (j & (kGroup - 1)) * plane;
+        const int n = size[j - 1], nq = n * QQ;
+        const CT *prev = ring + ((j - 1) & (kGroup - 1)) * plane;
+        CT *cur = ring + (j & (kGroup - 1)) * plane;
         int N = N0, q = q0;
         for (int e = threadIdx.x; e < plane; e += kCountThreads) {
-            unsigned long long sum = 0;
+            CT sum = 0;
             int Ni = N, qi = q, at = e; // at = Ni * QQ + qi
             for (;;) {
                 const bool two = Ni >= n;
                 const int second = two ? at - nq - (qi > 0) : at;
-                const unsigned long long a = (unsigned long long)prev[at], b = (unsigned long long)prev[second];
-                sum += a + (two ? b : 0);
-                sum = sum > (unsigned long long)kSat ? (unsigned long long)kSat : sum;
+                const CT c0 = prev[at], c1 = prev[second];
+                sum = add_terms(sum, c0, two ? c1 : (CT)0);
                 if (Ni - n < n) break;
                 Ni -= 2 * n;
                 at = second - nq - (qi > 1);
                 qi = qi > 2 ? qi - 2 : 0;
             }
-            cur[e] = (long long)sum;
+            cur[e] = sum;
             if (j == s.p) mine = sum > mine ? sum : mine;
             N += dN; q += dq;
             if (q >= QQ) { q -= QQ; ++N; }
         }
         __syncthreads(); // plane j complete
-        if ((j & (kGroup - 1)) != kGroup - 1 && j != s.p) continue;
-        const int last = j & (kGroup - 1), base = j - last; // planes base..j; what follows in a row compares greater than any list position
-        for (int i = threadIdx.x; i < plane * (kGroup / 2); i += kCountThreads) {
-            const int e = i / (kGroup / 2), k = i % (kGroup / 2) * 2;
-            const bool in0 = k <= last, in1 = k + 1 <= last;
-            const long long c0 = s_ring[k * plane + e], c1 = s_ring[(k + 1) * plane + e]; // past `last`: older planes or nothing, not used
-            const long long row = (long long)e * s.R + base + k;
-            *reinterpret_cast<longlong2 *>(s.cnt + row) =
-                make_longlong2(in0 ? c0 : 0x7FFFFFFFFFFFFFFFll, in1 ? c1 : 0x7FFFFFFFFFFFFFFFll);
-            *reinterpret_cast<uint2 *>(s.cnt32 + row) = make_uint2(in0 ? (unsigned)c0 : 0xFFFFFFFFu, in1 ? (unsigned)c1 : 0xFFFFFFFFu);
+        const int last = j & (kGroup - 1), base = j - last;
+        if (last != kGroup - 1 && j != s.p) continue;
+        // planes base..j; what follows in a row compares greater than any list position (slots past `last` hold older
+        // planes or nothing: read, not used)
+        if constexpr (sizeof(CT) == 4) {
+            for (int i = threadIdx.x; i < plane * 2; i += kCountThreads) {
+                const int e = i >> 1, k = (i & 1) * 4;
+                const CT *c = ring + k * plane + e;
+                uint4 v = make_uint4(c[0], c[plane], c[2 * plane], c[3 * plane]);
+                v.x = k <= last ? v.x : 0xFFFFFFFFu;
+                v.y = k + 1 <= last ? v.y : 0xFFFFFFFFu;
+                v.z = k + 2 <= last ? v.z : 0xFFFFFFFFu;
+                v.w = k + 3 <= last ? v.w : 0xFFFFFFFFu;
+                *reinterpret_cast<uint4 *>(s.cnt32 + (long long)e * s.R + base + k) = v;
+            }
+        } else {
+            for (int i = threadIdx.x; i < plane * 4; i += kCountThreads) {
+                const int e = i >> 2, k = (i & 3) * 2;
+                const CT c0 = ring[k * plane + e], c1 = ring[(k + 1) * plane + e];
+                const bool in0 = k <= last, in1 = k + 1 <= last;
+                const long long row = (long long)e * s.R + base + k;
+                *reinterpret_cast<ulonglong2 *>(s.cnt + row) =
+                    make_ulonglong2(in0 ? c0 : 0x7FFFFFFFFFFFFFFFull, in1 ? c1 : 0x7FFFFFFFFFFFFFFFull);
+                *reinterpret_cast<uint2 *>(s.cnt32 + row) = make_uint2(in0 ? (unsigned)c0 : 0xFFFFFFFFu, in1 ? (unsigned)c1 : 0xFFFFFFFFu);
+            }
         }
         __syncthreads(); // the next plane overwrites the first slot
     }
-    atomicMax(&s_max, mine);
-    // exclusive prefix over N' = N_lo..N_hi of the filtered list lengths C(p, N', f+1), by the first wave
-    if (threadIdx.x < 64) {
-        const long long *whole = s_ring + (s.p & (kGroup - 1)) * plane;
-        const int lane = threadIdx.x;
-        long long run = 0;
-        for (int i0 = 0; i0 < len; i0 += 64) {
-            const int i = i0 + lane;
-            long long v = i < len ? whole[(s.N_lo + i) * QQ + s.Q] : 0;
+    return mine;
+}
+
+// Exclusive prefix over N' = N_lo..N_hi of the filtered list lengths C(p, N', f+1), by one wave.
+template <typename CT> __device__ void write_offsets(const Spec &s, const CT *ring, long long *offsets, int *status) {
+    const int QQ = s.Q + 1, len = s.N_hi - s.N_lo + 1, lane = threadIdx.x;
+    const CT *whole = ring + (s.p & (kGroup - 1)) * (s.N_hi + 1) * QQ;
+    long long run = 0;
+    for (int i0 = 0; i0 < len; i0 += 64) {
+        const int i = i0 + lane;
+        long long v = i < len ? (long long)whole[(s.N_lo + i) * QQ + s.Q] : 0;
 #pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const long long u = __shfl_up(v, d, 64);
-                v = lane >= d ? sat_add(v, u) : v;
-            }
-            const long long before = __shfl_up(v, 1, 64);
-            if (i < len) offsets[i] = lane ? sat_add(run, before) : run;
-            run = sat_add(run, __shfl(v, 63, 64));
+        for (int d = 1; d < 64; d <<= 1) {
+            const long long u = __shfl_up(v, d, 64);
+            v = lane >= d ? sat_add(v, u) : v;
         }
-        if (lane == 0) {
-            offsets[len] = run;
-            *status = run >= kSat ? OOB_EOVERFLOW : OOB_OK;
+        const long long before = __shfl_up(v, 1, 64);
+        if (i < len) offsets[i] = lane ? sat_add(run, before) : run;
+        run = sat_add(run, __shfl(v, 63, 64));
+    }
+    if (lane == 0) {
+        offsets[len] = run;
+        *status = run >= kSat ? OOB_EOVERFLOW : OOB_OK;
+    }
+}
+
+__global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long long *offsets, int *status, int keep_wide) {
+    HIP_DYNAMIC_SHARED(unsigned long long, s_ring) // [kGroup][plane]: plane j at slot j % kGroup
+    __shared__ int s_size[OOB_INST_MAX_P];
+    __shared__ int s_bad;
+    __shared__ unsigned long long s_max;
+    __shared__ unsigned s_max32;
+    if (threadIdx.x == 0) { s_bad = 0; s_max = 0; s_max32 = 0; }
+    for (int j = threadIdx.x; j < s.p; j += kCountThreads) s_size[j] = size_of(s, j);
+    __syncthreads();
+    for (int j = threadIdx.x; j < s.p; j += kCountThreads)
+        if (s_size[j] < 1 || (j > 0 && s_size[j] <= s_size[j - 1])) s_bad = 1;
+    __syncthreads();
+    if (s_bad) { // uniform: every thread leaves here
+        const int len = s.N_hi - s.N_lo + 1;
+        for (int i = threadIdx.x; i <= len; i += kCountThreads) offsets[i] = 0;
+        if (threadIdx.x == 0) { *status = OOB_EINVAL; *s.narrow = 0; }
+        return;
+    }
+    if (!keep_wide) {
+        unsigned *ring = reinterpret_cast<unsigned *>(s_ring);
+        atomicMax(&s_max32, count_planes(s, ring, s_size));
+        __syncthreads();
+        if (s_max32 != 0xFFFFFFFFu) { // uniform: no addition saturated
+            if (threadIdx.x < 64) write_offsets(s, ring, offsets, status);
+            if (threadIdx.x == 0) *s.narrow = 1;
+            return;
         }
     }
+    atomicMax(&s_max, count_planes(s, s_ring, s_size));
     __syncthreads();
-    // the 32-bit copy halves what a lane of the enumeration reads per comparison step
+    if (threadIdx.x < 64) write_offsets(s, s_ring, offsets, status);
     if (threadIdx.x == 0) *s.narrow = s_max < (1ull << 32) && !keep_wide;
 }
 
