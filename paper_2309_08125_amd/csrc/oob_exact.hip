@@ -23,9 +23,9 @@
 //   k_exact_filter        keeps those whose bound does not exceed what was found;
 //   k_exact_eval<kRest>   evaluates these exactly, looking at the bounds again as the minima fall.
 // Small jobs (kDirectMax) skip the bounds and evaluate every stage but those too dear by their time alone.
-// Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.80 ms (1 400 of 17 524 slowest stages
+// Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.85 ms (1 400 of 17 524 slowest stages
 // evaluated); 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 69 us; 48 layers, 8 GPUs per node, N_b = 20 with
-// the limit binding 38.0 -> 2.7 ms (the evaluation of every stage in tables of the workspace before).
+// the limit binding 38.0 -> 2.7-4.0 ms by the instance (the evaluation of every stage in tables of the workspace before).
 //
 // k_exact_eval: one workgroup per slowest stage, everything in LDS, times as exact integers in doubles.
 // Phase 1, per wave, no workgroup barrier: the one-node table of start layer q, G_q[r][g] = least cost
@@ -411,7 +411,7 @@ __device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int p, int 
 // GPUs and at most S_max stages are used, whatever the prices.  The bound is the largest over the
 // multipliers.  Row after row of the two paths; a wave takes two lambdas, thirty-two lanes each share out the
 // starts of the last stage, eight GPU counts side by side.  Bound by the chain of rows (LDS read, reduction over the
-// lanes, LDS write per row) at one workgroup per bucket: 183 us at 98 layers x 8 GPUs, 274 buckets.
+// lanes, LDS write per row) at one workgroup per bucket: 175 us at 98 layers x 8 GPUs, 274 buckets.
 // ---------------------------------------------------------------------------------------------
 __device__ const double kLambdaGiven[kLambdas] = {0, 0.04, 0.1, 0.2, 0.4, 0.8, 1.6, 3.5}; // more nodes pay (C falls with n) ...
 __device__ const double kLambda4S[kLambdas] = {0, -0.06, -0.14, -0.25, -0.43, -0.7, -1.3, -3.5}; // ... or cost
@@ -630,8 +630,8 @@ __global__ void __launch_bounds__(256) k_exact_filter(Args a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact evaluation.  Bound by the latency of dependent LDS reads on the rows of the one-node tables: 171 us for the
-// first picks and 446 us for the rest at 98 layers x 8 GPUs (the version before, without a band and evaluating
+// Exact evaluation.  Bound by the latency of dependent LDS reads on the rows of the one-node tables: 160 us for the
+// first picks and 490 us for the rest at 98 layers x 8 GPUs (the version before, without a band and evaluating
 // everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table entry: 1, or S_max + 1 (STAGED).
 // ---------------------------------------------------------------------------------------------
 struct Eval {

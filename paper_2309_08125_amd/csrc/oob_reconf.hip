@@ -163,7 +163,7 @@ __device__ void run_in_lds(const Args &a, long long t, unsigned short *mine) {
 // most kPackedNodes = 128 nodes (a running sum of sizes then fits its byte, and (128 | r) - sum neither borrows
 // nor loses its top bit) and at most 4 W starting pipelines.
 //
-// What bounds it: the vector ALUs (about 200 instructions a step) at first, the 8 bytes a step moves next.  With the
+// What bounds it: the vector ALUs (176 instructions a wave and step) at first, the 8 bytes a step moves next.  With the
 // sizes in LDS a step read every position twice from there and the merge, which some lane of a wave needs at almost
 // every step, walked the list position by position: 318 us for 2^20 sequences of 57 steps with 13 pipelines,
 // against 258 us here.
