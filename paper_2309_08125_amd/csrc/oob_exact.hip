@@ -46,6 +46,7 @@
 #include <type_traits>
 
 #include "oob_exact.h"
+#include "oob_exact_sizes.h"
 #include "oob_layout.h"
 
 namespace oob_exact {
@@ -266,7 +267,8 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
     wg_sync();
     int total = 0;
     if (st == OOB_OK && narrow) { // list the possible slowest stages by time
-        const int kmin = (int)(s_min >> 44), inv = 65536 / M + 1;
+        const int kmin = (int)(s_min >> 44);
+        const unsigned inv = recip(M);
         for (int pass = 0; pass < 2; ++pass) {
             for (int v = 1 + wave; v <= L; v += nw) { // a wave takes the stages that end at layer v
                 const long long x = v < L ? bnd[v - 1] : 0;
@@ -276,7 +278,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int i = i0 + 64 * q, ic = i < v * M ? i : 0;
-                        const int u = (int)((unsigned)(ic * inv) >> 16), d = ic - u * M; // i / M: exact below 2^14 for M <= 64
+                        const int u = quot(ic, inv), d = ic - u * M;
                         const bool ok = (i < v * M) & (u >= s_lf[v * M + d]);
                         tau[q] = (double)(s_pt[v * M + d] - s_pt[ic] + x);
                         ud[q] = u | (d + 1) << 16;
@@ -936,9 +938,9 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     if (threadIdx.x < 2) e.ints[threadIdx.x] = 0;
     wg_sync();
     int mostP = 0, mostS = 0;
-    const int inv = 65536 / M + 1; // i / M = i inv >> 16, exact below 2^14
+    const unsigned inv = recip(M);
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
-        const int p = (int)((unsigned)(i * inv) >> 16), dd = i - p * M + 1;
+        const int p = quot(i, inv), dd = i - p * M + 1;
         int r = p;
         if (p >= 1 && p <= u) { r = reach_back<true>(e.pr, M, p, dd, tau); mostP = imax(mostP, (p - r) * M / dd); }
         else if (p >= v && p < L) { r = reach_on(e.pr, L, M, p, dd, tau); mostS = imax(mostS, (r - p) * M / dd); }

@@ -222,3 +222,17 @@ def test_jobs_large_enough_for_bounds(P, shape):
         st, got = P.ExactMinimum(inp, staged=staged).run()
         want = E.exact_minimum_staged(inp) if staged else E.exact_minimum(inp)
         assert st == P.OOB_OK and got == want, (shape, var)
+
+
+@pytest.mark.parametrize("shape", [(74, 31, 1, 2, 0), (66, 32, 1, 2, 66), (46, 48, 1, 2, 0), (30, 60, 1, 2, 30), (20, 64, 1, 2, 0),
+                                   (26, 64, 1, 1, 0)])
+def test_many_gpus_per_node_with_tables_in_lds(P, shape):
+    """Indices (layer, GPU count) beyond 2^16 / M, tables in LDS (a small workspace)."""
+    L, M, n_min, n_max, nb = shape
+    assert P.oob_exact_workspace_size(L, n_max, M) < (16 << 20)
+    for var in ("plain", "tight", "forbid"):
+        inp = inputs.random_small(13, L, M, n_min, n_max, nb, f=1, tight_mem=(var == "tight"),
+                                  forbid_some_d=(var == "forbid"))
+        print("case", shape, var, flush=True)
+        st, got = P.ExactMinimum(inp).run()
+        assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
