@@ -60,11 +60,8 @@ constexpr long long kForbidden = 1ll << 62;
 constexpr long long kDoubleExact = 1ll << 52;
 constexpr double kNone = __builtin_huge_val();
 constexpr unsigned long long kNoneBits = 0x7FF0000000000000ull;
-constexpr size_t kLdsLimit = 160 * 1024;
 
 constexpr int kPrepThreads = 1024, kBins = 4096;
-constexpr int kEvalThreads = 512;    // two workgroups per compute unit where LDS allows
-constexpr int kStagedThreads = 1024; // with stage counts: one, it needs all the LDS
 constexpr int kBoundThreads = 576;   // eight waves for the paths, one for the fewest nodes
 // No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second
 // evaluation take 70 us or more whatever the job, what evaluating some thousand stages of a short model takes.
@@ -94,16 +91,13 @@ struct Args {
     float *blb;           // [nbuckets][count] smallest bound of a bucket
     unsigned short *barg; // [nbuckets][count] and the entry it belongs to, from the first of the bucket
     unsigned *list;       // [ncand] entries left to evaluate
-    unsigned *over;       // [ncand] entries that k_exact_flat has to evaluate (tables beyond LDS)
+    unsigned *over;       // [ncand] entries that k_exact_flat has to evaluate (tables with stage counts beyond LDS)
     long long *slots;     // k_exact_flat: [slots][2][(L+1)][(Dmax+1)][J]
     unsigned long long *best; // per template: smallest cost so far
     int *status;
 };
 
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
-__host__ __device__ inline size_t tri(int L) { return (size_t)L * (L + 1) / 2; }
-__host__ __device__ inline int imin(int a, int b) { return a < b ? a : b; }
-__host__ __device__ inline int imax(int a, int b) { return a > b ? a : b; }
 
 // ---- what one workgroup's last act is: hand the minima to the caller ------------------------------
 // Results as int64: -1 where no pipeline exists, -2 (unstaged entry point) where the stage limit
@@ -363,7 +357,6 @@ __device__ __forceinline__ double row_below(double x) {
 // The profile in LDS: PT[l M + d-1] prefix sums, PX = PT plus the boundary term of a stage ending at layer l,
 // X the boundary terms, flo as in Args.
 struct Prof { double *PT, *PX, *X; unsigned char *flo; };
-__host__ __device__ inline size_t prof_doubles(int L, int M) { return 2 * (size_t)(L + 1) * M + (L + 1) + ((size_t)(L + 1) * M + 7) / 8; }
 __device__ __forceinline__ Prof load_prof(const Args &a, double *lds) {
     const int W = a.L + 1, n = W * a.M;
     Prof p;
@@ -640,7 +633,7 @@ struct Eval {
     Prof pr;
     unsigned char *reach; // [(L+1) M] of a stage into a layer p <= u / out of a layer p >= v
     double *pool;         // GU, W, then the waves' one-node tables
-    size_t pool_n;
+    long long pool_n;
     double *GU;           // [two sides][band][M, or staged_row(M)] covers next to the slowest stage, by the distance covered
     double *NP;           // [2 buffers][len+1 of both sides][J]
     double *OUT;          // [two sides][nodes][M][J] a whole nodes and g more GPUs
@@ -651,11 +644,6 @@ __host__ __device__ inline int staged_col(int g, int j) { return g * (g - 1) / 2
 __host__ __device__ inline int staged_row(int M) { return M * (M + 1) / 2 + 1; }
 // Entry (r, j) of a band matrix with rows r = 1 .. and columns 0 .. len - r.
 __device__ __forceinline__ int band_index(int r, int j, int len) { return (r - 1) * len - (r - 1) * (r - 2) / 2 + j; }
-__host__ __device__ inline size_t band_size(int band, int len) { return (size_t)band * len - (size_t)band * (band - 1) / 2; }
-
-__host__ __device__ inline size_t eval_fixed(int L, int M, int n_max, int J) {
-    return prof_doubles(L, M) + ((size_t)(L + 1) * M + 7) / 8 + 2 * (size_t)(L + 2) * J + 2 * (size_t)n_max * M * J + 8;
-}
 // One-node tables of a side (this wave's share): start positions idx = first .. in side coordinates (layers
 // from the far end of the side), rows r = layers covered.  Lanes = (start, part of the walk, GPUs g); with stage
 // counts the lanes that would share a walk out hold the counts j = 1 .. M instead.  A row takes the stages that
@@ -962,7 +950,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     // start layer (nodes against layers per node), and the covers next to the slowest stage are their last rows
     {
         const int nd = imax(cendP, cendS) * M, jd = STAGED ? imin(J, nd + 1) : 1;
-        const size_t need = ((size_t)lenP + 1 + lenS + 1) * nd * jd;
+        const long long need = ((long long)lenP + 1 + lenS + 1) * nd * jd;
         if (nhi * 4 <= imax(bandP, bandS) && need <= e.pool_n) {
             const int row_n = nd * jd;
             const int second = (lenP + 1) * row_n; // the other side's table
@@ -992,8 +980,8 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     const size_t gu = STAGED ? row_n : M;
     e.GU = e.pool;
     double *WP = e.GU + (bandP + bandS) * gu, *WS = WP + band_size(bandP, lenP) * mult, *G = WS + band_size(bandS, lenS) * mult;
-    const size_t used = (size_t)(G - e.pool), table = (size_t)(imax(bandP, bandS) + 1) * row_n;
-    if (used + table > e.pool_n) return false;
+    const long long used = G - e.pool, table = (long long)(imax(bandP, bandS) + 1) * row_n;
+    if (used + table > e.pool_n) return false; // (without stage counts they fit: eval_pool())
     const int fit = (int)((e.pool_n - used) / table); // one-node tables side by side
     // ---- phase 1
     {
@@ -1021,7 +1009,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
         }
     }
     // ---- phase 2: node after node, both sides at once.  Narrow bands: one wave each
-    const size_t histP = (size_t)cendP * (bandP + 1), histS = (size_t)cendS * (bandS + 1);
+    const long long histP = (long long)cendP * (bandP + 1), histS = (long long)cendS * (bandS + 1);
     if (!STAGED && imax(bandP, bandS) <= kChainBand && imax(lenP, lenS) <= kChainLen && used + histP + histS <= e.pool_n) {
         double *HP = G; // (in place of the one-node tables)
         wg_sync();
@@ -1071,7 +1059,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     e.NP = p;     p += 2 * (size_t)(L + 2) * J;
     e.OUT = p; p += 2 * (size_t)a.n_max * M * J;
     unsigned long long *s_best = (unsigned long long *)p; p += count;
-    e.pool = p; e.pool_n = (size_t)(lds_doubles - (p - s_dyn));
+    e.pool = p; e.pool_n = lds_doubles - (p - s_dyn);
     e.ints = s_ints;
     for (int i = tid; i < count; i += blockDim.x) s_best[i] = kNoneBits;
     const unsigned total = mode == kRest ? a.head->alive : a.head->ncand;
@@ -1135,7 +1123,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
             }
         }
         if (!evaluate<STAGED, MT>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
-            if (tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
+            if (STAGED && tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
             continue;
         }
         if (mode != kFirst) { // let the other workgroups know
@@ -1285,30 +1273,10 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
 
 inline size_t slot_bytes(int L, int Dmax, int J) { return align_up(sizeof(long long) * 2 * (size_t)(L + 1) * (Dmax + 1) * J); }
 
-// Threads of k_exact_eval: a wave takes 64 / M start layers at a time, two rounds of them.
-inline int eval_threads(int L, int M, bool staged) {
-    if (staged) return kStagedThreads;
-    int slots = 64, waves = 4;
-    while (slots > 1 && 64 / slots < M) slots >>= 1;
-    while (waves < kEvalThreads / 64 && waves * slots * 2 < L) waves *= 2;
-    return waves * 64;
-}
-// LDS of k_exact_eval in bytes: without stage counts the tables of any slowest stage fit (0: they do not, the
-// shape takes the general path); with stage counts whatever is left for them, entries beyond that take
-// the general path one by one.
-inline size_t eval_lds(int L, int M, int n_max, int J, bool staged) {
-    const size_t fixed = 8 * (eval_fixed(L, M, n_max, J) + n_max);
-    if (staged) return M <= 8 && fixed + 48 * 1024 <= kLdsLimit - 512 ? kLdsLimit - 512 : 0;
-    const size_t all = fixed + 8 * (tri(L) + (size_t)L * M + (size_t)(L + 1) * (M + 1));
-    if (all > kLdsLimit - 512) return 0;
-    // as many workgroups per compute unit as the registers allow (sixteen waves)
-    const size_t most = 1024 / eval_threads(L, M, false), k = (kLdsLimit - 512) / all;
-    return ((kLdsLimit / (k < most ? k : most) - 512) & ~(size_t)15);
-}
 inline int bound_mus(int L, int M, bool staged) {
     int mus = staged ? kMus : 1;
-    while (mus > 1 && 8 * bound_doubles(L, M, mus) > kLdsLimit - 512) --mus;
-    return 8 * bound_doubles(L, M, mus) <= kLdsLimit - 512 ? mus : 0;
+    while (mus > 1 && 8 * bound_doubles(L, M, mus) > kLdsLimit - kLdsStatic) --mus;
+    return 8 * bound_doubles(L, M, mus) <= kLdsLimit - kLdsStatic ? mus : 0;
 }
 struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blo, bfew, blb, barg, list, over, slots; };
 inline Layout layout(int L, int M, int n_max, bool fast, int mus, bool staged) { // mus: of the stage limit, 0: no bounds

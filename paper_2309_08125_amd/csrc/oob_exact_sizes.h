@@ -1,6 +1,8 @@
-// Index arithmetic of the exact minimum (oob_exact.hip) that the host can check over everything the entry points
+// Index arithmetic and LDS layout of the exact minimum (oob_exact.hip) that the host can check over everything the entry points
 // accept: plain C++, so that a CPU test compiles it too.
 #pragma once
+
+#include <stddef.h>
 
 #ifdef __HIPCC__
 #define OOB_HD __host__ __device__
@@ -16,5 +18,49 @@ namespace oob_exact {
 constexpr int kRecipShift = 20;
 OOB_HD inline unsigned recip(int M) { return (1u << kRecipShift) / (unsigned)M + 1; }
 OOB_HD inline int quot(int i, unsigned recip_M) { return (int)((unsigned)i * recip_M >> kRecipShift); }
+
+constexpr size_t kLdsLimit = 160 * 1024;
+constexpr size_t kLdsStatic = 512;   // left to the kernels' own static arrays
+constexpr int kEvalThreads = 512;    // two workgroups per compute unit where LDS allows
+constexpr int kStagedThreads = 1024; // with stage counts: one, it needs all the LDS
+
+OOB_HD inline size_t tri(int L) { return (size_t)L * (L + 1) / 2; }
+OOB_HD inline int imin(int a, int b) { return a < b ? a : b; }
+OOB_HD inline int imax(int a, int b) { return a > b ? a : b; }
+
+// The profile in LDS (see Prof), in doubles.
+OOB_HD inline size_t prof_doubles(int L, int M) { return 2 * (size_t)(L + 1) * M + (L + 1) + ((size_t)(L + 1) * M + 7) / 8; }
+// Entries of a band matrix with rows r = 1 .. band and columns 0 .. len - r.
+OOB_HD inline size_t band_size(int band, int len) { return (size_t)band * len - (size_t)band * (band - 1) / 2; }
+
+// Tables of k_exact_eval beside its pool and the minima: profile, reach, NP and OUT (see Eval), in doubles.
+OOB_HD inline size_t eval_fixed(int L, int M, int n_max, int J) {
+    return prof_doubles(L, M) + ((size_t)(L + 1) * M + 7) / 8 + 2 * (size_t)(L + 2) * J + 2 * (size_t)n_max * M * J + 8;
+}
+// Its pool for any slowest stage without stage counts, in doubles: the covers next to it, both W and one one-node table,
+// bands as wide as the sides are long.
+OOB_HD inline size_t eval_pool(int L, int M) { return tri(L) + (size_t)L * M + (size_t)(L + 1) * (M + 1); }
+
+// Threads of k_exact_eval: a wave takes 64 / M start layers at a time, two rounds of them.
+inline int eval_threads(int L, int M, bool staged) {
+    if (staged) return kStagedThreads;
+    int slots = 64, waves = 4;
+    while (slots > 1 && 64 / slots < M) slots >>= 1;
+    while (waves < kEvalThreads / 64 && waves * slots * 2 < L) waves *= 2;
+    return waves * 64;
+}
+// LDS of k_exact_eval in bytes: without stage counts the tables of any slowest stage fit (0: they do not, the
+// shape takes the general path); with stage counts whatever is left for them, entries beyond that take
+// the general path one by one.
+inline size_t eval_lds(int L, int M, int n_max, int J, bool staged) {
+    const size_t fixed = 8 * (eval_fixed(L, M, n_max, J) + n_max);
+    if (staged) return M <= 8 && fixed + 48 * 1024 <= kLdsLimit - kLdsStatic ? kLdsLimit - kLdsStatic : 0;
+    const size_t all = (fixed + 8 * eval_pool(L, M) + 15) & ~(size_t)15;
+    if (all + kLdsStatic > kLdsLimit) return 0;
+    // as many workgroups per compute unit as the registers allow (sixteen waves) and their tables leave room for: a share
+    // less its static arrays is never below `all`
+    const size_t most = 1024 / eval_threads(L, M, false), k = kLdsLimit / (all + kLdsStatic);
+    return (kLdsLimit / (k < most ? k : most) - kLdsStatic) & ~(size_t)15;
+}
 
 } // namespace oob_exact

@@ -236,3 +236,15 @@ def test_many_gpus_per_node_with_tables_in_lds(P, shape):
         print("case", shape, var, flush=True)
         st, got = P.ExactMinimum(inp).run()
         assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
+
+
+@pytest.mark.parametrize("shape", [(35, 1, 1, 1389, 0), (31, 2, 1, 840, 62), (1, 1, 1, 1681, 0), (90, 1, 4, 69, 90), (10, 1, 1, 1641, 10)])
+def test_shares_of_the_lds_that_just_hold_the_tables(P, shape):
+    """Two, three or four workgroups per compute unit, their tables next to the whole of their share; far
+    more nodes than layers."""
+    L, M, n_min, n_max, nb = shape
+    for var in ("plain", "tight"):
+        inp = inputs.random_small(5, L, M, n_min, n_max, nb, f=1, tight_mem=(var == "tight"))
+        print("case", shape, var, flush=True)
+        st, got = P.ExactMinimum(inp).run()
+        assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
