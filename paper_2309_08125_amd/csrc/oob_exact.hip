@@ -63,17 +63,8 @@ constexpr unsigned long long kNoneBits = 0x7FF0000000000000ull;
 
 constexpr int kPrepThreads = 1024, kBins = 4096;
 constexpr int kBoundThreads = 576;   // eight waves for the paths, one for the fewest nodes
-// No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second
-// evaluation take 70 us or more whatever the job, what evaluating some thousand stages of a short model takes.
-constexpr int kDirectMax = 4096;
-constexpr int kMaxBuckets = 512, kBucket = 64; // entries per bucket: 64, more only where that would exceed kMaxBuckets
-constexpr int kMaxCount = 64;        // templates per job that the bounds are kept for
-constexpr int kLambdas = 8, kMus = 8;
 constexpr int kFirst = 1, kRest = 2, kAll = 0;
 
-struct Head { // first words of the workspace
-    unsigned ncand, bucket, nbuckets, alive, next, done, over, narrow;
-};
 struct Args {
     oob_profile prof;
     int L, M, n_min, n_max, Nb, Dmax, Smax, fast, staged, bounds;
@@ -97,7 +88,6 @@ struct Args {
     int *status;
 };
 
-inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // ---- what one workgroup's last act is: hand the minima to the caller ------------------------------
 // Results as int64: -1 where no pipeline exists, -2 (unstaged entry point) where the stage limit
@@ -450,10 +440,6 @@ __device__ int fewest_nodes(int L, int M, const unsigned char *reach, unsigned c
     return n;
 }
 
-__host__ __device__ inline size_t bound_doubles(int L, int M, int mus) {
-    return prof_doubles(L, M) + 2 * (((size_t)(L + 1) * M + 7) / 8) + (size_t)mus * kLambdas * 2 * (L + 1) +
-           kBucket * kMaxCount / 2 + 32;
-}
 // What the multipliers k take off for a pipeline of n nodes, in units of the bucket's fastest stage.
 __device__ __forceinline__ double spent(const Args &a, int k, int n) {
     return (a.Nb > 0 ? kLambdaGiven[k % kLambdas] : kLambda4S[k % kLambdas]) * (n * a.M) + kMuStep[k / kLambdas] * a.Smax;
@@ -1123,7 +1109,8 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
             }
         }
         if (!evaluate<STAGED, MT>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
-            if (STAGED && tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
+            // (not the first picks: the filter keeps those that matter, so each entry comes here once at most)
+            if (STAGED && mode != kFirst && tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
             continue;
         }
         if (mode != kFirst) { // let the other workgroups know
@@ -1272,32 +1259,6 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
 }
 
 inline size_t slot_bytes(int L, int Dmax, int J) { return align_up(sizeof(long long) * 2 * (size_t)(L + 1) * (Dmax + 1) * J); }
-
-inline int bound_mus(int L, int M, bool staged) {
-    int mus = staged ? kMus : 1;
-    while (mus > 1 && 8 * bound_doubles(L, M, mus) > kLdsLimit - kLdsStatic) --mus;
-    return 8 * bound_doubles(L, M, mus) <= kLdsLimit - kLdsStatic ? mus : 0;
-}
-struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blo, bfew, blb, barg, list, over, slots; };
-inline Layout layout(int L, int M, int n_max, bool fast, int mus, bool staged) { // mus: of the stage limit, 0: no bounds
-    const size_t n = fast ? tri(L) * M : 0, cnt = (size_t)imin(n_max, kMaxCount);
-    Layout y;
-    size_t o = 0;
-    y.head = o; o = align_up(o + sizeof(Head));
-    y.PT = o;   o = align_up(o + 8 * (size_t)(L + 1) * M);
-    y.flo = o;  o = align_up(o + (size_t)(L + 1) * M);
-    y.ctau = o; o = align_up(o + 8 * n);
-    y.cuvd = o; o = align_up(o + 4 * n);
-    y.lb = o;   o = align_up(o + (n > kDirectMax ? 4 * n * kLambdas * mus : 0));
-    y.blo = o;  o = align_up(o + 8 * (size_t)kMaxBuckets);
-    y.bfew = o; o = align_up(o + 4 * (size_t)kMaxBuckets);
-    y.blb = o;  o = align_up(o + 4 * (size_t)kMaxBuckets * cnt);
-    y.barg = o; o = align_up(o + 2 * (size_t)kMaxBuckets * cnt);
-    y.list = o; o = align_up(o + 4 * n);
-    y.over = o; o = align_up(o + (staged ? 4 * n : 0));
-    y.slots = o;
-    return y;
-}
 
 } // namespace oob_exact
 

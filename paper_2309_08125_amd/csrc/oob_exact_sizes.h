@@ -1,4 +1,4 @@
-// Index arithmetic and LDS layout of the exact minimum (oob_exact.hip) that the host can check over everything the entry points
+// Index arithmetic, LDS and workspace layout of the exact minimum (oob_exact.hip) that the host can check over everything the entry points
 // accept: plain C++, so that a CPU test compiles it too.
 #pragma once
 
@@ -61,6 +61,50 @@ inline size_t eval_lds(int L, int M, int n_max, int J, bool staged) {
     // less its static arrays is never below `all`
     const size_t most = 1024 / eval_threads(L, M, false), k = kLdsLimit / (all + kLdsStatic);
     return (kLdsLimit / (k < most ? k : most) - kLdsStatic) & ~(size_t)15;
+}
+
+// No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second
+// evaluation take 70 us or more whatever the job, what evaluating some thousand stages of a short model takes.
+constexpr int kDirectMax = 4096;
+constexpr int kMaxBuckets = 512, kBucket = 64; // entries per bucket: 64, more only where that would exceed kMaxBuckets
+constexpr int kMaxCount = 64;        // templates per job that the bounds are kept for
+constexpr int kLambdas = 8, kMus = 8;
+
+// The workspace: these words, the lists and bounds of layout(), then the tables of k_exact_flat.
+struct Head {
+    unsigned ncand, bucket, nbuckets, alive, next, done, over, narrow;
+};
+inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// LDS of k_exact_bounds in doubles.
+OOB_HD inline size_t bound_doubles(int L, int M, int mus) {
+    return prof_doubles(L, M) + 2 * (((size_t)(L + 1) * M + 7) / 8) + (size_t)mus * kLambdas * 2 * (L + 1) +
+           kBucket * kMaxCount / 2 + 32;
+}
+inline int bound_mus(int L, int M, bool staged) {
+    int mus = staged ? kMus : 1;
+    while (mus > 1 && 8 * bound_doubles(L, M, mus) > kLdsLimit - kLdsStatic) --mus;
+    return 8 * bound_doubles(L, M, mus) <= kLdsLimit - kLdsStatic ? mus : 0;
+}
+struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blo, bfew, blb, barg, list, over, slots; };
+inline Layout layout(int L, int M, int n_max, bool fast, int mus, bool staged) { // mus: of the stage limit, 0: no bounds
+    const size_t n = fast ? tri(L) * M : 0, cnt = (size_t)imin(n_max, kMaxCount);
+    Layout y;
+    size_t o = 0;
+    y.head = o; o = align_up(o + sizeof(Head));
+    y.PT = o;   o = align_up(o + 8 * (size_t)(L + 1) * M);
+    y.flo = o;  o = align_up(o + (size_t)(L + 1) * M);
+    y.ctau = o; o = align_up(o + 8 * n);
+    y.cuvd = o; o = align_up(o + 4 * n);
+    y.lb = o;   o = align_up(o + (n > kDirectMax ? 4 * n * kLambdas * mus : 0));
+    y.blo = o;  o = align_up(o + 8 * (size_t)kMaxBuckets);
+    y.bfew = o; o = align_up(o + 4 * (size_t)kMaxBuckets);
+    y.blb = o;  o = align_up(o + 4 * (size_t)kMaxBuckets * cnt);
+    y.barg = o; o = align_up(o + 2 * (size_t)kMaxBuckets * cnt);
+    y.list = o; o = align_up(o + 4 * n);
+    y.over = o; o = align_up(o + (staged ? 4 * n : 0));
+    y.slots = o;
+    return y;
 }
 
 } // namespace oob_exact

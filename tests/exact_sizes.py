@@ -1,0 +1,54 @@
+"""csrc/oob_exact_sizes.h compiled for the host."""
+import ctypes as C
+import os
+import subprocess
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2309_08125_amd", "csrc")
+WRAPPERS = r"""
+#include "oob_exact_sizes.h"
+using namespace oob_exact;
+extern "C" {
+// first index at which the quotient is wrong, -1: none
+int wrong_quotient(int M) {
+    for (int i = 0; i < 256 * M; ++i) if (quot(i, recip(M)) != i / M) return i;
+    return -1;
+}
+// LDS of k_exact_eval for each accepted n_max of (L, M) against the tables of its largest slowest stage, the bands as wide
+// as the sides: the smallest surplus in doubles over all that take the LDS path (1 << 30: none does).
+int smallest_surplus(int L, int M) {
+    size_t tables = 0; // covers next to the stage, both W, one one-node table, by the layers before it
+    for (int P = 0; P <= L - 1; ++P) {
+        const int S = L - 1 - P, most = P > S ? P : S;
+        const size_t n = (size_t)(L - 1) * M + band_size(P, P) + band_size(S, S) + (size_t)(most + 1) * (M + 1);
+        tables = n > tables ? n : tables;
+    }
+    int least = 1 << 30;
+    for (int n = 1; n * M <= 4096; ++n) {
+        const size_t lds = eval_lds(L, M, n, 1, false);
+        if (lds == 0) continue;
+        if (lds > kLdsLimit - kLdsStatic) return -1;
+        const long long pool = (long long)(lds / 8) - (long long)(eval_fixed(L, M, n, 1) + n), surplus = pool - (long long)tables;
+        if (surplus < least) least = (int)surplus;
+    }
+    return least;
+}
+size_t offset_of_leftovers(int L, int M, int n_max, int counts) { return layout(L, M, n_max, true, bound_mus(L, M, counts), true).over; }
+}
+"""
+HEAD = ("ncand", "bucket", "nbuckets", "alive", "next", "done", "over", "narrow")  # first words of the workspace
+
+
+def build(directory):
+    src, lib = os.path.join(str(directory), "wrappers.cpp"), os.path.join(str(directory), "wrappers.so")
+    with open(src, "w") as f:
+        f.write(WRAPPERS)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, "-o", lib, src], check=True)
+    L = C.CDLL(lib)
+    L.offset_of_leftovers.restype = C.c_size_t
+    return L
+
+
+def head(workspace):
+    import torch
+
+    return dict(zip(HEAD, workspace[:32].view(torch.int32).tolist()))

@@ -5,6 +5,7 @@ import os
 
 import pytest
 
+import exact_sizes
 import inputs
 from oracle import exact_minimum as E
 
@@ -20,6 +21,11 @@ def P():
     assert torch.cuda.is_available()
     pkg.load()
     return pkg
+
+
+@pytest.fixture(scope="module")
+def sizes(tmp_path_factory):
+    return exact_sizes.build(tmp_path_factory.mktemp("exact_sizes"))
 
 
 SHAPES = [(1, 1, 1, 1, 4), (5, 1, 1, 3, 6), (6, 2, 1, 3, 8), (7, 2, 1, 2, 9), (6, 4, 1, 2, 12), (8, 4, 2, 2, 12),
@@ -248,3 +254,19 @@ def test_shares_of_the_lds_that_just_hold_the_tables(P, shape):
         print("case", shape, var, flush=True)
         st, got = P.ExactMinimum(inp).run()
         assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
+
+
+def test_leftovers_with_stage_counts_are_listed_once(P, sizes):
+    """Slowest stages whose tables exceed LDS are left to the general path: each at most once, whatever the
+    number of templates that pick it first."""
+    import torch
+
+    L, M, n_min, n_max, nb = 65, 8, 1, 8, 40
+    inp = inputs.random_small(7, L, M, n_min, n_max, nb, f=1)
+    e = P.ExactMinimum(inp, staged=True)
+    st, got = e.run()
+    assert st == P.OOB_OK and got == E.exact_minimum_staged(inp)
+    h = exact_sizes.head(e.workspace)
+    o = sizes.offset_of_leftovers(L, M, n_max, 1)
+    left = e.workspace[o: o + 4 * h["over"]].view(torch.int32).tolist()
+    assert 0 < len(left) == len(set(left)) <= h["alive"] <= h["ncand"]
