@@ -546,6 +546,11 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
         if (side) rows(std::true_type{}); else rows(std::false_type{});
     }
     wg_sync();
+    // Roundings: at most six per stage, so 6 L 2^-53 < 2e-13 of what is added up.  That is prices and stage times (a
+    // path may use 255 times the GPUs of the pipeline: lowered by 1e-9 of them), and prefix sums of the GPU count in use,
+    // twice over -- which hold also the layers whose time on that count no stage takes (by 1e-12 of the largest).
+    double total = 0;
+    for (int d = 0; d < M; ++d) total = fmax(total, s.PT[L * M + d]);
     // bounds of the bucket's entries, kBucket at a time; the smallest of every template
     const int count = a.n_max - a.n_min + 1, nk = mus * kLambdas;
     float mine = __builtin_huge_valf();
@@ -558,8 +563,7 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
             const int u = uvd & 255, v = uvd >> 8 & 255, d = uvd >> 16;
             const double tau = a.ctau[m0 + q], l = s_lam[k % kLambdas], mu = s_mu[k / kLambdas];
             const double base = mid * tau + PS[(size_t)k * 2 * W + u] + PS[((size_t)k * 2 + 1) * W + v] + l * d + mu;
-            // lowered by far more than a few roundings of sums of this size are worth
-            s_lb[i] = __double2float_rd(base - 1e-9 * (fabs(base) + mid * tau + s.PT[L * M] + fabs(l) * a.n_max * M + mu * a.Smax));
+            s_lb[i] = __double2float_rd(base - 1e-9 * (fabs(base) + mid * tau + fabs(l) * a.n_max * M + mu * a.Smax) - 1e-12 * total);
             a.lb[(size_t)m0 * nk + i] = s_lb[i];
         }
         wg_sync();

@@ -32,7 +32,11 @@ int smallest_surplus(int L, int M) {
     }
     return least;
 }
-size_t offset_of_leftovers(int L, int M, int n_max, int counts) { return layout(L, M, n_max, true, bound_mus(L, M, counts), true).over; }
+// offsets in the workspace of a job that takes the LDS path: times and stages of the list, its bounds, the leftovers
+void offsets(int L, int M, int n_max, int counts, int staged, size_t *at) {
+    const Layout y = layout(L, M, n_max, true, bound_mus(L, M, counts), staged);
+    at[0] = y.ctau; at[1] = y.cuvd; at[2] = y.lb; at[3] = y.over;
+}
 }
 """
 HEAD = ("ncand", "bucket", "nbuckets", "alive", "next", "done", "over", "narrow")  # first words of the workspace
@@ -43,9 +47,13 @@ def build(directory):
     with open(src, "w") as f:
         f.write(WRAPPERS)
     subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I", CSRC, "-o", lib, src], check=True)
-    L = C.CDLL(lib)
-    L.offset_of_leftovers.restype = C.c_size_t
-    return L
+    return C.CDLL(lib)
+
+
+def offsets(sizes, L, M, n_max, counts=False, staged=False):
+    at = (C.c_size_t * 4)()
+    sizes.offsets(L, M, n_max, int(counts), int(staged), at)
+    return dict(zip(("ctau", "cuvd", "lb", "over"), at))
 
 
 def head(workspace):

@@ -267,6 +267,69 @@ def test_leftovers_with_stage_counts_are_listed_once(P, sizes):
     st, got = e.run()
     assert st == P.OOB_OK and got == E.exact_minimum_staged(inp)
     h = exact_sizes.head(e.workspace)
-    o = sizes.offset_of_leftovers(L, M, n_max, 1)
+    o = exact_sizes.offsets(sizes, L, M, n_max, counts=True, staged=True)["over"]
     left = e.workspace[o: o + 4 * h["over"]].view(torch.int32).tolist()
     assert 0 < len(left) == len(set(left)) <= h["alive"] <= h["ncand"]
+
+
+LAMBDA_GIVEN = (0, 0.04, 0.1, 0.2, 0.4, 0.8, 1.6, 3.5)  # prices per GPU of the bounds, N_b given
+
+
+def bounds_of_a_job(P, sizes, inp):
+    """(bounds on the device [entries, prices], the same sums in 80-bit floats, their rounding): least sums over the
+    stages before and after each possible slowest stage, GPUs priced, N_b given, no stage limit."""
+    import numpy as np
+    import torch
+
+    L, M = inp.L, inp.gpus_per_node
+    e = P.ExactMinimum(inp)
+    st, got = e.run()
+    assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True)
+    h, at = exact_sizes.head(e.workspace), exact_sizes.offsets(sizes, L, M, inp.n_max)
+    n = h["ncand"]
+    part = lambda k, size, dt: e.workspace[at[k]: at[k] + size * n].view(dt).cpu().numpy()
+    tau, uvd = part("ctau", 8, torch.float64), part("cuvd", 4, torch.int32)
+    lb = part("lb", 4 * len(LAMBDA_GIVEN), torch.float32).reshape(n, len(LAMBDA_GIVEN))
+    big = np.longdouble
+    forbidden = (inp.fwd_ns >= 1 << 62) | (inp.bwd_ns >= 1 << 62)
+    assert not forbidden.any() and int(inp.mem_bytes.sum()) <= inp.mem_cap
+    PT = np.concatenate([np.zeros((1, M), dtype=np.int64), np.cumsum(inp.fwd_ns + inp.bwd_ns, axis=0)]).astype(big)
+    X = np.concatenate([[0], inp.boundary_ns[:-1], [0]]).astype(big)
+    d1 = np.arange(1, M + 1)
+    want, err = np.empty((n, len(LAMBDA_GIVEN)), dtype=big), np.empty((n, 1))
+    for c0 in range(0, n, h["bucket"]):
+        c = slice(c0, min(n, c0 + h["bucket"]))
+        lo, hi = tau[c].min(), tau[c].max()
+        err[c] = 6 * L * 2.0 ** -63 * (L * hi + 2 * float(PT.max()) + L * M * LAMBDA_GIVEN[-1] * lo)
+        for k, price in enumerate(LAMBDA_GIVEN):
+            lam = big(price * lo)
+            before, after = np.full(L + 1, big(np.inf)), np.full(L + 1, big(np.inf))
+            before[0] = after[L] = 0
+            for p in range(1, L + 1):
+                t = PT[p] + X[p] - PT[:p]  # stages [x, p)
+                before[p] = np.where(t <= hi, before[:p, None] + t + lam * d1, big(np.inf)).min()
+            for p in range(L - 1, -1, -1):
+                t = PT[p + 1:] + X[p + 1:, None] - PT[p]
+                after[p] = np.where(t <= hi, after[p + 1:, None] + 2 * t - big(hi) + lam * d1, big(np.inf)).min()
+            u, v, d = uvd[c] & 255, uvd[c] >> 8 & 255, uvd[c] >> 16
+            want[c, k] = inp.microbatches * tau[c].astype(big) + before[u] + after[v] + lam * d
+    return lb, want, err
+
+
+@pytest.mark.parametrize("never", [(), (0,), (3, 40)])
+def test_lower_bounds_are_below_what_they_bound(P, sizes, never):
+    """The bounds of every possible slowest stage against the sums they stand for, in more precision.  `never`: layers
+    whose time on two GPUs no pipeline of a minimum takes, near the largest that is accepted -- doubles of that size
+    round by a quarter of a nanosecond and more."""
+    import dataclasses
+
+    import numpy as np
+
+    inp = inputs.random_small(3, 66, 2, 1, 2, 4, f=1, t_lo=20, t_hi=50)
+    if never:
+        fwd = inp.fwd_ns.copy()
+        fwd[list(never), 1] = ((1 << 52) // (inp.microbatches + 2) - 10 ** 7) // len(never)
+        inp = dataclasses.replace(inp, fwd_ns=fwd)
+    lb, want, err = bounds_of_a_job(P, sizes, inp)
+    finite = np.isfinite(want)
+    assert finite.sum() > 4096 and (lb <= want + err)[finite].all(), float((lb - want)[finite].max())
