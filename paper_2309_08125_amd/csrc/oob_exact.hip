@@ -563,7 +563,9 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
             const int u = uvd & 255, v = uvd >> 8 & 255, d = uvd >> 16;
             const double tau = a.ctau[m0 + q], l = s_lam[k % kLambdas], mu = s_mu[k / kLambdas];
             const double base = mid * tau + PS[(size_t)k * 2 * W + u] + PS[((size_t)k * 2 + 1) * W + v] + l * d + mu;
-            s_lb[i] = __double2float_rd(base - 1e-9 * (fabs(base) + mid * tau + fabs(l) * a.n_max * M + mu * a.Smax) - 1e-12 * total);
+            const double low = base - 1e-9 * (fabs(base) + mid * tau + fabs(l) * a.n_max * M + mu * a.Smax) - 1e-12 * total;
+            // a side that stages of at most the bucket's slowest time cannot cover: no pipeline (and no infinity minus another)
+            s_lb[i] = base < kNone ? __double2float_rd(low) : __builtin_huge_valf();
             a.lb[(size_t)m0 * nk + i] = s_lb[i];
         }
         wg_sync();

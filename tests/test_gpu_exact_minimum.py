@@ -333,3 +333,29 @@ def test_lower_bounds_are_below_what_they_bound(P, sizes, never):
     lb, want, err = bounds_of_a_job(P, sizes, inp)
     finite = np.isfinite(want)
     assert finite.sum() > 4096 and (lb <= want + err)[finite].all(), float((lb - want)[finite].max())
+    # stages that no pipeline has as its slowest: the layers before or after them need a slower one
+    assert (~finite).any() and np.isposinf(lb[~finite]).all()
+
+
+def test_stages_that_leave_a_layer_uncovered_are_ruled_out(P):
+    """One layer that dwarfs the others, more GPUs per node than the count of the fewest nodes takes: what is
+    faster than that layer on all its GPUs is the slowest stage of no pipeline and is not evaluated."""
+    import dataclasses
+
+    L, M = 40, 9
+    inp = inputs.random_small(2, L, M, 1, 6, 0, f=1, t_lo=20, t_hi=50)
+    fwd = inp.fwd_ns.copy()
+    fwd[13] += 5000
+    inp = dataclasses.replace(inp, fwd_ns=fwd)
+    e = P.ExactMinimum(inp)
+    st, got = e.run()
+    assert st == P.OOB_OK and got == E.exact_minimum(inp)
+    least = (inp.fwd_ns + inp.bwd_ns)[13].min()  # (boundary terms only add to it)
+    cum = inp.fwd_ns + inp.bwd_ns
+    slow = 0
+    for d in range(M):
+        for u in range(L):
+            t = cum[u:, d].cumsum() + [b if v < L - 1 else 0 for v, b in enumerate(inp.boundary_ns[u:].tolist(), u)]
+            slow += int((t >= least).sum())
+    h = exact_sizes.head(e.workspace)
+    assert slow < h["ncand"] // 2 and h["alive"] <= slow + h["bucket"]
