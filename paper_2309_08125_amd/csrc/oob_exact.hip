@@ -89,6 +89,10 @@ struct Args {
 };
 
 
+// Whether the template for n nodes gets a minimum: without stage counts not where the stage limit can bind.  The others'
+// best stays infinite, and no bound, pick or evaluation is for them.
+__device__ __forceinline__ bool answered(const Args &a, int n) { return a.staged || a.Nb == 0 || a.Nb >= imin(a.L, n * a.M); }
+
 // ---- what one workgroup's last act is: hand the minima to the caller ------------------------------
 // Results as int64: -1 where no pipeline exists, -2 (unstaged entry point) where the stage limit
 // can bind, so that the minimum without it is not the answer.
@@ -97,7 +101,7 @@ __device__ void finish(const Args &a, bool from_double) {
         const int n = a.n_min + i;
         const unsigned long long b = __hip_atomic_load(&a.best[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         long long out;
-        if (!a.staged && a.Nb > 0 && a.Nb < imin(a.L, n * a.M)) out = -2;
+        if (!answered(a, n)) out = -2;
         else if (from_double) { const double x = __longlong_as_double((long long)b); out = x < kNone ? (long long)x : -1; }
         else out = (long long)b >= kInf / 2 ? -1 : (long long)b;
         ((long long *)a.best)[i] = out;
@@ -446,7 +450,7 @@ __device__ __forceinline__ double spent(const Args &a, int k, int n) {
 }
 // The bound of an entry (its values lb[0 .. nk-1]) of a bucket for n nodes; below all doubt where there is none.
 __device__ __forceinline__ double bound_of(const Args &a, const float *lb, double lo, int fewest, int n) {
-    if (n < fewest || n > a.L) return kNone;
+    if (n < fewest || n > a.L || !answered(a, n)) return kNone;
     double x = -kNone;
     for (int k = 0; k < a.nk; ++k) x = fmax(x, (double)lb[k] - lo * spent(a, k, n));
     return x;
@@ -833,7 +837,7 @@ __device__ void combine(const Args &a, const Eval &e, int d, double tau, int nhi
     const int places = M - d + 1;
     for (int i = threadIdx.x; i < cendP * cendS; i += blockDim.x) {
         const int ca = i / cendS, cb = i - ca * cendS, n = ca + cb + 1;
-        if (n < a.n_min || n > nhi || (!STAGED && a.Nb > 0 && a.Nb < imin(L, n * M))) continue;
+        if (n < a.n_min || n > nhi || !answered(a, n)) continue;
         double m = kNone;
         for (int g = 0; g < places; ++g) {
             if (!STAGED) m = fmin(m, e.OUT[ca * M + g] + e.OUT[(a.n_max + cb) * M + (M - d - g)]);
@@ -1094,7 +1098,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                 if (tid < count) {
                     const int n = a.n_min + tid, j = imin(L - (int)(uvd >> 8 & 255), n * M - (int)(uvd >> 16));
                     const double least = a.Nb > 0 ? (double)imax(a.Nb - j, 0) * tau : (3.0 * n + 1.0) * tau;
-                    if (least <= best_now(a, tid)) atomicMax(&s_nhi, n);
+                    if (answered(a, n) && least <= best_now(a, tid)) atomicMax(&s_nhi, n);
                 }
                 if (count > (int)blockDim.x && tid == 0) s_nhi = a.n_max;
                 wg_sync();
@@ -1240,7 +1244,7 @@ __global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
                 const int E = n * M - D - d;
                 if (E < 0) continue;
                 if (!STAGED) {
-                    if (a.Nb > 0 && a.Nb < min(L, n * M)) continue;
+                    if (!answered(a, n)) continue;
                     const long long suf = Suf[(size_t)v * plane + E];
                     if (suf >= kInf / 2) continue;
                     const long long tot = pre + (a.Nb > 0 ? (long long)a.Nb : 4ll) * tau + suf;

@@ -359,3 +359,20 @@ def test_stages_that_leave_a_layer_uncovered_are_ruled_out(P):
             slow += int((t >= least).sum())
     h = exact_sizes.head(e.workspace)
     assert slow < h["ncand"] // 2 and h["alive"] <= slow + h["bucket"]
+
+
+@pytest.mark.parametrize("shape", [(70, 2, 1, 30, 40), (50, 8, 1, 20, 33)])
+def test_templates_without_an_answer_cost_no_evaluations(P, shape):
+    """Templates whose stage limit can bind beside others: what the filter keeps is what it keeps for the
+    others alone, up to the order of equal times in the list."""
+    L, M, n_min, n_max, nb = shape
+    inp = inputs.random_small(4, L, M, n_min, n_max, nb, f=1, t_lo=20)
+    e = P.ExactMinimum(inp)
+    st, got = e.run()
+    want = E.exact_minimum(inp, allow_bound=True)
+    assert st == P.OOB_OK and got == want and got[-1] == P.OOB_EXACT_LIMIT_CAN_BIND
+    few = inputs.random_small(4, L, M, n_min, n_min + want.index(P.OOB_EXACT_LIMIT_CAN_BIND) - 1, nb, f=1, t_lo=20)
+    alone = P.ExactMinimum(few)
+    assert alone.run()[1] == want[: few.n_max - few.n_min + 1]
+    a, b = exact_sizes.head(e.workspace)["alive"], exact_sizes.head(alone.workspace)["alive"]
+    assert a <= 2 * b, (a, b)
