@@ -60,9 +60,9 @@ size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per_node, int 
  *                 mult w reaches the exact range, w = sum over the layers of (largest allowed F + B
  *                 of the layer over the GPU counts) + boundary_ns, mult = N_b + 2 (4 min(L, n_max
  *                 gpus_per_node) + 2 for N_b = 4 S): every cost stays below mult w.  The range is
- *                 2^52 where the tables are held in LDS as doubles (oob_exact_minimum on shapes up to
- *                 about 128 layers and 16 GPUs per node), 2^61 otherwise.  `best` is meaningless
- *                 unless OOB_OK.
+ *                 2^52 where oob_exact_minimum holds its tables in LDS as doubles (with up to 8 nodes: up to
+ *                 190 layers with 1 GPU per node, 168 with 8, 146 with 16, 111 with 32, 70 with 64; fewer
+ *                 layers with many more nodes), 2^61 otherwise.  `best` is meaningless unless OOB_OK.
  * Return OOB_OK once enqueued; OOB_EINVAL for arguments the host can reject; OOB_ECAPACITY for a
  * workspace that is too small. */
 int oob_exact_minimum(const oob_profile *profile, int L, int n_min, int n_max, int gpus_per_node,

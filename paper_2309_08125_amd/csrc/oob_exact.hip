@@ -68,6 +68,8 @@ constexpr int kFirst = 1, kRest = 2, kAll = 0;
 struct Args {
     oob_profile prof;
     int L, M, n_min, n_max, Nb, Dmax, Smax, fast, staged, bounds;
+    int sums;             // the profile without the ends of the stages (EvalLds)
+    int nodes, live;      // min(n_max, L): more nodes than layers make no pipeline; templates up to there
     long long cap;
     long long limit;      // every cost must stay below this (2^52 for the LDS path, 2^61 otherwise)
     Head *head;
@@ -349,18 +351,23 @@ __device__ __forceinline__ double row_below(double x) {
 }
 
 // The profile in LDS: PT[l M + d-1] prefix sums, PX = PT plus the boundary term of a stage ending at layer l,
-// X the boundary terms, flo as in Args.
+// X the boundary terms, flo as in Args.  SUM: PX is not kept but added up where it is read (integers below 2^52: the same
+// value), for shapes whose tables leave it no room.
 struct Prof { double *PT, *PX, *X; unsigned char *flo; };
-__device__ __forceinline__ Prof load_prof(const Args &a, double *lds) {
+template <bool SUM> __device__ __forceinline__ double stage_end(const Prof &s, int l, int i) { // i = l M + d-1
+    if constexpr (SUM) return s.PT[i] + s.X[l];
+    else return s.PX[i];
+}
+template <bool SUM> __device__ __forceinline__ Prof load_prof(const Args &a, double *lds) {
     const int W = a.L + 1, n = W * a.M;
     Prof p;
-    p.PT = lds; p.PX = p.PT + n; p.X = p.PX + n; p.flo = (unsigned char *)(p.X + W);
+    p.PT = lds; p.PX = p.PT + n; p.X = SUM ? p.PX : p.PX + n; p.flo = (unsigned char *)(p.X + W);
     const long long *bnd = (const long long *)a.prof.boundary_ns;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const int l = i / a.M;
         const double pt = (double)a.PT[i];
         p.PT[i] = pt;
-        p.PX[i] = pt + (l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0);
+        if (!SUM) p.PX[i] = pt + (l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0);
         p.flo[i] = a.flo[i];
     }
     for (int l = threadIdx.x; l < W; l += blockDim.x) p.X[l] = l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0;
@@ -368,9 +375,9 @@ __device__ __forceinline__ Prof load_prof(const Args &a, double *lds) {
 }
 // Reach of a stage on dd GPUs into layer p (before the slowest stage: it starts at r .. p-1; p: none) that
 // takes less than tau (STRICT) or at most tau: it only gets slower and heavier as its start goes down.
-template <bool STRICT>
+template <bool STRICT, bool SUM>
 __device__ __forceinline__ int reach_back(const Prof &s, int M, int p, int dd, double tau) {
-    const double end = s.PX[p * M + dd - 1];
+    const double end = stage_end<SUM>(s, p, p * M + dd - 1);
     int lo = s.flo[p * M + dd - 1], hi = p;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -468,7 +475,7 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
     const int L = a.L, M = MT ? MT : a.M, W = L + 1, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned c0 = b * K, c1 = min(a.head->ncand, c0 + K);
-    const Prof s = load_prof(a, s_dyn);
+    const Prof s = load_prof<false>(a, s_dyn);
     unsigned char *rb = (unsigned char *)(s_dyn + prof_doubles(L, M)), *rf = rb + ((size_t)W * M + 7) / 8 * 8;
     double *PS = (double *)(rf + ((size_t)W * M + 7) / 8 * 8); // [mu][lambda][side][L+1]
     float *s_lb = (float *)(PS + (size_t)mus * kLambdas * 2 * W); // [kBucket][kMaxCount]
@@ -483,7 +490,7 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
     const double lo = __longlong_as_double((long long)s_lo), hi = __longlong_as_double((long long)s_hi);
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
         const int p = i / M, dd = i - p * M + 1;
-        rb[i] = (unsigned char)reach_back<false>(s, M, p, dd, hi);
+        rb[i] = (unsigned char)reach_back<false, false>(s, M, p, dd, hi);
         rf[i] = (unsigned char)reach_on(s, L, M, p, dd, hi);
     }
     const bool given = a.Nb > 0;
@@ -645,7 +652,7 @@ __device__ __forceinline__ int band_index(int r, int j, int len) { return (r - 1
 // counts the lanes that would share a walk out hold the counts j = 1 .. M instead.  A row takes the stages that
 // cover its last k + 1 layers on CW GPU counts side by side: the CW table entries and the CW prefix sums of a
 // step are read before any of them is used.
-template <bool MIRROR, bool STAGED, int MT>
+template <bool MIRROR, bool STAGED, int MT, bool SUM>
 __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band, double tau, double wt, double add,
                                 double *Wm, double *GU, double *G, int first, int slots, int lgxs, int gbits) {
     constexpr int CW = MT ? MT : 8;
@@ -660,7 +667,7 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
     const int g = gi + 1, rows = live ? imin(band, len - idx) : 0;
     const bool use = live && (!STAGED || j <= g);                   // this lane has an entry in every row
     const int q = live ? (MIRROR ? L - idx : idx) : 0;                           // start layer
-    const double *far = MIRROR ? e.pr.PX : e.pr.PT;
+    auto far = [&](int l, int gc) { return MIRROR ? stage_end<SUM>(e.pr, l, l * M + gc) : e.pr.PT[l * M + gc]; };
     const int top = g + 1 - (j - 1);
     const int none = 0; // row 0 holds no cover (a node's first stage is taken on its own): always impossible
     if (slot < slots && gi == 0 && xs == 0) T[none] = kNone;
@@ -671,7 +678,7 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
         const int p = on ? (MIRROR ? q - r : q + r) : 0;
         { // one stage on all g GPUs covers everything
             const int gc = imin(gi, M - 1), rc = e.reach[p * M + gc];
-            const double here = MIRROR ? e.pr.PT[p * M + gc] : e.pr.PX[p * M + gc], all = far[q * M + gc];
+            const double here = MIRROR ? e.pr.PT[p * M + gc] : stage_end<SUM>(e.pr, p, p * M + gc), all = far(q, gc);
             const double tw = MIRROR ? all - here : here - all;
             const bool one = on & (j == 1) & (x0 == 0) & ((MIRROR ? rc - p : p - rc) >= r) & (!MIRROR | (tw <= tau));
             acc = one ? wt * tw + add : kNone;
@@ -683,7 +690,7 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
 #pragma unroll
             for (int w = 0; w < CW; ++w) {
                 const int dc = MT ? w : imin(d0 + w, M - 1), rc = e.reach[p * M + dc];
-                near[w] = wt * (MIRROR ? -e.pr.PT[p * M + dc] : e.pr.PX[p * M + dc]) + add;
+                near[w] = wt * (MIRROR ? -e.pr.PT[p * M + dc] : stage_end<SUM>(e.pr, p, p * M + dc)) + add;
                 late[w] = MIRROR ? e.pr.PT[p * M + dc] + tau : 0.0;
                 lim[w] = on && d0 + w + 1 < top ? imin(MIRROR ? rc - p : p - rc, r - 1) : 0; // the other stages need a GPU each
                 most = imax(most, lim[w]);
@@ -695,7 +702,7 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
                 double tv[CW], gv[CW];
 #pragma unroll
                 for (int w = 0; w < CW; ++w) {
-                    tv[w] = far[x * M + (MT ? w : imin(d0 + w, M - 1))];
+                    tv[w] = far(x, MT ? w : imin(d0 + w, M - 1));
                     gv[w] = T[k < lim[w] ? off[w] - kk * row_n : none]; // beyond the reach: an entry that is impossible
                 }
 #pragma unroll
@@ -840,9 +847,9 @@ __device__ void combine(const Args &a, const Eval &e, int d, double tau, int nhi
         if (n < a.n_min || n > nhi || !answered(a, n)) continue;
         double m = kNone;
         for (int g = 0; g < places; ++g) {
-            if (!STAGED) m = fmin(m, e.OUT[ca * M + g] + e.OUT[(a.n_max + cb) * M + (M - d - g)]);
+            if (!STAGED) m = fmin(m, e.OUT[ca * M + g] + e.OUT[(a.nodes + cb) * M + (M - d - g)]);
             else {
-                const double *p = e.OUT + (size_t)(ca * M + g) * J, *s = e.OUT + (size_t)((a.n_max + cb) * M + (M - d - g)) * J;
+                const double *p = e.OUT + (size_t)(ca * M + g) * J, *s = e.OUT + (size_t)((a.nodes + cb) * M + (M - d - g)) * J;
                 double pre = kNone; // least over the stages before, as many as the stages after leave room for
                 int j1 = 0;
                 for (int j2 = a.Smax - 1; j2 >= 0; --j2) {
@@ -858,7 +865,7 @@ __device__ void combine(const Args &a, const Eval &e, int d, double tau, int nhi
 
 // One row of the tables over (layers covered, GPUs used[, stages]) of a side: T[r][D][j], r layers from the far end of the
 // side on D GPUs, node after node.  Called by nth threads (whole waves); a thread has one (D, j) and a share of the walk.
-template <bool MIRROR, bool STAGED, int MT>
+template <bool MIRROR, bool STAGED, int MT, bool SUM>
 __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, double tau, double wt, double add, double *T, int th,
                         int nth) {
     constexpr int CW = MT ? MT : 8;
@@ -867,7 +874,7 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
     int lg = 0;
     while (lg < 6 && items << (lg + 1) <= nth) ++lg;
     const int XS = 1 << lg, x0 = th & (XS - 1);
-    const double *far = MIRROR ? e.pr.PX : e.pr.PT;
+    auto far = [&](int l, int gc) { return MIRROR ? stage_end<SUM>(e.pr, l, l * M + gc) : e.pr.PT[l * M + gc]; };
     for (int i0 = 0; i0 < items; i0 += nth >> lg) {
         const int i = i0 + (th >> lg), D = i % nd, j = STAGED ? i / nd + 1 : 1;
         const bool on = i < items && D > 0 && j <= D;
@@ -879,7 +886,7 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
 #pragma unroll
             for (int w = 0; w < CW; ++w) {
                 const int dc = MT ? w : imin(d0 + w, M - 1), rc = e.reach[p * M + dc];
-                near[w] = MIRROR ? e.pr.PT[p * M + dc] : e.pr.PX[p * M + dc];
+                near[w] = MIRROR ? e.pr.PT[p * M + dc] : stage_end<SUM>(e.pr, p, p * M + dc);
                 lim[w] = d0 + w < gD && (!STAGED || D - dc - 1 >= j - 1) ? imin(MIRROR ? rc - p : p - rc, r) : 0;
                 most = imax(most, lim[w]);
                 off[w] = (r - 1) * row_n + imax(D - dc - 1, 0) * jd + (STAGED ? j - 1 : 0);
@@ -889,7 +896,7 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
                 double tv[CW], gv[CW];
 #pragma unroll
                 for (int w = 0; w < CW; ++w) {
-                    tv[w] = far[x * M + (MT ? w : imin(d0 + w, M - 1))];
+                    tv[w] = far(x, MT ? w : imin(d0 + w, M - 1));
                     gv[w] = T[off[w] - kk * row_n];
                 }
 #pragma unroll
@@ -911,7 +918,7 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
 
 // The cost of the best pipelines around slowest stage (u, v, d) with n <= nhi nodes, merged into s_best.
 // Returns false (the same in every thread) if the tables do not fit the workgroup's LDS (STAGED only).
-template <bool STAGED, int MT>
+template <bool STAGED, int MT, bool SUM>
 __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int nhi, unsigned long long *s_best) {
     const int L = a.L, M = MT ? MT : a.M, J = STAGED ? a.Smax + 1 : 1, nw = blockDim.x >> 6, W = L + 1;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -926,7 +933,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
         const int p = quot(i, inv), dd = i - p * M + 1;
         int r = p;
-        if (p >= 1 && p <= u) { r = reach_back<true>(e.pr, M, p, dd, tau); mostP = imax(mostP, (p - r) * M / dd); }
+        if (p >= 1 && p <= u) { r = reach_back<true, SUM>(e.pr, M, p, dd, tau); mostP = imax(mostP, (p - r) * M / dd); }
         else if (p >= v && p < L) { r = reach_on(e.pr, L, M, p, dd, tau); mostS = imax(mostS, (r - p) * M / dd); }
         e.reach[i] = (unsigned char)r;
     }
@@ -956,14 +963,14 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
             }
             wg_sync();
             for (int r = 1; r <= imax(lenP, lenS); ++r) {
-                if (!mir) { if (r <= lenP) gpu_row<false, STAGED, MT>(a, e, r, nd, jd, tau, 1.0, ptau * tau, e.pool, th, nth); }
-                else      { if (r <= lenS) gpu_row<true, STAGED, MT>(a, e, r, nd, jd, tau, 2.0, stau * tau, e.pool + second, th, nth); }
+                if (!mir) { if (r <= lenP) gpu_row<false, STAGED, MT, SUM>(a, e, r, nd, jd, tau, 1.0, ptau * tau, e.pool, th, nth); }
+                else      { if (r <= lenS) gpu_row<true, STAGED, MT, SUM>(a, e, r, nd, jd, tau, 2.0, stau * tau, e.pool + second, th, nth); }
                 wg_sync();
             }
             for (int i = threadIdx.x; i < (cendP + cendS) * M * J; i += blockDim.x) {
                 const bool after = i >= cendP * M * J;
                 const int o = after ? i - cendP * M * J : i, d0 = o / J, j = o - d0 * J;
-                e.OUT[(after ? a.n_max * M * J : 0) + o] =
+                e.OUT[(after ? a.nodes * M * J : 0) + o] =
                     j < jd ? e.pool[(after ? second + lenS * row_n : lenP * row_n) + d0 * jd + j] : kNone;
             }
             wg_sync();
@@ -999,8 +1006,8 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
                 int side, i;
                 if (item < both) { side = item & 1; i = item >> 1; }
                 else { side = nS > nP; i = item - (both >> 1); }
-                if (!side) one_node_tables<false, STAGED, MT>(a, e, lenP, bandP, tau, 1.0, ptau * tau, WP, e.GU, mine, i * slots, slots, lgxs, gbits);
-                else       one_node_tables<true, STAGED, MT>(a, e, lenS, bandS, tau, 2.0, stau * tau, WS, e.GU + bandP * gu, mine, i * slots, slots, lgxs, gbits);
+                if (!side) one_node_tables<false, STAGED, MT, SUM>(a, e, lenP, bandP, tau, 1.0, ptau * tau, WP, e.GU, mine, i * slots, slots, lgxs, gbits);
+                else       one_node_tables<true, STAGED, MT, SUM>(a, e, lenS, bandS, tau, 2.0, stau * tau, WS, e.GU + bandP * gu, mine, i * slots, slots, lgxs, gbits);
             }
         }
     }
@@ -1018,7 +1025,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
             const double *H = HP + (after ? histP : 0) + c * (band + 1), *cov = e.GU + (after ? bandP * M : 0) + g;
             double m = g == 0 ? H[0] : kNone;
             if (g > 0) for (int r = 1; r <= band; ++r) m = fmin(m, H[r] + cov[(r - 1) * M]);
-            e.OUT[(after ? a.n_max * M : 0) + o] = m;
+            e.OUT[(after ? a.nodes * M : 0) + o] = m;
         }
         wg_sync();
     } else {
@@ -1029,7 +1036,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     wg_sync();
     for (int c = 0; c < imax(cendP, cendS); ++c) {
         if (c < cend) {
-            node_out<STAGED>(a, len, band, c, cur, e.GU + (mir ? bandP * gu : 0), e.OUT + (mir ? (size_t)a.n_max * M * J : 0), th, nth);
+            node_out<STAGED>(a, len, band, c, cur, e.GU + (mir ? bandP * gu : 0), e.OUT + (mir ? (size_t)a.nodes * M * J : 0), th, nth);
             if (c + 1 < cend) node_step<STAGED>(a, len, band, c, WP + (mir ? WS - WP : 0), cur, nxt, th, nth);
         }
         wg_sync();
@@ -1040,7 +1047,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     return true;
 }
 
-template <bool STAGED, int MT>
+template <bool STAGED, int MT, bool SUM>
 __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_exact_eval(Args a, int mode, int lds_doubles, int picks) {
     HIP_DYNAMIC_SHARED(double, s_dyn)
     __shared__ unsigned s_next;
@@ -1049,15 +1056,15 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     const int L = a.L, M = a.M, count = a.n_max - a.n_min + 1, J = STAGED ? a.Smax + 1 : 1, tid = threadIdx.x;
     if (idle) return;
     Eval e;
-    e.pr = load_prof(a, s_dyn);
-    double *p = s_dyn + prof_doubles(L, M);
+    e.pr = load_prof<SUM>(a, s_dyn);
+    double *p = s_dyn + prof_doubles(L, M, SUM);
     e.reach = (unsigned char *)p; p += ((size_t)(L + 1) * M + 7) / 8;
     e.NP = p;     p += 2 * (size_t)(L + 2) * J;
-    e.OUT = p; p += 2 * (size_t)a.n_max * M * J;
-    unsigned long long *s_best = (unsigned long long *)p; p += count;
+    e.OUT = p; p += 2 * (size_t)a.nodes * M * J;
+    unsigned long long *s_best = (unsigned long long *)p; p += a.live;
     e.pool = p; e.pool_n = lds_doubles - (p - s_dyn);
     e.ints = s_ints;
-    for (int i = tid; i < count; i += blockDim.x) s_best[i] = kNoneBits;
+    for (int i = tid; i < a.live; i += blockDim.x) s_best[i] = kNoneBits;
     const unsigned total = mode == kRest ? a.head->alive : a.head->ncand;
     for (int turn = 0;; ++turn) {
         wg_sync(); // the previous entry is done with LDS (and s_next has been read)
@@ -1095,12 +1102,11 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                 // (3 n + 1) tau (N_b = 4 S).  The list ascends, so the first entries' minima meet the slow ones.
                 const unsigned uvd = a.cuvd[c];
                 const double tau = a.ctau[c];
-                if (tid < count) {
+                if (tid < a.live) { // (at most L <= 255: a thread each)
                     const int n = a.n_min + tid, j = imin(L - (int)(uvd >> 8 & 255), n * M - (int)(uvd >> 16));
                     const double least = a.Nb > 0 ? (double)imax(a.Nb - j, 0) * tau : (3.0 * n + 1.0) * tau;
                     if (answered(a, n) && least <= best_now(a, tid)) atomicMax(&s_nhi, n);
                 }
-                if (count > (int)blockDim.x && tid == 0) s_nhi = a.n_max;
                 wg_sync();
                 nhi = s_nhi;
                 if (nhi == 0) continue;
@@ -1108,7 +1114,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
             if (mode == kRest) {
                 c = a.list[c];
                 // the minima may have fallen below this entry's bounds by now; n beyond the last template left is no use
-                if (tid < count) {
+                if (tid < a.live) {
                     const unsigned bk = c / a.head->bucket;
                     const double x = bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + tid);
                     if (x < kNone && x <= best_now(a, tid)) atomicMax(&s_nhi, a.n_min + tid);
@@ -1118,19 +1124,19 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                 if (nhi == 0) continue;
             }
         }
-        if (!evaluate<STAGED, MT>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
+        if (!evaluate<STAGED, MT, SUM>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
             // (not the first picks: the filter keeps those that matter, so each entry comes here once at most)
             if (STAGED && mode != kFirst && tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
             continue;
         }
         if (mode != kFirst) { // let the other workgroups know
             wg_sync();
-            for (int i = tid; i < count; i += blockDim.x)
+            for (int i = tid; i < a.live; i += blockDim.x)
                 if (s_best[i] < (unsigned long long)__double_as_longlong(best_now(a, i))) atomicMin(&a.best[i], s_best[i]);
         }
     }
     wg_sync();
-    for (int i = tid; i < count; i += blockDim.x)
+    for (int i = tid; i < a.live; i += blockDim.x)
         if (s_best[i] < (unsigned long long)__double_as_longlong(best_now(a, i))) atomicMin(&a.best[i], s_best[i]);
     if (mode != kFirst && !a.staged && last_workgroup(a)) finish(a, true); // (the staged entry point: k_exact_flat follows)
 }
@@ -1285,15 +1291,16 @@ static int exact_smax(int L, int n_max, int M, int Nb) {
 static bool exact_limit_binds(int L, int n_max, int M, int Nb) { return Nb > 0 && Nb < (L < n_max * M ? L : n_max * M); }
 
 // LDS of the fast path, 0: none for this shape.
-static size_t exact_lds(int L, int M, int n_max, int Nb, bool staged) {
+static oob_exact::EvalLds exact_lds(int L, int M, int n_max, int count, int Nb, bool staged) {
+    if (!staged && !oob_exact::in_doubles(L, M, n_max, count)) return {0, false};
     const bool counts = staged && exact_limit_binds(L, n_max, M, Nb);
-    return oob_exact::eval_lds(L, M, n_max, counts ? exact_smax(L, n_max, M, Nb) + 1 : 1, counts);
+    return oob_exact::eval_lds(L, M, n_max, count, counts ? exact_smax(L, n_max, M, Nb) + 1 : 1, counts);
 }
 
 extern "C" size_t oob_exact_workspace_size(int L, int n_max, int gpus_per_node) {
     using namespace oob_exact;
     if (!exact_dims_ok(L, n_max, gpus_per_node)) return 0;
-    const bool fast = exact_lds(L, gpus_per_node, n_max, 0, false) != 0;
+    const bool fast = exact_lds(L, gpus_per_node, n_max, n_max, 0, false).bytes != 0;
     size_t n = layout(L, gpus_per_node, n_max, fast, bound_mus(L, gpus_per_node, false), false).slots;
     if (!fast) n += (size_t)kFlatSlots * slot_bytes(L, n_max * gpus_per_node, 1); // tables beyond LDS: the general path
     return n;
@@ -1307,26 +1314,27 @@ extern "C" size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per
     size_t slots = want / slot;
     slots = slots < 16 ? 16 : slots > (size_t)kFlatSlots ? (size_t)kFlatSlots : slots;
     const int mus = bound_mus(L, gpus_per_node, exact_limit_binds(L, n_max, gpus_per_node, microbatches));
-    return layout(L, gpus_per_node, n_max, exact_lds(L, gpus_per_node, n_max, microbatches, true) != 0, mus, true).slots + slots * slot;
+    return layout(L, gpus_per_node, n_max, exact_lds(L, gpus_per_node, n_max, n_max, microbatches, true).bytes != 0, mus, true).slots + slots * slot;
 }
 
-template <bool STAGED, int MT>
+template <bool STAGED, int MT, bool SUM>
 static int eval_launch_m(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
     using namespace oob_exact;
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT>,
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT, SUM>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return OOB_EHIP;
-    hipLaunchKernelGGL((k_exact_eval<STAGED, MT>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
+    hipLaunchKernelGGL((k_exact_eval<STAGED, MT, SUM>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
     return OOB_OK;
 }
 template <bool STAGED> // a kernel of its own for the usual numbers of GPUs per node, known to the compiler
 static int eval_launch(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
+    if constexpr (!STAGED) if (a.sums) return eval_launch_m<false, 0, true>(a, mode, grid, threads, lds, picks, st);
     switch (a.M) {
-    case 1: return eval_launch_m<STAGED, 1>(a, mode, grid, threads, lds, picks, st);
-    case 2: return eval_launch_m<STAGED, 2>(a, mode, grid, threads, lds, picks, st);
-    case 4: return eval_launch_m<STAGED, 4>(a, mode, grid, threads, lds, picks, st);
-    case 8: return eval_launch_m<STAGED, 8>(a, mode, grid, threads, lds, picks, st);
-    default: return eval_launch_m<STAGED, 0>(a, mode, grid, threads, lds, picks, st);
+    case 1: return eval_launch_m<STAGED, 1, false>(a, mode, grid, threads, lds, picks, st);
+    case 2: return eval_launch_m<STAGED, 2, false>(a, mode, grid, threads, lds, picks, st);
+    case 4: return eval_launch_m<STAGED, 4, false>(a, mode, grid, threads, lds, picks, st);
+    case 8: return eval_launch_m<STAGED, 8, false>(a, mode, grid, threads, lds, picks, st);
+    default: return eval_launch_m<STAGED, 0, false>(a, mode, grid, threads, lds, picks, st);
     }
 }
 
@@ -1353,11 +1361,14 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
     a.prof = *profile; a.L = L; a.M = M; a.n_min = n_min; a.n_max = n_max; a.Nb = microbatches; a.Dmax = Dmax;
     a.Smax = exact_smax(L, n_max, M, microbatches);
     a.cap = mem_cap;
+    a.nodes = imin(n_max, L); a.live = imax(0, a.nodes - n_min + 1);
     // stage counts are only carried where the limit can bind
     const bool counts = staged && exact_limit_binds(L, n_max, M, microbatches);
     const int J = counts ? a.Smax + 1 : 1;
-    const size_t lds = exact_lds(L, M, n_max, microbatches, staged);
+    const EvalLds ev = exact_lds(L, M, n_max, staged ? n_max : count, microbatches, staged); // (staged: as its workspace is sized)
+    const size_t lds = ev.bytes;
     a.fast = lds != 0;
+    a.sums = ev.sums;
     a.staged = staged;
     const size_t ntri = tri(L) * M;
     const int mus = bound_mus(L, M, counts);

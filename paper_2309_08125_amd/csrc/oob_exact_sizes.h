@@ -4,6 +4,8 @@
 
 #include <stddef.h>
 
+#include <initializer_list>
+
 #ifdef __HIPCC__
 #define OOB_HD __host__ __device__
 #else
@@ -29,13 +31,18 @@ OOB_HD inline int imin(int a, int b) { return a < b ? a : b; }
 OOB_HD inline int imax(int a, int b) { return a > b ? a : b; }
 
 // The profile in LDS (see Prof), in doubles.
-OOB_HD inline size_t prof_doubles(int L, int M) { return 2 * (size_t)(L + 1) * M + (L + 1) + ((size_t)(L + 1) * M + 7) / 8; }
+OOB_HD inline size_t prof_doubles(int L, int M, bool sums = false) {
+    return (sums ? 1 : 2) * (size_t)(L + 1) * M + (L + 1) + ((size_t)(L + 1) * M + 7) / 8;
+}
 // Entries of a band matrix with rows r = 1 .. band and columns 0 .. len - r.
 OOB_HD inline size_t band_size(int band, int len) { return (size_t)band * len - (size_t)band * (band - 1) / 2; }
 
-// Tables of k_exact_eval beside its pool and the minima: profile, reach, NP and OUT (see Eval), in doubles.
-OOB_HD inline size_t eval_fixed(int L, int M, int n_max, int J) {
-    return prof_doubles(L, M) + ((size_t)(L + 1) * M + 7) / 8 + 2 * (size_t)(L + 2) * J + 2 * (size_t)n_max * M * J + 8;
+// Tables of k_exact_eval beside its pool: profile, reach, NP, OUT (see Eval) and the minima, in doubles.  No pipeline has
+// more nodes than layers.
+OOB_HD inline size_t eval_fixed(int L, int M, int n_max, int count, int J, bool sums = false) {
+    const int nodes = imin(n_max, L);
+    return prof_doubles(L, M, sums) + ((size_t)(L + 1) * M + 7) / 8 + 2 * (size_t)(L + 2) * J + 2 * (size_t)nodes * M * J + 8 +
+           imin(count, nodes);
 }
 // Its pool for any slowest stage without stage counts, in doubles: the covers next to it, both W and one one-node table,
 // bands as wide as the sides are long.
@@ -49,18 +56,30 @@ inline int eval_threads(int L, int M, bool staged) {
     while (waves < kEvalThreads / 64 && waves * slots * 2 < L) waves *= 2;
     return waves * 64;
 }
-// LDS of k_exact_eval in bytes: without stage counts the tables of any slowest stage fit (0: they do not, the
-// shape takes the general path); with stage counts whatever is left for them, entries beyond that take
+// Whether oob_exact_minimum holds its tables in LDS, as doubles: then no other path follows and the times of a job have to stay
+// in the range where doubles are exact.  Status and workspace of a shape follow from it, so the line is a part of
+// the interface and stays where the first layout of these tables (two one-node tables, no copy of the profile) filled the LDS.
+inline bool in_doubles(int L, int M, int n_max, int count) {
+    const size_t row = (size_t)(L + 1) * M;
+    return 8 * (tri(L) + row + (row + 1) / 2 + 2 * (size_t)n_max * M + 5 * (size_t)L + (L + 1) / 2 + 5 + count +
+                2 * (size_t)(L + 4) * (M + 1) + 8) <= kLdsLimit;
+}
+// LDS of k_exact_eval.  Without stage counts the tables of any slowest stage fit (0 bytes: they do not, the
+// shape takes the general path), at the latest with the ends of the stages added up where they are read; every
+// shape of in_doubles() fits.  With stage counts whatever is left for them, entries beyond that take
 // the general path one by one.
-inline size_t eval_lds(int L, int M, int n_max, int J, bool staged) {
-    const size_t fixed = 8 * (eval_fixed(L, M, n_max, J) + n_max);
-    if (staged) return M <= 8 && fixed + 48 * 1024 <= kLdsLimit - kLdsStatic ? kLdsLimit - kLdsStatic : 0;
-    const size_t all = (fixed + 8 * eval_pool(L, M) + 15) & ~(size_t)15;
-    if (all + kLdsStatic > kLdsLimit) return 0;
-    // as many workgroups per compute unit as the registers allow (sixteen waves) and their tables leave room for: a share
-    // less its static arrays is never below `all`
-    const size_t most = 1024 / eval_threads(L, M, false), k = kLdsLimit / (all + kLdsStatic);
-    return (kLdsLimit / (k < most ? k : most) - kLdsStatic) & ~(size_t)15;
+struct EvalLds { size_t bytes; bool sums; };
+inline EvalLds eval_lds(int L, int M, int n_max, int count, int J, bool staged) {
+    if (staged) return {M <= 8 && 8 * eval_fixed(L, M, n_max, count, J) + 48 * 1024 <= kLdsLimit - kLdsStatic ? kLdsLimit - kLdsStatic : 0, false};
+    for (const bool sums : {false, true}) {
+        const size_t all = (8 * (eval_fixed(L, M, n_max, count, 1, sums) + eval_pool(L, M)) + 15) & ~(size_t)15;
+        if (all + kLdsStatic > kLdsLimit) continue;
+        // as many workgroups per compute unit as the registers allow (sixteen waves) and their tables leave room for: a share
+        // less its static arrays is never below `all`
+        const size_t most = 1024 / eval_threads(L, M, false), k = kLdsLimit / (all + kLdsStatic);
+        return {(kLdsLimit / (k < most ? k : most) - kLdsStatic) & ~(size_t)15, sums};
+    }
+    return {0, false};
 }
 
 // No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second

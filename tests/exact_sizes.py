@@ -13,8 +13,9 @@ int wrong_quotient(int M) {
     for (int i = 0; i < 256 * M; ++i) if (quot(i, recip(M)) != i / M) return i;
     return -1;
 }
-// LDS of k_exact_eval for each accepted n_max of (L, M) against the tables of its largest slowest stage, the bands as wide
-// as the sides: the smallest surplus in doubles over all that take the LDS path (1 << 30: none does).
+// LDS of k_exact_eval for each accepted n_max of (L, M), one template and all of them, against the tables of its largest
+// slowest stage, the bands as wide as the sides: the smallest surplus in doubles over all that take the LDS path
+// (1 << 30: none does); -2 for a shape whose times have to stay exact in doubles and that has no tables in LDS.
 int smallest_surplus(int L, int M) {
     size_t tables = 0; // covers next to the stage, both W, one one-node table, by the layers before it
     for (int P = 0; P <= L - 1; ++P) {
@@ -23,14 +24,21 @@ int smallest_surplus(int L, int M) {
         tables = n > tables ? n : tables;
     }
     int least = 1 << 30;
-    for (int n = 1; n * M <= 4096; ++n) {
-        const size_t lds = eval_lds(L, M, n, 1, false);
-        if (lds == 0) continue;
-        if (lds > kLdsLimit - kLdsStatic) return -1;
-        const long long pool = (long long)(lds / 8) - (long long)(eval_fixed(L, M, n, 1) + n), surplus = pool - (long long)tables;
-        if (surplus < least) least = (int)surplus;
-    }
+    for (int n = 1; n * M <= 4096; ++n)
+        for (int count : {1, n}) {
+            const EvalLds e = eval_lds(L, M, n, count, 1, false);
+            if (e.bytes == 0) { if (in_doubles(L, M, n, count)) return -2; else continue; }
+            if (e.bytes > kLdsLimit - kLdsStatic) return -1;
+            const long long pool = (long long)(e.bytes / 8) - (long long)eval_fixed(L, M, n, count, 1, e.sums);
+            const long long surplus = pool - (long long)tables;
+            if (surplus < least) least = (int)surplus;
+        }
     return least;
+}
+// whether the tables of (L, M, n_max) for all templates leave out the ends of the stages; -1: no tables in LDS
+int sums(int L, int M, int n_max) {
+    const EvalLds e = eval_lds(L, M, n_max, n_max, 1, false);
+    return e.bytes ? e.sums : -1;
 }
 // offsets in the workspace of a job that takes the LDS path: times and stages of the list, its bounds, the leftovers
 void offsets(int L, int M, int n_max, int counts, int staged, size_t *at) {

@@ -256,6 +256,36 @@ def test_shares_of_the_lds_that_just_hold_the_tables(P, shape):
         assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
 
 
+@pytest.mark.parametrize("shape", [(72, 64, 1, 1, 0), (105, 32, 1, 2, 105), (142, 16, 1, 2, 0), (167, 8, 1, 3, 167), (178, 5, 1, 2, 0)])
+def test_tables_in_lds_without_the_ends_of_the_stages(P, sizes, shape):
+    """The largest shapes whose times are held as doubles: their tables leave no room for the ends of the
+    stages, which are added up where they are read; a small workspace."""
+    L, M, n_min, n_max, nb = shape
+    assert sizes.sums(L, M, n_max) == 1 and P.oob_exact_workspace_size(L, n_max, M) < (16 << 20)
+    for var in ("plain", "forbid"):
+        inp = inputs.random_small(17, L, M, n_min, n_max, nb, f=1, forbid_some_d=(var == "forbid"))
+        print("case", shape, var, flush=True)
+        st, got = P.ExactMinimum(inp).run()
+        assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
+
+
+@pytest.mark.parametrize("shape", [(192, 1, 1, 8, 192), (189, 2, 1, 2, 0), (171, 8, 1, 1, 0)])
+def test_shapes_beyond_doubles_take_times_beyond_them(P, sizes, shape):
+    """Shapes whose tables would fit the LDS but whose times may exceed 2^52: answered in 64-bit integers."""
+    import dataclasses
+
+    L, M, n_min, n_max, nb = shape
+    assert sizes.sums(L, M, n_max) >= 0
+    inp = inputs.random_small(19, L, M, n_min, n_max, nb, f=1)
+    for add in (0, 1 << 42):
+        big = dataclasses.replace(inp, fwd_ns=inp.fwd_ns + add)
+        want = E.exact_minimum(big)
+        for staged in (False, True):
+            print("case", shape, add, staged, flush=True)
+            st, got = P.ExactMinimum(big, staged=staged).run()
+            assert st == P.OOB_OK and got == want, (shape, add, staged)
+
+
 def test_leftovers_with_stage_counts_are_listed_once(P, sizes):
     """Slowest stages whose tables exceed LDS are left to the general path: each at most once, whatever the
     number of templates that pick it first."""
