@@ -1151,9 +1151,12 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
 // One workgroup takes one candidate slowest stage at a time (a grid-stride loop), walks the layers
 // with two barriers per layer (the stage times into / out of the layer are staged in LDS), each
 // thread owning (GPUs, stages) positions.
+// Eight waves per SIMD are asked for: the up to kFlatSlots = 2 048 workgroups then run all at once.  Left to itself the compiler
+// takes 106 scalar registers, which leaves seven, and the last eighth runs alone: 20.8 against 17.5 ms for 30 layers,
+// 16 GPUs per node, 4 nodes, N_b = 20, and 64.0 against 48.3 ms for 60 layers, 2 nodes, N_b = 6.
 // ---------------------------------------------------------------------------------------------
 template <bool STAGED>
-__global__ void __launch_bounds__(kThreads) k_exact_flat(Args a) {
+__global__ void __launch_bounds__(kThreads, 8) k_exact_flat(Args a) {
     HIP_DYNAMIC_SHARED(long long, s_flat) // [L * M] stage times into (or out of) the current layer, then [count] minima
     const int L = a.L, M = a.M, W = a.Dmax + 1, J = STAGED ? a.Smax + 1 : 1, count = a.n_max - a.n_min + 1;
     long long *s_col = s_flat, *s_best = s_flat + (size_t)L * M;
