@@ -130,8 +130,9 @@ __global__ void __launch_bounds__(1024) k_inst_count(Spec s, long long *offsets,
 // is a line of its own, and the 32-bit copy was a further pass that waited for a read of memory per 1 024 counts; here
 // kGroup planes are kept and written as whole pieces of their rows.  The pair (N', q) of a thread's entries comes
 // from one division per thread instead of one per entry and plane.  The planes are counted in 32 bits with
-// saturating additions first; only where that saturates (or the 64-bit table is asked for) they are counted
-// again in 64 bits, which writes both tables.
+// saturating additions first; from the first group of planes that saturates (the first of all where the 64-bit table
+// is asked for) they are counted in 64 bits.  (A second pass over all planes from the start: 190 us for the 150
+// sizes 1..150, f = 3, up to 128 nodes, whose last planes outgrow 32 bits; 110 us here; two planes at a time in 64 bits 113 us.)
 // 56 sizes of 8..64 from a list, f = 8, up to 128 nodes: 44 us, 59 us with 64 bits throughout; counting and listing
 // 217 -> 152 us as a caller sees them.  29 sizes 4..32, f = 4: 17 us, 21 us with 64 bits.
 constexpr size_t kRingLdsBytes = 152 * 1024; // beside 4 KB of sizes, of the 160 KB of a compute unit
@@ -147,19 +148,20 @@ __device__ __forceinline__ unsigned long long add_terms(unsigned long long sum, 
     return c > (unsigned long long)kSat ? (unsigned long long)kSat : c;
 }
 
-// All planes of the table in CT; the last one stays in the ring.  Returns the largest count of this thread's entries of
-// the last plane (no plane before holds a larger one).  Called and left by the whole workgroup.
-template <typename CT> __device__ CT count_planes(const Spec &s, CT *ring, const int *size) {
+// The planes from the group that starts with plane `base` on, in CT; the plane before them is in the ring, the last one
+// stays there.  In 32 bits it ends before a group with a count that does not fit, sets *top to it and returns the group's
+// first plane, else p + 1; in 64 bits *top is raised to the largest count (of the last plane: no plane before holds a
+// larger one).  Called and left by the whole workgroup.
+template <typename CT> __device__ int count_planes(const Spec &s, CT *ring, const int *size, int base, CT *top) {
     const int QQ = s.Q + 1, plane = (s.N_hi + 1) * QQ;
     const int N0 = (int)threadIdx.x / QQ, q0 = (int)threadIdx.x - N0 * QQ;
     const int dN = kCountThreads / QQ, dq = kCountThreads - dN * QQ; // from one entry of a thread to its next
-    for (int e = threadIdx.x; e < plane; e += kCountThreads) ring[e] = e == 0 ? 1 : 0; // C(0, ., .)
-    __syncthreads();
     CT mine = 0;
-    for (int j = 1; j <= s.p; ++j) {
+    for (int j = base > 0 ? base : 1; j <= s.p; ++j) {
         const int n = size[j - 1], nq = n * QQ;
         const CT *prev = ring + ((j - 1) & (kGroup - 1)) * plane;
         CT *cur = ring + (j & (kGroup - 1)) * plane;
+        const bool write = (j & (kGroup - 1)) == kGroup - 1 || j == s.p; // the group is complete
         int N = N0, q = q0;
         for (int e = threadIdx.x; e < plane; e += kCountThreads) {
             CT sum = 0;
@@ -175,13 +177,17 @@ template <typename CT> __device__ CT count_planes(const Spec &s, CT *ring, const
                 qi = qi > 2 ? qi - 2 : 0;
             }
             cur[e] = sum;
-            if (j == s.p) mine = sum > mine ? sum : mine;
+            if (write) mine = sum > mine ? sum : mine;
             N += dN; q += dq;
             if (q >= QQ) { q -= QQ; ++N; }
         }
+        if (sizeof(CT) == 4) {
+            if (write && mine == (CT)~(CT)0) *top = mine; // (every writer the same)
+        } else if (j == s.p) atomicMax(top, mine);
         __syncthreads(); // plane j complete
+        if (!write) continue;
         const int last = j & (kGroup - 1), base = j - last;
-        if (last != kGroup - 1 && j != s.p) continue;
+        if (sizeof(CT) == 4 && *top == (CT)~(CT)0) return base; // uniform
         // planes base..j; what follows in a row compares greater than any list position (slots past `last` hold older
         // planes or nothing: read, not used)
         if constexpr (sizeof(CT) == 4) {
@@ -208,7 +214,7 @@ template <typename CT> __device__ CT count_planes(const Spec &s, CT *ring, const
         }
         __syncthreads(); // the next plane overwrites the first slot
     }
-    return mine;
+    return s.p + 1;
 }
 
 // Exclusive prefix over N' = N_lo..N_hi of the filtered list lengths C(p, N', f+1), by one wave.
@@ -252,18 +258,33 @@ __global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long 
         if (threadIdx.x == 0) { *status = OOB_EINVAL; *s.narrow = 0; }
         return;
     }
+    const int plane = (s.N_hi + 1) * (s.Q + 1);
+    int base = 0; // of the planes to count in 64 bits
     if (!keep_wide) {
         unsigned *ring = reinterpret_cast<unsigned *>(s_ring);
-        atomicMax(&s_max32, count_planes(s, ring, s_size));
+        for (int e = threadIdx.x; e < plane; e += kCountThreads) ring[e] = e == 0 ? 1 : 0; // C(0, ., .)
         __syncthreads();
-        if (s_max32 != 0xFFFFFFFFu) { // uniform: no addition saturated
+        base = count_planes(s, ring, s_size, 0, &s_max32);
+        if (base > s.p) { // uniform: every count fits
             if (threadIdx.x < 64) write_offsets(s, ring, offsets, status);
             if (threadIdx.x == 0) *s.narrow = 1;
             return;
         }
+        // the groups before: from the 32-bit table, half a group a thread and step
+        const int halves = base / (kGroup / 2);
+        for (int i = threadIdx.x; i < plane * halves; i += kCountThreads) {
+            const int e = i / halves, k = (i - e * halves) * (kGroup / 2);
+            const uint4 v = *reinterpret_cast<const uint4 *>(s.cnt32 + (long long)e * s.R + k);
+            ulonglong2 *wide = reinterpret_cast<ulonglong2 *>(s.cnt + (long long)e * s.R + k);
+            wide[0] = make_ulonglong2(v.x, v.y);
+            wide[1] = make_ulonglong2(v.z, v.w);
+        }
     }
-    atomicMax(&s_max, count_planes(s, s_ring, s_size));
+    const int before = base > 0 ? kGroup - 1 : 0; // slot of the plane before (of plane 0 itself)
+    for (int e = threadIdx.x; e < plane; e += kCountThreads)
+        s_ring[before * plane + e] = base > 0 ? s.cnt32[(long long)e * s.R + base - 1] : e == 0 ? 1 : 0;
     __syncthreads();
+    count_planes(s, s_ring, s_size, base, &s_max);
     if (threadIdx.x < 64) write_offsets(s, s_ring, offsets, status);
     if (threadIdx.x == 0) *s.narrow = s_max < (1ull << 32) && !keep_wide;
 }

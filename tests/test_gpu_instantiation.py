@@ -163,3 +163,34 @@ def test_list_lengths_beyond_32_bits(P, N_hi, p, f):
     off, st = P.Instantiator(None, N_lo, N_hi, f, n0=1, p=p).count()
     assert off.tolist() == [min(w, 1 << 62) for w in want]
     assert st == (P.OOB_OK if want[-1] < 1 << 62 else P.OOB_EOVERFLOW)
+
+
+@pytest.mark.parametrize("N_hi,p,f,first", [(1200, 9, 0, 6), (600, 8, 0, 7), (365, 20, 3, 8), (340, 9, 3, 9), (250, 12, 3, 10),
+                                            (135, 24, 3, 24), (140, 60, 3, 21), (128, 128, 3, 53)])
+def test_table_that_outgrows_32_bits_on_the_way(P, N_hi, p, f, first):
+    """Counts that fit 32 bits up to a plane, at any place in its group of eight planes: from there on 64 bits, and the
+    planes before are widened.  The same table as counted in 64 bits from the start."""
+    import torch
+
+    C = [[0] * (f + 2) for _ in range(N_hi + 1)]
+    C[0][0] = 1
+    planes = [[row[:] for row in C]]
+    for n in range(1, p + 1):
+        for x in range(n, N_hi + 1):
+            C[x] = [C[x][q] + C[x - n][max(q - 1, 0)] for q in range(f + 2)]
+        planes.append([row[:] for row in C])
+    assert [max(map(max, c)) >= (1 << 32) - 1 for c in planes].index(True) == first
+    R = (p + 8) // 8 * 8
+    want = np.array(planes).transpose(1, 2, 0)                              # [N'][q][j]
+    lib = P.load()
+    for wide in (1, 0):
+        lib.oob_inst_keep_wide_table(wide)
+        try:
+            inst = P.Instantiator(None, N_hi, N_hi, f, n0=1, p=p)
+            off, st = inst.count()
+        finally:
+            lib.oob_inst_keep_wide_table(0)
+        assert st == P.OOB_OK and int(off[-1]) == planes[p][N_hi][f + 1]
+        n = (N_hi + 1) * (f + 2) * R
+        table = inst.workspace[256: 256 + 8 * n].view(torch.int64).reshape(N_hi + 1, f + 2, R)[:, :, : p + 1]
+        assert np.array_equal(table.cpu().numpy(), want), wide
