@@ -270,16 +270,20 @@ __global__ void __launch_bounds__(kLanes) k_dist_solve(Args a) {
 }
 
 // Plan choice: the smallest `slowest` among the solved plans of a group, the first of equals.
-// Workgroup (g, y) reduces every gridDim.y-th stretch of kChooseThreads plans of group g (lanes keep the
-// first minimum of their strided share, waves and then the workgroup combine (value, index) pairs
+// Workgroup (g, y) reduces every s-th stretch of kChooseThreads plans of group g, s = as many workgroups as have
+// kChoosePlans plans each (lanes keep the first minimum of their strided share, waves and then the workgroup combine (value, index) pairs
 // lexicographically) and merges its winner into best[group] with a compare-and-swap on the index:
 // `slowest` does not change during the launch, so "is plan i better than the plan best[group]
 // names now" is decided by reading both values, and the loop ends as soon as the entry names a plan
 // that is at least as good.  k_dist_choose_init sets every entry to -1 ("no plan") first.
-// Workgroups over stretches of the whole list walked the groups of their stretch one after the other, and the
-// small groups share one stretch: 56 us for 1 343 380 plans in 57 groups and 45 us for 10 251 in 29, against 25 and 5 us.
+// Workgroups over stretches of the whole list, which walk the groups of their stretch one after the other: 33 us for
+// 1 343 380 plans in 57 groups, 32 for 10 251 in 29, 25 for a million in 4 000 groups of one size, 760 in 4 000 groups of
+// five; here 15, 7, 10 and 10 us.  64 workgroups for every group, whatever its size: 25, 6, 60 and 60 us (and 865 for
+// 60 000 groups, 72 here).
 constexpr int kChooseThreads = 256, kChooseLoads = 4;
-constexpr long long kChooseMaxSlices = 64; // slices of a group; a group rarely holds more than a tenth of the plans
+// Fewer plans to a workgroup than these and what takes the time is the merging, one winner of a group after the other;
+// many groups get few workgroups each, because those without plans have to be launched too.
+constexpr long long kChooseMaxSlices = 64, kChoosePlans = 2048, kChooseWorkgroups = 16384;
 __global__ void k_dist_choose_init(long long *best, int segments) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g < segments) best[g] = -1;
@@ -293,8 +297,9 @@ __global__ void __launch_bounds__(kChooseThreads) k_dist_choose(const long long 
     __shared__ long long s_v[kChooseThreads / 64], s_i[kChooseThreads / 64];
     const int g = blockIdx.x;
     const long long lo = offsets[g], most = offsets[0] + count, hi = offsets[g + 1] < most ? offsets[g + 1] : most;
-    const long long stride = (long long)gridDim.y * kChooseThreads;
-    if (lo + (long long)blockIdx.y * kChooseThreads >= hi) return; // the same for the whole workgroup
+    const long long slices = std::min<long long>(gridDim.y, (hi - lo + kChoosePlans - 1) / kChoosePlans);
+    const long long stride = slices * kChooseThreads;
+    if ((long long)blockIdx.y >= slices) return; // the same for the whole workgroup (every slice has plans)
     long long bv = 0, bi = -1;
     for (long long i0 = lo + (long long)blockIdx.y * kChooseThreads + threadIdx.x; i0 < hi; i0 += stride * kChooseLoads) {
         long long v[kChooseLoads];
@@ -351,7 +356,8 @@ extern "C" int oob_dist_choose(const int64_t *offsets, int segments, int64_t cou
     using namespace oob_dist;
     if (!offsets || !slowest || !status || !best || segments < 0 || count < 0) return OOB_EINVAL;
     if (segments == 0) return OOB_OK;
-    const long long slices = std::min<long long>((count + kChooseThreads - 1) / kChooseThreads, kChooseMaxSlices);
+    const long long slices = std::min({(count + kChoosePlans - 1) / kChoosePlans, kChooseMaxSlices,
+                                       std::max(1ll, kChooseWorkgroups / segments)});
     hipLaunchKernelGGL(k_dist_choose_init, dim3((unsigned)((segments + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                        (long long *)best, segments);
     if (slices > 0)

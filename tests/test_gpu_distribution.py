@@ -160,7 +160,8 @@ def test_choice_of_the_plan_against_the_oracle(P):
     assert checked >= 15
 
 
-@pytest.mark.parametrize("groups", [[1], [0, 255, 256, 257, 0], [70000, 3, 65537], [5] * 300])
+@pytest.mark.parametrize("groups", [[1], [0, 255, 256, 257, 0], [70000, 3, 65537], [5] * 300, [2047, 2048, 2049, 4097], [140000],
+                                    [1, 0, 2] * 6000, [1] * 300 + [9000]])
 def test_choice_in_groups_of_any_size(P, groups):
     """Groups below, at and above the shares of a workgroup, empty ones, more groups than lanes; few distinct times, so
     that the first of equals decides, and plans that cannot be distributed."""
