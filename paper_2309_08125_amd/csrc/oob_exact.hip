@@ -663,7 +663,7 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
     const int j = STAGED ? xs + 1 : 1;
     const int XS = STAGED ? 1 : 1 << lgxs, x0 = STAGED ? 0 : xs;
     const int row_n = STAGED ? staged_row(M) : M + 1;               // entries per row of a table
-    double *T = G + (size_t)slot * (band + 1) * row_n;
+    double *T = G + (size_t)(slot < slots ? slot : 0) * (band + 1) * row_n; // (lanes beyond the tables read one and use nothing of it)
     const int g = gi + 1, rows = live ? imin(band, len - idx) : 0;
     const bool use = live && (!STAGED || j <= g);                   // this lane has an entry in every row
     const int q = live ? (MIRROR ? L - idx : idx) : 0;                           // start layer
