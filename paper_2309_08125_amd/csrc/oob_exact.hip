@@ -69,7 +69,8 @@ struct Args {
     oob_profile prof;
     int L, M, n_min, n_max, Nb, Dmax, Smax, fast, staged, bounds;
     int sums;             // the profile without the ends of the stages (EvalLds)
-    int nodes, live;      // min(n_max, L): more nodes than layers make no pipeline; templates up to there
+    int nodes;            // min(n_max, L): more nodes than layers make no pipeline
+    int top, live;        // last template that can get a minimum (answered(), nodes), number of templates up to it
     long long cap;
     long long limit;      // every cost must stay below this (2^52 for the LDS path, 2^61 otherwise)
     Head *head;
@@ -455,15 +456,17 @@ __device__ int fewest_nodes(int L, int M, const unsigned char *reach, unsigned c
 __device__ __forceinline__ double spent(const Args &a, int k, int n) {
     return (a.Nb > 0 ? kLambdaGiven[k % kLambdas] : kLambda4S[k % kLambdas]) * (n * a.M) + kMuStep[k / kLambdas] * a.Smax;
 }
-// The bound of an entry (its values lb[0 .. nk-1]) of a bucket for n nodes; below all doubt where there is none.
+// The bound of an entry (its values lb[0 .. nk-1]) of a bucket for n <= a.top nodes; below all doubt where there is none.
 __device__ __forceinline__ double bound_of(const Args &a, const float *lb, double lo, int fewest, int n) {
-    if (n < fewest || n > a.L || !answered(a, n)) return kNone;
+    if (n < fewest) return kNone;
     double x = -kNone;
     for (int k = 0; k < a.nk; ++k) x = fmax(x, (double)lb[k] - lo * spent(a, k, n));
     return x;
 }
+// Six waves per SIMD asked for where M is known: 78 registers, which is also the faster schedule of the rows (170 us at 98 layers x
+// 8 GPUs, against 207 with the 94 that the compiler takes by itself; it stays at two workgroups per compute unit either way).
 template <int MT>
-__global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus) {
+__global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args a, int mus) {
     constexpr int CW = MT ? MT : 8;
     HIP_DYNAMIC_SHARED(double, s_dyn)
     __shared__ unsigned long long s_lo, s_hi;
@@ -581,7 +584,7 @@ __global__ void __launch_bounds__(kBoundThreads) k_exact_bounds(Args a, int mus)
         }
         wg_sync();
         // lanes: templates; the entries shared out among the waves
-        for (int ni = lane; ni < count; ni += 64)
+        for (int ni = lane; ni < a.live; ni += 64)
             for (int q = wave; q < m; q += nw) {
                 const double x = bound_of(a, s_lb + q * nk, lo, s_fewest, a.n_min + ni);
                 if (x < (double)mine) { mine = __double2float_rd(x); arg = m0 + q; }
@@ -610,15 +613,15 @@ __device__ __forceinline__ double best_now(const Args &a, int i) {
 // A wave looks through 64 consecutive entries, lanes = templates, and appends what is left with one atomic.
 __global__ void __launch_bounds__(256) k_exact_filter(Args a) {
     if (*a.status != OOB_OK || !a.head->narrow) return;
-    const unsigned lane = threadIdx.x & 63, total = a.head->ncand, count = (unsigned)(a.n_max - a.n_min + 1);
+    const unsigned lane = threadIdx.x & 63, total = a.head->ncand, live = (unsigned)a.live;
     const unsigned c0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
     if (c0 >= total) return;
-    const double best = lane < count ? __longlong_as_double((long long)a.best[lane]) : -1.0;
+    const double best = lane < live ? __longlong_as_double((long long)a.best[lane]) : -1.0;
     unsigned long long keep = 0;
     const unsigned K = a.head->bucket;
     for (unsigned q = 0; q < 64 && c0 + q < total; ++q) {
         const unsigned c = c0 + q, bk = c / K;
-        const double x = lane < count ? bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + (int)lane) : kNone;
+        const double x = lane < live ? bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + (int)lane) : kNone;
         if (__any(x < kNone && x <= best)) keep |= 1ull << q;
     }
     unsigned at = 0;
@@ -636,7 +639,7 @@ struct Eval {
     Prof pr;
     unsigned char *reach; // [(L+1) M] of a stage into a layer p <= u / out of a layer p >= v
     double *pool;         // GU, W, then the waves' one-node tables
-    long long pool_n;
+    unsigned pool_n;      // (sizes of tables are unsigned 32-bit numbers: signed ones cost k_exact_eval<false, 8> 16 more spilled registers, 64 bits 6)
     double *GU;           // [two sides][band][M, or staged_row(M)] covers next to the slowest stage, by the distance covered
     double *NP;           // [2 buffers][len+1 of both sides][J]
     double *OUT;          // [two sides][nodes][M][J] a whole nodes and g more GPUs
@@ -836,7 +839,7 @@ __device__ __forceinline__ void node_chain_any(int len, int band, int cend, cons
 }
 
 // The slowest stage at every place it fits: ca whole nodes and g GPUs before it, cb whole nodes and M - d - g
-// GPUs after it, n = ca + cb + 1, for every template whose stage limit cannot bind (or obeying it).
+// GPUs after it, n = ca + cb + 1, for every template up to nhi <= a.top.
 template <bool STAGED>
 __device__ void combine(const Args &a, const Eval &e, int d, double tau, int nhi, int cendP, int cendS, double mid,
                         unsigned long long *s_best) {
@@ -844,7 +847,7 @@ __device__ void combine(const Args &a, const Eval &e, int d, double tau, int nhi
     const int places = M - d + 1;
     for (int i = threadIdx.x; i < cendP * cendS; i += blockDim.x) {
         const int ca = i / cendS, cb = i - ca * cendS, n = ca + cb + 1;
-        if (n < a.n_min || n > nhi || !answered(a, n)) continue;
+        if (n < a.n_min || n > nhi) continue;
         double m = kNone;
         for (int g = 0; g < places; ++g) {
             if (!STAGED) m = fmin(m, e.OUT[ca * M + g] + e.OUT[(a.nodes + cb) * M + (M - d - g)]);
@@ -953,7 +956,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     // start layer (nodes against layers per node), and the covers next to the slowest stage are their last rows
     {
         const int nd = imax(cendP, cendS) * M, jd = STAGED ? imin(J, nd + 1) : 1;
-        const long long need = ((long long)lenP + 1 + lenS + 1) * nd * jd;
+        const unsigned need = ((unsigned)lenP + 1 + lenS + 1) * nd * jd; // below 2^29
         if (nhi * 4 <= imax(bandP, bandS) && need <= e.pool_n) {
             const int row_n = nd * jd;
             const int second = (lenP + 1) * row_n; // the other side's table
@@ -983,7 +986,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     const size_t gu = STAGED ? row_n : M;
     e.GU = e.pool;
     double *WP = e.GU + (bandP + bandS) * gu, *WS = WP + band_size(bandP, lenP) * mult, *G = WS + band_size(bandS, lenS) * mult;
-    const long long used = G - e.pool, table = (long long)(imax(bandP, bandS) + 1) * row_n;
+    const unsigned used = (unsigned)(G - e.pool), table = (unsigned)(imax(bandP, bandS) + 1) * row_n;
     if (used + table > e.pool_n) return false; // (without stage counts they fit: eval_pool())
     const int fit = (int)((e.pool_n - used) / table); // one-node tables side by side
     // ---- phase 1
@@ -1012,7 +1015,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
         }
     }
     // ---- phase 2: node after node, both sides at once.  Narrow bands: one wave each
-    const long long histP = (long long)cendP * (bandP + 1), histS = (long long)cendS * (bandS + 1);
+    const unsigned histP = (unsigned)cendP * (bandP + 1), histS = (unsigned)cendS * (bandS + 1);
     if (!STAGED && imax(bandP, bandS) <= kChainBand && imax(lenP, lenS) <= kChainLen && used + histP + histS <= e.pool_n) {
         double *HP = G; // (in place of the one-node tables)
         wg_sync();
@@ -1062,7 +1065,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     e.NP = p;     p += 2 * (size_t)(L + 2) * J;
     e.OUT = p; p += 2 * (size_t)a.nodes * M * J;
     unsigned long long *s_best = (unsigned long long *)p; p += a.live;
-    e.pool = p; e.pool_n = lds_doubles - (p - s_dyn);
+    e.pool = p; e.pool_n = (unsigned)(lds_doubles - (p - s_dyn));
     e.ints = s_ints;
     for (int i = tid; i < a.live; i += blockDim.x) s_best[i] = kNoneBits;
     const unsigned total = mode == kRest ? a.head->alive : a.head->ncand;
@@ -1105,7 +1108,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                 if (tid < a.live) { // (at most L <= 255: a thread each)
                     const int n = a.n_min + tid, j = imin(L - (int)(uvd >> 8 & 255), n * M - (int)(uvd >> 16));
                     const double least = a.Nb > 0 ? (double)imax(a.Nb - j, 0) * tau : (3.0 * n + 1.0) * tau;
-                    if (answered(a, n) && least <= best_now(a, tid)) atomicMax(&s_nhi, n);
+                    if (least <= best_now(a, tid)) atomicMax(&s_nhi, n);
                 }
                 wg_sync();
                 nhi = s_nhi;
@@ -1364,7 +1367,9 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
     a.prof = *profile; a.L = L; a.M = M; a.n_min = n_min; a.n_max = n_max; a.Nb = microbatches; a.Dmax = Dmax;
     a.Smax = exact_smax(L, n_max, M, microbatches);
     a.cap = mem_cap;
-    a.nodes = imin(n_max, L); a.live = imax(0, a.nodes - n_min + 1);
+    a.nodes = imin(n_max, L);
+    a.top = staged || microbatches == 0 || microbatches >= L ? a.nodes : imin(a.nodes, microbatches / M); // as answered(): n M <= N_b
+    a.live = imax(0, a.top - n_min + 1);
     // stage counts are only carried where the limit can bind
     const bool counts = staged && exact_limit_binds(L, n_max, M, microbatches);
     const int J = counts ? a.Smax + 1 : 1;
