@@ -230,6 +230,27 @@ def test_jobs_large_enough_for_bounds(P, shape):
         assert st == P.OOB_OK and got == want, (shape, var)
 
 
+@pytest.mark.parametrize("shape", [(100, 1, 20, 92, 0), (66, 2, 1, 66, 132), (66, 2, 3, 68, 132)])
+def test_more_templates_than_bounds_are_kept_for(P, shape):
+    """More than 64 templates: every stage is evaluated but those too dear by their time alone."""
+    L, M, n_min, n_max, nb = shape
+    assert n_max - n_min + 1 > 64 and L * (L + 1) // 2 * M > 4096
+    for var in ("plain", "tight", "forbid"):
+        inp = inputs.random_small(23, L, M, n_min, n_max, nb, f=1, tight_mem=(var == "tight"), forbid_some_d=(var == "forbid"))
+        st, got = P.ExactMinimum(inp).run()
+        assert st == P.OOB_OK and got == E.exact_minimum(inp), (shape, var)
+
+
+def test_buckets_of_more_entries_than_are_bounded_at_once(P, sizes):
+    """More possible slowest stages than 512 buckets of 64 hold."""
+    inp = inputs.random_small(29, 98, 8, 1, 2, 98, f=1)
+    e = P.ExactMinimum(inp)
+    st, got = e.run()
+    h = exact_sizes.head(e.workspace)
+    assert h["bucket"] > 64 and h["nbuckets"] <= 512
+    assert st == P.OOB_OK and got == E.exact_minimum(inp)
+
+
 @pytest.mark.parametrize("shape", [(74, 31, 1, 2, 0), (66, 32, 1, 2, 66), (46, 48, 1, 2, 0), (30, 60, 1, 2, 30), (20, 64, 1, 2, 0),
                                    (26, 64, 1, 1, 0)])
 def test_many_gpus_per_node_with_tables_in_lds(P, shape):
@@ -244,10 +265,11 @@ def test_many_gpus_per_node_with_tables_in_lds(P, shape):
         assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
 
 
-@pytest.mark.parametrize("shape", [(35, 1, 1, 1389, 0), (31, 2, 1, 840, 62), (1, 1, 1, 1681, 0), (90, 1, 4, 69, 90), (10, 1, 1, 1641, 10)])
+@pytest.mark.parametrize("shape", [(35, 1, 1, 1389, 0), (31, 2, 1, 840, 62), (1, 1, 1, 1681, 0), (90, 1, 4, 69, 90), (10, 1, 1, 1641, 10),
+                                   (130, 2, 1, 3, 0), (105, 1, 1, 104, 105), (100, 3, 2, 2, 0), (88, 2, 4, 4, 88)])
 def test_shares_of_the_lds_that_just_hold_the_tables(P, shape):
-    """Two, three or four workgroups per compute unit, their tables next to the whole of their share; far
-    more nodes than layers."""
+    """Far more nodes than layers (tables as for as many nodes as layers), and two, three or four workgroups per compute
+    unit whose tables take the whole of their share."""
     L, M, n_min, n_max, nb = shape
     for var in ("plain", "tight"):
         inp = inputs.random_small(5, L, M, n_min, n_max, nb, f=1, tight_mem=(var == "tight"))
