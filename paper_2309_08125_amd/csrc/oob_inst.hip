@@ -132,9 +132,10 @@ __global__ void __launch_bounds__(1024) k_inst_count(Spec s, long long *offsets,
 // from one division per thread instead of one per entry and plane.  The planes are counted in 32 bits with
 // saturating additions first; from the first group of planes that saturates (the first of all where the 64-bit table
 // is asked for) they are counted in 64 bits.  (A second pass over all planes from the start: 190 us for the 150
-// sizes 1..150, f = 3, up to 128 nodes, whose last planes outgrow 32 bits; 110 us here; two planes at a time in 64 bits 113 us.)
-// 56 sizes of 8..64 from a list, f = 8, up to 128 nodes: 44 us, 59 us with 64 bits throughout; counting and listing
-// 217 -> 152 us as a caller sees them.  29 sizes 4..32, f = 4: 17 us, 21 us with 64 bits.
+// sizes 1..150, f = 3, up to 128 nodes, whose last planes outgrow 32 bits; 104 us here; two planes at a time in 64 bits 113 us.)  The loop over
+// the planes of a group has no exit of its own: with one the 57 sizes 8..64 take 47 us in place of 43.4.
+// 56 sizes of 8..64 from a list, f = 8, up to 128 nodes: 43 us, 59 us with 64 bits throughout; counting and listing
+// 217 -> 150 us as a caller sees them.  29 sizes 4..32, f = 4: 16 us, 21 us with 64 bits.
 constexpr size_t kRingLdsBytes = 152 * 1024; // beside 4 KB of sizes, of the 160 KB of a compute unit
 constexpr int kCountThreads = 1024;
 static_assert(kGroup == 8, "a row's piece is stored as two or four vectors");
@@ -148,59 +149,59 @@ __device__ __forceinline__ unsigned long long add_terms(unsigned long long sum, 
     return c > (unsigned long long)kSat ? (unsigned long long)kSat : c;
 }
 
-// The planes from the group that starts with plane `base` on, in CT; the plane before them is in the ring, the last one
-// stays there.  In 32 bits it ends before a group with a count that does not fit, sets *top to it and returns the group's
+// The planes from the group that starts with plane `first` on, in CT; the plane before them is in the ring, the last one
+// stays there.  In 32 bits it ends after a group with a count that does not fit, sets *top to it and returns the group's
 // first plane, else p + 1; in 64 bits *top is raised to the largest count (of the last plane: no plane before holds a
 // larger one).  Called and left by the whole workgroup.
-template <typename CT> __device__ int count_planes(const Spec &s, CT *ring, const int *size, int base, CT *top) {
+template <typename CT> __device__ int count_planes(const Spec &s, CT *ring, const int *size, int first, CT *top) {
     const int QQ = s.Q + 1, plane = (s.N_hi + 1) * QQ;
     const int N0 = (int)threadIdx.x / QQ, q0 = (int)threadIdx.x - N0 * QQ;
     const int dN = kCountThreads / QQ, dq = kCountThreads - dN * QQ; // from one entry of a thread to its next
     CT mine = 0;
-    for (int j = base > 0 ? base : 1; j <= s.p; ++j) {
-        const int n = size[j - 1], nq = n * QQ;
-        const CT *prev = ring + ((j - 1) & (kGroup - 1)) * plane;
-        CT *cur = ring + (j & (kGroup - 1)) * plane;
-        const bool write = (j & (kGroup - 1)) == kGroup - 1 || j == s.p; // the group is complete
-        int N = N0, q = q0;
-        for (int e = threadIdx.x; e < plane; e += kCountThreads) {
-            CT sum = 0;
-            int Ni = N, qi = q, at = e; // at = Ni * QQ + qi
-            for (;;) {
-                const bool two = Ni >= n;
-                const int second = two ? at - nq - (qi > 0) : at;
-                const CT c0 = prev[at], c1 = prev[second];
-                sum = add_terms(sum, c0, two ? c1 : (CT)0);
-                if (Ni - n < n) break;
-                Ni -= 2 * n;
-                at = second - nq - (qi > 1);
-                qi = qi > 2 ? qi - 2 : 0;
+    for (int base = first; base <= s.p; base += kGroup) {
+        const int last = s.p - base < kGroup - 1 ? s.p - base : kGroup - 1;
+        for (int slot = base > 0 ? 0 : 1; slot <= last; ++slot) {
+            const int j = base + slot, n = size[j - 1], nq = n * QQ;
+            const CT *prev = ring + ((slot - 1) & (kGroup - 1)) * plane;
+            CT *cur = ring + slot * plane;
+            int N = N0, q = q0;
+            for (int e = threadIdx.x; e < plane; e += kCountThreads) {
+                CT sum = 0;
+                int Ni = N, qi = q, at = e; // at = Ni * QQ + qi
+                for (;;) {
+                    const bool two = Ni >= n;
+                    const int second = two ? at - nq - (qi > 0) : at;
+                    const CT c0 = prev[at], c1 = prev[second];
+                    sum = add_terms(sum, c0, two ? c1 : (CT)0);
+                    if (Ni - n < n) break;
+                    Ni -= 2 * n;
+                    at = second - nq - (qi > 1);
+                    qi = qi > 2 ? qi - 2 : 0;
+                }
+                cur[e] = sum;
+                if (sizeof(CT) == 8 && j == s.p) mine = sum > mine ? sum : mine;
+                N += dN; q += dq;
+                if (q >= QQ) { q -= QQ; ++N; }
             }
-            cur[e] = sum;
-            if (write) mine = sum > mine ? sum : mine;
-            N += dN; q += dq;
-            if (q >= QQ) { q -= QQ; ++N; }
+            __syncthreads(); // plane j complete
         }
-        if (sizeof(CT) == 4) {
-            if (write && mine == (CT)~(CT)0) *top = mine; // (every writer the same)
-        } else if (j == s.p) atomicMax(top, mine);
-        __syncthreads(); // plane j complete
-        if (!write) continue;
-        const int last = j & (kGroup - 1), base = j - last;
-        if (sizeof(CT) == 4 && *top == (CT)~(CT)0) return base; // uniform
-        // planes base..j; what follows in a row compares greater than any list position (slots past `last` hold older
+        // the group's planes; what follows in a row compares greater than any list position (slots past `last` hold older
         // planes or nothing: read, not used)
         if constexpr (sizeof(CT) == 4) {
+            unsigned most = 0; // no plane before holds a larger count than the last one
             for (int i = threadIdx.x; i < plane * 2; i += kCountThreads) {
                 const int e = i >> 1, k = (i & 1) * 4;
                 const CT *c = ring + k * plane + e;
                 uint4 v = make_uint4(c[0], c[plane], c[2 * plane], c[3 * plane]);
+                const unsigned at = last - k == 0 ? v.x : last - k == 1 ? v.y : last - k == 2 ? v.z : last - k == 3 ? v.w : 0;
+                most = at > most ? at : most;
                 v.x = k <= last ? v.x : 0xFFFFFFFFu;
                 v.y = k + 1 <= last ? v.y : 0xFFFFFFFFu;
                 v.z = k + 2 <= last ? v.z : 0xFFFFFFFFu;
                 v.w = k + 3 <= last ? v.w : 0xFFFFFFFFu;
                 *reinterpret_cast<uint4 *>(s.cnt32 + (long long)e * s.R + base + k) = v;
             }
+            if (most == 0xFFFFFFFFu) *top = most; // (every writer the same)
         } else {
             for (int i = threadIdx.x; i < plane * 4; i += kCountThreads) {
                 const int e = i >> 2, k = (i & 3) * 2;
@@ -213,6 +214,11 @@ template <typename CT> __device__ int count_planes(const Spec &s, CT *ring, cons
             }
         }
         __syncthreads(); // the next plane overwrites the first slot
+        if (sizeof(CT) == 4 && *top == (CT)~(CT)0) return base; // uniform
+    }
+    if (sizeof(CT) == 8) {
+        atomicMax(top, mine);
+        __syncthreads();
     }
     return s.p + 1;
 }
