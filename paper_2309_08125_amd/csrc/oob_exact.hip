@@ -408,7 +408,7 @@ __device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int p, int 
 // GPUs and at most S_max stages are used, whatever the prices.  The bound is the largest over the
 // multipliers.  Row after row of the two paths; a wave takes two lambdas, thirty-two lanes each share out the
 // starts of the last stage, eight GPU counts side by side.  Bound by the chain of rows (LDS read, reduction over the
-// lanes, LDS write per row) at one workgroup per bucket: 175 us at 98 layers x 8 GPUs, 274 buckets.
+// lanes, LDS write per row) at one workgroup per bucket, 63 % of the LDS cycles bank conflicts: 170 us at 98 layers x 8 GPUs, 274 buckets.
 // ---------------------------------------------------------------------------------------------
 __device__ const double kLambdaGiven[kLambdas] = {0, 0.04, 0.1, 0.2, 0.4, 0.8, 1.6, 3.5}; // more nodes pay (C falls with n) ...
 __device__ const double kLambda4S[kLambdas] = {0, -0.06, -0.14, -0.25, -0.43, -0.7, -1.3, -3.5}; // ... or cost
@@ -631,9 +631,11 @@ __global__ void __launch_bounds__(256) k_exact_filter(Args a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact evaluation.  Bound by the latency of dependent LDS reads on the rows of the one-node tables: 160 us for the
-// first picks and 490 us for the rest at 98 layers x 8 GPUs (the version before, without a band and evaluating
-// everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table entry: 1, or S_max + 1 (STAGED).
+// Exact evaluation.  Bound by chains of dependent LDS reads on the rows of the one-node tables; at 8 GPUs per node 47 % of the LDS cycles
+// are bank conflicts (neighbouring lanes read rows 64 bytes apart) and 30 registers of k_exact_eval<false, 8> are spilled: 29 MB of scratch
+// written per launch.  155 us for the first picks and 430 us for the rest at 98 layers x 8 GPUs (the version before, without a band and
+// evaluating everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table
+// entry: 1, or S_max + 1 (STAGED).
 // ---------------------------------------------------------------------------------------------
 struct Eval {
     Prof pr;
