@@ -15,7 +15,7 @@
 //     slowest stage in B:                     T = A.T1 + (B.T + cr * B.tmax)
 // where X.T is the child's own total under its own stage count, and (cl, cr) = (-r, 0) when
 // N_b is the caller's microbatch count or (3r, 4s) when N_b = 4 S' per state.  So the hot
-// loop needs only (T, T1, tmax) per child: 2 adds, 1 compare, 2 selects, 1 min per candidate.
+// loop needs only (T, T1, tmax) per child: 2 adds (the second under a mask), 1 compare, 1 min per candidate.
 // T3 and k* are carried per state for the output only.
 //
 // One level S' = split kernels, then a select kernel.
@@ -444,11 +444,16 @@ __device__ __forceinline__ Rec24 stage_load(const Stage &g, const StagePoint &sp
 // (T + cl tmax, T1), right records as (2 T1, T + cr tmax).  The slowest-stage test of Eq. 3 is
 // "left tmax >= right tmax"; the step loop always tests "streaming >= stationary", so when the
 // right child streams both tmax are stored negated.
+__device__ __forceinline__ int dpp_xor1(int x) { return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, true); }  // quad_perm [1,0,3,2]
+__device__ __forceinline__ int dpp_xor2(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, true); }  // quad_perm [2,3,0,1]
+__device__ __forceinline__ int dpp_down4(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, true); } // row_shl:4, lane i reads lane i + 4
+__device__ __forceinline__ double hilo(int hi, int lo) { return __hiloint2double(hi, lo); }
 __device__ __forceinline__ void stage_store(const Stage &g, double2 *pair, double *tm, int e, const Rec24 &rc) {
-    if (e >= g.fill) return;
+    if (e >= g.fill) return; // (fill is a multiple of eight: the lanes of a table are all here or none)
     const bool left = (e < g.fillY) == (g.y_is_left != 0);
     pair[e] = left ? make_double2(rc.a.x + g.cl * rc.tm, rc.a.y) : make_double2(2.0 * rc.a.y, rc.a.x + g.cr * rc.tm);
-    tm[e] = g.y_is_left ? rc.tm : -rc.tm;
+    const double x = g.y_is_left ? rc.tm : -rc.tm;
+    tm[e] = x;
 }
 
 // floor(x / d) for 0 <= x < 10000 and 1 <= d <= 4 without the division sequence (x 21846 >> 16 is
@@ -468,10 +473,50 @@ __host__ __device__ __forceinline__ int role_cost(int y0, int y1, int q0, int q1
     return c;
 }
 
+// Four candidates of a step: streaming record (p, atm) against four stationary ones, into the minima a0..a3
+// (LAST: a3 starts with its candidate).  The kernel is bound by the instructions its waves issue.  Written as a
+// compare and a select a candidate takes 6 vector instructions (a 64-bit select is two, and two idle slots before
+// them wait for the mask); here the sum of the other side overwrites the first one under the mask of the lanes that
+// take it: 4 vector instructions and a move on the scalar unit.  Measured: headline workload 9.03 -> 8.35 ms a call,
+// batch of 32 jobs 134 -> 124 ms, 61 layers 2.38 -> 2.29 ms.
+template <bool LAST>
+__device__ __forceinline__ void four_candidates(double &a0, double &a1, double &a2, double &a3, const double *bb2, const double *bbt,
+                                                const double *btm, const double2 p, const double atm) {
+    double t0, t1, t2;
+    unsigned long long m0, m1, m2, m3, ex;
+#define OOB_MIN3 "v_min_f64 %[a0], %[a0], %[t0]\n v_min_f64 %[a1], %[a1], %[t1]\n v_min_f64 %[a2], %[a2], %[t2]\n"
+#define OOB_FOUR(T3, MIN3)                                                                                             \
+    asm("v_cmp_lt_f64 %[m0], %[tm], %[c0]\n v_cmp_lt_f64 %[m1], %[tm], %[c1]\n"                                          \
+        "v_cmp_lt_f64 %[m2], %[tm], %[c2]\n v_cmp_lt_f64 %[m3], %[tm], %[c3]\n s_mov_b64 %[ex], exec\n"                  \
+        "v_add_f64 %[t0], %[px], %[x0]\n v_add_f64 %[t1], %[px], %[x1]\n v_add_f64 %[t2], %[px], %[x2]\n v_add_f64 " T3 ", %[px], %[x3]\n" \
+        "s_mov_b64 exec, %[m0]\n v_add_f64 %[t0], %[py], %[y0]\n s_mov_b64 exec, %[m1]\n v_add_f64 %[t1], %[py], %[y1]\n" \
+        "s_mov_b64 exec, %[m2]\n v_add_f64 %[t2], %[py], %[y2]\n s_mov_b64 exec, %[m3]\n v_add_f64 " T3 ", %[py], %[y3]\n" \
+        "s_mov_b64 exec, %[ex]\n" OOB_MIN3 MIN3
+#define OOB_FOUR_IN                                                                                                    \
+    [px] "v"(p.x), [py] "v"(p.y), [tm] "v"(atm), [x0] "v"(bb2[0]), [x1] "v"(bb2[1]), [x2] "v"(bb2[2]), [x3] "v"(bb2[3]), \
+        [y0] "v"(bbt[0]), [y1] "v"(bbt[1]), [y2] "v"(bbt[2]), [y3] "v"(bbt[3]), [c0] "v"(btm[0]), [c1] "v"(btm[1]),      \
+        [c2] "v"(btm[2]), [c3] "v"(btm[3])
+    if (LAST) {
+        OOB_FOUR("%[a3]", "")
+            : [a0] "+v"(a0), [a1] "+v"(a1), [a2] "+v"(a2), [a3] "=&v"(a3), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [m0] "=&s"(m0),
+              [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3), [ex] "=&s"(ex)
+            : OOB_FOUR_IN : "scc");
+    } else {
+        double t3;
+        OOB_FOUR("%[t3]", "v_min_f64 %[a3], %[a3], %[t3]\n")
+            : [a0] "+v"(a0), [a1] "+v"(a1), [a2] "+v"(a2), [a3] "+v"(a3), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [m0] "=&s"(m0),
+              [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3), [ex] "=&s"(ex)
+            : OOB_FOUR_IN : "scc");
+    }
+#undef OOB_FOUR
+#undef OOB_FOUR_IN
+#undef OOB_MIN3
+}
+
 // One split point per pass, one LDS buffer: while the waves work on k, every thread has the
 // records of k+1 in flight from HBM/L2 and drops them into the buffer between the two barriers
 // of the pass (NBUF = 2: two buffers and one barrier; needs more LDS, measured slower).
-// FB = kFillBatch: 167 vector registers, three waves per SIMD.  FB = kFillBatchSmall: launch bounds hold
+// FB = kFillBatch: 152 vector registers, three waves per SIMD.  FB = kFillBatchSmall: launch bounds hold
 // the kernel to 128 registers (four waves per SIMD, for launches whose LDS admits a fourth workgroup
 // per compute unit) at the price of 24 bytes of spills per lane in the per-pass code, none in the step
 // loop; records beyond FB per thread are fetched between the barriers.  Measured on the headline
@@ -634,11 +679,8 @@ __global__ void __launch_bounds__(256, FB == kFillBatch ? 1 : 4) k_split_key(Tab
         pa += 8; ta += 8;                                                                             \
         const double2 pn = *pa; /* may read one record past the last one: staged memory, unused */    \
         const double tn = *ta;                                                                        \
-        _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                               \
-            const double T = atm >= btm[i] ? p.x + bb2[i] : p.y + bbt[i];                             \
-            /* the eighth candidate is the first one of its target: its slot was flushed one step ago */ \
-            acc[((j) + i) & 7] = i == 7 ? T : fmin(acc[((j) + i) & 7], T);                            \
-        }                                                                                             \
+        four_candidates<false>(acc[(j) & 7], acc[((j) + 1) & 7], acc[((j) + 2) & 7], acc[((j) + 3) & 7], bb2, bbt, btm, p, atm); \
+        four_candidates<true>(acc[((j) + 4) & 7], acc[((j) + 5) & 7], acc[((j) + 6) & 7], acc[((j) + 7) & 7], bb2 + 4, bbt + 4, btm + 4, p, atm); \
         const int row = imin(imax(m + aoff, -1), na) + 1;                                             \
         atomicMin(&s_acc[row * 64 + col], (unsigned long long)__double_as_longlong(fma(acc[(j)], KS, kd))); \
         p = pn; atm = tn;                                                                             \
