@@ -130,25 +130,32 @@ __host__ __device__ inline void tile_decode(int L, int S, int t, int *ub, int *v
 __host__ __device__ inline int tile_vmax(int L, int vb) { return vb * 8 + 7 - col_shift(L); }
 
 // Split points k of a block of the plane at level S': kmin = 8 ub + s .. kmax = vmax - (S' - s):
-// their number does not depend on s.  The keyed split kernel cuts this range into segments of
-// about seg_target() consecutive k, one workgroup each: as many segments as the range divided by
-// the target gives, rounded to the nearest (at least one), all of the same length up to one
-// split point -- so no workgroup is left with a stub of one or two split points, which would pay
-// the whole set-up and the merge of its keys for next to nothing.
-constexpr int kSegTarget = 8, kSegTargetTop = 3, kSegTopLayers = 28; // measured on the headline workload
-constexpr int kSegMin = 3; // no target below this (sizes the task lists)
-// The top levels (fewer than kSegTopLayers layers of slack, a handful of blocks) cannot fill the
-// machine with workgroups of eight split points: there the target is three.
-__host__ __device__ inline int seg_target(int L, int S) { return L - S < kSegTopLayers ? kSegTargetTop : kSegTarget; }
+// their number does not depend on s.  The keyed split kernel cuts this range into segments, one workgroup each, of
+// whole groups of kSegUnit consecutive k (what it stages at a time; the last group may be short): as many segments as
+// the range divided by the target gives, rounded to the nearest, all of the same number of groups up to one.
+constexpr int kSegUnit = 4;
+constexpr int kSegTarget = 16, kSegTargetMid = 8, kSegTargetTop = 4, kSegMidLayers = 40, kSegTopLayers = 28;
+constexpr int kSegMin = 4; // no target below this (sizes the task lists)
+// The top levels (fewer than kSegTopLayers layers of slack, a handful of blocks) cannot fill the machine with
+// workgroups of sixteen split points, or of eight: there the target is four, and eight up to kSegMidLayers.  A longer
+// segment pays the set-up and the merge of its keys less often: 16 instead of 8 everywhere above took a batch of 32
+// jobs of 24..128 layers from 122 to 113 ms; with the line of the eight at 60 or 75 layers 101 and 104 ms instead of
+// 99 ms, the headline workload 7.97 and 8.16 ms instead of 7.64 ms; 24 or 32 split points were no better.
+__host__ __device__ inline int seg_target(int L, int S) {
+    return L - S < kSegTopLayers ? kSegTargetTop : L - S < kSegMidLayers ? kSegTargetMid : kSegTarget;
+}
 __host__ __device__ inline int tile_krange(int L, int S, int ub, int vb) {
     return tile_vmax(L, vb) - ub * 8 - S + 1;
 }
-__host__ __device__ inline int seg_n(int krange, int target) { return imax(1, (krange + target / 2) / target); }
+__host__ __device__ inline int seg_n(int krange, int target) {
+    const int units = (krange + kSegUnit - 1) / kSegUnit, per = target / kSegUnit;
+    return imax(1, (units + per / 2) / per);
+}
 // Segment j of n over a range of `krange` split points: offset of its first one and its length.
 __host__ __device__ inline void seg_span(int krange, int n, int j, int *ofs, int *len) {
-    const int base = krange / n, extra = krange % n;
-    *ofs = j * base + imin(j, extra);
-    *len = base + (j < extra ? 1 : 0);
+    const int units = (krange + kSegUnit - 1) / kSegUnit, base = units / n, extra = units % n;
+    *ofs = (j * base + imin(j, extra)) * kSegUnit;
+    *len = imin((base + (j < extra ? 1 : 0)) * kSegUnit, krange - *ofs);
 }
 __host__ __device__ inline int seg_count(int L, int S) { // over all blocks of the level
     const int NB = nblocks_of(L), ubmax = (L - S) / 8;

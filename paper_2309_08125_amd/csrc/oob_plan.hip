@@ -59,6 +59,7 @@ struct Tables {
     int coff;             // column shift of the plane: v sits in block column (v + coff) / 8
     int tab_recs;         // records per table = tri_blocks(NB) * 64
     long long *lvl_tab;   // [Smax+2] index of the first table of level S'
+    int2 *lvl_dir;        // [Smax+2] x: table of device set delta minus delta, y: ceil(S' / M)
     long long *PT;        // [(M+1)*(L+1)] prefix sums of F+B for d GPUs (row d)
     int *PF;              // [(M+1)*(L+1)] prefix counts of forbidden entries
     long long *PM;        // [L+1] prefix sums of bytes
@@ -175,6 +176,7 @@ __device__ void setup_body(const Tables &t, const oob_profile &prof, int force_p
         long long tab = 0;
         for (int S = 1; S <= t.sh.Smax + 1; ++S) {
             t.lvl_tab[S] = tab;
+            t.lvl_dir[S] = make_int2((int)tab - dlo_of(S, M), cdiv(S, M));
             const int nd = dhi_of(S, M, t.sh.n_max) - dlo_of(S, M) + 1;
             if (S <= t.sh.Smax && nd > 0) tab += nd;
         }
@@ -374,19 +376,33 @@ __global__ void __launch_bounds__(512) k_split(Tables t, int Sp, int fam, int NT
 // Levels S' >= 2, first kernel, keyed variant (runs when flags[0] = 1).
 //
 // Same result as k_split, different mapping.  A workgroup owns (block of the plane, segment of
-// its split points, s) and a group of up to kKeyTargets target sets; per split point it stages
-// the records of both children for every unit count it needs in LDS.  Work items are (k, block
-// of eight unit counts of one child); the waves take them round robin.  An item keeps those
-// eight records in registers and streams the other child: a step forms eight candidates, which
-// belong to eight consecutive targets.  The eight running minima rotate: after a step the
-// minimum of the lowest target is complete for this item and is merged into the workgroup's
-// LDS table acc[a][lane] with an integer atomic min on the bits of key = total * 2^kbits + k
+// its split points, s) and a group of up to kKeyTargets target sets; each of its waves takes every nw-th split point k
+// of the segment for itself: it stages the streaming child's records for every unit count it needs in LDS, and the
+// other child's eight unit counts at a time.  The (m, m') pairs of a split form a rectangle; an item keeps eight records
+// of one side in registers (the STATIONARY side, cut into blocks of eight unit counts, the last one padded) and
+// streams the other side.  Which child is stationary is chosen per workgroup so that the padding is smaller (it is the
+// same work either way).  A step forms eight candidates, which belong to eight consecutive targets.  The eight running
+// minima rotate: after a step the minimum of the lowest target is complete for this item and is merged into the
+// workgroup's LDS table acc[a][lane] with an integer atomic min on the bits of key = total * 2^kbits + k
 // (non-negative doubles order like their bit patterns).  The key makes the merge order-free
 // and yields, per (s, state), the smallest total and the first k reaching it at once.
+//
+// What bounds it: the instructions a wave issues, and its waits.  The step loop alone, out of LDS, takes 175 cycles of
+// a SIMD a step (eight candidates of 64 lanes) with four waves per SIMD, 186 with three, 206 with two, and about ten
+// steps make an item.  When the four waves of a workgroup shared a split point they staged it together between two
+// barriers and did about five steps each between them: as many scalar as vector instructions, half of the vector
+// ones outside the steps, 40 % of a wave's time in waits.  A split point per wave has no barrier between set-up and
+// merge, no item cut in pieces and a quarter of the scalar work, and pays with LDS (a staged streaming side per wave:
+// two or three waves per SIMD instead of four), which costs the steps less than the barriers did.  The stationary side
+// needs LDS for one block only and is loaded while the block before is worked on.  Measured: batch of 32 jobs of 24..128
+// layers 124 -> 99 ms; staged by the workgroup four split points at a time with eight waves 149 ms; both
+// children staged per wave 113 ms; three waves per workgroup 101 ms; held to 128 registers for a fourth wave per
+// SIMD 104-121 ms.
 // ---------------------------------------------------------------------------------------
 constexpr int kKeyTargets = 64;
-constexpr int kFillBatch = 3;      // records a thread has in flight while staging: three waves per SIMD
-constexpr int kFillBatchSmall = 2; // the same for launches whose LDS admits four workgroups per compute unit
+constexpr int kKeyPad = 7;    // rows of the key table on either side of the targets
+constexpr int kFillBatch = 2; // eights of streaming tables a wave has in flight while it works on the split point before
+constexpr int kWavesPerSimd = 3;
 
 // Workgroup x of a launch of n -> position in the task list (handle option OOB_OPT_XCD_ORDER only).  The hardware
 // deals consecutive workgroups out to the 8 XCDs in turn; this hands every XCD one contiguous
@@ -399,79 +415,11 @@ __device__ __forceinline__ int xcd_chunked(int x, int n) {
     return c * q + imin(c, rem) + i;
 }
 
-// The (m, m') pairs of a split form a rectangle; an item keeps eight records of one side in
-// registers (the STATIONARY side, cut into blocks of eight unit counts, the last one padded) and
-// streams the other side.  Which child is stationary is chosen per workgroup so that the padding
-// is smaller (it is the same work either way).  Staging order for split point k:
-// [streaming tables][lane index], then [stationary tables, padded][lane index]; the lane index
-// is u for records of the left child and v for records of the right child.
-struct Stage {
-    const Rec *recY, *recS; // first record of the table of unit count 0 of the streaming / stationary side
-    int tab_recs, NB, coff, ub, vb, nS, fillY, fill;
-    int y_is_left;          // 1: left child streams, right child stationary; 0: the other way round
-    double cl, cr;
-};
 struct Rec24 { double2 a; double tm; }; // (T, T1), tmax: the 24 bytes of a record the splits need
 
-// Where the records of split point k sit inside a table: the left child (s, u, k, m) is row u of
-// block (ub, k/8), column k; the right child (r, k, v, m') is row k of block (k/8, vb), column v.
-// Scalar work, once per split point; per staged record only a 32-bit offset is left to form
-// (tables of one side x records of a table x 32 bytes stays below 2^32).
-struct StagePoint { const Rec *py, *ps; int shY, shS; };
-__device__ __forceinline__ StagePoint stage_point(const Stage &g, int k) {
-    const int ck = k + g.coff; // column of split point k in the left child's table
-    const int offL = tri_index(g.ub, ck >> 3, g.NB) * 64 + (ck & 7), offR = tri_index(k >> 3, g.vb, g.NB) * 64 + ((k & 7) << 3);
-    StagePoint sp;
-    sp.py = g.recY + (g.y_is_left ? offL : offR);
-    sp.ps = g.recS + (g.y_is_left ? offR : offL);
-    sp.shY = g.y_is_left ? 3 : 0; // the lane index is a row of the block for left records, a column for right ones
-    sp.shS = g.y_is_left ? 0 : 3;
-    return sp;
-}
-__device__ __forceinline__ Rec24 stage_load(const Stage &g, const StagePoint &sp, int e) {
-    Rec24 rc = {make_double2(kNone, kNone), 0.0};
-    const bool stream = e < g.fillY;
-    const int e2 = stream ? e : e - g.fillY, tab = e2 >> 3, idx = e2 & 7;
-    if (e < g.fill && (stream || tab < g.nS)) {
-        const unsigned off = (__umul24((unsigned)tab, (unsigned)g.tab_recs) + ((unsigned)idx << (stream ? sp.shY : sp.shS))) << 5;
-        const Rec *p = (const Rec *)((const char *)(stream ? sp.py : sp.ps) + off);
-        rc.a = *(const double2 *)p;
-        rc.tm = p->tmax;
-    }
-    return rc;
-}
-// LDS order = staging order; values pre-combined with the level's coefficients: left records as
-// (T + cl tmax, T1), right records as (2 T1, T + cr tmax).  The slowest-stage test of Eq. 3 is
-// "left tmax >= right tmax"; the step loop always tests "streaming >= stationary", so when the
-// right child streams both tmax are stored negated.
-__device__ __forceinline__ int dpp_xor1(int x) { return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, true); }  // quad_perm [1,0,3,2]
-__device__ __forceinline__ int dpp_xor2(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, true); }  // quad_perm [2,3,0,1]
-__device__ __forceinline__ int dpp_down4(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0xf, true); } // row_shl:4, lane i reads lane i + 4
-__device__ __forceinline__ double hilo(int hi, int lo) { return __hiloint2double(hi, lo); }
-__device__ __forceinline__ void stage_store(const Stage &g, double2 *pair, double *tm, int e, const Rec24 &rc) {
-    if (e >= g.fill) return; // (fill is a multiple of eight: the lanes of a table are all here or none)
-    const bool left = (e < g.fillY) == (g.y_is_left != 0);
-    pair[e] = left ? make_double2(rc.a.x + g.cl * rc.tm, rc.a.y) : make_double2(2.0 * rc.a.y, rc.a.x + g.cr * rc.tm);
-    const double x = g.y_is_left ? rc.tm : -rc.tm;
-    tm[e] = x;
-}
-
-// floor(x / d) for 0 <= x < 10000 and 1 <= d <= 4 without the division sequence (x 21846 >> 16 is
-// exact for thirds in that range).
-__device__ __forceinline__ int div_small(int x, int d) {
-    return d == 1 ? x : d == 2 ? x >> 1 : d == 4 ? x >> 2 : (x * 21846) >> 16;
-}
-
-// Candidate slots an assignment of roles executes: per block of eight stationary unit counts the
-// streaming range that pairs with it (targets a0..a1), times eight.
-__host__ __device__ __forceinline__ int role_cost(int y0, int y1, int q0, int q1, int a0, int a1) {
-    int c = 0;
-    for (int qb = q0; qb <= q1; qb += 8) {
-        const int lo = imax(y0, a0 - (qb + 7)), hi = imin(y1, a1 - qb);
-        if (lo <= hi) c += hi - lo + 1;
-    }
-    return c;
-}
+// Which child streams: the one that leaves less padding when the other one is cut into blocks of eight.
+__host__ __device__ __forceinline__ bool left_streams(int nA, int nB) { return nA * ((nB + 7) & ~7) <= nB * ((nA + 7) & ~7); }
+__device__ __forceinline__ int log2_up(int x) { return 32 - __clz(x - 1); } // smallest b with 2^b >= x, x >= 1
 
 // Four candidates of a step: streaming record (p, atm) against four stationary ones, into the minima a0..a3
 // (LAST: a3 starts with its candidate).  The kernel is bound by the instructions its waves issue.  Written as a
@@ -513,42 +461,53 @@ __device__ __forceinline__ void four_candidates(double &a0, double &a1, double &
 #undef OOB_MIN3
 }
 
-// One split point per pass, one LDS buffer: while the waves work on k, every thread has the
-// records of k+1 in flight from HBM/L2 and drops them into the buffer between the two barriers
-// of the pass (NBUF = 2: two buffers and one barrier; needs more LDS, measured slower).
-// FB = kFillBatch: 152 vector registers, three waves per SIMD.  FB = kFillBatchSmall: launch bounds hold
-// the kernel to 128 registers (four waves per SIMD, for launches whose LDS admits a fourth workgroup
-// per compute unit) at the price of 24 bytes of spills per lane in the per-pass code, none in the step
-// loop; records beyond FB per thread are fetched between the barriers.  Measured on the headline
-// workload: nothing in flight 9.78 ms, one record 9.84 ms, two 9.64 ms for the levels.
-template <int NTAB, int NBUF, int FB>
-__global__ void __launch_bounds__(256, FB == kFillBatch ? 1 : 4) k_split_key(Tables t, int Sp, int fam0, int gz, int NT, int NAall, int halves,
-                                                   int s0, int sstep) {
-    // Separate arrays (the staged records static, the key table the launch's dynamic LDS, sized by
-    // its target count): the compiler then knows that the key merges (atomics on s_acc) never touch
-    // the staged records, and keeps the reads of the next step ahead of them.
-    __shared__ double2 s_pair[NBUF][NTAB * 8]; // [buffer][staging order]: pre-combined pairs
-    __shared__ double s_tm[NBUF][NTAB * 8];    // tmax (negated when the right child streams)
-    HIP_DYNAMIC_SHARED(unsigned long long, s_acc)       // [(na + 2) * 64] keys, rows 1..na (sized by the launch)
+// A keyed launch (level, families, splits); filled in by the host.
+struct KeyArgs {
+    int Sp, fam0, gz;    // the first gz target groups of the launch belong to family fam0, the rest (a launch that covers
+                         // both families of a low level) to the whole-node family
+    int NT, NAall;
+    int s0, sstep;       // a launch covers the splits s0, s0 + sstep, ...
+    int t_lo1, dlo;      // smallest target of the whole-node family; first device set of the level
+    int pack, xcd;       // several items per wave near the range ends; XCD-chunked task order
+};
+
+// Order of a wave's LDS operations against those of its other lanes (they execute in order: only the compiler has to
+// be told).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ Rec24 load24(const void *base, unsigned off) {
+    const Rec *p = (const Rec *)((const char *)base + off);
+    Rec24 rc;
+    rc.a = *(const double2 *)p;
+    rc.tm = p->tmax;
+    return rc;
+}
+
+template <int ROWS>
+__global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyArgs ka) {
+    // Separate arrays (the key table static, the staged records the launch's dynamic LDS): the compiler then knows
+    // that the key merges (atomics on s_acc) never touch the staged records, and keeps the reads of the next step
+    // ahead of them.
+    __shared__ unsigned long long s_acc[ROWS * 64]; // keys: targets are rows kKeyPad .. kKeyPad + na - 1
+    HIP_DYNAMIC_SHARED(double2, s_rec)              // per wave [TS] pre-combined pairs, [TS] tmax (negated when the right child streams)
+    const int Sp = ka.Sp, s = ka.s0 + blockIdx.y * ka.sstep, r = Sp - s;
+    const int2 sg = t.seg_tab[(long long)(Sp - 2) * t.seg_stride + (ka.xcd ? xcd_chunked(blockIdx.x, gridDim.x) : (int)blockIdx.x)]; // x: tile index, y: ub | vb << 8 | seg << 16
+    const int2 dA = t.lvl_dir[s], dB = t.lvl_dir[r];
     if (t.flags[0] == 0) return;        // keys do not fit: k_select evaluates the candidates itself
     const int L = t.sh.L, M = t.sh.M, n_max = t.sh.n_max;
-    const int s = s0 + blockIdx.y * sstep, r = Sp - s; // a launch covers the splits s0, s0 + sstep, ...
     // the wave index is the same in all lanes: say so, and everything derived from it (work item,
     // m range, key row) is scalar arithmetic and scalar branches
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
-    const int2 sg = t.seg_tab[(long long)(Sp - 2) * t.seg_stride + ((halves & 8) ? xcd_chunked(blockIdx.x, gridDim.x) : (int)blockIdx.x)]; // x: tile index, y: ub | vb << 8 | seg << 16
     const int tile = sg.x, ub = sg.y & 255, vb = (sg.y >> 8) & 255, seg = sg.y >> 16;
-    // the first gz target groups of the launch belong to family fam0, the rest (a launch that covers
-    // both families of a low level) to the whole-node family
-    const int fam = (int)blockIdx.z < gz ? fam0 : 1, zg = (int)blockIdx.z < gz ? (int)blockIdx.z : (int)blockIdx.z - gz;
+    const int fam = (int)blockIdx.z < ka.gz ? ka.fam0 : 1, zg = (int)blockIdx.z < ka.gz ? (int)blockIdx.z : (int)blockIdx.z - ka.gz;
     const int fam_base = fam ? M - 2 : -1;
-    int t_lo, t_hi;
-    target_units(fam, Sp, M, n_max, &t_lo, &t_hi);
-    const int a_g0 = t_lo + zg * kKeyTargets, a_g1 = imin(t_hi, a_g0 + kKeyTargets - 1);
+    const int a_g0 = (fam ? ka.t_lo1 : Sp) + zg * kKeyTargets, a_g1 = imin(fam ? imin(Sp, n_max) : M, a_g0 + kKeyTargets - 1);
     const int na = a_g1 - a_g0 + 1;
-    int A_lo, A_hi, B_lo, B_hi;
-    child_units(fam, s, M, n_max, &A_lo, &A_hi);
-    child_units(fam, r, M, n_max, &B_lo, &B_hi);
+    const int A_lo = fam ? dA.y : s, A_hi = fam ? imin(s, n_max) : M - 1, B_lo = fam ? dB.y : r, B_hi = fam ? imin(r, n_max) : M - 1;
     const int mA0 = imax(A_lo, a_g0 - B_hi), mA1 = imin(A_hi, a_g1 - B_lo);
     const int mB0 = imax(B_lo, a_g0 - A_hi), mB1 = imin(B_hi, a_g1 - A_lo);
     // this workgroup's segment of the split points of the block
@@ -560,110 +519,115 @@ __global__ void __launch_bounds__(256, FB == kFillBatch ? 1 : 4) k_split_key(Tab
     }
     const int kmin = ub * 8 + s + kofs, kmax = imin(vmax - r, kmin + klen - 1);
     if (!(mA0 <= mA1 && mB0 <= mB1 && kmin <= kmax)) return; // nothing to merge
-    // roles: the left child streams (and the right one is stationary) unless the other way pads less
-    const bool y_left = role_cost(mA0, mA1, mB0, mB1, a_g0, a_g1) <= role_cost(mB0, mB1, mA0, mA1, a_g0, a_g1);
+    const bool y_left = left_streams(mA1 - mA0 + 1, mB1 - mB0 + 1);
     const int yM0 = y_left ? mA0 : mB0, yM1 = y_left ? mA1 : mB1; // streaming unit counts
     const int qM0 = y_left ? mB0 : mA0, qM1 = y_left ? mB1 : mA1; // stationary unit counts
-    const int nY = yM1 - yM0 + 1, nS = qM1 - qM0 + 1, nmb = cdiv(nS, 8);
-    const int fillY = nY * 8, TS = fillY + nmb * 64;
+    const int nY = yM1 - yM0 + 1, nS = qM1 - qM0 + 1, nyb = (nY + 7) >> 3, nmb = (nS + 7) >> 3;
+    const int fillY = nyb * 64, TS = fillY + 64; // records staged: the streaming side of a split point, one block of the stationary side
     const unsigned long long kNoneBits = 0x7FF0000000000000ull;
     const double KS = (double)(1 << key_bits(L));
 
-    Stage g;
-    const long long tabA = t.lvl_tab[s] - dlo_of(s, M) + fam_base, tabB = t.lvl_tab[r] - dlo_of(r, M) + fam_base;
-    g.recY = t.rec + (y_left ? tabA + mA0 : tabB + mB0) * t.tab_recs;
-    g.recS = t.rec + (y_left ? tabB + mB0 : tabA + mA0) * t.tab_recs;
-    g.tab_recs = t.tab_recs; g.NB = t.NB; g.coff = t.coff; g.ub = ub; g.vb = vb; g.nS = nS;
-    g.fillY = fillY; g.fill = TS; g.y_is_left = y_left;
-    g.cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r;
-    g.cr = t.sh.Nb > 0 ? 0.0 : 4.0 * s;
+    // Staging.  The left child (s, u, k, m) is row u of block (ub, k/8), column k; the right child (r, k, v, m') is row
+    // k of block (k/8, vb), column v.  What depends on the lane does not depend on k: eight tables ahead is a constant
+    // distance, and only the last eight tables of a side may not all exist (streaming: the last one again, stationary:
+    // "no such state").
+    const double cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r, cr = t.sh.Nb > 0 ? 0.0 : 4.0 * s;
+    const long long tabA = (long long)(dA.x + fam_base + mA0) * t.tab_recs, tabB = (long long)(dB.x + fam_base + mB0) * t.tab_recs;
+    const Rec *const recY = t.rec + (y_left ? tabA : tabB), *const recS = t.rec + (y_left ? tabB : tabA);
+    const int lt = lane >> 3, li = lane & 7, shY = y_left ? 3 : 0, shS = y_left ? 0 : 3;
+    auto off8 = [=](int sh, int top) { return (__umul24(imin(lt, top), t.tab_recs) + (li << sh)) * 32u; }; // lane's record of eight tables 0..top
+    const int lastY = nY - 1 - 8 * (nyb - 1); // last table of the last eight of the streaming side that exists
+    const int last = nS - 1 - 8 * (nmb - 1); // last table of the last stationary block that exists
+    const size_t step8 = (size_t)t.tab_recs * 8 * sizeof(Rec);
+    double2 *const pair = s_rec + wave * TS + (wave * TS >> 1);
+    double *const tmv = (double *)(pair + TS);
+    struct Src { const char *y, *s; };
+    auto source = [=](int k) { // records of split point k of the two sides' first tables
+        const int ck = k + t.coff; // column of split point k in the left child's table
+        const int offL = tri_index(ub, ck >> 3, t.NB) * 64 + (ck & 7), offR = tri_index(k >> 3, vb, t.NB) * 64 + ((k & 7) << 3);
+        return Src{(const char *)(recY + (y_left ? offL : offR)), (const char *)(recS + (y_left ? offR : offL))};
+    };
+    // Staged values are pre-combined with the level's coefficients: left records as (T + cl tmax, T1), right records as
+    // (2 T1, T + cr tmax).  The slowest-stage test of Eq. 3 is "left tmax >= right tmax"; the step loop always tests
+    // "streaming >= stationary", so when the right child streams both tmax are stored negated.
+    auto combine = [=](const Rec24 &rc, bool left) {
+        return Rec24{left ? make_double2(rc.a.x + cl * rc.tm, rc.a.y) : make_double2(2.0 * rc.a.y, rc.a.x + cr * rc.tm), y_left ? rc.tm : -rc.tm};
+    };
+    auto store = [=](int at, const Rec24 &rc) { pair[at] = rc.a; tmv[at] = rc.tm; };
 
-    // rows 1..na are the targets; rows 0 and na+1 swallow the minima of targets outside the group
-    for (int e = threadIdx.x; e < (na + 2) * 64; e += blockDim.x) s_acc[e] = kNoneBits;
-    Rec24 pre[FB ? FB : 1];
-    {
-        const StagePoint sp0 = stage_point(g, kmin);
+    Rec24 preY[kFillBatch], preS; // in flight: streaming side of the next split point, next stationary block
+    int k = kmin + wave;
+    auto loadY = [=](const Src &src, int i) { return load24(src.y + i * step8, off8(shY, i == nyb - 1 ? lastY : 7)); };
+    auto loadS = [=](const Src &src, int i) { return load24(src.s + i * step8, off8(shS, i == nmb - 1 ? last : 7)); };
+    if (k <= kmax) {
+        const Src src = source(k);
 #pragma unroll
-        for (int q = 0; q < FB; ++q) pre[q] = stage_load(g, sp0, threadIdx.x + q * blockDim.x);
-#pragma unroll
-        for (int q = 0; q < FB; ++q) stage_store(g, s_pair[0], s_tm[0], threadIdx.x + q * blockDim.x, pre[q]);
-        for (int e = threadIdx.x + FB * blockDim.x; e < TS; e += blockDim.x)
-            stage_store(g, s_pair[0], s_tm[0], e, stage_load(g, sp0, e));
+        for (int i = 0; i < kFillBatch; ++i)
+            if (i < nyb) preY[i] = loadY(src, i);
+        preS = loadS(src, 0);
     }
+    for (int e = threadIdx.x; e < (na + 2 * kKeyPad) * 64; e += blockDim.x) s_acc[e] = kNoneBits;
     __syncthreads();
-
-    // Work items of a split point: the 8-blocks of the stationary side, `R` of them side by side in a
-    // wave (see below).  Whole items go round robin over the waves; the items left over after the last
-    // full round are cut into `parts` pieces of their streaming range so that every wave gets one
-    // (halves = 0 disables the cutting).
-    const int chi = 7; // last column of the block that exists (a block column that is not full lacks its FIRST columns)
-    for (int k = kmin; k <= kmax; ++k) {
-        const int cur = NBUF == 2 ? (k - kmin) & 1 : 0, nxt = NBUF == 2 ? cur ^ 1 : 0;
-        const double2 *pair = s_pair[cur];
-        const double *tmv = s_tm[cur];
-        const StagePoint spn = stage_point(g, k + 1);
-        if (k < kmax) { // records of the next split point: in flight during this pass
+    for (; k <= kmax; k += nw) {
+        const Src src = source(k);
 #pragma unroll
-            for (int q = 0; q < FB; ++q) pre[q] = stage_load(g, spn, threadIdx.x + q * blockDim.x);
+        for (int i = 0; i < kFillBatch; ++i)
+            if (i < nyb) store(i * 64 + lane, combine(preY[i], y_left));
+        for (int i = kFillBatch; i < nyb; ++i) store(i * 64 + lane, combine(loadY(src, i), y_left));
+        const Src next = source(imin(k + nw, kmax));
+        if (k + nw <= kmax) { // records of this wave's next split point: in flight during this one
+#pragma unroll
+            for (int i = 0; i < kFillBatch; ++i)
+                if (i < nyb) preY[i] = loadY(next, i);
         }
-        // Lanes of this pass.  Only the rows 0..jr of the block hold states that can be split at k
-        // (u + s <= k), and only the columns chi-jc..chi (k <= v - r): near the ends of the block's
-        // split range most of the 64 states idle.  Then the wave takes R items at once: the rows (or
+        wave_fence();
+        // Work items: the 8-blocks of the stationary side, 2^lgR of them side by side.
+        // Only the rows 0..jr of the block hold states that can be split at k (u + s <= k), and only the
+        // columns 7-jc..7 (k <= v - r; a block column that is not full lacks its first columns): near the ends
+        // of the block's split range most of the 64 states idle.  Then the wave takes R items at once: the rows (or
         // columns) that matter, padded to a power of two, times R stationary blocks.
         const int jr = k - (ub * 8 + s), jc = vmax - r - k;
-        const int nr = imin(jr, 7) + 1, nc = imin(jc, chi) + 1;
-        const int lr = nr <= 1 ? 0 : nr <= 2 ? 1 : nr <= 4 ? 2 : 3, lc = nc <= 1 ? 0 : nc <= 2 ? 1 : nc <= 4 ? 2 : 3;
-        int R, lgR, slot, ue, ve; // items side by side (and its binary logarithm), this lane's item among them, its row and column
-        if (lr <= lc) {      // rows 0..2^lr-1, all columns
-            R = 8 >> lr; lgR = 3 - lr; slot = lane >> (3 + lr); ue = (lane >> 3) & ((1 << lr) - 1); ve = lane & 7;
-        } else {             // all rows, the last 2^lc columns that exist
-            R = 8 >> lc; lgR = 3 - lc; slot = lane >> (3 + lc);
-            const int w = lane & ((8 << lc) - 1);
-            ue = w >> lc; ve = imax(0, chi - (1 << lc) + 1) + (w & ((1 << lc) - 1));
-        }
-        // The items of the pass, with (PACK) or without several of them side by side in a wave; the
-        // plain variant keeps the item's block, row offset and key column in scalar registers.
-        auto run_items = [&](auto pack_c, const int R, const int lgR, const int slot, const int ue, const int ve) {
-        constexpr bool PACK = decltype(pack_c)::value;
-        const int yl = y_left ? ue : ve, ql = y_left ? ve : ue; // lane index of a streaming / stationary record
-        const int col = PACK ? ue * 8 + ve : lane;              // this lane's state: its column of the key table
-        // (R is a power of two, a workgroup has at most four waves: no integer division below)
-        const int nsup = (nmb + R - 1) >> lgR;
-        const int rem = nsup - div_small(nsup, nw) * nw, full = nsup - rem;
-        const int parts = ((halves & 3) && rem) ? (rem == 1 ? nw : (nw == 4 && rem == 2) ? 2 : 1) : 1;
-        const int nitems = full + rem * parts;
-        for (int item = wave; item < nitems; item += nw) {
-            const int cut = item >= full, jj = item - full;
-            const int jq = div_small(jj, parts);
-            const int sb = cut ? full + jq : item, part = cut ? jj - jq * parts : 0, np = cut ? parts : 1;
-            // stationary blocks sb R .. sb R + R - 1 (those that exist); this lane's is mb
-            const int mb_first = sb * R, mb_last = imin(mb_first + R - 1, nmb - 1);
-            // a lane without a block of its own repeats the last block's work for its state: the same
-            // candidates into the same keys, which a minimum does not notice (masking them cost 32
-            // selects per item)
+        const int lr = log2_up(imin(jr, 7) + 1), lc = log2_up(imin(jc, 7) + 1);
+        const int lgR = ka.pack && nmb > 1 ? 3 - imin(lr, lc) : 0;
+        const int nsup = (nmb + (1 << lgR) - 1) >> lgR;
+        const double kd = (double)k;
+        // One item, with (PACK) or without several stationary blocks side by side in the wave; the plain variant
+        // keeps the item's block and row offset in scalar registers.
+        auto run = [&](auto pack_c, const int sb, const int slot, const int ue, const int ve) {
+            constexpr bool PACK = decltype(pack_c)::value;
+            const int yl = y_left ? ue : ve, ql = y_left ? ve : ue; // lane index of a streaming / stationary record
+            const int col = PACK ? ue * 8 + ve : lane;              // this lane's state: its column of the key table
+            // stationary blocks mb_first .. mb_last (those that exist); this lane's is mb.  A lane without a
+            // block of its own repeats the last block's work for its state: the same candidates into the same
+            // keys, which a minimum does not notice
+            const int mb_first = PACK ? sb << lgR : sb, mb_last = PACK ? imin(mb_first + (1 << lgR) - 1, nmb - 1) : sb;
             const int mb = PACK ? imin(mb_first + slot, mb_last) : sb;
-            const int q0 = qM0 + 8 * mb;                // first stationary unit count of this lane's block
-            // streaming range: every unit count some block of the item pairs with inside the target
-            // group; a lane's surplus steps fall on targets outside the group and are swallowed
-            int mlo = imax(yM0, a_g0 - (qM0 + 8 * mb_last + 7)), mhi = imin(yM1, a_g1 - (qM0 + 8 * mb_first));
-            if (np > 1 && mlo <= mhi) { // piece `part` of `np` of that range
-                const int len = mhi - mlo + 1, lo = mlo + div_small(len * part, np);
-                mhi = mlo + div_small(len * (part + 1), np) - 1;
-                mlo = lo;
-            }
-            if (mlo > mhi) continue;
+            // streaming range: every unit count some block of the item pairs with inside the target group
+            const int mlo = imax(yM0, a_g0 - (qM0 + 8 * mb_last + 7)), mhi = imin(yM1, a_g1 - (qM0 + 8 * mb_first));
+            if (mlo > mhi) return;
             double bb2[8], bbt[8], btm[8], acc[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const int o = fillY + (8 * mb + i) * 8 + ql;
-                const double2 p = pair[o];
-                bb2[i] = p.x; bbt[i] = p.y; btm[i] = tmv[o];
+                if (PACK) { // each lane reads its own block's records
+                    const int tab = 8 * mb + i;
+                    Rec24 rc = load24(src.s, (__umul24(imin(tab, nS - 1), t.tab_recs) + (ql << shS)) * 32u);
+                    if (tab >= nS) rc.a.x = rc.a.y = kNone;
+                    rc = combine(rc, !y_left);
+                    bb2[i] = rc.a.x; bbt[i] = rc.a.y; btm[i] = rc.tm;
+                } else {
+                    const int o = fillY + i * 8 + ql;
+                    const double2 p = pair[o];
+                    bb2[i] = p.x; bbt[i] = p.y; btm[i] = tmv[o];
+                }
                 acc[i] = kNone;
             }
-            const double kd = (double)k;
-            const int len = mhi - mlo + 1, j0 = (8 - (len & 7)) & 7;
+            const int j0 = (mlo - mhi - 1) & 7;
             int mbase = mlo - j0; // step j of a group handles streaming unit count mbase + j; the first group may start at j0
-            const int aoff = q0 - a_g0;
+            // row of the key table of target y + q0.  Its distance from the target group is at most seven in the plain
+            // variant (the padding rows take those); side by side a lane's surplus steps may lie further out and
+            // are turned to the first padding row on either side.
+            int row = mbase + qM0 + 8 * mb - a_g0 + kKeyPad;
+            unsigned long long *kcol = s_acc + (PACK ? col : row * 64 + col);
             // one step: the streaming record y against the eight stationary ones, candidates for the
             // targets y + q0 + i, into the rotating minima; then the minimum of target y + q0 is
             // complete for this item.  The streaming record of the NEXT step is read before this
@@ -673,55 +637,68 @@ __global__ void __launch_bounds__(256, FB == kFillBatch ? 1 : 4) k_split_key(Tab
             const double *ta = tmv + (mlo - yM0) * 8 + yl;
             double2 p = *pa;
             double atm = *ta;
+            auto merge = [&](int j, const double T) {
+                unsigned long long *dst = PACK ? kcol + imin(imax(row + j, kKeyPad - 1), kKeyPad + na) * 64 : kcol + j * 64;
+                atomicMin(dst, (unsigned long long)__double_as_longlong(fma(T, KS, kd)));
+            };
 #define OOB_STEP(j)                                                                                   \
     {                                                                                                 \
-        const int m = mbase + (j);                                                                    \
         pa += 8; ta += 8;                                                                             \
         const double2 pn = *pa; /* may read one record past the last one: staged memory, unused */    \
         const double tn = *ta;                                                                        \
+        /* the eighth candidate is the first one of its target: its slot was flushed one step ago */  \
         four_candidates<false>(acc[(j) & 7], acc[((j) + 1) & 7], acc[((j) + 2) & 7], acc[((j) + 3) & 7], bb2, bbt, btm, p, atm); \
         four_candidates<true>(acc[((j) + 4) & 7], acc[((j) + 5) & 7], acc[((j) + 6) & 7], acc[((j) + 7) & 7], bb2 + 4, bbt + 4, btm + 4, p, atm); \
-        const int row = imin(imax(m + aoff, -1), na) + 1;                                             \
-        atomicMin(&s_acc[row * 64 + col], (unsigned long long)__double_as_longlong(fma(acc[(j)], KS, kd))); \
+        merge(j, acc[(j)]);                                                                           \
         p = pn; atm = tn;                                                                             \
     }
             if (j0) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
                     if (j >= j0) OOB_STEP(j)
-                mbase += 8;
+                mbase += 8; row += 8;
+                if (!PACK) kcol += 8 * 64;
             }
             for (; mbase <= mhi; mbase += 8) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) OOB_STEP(j)
+                row += 8;
+                if (!PACK) kcol += 8 * 64;
             }
 #undef OOB_STEP
             // the last step was j = 7 with unit count mhi: minima 0..6 belong to targets mhi + q0 + 1 + i
 #pragma unroll
-            for (int i = 0; i < 7; ++i) {
-                const int row = imin(imax(mhi + 1 + i + aoff, -1), na) + 1;
-                atomicMin(&s_acc[row * 64 + col], (unsigned long long)__double_as_longlong(fma(acc[i], KS, kd)));
+            for (int i = 0; i < 7; ++i) merge(i, acc[i]);
+        };
+        if (lgR > 0) {
+            int slot, ue, ve; // this lane's block among the item's, its row and column
+            if (lr <= lc) {   // rows 0..2^lr-1, all columns
+                slot = lane >> (3 + lr); ue = (lane >> 3) & ((1 << lr) - 1); ve = lane & 7;
+            } else {          // all rows, the last 2^lc columns
+                const int w = lane & ((8 << lc) - 1);
+                slot = lane >> (3 + lc); ue = w >> lc; ve = 8 - (1 << lc) + (w & ((1 << lc) - 1));
+            }
+            for (int item = 0; item < nsup; ++item) run(std::true_type{}, item, slot, ue, ve);
+            preS = loadS(next, 0);
+        } else {
+            for (int item = 0; item < nmb; ++item) {
+                if (item == nmb - 1 && lt > last) preS = Rec24{make_double2(kNone, kNone), 0.0};
+                store(fillY + lane, combine(preS, !y_left));
+                preS = item + 1 < nmb ? loadS(src, item + 1) : loadS(next, 0); // in flight during this item
+                wave_fence();
+                run(std::false_type{}, item, 0, lane >> 3, lane & 7);
+                wave_fence();
             }
         }
-        };
-        if (R > 1 && nmb > 1 && (halves & 4)) run_items(std::true_type{}, R, lgR, slot, ue, ve);
-        else run_items(std::false_type{}, 1, 0, 0, lane >> 3, lane & 7);
-        if (NBUF == 1) __syncthreads(); // one buffer: everybody is done reading it before it is refilled
-        if (k < kmax) {
-#pragma unroll
-            for (int q = 0; q < FB; ++q)
-                stage_store(g, s_pair[nxt], s_tm[nxt], threadIdx.x + q * blockDim.x, pre[q]);
-            for (int e = threadIdx.x + FB * blockDim.x; e < TS; e += blockDim.x)
-                stage_store(g, s_pair[nxt], s_tm[nxt], e, stage_load(g, spn, e));
-        }
-        __syncthreads(); // buffer cur fully consumed, buffer cur^1 complete
+        wave_fence();
     }
+    wg_sync();
     // merge into the level's keys: other segments of the same block do the same
     for (int e = threadIdx.x; e < na * 64; e += blockDim.x) {
-        const unsigned long long key = s_acc[64 + e];
+        const unsigned long long key = s_acc[kKeyPad * 64 + e];
         if (key == kNoneBits) continue;
-        const int aidx = fam_base + a_g0 + (e >> 6) - dlo_of(Sp, M);
-        const long long slot = ((long long)(s - 1) * NAall + aidx) * NT + tile;
+        const int aidx = fam_base + a_g0 + (e >> 6) - ka.dlo;
+        const long long slot = ((long long)(s - 1) * ka.NAall + aidx) * ka.NT + tile;
         atomicMin(&t.partKey[slot * 64 + (e & 63)], key);
     }
 }
@@ -901,12 +878,7 @@ constexpr int kSel8Keys = 8;   // keys a lane has in flight (64 splits per round
 constexpr int kSel8Outer = 4;  // candidates of the outer splits a lane has in flight
 constexpr int kSel8M = 2;      // m a lane tests per round (16 per state)
 
-__device__ __forceinline__ Rec24 load24(const Rec *p) {
-    Rec24 r;
-    r.a = *(const double2 *)p;
-    r.tm = p->tmax;
-    return r;
-}
+__device__ __forceinline__ Rec24 load24(const Rec *p) { return load24(p, 0); }
 // Eq. 1-3 for one candidate from the (T, T1, tmax) of its children.
 __device__ __forceinline__ double cand_total(const Rec24 &a, const Rec24 &b, double cl, double cr) {
     return a.tm >= b.tm ? (a.a.x + cl * a.tm) + 2.0 * b.a.y : a.a.y + (b.a.x + cr * b.tm);
@@ -1213,7 +1185,7 @@ long long part_slots(int L, int M, int n_max, int Nb) {
 }
 
 struct Carve {
-    size_t lvl_tab, PT, PF, PM, rec, kstar, choice, partT, partK, stack, flags, seg_tab, total;
+    size_t lvl_tab, lvl_dir, PT, PF, PM, rec, kstar, choice, partT, partK, stack, flags, seg_tab, total;
     long long recs, slots;
 };
 // Byte offsets of the workspace arrays, sized for the handle's maxima.
@@ -1225,6 +1197,7 @@ Carve carve(int L, int nodes, int M) {
     const int Smax = smax_of(L, nodes, M, 0);
     size_t o = 0;
     c.lvl_tab = o; o = align_up(o + sizeof(long long) * (OOB_MAX_L + 3));
+    c.lvl_dir = o; o = align_up(o + sizeof(int2) * (OOB_MAX_L + 3));
     c.PT = o;      o = align_up(o + sizeof(long long) * (size_t)(M + 1) * (L + 1));
     c.PF = o;      o = align_up(o + sizeof(int) * (size_t)(M + 1) * (L + 1));
     c.PM = o;      o = align_up(o + sizeof(long long) * (size_t)(L + 1));
@@ -1269,7 +1242,7 @@ constexpr size_t kLdsLimit = 160 * 1024; // gfx950: 160 KB of LDS per workgroup
 constexpr size_t kLdsPrefer = 64 * 1024; // at least two workgroups per compute unit
 
 // Launch shape of k_split for one family of one level.
-struct SplitPlan { int waves, groups, pc, cls, ntab, na; size_t lds; };
+struct SplitPlan { int waves, groups, pc, ntab, na; size_t lds; };
 bool plan_split(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
     target_units(fam, Sp, sh.M, sh.n_max, &t_lo, &t_hi);
@@ -1302,8 +1275,7 @@ int env_or(const char *name, int dflt) {
     return v && *v ? atoi(v) : dflt;
 }
 // Debug knobs, read once when the library is loaded (the defaults are the measured optimum).
-static const int kKeyWaves = env_or("OOB_TUNE_KEY_WAVES", 4);
-static const int kKeyHalves = env_or("OOB_TUNE_KEY_HALVES", 2);
+static const int kKeyWaves = imin(env_or("OOB_TUNE_KEY_WAVES", 4), 4);
 static const int kKeyPack = env_or("OOB_TUNE_KEY_PACK", 1);
 static const int kBatchOverlap = env_or("OOB_TUNE_BATCH_OVERLAP", 0);
 static const int kBatchLanes = env_or("OOB_TUNE_BATCH_LANES", 8);
@@ -1312,7 +1284,7 @@ static const int kBatchLanes = env_or("OOB_TUNE_BATCH_LANES", 8);
 // the plain select only wait longer for a place); measured on the headline workload, where 78-88 gave
 // the same time.  Handle options move both thresholds.
 constexpr int kSelect8From = 82, kFuseFrom = 82;
-bool plan_split_key(const Shape &sh, int Sp, int fam, int xcd_order, SplitPlan *p) {
+bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
     target_units(fam, Sp, sh.M, sh.n_max, &t_lo, &t_hi);
     if (fam == 0 && Sp > sh.M) return false;
@@ -1328,17 +1300,16 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, int xcd_order, SplitPlan *
             const int a0 = t_lo + g * kKeyTargets, a1 = imin(t_hi, a0 + kKeyTargets - 1);
             const int mA0 = imax(A_lo, a0 - B_hi), mA1 = imin(A_hi, a1 - B_lo);
             const int mB0 = imax(B_lo, a0 - A_hi), mB1 = imin(B_hi, a1 - A_lo);
-            if (mA0 <= mA1 && mB0 <= mB1) { // either child may be the stationary (padded) side
+            if (mA0 <= mA1 && mB0 <= mB1) {
                 const int nA = mA1 - mA0 + 1, nB = mB1 - mB0 + 1;
-                ntab = imax(ntab, imax(nA + 8 * cdiv(nB, 8), nB + 8 * cdiv(nA, 8)));
+                ntab = imax(ntab, 8 * cdiv(left_streams(nA, nB) ? nA : nB, 8) + 8); // streaming side, one block of the stationary side
             }
         }
     }
-    p->pc = (kKeyHalves & 3) | (kKeyPack ? 4 : 0) | (xcd_order ? 8 : 0); // bits 0-1: cut left-over items; bit 2: several items per wave near the range ends; bit 3: XCD-chunked task order
     p->ntab = ntab;
     p->na = imin(cnt, kKeyTargets);
     p->lds = 0; // staged records in static LDS by capacity class, key table in dynamic LDS: see the launch site
-    p->waves = kKeyWaves;
+    p->pc = 0; p->waves = kKeyWaves; // by launch, see launch_split_keys
     return true;
 }
 
@@ -1478,6 +1449,7 @@ static Tables make_tables(const oob_plan *h, int lane, const Shape &sh, int *sta
     t.coff = col_shift(sh.L);
     t.tab_recs = tri_blocks(t.NB) * 64;
     t.lvl_tab = (long long *)(ws + h->cv.lvl_tab);
+    t.lvl_dir = (int2 *)(ws + h->cv.lvl_dir);
     t.PT = (long long *)(ws + h->cv.PT);
     t.PF = (int *)(ws + h->cv.PF);
     t.PM = (long long *)(ws + h->cv.PM);
@@ -1503,10 +1475,8 @@ static bool out_ok(const oob_templates *o) {
 
 // The splits s0, s0 + sstep, ... (scount of them) of level S.
 struct SplitRange { int s0, sstep, scount; };
-// Waves per workgroup of a keyed launch: as many as the split with the most work items (8-blocks of
-// the stationary side) offers per split point, at most kKeyWaves.  The low levels have one or two
-// items per split point: more waves would only idle at the barriers and take up residency.
-static int waves_for(const Shape &sh, int S, int fam, const SplitPlan &sp, SplitRange sr) {
+// 8-blocks of the stationary side of the split that has the most of them.
+static int most_blocks(const Shape &sh, int S, int fam, const SplitPlan &sp, SplitRange sr) {
     int t_lo, t_hi;
     target_units(fam, S, sh.M, sh.n_max, &t_lo, &t_hi);
     int most = 1;
@@ -1517,72 +1487,57 @@ static int waves_for(const Shape &sh, int S, int fam, const SplitPlan &sp, Split
         child_units(fam, r, sh.M, sh.n_max, &B_lo, &B_hi);
         for (int g = 0; g < sp.groups; ++g) {
             const int a0 = t_lo + g * kKeyTargets, a1 = imin(t_hi, a0 + kKeyTargets - 1);
-            const int mA0 = imax(A_lo, a0 - B_hi), mA1 = imin(A_hi, a1 - B_lo);
-            const int mB0 = imax(B_lo, a0 - A_hi), mB1 = imin(B_hi, a1 - A_lo);
-            if (mA0 > mA1 || mB0 > mB1) continue;
-            const bool y_left = role_cost(mA0, mA1, mB0, mB1, a0, a1) <= role_cost(mB0, mB1, mA0, mA1, a0, a1);
-            most = imax(most, cdiv(y_left ? mB1 - mB0 + 1 : mA1 - mA0 + 1, 8));
+            const int nA = imin(A_hi, a1 - B_lo) - imax(A_lo, a0 - B_hi) + 1, nB = imin(B_hi, a1 - A_lo) - imax(B_lo, a0 - A_hi) + 1;
+            if (nA > 0 && nB > 0) most = imax(most, cdiv(left_streams(nA, nB) ? nB : nA, 8));
         }
     }
-    return imin(kKeyWaves, most);
+    return most;
 }
 
-// LDS of a keyed launch: the staged records of one split point (static, by capacity class NTAB of the
-// tables staged) and the key table of the launch's own target count (dynamic).  A launch whose
-// workgroups fit a compute unit's LDS four times runs the variant held to 128 registers (four
-// waves per SIMD), else the one with three records in flight (three waves per SIMD either way).
-static const int kKeyClasses[] = {24, 32, 48, 64, 96, 136};
-static int key_class(int ntab, int na) {
-    (void)na;
-    for (int c = 0; c < 6; ++c)
-        if (ntab <= kKeyClasses[c]) return c;
-    return -1;
-}
-static size_t key_table_bytes(int na) { return (size_t)(na + 2) * 64 * sizeof(unsigned long long); }
 // A keyed launch: the target groups of family `fam` (gz of them) and, in a launch for both families
-// of a low level, those of the whole-node family behind them (`groups` in all).
-struct KeyLaunch { int fam, gz, groups, cls, na, pc, waves; };
-template <int NTAB>
-static void launch_split_key_c(const Tables &t, int S, const KeyLaunch &kl, int NT, int NAall, SplitRange sr,
-                               hipStream_t st) {
-    const dim3 grid(seg_count(t.sh.L, S), sr.scount, kl.groups);
-    const size_t dyn = key_table_bytes(kl.na), total = (size_t)NTAB * 8 * 24 + dyn;
-    if (4 * total <= kLdsLimit)
-        hipLaunchKernelGGL((k_split_key<NTAB, 1, kFillBatchSmall>), grid, dim3(kl.waves * 64), dyn, st, t, S, kl.fam, kl.gz, NT, NAall,
-                           kl.pc, sr.s0, sr.sstep);
-    else
-        hipLaunchKernelGGL((k_split_key<NTAB, 1, kFillBatch>), grid, dim3(kl.waves * 64), dyn, st, t, S, kl.fam, kl.gz, NT,
-                           NAall, kl.pc, sr.s0, sr.sstep);
-}
-static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int NAall, SplitRange sr,
-                             hipStream_t st) {
-    if (sr.scount < 1) return;
-    switch (kl.cls) {
-    case 0: launch_split_key_c<24>(t, S, kl, NT, NAall, sr, st); break;
-    case 1: launch_split_key_c<32>(t, S, kl, NT, NAall, sr, st); break;
-    case 2: launch_split_key_c<48>(t, S, kl, NT, NAall, sr, st); break;
-    case 3: launch_split_key_c<64>(t, S, kl, NT, NAall, sr, st); break;
-    case 4: launch_split_key_c<96>(t, S, kl, NT, NAall, sr, st); break;
-    default: launch_split_key_c<136>(t, S, kl, NT, NAall, sr, st); break;
+// of a low level, those of the whole-node family behind them (`groups` in all); at most ntab tables
+// staged per split point, na targets per group, `blocks` work items per split point.
+struct KeyLaunch { int fam, gz, groups, ntab, na, blocks; };
+constexpr int kKeyTables = 144; // most tables per split point the keyed kernel serves
+static size_t key_table_bytes(int na) { return (size_t)(na + 2 * kKeyPad) * 64 * sizeof(unsigned long long); }
+template <int ROWS>
+static void launch_split_key_r(const Tables &t, const KeyArgs &ka, const KeyLaunch &kl, SplitRange sr, hipStream_t st) {
+    // waves per workgroup: as many as put the most waves on a compute unit (they share the key table), four at most
+    const size_t keys = (size_t)ROWS * 512, per = (size_t)kl.ntab * 192;
+    int waves = 1, most = 0;
+    for (int w = 1; w <= kKeyWaves; ++w) {
+        const int on = imin((int)(kLdsLimit / (keys + w * per)) * w, 4 * kWavesPerSimd);
+        if (on > most) { most = on; waves = w; }
     }
+    hipLaunchKernelGGL(k_split_key<ROWS>, dim3(seg_count(t.sh.L, ka.Sp), sr.scount, kl.groups), dim3(waves * 64), waves * per, st, t, ka);
+}
+static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int NAall, int xcd, SplitRange sr, hipStream_t st) {
+    KeyArgs ka;
+    ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.NAall = NAall; ka.s0 = sr.s0; ka.sstep = sr.sstep;
+    ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
+    const int rows = kl.na + 2 * kKeyPad;
+    if (rows <= 24) launch_split_key_r<24>(t, ka, kl, sr, st);
+    else if (rows <= 36) launch_split_key_r<36>(t, ka, kl, sr, st);
+    else if (rows <= 48) launch_split_key_r<48>(t, ka, kl, sr, st);
+    else if (rows <= 60) launch_split_key_r<60>(t, ka, kl, sr, st);
+    else launch_split_key_r<kKeyTargets + 2 * kKeyPad>(t, ka, kl, sr, st);
 }
 // The keyed launches of the splits `sr` of a level: one per family, or one for both.
-static void launch_split_keys(const Tables &t, int S, const bool *have, const SplitPlan *kp, int NT, int NAall,
+static void launch_split_keys(const Tables &t, int S, const bool *have, const SplitPlan *kp, int NT, int NAall, int xcd,
                               SplitRange sr, hipStream_t st) {
     if (sr.scount < 1) return;
     KeyLaunch kl[2];
     for (int fam = 0; fam < 2; ++fam)
         if (have[fam])
-            kl[fam] = KeyLaunch{fam, kp[fam].groups, kp[fam].groups, kp[fam].cls, kp[fam].na, kp[fam].pc,
-                                waves_for(t.sh, S, fam, kp[fam], sr)};
+            kl[fam] = KeyLaunch{fam, kp[fam].groups, kp[fam].groups, kp[fam].ntab, kp[fam].na, most_blocks(t.sh, S, fam, kp[fam], sr)};
     if (have[0] && have[1]) {
-        const KeyLaunch both{0, kl[0].groups, kl[0].groups + kl[1].groups, imax(kl[0].cls, kl[1].cls),
-                             imax(kl[0].na, kl[1].na), kl[0].pc, imax(kl[0].waves, kl[1].waves)};
-        launch_split_key(t, S, both, NT, NAall, sr, st);
+        const KeyLaunch both{0, kl[0].groups, kl[0].groups + kl[1].groups, imax(kl[0].ntab, kl[1].ntab),
+                             imax(kl[0].na, kl[1].na), imax(kl[0].blocks, kl[1].blocks)};
+        launch_split_key(t, S, both, NT, NAall, xcd, sr, st);
         return;
     }
     for (int fam = 0; fam < 2; ++fam)
-        if (have[fam]) launch_split_key(t, S, kl[fam], NT, NAall, sr, st);
+        if (have[fam]) launch_split_key(t, S, kl[fam], NT, NAall, xcd, sr, st);
 }
 
 template <int PC>
@@ -1621,7 +1576,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     for (int S = 2; S <= sh.Smax; ++S)
         for (int fam = 0; fam < 2; ++fam) {
             SplitPlan sp;
-            if (plan_split_key(sh, S, fam, h->opt_xcd, &sp) && key_class(sp.ntab, sp.na) < 0) force_plain = 1;
+            if (plan_split_key(sh, S, fam, &sp) && sp.ntab > kKeyTables) force_plain = 1;
         }
     if (force_plain)
         for (int S = 2; S <= sh.Smax; ++S)
@@ -1668,14 +1623,13 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         SplitPlan sp[2], kp[2];
         bool have[2];
         for (int fam = 0; fam < 2; ++fam) {
-            have[fam] = plan_split(sh, S, fam, &sp[fam]) && plan_split_key(sh, S, fam, h->opt_xcd, &kp[fam]);
-            if (have[fam]) kp[fam].cls = key_class(kp[fam].ntab, kp[fam].na);
+            have[fam] = plan_split(sh, S, fam, &sp[fam]) && plan_split_key(sh, S, fam, &kp[fam]);
         }
         const bool inner = overlap && S >= 4;
         if (inner) {
             hipStream_t sx = (S & 1) ? lane.aux2 : lane.aux;
             OOB_HIP_CHECK(hipStreamWaitEvent(sx, lane.ev_level[2 * (S - 2)], 0)); // select of level S'-2
-            launch_split_keys(tl, S, have, kp, NT, NAall, SplitRange{2, 1, S - 3}, sx);
+            launch_split_keys(tl, S, have, kp, NT, NAall, h->opt_xcd, SplitRange{2, 1, S - 3}, sx);
             OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S + 1], sx));
         }
         // the outer splits: launches of their own, or evaluated by the select kernel itself
@@ -1683,7 +1637,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         if (!force_plain) {
             SplitRange sr = inner ? SplitRange{1, S - 2, 2} : SplitRange{1, 1, S - 1};
             if (fuse) sr = inner ? SplitRange{1, 1, 0} : SplitRange{2, 1, S - 3};
-            launch_split_keys(tl, S, have, kp, NT, NAall, sr, st);
+            launch_split_keys(tl, S, have, kp, NT, NAall, h->opt_xcd, sr, st);
         }
         for (int fam = 0; fam < 2 && force_plain; ++fam) {
             if (!have[fam]) continue;
