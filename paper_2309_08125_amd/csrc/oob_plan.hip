@@ -20,10 +20,10 @@
 //
 // One level S' = split kernels, then a select kernel.
 //   k_split_key  per (block of the (u,v) plane, segment of its split points k, split s, group of
-//            target device sets): the minimum over (k, m) of Eq. 1-3 per state as a key
-//            total * 2^kbits + k, merged into the level's key array (described at the kernel).
-//            k_split is the variant without keys for shapes beyond its LDS classes.
-//   k_select / k_select8  per state: first s with the smallest key, then the first m at that
+//            target device sets): the minimum over (k, m) of Eq. 1-3 per state as a
+//            key of (total, s, k), merged into the level's key array (described at the kernel).
+//            k_split is the variant without keys for shapes beyond its LDS.
+//   k_select_key / k_select  per state: from the smallest key (from the per-split minima) the first m at that
 //            (s, k) whose candidate equals it -- the smallest (T, s, k, m) -- and the record.
 // Before level 1 one launch (k_prepare) scans and validates the profile, lays out the tables, lists the
 // tasks of every level and clears the keys; after the last level k_pick chooses the stage count of
@@ -66,7 +66,7 @@ struct Tables {
     Rec *rec;             // [tables * tab_recs]
     int *kstar, *choice;  // [tables * tab_recs]
     double *partT;        // [(S'-1) * deltas * tiles * 64] per-split minima of the current level
-    unsigned long long *partKey; // the same memory: keys total * 2^kbits + k (keyed kernel)
+    unsigned long long *key; // the same memory: [deltas * tiles * 64] keys of the current level (keyed kernel)
     int *partK;           // same shape: first k reaching the minimum
     int *stack;           // backtracking stacks / coverage ring
     int2 *seg_tab;        // per level: (tile index, ub | vb << 8 | segment << 16) of every split task
@@ -385,7 +385,11 @@ __global__ void __launch_bounds__(512) k_split(Tables t, int Sp, int fam, int NT
 // minima rotate: after a step the minimum of the lowest target is complete for this item and is merged into the
 // workgroup's LDS table acc[a][lane] with an integer atomic min on the bits of key = total * 2^kbits + k
 // (non-negative doubles order like their bit patterns).  The key makes the merge order-free
-// and yields, per (s, state), the smallest total and the first k reaching it at once.
+// and yields, per (s, state), the smallest total and the first k reaching it at once.  At the end the workgroup merges
+// its keys, with the split in them, into the level's key per state: one key to read for the select where there
+// was one per split, and two orders of magnitude less memory to clear (batch of 32 jobs 99 -> 95 ms, headline
+// workload 8.43 -> 8.28 ms; reading the key first to save the atomic costs more than the atomic: 103 ms; eight or
+// sixteen keys per state against contention 96.6 and 97.8 ms).
 //
 // What bounds it: the instructions a wave issues, and its waits.  The step loop alone, out of LDS, takes 175 cycles of
 // a SIMD a step (eight candidates of 64 lanes) with four waves per SIMD, 186 with three, 206 with two, and about ten
@@ -470,6 +474,15 @@ struct KeyArgs {
     int t_lo1, dlo;      // smallest target of the whole-node family; first device set of the level
     int pack, xcd;       // several items per wave near the range ends; XCD-chunked task order
 };
+
+// Key of a level: total, split and split point as one integer, so that the smallest key is the smallest (T, s, k).  The
+// key of a workgroup is total * 2^kb + k below 2^52 in a double; s and k take kb <= 10 bits each.
+constexpr unsigned long long kNoKey = 0x7FF0000000000000ull;
+
+__device__ __forceinline__ unsigned long long wide_key(double part, int s, int kb) {
+    const unsigned long long v = (unsigned long long)__double_as_longlong(part + 0x1p52) & ((1ull << 52) - 1);
+    return (((v >> kb) << kb | (unsigned)s) << kb) | (v & ((1ull << kb) - 1));
+}
 
 // Order of a wave's LDS operations against those of its other lanes (they execute in order: only the compiler has to
 // be told).
@@ -693,13 +706,16 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
         wave_fence();
     }
     wg_sync();
-    // merge into the level's keys: other segments of the same block do the same
+    // merge into the level's keys, total, split and split point: other splits and segments of the same block do the
+    // same
+    const int kb = key_bits(L);
+    unsigned long long *const dst = t.key + ((long long)(fam_base + a_g0 - ka.dlo) * ka.NT + tile) * 64;
+    const long long row = (long long)ka.NT * 64; // keys of one device set
     for (int e = threadIdx.x; e < na * 64; e += blockDim.x) {
-        const unsigned long long key = s_acc[kKeyPad * 64 + e];
-        if (key == kNoneBits) continue;
-        const int aidx = fam_base + a_g0 + (e >> 6) - ka.dlo;
-        const long long slot = ((long long)(s - 1) * ka.NAall + aidx) * ka.NT + tile;
-        atomicMin(&t.partKey[slot * 64 + (e & 63)], key);
+        const unsigned long long part = s_acc[kKeyPad * 64 + e];
+        if (part == kNoneBits) continue;
+        const unsigned long long key = wide_key(__longlong_as_double((long long)part), s, kb);
+        atomicMin(dst + (e >> 6) * row + (e & 63), key);
     }
 }
 
@@ -737,24 +753,21 @@ __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
 
 // Everything a call needs before level 1, as one launch of kSetupThreads-wide workgroups:
 // workgroup 0 the set-up, workgroups 1 .. Smax-1 the task lists of the levels 2 .. Smax, the rest
-// set the n keys of the per-split minima to "no such state".  The three parts touch disjoint memory.
+// set the n keys of either buffer to "no such state".  The three parts touch disjoint memory.
 __global__ void __launch_bounds__(kSetupThreads) k_prepare(Tables t, oob_profile prof, int force_plain, int by_row,
-                                                           unsigned long long *keys, long long n) {
+                                                           long long stride, long long n) {
     const int b = blockIdx.x, nseg = imax(t.sh.Smax - 1, 0);
     if (b == 0) { setup_body(t, prof, force_plain); return; }
     if (b <= nseg) { seg_tab_body(t, b + 1, by_row); return; }
     const long long i = (long long)(b - 1 - nseg) * blockDim.x + threadIdx.x;
-    if (i < n) keys[i] = 0x7FF0000000000000ull;
+    if (i < 2 * n) t.key[i < n ? i : stride + i - n] = kNoKey;
 }
 
 // ---------------------------------------------------------------------------------------
 // Levels S' >= 2, second kernel: grid (block of the plane, delta), one lane per state.
 // ---------------------------------------------------------------------------------------
-// Loads a lane of k_select keeps in flight: keys of the splits, and pairs of child records while it looks
-// for the first m.  With 16 and 4 the kernel needs 98 registers, with 16 and 2 it needs 64 and the call
-// is 1 % faster (its waves sit on the chain between the levels and find room beside the split kernels'
-// sooner); 8 and 2 the same; one pair or 4 keys at a time: slower again, the kernel's own latency shows.
-constexpr int kSelKeys = 16, kSelPairs = 2;
+// Without the keys of k_split_key: the per-split minima of k_split (flags[1]), or every candidate.
+constexpr int kSelPairs = 2; // pairs of child records a lane has in flight while it looks for the first m
 __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall) {
     const int L = t.sh.L, M = t.sh.M, lane = threadIdx.x;
     int ub, vb;
@@ -763,23 +776,7 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
     const int u = ub * 8 + (lane >> 3), v = vb * 8 + (lane & 7) - t.coff;
     double best = kNone;
     int bs = 0, bk = 0;
-    if (t.flags[0]) { // keys total * 2^kbits + k; consumed keys go back to "no such state"
-        const double KS = (double)(1 << key_bits(L)), inv = 1.0 / KS;
-        const long long o0 = ((long long)aidx * NT + blockIdx.x) * 64 + lane, os = (long long)NAall * NT * 64;
-        double bkey = kNone;
-        for (int s0 = 1; s0 < Sp; s0 += kSelKeys) { // independent loads in flight
-            double key[kSelKeys];
-#pragma unroll
-            for (int q = 0; q < kSelKeys; ++q) key[q] = s0 + q < Sp ? t.partT[o0 + (s0 + q - 1) * os] : kNone;
-#pragma unroll
-            for (int q = 0; q < kSelKeys; ++q) {
-                const double T = floor(key[q] * inv); // +inf stays +inf
-                if (T < best) { best = T; bs = s0 + q; bkey = key[q]; }
-            }
-        }
-        if (best < kNone) bk = (int)(bkey - best * KS);
-        for (int s = 1; s < Sp; ++s) t.partT[o0 + (s - 1) * os] = kNone;
-    } else if (t.flags[1]) {
+    if (t.flags[1]) {
         for (int s = 1; s < Sp; ++s) { // first s with the smallest minimum
             const long long o = (((long long)(s - 1) * NAall + aidx) * NT + blockIdx.x) * 64 + lane;
             const double T = t.partT[o];
@@ -791,7 +788,7 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
     const Family fam = family_of(delta, M);
     int bm = 0;
     Rec a = out, b = out;
-    if (!t.flags[0] && !t.flags[1]) {
+    if (!t.flags[1]) {
         // Totals too large for keys (decided by the set-up kernel from the profile): every candidate
         // (s, k, m) of this state in that order with a strict-minimum update.  Slow, exact, rare.
         if (v <= L && v - u >= Sp)
@@ -859,24 +856,23 @@ __global__ void __launch_bounds__(64) k_select(Tables t, int Sp, int NT, int NAa
 }
 
 // ---------------------------------------------------------------------------------------
-// Levels S' >= 2, second kernel, keyed path: grid (block of the plane, delta, row of the block),
-// eight lanes per state (a wave holds the eight states of one row of the block).
+// Levels S' >= 2, second kernel, keyed path: grid (block of the plane, delta, LPS parts of the block),
+// LPS lanes per state.
 //
 // The lanes of a state share out what the state has to look at, so that each dependent round trip
-// to memory covers eight times as much as it would with one lane per state; the kernel sits on the
+// to memory covers LPS times as much as it would with one lane per state; the kernel sits on the
 // chain between the levels and its duration is made of such round trips.
 //   1. FUSE only: the two outer splits s = 1 and s = S'-1, whose one-stage child has a single unit
 //      count across nodes (a line of candidates instead of a rectangle), are evaluated here,
 //      candidate by candidate from the child records; no split kernel is launched for them.
-//   2. The keys of the (other) splits: smallest total, then smallest s (a key holds its smallest k).
-//   3. The eight partial minima of a state are merged in the order (T, s, k, m).
-//   4. A winner that came from a key does not know its m yet: the lanes test eight m at a time.
+//   2. The key of the (other) splits holds the smallest (T, s, k).
+//   3. FUSE only: the lanes' partial minima are merged in the order (T, s, k, m).
+//   4. A winner that came from a key does not know its m yet: the lanes test LPS m at a time.
 //   5. Lane 0 of the state forms the record from the two child records.
-// Without keys (flags[0] = 0) the wave of row 0 evaluates the block one lane per state as k_select does.
+// Without keys (flags[0] = 0) the wave of part 0 evaluates the block one lane per state as k_select does.
 // ---------------------------------------------------------------------------------------
-constexpr int kSel8Keys = 8;   // keys a lane has in flight (64 splits per round of a state)
 constexpr int kSel8Outer = 4;  // candidates of the outer splits a lane has in flight
-constexpr int kSel8M = 2;      // m a lane tests per round (16 per state)
+constexpr int kSel8M = 2;      // m a lane tests per round
 
 __device__ __forceinline__ Rec24 load24(const Rec *p) { return load24(p, 0); }
 // Eq. 1-3 for one candidate from the (T, T1, tmax) of its children.
@@ -884,17 +880,17 @@ __device__ __forceinline__ double cand_total(const Rec24 &a, const Rec24 &b, dou
     return a.tm >= b.tm ? (a.a.x + cl * a.tm) + 2.0 * b.a.y : a.a.y + (b.a.x + cr * b.tm);
 }
 
-template <bool FUSE>
-__global__ void __launch_bounds__(64) k_select8(Tables t, int Sp, int NT, int NAall) {
+template <int LPS, bool FUSE>
+__global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int NAall) {
     if (t.flags[0] == 0) {
         if (blockIdx.z == 0) select_lane_per_state(t, Sp, NT, NAall);
         return;
     }
-    const int L = t.sh.L, M = t.sh.M, lane = threadIdx.x, sub = lane & 7, st = lane >> 3;
+    const int L = t.sh.L, M = t.sh.M, lane = threadIdx.x, sub = lane & (LPS - 1);
     int ub, vb;
     tile_decode(L, Sp, blockIdx.x, &ub, &vb);
     const int aidx = blockIdx.y, delta = dlo_of(Sp, M) + aidx;
-    const int tl = blockIdx.z * 8 + st, u = ub * 8 + blockIdx.z, v = vb * 8 + st - t.coff;
+    const int tl = blockIdx.z * (64 / LPS) + lane / LPS, u = ub * 8 + (tl >> 3), v = vb * 8 + (tl & 7) - t.coff;
     const bool valid = v <= L && v - u >= Sp;
     const Family fam = family_of(delta, M);
     const bool fixed_nb = t.sh.Nb > 0;
@@ -912,12 +908,12 @@ __global__ void __launch_bounds__(64) k_select8(Tables t, int Sp, int NT, int NA
             const Rec *baseA = t.rec + (t.lvl_tab[s] - dlo_of(s, M) + fam.fam_base) * trecs;
             const Rec *baseB = t.rec + (t.lvl_tab[r] - dlo_of(r, M) + fam.fam_base + fam.units) * trecs;
             for (int m = mlo; m <= mhi; ++m)
-                for (int j0 = sub; j0 < nk; j0 += 8 * kSel8Outer) {
+                for (int j0 = sub; j0 < nk; j0 += LPS * kSel8Outer) {
                     Rec24 ra[kSel8Outer], rb[kSel8Outer];
                     int kk[kSel8Outer];
 #pragma unroll
                     for (int q = 0; q < kSel8Outer; ++q) { // past the end: the last candidate again
-                        const int k = u + s + imin(j0 + 8 * q, nk - 1);
+                        const int k = u + s + imin(j0 + LPS * q, nk - 1);
                         kk[q] = k;
                         ra[q] = load24(baseA + m * trecs + rec_off(u, k, t.coff, t.NB));
                         rb[q] = load24(baseB - m * trecs + rec_off(k, v, t.coff, t.NB));
@@ -931,43 +927,28 @@ __global__ void __launch_bounds__(64) k_select8(Tables t, int Sp, int NT, int NA
                 }
         }
     }
-    if (valid) { // keys total * 2^kbits + k; consumed keys go back to "no such state"
-        const double KS = (double)(1 << key_bits(L)), inv = 1.0 / KS;
-        const int s_lo = FUSE ? 2 : 1, s_hi = FUSE ? Sp - 2 : Sp - 1;
-        const long long o0 = ((long long)aidx * NT + blockIdx.x) * 64 + tl, os = (long long)NAall * NT * 64;
-        for (int s0 = s_lo + sub; s0 <= s_hi; s0 += 8 * kSel8Keys) {
-            double key[kSel8Keys];
-#pragma unroll
-            for (int q = 0; q < kSel8Keys; ++q) {
-                const int s = s0 + 8 * q;
-                key[q] = s <= s_hi ? t.partT[o0 + (s - 1) * os] : kNone;
-            }
-#pragma unroll
-            for (int q = 0; q < kSel8Keys; ++q) {
-                const int s = s0 + 8 * q;
-                if (s <= s_hi) t.partT[o0 + (s - 1) * os] = kNone;
-            }
-#pragma unroll
-            for (int q = 0; q < kSel8Keys; ++q) {
-                const int s = s0 + 8 * q;
-                const double T = floor(key[q] * inv);
-                if (T < kNone) {
-                    const unsigned tag = ((unsigned)s << 21) | ((unsigned)(int)(key[q] - T * KS) << 10);
-                    if (T < best || (T == best && tag < btag)) { best = T; btag = tag; }
-                }
-            }
+    if (valid) { // the consumed key goes back to "no such state"
+        const int kb = key_bits(L), mask = (1 << kb) - 1;
+        unsigned long long *const at = t.key + ((long long)aidx * NT + blockIdx.x) * 64 + tl;
+        const unsigned long long key = *at;
+        if (key != kNoKey) {
+            const double T = (double)(long long)(key >> 2 * kb);
+            const unsigned tag = ((unsigned)(key >> kb) & mask) << 21 | ((unsigned)key & mask) << 10;
+            if (T < best || (T == best && tag < btag)) { best = T; btag = tag; }
+            if (sub == 0) *at = kNoKey;
         }
     }
-    // the eight lanes of a state: smallest (T, s, k, m)
+    if (FUSE) { // the lanes of a state: smallest (T, s, k, m)
 #pragma unroll
-    for (int d = 1; d < 8; d <<= 1) {
-        const double ob = __shfl_xor(best, d, 64);
-        const unsigned ot = (unsigned)__shfl_xor((int)btag, d, 64);
-        if (ob < best || (ob == best && ot < btag)) { best = ob; btag = ot; }
+        for (int d = 1; d < LPS; d <<= 1) {
+            const double ob = __shfl_xor(best, d, 64);
+            const unsigned ot = (unsigned)__shfl_xor((int)btag, d, 64);
+            if (ob < best || (ob == best && ot < btag)) { best = ob; btag = ot; }
+        }
     }
     const int bs = (int)(btag >> 21), bk = (int)((btag >> 10) & 2047u);
     int bm = (int)(btag & 1023u);
-    if (best < kNone && bm == 0) { // first m whose candidate equals the minimum, eight m side by side
+    if (best < kNone && bm == 0) { // first m whose candidate equals the minimum, the lanes side by side
         const int r = Sp - bs;
         int mlo, mhi;
         m_range(fam.fam, fam.units, bs, r, M, t.sh.n_max, &mlo, &mhi);
@@ -976,22 +957,22 @@ __global__ void __launch_bounds__(64) k_select8(Tables t, int Sp, int NT, int NA
                            rec_off(u, bk, t.coff, t.NB);
         const Rec *baseB = t.rec + (t.lvl_tab[r] - dlo_of(r, M) + fam.fam_base + fam.units) * trecs +
                            rec_off(bk, v, t.coff, t.NB);
-        for (int m0 = mlo + sub; m0 - sub <= mhi && bm == 0; m0 += 8 * kSel8M) {
+        for (int m0 = mlo + sub; m0 - sub <= mhi && bm == 0; m0 += LPS * kSel8M) {
             Rec24 ra[kSel8M], rb[kSel8M];
 #pragma unroll
             for (int q = 0; q < kSel8M; ++q) {
-                const int m = imin(m0 + 8 * q, mhi);
+                const int m = imin(m0 + LPS * q, mhi);
                 ra[q] = load24(baseA + m * trecs);
                 rb[q] = load24(baseB - m * trecs);
             }
             int found = 0x7fffffff;
 #pragma unroll
             for (int q = kSel8M - 1; q >= 0; --q) {
-                const int m = m0 + 8 * q;
+                const int m = m0 + LPS * q;
                 if (m <= mhi && cand_total(ra[q], rb[q], cl, cr) == best) found = m;
             }
 #pragma unroll
-            for (int d = 1; d < 8; d <<= 1) found = imin(found, __shfl_xor(found, d, 64));
+            for (int d = 1; d < LPS; d <<= 1) found = imin(found, __shfl_xor(found, d, 64));
             if (found != 0x7fffffff) bm = found;
         }
     }
@@ -1284,6 +1265,7 @@ static const int kBatchLanes = env_or("OOB_TUNE_BATCH_LANES", 8);
 // the plain select only wait longer for a place); measured on the headline workload, where 78-88 gave
 // the same time.  Handle options move both thresholds.
 constexpr int kSelect8From = 82, kFuseFrom = 82;
+constexpr int kSelLanes = 1; // lanes per state below that
 bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
     target_units(fam, Sp, sh.M, sh.n_max, &t_lo, &t_hi);
@@ -1457,7 +1439,7 @@ static Tables make_tables(const oob_plan *h, int lane, const Shape &sh, int *sta
     t.kstar = (int *)(ws + h->cv.kstar);
     t.choice = (int *)(ws + h->cv.choice);
     t.partT = (double *)(ws + h->cv.partT);
-    t.partKey = (unsigned long long *)(ws + h->cv.partT);
+    t.key = (unsigned long long *)(ws + h->cv.partT);
     t.partK = (int *)(ws + h->cv.partK);
     t.stack = (int *)(ws + h->cv.stack);
     t.flags = (int *)(ws + h->cv.flags);
@@ -1588,8 +1570,10 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     work_counts(sh, (long long *)&out->states, (long long *)&out->candidates);
 
     const long long slot_stride = h->cv.slots * 64; // distance between the two buffers of per-split minima
-    hipLaunchKernelGGL(k_prepare, dim3((unsigned)(1 + imax(sh.Smax - 1, 0) + (2 * slot_stride + kSetupThreads - 1) / kSetupThreads)),
-                       dim3(kSetupThreads), 0, st, t, *profile, force_plain, h->opt_xcd, t.partKey, 2 * slot_stride);
+    long long keys = 0; // of the level that has most of them
+    for (int S = 2; S <= sh.Smax; ++S) keys = std::max(keys, (long long)(dhi_of(S, M, n_max) - dlo_of(S, M) + 1) * tile_count(L, S) * 64);
+    hipLaunchKernelGGL(k_prepare, dim3((unsigned)(1 + imax(sh.Smax - 1, 0) + (2 * keys + kSetupThreads - 1) / kSetupThreads)),
+                       dim3(kSetupThreads), 0, st, t, *profile, force_plain, h->opt_xcd, slot_stride, keys);
     hipLaunchKernelGGL(k_level1, dim3(tile_count(L, 1), M), dim3(64), 0, st, t,
                        (const long long *)profile->boundary_ns);
     // Levels.  Level S' depends on the lower levels like this: its inner splits 2 <= s <= S'-2 read the
@@ -1619,7 +1603,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         const int NT = tile_count(L, S);
         Tables tl = t; // this level's buffer of per-split minima
         tl.partT = t.partT + (S & 1) * slot_stride;
-        tl.partKey = t.partKey + (S & 1) * slot_stride;
+        tl.key = t.key + (S & 1) * slot_stride;
         SplitPlan sp[2], kp[2];
         bool have[2];
         for (int fam = 0; fam < 2; ++fam) {
@@ -1646,9 +1630,10 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
             else launch_split<1>(tl, S, fam, sp[fam], NT, NAall, st);
         }
         if (inner) OOB_HIP_CHECK(hipStreamWaitEvent(st, lane.ev_level[2 * S + 1], 0));
-        if (force_plain || (!fuse && S < h->opt_select8_from)) hipLaunchKernelGGL(k_select, dim3(NT, NAall), dim3(64), 0, st, tl, S, NT, NAall);
-        else if (fuse) hipLaunchKernelGGL(k_select8<true>, dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
-        else hipLaunchKernelGGL(k_select8<false>, dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
+        if (force_plain) hipLaunchKernelGGL(k_select, dim3(NT, NAall), dim3(64), 0, st, tl, S, NT, NAall);
+        else if (fuse) hipLaunchKernelGGL((k_select_key<8, true>), dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
+        else if (S >= h->opt_select8_from) hipLaunchKernelGGL((k_select_key<8, false>), dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
+        else hipLaunchKernelGGL((k_select_key<kSelLanes, false>), dim3(NT, NAall, kSelLanes), dim3(64), 0, st, tl, S, NT, NAall);
         if (overlap) OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S], st));
     }
     if (timed) { OOB_HIP_CHECK(hipEventRecord(h->ev_end, st)); h->timed = true; }
