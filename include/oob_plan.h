@@ -157,7 +157,7 @@ int oob_plan_destroy(oob_plan *h);
  *                        every XCD walks one contiguous stretch of that list (fewer bytes from
  *                        HBM, slightly more time on the headline workload); default 0
  *   OOB_OPT_ONE_STREAM   1: all levels on the caller's stream (no other stream, no events);
- *                        default 0: the inner splits of consecutive levels run on two streams of the
+ *                        default 0: the inner splits of the larger levels run on two streams of the
  *                        library beside the caller's, which carries the outer splits and the selects
  *   OOB_OPT_SELECT8_FROM value = first level S' whose select kernel works with eight lanes per
  *                        state (below it: one lane per state); default 82 (the top levels, where
@@ -166,12 +166,17 @@ int oob_plan_destroy(oob_plan *h);
  *                        evaluated inside that select kernel instead of by split launches of
  *                        their own; default 82.  A value of 2 covers every level, one above the
  *                        stage limit none
+ *   OOB_OPT_OVERLAP_FROM value = thousands of (s, k, m) candidates: the levels from the first to the last
+ *                        one with at least that many run their inner splits on the two streams of
+ *                        the library, the others run everything on the caller's stream; default
+ *                        24000 (a smaller level is done before the events of an overlap are enqueued)
  * Returns OOB_EINVAL for an unknown option. */
 #define OOB_OPT_PLAIN_SPLIT 1
 #define OOB_OPT_XCD_ORDER 2
 #define OOB_OPT_ONE_STREAM 3
 #define OOB_OPT_SELECT8_FROM 4
 #define OOB_OPT_FUSE_FROM 5
+#define OOB_OPT_OVERLAP_FROM 6
 int oob_plan_set_option(oob_plan *h, int option, int value);
 
 /* Test hook, host only (no GPU is touched): checks the table layout and the per-level task lists the

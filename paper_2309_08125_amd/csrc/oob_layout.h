@@ -134,15 +134,22 @@ __host__ __device__ inline int tile_vmax(int L, int vb) { return vb * 8 + 7 - co
 // whole groups of kSegUnit consecutive k (what it stages at a time; the last group may be short): as many segments as
 // the range divided by the target gives, rounded to the nearest, all of the same number of groups up to one.
 constexpr int kSegUnit = 4;
-constexpr int kSegTarget = 16, kSegTargetMid = 8, kSegTargetTop = 4, kSegMidLayers = 40, kSegTopLayers = 28;
 constexpr int kSegMin = 4; // no target below this (sizes the task lists)
-// The top levels (fewer than kSegTopLayers layers of slack, a handful of blocks) cannot fill the machine with
-// workgroups of sixteen split points, or of eight: there the target is four, and eight up to kSegMidLayers.  A longer
-// segment pays the set-up and the merge of its keys less often: 16 instead of 8 everywhere above took a batch of 32
-// jobs of 24..128 layers from 122 to 113 ms; with the line of the eight at 60 or 75 layers 101 and 104 ms instead of
-// 99 ms, the headline workload 7.97 and 8.16 ms instead of 7.64 ms; 24 or 32 split points were no better.
+constexpr int kSegTarget = 16, kSegWorkgroups = 512;
+// Split points of all blocks of the level, for one split.
+__host__ __device__ inline int level_krange(int L, int S) {
+    const int NB = nblocks_of(L), ubmax = (L - S) / 8;
+    int c = 0;
+    for (int d = NB - 1; d >= tile_dmin(L, S); --d) c += (imin(ubmax, NB - 1 - d) + 1) * (8 * d + 8 - col_shift(L) - S);
+    return c;
+}
+// The longest segments (16, 8 or 4 split points) that still make kSegWorkgroups workgroups of the level: a longer segment
+// pays the set-up and the merge of its keys less often, a shorter one fills the machine and shortens the level.
+// Measured with 256, 512, 1 024, 2 048 workgroups wanted: headline workload 7.44, 7.36, 7.62, 8.61 ms; 61 layers 1.80,
+// 1.57, 1.67, 1.57 ms; batch of 32 jobs 95.6, 95.8, 97.3, 100.8 ms.
 __host__ __device__ inline int seg_target(int L, int S) {
-    return L - S < kSegTopLayers ? kSegTargetTop : L - S < kSegMidLayers ? kSegTargetMid : kSegTarget;
+    const long long passes = (long long)level_krange(L, S) * (S - 1);
+    return passes >= (long long)kSegTarget * kSegWorkgroups ? kSegTarget : passes >= (long long)kSegTarget / 2 * kSegWorkgroups ? kSegTarget / 2 : kSegMin;
 }
 __host__ __device__ inline int tile_krange(int L, int S, int ub, int vb) {
     return tile_vmax(L, vb) - ub * 8 - S + 1;
@@ -158,10 +165,9 @@ __host__ __device__ inline void seg_span(int krange, int n, int j, int *ofs, int
     *len = imin((base + (j < extra ? 1 : 0)) * kSegUnit, krange - *ofs);
 }
 __host__ __device__ inline int seg_count(int L, int S) { // over all blocks of the level
-    const int NB = nblocks_of(L), ubmax = (L - S) / 8;
+    const int NB = nblocks_of(L), ubmax = (L - S) / 8, target = seg_target(L, S);
     int c = 0;
-    for (int d = NB - 1; d >= tile_dmin(L, S); --d)
-        for (int ub = 0; ub <= imin(ubmax, NB - 1 - d); ++ub) c += seg_n(tile_krange(L, S, ub, ub + d), seg_target(L, S));
+    for (int d = NB - 1; d >= tile_dmin(L, S); --d) c += (imin(ubmax, NB - 1 - d) + 1) * seg_n(tile_krange(L, S, 0, d), target);
     return c;
 }
 // Upper bounds that grow with L, for sizing a workspace that serves every L up to a maximum: the

@@ -471,6 +471,7 @@ struct KeyArgs {
                          // both families of a low level) to the whole-node family
     int NT, NAall;
     int s0, sstep;       // a launch covers the splits s0, s0 + sstep, ...
+    int target;          // split points of a segment
     int t_lo1, dlo;      // smallest target of the whole-node family; first device set of the level
     int pack, xcd;       // several items per wave near the range ends; XCD-chunked task order
 };
@@ -528,7 +529,7 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     int kofs, klen;
     {
         const int kr = tile_krange(L, Sp, ub, vb);
-        seg_span(kr, seg_n(kr, seg_target(L, Sp)), seg, &kofs, &klen);
+        seg_span(kr, seg_n(kr, ka.target), seg, &kofs, &klen);
     }
     const int kmin = ub * 8 + s + kofs, kmax = imin(vmax - r, kmin + klen - 1);
     if (!(mA0 <= mA1 && mB0 <= mB1 && kmin <= kmax)) return; // nothing to merge
@@ -726,24 +727,24 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
 // points k and stage the same left-child records.
 __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
     if (S > t.sh.Smax || threadIdx.x != 0) return;
-    const int L = t.sh.L, NB = nblocks_of(L), ubmax = (L - S) / 8, dmin = tile_dmin(L, S);
+    const int L = t.sh.L, NB = nblocks_of(L), ubmax = (L - S) / 8, dmin = tile_dmin(L, S), target = seg_target(L, S);
     int2 *out = t.seg_tab + (long long)(S - 2) * t.seg_stride;
     int n = 0;
     if (!by_row) {
         int tt = 0;
         for (int d = NB - 1; d >= dmin; --d)
             for (int u = 0; u <= imin(ubmax, NB - 1 - d); ++u, ++tt) {
-                const int c = seg_n(tile_krange(L, S, u, u + d), seg_target(L, S));
+                const int c = seg_n(tile_krange(L, S, u, u + d), target);
                 for (int j = 0; j < c; ++j) out[n++] = make_int2(tt, u | ((u + d) << 8) | (j << 16));
             }
         return;
     }
     for (int u = 0; u <= imin(ubmax, NB - 1 - dmin); ++u) {
-        const int cmax = seg_n(tile_krange(L, S, u, NB - 1), seg_target(L, S)); // the row's longest split range
+        const int cmax = seg_n(tile_krange(L, S, u, NB - 1), target); // the row's longest split range
         for (int j = 0; j < cmax; ++j) {
             int tt = u; // index of block (u, u + d) in tile order: the blocks of all larger d come first
             for (int d = NB - 1; d >= dmin; --d) {
-                if (u + d <= NB - 1 && j < seg_n(tile_krange(L, S, u, u + d), seg_target(L, S)))
+                if (u + d <= NB - 1 && j < seg_n(tile_krange(L, S, u, u + d), target))
                     out[n++] = make_int2(tt, u | ((u + d) << 8) | (j << 16));
                 tt += imin(ubmax, NB - 1 - d) + 1;
             }
@@ -1196,27 +1197,24 @@ Carve carve(int L, int nodes, int M) {
     return c;
 }
 
-// Structural work counts: states = (u, v) with v - u >= S' per table; candidates = (s, k, m)
+// Structural work counts of a level: states = (u, v) with v - u >= S' per table; candidates = (s, k, m)
 // with both children valid: per (s, m) pair one per (u, k, v), u + s <= k <= v - r.
-void work_counts(const Shape &sh, long long *states, long long *cands) {
-    long long st = 0, ca = 0;
-    for (int S = 1; S <= sh.Smax; ++S) {
-        const long long n = sh.L - S + 1;
-        const int dlo = dlo_of(S, sh.M), dhi = dhi_of(S, sh.M, sh.n_max);
-        for (int delta = dlo; delta <= dhi; ++delta) {
-            st += n * (n + 1) / 2;
-            if (S == 1) continue;
-            const Family fam = family_of(delta, sh.M);
-            long long pairs = 0;
-            for (int s = 1; s < S; ++s) {
+void level_counts(const Shape &sh, int S, long long *states, long long *cands) {
+    const long long n = sh.L - S + 1;
+    const int dlo = dlo_of(S, sh.M), dhi = dhi_of(S, sh.M, sh.n_max);
+    long long pairs = 0;
+    for (int s = 1; s < S; ++s) // (m, m') pairs of all targets
+        for (int fam = S <= sh.M ? 0 : 1; fam < 2; ++fam) {
+            int t_lo, t_hi;
+            target_units(fam, S, sh.M, sh.n_max, &t_lo, &t_hi);
+            for (int a = t_lo; a <= t_hi; ++a) {
                 int lo, hi;
-                m_range(fam.fam, fam.units, s, S - s, sh.M, sh.n_max, &lo, &hi);
+                m_range(fam, a, s, S - s, sh.M, sh.n_max, &lo, &hi);
                 if (hi >= lo) pairs += hi - lo + 1;
             }
-            ca += pairs * (n * (n + 1) * (n + 2) / 6);
         }
-    }
-    *states = st; *cands = ca;
+    *states = dhi >= dlo ? (dhi - dlo + 1) * (n * (n + 1) / 2) : 0;
+    *cands = pairs * (n * (n + 1) * (n + 2) / 6);
 }
 
 constexpr size_t kLdsLimit = 160 * 1024; // gfx950: 160 KB of LDS per workgroup
@@ -1265,6 +1263,7 @@ static const int kBatchLanes = env_or("OOB_TUNE_BATCH_LANES", 8);
 // the plain select only wait longer for a place); measured on the headline workload, where 78-88 gave
 // the same time.  Handle options move both thresholds.
 constexpr int kSelect8From = 82, kFuseFrom = 82;
+constexpr int kOverlapFrom = 24000; // thousand candidates of a level: see enqueue_job
 constexpr int kSelLanes = 1; // lanes per state below that
 bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
@@ -1356,7 +1355,7 @@ struct oob_plan {
     bool have_last;
     hipEvent_t ev_begin, ev_end; // optional: recorded around the level launches
     bool timed;
-    int opt_plain, opt_xcd, opt_one_stream, opt_select8_from, opt_fuse_from; // oob_plan_set_option
+    int opt_plain, opt_xcd, opt_one_stream, opt_select8_from, opt_fuse_from, opt_overlap_from; // oob_plan_set_option
 };
 
 #define OOB_HIP_CHECK(expr)                                                                   \
@@ -1399,7 +1398,7 @@ extern "C" int oob_plan_create(oob_plan **h, int max_L, int max_nodes, int max_g
     p->lanes = (int)std::min<size_t>(kMaxLanes, std::max<size_t>(1, workspace_bytes / p->lane_bytes));
     p->ev_fork = nullptr; p->last_lane = 0;
     p->opt_plain = p->opt_xcd = p->opt_one_stream = 0;
-    p->opt_select8_from = kSelect8From; p->opt_fuse_from = kFuseFrom;
+    p->opt_select8_from = kSelect8From; p->opt_fuse_from = kFuseFrom; p->opt_overlap_from = kOverlapFrom;
     *h = p;
     return OOB_OK;
 }
@@ -1496,7 +1495,7 @@ static void launch_split_key_r(const Tables &t, const KeyArgs &ka, const KeyLaun
 static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int NAall, int xcd, SplitRange sr, hipStream_t st) {
     KeyArgs ka;
     ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.NAall = NAall; ka.s0 = sr.s0; ka.sstep = sr.sstep;
-    ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
+    ka.target = seg_target(t.sh.L, S); ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
     const int rows = kl.na + 2 * kKeyPad;
     if (rows <= 24) launch_split_key_r<24>(t, ka, kl, sr, st);
     else if (rows <= 36) launch_split_key_r<36>(t, ka, kl, sr, st);
@@ -1567,7 +1566,15 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
                 if (plan_split(sh, S, fam, &sp) && sp.lds > kLdsLimit) return OOB_ECAPACITY;
             }
     const Tables t = make_tables(h, ln, sh, (int *)out->status);
-    work_counts(sh, (long long *)&out->states, (long long *)&out->candidates);
+    // states and candidates; the levels worth an overlap (below)
+    int ov_lo = sh.Smax + 1, ov_hi = 0;
+    out->states = out->candidates = 0;
+    for (int S = 1; S <= sh.Smax; ++S) {
+        long long states, cands;
+        level_counts(sh, S, &states, &cands);
+        out->states += states; out->candidates += cands;
+        if (S >= 4 && cands >= h->opt_overlap_from * 1000ll) { ov_lo = imin(ov_lo, S); ov_hi = S; }
+    }
 
     const long long slot_stride = h->cv.slots * 64; // distance between the two buffers of per-split minima
     long long keys = 0; // of the level that has most of them
@@ -1582,9 +1589,14 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     // outer splits of the next level ..., two small launches per level, and it runs on the caller's
     // stream.  The inner splits, nearly all of the arithmetic, run on two streams of the library (even
     // and odd levels), each launch waiting for the select of level S'-2 and awaited by the select of its
-    // own level; they fill the machine around the chain.  Each parity has its own buffer of per-split
-    // minima (a select hands its buffer back reset before the inner splits of level S'+2 start).
-    bool overlap = want_overlap && !force_plain && sh.Smax >= 4;
+    // own level; they fill the machine around the chain.  Each parity has its own buffer of
+    // keys (a select hands its buffer back reset before the inner splits of level S'+2 start).
+    // That pays from the first to the last level of at least opt_overlap_from thousand candidates.  The other levels
+    // put all their splits into one launch on the caller's stream: a level takes 10-25 us there, and the two event
+    // records, the two waits and the third launch of an overlapped one occupy the host for longer (one stream
+    // throughout, against three: 26 layers 312 and 732 us, 61 layers 1.62 and 1.78 ms, headline workload 10.5 and
+    // 7.5 ms; the line at 0, 20, 40, 80 million candidates: headline workload 7.47, 7.60, 7.69, 7.89 ms).
+    bool overlap = want_overlap && !force_plain && ov_lo <= ov_hi;
     if (overlap && !lane.aux) lane.aux = borrow_stream();
     if (overlap && !lane.aux2) lane.aux2 = borrow_stream();
     if (overlap && lane.aux && lane.aux2) {
@@ -1609,7 +1621,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         for (int fam = 0; fam < 2; ++fam) {
             have[fam] = plan_split(sh, S, fam, &sp[fam]) && plan_split_key(sh, S, fam, &kp[fam]);
         }
-        const bool inner = overlap && S >= 4;
+        const bool inner = overlap && S >= ov_lo && S <= ov_hi;
         if (inner) {
             hipStream_t sx = (S & 1) ? lane.aux2 : lane.aux;
             OOB_HIP_CHECK(hipStreamWaitEvent(sx, lane.ev_level[2 * (S - 2)], 0)); // select of level S'-2
@@ -1634,7 +1646,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         else if (fuse) hipLaunchKernelGGL((k_select_key<8, true>), dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
         else if (S >= h->opt_select8_from) hipLaunchKernelGGL((k_select_key<8, false>), dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
         else hipLaunchKernelGGL((k_select_key<kSelLanes, false>), dim3(NT, NAall, kSelLanes), dim3(64), 0, st, tl, S, NT, NAall);
-        if (overlap) OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S], st));
+        if (overlap && S + 2 >= ov_lo && S + 2 <= ov_hi) OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S], st));
     }
     if (timed) { OOB_HIP_CHECK(hipEventRecord(h->ev_end, st)); h->timed = true; }
     hipLaunchKernelGGL(k_pick, dim3(sh.count), dim3(64), 0, st, t, *out);
@@ -1701,6 +1713,7 @@ extern "C" int oob_plan_set_option(oob_plan *h, int option, int value) {
     case OOB_OPT_ONE_STREAM: h->opt_one_stream = value != 0; break;
     case OOB_OPT_SELECT8_FROM: h->opt_select8_from = value; break;
     case OOB_OPT_FUSE_FROM: h->opt_fuse_from = value; break;
+    case OOB_OPT_OVERLAP_FROM: h->opt_overlap_from = value; break;
     default: return OOB_EINVAL;
     }
     return OOB_OK;

@@ -346,6 +346,35 @@ def test_select_with_eight_lanes_per_state(P):
     assert seen == {(0, 0), (1, 0)}, "keys and the evaluation without keys must both have run"
 
 
+@pytest.mark.parametrize("overlap_from", [0, 20, 200])
+def test_levels_on_several_streams(P, overlap_from):
+    """The inner splits of the levels of at least `overlap_from` thousand candidates on streams of the library: all
+    levels, or a stretch of them with levels before and behind it on the caller's stream; called directly and replayed
+    from a captured graph."""
+    import torch
+
+    for inp in (inputs.config(2), inputs.random_small(5, 60, 2, 1, 6, 11, f=2), inputs.random_small(4, 30, 3, 2, 30, 0, f=2)):
+        say(f"overlap from {overlap_from} {inp.name} {inp.L}")
+        planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+        planner.set_option(P.OOB_OPT_OVERLAP_FROM, overlap_from)
+        full_check(P, planner, inp)
+        prof, out = P.DeviceProfile(inp), planner.new_outputs(inp)
+        planner.enqueue(prof, out)
+        want = out.to_host()
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            planner.enqueue(prof, out)
+        for i in range(3):
+            out.base.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            got = out.to_host()
+            assert all(np.array_equal(got[k], want[k]) for k in out.t), (inp.name, i)
+        planner.close()
+
+
 def test_two_calls_same_answer(P):
     """Determinism: the same job twice on one handle gives identical tables."""
     inp = inputs.config(2)
