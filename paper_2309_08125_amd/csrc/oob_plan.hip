@@ -60,9 +60,6 @@ struct Tables {
     int tab_recs;         // records per table = tri_blocks(NB) * 64
     long long *lvl_tab;   // [Smax+2] index of the first table of level S'
     int2 *lvl_dir;        // [Smax+2] x: table of device set delta minus delta, y: ceil(S' / M)
-    long long *PT;        // [(M+1)*(L+1)] prefix sums of F+B for d GPUs (row d)
-    int *PF;              // [(M+1)*(L+1)] prefix counts of forbidden entries
-    long long *PM;        // [L+1] prefix sums of bytes
     Rec *rec;             // [tables * tab_recs]
     int *kstar, *choice;  // [tables * tab_recs]
     double *partT;        // [(S'-1) * deltas * tiles * 64] per-split minima of the current level
@@ -113,8 +110,55 @@ __device__ __forceinline__ int scan_int(int x, int lane) {
     return x;
 }
 
+// One wave scans the profile row of d GPUs: prefix sums of F + B and prefix counts of forbidden entries (Eq. 4's sums
+// become differences).  Returns the row's sum; *bad collects what is wrong with the entries (1 negative, 2 too large).
+__device__ __forceinline__ unsigned long long scan_times(const oob_profile &prof, int L, int M, int d, int lane, long long *PT, int *PF, int *bad) {
+    const unsigned long long capT = (unsigned long long)kExactBound;
+    unsigned long long carry = 0;
+    int fcarry = 0;
+    if (PT && lane == 0) { PT[0] = 0; PF[0] = 0; }
+    for (int l0 = 0; l0 < L; l0 += 64) {
+        const int l = l0 + lane;
+        const bool in = l < L;
+        const long long F = in ? prof.fwd_ns[(size_t)l * M + d - 1] : 0, B = in ? prof.bwd_ns[(size_t)l * M + d - 1] : 0;
+        const bool neg = F < 0 || B < 0;
+        const bool fb = F >= OOB_FORBIDDEN || B >= OOB_FORBIDDEN;
+        const bool big = !neg && !fb && (F >= kExactBound || B >= kExactBound);
+        if (neg) *bad = imax(*bad, 1);
+        if (big) *bad = imax(*bad, 2);
+        unsigned long long x = (neg || fb || big) ? 0ull : (unsigned long long)(F + B);
+        if (x > capT) x = capT;
+        x = scan_sat(x, capT, lane) + carry;
+        if (x > capT) x = capT;
+        const int c = scan_int(fb ? 1 : 0, lane) + fcarry;
+        if (PT && in) { PT[l + 1] = (long long)x; PF[l + 1] = c; }
+        carry = __shfl(x, 63, 64);
+        fcarry = __shfl(c, 63, 64);
+    }
+    return carry;
+}
+// The same for the bytes.
+__device__ __forceinline__ unsigned long long scan_bytes(const oob_profile &prof, int L, int lane, long long *PM, int *bad) {
+    const unsigned long long capM = (unsigned long long)OOB_FORBIDDEN;
+    unsigned long long carry = 0;
+    if (PM && lane == 0) PM[0] = 0;
+    for (int l0 = 0; l0 < L; l0 += 64) {
+        const int l = l0 + lane;
+        const bool in = l < L;
+        const long long mb = in ? prof.mem_bytes[l] : 0;
+        const bool badm = mb < 0 || mb >= OOB_FORBIDDEN;
+        if (badm) *bad = imax(*bad, 1);
+        unsigned long long m = badm ? 0ull : (unsigned long long)mb;
+        m = scan_sat(m, capM, lane) + carry;
+        if (m > capM) m = capM;
+        if (PM && in) PM[l + 1] = (long long)m;
+        carry = __shfl(m, 63, 64);
+    }
+    return carry;
+}
+
 __device__ void setup_body(const Tables &t, const oob_profile &prof, int force_plain) {
-    const int L = t.sh.L, M = t.sh.M, W = L + 1;
+    const int L = t.sh.L, M = t.sh.M;
     __shared__ long long s_worst[OOB_MAX_GPUS + 1];
     __shared__ int s_bad;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -123,51 +167,23 @@ __device__ void setup_body(const Tables &t, const oob_profile &prof, int force_p
     const unsigned long long capT = (unsigned long long)kExactBound, capM = (unsigned long long)OOB_FORBIDDEN;
     int bad = 0;
     for (int d = 1 + wave; d <= M && wave < nw - 2; d += nw - 2) { // row of d GPUs
-        unsigned long long carry = 0;
-        int fcarry = 0;
-        if (lane == 0) { t.PT[d * W] = 0; t.PF[d * W] = 0; }
-        for (int l0 = 0; l0 < L; l0 += 64) {
-            const int l = l0 + lane;
-            const bool in = l < L;
-            const long long F = in ? prof.fwd_ns[(size_t)l * M + d - 1] : 0, B = in ? prof.bwd_ns[(size_t)l * M + d - 1] : 0;
-            const bool neg = F < 0 || B < 0;
-            const bool fb = F >= OOB_FORBIDDEN || B >= OOB_FORBIDDEN;
-            const bool big = !neg && !fb && (F >= kExactBound || B >= kExactBound);
-            if (neg) bad = imax(bad, 1);
-            if (big) bad = imax(bad, 2);
-            unsigned long long x = (neg || fb || big) ? 0ull : (unsigned long long)(F + B);
-            if (x > capT) x = capT;
-            x = scan_sat(x, capT, lane) + carry;
-            if (x > capT) x = capT;
-            const int c = scan_int(fb ? 1 : 0, lane) + fcarry;
-            if (in) { t.PT[d * W + l + 1] = (long long)x; t.PF[d * W + l + 1] = c; }
-            carry = __shfl(x, 63, 64);
-            fcarry = __shfl(c, 63, 64);
-        }
-        if (carry >= capT) bad = imax(bad, 2);
-        if (lane == 0) s_worst[d] = (long long)carry;
+        const unsigned long long sum = scan_times(prof, L, M, d, lane, nullptr, nullptr, &bad);
+        if (sum >= capT) bad = imax(bad, 2);
+        if (lane == 0) s_worst[d] = (long long)sum;
     }
     if (wave == nw - 2) { // bytes and boundary terms
-        unsigned long long cm = 0, cx = 0;
-        if (lane == 0) t.PM[0] = 0;
+        if (scan_bytes(prof, L, lane, nullptr, &bad) >= capM) bad = imax(bad, 1);
+        unsigned long long cx = 0;
         for (int l0 = 0; l0 < L; l0 += 64) {
             const int l = l0 + lane;
-            const bool in = l < L;
-            const long long mb = in ? prof.mem_bytes[l] : 0, xb = in ? prof.boundary_ns[l] : 0;
-            const bool badm = mb < 0 || mb >= OOB_FORBIDDEN;
-            if (badm || xb < 0) bad = imax(bad, 1);
+            const long long xb = l < L ? prof.boundary_ns[l] : 0;
+            if (xb < 0) bad = imax(bad, 1);
             if (xb >= kExactBound) bad = imax(bad, 2);
-            unsigned long long m = badm ? 0ull : (unsigned long long)mb;
-            m = scan_sat(m, capM, lane) + cm;
-            if (m > capM) m = capM;
             unsigned long long x = (xb < 0 || xb >= kExactBound) ? 0ull : (unsigned long long)xb;
             x = scan_sat(x, capT, lane) + cx;
             if (x > capT) x = capT;
-            if (in) t.PM[l + 1] = (long long)m;
-            cm = __shfl(m, 63, 64);
             cx = __shfl(x, 63, 64);
         }
-        if (cm >= capM) bad = imax(bad, 1);
         if (cx >= capT) bad = imax(bad, 2);
         if (lane == 0) s_worst[0] = (long long)cx;
     }
@@ -207,37 +223,36 @@ __device__ void setup_body(const Tables &t, const oob_profile &prof, int force_p
     }
 }
 
-// Stage time and feasibility of layers [u, v) on d GPUs of one node (Eq. 4; memory rule:
-// ceil(bytes / d) <= cap; boundary term for a stage that is not the model's last).
-__device__ __forceinline__ bool stage_time(const Tables &t, const long long *X, int u, int v, int d,
-                                           long long *out) {
-    const int W = t.sh.L + 1;
-    if (t.PF[d * W + v] - t.PF[d * W + u] != 0) return false;
-    const long long bytes = t.PM[v] - t.PM[u];
-    if ((bytes + d - 1) / d > t.sh.cap) return false;
-    *out = t.PT[d * W + v] - t.PT[d * W + u] + (v < t.sh.L ? X[v - 1] : 0);
-    return true;
-}
-
 // ---------------------------------------------------------------------------------------
-// Level 1 ("Conquer", Eq. 4): grid (block of the plane, delta), one lane per (u, v).
+// Level 1 ("Conquer", Eq. 4): stage time of layers [u, v) on d GPUs of one node (memory rule: ceil(bytes / d) <= cap;
+// boundary term for a stage that is not the model's last).  Workgroup wg = (delta, four blocks of the plane), one wave
+// per block, one lane per (u, v); it scans the two profile rows it needs for itself, which takes less time than waiting
+// for another launch to have done it.
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) k_level1(Tables t, const long long *X) {
-    const int L = t.sh.L, M = t.sh.M;
+__device__ void level1_body(const Tables &t, const oob_profile &prof, int wg) {
+    const int L = t.sh.L, M = t.sh.M, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ long long s_PT[OOB_MAX_L + 1], s_PM[OOB_MAX_L + 1];
+    __shared__ int s_PF[OOB_MAX_L + 1];
+    const int tiles = tile_count(L, 1), quads = (tiles + 3) / 4, delta = wg / quads, tile = (wg - delta * quads) * 4 + wave;
+    const int d = delta < M - 1 ? delta + 1 : M;
+    int bad = 0;
+    if (wave == 0) scan_times(prof, L, M, d, lane, s_PT, s_PF, &bad);
+    if (wave == 1) scan_bytes(prof, L, lane, s_PM, &bad);
+    __syncthreads();
+    if (tile >= tiles) return;
     int ub, vb;
-    tile_decode(L, 1, blockIdx.x, &ub, &vb);
-    const int delta = blockIdx.y, u = ub * 8 + (threadIdx.x >> 3), v = vb * 8 + (threadIdx.x & 7) - t.coff;
+    tile_decode(L, 1, tile, &ub, &vb);
+    const int u = ub * 8 + (lane >> 3), v = vb * 8 + (lane & 7) - t.coff;
     Rec r = {kNone, kNone, 0.0, 0.0};
-    if (u < L && v <= L && v - u >= 1) { // (v < 0 in the first block column: no state)
-        const int d = delta < M - 1 ? delta + 1 : M;
-        long long st;
-        if (stage_time(t, X, u, v, d, &st)) {
+    if (u < L && v <= L && v - u >= 1 && s_PF[v] == s_PF[u]) { // (v < 0 in the first block column: no state)
+        const long long bytes = s_PM[v] - s_PM[u];
+        if ((bytes + d - 1) / d <= t.sh.cap) {
             const double nb = t.sh.Nb > 0 ? (double)t.sh.Nb : 4.0;
-            r.T1 = r.tmax = r.T3 = (double)st;
+            r.T1 = r.tmax = r.T3 = (double)(s_PT[v] - s_PT[u] + (v < L ? prof.boundary_ns[v - 1] : 0));
             r.T = r.T1 + (nb - 2.0) * r.tmax + r.T3; // Eq. 2 with S' = 1, k* = 0
         }
     }
-    const long long o = rec_block(t, 1, delta, ub, vb) + threadIdx.x;
+    const long long o = (long long)delta * t.tab_recs + tri_index(ub, vb, t.NB) * 64 + lane; // level 1 has the first tables
     t.rec[o] = r;
     t.kstar[o] = 0;
     t.choice[o] = 0;
@@ -752,13 +767,16 @@ __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
     }
 }
 
-// Everything a call needs before level 1, as one launch of kSetupThreads-wide workgroups:
-// workgroup 0 the set-up, workgroups 1 .. Smax-1 the task lists of the levels 2 .. Smax, the rest
-// set the n keys of either buffer to "no such state".  The three parts touch disjoint memory.
-__global__ void __launch_bounds__(kSetupThreads) k_prepare(Tables t, oob_profile prof, int force_plain, int by_row,
+// Everything up to level 1, as one launch of kSetupThreads-wide workgroups: workgroup 0 the set-up, `ones` workgroups
+// level 1, Smax-1 the task lists of the levels 2 .. Smax, the rest set the n keys of either buffer to "no such state".
+// The four parts touch disjoint memory.
+__global__ void __launch_bounds__(kSetupThreads) k_prepare(Tables t, oob_profile prof, int force_plain, int by_row, int ones,
                                                            long long stride, long long n) {
-    const int b = blockIdx.x, nseg = imax(t.sh.Smax - 1, 0);
+    const int nseg = imax(t.sh.Smax - 1, 0);
+    int b = blockIdx.x;
     if (b == 0) { setup_body(t, prof, force_plain); return; }
+    if (b <= ones) { level1_body(t, prof, b - 1); return; }
+    b -= ones;
     if (b <= nseg) { seg_tab_body(t, b + 1, by_row); return; }
     const long long i = (long long)(b - 1 - nseg) * blockDim.x + threadIdx.x;
     if (i < 2 * n) t.key[i < n ? i : stride + i - n] = kNoKey;
@@ -1040,12 +1058,54 @@ __global__ void __launch_bounds__(64) k_pick(Tables t, oob_templates out) {
     out.T[i] = T; out.T1[i] = T1; out.T2[i] = T2; out.T3[i] = T3; out.tmax[i] = tm; out.kstar[i] = ks;
 }
 
+// ---------------------------------------------------------------------------------------
+// Node specification and coverage (Section 4.1.1, Appendix A), one workgroup.  The template sizes
+// are the consecutive integers n0..n_hi, so c pipelines can use exactly the node counts
+// c n0 .. c n_hi; the largest pipeline count whose sizes sum to x is therefore
+// c = floor(x / n0) when x <= c n_hi, and x is no sum of sizes at all otherwise (fewer
+// pipelines reach even less).  That is the value the coin-change recursion of Section 4.2.1
+// gives, without the table.
+// ---------------------------------------------------------------------------------------
+__device__ void coverage_body(const Tables &t, const oob_templates &out, int len) {
+    __shared__ int s_i0, s_i1, s_thm, s_tail;
+    const int cnt = t.sh.count, f = t.sh.f, lane = threadIdx.x;
+    if (lane == 0) {
+        int i0 = -1;
+        for (int q = 0; q < cnt; ++q) if (out.feasible[q]) { i0 = q; break; }
+        int i1 = i0;
+        while (i0 >= 0 && i1 + 1 < cnt && out.feasible[i1 + 1]) ++i1;
+        s_i0 = i0; s_i1 = i1; s_thm = 1; s_tail = 1;
+    }
+    for (int q = lane; q < len; q += blockDim.x) out.cover_maxpipes[q] = 0;
+    __syncthreads();
+    if (s_i0 < 0) {
+        if (lane < 8) out.cover_hdr[lane] = 0;
+        return;
+    }
+    const int n0 = t.sh.n_min + s_i0, n_hi = t.sh.n_min + s_i1, p = n_hi - n0 + 1;
+    const int N = n_hi + f * n0;
+    const int lo_thm = (f + 1) * n0, lo_tail = N - f < 1 ? 1 : N - f;
+    const int lo = lo_thm < lo_tail ? lo_thm : lo_tail;
+    for (int x = lo + lane; x <= N; x += blockDim.x) {
+        int c = x / n0;
+        if ((long long)c * n_hi < x) c = 0;
+        if (x - lo < len) out.cover_maxpipes[x - lo] = c;
+        if (x >= lo_thm && c < f + 1) atomicMin(&s_thm, 0);
+        if (x >= lo_tail && c < 1) atomicMin(&s_tail, 0);
+    }
+    __syncthreads();
+    if (lane == 0) {
+        out.cover_hdr[0] = n0; out.cover_hdr[1] = n_hi; out.cover_hdr[2] = p; out.cover_hdr[3] = N;
+        out.cover_hdr[4] = p > n0 - 1; out.cover_hdr[5] = lo; out.cover_hdr[6] = s_thm; out.cover_hdr[7] = s_tail;
+    }
+}
+
 // Stages of each template from the stored (s, k, m) tree: one workgroup per template, one thread
 // per stage.  Thread p walks from the root to the p-th leaf (left subtree if p is below the left
 // child's stage count, else right with p reduced by it), so the walks of a template run side by
 // side and the kernel takes as long as the deepest leaf, not as the whole tree.
-// Workgroup `count` only writes the end of the offsets.
-__global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out) {
+// Workgroup `count` writes the end of the offsets and the coverage.
+__global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out, int len) {
     __shared__ long long s_lvl[OOB_MAX_L + 3];
     __shared__ int s_part[128];
     const int i = blockIdx.x, tid = threadIdx.x, cnt = t.sh.count;
@@ -1057,7 +1117,7 @@ __global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out) 
     int off = 0;
     for (int q = 0; q < (int)blockDim.x; ++q) off += s_part[q];
     if (tid == 0) out.stage_off[i] = off;
-    if (i >= cnt) return;
+    if (i >= cnt) { coverage_body(t, out, len); return; }
     const int S = out.S[i];
     if (S == 0) return;
     const int L = t.sh.L, M = t.sh.M;
@@ -1078,48 +1138,6 @@ __global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out) 
         gpus[p] = delta < M - 1 ? delta + 1 : M;
     }
     if (tid == 0) begin[S] = L;
-}
-
-// ---------------------------------------------------------------------------------------
-// Node specification and coverage (Section 4.1.1, Appendix A), one wave.  The template sizes
-// are the consecutive integers n0..n_hi, so c pipelines can use exactly the node counts
-// c n0 .. c n_hi; the largest pipeline count whose sizes sum to x is therefore
-// c = floor(x / n0) when x <= c n_hi, and x is no sum of sizes at all otherwise (fewer
-// pipelines reach even less).  That is the value the coin-change recursion of Section 4.2.1
-// gives, without the table.
-// ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) k_coverage(Tables t, oob_templates out, int len) {
-    __shared__ int s_i0, s_i1, s_thm, s_tail;
-    const int cnt = t.sh.count, f = t.sh.f, lane = threadIdx.x;
-    if (lane == 0) {
-        int i0 = -1;
-        for (int q = 0; q < cnt; ++q) if (out.feasible[q]) { i0 = q; break; }
-        int i1 = i0;
-        while (i0 >= 0 && i1 + 1 < cnt && out.feasible[i1 + 1]) ++i1;
-        s_i0 = i0; s_i1 = i1; s_thm = 1; s_tail = 1;
-    }
-    for (int q = lane; q < len; q += 64) out.cover_maxpipes[q] = 0;
-    __syncthreads();
-    if (s_i0 < 0) {
-        if (lane < 8) out.cover_hdr[lane] = 0;
-        return;
-    }
-    const int n0 = t.sh.n_min + s_i0, n_hi = t.sh.n_min + s_i1, p = n_hi - n0 + 1;
-    const int N = n_hi + f * n0;
-    const int lo_thm = (f + 1) * n0, lo_tail = N - f < 1 ? 1 : N - f;
-    const int lo = lo_thm < lo_tail ? lo_thm : lo_tail;
-    for (int x = lo + lane; x <= N; x += 64) {
-        int c = x / n0;
-        if ((long long)c * n_hi < x) c = 0;
-        if (x - lo < len) out.cover_maxpipes[x - lo] = c;
-        if (x >= lo_thm && c < f + 1) atomicMin(&s_thm, 0);
-        if (x >= lo_tail && c < 1) atomicMin(&s_tail, 0);
-    }
-    __syncthreads();
-    if (lane == 0) {
-        out.cover_hdr[0] = n0; out.cover_hdr[1] = n_hi; out.cover_hdr[2] = p; out.cover_hdr[3] = N;
-        out.cover_hdr[4] = p > n0 - 1; out.cover_hdr[5] = lo; out.cover_hdr[6] = s_thm; out.cover_hdr[7] = s_tail;
-    }
 }
 
 // Copies one table into dense n x n arrays, n = L-S'+1, entry [u][v - S'] (tests only).
@@ -1167,7 +1185,7 @@ long long part_slots(int L, int M, int n_max, int Nb) {
 }
 
 struct Carve {
-    size_t lvl_tab, lvl_dir, PT, PF, PM, rec, kstar, choice, partT, partK, stack, flags, seg_tab, total;
+    size_t lvl_tab, lvl_dir, rec, kstar, choice, partT, partK, stack, flags, seg_tab, total;
     long long recs, slots;
 };
 // Byte offsets of the workspace arrays, sized for the handle's maxima.
@@ -1180,9 +1198,6 @@ Carve carve(int L, int nodes, int M) {
     size_t o = 0;
     c.lvl_tab = o; o = align_up(o + sizeof(long long) * (OOB_MAX_L + 3));
     c.lvl_dir = o; o = align_up(o + sizeof(int2) * (OOB_MAX_L + 3));
-    c.PT = o;      o = align_up(o + sizeof(long long) * (size_t)(M + 1) * (L + 1));
-    c.PF = o;      o = align_up(o + sizeof(int) * (size_t)(M + 1) * (L + 1));
-    c.PM = o;      o = align_up(o + sizeof(long long) * (size_t)(L + 1));
     c.rec = o;     o = align_up(o + sizeof(Rec) * E);
     c.kstar = o;   o = align_up(o + sizeof(int) * E);
     c.choice = o;  o = align_up(o + sizeof(int) * E);
@@ -1431,9 +1446,6 @@ static Tables make_tables(const oob_plan *h, int lane, const Shape &sh, int *sta
     t.tab_recs = tri_blocks(t.NB) * 64;
     t.lvl_tab = (long long *)(ws + h->cv.lvl_tab);
     t.lvl_dir = (int2 *)(ws + h->cv.lvl_dir);
-    t.PT = (long long *)(ws + h->cv.PT);
-    t.PF = (int *)(ws + h->cv.PF);
-    t.PM = (long long *)(ws + h->cv.PM);
     t.rec = (Rec *)(ws + h->cv.rec);
     t.kstar = (int *)(ws + h->cv.kstar);
     t.choice = (int *)(ws + h->cv.choice);
@@ -1579,10 +1591,9 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     const long long slot_stride = h->cv.slots * 64; // distance between the two buffers of per-split minima
     long long keys = 0; // of the level that has most of them
     for (int S = 2; S <= sh.Smax; ++S) keys = std::max(keys, (long long)(dhi_of(S, M, n_max) - dlo_of(S, M) + 1) * tile_count(L, S) * 64);
-    hipLaunchKernelGGL(k_prepare, dim3((unsigned)(1 + imax(sh.Smax - 1, 0) + (2 * keys + kSetupThreads - 1) / kSetupThreads)),
-                       dim3(kSetupThreads), 0, st, t, *profile, force_plain, h->opt_xcd, slot_stride, keys);
-    hipLaunchKernelGGL(k_level1, dim3(tile_count(L, 1), M), dim3(64), 0, st, t,
-                       (const long long *)profile->boundary_ns);
+    const int ones = M * ((tile_count(L, 1) + 3) / 4);
+    hipLaunchKernelGGL(k_prepare, dim3((unsigned)(1 + ones + imax(sh.Smax - 1, 0) + (2 * keys + kSetupThreads - 1) / kSetupThreads)),
+                       dim3(kSetupThreads), 0, st, t, *profile, force_plain, h->opt_xcd, ones, slot_stride, keys);
     // Levels.  Level S' depends on the lower levels like this: its inner splits 2 <= s <= S'-2 read the
     // levels up to S'-2 only, its two outer splits (s = 1 and S'-1) read level S'-1, and its select
     // needs all its splits.  So the chain that cannot be shortened is outer splits -> select ->
@@ -1650,9 +1661,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     }
     if (timed) { OOB_HIP_CHECK(hipEventRecord(h->ev_end, st)); h->timed = true; }
     hipLaunchKernelGGL(k_pick, dim3(sh.count), dim3(64), 0, st, t, *out);
-    hipLaunchKernelGGL(k_backtrack, dim3(sh.count + 1), dim3(128), 0, st, t, *out);
-    const int len = sh.count > f + 1 ? sh.count : f + 1;
-    hipLaunchKernelGGL(k_coverage, dim3(1), dim3(64), 0, st, t, *out, len);
+    hipLaunchKernelGGL(k_backtrack, dim3(sh.count + 1), dim3(128), 0, st, t, *out, sh.count > f + 1 ? sh.count : f + 1);
     OOB_HIP_CHECK(hipGetLastError());
     h->last = sh;
     h->last_lane = ln;
