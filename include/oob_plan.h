@@ -170,6 +170,10 @@ int oob_plan_destroy(oob_plan *h);
  *                        one with at least that many run their inner splits on the two streams of
  *                        the library, the others run everything on the caller's stream; default
  *                        24000 (a smaller level is done before the events of an overlap are enqueued)
+ *   OOB_OPT_SMALL_STATE  value = candidates of a state: a level whose widest state has no more is done by one
+ *                        launch, candidate by candidate (up to half a million candidates of the level); default 640,
+ *                        0: none.  The options XCD_ORDER, SELECT8_FROM, FUSE_FROM and OVERLAP_FROM set it to 0
+ *                        (they are about the kernels of larger levels)
  * Returns OOB_EINVAL for an unknown option. */
 #define OOB_OPT_PLAIN_SPLIT 1
 #define OOB_OPT_XCD_ORDER 2
@@ -177,6 +181,7 @@ int oob_plan_destroy(oob_plan *h);
 #define OOB_OPT_SELECT8_FROM 4
 #define OOB_OPT_FUSE_FROM 5
 #define OOB_OPT_OVERLAP_FROM 6
+#define OOB_OPT_SMALL_STATE 7
 int oob_plan_set_option(oob_plan *h, int option, int value);
 
 /* Test hook, host only (no GPU is touched): checks the table layout and the per-level task lists the

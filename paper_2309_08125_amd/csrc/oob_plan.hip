@@ -23,11 +23,12 @@
 //            target device sets): the minimum over (k, m) of Eq. 1-3 per state as a
 //            key of (total, s, k), merged into the level's key array (described at the kernel).
 //            k_split is the variant without keys for shapes beyond its LDS.
+//   k_level_small   both of these for a level of few candidates.
 //   k_select_key / k_select  per state: from the smallest key (from the per-split minima) the first m at that
 //            (s, k) whose candidate equals it -- the smallest (T, s, k, m) -- and the record.
-// Before level 1 one launch (k_prepare) scans and validates the profile, lays out the tables, lists the
-// tasks of every level and clears the keys; after the last level k_pick chooses the stage count of
-// every template size, k_backtrack expands the stages, k_coverage does Section 4.1.1's node specification.
+// Before that one launch (k_prepare) scans and validates the profile, lays out the tables, lists the
+// tasks of every level, clears the keys and does level 1; after the last level k_pick chooses the stage count of
+// every template size, k_backtrack expands the stages and does Section 4.1.1's node specification.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -1021,6 +1022,131 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
 }
 
 // ---------------------------------------------------------------------------------------
+// Levels S' >= 2, small levels: grid (block of the plane, delta, row of the block); one launch does the level.
+//
+// A level of few candidates is bound by its launches and by the round trips to memory inside them, so splits and select are
+// one kernel without keys: a workgroup evaluates the eight states (u, v) of a row of a block, candidate by candidate
+// from the child records, 32 lanes a state.  The lanes of a wave are eight columns times eight consecutive split
+// points: the left records of a load are eight neighbours, the right ones eight rows of eight neighbours.
+// The (s, m) pairs of the device set are listed in LDS first; candidate i is pair i / nk, split point i % nk of the
+// widest state of the row (a narrower one reads "no such state" beyond its own).  Smallest (T, s, k, m) by comparison,
+// so the kernel does not depend on keys fitting a double.
+// ---------------------------------------------------------------------------------------
+constexpr int kSmallPairs = 1024;  // (s, m) pairs of a device set the kernel has room for
+constexpr int kSmallThreads = 256; // 32 lanes a state
+constexpr int kSmallFlight = 4;    // candidates a lane has in flight
+__global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp) {
+    __shared__ int4 s_pair[kSmallPairs]; // left table, right table (byte offsets of their first records), s, m
+    __shared__ int s_sum[kSmallThreads / 64];
+    __shared__ double s_best[kSmallThreads / 64][8];
+    __shared__ unsigned s_tag[kSmallThreads / 64][8];
+    const int L = t.sh.L, M = t.sh.M, n_max = t.sh.n_max, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int ub, vb;
+    tile_decode(L, Sp, blockIdx.x, &ub, &vb);
+    const int2 dT = t.lvl_dir[Sp];
+    const int delta = dlo_of(Sp, M) + blockIdx.y;
+    const Family fam = family_of(delta, M);
+    const int u = ub * 8 + blockIdx.z, v = vb * 8 + (tid & 7) - t.coff, nk = tile_vmax(L, vb) - u - Sp + 1;
+    const unsigned tab_bytes = (unsigned)t.tab_recs * (unsigned)sizeof(Rec);
+    const bool fixed_nb = t.sh.Nb > 0;
+    int np = 0;
+    if (nk > 0) {
+        for (int s0 = 1; s0 < Sp; s0 += kSmallThreads) {
+            const int s = s0 + tid, r = Sp - s;
+            int mlo = 1, mhi = 0;
+            int2 dA = {0, 0}, dB = {0, 0};
+            if (r > 0) { // unit counts of the children (child_units with the level's ceil(S / M))
+                dA = t.lvl_dir[s]; dB = t.lvl_dir[r];
+                const int alo = fam.fam ? dA.y : s, ahi = fam.fam ? imin(s, n_max) : M - 1;
+                const int blo = fam.fam ? dB.y : r, bhi = fam.fam ? imin(r, n_max) : M - 1;
+                mlo = imax(alo, fam.units - bhi);
+                mhi = imin(ahi, fam.units - blo);
+            }
+            const int cnt = imax(0, mhi - mlo + 1), incl = scan_int(cnt, lane);
+            __syncthreads(); // (s_sum of the round before is read)
+            if (lane == 63) s_sum[wave] = incl;
+            __syncthreads();
+            int at = np + incl - cnt;
+            for (int w = 0; w < kSmallThreads / 64; ++w) {
+                if (w < wave) at += s_sum[w];
+                np += s_sum[w];
+            }
+            for (int m = mlo; m <= mhi; ++m, ++at)
+                if (at < kSmallPairs) // (the host has checked that they fit)
+                    s_pair[at] = make_int4((dA.x + fam.fam_base + m) * tab_bytes, (dB.x + fam.fam_base + fam.units - m) * tab_bytes, s, m);
+        }
+        np = imin(np, kSmallPairs);
+    }
+    __syncthreads();
+    double best = kNone;
+    unsigned btag = 0xffffffffu; // s << 21 | k << 10 | m
+    const int total = np * nk, g = tid >> 3;
+    if (nk > 0 && np > 0) {
+        constexpr int G = kSmallThreads / 8;
+        const int dp = G / nk, dk = G - dp * nk, c = t.coff, vcol = (v + c) & 7;
+        const int rowA = ub * t.NB - ub * (ub - 1) / 2 - ub; // block (ub, b) is number rowA + b
+        const char *const rec = (const char *)t.rec;
+        int p = g / nk, kk = g - p * nk;
+        for (int i = g; i < total; i += G * kSmallFlight) {
+            Rec24 ra[kSmallFlight], rb[kSmallFlight];
+            unsigned tag[kSmallFlight];
+            double cl[kSmallFlight], cr[kSmallFlight];
+#pragma unroll
+            for (int q = 0; q < kSmallFlight; ++q) {
+                const int4 e = s_pair[imin(p, np - 1)]; // past the end: some candidate of the last pair again
+                const int s = e.z, r = Sp - s, k = u + s + kk, kb = k >> 3;
+                const unsigned oa = ((rowA + ((k + c) >> 3)) * 64 + ((u & 7) << 3) + ((k + c) & 7)) * (unsigned)sizeof(Rec);
+                const unsigned ob = ((kb * t.NB - kb * (kb - 1) / 2 + vb - kb) * 64 + ((k & 7) << 3) + vcol) * (unsigned)sizeof(Rec);
+                ra[q] = load24(rec, (unsigned)e.x + oa);
+                rb[q] = load24(rec, (unsigned)e.y + ob);
+                tag[q] = ((unsigned)s << 21) | ((unsigned)k << 10) | (unsigned)e.w;
+                cl[q] = fixed_nb ? -(double)r : 3.0 * r;
+                cr[q] = fixed_nb ? 0.0 : 4.0 * s;
+                p += dp; kk += dk;
+                if (kk >= nk) { kk -= nk; ++p; }
+            }
+#pragma unroll
+            for (int q = 0; q < kSmallFlight; ++q) {
+                const double T = cand_total(ra[q], rb[q], cl[q], cr[q]);
+                if (T < best || (T == best && tag[q] < btag)) { best = T; btag = tag[q]; }
+            }
+        }
+    }
+#pragma unroll
+    for (int d = 8; d < 64; d <<= 1) {
+        const double ob = __shfl_xor(best, d, 64);
+        const unsigned ot = (unsigned)__shfl_xor((int)btag, d, 64);
+        if (ob < best || (ob == best && ot < btag)) { best = ob; btag = ot; }
+    }
+    if (lane < 8) { s_best[wave][lane] = best; s_tag[wave][lane] = btag; }
+    __syncthreads();
+    if (tid >= 8) return;
+    for (int w = 1; w < kSmallThreads / 64; ++w) {
+        const double ob = s_best[w][tid];
+        const unsigned ot = s_tag[w][tid];
+        if (ob < best || (ob == best && ot < btag)) { best = ob; btag = ot; }
+    }
+    Rec out = {kNone, kNone, 0.0, 0.0};
+    int ks = 0, ch = 0;
+    if (best < kNone) {
+        const int s = (int)(btag >> 21), k = (int)((btag >> 10) & 2047u), m = (int)(btag & 1023u), r = Sp - s;
+        const long long oa = (long long)(t.lvl_dir[s].x + fam.fam_base + m) * t.tab_recs + rec_off(u, k, t.coff, t.NB);
+        const long long ob = (long long)(t.lvl_dir[r].x + fam.fam_base + fam.units - m) * t.tab_recs + rec_off(k, v, t.coff, t.NB);
+        const Rec a = t.rec[oa], b = t.rec[ob];
+        const int ka = t.kstar[oa], kb = t.kstar[ob];
+        out.T = best;
+        out.T1 = a.T1 + b.T1;                                                     // Eq. 1
+        if (a.tmax >= b.tmax) { out.tmax = a.tmax; ks = ka; out.T3 = a.T3 + b.T1; } // Eq. 3
+        else                  { out.tmax = b.tmax; ks = s + kb; out.T3 = b.T3; }
+        ch = s | (k << 10) | (m << 21);
+    }
+    const long long o = (long long)(dT.x + delta) * t.tab_recs + tri_index(ub, vb, t.NB) * 64 + (blockIdx.z << 3) + tid;
+    t.rec[o] = out;
+    t.kstar[o] = ks;
+    t.choice[o] = ch;
+}
+
+// ---------------------------------------------------------------------------------------
 // Template extraction ("Choosing the number of stages"): one wave per template size
 // n = n_min + blockIdx.x, the lanes share out the stage counts; smallest T, then smallest S.
 // ---------------------------------------------------------------------------------------
@@ -1214,20 +1340,26 @@ Carve carve(int L, int nodes, int M) {
 
 // Structural work counts of a level: states = (u, v) with v - u >= S' per table; candidates = (s, k, m)
 // with both children valid: per (s, m) pair one per (u, k, v), u + s <= k <= v - r.
-void level_counts(const Shape &sh, int S, long long *states, long long *cands) {
+// *most: (s, m) pairs of the target that has most of them.
+void level_counts(const Shape &sh, int S, long long *states, long long *cands, int *most) {
     const long long n = sh.L - S + 1;
     const int dlo = dlo_of(S, sh.M), dhi = dhi_of(S, sh.M, sh.n_max);
     long long pairs = 0;
-    for (int s = 1; s < S; ++s) // (m, m') pairs of all targets
-        for (int fam = S <= sh.M ? 0 : 1; fam < 2; ++fam) {
-            int t_lo, t_hi;
-            target_units(fam, S, sh.M, sh.n_max, &t_lo, &t_hi);
-            for (int a = t_lo; a <= t_hi; ++a) {
+    *most = 0;
+    for (int fam = S <= sh.M ? 0 : 1; fam < 2; ++fam) {
+        int t_lo, t_hi;
+        target_units(fam, S, sh.M, sh.n_max, &t_lo, &t_hi);
+        for (int a = t_lo; a <= t_hi; ++a) {
+            int here = 0;
+            for (int s = 1; s < S; ++s) {
                 int lo, hi;
                 m_range(fam, a, s, S - s, sh.M, sh.n_max, &lo, &hi);
-                if (hi >= lo) pairs += hi - lo + 1;
+                if (hi >= lo) here += hi - lo + 1;
             }
+            pairs += here;
+            *most = imax(*most, here);
         }
+    }
     *states = dhi >= dlo ? (dhi - dlo + 1) * (n * (n + 1) / 2) : 0;
     *cands = pairs * (n * (n + 1) * (n + 2) / 6);
 }
@@ -1278,6 +1410,12 @@ static const int kBatchLanes = env_or("OOB_TUNE_BATCH_LANES", 8);
 // the plain select only wait longer for a place); measured on the headline workload, where 78-88 gave
 // the same time.  Handle options move both thresholds.
 constexpr int kSelect8From = 82, kFuseFrom = 82;
+// Levels that k_level_small does: as many candidates of the widest state as 32 lanes look at in five round trips, and
+// so few in all that their scattered reads are not what the launch takes (it reads 0.15 million candidates a
+// microsecond).  Measured against split and select launches: 26 layers 308 -> 232 us with the line at 640
+// (320: 274 us, 1 000: 232 us), smallest job 39 -> 27 us on the GPU; 61 layers 1 294 us either way (1 000: 1 315 us);
+// 128 lanes a state: 268 us for the 26 layers.
+constexpr int kSmallState = 640, kSmallLevel = 500000;
 constexpr int kOverlapFrom = 24000; // thousand candidates of a level: see enqueue_job
 constexpr int kSelLanes = 1; // lanes per state below that
 bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
@@ -1370,7 +1508,7 @@ struct oob_plan {
     bool have_last;
     hipEvent_t ev_begin, ev_end; // optional: recorded around the level launches
     bool timed;
-    int opt_plain, opt_xcd, opt_one_stream, opt_select8_from, opt_fuse_from, opt_overlap_from; // oob_plan_set_option
+    int opt_plain, opt_xcd, opt_one_stream, opt_select8_from, opt_fuse_from, opt_overlap_from, opt_small_state; // oob_plan_set_option
 };
 
 #define OOB_HIP_CHECK(expr)                                                                   \
@@ -1413,7 +1551,7 @@ extern "C" int oob_plan_create(oob_plan **h, int max_L, int max_nodes, int max_g
     p->lanes = (int)std::min<size_t>(kMaxLanes, std::max<size_t>(1, workspace_bytes / p->lane_bytes));
     p->ev_fork = nullptr; p->last_lane = 0;
     p->opt_plain = p->opt_xcd = p->opt_one_stream = 0;
-    p->opt_select8_from = kSelect8From; p->opt_fuse_from = kFuseFrom; p->opt_overlap_from = kOverlapFrom;
+    p->opt_select8_from = kSelect8From; p->opt_fuse_from = kFuseFrom; p->opt_overlap_from = kOverlapFrom; p->opt_small_state = kSmallState;
     *h = p;
     return OOB_OK;
 }
@@ -1580,13 +1718,18 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     const Tables t = make_tables(h, ln, sh, (int *)out->status);
     // states and candidates; the levels worth an overlap (below)
     int ov_lo = sh.Smax + 1, ov_hi = 0;
+    bool small[OOB_MAX_L + 1]; // levels done by one launch
     out->states = out->candidates = 0;
     for (int S = 1; S <= sh.Smax; ++S) {
         long long states, cands;
-        level_counts(sh, S, &states, &cands);
+        int most;
+        level_counts(sh, S, &states, &cands, &most);
         out->states += states; out->candidates += cands;
         if (S >= 4 && cands >= h->opt_overlap_from * 1000ll) { ov_lo = imin(ov_lo, S); ov_hi = S; }
+        small[S] = S >= 2 && most <= kSmallPairs && (long long)most * (L - S + 1) <= h->opt_small_state && cands <= kSmallLevel;
     }
+    if (table_count(L, M, n_max, microbatches) * tri_blocks(nblocks_of(L)) * 64 * (long long)sizeof(Rec) >= 1ll << 32 || force_plain)
+        std::fill(small, small + sh.Smax + 1, false); // its offsets are 32 bits
 
     const long long slot_stride = h->cv.slots * 64; // distance between the two buffers of per-split minima
     long long keys = 0; // of the level that has most of them
@@ -1624,6 +1767,11 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         const int NAall = dhi_of(S, M, n_max) - dlo_of(S, M) + 1;
         if (NAall <= 0) continue;
         const int NT = tile_count(L, S);
+        if (small[S]) {
+            hipLaunchKernelGGL(k_level_small, dim3(NT, NAall, 8), dim3(kSmallThreads), 0, st, t, S);
+            if (overlap && S + 2 >= ov_lo && S + 2 <= ov_hi) OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S], st));
+            continue;
+        }
         Tables tl = t; // this level's buffer of per-split minima
         tl.partT = t.partT + (S & 1) * slot_stride;
         tl.key = t.key + (S & 1) * slot_stride;
@@ -1718,11 +1866,13 @@ extern "C" int oob_plan_set_option(oob_plan *h, int option, int value) {
     if (!h) return OOB_EINVAL;
     switch (option) {
     case OOB_OPT_PLAIN_SPLIT: h->opt_plain = value != 0; break;
-    case OOB_OPT_XCD_ORDER: h->opt_xcd = value != 0; break;
+    // options of kernels that small levels do not run: they ask for those kernels
+    case OOB_OPT_XCD_ORDER: h->opt_xcd = value != 0; h->opt_small_state = 0; break;
     case OOB_OPT_ONE_STREAM: h->opt_one_stream = value != 0; break;
-    case OOB_OPT_SELECT8_FROM: h->opt_select8_from = value; break;
-    case OOB_OPT_FUSE_FROM: h->opt_fuse_from = value; break;
-    case OOB_OPT_OVERLAP_FROM: h->opt_overlap_from = value; break;
+    case OOB_OPT_SELECT8_FROM: h->opt_select8_from = value; h->opt_small_state = 0; break;
+    case OOB_OPT_FUSE_FROM: h->opt_fuse_from = value; h->opt_small_state = 0; break;
+    case OOB_OPT_OVERLAP_FROM: h->opt_overlap_from = value; h->opt_small_state = 0; break;
+    case OOB_OPT_SMALL_STATE: h->opt_small_state = value; break;
     default: return OOB_EINVAL;
     }
     return OOB_OK;

@@ -375,6 +375,22 @@ def test_levels_on_several_streams(P, overlap_from):
         planner.close()
 
 
+@pytest.mark.parametrize("small_state", [0, 100, 1 << 30])
+def test_levels_by_one_launch(P, small_state):
+    """Levels of at most `small_state` candidates a state candidate by candidate: none, some, all of them; one to
+    sixteen GPUs per node, both N_b modes, tight memory, totals too large for keys, more than 64 pairs of a device
+    set, blocks whose first column lacks layers."""
+    for inp in (inputs.config(1), inputs.config(2), inputs.random_small(3, 37, 3, 1, 5, 9, f=1, tight_mem=True),
+                inputs.random_small(5, 60, 2, 1, 6, 11, f=2), inputs.random_small(4, 30, 3, 2, 30, 0, f=2),
+                inputs.random_small(7, 12, 8, 1, 3, 5), inputs.random_small(8, 40, 16, 1, 3, 0), inputs.random_small(9, 7, 1, 1, 7, 0),
+                inputs.random_small(21, 9, 2, 1, 3, 7, t_lo=(1 << 38), t_hi=(1 << 39))):
+        say(f"small state {small_state} {inp.name} {inp.L}")
+        planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+        planner.set_option(P.OOB_OPT_SMALL_STATE, small_state)
+        full_check(P, planner, inp)
+        planner.close()
+
+
 def test_two_calls_same_answer(P):
     """Determinism: the same job twice on one handle gives identical tables."""
     inp = inputs.config(2)
