@@ -412,17 +412,22 @@ __global__ void __launch_bounds__(512) k_split(Tables t, int Sp, int fam, int NT
 // steps make an item.  When the four waves of a workgroup shared a split point they staged it together between two
 // barriers and did about five steps each between them: as many scalar as vector instructions, half of the vector
 // ones outside the steps, 40 % of a wave's time in waits.  A split point per wave has no barrier between set-up and
-// merge, no item cut in pieces and a quarter of the scalar work, and pays with LDS (a staged streaming side per wave:
-// two or three waves per SIMD instead of four), which costs the steps less than the barriers did.  The stationary side
-// needs LDS for one block only and is loaded while the block before is worked on.  Measured: batch of 32 jobs of 24..128
-// layers 124 -> 99 ms; staged by the workgroup four split points at a time with eight waves 149 ms; both
-// children staged per wave 113 ms; three waves per workgroup 101 ms; held to 128 registers for a fourth wave per
-// SIMD 104-121 ms.
+// merge, no item cut in pieces and a quarter of the scalar work, and pays with LDS for a streaming side per wave; the
+// stationary side needs LDS for one block only and is loaded while the block before is worked on.  Measured: batch of 32
+// jobs of 24..128 layers 124 -> 99 ms; staged by the workgroup four split points at a time with eight waves 149 ms; both
+// children staged per wave 113 ms; three waves per workgroup 101 ms.
+// Then what decides is how many waves share a compute unit.  The key table has a row per target and none beside them
+// (minima of targets outside the group are dropped instead of collected in seven padding rows on either side), the
+// staged side is as long as it is, and the kernel holds 128 registers without spills for four waves per SIMD: lane offsets
+// of the staging are formed where they are used, and one eight of streaming tables is in flight instead of three.
+// Batch 96 -> 79 ms, headline workload 7.36 -> 6.86 ms, 61 layers 1.30 -> 1.19 ms.  (Padding rows in classes of six
+// rows and three waves per SIMD: 87 and 7.06 ms; five spilled registers: 83 and 7.17 ms, and 4 us a launch; the
+// groups of four candidates whose select is the same in all lanes done by an add and a min, 57-77 % of them: 103 and
+// 8.4 ms, the branches to them cost more than they save.)
 // ---------------------------------------------------------------------------------------
 constexpr int kKeyTargets = 64;
-constexpr int kKeyPad = 7;    // rows of the key table on either side of the targets
-constexpr int kFillBatch = 2; // eights of streaming tables a wave has in flight while it works on the split point before
-constexpr int kWavesPerSimd = 3;
+constexpr int kFillBatch = 1; // eights of streaming tables a wave has in flight while it works on the split point before
+constexpr int kWavesPerSimd = 4;
 
 // Workgroup x of a launch of n -> position in the task list (handle option OOB_OPT_XCD_ORDER only).  The hardware
 // deals consecutive workgroups out to the 8 XCDs in turn; this hands every XCD one contiguous
@@ -488,6 +493,7 @@ struct KeyArgs {
     int NT, NAall;
     int s0, sstep;       // a launch covers the splits s0, s0 + sstep, ...
     int target;          // split points of a segment
+    int na;              // rows of the key table: targets of the largest group
     int t_lo1, dlo;      // smallest target of the whole-node family; first device set of the level
     int pack, xcd;       // several items per wave near the range ends; XCD-chunked task order
 };
@@ -499,6 +505,11 @@ constexpr unsigned long long kNoKey = 0x7FF0000000000000ull;
 __device__ __forceinline__ unsigned long long wide_key(double part, int s, int kb) {
     const unsigned long long v = (unsigned long long)__double_as_longlong(part + 0x1p52) & ((1ull << 52) - 1);
     return (((v >> kb) << kb | (unsigned)s) << kb) | (v & ((1ull << kb) - 1));
+}
+
+// A value that is the same in all lanes, in scalar registers.
+__device__ __forceinline__ double uniform(double x) {
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)), __builtin_amdgcn_readfirstlane(__double2loint(x)));
 }
 
 // Order of a wave's LDS operations against those of its other lanes (they execute in order: only the compiler has to
@@ -517,13 +528,10 @@ __device__ __forceinline__ Rec24 load24(const void *base, unsigned off) {
     return rc;
 }
 
-template <int ROWS>
 __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyArgs ka) {
-    // Separate arrays (the key table static, the staged records the launch's dynamic LDS): the compiler then knows
-    // that the key merges (atomics on s_acc) never touch the staged records, and keeps the reads of the next step
-    // ahead of them.
-    __shared__ unsigned long long s_acc[ROWS * 64]; // keys: targets are rows kKeyPad .. kKeyPad + na - 1
-    HIP_DYNAMIC_SHARED(double2, s_rec)              // per wave [TS] pre-combined pairs, [TS] tmax (negated when the right child streams)
+    // the launch's LDS: [na of the launch * 64] keys, row = target; then per wave [TS] pre-combined pairs, [TS] tmax
+    // (negated when the right child streams)
+    HIP_DYNAMIC_SHARED(unsigned long long, s_acc)
     const int Sp = ka.Sp, s = ka.s0 + blockIdx.y * ka.sstep, r = Sp - s;
     const int2 sg = t.seg_tab[(long long)(Sp - 2) * t.seg_stride + (ka.xcd ? xcd_chunked(blockIdx.x, gridDim.x) : (int)blockIdx.x)]; // x: tile index, y: ub | vb << 8 | seg << 16
     const int2 dA = t.lvl_dir[s], dB = t.lvl_dir[r];
@@ -553,23 +561,27 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     const int yM0 = y_left ? mA0 : mB0, yM1 = y_left ? mA1 : mB1; // streaming unit counts
     const int qM0 = y_left ? mB0 : mA0, qM1 = y_left ? mB1 : mA1; // stationary unit counts
     const int nY = yM1 - yM0 + 1, nS = qM1 - qM0 + 1, nyb = (nY + 7) >> 3, nmb = (nS + 7) >> 3;
-    const int fillY = nyb * 64, TS = fillY + 64; // records staged: the streaming side of a split point, one block of the stationary side
+    const int fillY = nY * 8, TS = fillY + 64; // records staged: the streaming side of a split point, one block of the stationary side
     const unsigned long long kNoneBits = 0x7FF0000000000000ull;
-    const double KS = (double)(1 << key_bits(L));
+    const double KS = uniform((double)(1 << key_bits(L)));
 
     // Staging.  The left child (s, u, k, m) is row u of block (ub, k/8), column k; the right child (r, k, v, m') is row
     // k of block (k/8, vb), column v.  What depends on the lane does not depend on k: eight tables ahead is a constant
     // distance, and only the last eight tables of a side may not all exist (streaming: the last one again, stationary:
     // "no such state").
-    const double cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r, cr = t.sh.Nb > 0 ? 0.0 : 4.0 * s;
+    const double cl = uniform(t.sh.Nb > 0 ? -(double)r : 3.0 * r), cr = uniform(t.sh.Nb > 0 ? 0.0 : 4.0 * s);
     const long long tabA = (long long)(dA.x + fam_base + mA0) * t.tab_recs, tabB = (long long)(dB.x + fam_base + mB0) * t.tab_recs;
     const Rec *const recY = t.rec + (y_left ? tabA : tabB), *const recS = t.rec + (y_left ? tabB : tabA);
     const int lt = lane >> 3, li = lane & 7, shY = y_left ? 3 : 0, shS = y_left ? 0 : 3;
-    auto off8 = [=](int sh, int top) { return (__umul24(imin(lt, top), t.tab_recs) + (li << sh)) * 32u; }; // lane's record of eight tables 0..top
+    auto off8 = [=](int sh, int top) { // lane's record of eight tables 0..top
+        int ln = lane;
+        asm volatile("" : "+v"(ln)); // formed where it is used: kept across the split points these offsets cost registers the kernel does not have
+        return (__umul24(imin(ln >> 3, top), t.tab_recs) + ((ln & 7) << sh)) * 32u;
+    };
     const int lastY = nY - 1 - 8 * (nyb - 1); // last table of the last eight of the streaming side that exists
     const int last = nS - 1 - 8 * (nmb - 1); // last table of the last stationary block that exists
     const size_t step8 = (size_t)t.tab_recs * 8 * sizeof(Rec);
-    double2 *const pair = s_rec + wave * TS + (wave * TS >> 1);
+    double2 *const pair = (double2 *)(s_acc + ka.na * 64) + wave * (TS + TS / 2);
     double *const tmv = (double *)(pair + TS);
     struct Src { const char *y, *s; };
     auto source = [=](int k) { // records of split point k of the two sides' first tables
@@ -584,6 +596,9 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
         return Rec24{left ? make_double2(rc.a.x + cl * rc.tm, rc.a.y) : make_double2(2.0 * rc.a.y, rc.a.x + cr * rc.tm), y_left ? rc.tm : -rc.tm};
     };
     auto store = [=](int at, const Rec24 &rc) { pair[at] = rc.a; tmv[at] = rc.tm; };
+    auto storeY = [=](int i, const Rec24 &rc) { // eight tables of the streaming side, those that exist
+        if (i < nyb - 1 || lt <= lastY) store(i * 64 + lane, combine(rc, y_left));
+    };
 
     Rec24 preY[kFillBatch], preS; // in flight: streaming side of the next split point, next stationary block
     int k = kmin + wave;
@@ -596,14 +611,14 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
             if (i < nyb) preY[i] = loadY(src, i);
         preS = loadS(src, 0);
     }
-    for (int e = threadIdx.x; e < (na + 2 * kKeyPad) * 64; e += blockDim.x) s_acc[e] = kNoneBits;
+    for (int e = threadIdx.x; e < na * 64; e += blockDim.x) s_acc[e] = kNoneBits;
     __syncthreads();
     for (; k <= kmax; k += nw) {
         const Src src = source(k);
 #pragma unroll
         for (int i = 0; i < kFillBatch; ++i)
-            if (i < nyb) store(i * 64 + lane, combine(preY[i], y_left));
-        for (int i = kFillBatch; i < nyb; ++i) store(i * 64 + lane, combine(loadY(src, i), y_left));
+            if (i < nyb) storeY(i, preY[i]);
+        for (int i = kFillBatch; i < nyb; ++i) storeY(i, loadY(src, i));
         const Src next = source(imin(k + nw, kmax));
         if (k + nw <= kmax) { // records of this wave's next split point: in flight during this one
 #pragma unroll
@@ -636,6 +651,8 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
             const int mlo = imax(yM0, a_g0 - (qM0 + 8 * mb_last + 7)), mhi = imin(yM1, a_g1 - (qM0 + 8 * mb_first));
             if (mlo > mhi) return;
             double bb2[8], bbt[8], btm[8], acc[8];
+            const double2 *const pairS = pair + fillY + ql;
+            const double *const tmS = tmv + fillY + ql;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 if (PACK) { // each lane reads its own block's records
@@ -645,18 +662,16 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
                     rc = combine(rc, !y_left);
                     bb2[i] = rc.a.x; bbt[i] = rc.a.y; btm[i] = rc.tm;
                 } else {
-                    const int o = fillY + i * 8 + ql;
-                    const double2 p = pair[o];
-                    bb2[i] = p.x; bbt[i] = p.y; btm[i] = tmv[o];
+                    const double2 p = pairS[i * 8];
+                    bb2[i] = p.x; bbt[i] = p.y; btm[i] = tmS[i * 8];
                 }
                 acc[i] = kNone;
             }
             const int j0 = (mlo - mhi - 1) & 7;
             int mbase = mlo - j0; // step j of a group handles streaming unit count mbase + j; the first group may start at j0
-            // row of the key table of target y + q0.  Its distance from the target group is at most seven in the plain
-            // variant (the padding rows take those); side by side a lane's surplus steps may lie further out and
-            // are turned to the first padding row on either side.
-            int row = mbase + qM0 + 8 * mb - a_g0 + kKeyPad;
+            // row of the key table of target y + q0.  Minima of targets outside the group are dropped: in the plain
+            // variant those of the first steps (rows below 0) and of the drain, side by side by lane.
+            int row = mbase + qM0 + 8 * mb - a_g0;
             unsigned long long *kcol = s_acc + (PACK ? col : row * 64 + col);
             // one step: the streaming record y against the eight stationary ones, candidates for the
             // targets y + q0 + i, into the rotating minima; then the minimum of target y + q0 is
@@ -668,8 +683,8 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
             double2 p = *pa;
             double atm = *ta;
             auto merge = [&](int j, const double T) {
-                unsigned long long *dst = PACK ? kcol + imin(imax(row + j, kKeyPad - 1), kKeyPad + na) * 64 : kcol + j * 64;
-                atomicMin(dst, (unsigned long long)__double_as_longlong(fma(T, KS, kd)));
+                if (PACK ? (unsigned)(row + j) < (unsigned)na : row + j >= 0)
+                    atomicMin(PACK ? kcol + (row + j) * 64 : kcol + j * 64, (unsigned long long)__double_as_longlong(fma(T, KS, kd)));
             };
 #define OOB_STEP(j)                                                                                   \
     {                                                                                                 \
@@ -698,7 +713,10 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
 #undef OOB_STEP
             // the last step was j = 7 with unit count mhi: minima 0..6 belong to targets mhi + q0 + 1 + i
 #pragma unroll
-            for (int i = 0; i < 7; ++i) merge(i, acc[i]);
+            for (int i = 0; i < 7; ++i) {
+                if (!PACK && row + i >= na) break;
+                merge(i, acc[i]);
+            }
         };
         if (lgR > 0) {
             int slot, ue, ve; // this lane's block among the item's, its row and column
@@ -729,7 +747,7 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     unsigned long long *const dst = t.key + ((long long)(fam_base + a_g0 - ka.dlo) * ka.NT + tile) * 64;
     const long long row = (long long)ka.NT * 64; // keys of one device set
     for (int e = threadIdx.x; e < na * 64; e += blockDim.x) {
-        const unsigned long long part = s_acc[kKeyPad * 64 + e];
+        const unsigned long long part = s_acc[e];
         if (part == kNoneBits) continue;
         const unsigned long long key = wide_key(__longlong_as_double((long long)part), s, kb);
         atomicMin(dst + (e >> 6) * row + (e & 63), key);
@@ -1436,7 +1454,7 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
             const int mB0 = imax(B_lo, a0 - A_hi), mB1 = imin(B_hi, a1 - A_lo);
             if (mA0 <= mA1 && mB0 <= mB1) {
                 const int nA = mA1 - mA0 + 1, nB = mB1 - mB0 + 1;
-                ntab = imax(ntab, 8 * cdiv(left_streams(nA, nB) ? nA : nB, 8) + 8); // streaming side, one block of the stationary side
+                ntab = imax(ntab, (left_streams(nA, nB) ? nA : nB) + 8); // streaming side, one block of the stationary side
             }
         }
     }
@@ -1630,28 +1648,20 @@ static int most_blocks(const Shape &sh, int S, int fam, const SplitPlan &sp, Spl
 // staged per split point, na targets per group, `blocks` work items per split point.
 struct KeyLaunch { int fam, gz, groups, ntab, na, blocks; };
 constexpr int kKeyTables = 144; // most tables per split point the keyed kernel serves
-static size_t key_table_bytes(int na) { return (size_t)(na + 2 * kKeyPad) * 64 * sizeof(unsigned long long); }
-template <int ROWS>
-static void launch_split_key_r(const Tables &t, const KeyArgs &ka, const KeyLaunch &kl, SplitRange sr, hipStream_t st) {
-    // waves per workgroup: as many as put the most waves on a compute unit (they share the key table), four at most
-    const size_t keys = (size_t)ROWS * 512, per = (size_t)kl.ntab * 192;
+static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int NAall, int xcd, SplitRange sr, hipStream_t st) {
+    // waves per workgroup: as many as put the most waves on a compute unit (they share the key table), four at most; of
+    // equal numbers the larger, which has fewer split points to do one after the other (61 layers 1.31 -> 1.19 ms)
+    const size_t keys = (size_t)kl.na * 512, per = (size_t)kl.ntab * 192;
     int waves = 1, most = 0;
     for (int w = 1; w <= kKeyWaves; ++w) {
         const int on = imin((int)(kLdsLimit / (keys + w * per)) * w, 4 * kWavesPerSimd);
-        if (on > most) { most = on; waves = w; }
+        if (on >= most) { most = on; waves = w; }
     }
-    hipLaunchKernelGGL(k_split_key<ROWS>, dim3(seg_count(t.sh.L, ka.Sp), sr.scount, kl.groups), dim3(waves * 64), waves * per, st, t, ka);
-}
-static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int NAall, int xcd, SplitRange sr, hipStream_t st) {
     KeyArgs ka;
+    ka.na = kl.na;
     ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.NAall = NAall; ka.s0 = sr.s0; ka.sstep = sr.sstep;
     ka.target = seg_target(t.sh.L, S); ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
-    const int rows = kl.na + 2 * kKeyPad;
-    if (rows <= 24) launch_split_key_r<24>(t, ka, kl, sr, st);
-    else if (rows <= 36) launch_split_key_r<36>(t, ka, kl, sr, st);
-    else if (rows <= 48) launch_split_key_r<48>(t, ka, kl, sr, st);
-    else if (rows <= 60) launch_split_key_r<60>(t, ka, kl, sr, st);
-    else launch_split_key_r<kKeyTargets + 2 * kKeyPad>(t, ka, kl, sr, st);
+    hipLaunchKernelGGL(k_split_key, dim3(seg_count(t.sh.L, S), sr.scount, kl.groups), dim3(waves * 64), keys + waves * per, st, t, ka);
 }
 // The keyed launches of the splits `sr` of a level: one per family, or one for both.
 static void launch_split_keys(const Tables &t, int S, const bool *have, const SplitPlan *kp, int NT, int NAall, int xcd,
