@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
         *a.status = st;
         Head h;
         h.ncand = (unsigned)total;
-        h.bucket = (unsigned)imax(kBucket, (total + kMaxBuckets - 1) / kMaxBuckets);
+        h.bucket = (unsigned)imax(bucket_least(a.nk), (total + kMaxBuckets - 1) / kMaxBuckets);
         h.nbuckets = ((unsigned)total + h.bucket - 1) / h.bucket;
         h.alive = h.next = h.done = h.over = 0;
         h.narrow = narrow;
@@ -408,7 +408,7 @@ __device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int p, int 
 // GPUs and at most S_max stages are used, whatever the prices.  The bound is the largest over the
 // multipliers.  Row after row of the two paths; a wave takes two lambdas, thirty-two lanes each share out the
 // starts of the last stage, eight GPU counts side by side.  Bound by the chain of rows (LDS read, reduction over the
-// lanes, LDS write per row) at one workgroup per bucket, 63 % of the LDS cycles bank conflicts: 170 us at 98 layers x 8 GPUs, 274 buckets.
+// lanes, LDS write per row) at one workgroup per bucket, 63 % of the LDS cycles bank conflicts: 212 us at 98 layers x 8 GPUs, 512 buckets (170 us with 274).
 // ---------------------------------------------------------------------------------------------
 __device__ const double kLambdaGiven[kLambdas] = {0, 0.04, 0.1, 0.2, 0.4, 0.8, 1.6, 3.5}; // more nodes pay (C falls with n) ...
 __device__ const double kLambda4S[kLambdas] = {0, -0.06, -0.14, -0.25, -0.43, -0.7, -1.3, -3.5}; // ... or cost
@@ -610,30 +610,60 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
 __device__ __forceinline__ double best_now(const Args &a, int i) {
     return __longlong_as_double((long long)__hip_atomic_load(&a.best[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
-// A wave looks through 64 consecutive entries, lanes = templates, and appends what is left with one atomic.
-__global__ void __launch_bounds__(256) k_exact_filter(Args a) {
+// A wave looks through kFilterEntries consecutive entries, as many at once as have lanes for their templates, and appends
+// what is left with one atomic.  What the multipliers take off per template is formed once per workgroup.  Bound by the
+// loads of the bounds (64 numbers an entry with eight mus): 388 -> 8 us for 48 layers x 8 GPUs with the stage
+// limit binding, 52 -> 12 us at 98 layers x 8 GPUs, against one entry at a time and 64 entries a wave.
+constexpr int kFilterEntries = 16, kFilterThreads = 256;
+__global__ void __launch_bounds__(kFilterThreads) k_exact_filter(Args a) {
+    HIP_DYNAMIC_SHARED(double, s_spent) // [nk][live]
     if (*a.status != OOB_OK || !a.head->narrow) return;
-    const unsigned lane = threadIdx.x & 63, total = a.head->ncand, live = (unsigned)a.live;
-    const unsigned c0 = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
+    const int lane = threadIdx.x & 63, live = a.live;
+    const unsigned total = a.head->ncand, w0 = blockIdx.x * (kFilterThreads / 64) * kFilterEntries;
+    if (w0 >= total) return;
+    for (int i = threadIdx.x; i < a.nk * live; i += kFilterThreads) s_spent[i] = spent(a, i / live, a.n_min + i % live);
+    wg_sync();
+    const unsigned c0 = w0 + (threadIdx.x >> 6) * kFilterEntries;
     if (c0 >= total) return;
-    const double best = lane < live ? __longlong_as_double((long long)a.best[lane]) : -1.0;
-    unsigned long long keep = 0;
+    int lg = 2; // lanes per entry: the templates, rounded up to a power of two
+    while (1 << lg < live) ++lg;
+    const int E = 64 >> lg, ni = lane & ((1 << lg) - 1);
+    const double best = ni < live ? __longlong_as_double((long long)a.best[ni]) : -1.0;
+    const unsigned long long group = lg == 6 ? ~0ull : (1ull << (1 << lg)) - 1;
+    unsigned keep = 0;
     const unsigned K = a.head->bucket;
-    for (unsigned q = 0; q < 64 && c0 + q < total; ++q) {
-        const unsigned c = c0 + q, bk = c / K;
-        const double x = lane < live ? bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + (int)lane) : kNone;
-        if (__any(x < kNone && x <= best)) keep |= 1ull << q;
+    for (int q0 = 0; q0 < kFilterEntries; q0 += E) {
+        const int q = q0 + (lane >> lg);
+        const unsigned c = c0 + q;
+        bool in = q < kFilterEntries && c < total && ni < live;
+        if (in) {
+            const unsigned bk = c / K;
+            const double lo = a.blo[bk];
+            const float4 *lb = (const float4 *)(a.lb + (size_t)c * a.nk); // (nk is a multiple of eight)
+            double x = -kNone;
+            for (int k = 0; k < a.nk; k += 8) {
+                const float4 f = lb[k / 4], g = lb[k / 4 + 1];
+                const double *sp = s_spent + k * live + ni;
+                x = fmax(fmax(x, (double)f.x - lo * sp[0]), fmax((double)f.y - lo * sp[live], (double)f.z - lo * sp[2 * live]));
+                x = fmax(fmax(x, (double)f.w - lo * sp[3 * live]), fmax((double)g.x - lo * sp[4 * live], (double)g.y - lo * sp[5 * live]));
+                x = fmax(x, fmax((double)g.z - lo * sp[6 * live], (double)g.w - lo * sp[7 * live]));
+            }
+            in = a.n_min + ni >= a.bfew[bk] && x < kNone && x <= best;
+        }
+        const unsigned long long m = __ballot(in);
+        for (int e = 0; e < E && q0 + e < kFilterEntries; ++e)
+            if (m >> (e << lg) & group) keep |= 1u << (q0 + e);
     }
     unsigned at = 0;
-    if (lane == 0 && keep) at = atomicAdd(&a.head->alive, (unsigned)__popcll(keep));
+    if (lane == 0 && keep) at = atomicAdd(&a.head->alive, (unsigned)__popc(keep));
     at = __shfl(at, 0, 64);
-    if (keep >> lane & 1) a.list[at + __popcll(keep & ((1ull << lane) - 1))] = c0 + lane;
+    if (lane < kFilterEntries && keep >> lane & 1) a.list[at + __popc(keep & ((1u << lane) - 1))] = c0 + lane;
 }
 
 // ---------------------------------------------------------------------------------------------
 // Exact evaluation.  Bound by chains of dependent LDS reads on the rows of the one-node tables; at 8 GPUs per node 47 % of the LDS cycles
 // are bank conflicts (neighbouring lanes read rows 64 bytes apart) and 30 registers of k_exact_eval<false, 8> are spilled: 29 MB of scratch
-// written per launch.  155 us for the first picks and 430 us for the rest at 98 layers x 8 GPUs (the version before, without a band and
+// written per launch.  173 us for the first picks and 290-340 us for the rest at 98 layers x 8 GPUs (430 us with buckets of 64; the version before, without a band and
 // evaluating everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table
 // entry: 1, or S_max + 1 (STAGED).
 // ---------------------------------------------------------------------------------------------
@@ -1119,10 +1149,24 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
             if (mode == kRest) {
                 c = a.list[c];
                 // the minima may have fallen below this entry's bounds by now; n beyond the last template left is no use
-                if (tid < a.live) {
+                if constexpr (!STAGED) {
+                    if (tid < a.live) {
+                        const unsigned bk = c / a.head->bucket;
+                        const double x = bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + tid);
+                        if (x < kNone && x <= best_now(a, tid)) atomicMax(&s_nhi, a.n_min + tid);
+                    }
+                } else { // up to 64 multipliers: a lane per template and multiplier instead of a chain of reads per template
                     const unsigned bk = c / a.head->bucket;
-                    const double x = bound_of(a, a.lb + (size_t)c * a.nk, a.blo[bk], a.bfew[bk], a.n_min + tid);
-                    if (x < kNone && x <= best_now(a, tid)) atomicMax(&s_nhi, a.n_min + tid);
+                    const int lg = 32 - __clz(a.nk - 1), k = tid & ((1 << lg) - 1), per = (int)blockDim.x >> lg; // nk = 8 .. 64
+                    const double lo = a.blo[bk];
+                    const float lbk = k < a.nk ? a.lb[(size_t)c * a.nk + k] : 0.0f;
+                    const int fewest = a.bfew[bk];
+                    for (int n0 = 0; n0 < a.live; n0 += per) {
+                        const int ni = n0 + (tid >> lg), n = a.n_min + ni;
+                        double x = k < a.nk ? (double)lbk - lo * spent(a, k, n) : -kNone;
+                        for (int d = 1; d < 1 << lg; d <<= 1) x = fmax(x, __shfl_xor(x, d, 64));
+                        if (k == 0 && ni < a.live && n >= fewest && x < kNone && x <= best_now(a, ni)) atomicMax(&s_nhi, n);
+                    }
                 }
                 wg_sync();
                 nhi = s_nhi;
@@ -1352,7 +1396,7 @@ static int bounds_launch(const oob_exact::Args &a, int mus, size_t lds, hipStrea
     if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_bounds<MT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                (int)lds) != hipSuccess)
         return OOB_EHIP;
-    const unsigned nb = (unsigned)((tri(a.L) * a.M + kBucket - 1) / kBucket);
+    const unsigned nb = (unsigned)((tri(a.L) * a.M + bucket_least(a.nk) - 1) / bucket_least(a.nk));
     hipLaunchKernelGGL(k_exact_bounds<MT>, dim3(nb < (unsigned)kMaxBuckets ? nb : (unsigned)kMaxBuckets), dim3(kBoundThreads), lds, st, a, mus);
     return OOB_OK;
 }
@@ -1421,11 +1465,12 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
             default: rc = bounds_launch<0>(a, mus, bl, st); break;
             }
             if (rc != OOB_OK) return rc;
-            const int picks = imax(1, imin(10, (int)(fill / count)));
+            const int picks = imax(1, imin(16, (int)(fill / count))); // (10: 3.06 instead of 2.97 ms for 48 layers, 8 nodes, limit binding)
             rc = counts ? eval_launch<true>(a, kFirst, count * picks, threads, lds, picks, st)
                         : eval_launch<false>(a, kFirst, count * picks, threads, lds, picks, st);
             if (rc != OOB_OK) return rc;
-            hipLaunchKernelGGL(k_exact_filter, dim3((unsigned)((ntri + 255) / 256)), dim3(256), 0, st, a);
+            constexpr int per = kFilterThreads / 64 * kFilterEntries;
+            hipLaunchKernelGGL(k_exact_filter, dim3((unsigned)((ntri + per - 1) / per)), dim3(kFilterThreads), 8 * (size_t)a.nk * a.live, st, a);
             rc = counts ? eval_launch<true>(a, kRest, fill, threads, lds, 0, st) : eval_launch<false>(a, kRest, fill, threads, lds, 0, st);
         } else {
             const unsigned some = fill < 512 ? fill : 512, grid = ntri < some ? (unsigned)ntri : some; // few enough to learn from each other

@@ -85,9 +85,14 @@ inline EvalLds eval_lds(int L, int M, int n_max, int count, int J, bool staged) 
 // No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second
 // evaluation take 70 us or more whatever the job, what evaluating some thousand stages of a short model takes.
 constexpr int kDirectMax = 4096;
-constexpr int kMaxBuckets = 512, kBucket = 64; // entries per bucket: 64, more only where that would exceed kMaxBuckets
+constexpr int kMaxBuckets = 512;
+constexpr int kBucket = 64; // entries whose bounds a workgroup holds at a time
 constexpr int kMaxCount = 64;        // templates per job that the bounds are kept for
 constexpr int kLambdas = 8, kMus = 8;
+// Least entries per bucket (more only where that would exceed kMaxBuckets).  With the lambdas alone a smaller bucket pays:
+// its bounds are tighter and the workgroups of 64 leave compute units idle (98 layers x 8 GPUs 880 -> 760 us, 16: 759 us).
+// With eight mus the bounds are a quarter of the time and it does not (48 layers, limit binding: 3.05 and 3.30 ms).
+OOB_HD inline int bucket_least(int multipliers) { return multipliers > kLambdas ? 64 : 32; }
 
 // The workspace: these words, the lists and bounds of layout(), then the tables of k_exact_flat.
 struct Head {
