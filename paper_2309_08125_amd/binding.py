@@ -7,6 +7,7 @@ There is no CPU fallback: if the library is missing, loading fails.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Dict, List, Optional, Sequence
 
@@ -281,33 +282,48 @@ class DeviceTemplates:
     def __init__(self, count: int, Smax: int, f: int, device="cuda:0"):
         import torch
 
-        sizes = {"feasible": count, "S": count, "kstar": count, "stage_off": count + 1,
-                 "stage_begin": count * (Smax + 1), "stage_gpus": count * Smax, "cover_hdr": 8,
-                 "cover_maxpipes": max(count, f + 1), "status": 1}
-        # the 64-bit arrays first, then the 32-bit ones, every array on an 8-byte boundary
-        self.layout, o = {}, 0
-        for k in self.I64:
-            self.layout[k] = (o, count, torch.int64)
-            o += 8 * count
-        for k in self.I32:
-            n = max(1, sizes[k])
-            self.layout[k] = (o, n, torch.int32)
-            o += (4 * n + 7) // 8 * 8
-        self.base = torch.zeros(o, dtype=torch.uint8, device=device)
-        self.t = {k: self.base[off: off + n * (8 if dt == torch.int64 else 4)].view(dt)
-                  for k, (off, n, dt) in self.layout.items()}
-        self.c = oob_templates()
-        for k in self.I32 + self.I64:
-            setattr(self.c, k, self.t[k].data_ptr())
+        self.layout, nbytes = _templates_layout(count, Smax, f)
+        self.base = torch.zeros(nbytes, dtype=torch.uint8, device=device)
+        self._t = None
+        p = self.base.data_ptr()
+        self.c = oob_templates(*(p + self.layout[k][0] for k, _ in oob_templates._fields_[:14]))
 
-    def to_host(self) -> Dict[str, "object"]:
+    @property
+    def t(self) -> Dict[str, "object"]:
+        """The arrays as device tensors (made when first asked for: a caller that only wants them on the host
+        never does)."""
         import torch
 
-        host = self.base.cpu()  # waits for the stream's work, then one copy
-        r = {k: host[off: off + n * (8 if dt == torch.int64 else 4)].view(dt).numpy()
-             for k, (off, n, dt) in self.layout.items()}
+        if self._t is None:
+            self._t = {k: self.base[off: off + n * w].view(torch.int64 if w == 8 else torch.int32)
+                       for k, (off, n, w) in self.layout.items()}
+        return self._t
+
+    def to_host(self) -> Dict[str, "object"]:
+        import numpy as np
+
+        host = self.base.cpu().numpy()  # waits for the stream's work, then one copy
+        r = {k: host[off: off + n * w].view(np.int64 if w == 8 else np.int32) for k, (off, n, w) in self.layout.items()}
         r["states"], r["candidates"] = int(self.c.states), int(self.c.candidates)
         return r
+
+
+@functools.lru_cache(maxsize=64)
+def _templates_layout(count: int, Smax: int, f: int):
+    """(offset, entries, bytes of an entry) of every result array, and the bytes of them all: the 64-bit arrays first,
+    then the 32-bit ones, every array on an 8-byte boundary."""
+    sizes = {"feasible": count, "S": count, "kstar": count, "stage_off": count + 1,
+             "stage_begin": count * (Smax + 1), "stage_gpus": count * Smax, "cover_hdr": 8,
+             "cover_maxpipes": max(count, f + 1), "status": 1}
+    layout, o = {}, 0
+    for k in DeviceTemplates.I64:
+        layout[k] = (o, count, 8)
+        o += 8 * count
+    for k in DeviceTemplates.I32:
+        n = max(1, sizes[k])
+        layout[k] = (o, n, 4)
+        o += (4 * n + 7) // 8 * 8
+    return layout, o
 
 
 class Planner:
@@ -390,12 +406,9 @@ class Planner:
         return [o.to_host() for o in outs]
 
     def plan(self, inp) -> Dict[str, "object"]:
-        import torch
-
         prof = DeviceProfile(inp, self.device)
         out = self.new_outputs(inp)
         self.enqueue(prof, out)
-        torch.cuda.synchronize(self.device)
         return out.to_host()
 
     def set_option(self, option: int, value: int):
