@@ -145,8 +145,8 @@ __host__ __device__ inline int level_krange(int L, int S) {
 }
 // The longest segments (16, 8 or 4 split points) that still make kSegWorkgroups workgroups of the level: a longer segment
 // pays the set-up and the merge of its keys less often, a shorter one fills the machine and shortens the level.
-// Measured with 256, 512, 1 024, 2 048 workgroups wanted: headline workload 7.44, 7.36, 7.62, 8.61 ms; 61 layers 1.80,
-// 1.57, 1.67, 1.57 ms; batch of 32 jobs 95.6, 95.8, 97.3, 100.8 ms.
+// Measured with 256, 512, 768 workgroups wanted: headline workload 6.93, 6.82, 6.89 ms; 61 layers 1.35, 1.19, 1.26 ms;
+// batch of 32 jobs 78.5, 79.1, 79.4 ms.  8 or 32 split points at most: 7.27, 7.10 ms; 1.19, 1.27 ms; 86.7, 77.1 ms.
 __host__ __device__ inline int seg_target(int L, int S) {
     const long long passes = (long long)level_krange(L, S) * (S - 1);
     return passes >= (long long)kSegTarget * kSegWorkgroups ? kSegTarget : passes >= (long long)kSegTarget / 2 * kSegWorkgroups ? kSegTarget / 2 : kSegMin;

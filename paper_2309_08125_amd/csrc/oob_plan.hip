@@ -67,7 +67,7 @@ struct Tables {
     unsigned long long *key; // the same memory: [deltas * tiles * 64] keys of the current level (keyed kernel)
     int *partK;           // same shape: first k reaching the minimum
     int *stack;           // backtracking stacks / coverage ring
-    int2 *seg_tab;        // per level: (tile index, ub | vb << 8 | segment << 16) of every split task
+    int2 *seg_tab;        // per level: (tile | split points << 16, ub | vb << 8 | offset of the first one << 16) of every split task
     int seg_stride;       // entries reserved per level in seg_tab (level S' starts at (S'-2) * seg_stride)
     int *flags;           // [0] 1: (total, k) keys fit a double and k_split_key runs
                           // [1] 1: the host chose the plain split kernel k_split for this job (then [0] = 0)
@@ -492,7 +492,6 @@ struct KeyArgs {
                          // both families of a low level) to the whole-node family
     int NT, NAall;
     int s0, sstep;       // a launch covers the splits s0, s0 + sstep, ...
-    int target;          // split points of a segment
     int na;              // rows of the key table: targets of the largest group
     int t_lo1, dlo;      // smallest target of the whole-node family; first device set of the level
     int pack, xcd;       // several items per wave near the range ends; XCD-chunked task order
@@ -533,14 +532,14 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     // (negated when the right child streams)
     HIP_DYNAMIC_SHARED(unsigned long long, s_acc)
     const int Sp = ka.Sp, s = ka.s0 + blockIdx.y * ka.sstep, r = Sp - s;
-    const int2 sg = t.seg_tab[(long long)(Sp - 2) * t.seg_stride + (ka.xcd ? xcd_chunked(blockIdx.x, gridDim.x) : (int)blockIdx.x)]; // x: tile index, y: ub | vb << 8 | seg << 16
+    const int2 sg = t.seg_tab[(long long)(Sp - 2) * t.seg_stride + (ka.xcd ? xcd_chunked(blockIdx.x, gridDim.x) : (int)blockIdx.x)];
     const int2 dA = t.lvl_dir[s], dB = t.lvl_dir[r];
     if (t.flags[0] == 0) return;        // keys do not fit: k_select evaluates the candidates itself
     const int L = t.sh.L, M = t.sh.M, n_max = t.sh.n_max;
     // the wave index is the same in all lanes: say so, and everything derived from it (work item,
     // m range, key row) is scalar arithmetic and scalar branches
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
-    const int tile = sg.x, ub = sg.y & 255, vb = (sg.y >> 8) & 255, seg = sg.y >> 16;
+    const int tile = sg.x & 0xffff, klen = sg.x >> 16, ub = sg.y & 255, vb = (sg.y >> 8) & 255, kofs = sg.y >> 16;
     const int fam = (int)blockIdx.z < ka.gz ? ka.fam0 : 1, zg = (int)blockIdx.z < ka.gz ? (int)blockIdx.z : (int)blockIdx.z - ka.gz;
     const int fam_base = fam ? M - 2 : -1;
     const int a_g0 = (fam ? ka.t_lo1 : Sp) + zg * kKeyTargets, a_g1 = imin(fam ? imin(Sp, n_max) : M, a_g0 + kKeyTargets - 1);
@@ -548,14 +547,8 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     const int A_lo = fam ? dA.y : s, A_hi = fam ? imin(s, n_max) : M - 1, B_lo = fam ? dB.y : r, B_hi = fam ? imin(r, n_max) : M - 1;
     const int mA0 = imax(A_lo, a_g0 - B_hi), mA1 = imin(A_hi, a_g1 - B_lo);
     const int mB0 = imax(B_lo, a_g0 - A_hi), mB1 = imin(B_hi, a_g1 - A_lo);
-    // this workgroup's segment of the split points of the block
     const int vmax = tile_vmax(L, vb); // last layer position of the block's columns (never beyond L)
-    int kofs, klen;
-    {
-        const int kr = tile_krange(L, Sp, ub, vb);
-        seg_span(kr, seg_n(kr, ka.target), seg, &kofs, &klen);
-    }
-    const int kmin = ub * 8 + s + kofs, kmax = imin(vmax - r, kmin + klen - 1);
+    const int kmin = ub * 8 + s + kofs, kmax = imin(vmax - r, kmin + klen - 1); // this workgroup's segment of the block's split points
     if (!(mA0 <= mA1 && mB0 <= mB1 && kmin <= kmax)) return; // nothing to merge
     const bool y_left = left_streams(mA1 - mA0 + 1, mB1 - mB0 + 1);
     const int yM0 = y_left ? mA0 : mB0, yM1 = y_left ? mA1 : mB1; // streaming unit counts
@@ -763,13 +756,18 @@ __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
     if (S > t.sh.Smax || threadIdx.x != 0) return;
     const int L = t.sh.L, NB = nblocks_of(L), ubmax = (L - S) / 8, dmin = tile_dmin(L, S), target = seg_target(L, S);
     int2 *out = t.seg_tab + (long long)(S - 2) * t.seg_stride;
+    auto task = [](int tile, int ub, int vb, int kr, int c, int j) {
+        int ofs, len;
+        seg_span(kr, c, j, &ofs, &len);
+        return make_int2(tile | len << 16, ub | vb << 8 | ofs << 16);
+    };
     int n = 0;
     if (!by_row) {
         int tt = 0;
         for (int d = NB - 1; d >= dmin; --d)
             for (int u = 0; u <= imin(ubmax, NB - 1 - d); ++u, ++tt) {
-                const int c = seg_n(tile_krange(L, S, u, u + d), target);
-                for (int j = 0; j < c; ++j) out[n++] = make_int2(tt, u | ((u + d) << 8) | (j << 16));
+                const int kr = tile_krange(L, S, u, u + d), c = seg_n(kr, target);
+                for (int j = 0; j < c; ++j) out[n++] = task(tt, u, u + d, kr, c, j);
             }
         return;
     }
@@ -779,7 +777,7 @@ __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
             int tt = u; // index of block (u, u + d) in tile order: the blocks of all larger d come first
             for (int d = NB - 1; d >= dmin; --d) {
                 if (u + d <= NB - 1 && j < seg_n(tile_krange(L, S, u, u + d), target))
-                    out[n++] = make_int2(tt, u | ((u + d) << 8) | (j << 16));
+                    out[n++] = task(tt, u, u + d, tile_krange(L, S, u, u + d), seg_n(tile_krange(L, S, u, u + d), target), j);
                 tt += imin(ubmax, NB - 1 - d) + 1;
             }
         }
@@ -1660,7 +1658,7 @@ static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT
     KeyArgs ka;
     ka.na = kl.na;
     ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.NAall = NAall; ka.s0 = sr.s0; ka.sstep = sr.sstep;
-    ka.target = seg_target(t.sh.L, S); ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
+    ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
     hipLaunchKernelGGL(k_split_key, dim3(seg_count(t.sh.L, S), sr.scount, kl.groups), dim3(waves * 64), keys + waves * per, st, t, ka);
 }
 // The keyed launches of the splits `sr` of a level: one per family, or one for both.
