@@ -151,7 +151,7 @@ int oob_plan_destroy(oob_plan *h);
 /* Launch options of a handle (tests and measurements; every setting gives bit-identical results).
  * Takes effect from the next oob_plan_templates / oob_plan_templates_batch call on.
  *   OOB_OPT_PLAIN_SPLIT  1: the levels S' >= 2 run the tiled split kernel without (total, k) keys,
- *                        which otherwise only serves shapes beyond the keyed kernel's LDS classes
+ *                        which otherwise only serves shapes that stage more tables than the keyed kernel holds
  *                        (hundreds of nodes); default 0
  *   OOB_OPT_XCD_ORDER    1: the workgroup tasks of a level are ordered block row by block row and
  *                        every XCD walks one contiguous stretch of that list (fewer bytes from

@@ -490,7 +490,7 @@ __device__ __forceinline__ void four_candidates(double &a0, double &a1, double &
 struct KeyArgs {
     int Sp, fam0, gz;    // the first gz target groups of the launch belong to family fam0, the rest (a launch that covers
                          // both families of a low level) to the whole-node family
-    int NT, NAall;
+    int NT;
     int s0, sstep;       // a launch covers the splits s0, s0 + sstep, ...
     int na;              // rows of the key table: targets of the largest group
     int t_lo1, dlo;      // smallest target of the whole-node family; first device set of the level
@@ -1458,8 +1458,7 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     }
     p->ntab = ntab;
     p->na = imin(cnt, kKeyTargets);
-    p->lds = 0; // staged records in static LDS by capacity class, key table in dynamic LDS: see the launch site
-    p->pc = 0; p->waves = kKeyWaves; // by launch, see launch_split_keys
+    p->lds = 0; p->pc = 0; p->waves = 0; // by launch, see launch_split_key
     return true;
 }
 
@@ -1622,31 +1621,13 @@ static bool out_ok(const oob_templates *o) {
 
 // The splits s0, s0 + sstep, ... (scount of them) of level S.
 struct SplitRange { int s0, sstep, scount; };
-// 8-blocks of the stationary side of the split that has the most of them.
-static int most_blocks(const Shape &sh, int S, int fam, const SplitPlan &sp, SplitRange sr) {
-    int t_lo, t_hi;
-    target_units(fam, S, sh.M, sh.n_max, &t_lo, &t_hi);
-    int most = 1;
-    for (int i = 0; i < sr.scount; ++i) {
-        const int s = sr.s0 + i * sr.sstep, r = S - s;
-        int A_lo, A_hi, B_lo, B_hi;
-        child_units(fam, s, sh.M, sh.n_max, &A_lo, &A_hi);
-        child_units(fam, r, sh.M, sh.n_max, &B_lo, &B_hi);
-        for (int g = 0; g < sp.groups; ++g) {
-            const int a0 = t_lo + g * kKeyTargets, a1 = imin(t_hi, a0 + kKeyTargets - 1);
-            const int nA = imin(A_hi, a1 - B_lo) - imax(A_lo, a0 - B_hi) + 1, nB = imin(B_hi, a1 - A_lo) - imax(B_lo, a0 - A_hi) + 1;
-            if (nA > 0 && nB > 0) most = imax(most, cdiv(left_streams(nA, nB) ? nB : nA, 8));
-        }
-    }
-    return most;
-}
 
 // A keyed launch: the target groups of family `fam` (gz of them) and, in a launch for both families
 // of a low level, those of the whole-node family behind them (`groups` in all); at most ntab tables
-// staged per split point, na targets per group, `blocks` work items per split point.
-struct KeyLaunch { int fam, gz, groups, ntab, na, blocks; };
+// staged per split point, na targets per group.
+struct KeyLaunch { int fam, gz, groups, ntab, na; };
 constexpr int kKeyTables = 144; // most tables per split point the keyed kernel serves
-static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int NAall, int xcd, SplitRange sr, hipStream_t st) {
+static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int xcd, SplitRange sr, hipStream_t st) {
     // waves per workgroup: as many as put the most waves on a compute unit (they share the key table), four at most; of
     // equal numbers the larger, which has fewer split points to do one after the other (61 layers 1.31 -> 1.19 ms)
     const size_t keys = (size_t)kl.na * 512, per = (size_t)kl.ntab * 192;
@@ -1657,26 +1638,26 @@ static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT
     }
     KeyArgs ka;
     ka.na = kl.na;
-    ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.NAall = NAall; ka.s0 = sr.s0; ka.sstep = sr.sstep;
+    ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.s0 = sr.s0; ka.sstep = sr.sstep;
     ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
     hipLaunchKernelGGL(k_split_key, dim3(seg_count(t.sh.L, S), sr.scount, kl.groups), dim3(waves * 64), keys + waves * per, st, t, ka);
 }
 // The keyed launches of the splits `sr` of a level: one per family, or one for both.
-static void launch_split_keys(const Tables &t, int S, const bool *have, const SplitPlan *kp, int NT, int NAall, int xcd,
+static void launch_split_keys(const Tables &t, int S, const bool *have, const SplitPlan *kp, int NT, int xcd,
                               SplitRange sr, hipStream_t st) {
     if (sr.scount < 1) return;
     KeyLaunch kl[2];
     for (int fam = 0; fam < 2; ++fam)
         if (have[fam])
-            kl[fam] = KeyLaunch{fam, kp[fam].groups, kp[fam].groups, kp[fam].ntab, kp[fam].na, most_blocks(t.sh, S, fam, kp[fam], sr)};
+            kl[fam] = KeyLaunch{fam, kp[fam].groups, kp[fam].groups, kp[fam].ntab, kp[fam].na};
     if (have[0] && have[1]) {
         const KeyLaunch both{0, kl[0].groups, kl[0].groups + kl[1].groups, imax(kl[0].ntab, kl[1].ntab),
-                             imax(kl[0].na, kl[1].na), imax(kl[0].blocks, kl[1].blocks)};
-        launch_split_key(t, S, both, NT, NAall, xcd, sr, st);
+                             imax(kl[0].na, kl[1].na)};
+        launch_split_key(t, S, both, NT, xcd, sr, st);
         return;
     }
     for (int fam = 0; fam < 2; ++fam)
-        if (have[fam]) launch_split_key(t, S, kl[fam], NT, NAall, xcd, sr, st);
+        if (have[fam]) launch_split_key(t, S, kl[fam], NT, xcd, sr, st);
 }
 
 template <int PC>
@@ -1710,7 +1691,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     sh.cap = mem_cap; sh.count = n_max - n_min + 1;
     sh.Smax = smax_of(L, n_max, M, microbatches);
     // launch shapes first, so that nothing is enqueued when a level cannot be staged in LDS
-    // a level's tables exceed the keyed kernel's LDS classes (or the debug knob says so): plain kernel everywhere
+    // a level stages more tables than the keyed kernel serves (or the debug knob says so): plain kernel everywhere
     int force_plain = h->opt_plain != 0;
     for (int S = 2; S <= sh.Smax; ++S)
         for (int fam = 0; fam < 2; ++fam) {
@@ -1792,7 +1773,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         if (inner) {
             hipStream_t sx = (S & 1) ? lane.aux2 : lane.aux;
             OOB_HIP_CHECK(hipStreamWaitEvent(sx, lane.ev_level[2 * (S - 2)], 0)); // select of level S'-2
-            launch_split_keys(tl, S, have, kp, NT, NAall, h->opt_xcd, SplitRange{2, 1, S - 3}, sx);
+            launch_split_keys(tl, S, have, kp, NT, h->opt_xcd, SplitRange{2, 1, S - 3}, sx);
             OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S + 1], sx));
         }
         // the outer splits: launches of their own, or evaluated by the select kernel itself
@@ -1800,7 +1781,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         if (!force_plain) {
             SplitRange sr = inner ? SplitRange{1, S - 2, 2} : SplitRange{1, 1, S - 1};
             if (fuse) sr = inner ? SplitRange{1, 1, 0} : SplitRange{2, 1, S - 3};
-            launch_split_keys(tl, S, have, kp, NT, NAall, h->opt_xcd, sr, st);
+            launch_split_keys(tl, S, have, kp, NT, h->opt_xcd, sr, st);
         }
         for (int fam = 0; fam < 2 && force_plain; ++fam) {
             if (!have[fam]) continue;

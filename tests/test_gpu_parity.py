@@ -293,8 +293,8 @@ def test_large_times_stay_exact_on_both_paths(P):
 
 
 def test_plain_split_kernel(P):
-    """The tiled split kernel without keys serves shapes whose tables exceed the keyed kernel's
-    LDS classes (hundreds of nodes); the handle option routes ordinary shapes through it."""
+    """The tiled split kernel without keys serves shapes that stage more tables than the keyed
+    kernel holds (hundreds of nodes); the handle option routes ordinary shapes through it."""
     for inp in (inputs.config(1), inputs.config(2),
                 inputs.random_small(3, 37, 3, 1, 5, 9, f=1, tight_mem=True),
                 inputs.random_small(4, 30, 3, 2, 30, 0, f=2),
@@ -305,6 +305,24 @@ def test_plain_split_kernel(P):
         full_check(P, planner, inp)
         assert planner.flags()[:2] == [0, 1]
         planner.close()
+
+
+@pytest.mark.parametrize("nb", [0, 300])
+def test_split_kernel_with_more_than_half_of_the_lds(P, nb):
+    """128 layers on up to 128 nodes: full groups of 64 targets and second groups, launches of 64-88 KB of LDS (four waves'
+    staged tables), against the plain split kernel, which the tests above compare with the oracle."""
+    inp = inputs.random_small(61, 128, 8, 1, 128, nb, f=2)
+    say(f"keyed and plain, N_b {nb}")
+    planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+    got = planner.plan(inp)
+    assert planner.flags()[:2] == [1, 0]
+    planner.set_option(P.OOB_OPT_PLAIN_SPLIT, 1)
+    want = planner.plan(inp)
+    assert planner.flags()[:2] == [0, 1]
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+    assert int(got["status"][0]) == P.OOB_OK
+    planner.close()
 
 
 def test_xcd_chunked_task_order(P):
