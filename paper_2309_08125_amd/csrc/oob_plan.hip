@@ -752,8 +752,10 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
 // first.  by_row = 1 (handle option OOB_OPT_XCD_ORDER, used together with xcd_chunked): block row ub, then segment,
 // then the blocks of that row from the far end, so that neighbours in the list split at the same
 // points k and stage the same left-child records.
+// Bound by the longest list (819 tasks at 98 layers, level 2), hence a task per thread in the default order: one thread for
+// a level's list made the set-up launch 56 us, headline workload 7.59 -> 7.49 ms, 61 layers host to host 1.339 -> 1.332 ms.
 __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
-    if (S > t.sh.Smax || threadIdx.x != 0) return;
+    if (S > t.sh.Smax) return;
     const int L = t.sh.L, NB = nblocks_of(L), ubmax = (L - S) / 8, dmin = tile_dmin(L, S), target = seg_target(L, S);
     int2 *out = t.seg_tab + (long long)(S - 2) * t.seg_stride;
     auto task = [](int tile, int ub, int vb, int kr, int c, int j) {
@@ -762,15 +764,20 @@ __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
         return make_int2(tile | len << 16, ub | vb << 8 | ofs << 16);
     };
     int n = 0;
-    if (!by_row) {
+    if (!by_row) { // diagonal after diagonal, the tasks of one side by side: its blocks have equally many segments
         int tt = 0;
-        for (int d = NB - 1; d >= dmin; --d)
-            for (int u = 0; u <= imin(ubmax, NB - 1 - d); ++u, ++tt) {
-                const int kr = tile_krange(L, S, u, u + d), c = seg_n(kr, target);
-                for (int j = 0; j < c; ++j) out[n++] = task(tt, u, u + d, kr, c, j);
+        for (int d = NB - 1; d >= dmin; --d) {
+            const int blocks = imin(ubmax, NB - 1 - d) + 1, kr = tile_krange(L, S, 0, d), c = seg_n(kr, target);
+            for (int e = threadIdx.x; e < blocks * c; e += blockDim.x) {
+                const int u = e / c;
+                out[n + e] = task(tt + u, u, u + d, kr, c, e - u * c);
             }
+            n += blocks * c;
+            tt += blocks;
+        }
         return;
     }
+    if (threadIdx.x != 0) return;
     for (int u = 0; u <= imin(ubmax, NB - 1 - dmin); ++u) {
         const int cmax = seg_n(tile_krange(L, S, u, NB - 1), target); // the row's longest split range
         for (int j = 0; j < cmax; ++j) {
