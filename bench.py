@@ -22,12 +22,12 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 # Arithmetic per candidate split (s, k, m) as the level kernels execute it (Eq. 1-3 with the child's
-# own total stored, every time an exact integer in a double): 2 adds, 1 compare, 2 selects, 1 min
-# = 6 fp64 vector instructions.  gfx950 issues fp64 add / min / compare / select at one lane
+# own total stored, every time an exact integer in a double): 1 compare, 2 adds (the second one under the
+# mask of the compare), 1 min = 4 fp64 vector instructions.  gfx950 issues fp64 add / min / compare at one lane
 # per SIMD lane and clock: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-instructions/s
 # (half of the 78.6 TFLOP/s quoted for fp64 FMA, which counts two flops per lane-instruction).
-# `roofline.frac` = structural candidates x 6 / time of the level launches / that peak.
-FP64_OPS_PER_CANDIDATE = 6
+# `roofline.frac` = structural candidates x 4 / time of the level launches / that peak.
+FP64_OPS_PER_CANDIDATE = 4
 PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # The same work in the int64 formulation of Eq. 1-3 (4 adds, one 64-bit compare with 3 selects, one
 # 64x32 multiply, one (cost, index) compare-and-select: about 30 32-bit lane operations), kept as
@@ -38,11 +38,11 @@ INT64_OPS_PER_CANDIDATE = 30
 # (profiles/k_split_key_config4.md; not measured by this script): HBM bytes per call from the two
 # rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE over all level kernels, each scaled by what the same
 # counter reads for one 256 MiB device-to-device copy), and vector-ALU wave-instructions per call
-# (SQ_INSTS_VALU of k_split_key + k_select).
+# (SQ_INSTS_VALU of k_split_key + k_select_key + k_level_small).
 PROFILE_CONFIG4 = {"source": "profiles/k_split_key_config4.md",
-                   "hbm_read_bytes_per_call": 19.29e9, "hbm_written_bytes_per_call": 6.27e9,
-                   "valu_wave_insts_per_call": 3.06e9 + 0.07e9,
-                   "kernel_launches_per_call": 277}  # 175 k_split_key + 97 k_select / k_select8 + 5 others (kernel trace)
+                   "hbm_read_bytes_per_call": 16.15e9, "hbm_written_bytes_per_call": 2.29e9,
+                   "valu_wave_insts_per_call": 2.02e9 + 0.04e9,
+                   "kernel_launches_per_call": 268}  # 168 k_split_key + 97 k_select_key + 3 others (kernel trace)
 
 
 def median(xs):
@@ -537,7 +537,7 @@ def main():
                      "traffic": ((prof4["hbm_read_bytes_per_call"] + prof4["hbm_written_bytes_per_call"]) / launches
                                  if prof4 else None),
                      "traffic_unit": "HBM bytes per level (one launch group), rocprofv3 --pmc",
-                     "kernel": "level kernels S'>=2 (divide/combine, Eq. 1-3): k_split_key + k_select / k_select8",
+                     "kernel": "level kernels S'>=2 (divide/combine, Eq. 1-3): k_split_key + k_select_key, k_level_small",
                      "ops_per_candidate": FP64_OPS_PER_CANDIDATE, "launches": launches,
                      "avg_launch_ms": lvl_ms / launches, "levels_ms_per_step": lvl_ms,
                      "candidates_per_s": cands / (lvl_ms * 1e-3),

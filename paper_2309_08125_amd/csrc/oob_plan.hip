@@ -753,7 +753,7 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
 // then the blocks of that row from the far end, so that neighbours in the list split at the same
 // points k and stage the same left-child records.
 // Bound by the longest list (819 tasks at 98 layers, level 2), hence a task per thread in the default order: one thread for
-// a level's list made the set-up launch 56 us, headline workload 7.59 -> 7.49 ms, 61 layers host to host 1.339 -> 1.332 ms.
+// a level's list made the set-up launch 56 instead of 17 us, headline workload 7.59 -> 7.49 ms, 61 layers host to host 1.339 -> 1.332 ms.
 __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
     if (S > t.sh.Smax) return;
     const int L = t.sh.L, NB = nblocks_of(L), ubmax = (L - S) / 8, dmin = tile_dmin(L, S), target = seg_target(L, S);
