@@ -222,9 +222,11 @@ int oob_plan_export_block(oob_plan *h, int S, int delta, double *T, double *T1, 
                           double *T3, int32_t *kstar, int32_t *choice, void *stream);
 
 /* Introspection for tests: copies four int32 flags of the last call to a DEVICE array.
- * flags[0] = 1 when every (total, split point) pair fitted one double key, so that the keyed
- * split kernel did the levels S' >= 2; 0 when the plain split kernel did (totals near the top
- * of the exact range).  Both give identical results.  flags[1..3] are reserved. */
+ * flags[0] = 1 when every (total, split point) pair fitted one double key, so that the levels S' >= 2 beyond
+ * those of flags[2] ran the keyed split kernel; 0 when they did not (totals near the top of the exact range: the select
+ * kernel evaluates every candidate) or flags[1] is set.  flags[1] = 1 when they ran the plain split
+ * kernel.  flags[2] = levels done by one launch each, which uses no keys (OOB_OPT_SMALL_STATE).  flags[3] =
+ * levels whose inner splits ran on the streams of the library.  The results are identical. */
 int oob_plan_export_flags(oob_plan *h, int32_t *flags, void *stream);
 
 #ifdef __cplusplus

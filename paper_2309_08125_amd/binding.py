@@ -415,7 +415,8 @@ class Planner:
         check(load().oob_plan_set_option(self.h, option, value), "oob_plan_set_option")
 
     def flags(self):
-        """[keyed split kernel used, reserved x3] of the last call."""
+        """[(total, split point) keys fit a double, plain split kernel used, levels done by one launch each, levels with splits
+        on other streams] of the last call."""
         import torch
 
         buf = torch.zeros(4, dtype=torch.int32, device=self.device)

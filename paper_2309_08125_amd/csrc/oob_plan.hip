@@ -72,6 +72,7 @@ struct Tables {
     int *flags;           // [0] 1: (total, k) keys fit a double and k_split_key runs
                           // [1] 1: the host chose the plain split kernel k_split for this job (then [0] = 0)
                           // [0] = [1] = 0: k_select evaluates every candidate itself
+                          // [2], [3]: levels done by k_level_small, levels with splits on other streams (tests)
     int *status;
 };
 
@@ -158,7 +159,7 @@ __device__ __forceinline__ unsigned long long scan_bytes(const oob_profile &prof
     return carry;
 }
 
-__device__ void setup_body(const Tables &t, const oob_profile &prof, int force_plain) {
+__device__ void setup_body(const Tables &t, const oob_profile &prof, int force_plain, int2 ran) {
     const int L = t.sh.L, M = t.sh.M;
     __shared__ long long s_worst[OOB_MAX_GPUS + 1];
     __shared__ int s_bad;
@@ -220,6 +221,7 @@ __device__ void setup_body(const Tables &t, const oob_profile &prof, int force_p
         }
         if (st != OOB_OK) t.flags[0] = 0;
         t.flags[1] = force_plain;
+        t.flags[2] = ran.x; t.flags[3] = ran.y;
         *t.status = st;
     }
 }
@@ -794,11 +796,11 @@ __device__ void seg_tab_body(const Tables &t, int S, int by_row) {
 // Everything up to level 1, as one launch of kSetupThreads-wide workgroups: workgroup 0 the set-up, `ones` workgroups
 // level 1, Smax-1 the task lists of the levels 2 .. Smax, the rest set the n keys of either buffer to "no such state".
 // The four parts touch disjoint memory.
-__global__ void __launch_bounds__(kSetupThreads) k_prepare(Tables t, oob_profile prof, int force_plain, int by_row, int ones,
+__global__ void __launch_bounds__(kSetupThreads) k_prepare(Tables t, oob_profile prof, int force_plain, int2 ran, int by_row, int ones,
                                                            long long stride, long long n) {
     const int nseg = imax(t.sh.Smax - 1, 0);
     int b = blockIdx.x;
-    if (b == 0) { setup_body(t, prof, force_plain); return; }
+    if (b == 0) { setup_body(t, prof, force_plain, ran); return; }
     if (b <= ones) { level1_body(t, prof, b - 1); return; }
     b -= ones;
     if (b <= nseg) { seg_tab_body(t, b + 1, by_row); return; }
@@ -1730,9 +1732,15 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     const long long slot_stride = h->cv.slots * 64; // distance between the two buffers of per-split minima
     long long keys = 0; // of the level that has most of them
     for (int S = 2; S <= sh.Smax; ++S) keys = std::max(keys, (long long)(dhi_of(S, M, n_max) - dlo_of(S, M) + 1) * tile_count(L, S) * 64);
+    bool overlap = want_overlap && !force_plain && ov_lo <= ov_hi;
+    int2 ran = make_int2(0, 0);
+    for (int S = 2; S <= sh.Smax; ++S) {
+        ran.x += small[S];
+        ran.y += overlap && !small[S] && S >= ov_lo && S <= ov_hi;
+    }
     const int ones = M * ((tile_count(L, 1) + 3) / 4);
     hipLaunchKernelGGL(k_prepare, dim3((unsigned)(1 + ones + imax(sh.Smax - 1, 0) + (2 * keys + kSetupThreads - 1) / kSetupThreads)),
-                       dim3(kSetupThreads), 0, st, t, *profile, force_plain, h->opt_xcd, ones, slot_stride, keys);
+                       dim3(kSetupThreads), 0, st, t, *profile, force_plain, ran, h->opt_xcd, ones, slot_stride, keys);
     // Levels.  Level S' depends on the lower levels like this: its inner splits 2 <= s <= S'-2 read the
     // levels up to S'-2 only, its two outer splits (s = 1 and S'-1) read level S'-1, and its select
     // needs all its splits.  So the chain that cannot be shortened is outer splits -> select ->
@@ -1746,7 +1754,6 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     // records, the two waits and the third launch of an overlapped one occupy the host for longer (one stream
     // throughout, against three: 26 layers 312 and 732 us, 61 layers 1.62 and 1.78 ms, headline workload 10.5 and
     // 7.5 ms; the line at 0, 20, 40, 80 million candidates: headline workload 7.47, 7.60, 7.69, 7.89 ms).
-    bool overlap = want_overlap && !force_plain && ov_lo <= ov_hi;
     if (overlap && !lane.aux) lane.aux = borrow_stream();
     if (overlap && !lane.aux2) lane.aux2 = borrow_stream();
     if (overlap && lane.aux && lane.aux2) {

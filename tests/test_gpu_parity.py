@@ -393,6 +393,51 @@ def test_levels_on_several_streams(P, overlap_from):
         planner.close()
 
 
+def level_counts(inp):
+    """Per level S' >= 2: candidates, and those of the widest state of the device set with most (s, m) pairs."""
+    L, M = inp.L, inp.gpus_per_node
+    out = {}
+    for S in range(2, min(L, inp.n_max * M, inp.microbatches or L) + 1):
+        pairs = {}
+        for s in range(1, S):
+            r = S - s
+            for a in range(s, M):  # GPUs inside a node
+                for b in range(r, M - a + 1):
+                    if b < M:
+                        pairs[0, a + b] = pairs.get((0, a + b), 0) + 1
+            for a in range(-(-s // M), min(s, inp.n_max) + 1):  # whole nodes
+                for b in range(-(-r // M), min(r, inp.n_max - a) + 1):
+                    pairs[1, a + b] = pairs.get((1, a + b), 0) + 1
+        n = L - S + 1
+        out[S] = sum(pairs.values()) * (n * (n + 1) * (n + 2) // 6), max(pairs.values(), default=0) * n
+    return out
+
+
+@pytest.mark.parametrize("job", [1, 2, 3, (60, 2, 1, 6, 11), (30, 3, 2, 30, 0), (40, 16, 1, 3, 0)])
+def test_flags_say_which_launches_did_the_levels(P, job):
+    """How many levels one launch did, and how many put their inner splits on other streams."""
+    inp = inputs.config(job) if isinstance(job, int) else inputs.random_small(5, *job, f=2)
+    levels = level_counts(inp)
+    planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+    got = planner.plan(inp)
+    assert got["candidates"] == sum(c for c, _ in levels.values())
+    small = {S for S, (c, widest) in levels.items() if widest <= 640 and c <= 500000}
+    assert planner.flags() == [1, 0, len(small), 0]
+    planner.set_option(P.OOB_OPT_PLAIN_SPLIT, 1)
+    planner.plan(inp)
+    assert planner.flags() == [0, 1, 0, 0]
+    planner.set_option(P.OOB_OPT_PLAIN_SPLIT, 0)
+    planner.set_option(P.OOB_OPT_OVERLAP_FROM, 20)
+    planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
+    planner.plan(inp)
+    large = [S for S, (c, _) in levels.items() if S >= 4 and c >= 20000]
+    assert planner.flags() == [1, 0, 0, max(large) - min(large) + 1 if large else 0]
+    planner.set_option(P.OOB_OPT_ONE_STREAM, 1)
+    planner.plan(inp)
+    assert planner.flags() == [1, 0, 0, 0]
+    planner.close()
+
+
 @pytest.mark.parametrize("small_state", [0, 100, 1 << 30])
 def test_levels_by_one_launch(P, small_state):
     """Levels of at most `small_state` candidates a state candidate by candidate: none, some, all of them; one to
