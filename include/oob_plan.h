@@ -172,8 +172,8 @@ int oob_plan_destroy(oob_plan *h);
  *                        24000 (a smaller level is done before the events of an overlap are enqueued)
  *   OOB_OPT_SMALL_STATE  value = candidates of a state: a level whose widest state has no more is done by one
  *                        launch, candidate by candidate (up to half a million candidates of the level); default 640,
- *                        0: none.  The options XCD_ORDER, SELECT8_FROM, FUSE_FROM and OVERLAP_FROM set it to 0
- *                        (they are about the kernels of larger levels)
+ *                        0: none.  The options XCD_ORDER, SELECT8_FROM, FUSE_FROM and OVERLAP_FROM are about the
+ *                        kernels of the other levels: 0 here puts every level through those
  * Returns OOB_EINVAL for an unknown option. */
 #define OOB_OPT_PLAIN_SPLIT 1
 #define OOB_OPT_XCD_ORDER 2

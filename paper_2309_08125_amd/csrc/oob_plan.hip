@@ -1869,12 +1869,11 @@ extern "C" int oob_plan_set_option(oob_plan *h, int option, int value) {
     if (!h) return OOB_EINVAL;
     switch (option) {
     case OOB_OPT_PLAIN_SPLIT: h->opt_plain = value != 0; break;
-    // options of kernels that small levels do not run: they ask for those kernels
-    case OOB_OPT_XCD_ORDER: h->opt_xcd = value != 0; h->opt_small_state = 0; break;
+    case OOB_OPT_XCD_ORDER: h->opt_xcd = value != 0; break;
     case OOB_OPT_ONE_STREAM: h->opt_one_stream = value != 0; break;
-    case OOB_OPT_SELECT8_FROM: h->opt_select8_from = value; h->opt_small_state = 0; break;
-    case OOB_OPT_FUSE_FROM: h->opt_fuse_from = value; h->opt_small_state = 0; break;
-    case OOB_OPT_OVERLAP_FROM: h->opt_overlap_from = value; h->opt_small_state = 0; break;
+    case OOB_OPT_SELECT8_FROM: h->opt_select8_from = value; break;
+    case OOB_OPT_FUSE_FROM: h->opt_fuse_from = value; break;
+    case OOB_OPT_OVERLAP_FROM: h->opt_overlap_from = value; break;
     case OOB_OPT_SMALL_STATE: h->opt_small_state = value; break;
     default: return OOB_EINVAL;
     }

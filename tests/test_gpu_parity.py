@@ -335,6 +335,7 @@ def test_xcd_chunked_task_order(P):
         print("xcd", inp.name, inp.L, flush=True)
         planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
         planner.set_option(P.OOB_OPT_XCD_ORDER, 1)
+        planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
         full_check(P, planner, inp)
         planner.close()
 
@@ -355,6 +356,7 @@ def test_select_with_eight_lanes_per_state(P):
                     inputs.random_small(21, 9, 2, 1, 3, 7, t_lo=(1 << 38), t_hi=(1 << 39))):
             print("select8", fuse_from, inp.name, inp.L, flush=True)
             planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+            planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
             planner.set_option(P.OOB_OPT_SELECT8_FROM, 2)
             planner.set_option(P.OOB_OPT_FUSE_FROM, fuse_from)
             planner.set_option(P.OOB_OPT_ONE_STREAM, one_stream)
@@ -374,6 +376,7 @@ def test_levels_on_several_streams(P, overlap_from):
     for inp in (inputs.config(2), inputs.random_small(5, 60, 2, 1, 6, 11, f=2), inputs.random_small(4, 30, 3, 2, 30, 0, f=2)):
         say(f"overlap from {overlap_from} {inp.name} {inp.L}")
         planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+        planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
         planner.set_option(P.OOB_OPT_OVERLAP_FROM, overlap_from)
         full_check(P, planner, inp)
         prof, out = P.DeviceProfile(inp), planner.new_outputs(inp)
@@ -436,6 +439,32 @@ def test_flags_say_which_launches_did_the_levels(P, job):
     planner.plan(inp)
     assert planner.flags() == [1, 0, 0, 0]
     planner.close()
+
+
+def test_options_do_not_change_each_other(P):
+    """An option at its default value changes nothing, and the order of the calls does not matter."""
+    inp = inputs.config(3)
+    planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+    planner.plan(inp)
+    flags = planner.flags()
+    assert flags[2] > 0 and flags[3] == 0
+    for option, value in ((P.OOB_OPT_PLAIN_SPLIT, 0), (P.OOB_OPT_XCD_ORDER, 0), (P.OOB_OPT_ONE_STREAM, 0),
+                          (P.OOB_OPT_SELECT8_FROM, 82), (P.OOB_OPT_FUSE_FROM, 82), (P.OOB_OPT_OVERLAP_FROM, 24000),
+                          (P.OOB_OPT_SMALL_STATE, 640)):
+        planner.set_option(option, value)
+        planner.plan(inp)
+        assert planner.flags() == flags, option
+    planner.close()
+    seen = []
+    options = [(P.OOB_OPT_SMALL_STATE, 1000), (P.OOB_OPT_OVERLAP_FROM, 200), (P.OOB_OPT_XCD_ORDER, 1)]
+    for order in (options, options[::-1]):
+        planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+        for option, value in order:
+            planner.set_option(option, value)
+        planner.plan(inp)
+        seen.append(planner.flags())
+        planner.close()
+    assert seen[0] == seen[1] and seen[0][2] > 0 and seen[0][3] > 0, seen
 
 
 @pytest.mark.parametrize("small_state", [0, 100, 1 << 30])
