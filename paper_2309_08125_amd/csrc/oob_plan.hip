@@ -1635,21 +1635,29 @@ struct SplitRange { int s0, sstep, scount; };
 // of a low level, those of the whole-node family behind them (`groups` in all); at most ntab tables
 // staged per split point, na targets per group.
 struct KeyLaunch { int fam, gz, groups, ntab, na; };
-constexpr int kKeyTables = 144; // most tables per split point the keyed kernel serves
-static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int xcd, SplitRange sr, hipStream_t st) {
-    // waves per workgroup: as many as put the most waves on a compute unit (they share the key table), four at most; of
-    // equal numbers the larger, which has fewer split points to do one after the other (61 layers 1.31 -> 1.19 ms)
-    const size_t keys = (size_t)kl.na * 512, per = (size_t)kl.ntab * 192;
+// Most tables per split point the keyed kernel serves: with a full group of targets four waves then still fit a
+// compute unit, in a workgroup of 140 KB.  Measured against the plain kernel, most tables, layers x nodes x GPUs per node:
+// 76, 150 x 150 x 8: 109 and 329 ms; 82, 140 x 140 x 64: 137 and 452 ms; 99, 176 x 176 x 8: 313 and 833 ms; 120, 200 x 200 x 8:
+// 747 and 1 790 ms; 136, 240 x 200 x 8: 2.67 and 5.50 s.
+constexpr int kKeyTables = 144;
+// Waves per workgroup of a keyed launch: as many as put the most waves on a compute unit (they share the key table), four
+// at most; of equal numbers the larger, which has fewer split points to do one after the other (61 layers 1.31 -> 1.19 ms).
+static int key_waves(int na, int ntab) {
+    const size_t keys = (size_t)na * 512, per = (size_t)ntab * 192;
     int waves = 1, most = 0;
     for (int w = 1; w <= kKeyWaves; ++w) {
         const int on = imin((int)(kLdsLimit / (keys + w * per)) * w, 4 * kWavesPerSimd);
         if (on >= most) { most = on; waves = w; }
     }
+    return waves;
+}
+static size_t key_lds(int na, int ntab) { return (size_t)na * 512 + (size_t)key_waves(na, ntab) * ntab * 192; }
+static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int xcd, SplitRange sr, hipStream_t st) {
     KeyArgs ka;
     ka.na = kl.na;
     ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.s0 = sr.s0; ka.sstep = sr.sstep;
     ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
-    hipLaunchKernelGGL(k_split_key, dim3(seg_count(t.sh.L, S), sr.scount, kl.groups), dim3(waves * 64), keys + waves * per, st, t, ka);
+    hipLaunchKernelGGL(k_split_key, dim3(seg_count(t.sh.L, S), sr.scount, kl.groups), dim3(key_waves(kl.na, kl.ntab) * 64), key_lds(kl.na, kl.ntab), st, t, ka);
 }
 // The keyed launches of the splits `sr` of a level: one per family, or one for both.
 static void launch_split_keys(const Tables &t, int S, const bool *have, const SplitPlan *kp, int NT, int xcd,
@@ -1702,11 +1710,18 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     // launch shapes first, so that nothing is enqueued when a level cannot be staged in LDS
     // a level stages more tables than the keyed kernel serves (or the debug knob says so): plain kernel everywhere
     int force_plain = h->opt_plain != 0;
-    for (int S = 2; S <= sh.Smax; ++S)
+    size_t lds = 0; // of the largest keyed launch
+    for (int S = 2; S <= sh.Smax; ++S) {
+        int ntab = 0, na = 0;
         for (int fam = 0; fam < 2; ++fam) {
             SplitPlan sp;
-            if (plan_split_key(sh, S, fam, &sp) && sp.ntab > kKeyTables) force_plain = 1;
+            if (plan_split_key(sh, S, fam, &sp)) { ntab = imax(ntab, sp.ntab); na = imax(na, sp.na); }
         }
+        if (ntab > kKeyTables) force_plain = 1;
+        else if (ntab) lds = std::max(lds, key_lds(na, ntab));
+    }
+    if (!force_plain && lds > kLdsPrefer) // beyond the default dynamic-LDS limit of a launch
+        OOB_HIP_CHECK(hipFuncSetAttribute((const void *)k_split_key, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit));
     if (force_plain)
         for (int S = 2; S <= sh.Smax; ++S)
             for (int fam = 0; fam < 2; ++fam) {

@@ -325,6 +325,24 @@ def test_split_kernel_with_more_than_half_of_the_lds(P, nb):
     planner.close()
 
 
+@pytest.mark.parametrize("shape", [(150, 1, 150, 8, 0), (140, 1, 140, 64, 290), (176, 1, 176, 8, 0), (200, 1, 200, 8, 410)])
+def test_split_kernel_of_the_most_nodes_it_serves(P, shape):
+    """One hundred and forty to two hundred nodes: 76 to 120 tables staged per split point, launches of 81 to 125 KB of LDS,
+    against the plain split kernel."""
+    L, n_min, n_max, M, nb = shape
+    inp = inputs.random_small(61, L, M, n_min, n_max, nb, f=2)
+    planner = P.Planner(L, n_max, M)
+    got, flags = planner.plan(inp), planner.flags()
+    assert flags[:2] == [1, 0]
+    planner.set_option(P.OOB_OPT_PLAIN_SPLIT, 1)
+    want = planner.plan(inp)
+    assert planner.flags()[:2] == [0, 1]
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+    assert int(got["status"][0]) == P.OOB_OK
+    planner.close()
+
+
 def test_xcd_chunked_task_order(P):
     """The other order of the workgroup tasks (block row by block row, each XCD walking one
     contiguous stretch of the list) computes the same tables."""
