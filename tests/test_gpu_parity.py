@@ -72,18 +72,26 @@ SHAPES = [(5, 1, 1, 3, 6), (6, 2, 1, 3, 8), (7, 2, 1, 2, 5), (6, 4, 1, 2, 12), (
           (40, 64, 1, 1, 0), (20, 64, 1, 2, 24)]
 
 
+# Levels of few candidates are done by one launch, which leaves little of a small job to the split and select kernels:
+# the sweeps below run as a caller gets them and with every level through those kernels.
+every_kernel = pytest.mark.parametrize("small_state", [640, 0])
+
+
+@every_kernel
 @pytest.mark.parametrize("shape", SHAPES)
-def test_small_random_every_state(P, shape):
+def test_small_random_every_state(P, shape, small_state):
     """Small and ragged shapes (L not a multiple of any tile, L = 1, more nodes than layers,
     N_b below the stage limit, the paper's N_b = 4 S' mode), three variants of the memory cap /
     forbidden GPU counts, every state compared."""
     L, M, n_min, n_max, nb = shape
     planner = P.Planner(L, n_max, M)
+    planner.set_option(P.OOB_OPT_SMALL_STATE, small_state)
     for seed in range(3):
         for var in ("plain", "tight", "forbid"):
             inp = inputs.random_small(seed, L, M, n_min, n_max, nb, f=seed,
                                       tight_mem=(var == "tight"), forbid_some_d=(var == "forbid"))
             full_check(P, planner, inp)
+            assert small_state or planner.flags()[2] == 0
     planner.close()
 
 
@@ -97,7 +105,8 @@ def test_longest_model_the_library_takes(P):
     planner.close()
 
 
-def test_many_random_shapes_on_one_handle(P):
+@every_kernel
+def test_many_random_shapes_on_one_handle(P, small_state):
     """Four hundred random shapes (L, GPUs per node, template range, N_b, f, memory and
     forbidden-GPU-count variants, large times, uniform layers) back to back on one handle, every
     state of every case against the oracle."""
@@ -105,6 +114,7 @@ def test_many_random_shapes_on_one_handle(P):
 
     rng = random.Random(2309)
     planner = P.Planner(60, 24, 16)
+    planner.set_option(P.OOB_OPT_SMALL_STATE, small_state)
     states = 0
     for case in range(400):
         M = rng.choice([1, 1, 2, 3, 4, 5, 8, 8, 12, 16])
@@ -128,9 +138,11 @@ def test_many_random_shapes_on_one_handle(P):
     assert states > 1_000_000
 
 
-def test_handle_reuse_across_shapes(P):
+@every_kernel
+def test_handle_reuse_across_shapes(P, small_state):
     """One handle sized for the maxima serves smaller jobs back to back."""
     planner = P.Planner(40, 6, 4)
+    planner.set_option(P.OOB_OPT_SMALL_STATE, small_state)
     for i, (L, M, n_max, nb) in enumerate([(40, 4, 6, 16), (9, 2, 3, 5), (25, 3, 6, 0), (40, 1, 6, 40)]):
         full_check(P, planner, inputs.random_small(50 + i, L, M, 1, n_max, nb, f=1, tight_mem=(i % 2 == 0)))
     planner.close()
@@ -224,9 +236,10 @@ def test_config4_repeated_calls_on_one_handle_stay_identical(P):
     planner.close()
 
 
-def test_call_can_be_captured_into_a_graph_and_replayed(P):
-    """The call forks to the handle's second stream and joins it again with events, so a caller
-    may capture it.  The graph is replayed three times with eager work in between; every replay
+@pytest.mark.parametrize("fork", [False, True])
+def test_call_can_be_captured_into_a_graph_and_replayed(P, fork):
+    """The call stays on the caller's stream, or forks to the streams of the handle and joins them again with
+    events, so a caller may capture it.  The graph is replayed three times with eager work in between; every replay
     must give the oracle's templates again (the output buffers are cleared before each)."""
     import torch
 
@@ -234,12 +247,16 @@ def test_call_can_be_captured_into_a_graph_and_replayed(P):
     o, want = oracle_expected(inp)
     o.close()
     planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+    if fork:
+        planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
+        planner.set_option(P.OOB_OPT_OVERLAP_FROM, 0)
     prof = P.DeviceProfile(inp)
     out = planner.new_outputs(inp)
     side = torch.cuda.Stream()
     with torch.cuda.stream(side):
-        planner.enqueue(prof, out)  # first call: the handle creates its second stream and events
+        planner.enqueue(prof, out)  # first call: the handle creates its streams and events
     torch.cuda.synchronize()
+    assert planner.flags()[2:] == ([0, 23] if fork else [25, 0])
     PU.compare_templates(out.to_host(), want, inp.n_max - inp.n_min + 1)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=side):
@@ -273,12 +290,14 @@ def test_device_status_reports_bad_profile_values(P):
     planner.close()
 
 
-def test_large_times_stay_exact_on_both_paths(P):
+@every_kernel
+def test_large_times_stay_exact_on_both_paths(P, small_state):
     """Times near the top of the exactly representable range.  Up to a bound the set-up
     kernel checks, (total, split point) pairs fit one double and the keyed split kernel runs;
     above it the select kernel evaluates every candidate itself.  Both must match the oracle
-    bit for bit."""
+    bit for bit; so must the launch of the small levels, which has no keys."""
     planner = P.Planner(12, 4, 3)
+    planner.set_option(P.OOB_OPT_SMALL_STATE, small_state)
     seen = set()
     for seed in range(4):
         for inp in (inputs.random_small(20 + seed, 9, 2, 1, 3, 7, t_lo=(1 << 38), t_hi=(1 << 39)),
@@ -288,8 +307,36 @@ def test_large_times_stay_exact_on_both_paths(P):
                     inputs.random_small(50 + seed, 12, 3, 1, 4, 9)):
             full_check(P, planner, inp)
             seen.add(tuple(planner.flags()[:2]))
+            assert small_state or planner.flags()[2] == 0
     assert seen == {(0, 0), (1, 0)}, "keyed kernel and in-select evaluation must both have run"
     planner.close()
+
+
+@pytest.mark.parametrize("shape", [(40, 1, 1, 5, 4000), (63, 1, 1, 4, 3000), (64, 1, 2, 3, 2500), (20, 2, 1, 4, 2000), (12, 3, 1, 4, 0)])
+def test_totals_just_below_and_above_what_a_key_holds(P, shape):
+    """The largest profile whose totals fit keys and the smallest whose do not, one unit of the bound apart.  A key of a
+    level is total, split and split point: with a microbatch count far above the stage count the totals come within a
+    few per cent of the field they have (one GPU per node, most of the time in one layer)."""
+    import dataclasses
+
+    L, M, n_min, n_max, nb = shape
+    base = inputs.random_small(17, L, M, n_min, n_max, nb, t_lo=1 << 10, t_hi=1 << 11)
+    base.fwd_ns[L // 3] = 1 << 24
+    Smax = P.oob_plan_max_stages(L, n_max, M, nb)
+    mult = (nb or 4 * Smax) + 4 * Smax + 4
+    line = ((1 << 52) >> L.bit_length()) // mult  # keys fit iff the sum below stays under this
+    w = int((base.fwd_ns + base.bwd_ns).sum() + base.boundary_ns.sum())
+    scale = (line - 1) // w
+    for above in (False, True):
+        inp = dataclasses.replace(base, fwd_ns=base.fwd_ns * scale, bwd_ns=base.bwd_ns * scale, boundary_ns=base.boundary_ns * scale)
+        inp.fwd_ns[L // 3, 0] += line - 1 + above - w * scale  # the sum is now line - 1 or line
+        planner = P.Planner(L, n_max, M)
+        planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
+        got, _ = full_check(P, planner, inp)
+        assert planner.flags()[:3] == [0 if above else 1, 0, 0], above
+        top = int(got["T"][got["S"] > 1].max()) << L.bit_length()  # (one stage: no key)
+        assert top < 1 << 52 and (M > 1 or top > 0.95 * (1 << 52)), top / (1 << 52)
+        planner.close()
 
 
 def test_plain_split_kernel(P):
@@ -501,10 +548,12 @@ def test_levels_by_one_launch(P, small_state):
         planner.close()
 
 
-def test_two_calls_same_answer(P):
+@every_kernel
+def test_two_calls_same_answer(P, small_state):
     """Determinism: the same job twice on one handle gives identical tables."""
     inp = inputs.config(2)
     planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+    planner.set_option(P.OOB_OPT_SMALL_STATE, small_state)
     a = planner.plan(inp)
     blocks_a = {(S, d): planner.block(S, d) for S in (2, 5, 9) for d in range(3, 12)}
     b = planner.plan(inp)
