@@ -413,19 +413,21 @@ def test_stages_that_leave_a_layer_uncovered_are_ruled_out(P):
     assert slow < h["ncand"] // 2 and h["alive"] <= slow + h["bucket"]
 
 
-@pytest.mark.parametrize("templates", [1, 3, 4, 5, 32, 33, 64])
-def test_filter_with_one_to_sixty_four_templates(P, templates):
-    """The filter gives an entry as many lanes as its templates round up to: one template to all of a wave, stage counts
-    (up to 64 multipliers) and without."""
-    for staged, L, M, nb in ((False, 40, 6, 0), (True, 40, 6, 22)):
-        n_max = min(templates, 8) if staged else templates
-        inp = inputs.random_small(31, L, M, 1, n_max, nb, f=1, t_lo=20)
-        e = P.ExactMinimum(inp, staged=staged)
-        st, got = e.run()
-        h = exact_sizes.head(e.workspace)
-        want = E.exact_minimum_staged(inp) if staged else E.exact_minimum(inp)
-        assert st == P.OOB_OK and got == want, (staged, templates)
-        assert 0 < h["alive"] <= h["ncand"] and h["bucket"] >= 32
+@pytest.mark.parametrize("templates", [1, 3, 4, 5, 32, 33, 63, 64])
+@pytest.mark.parametrize("job", [(40, 6, 0), (66, 2, 0), (66, 2, 20)])
+def test_filter_with_one_to_sixty_four_templates(P, templates, job):
+    """The filter gives an entry as many lanes as its templates round up to (those of at most a node per layer): from one
+    template to all of a wave, with stage counts (the limit binds: 64 multipliers) and without."""
+    L, M, nb = job
+    staged = nb > 0
+    n_max = max(templates, 12) if staged else templates
+    inp = inputs.random_small(31, L, M, n_max - templates + 1, n_max, nb, f=1, t_lo=20)
+    e = P.ExactMinimum(inp, staged=staged)
+    st, got = e.run()
+    h = exact_sizes.head(e.workspace)
+    want = E.exact_minimum_staged(inp) if staged else E.exact_minimum(inp)
+    assert st == P.OOB_OK and got == want
+    assert 0 < h["alive"] <= h["ncand"] and h["bucket"] >= (64 if staged else 32)
 
 
 @pytest.mark.parametrize("shape", [(70, 2, 1, 30, 40), (50, 8, 1, 20, 33)])
