@@ -811,10 +811,17 @@ __global__ void __launch_bounds__(kSetupThreads) k_prepare(Tables t, oob_profile
 // ---------------------------------------------------------------------------------------
 // Levels S' >= 2, second kernel: grid (block of the plane, delta), one lane per state.
 // ---------------------------------------------------------------------------------------
+__device__ __forceinline__ Rec24 load24(const Rec *p) { return load24(p, 0); }
+// Eq. 1-3 for one candidate from the (T, T1, tmax) of its children.
+__device__ __forceinline__ double cand_total(const Rec24 &a, const Rec24 &b, double cl, double cr) {
+    return a.tm >= b.tm ? (a.a.x + cl * a.tm) + 2.0 * b.a.y : a.a.y + (b.a.x + cr * b.tm);
+}
+
 // Without the keys of k_split_key: the per-split minima of k_split (flags[1]), or every candidate.
 constexpr int kSelPairs = 2; // pairs of child records a lane has in flight while it looks for the first m
 __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall) {
     const int L = t.sh.L, M = t.sh.M, lane = threadIdx.x;
+    const long long trecs = t.tab_recs;
     int ub, vb;
     tile_decode(L, Sp, blockIdx.x, &ub, &vb);
     const int aidx = blockIdx.y, delta = dlo_of(Sp, M) + aidx;
@@ -832,7 +839,6 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
     int ks = 0, ch = 0;
     const Family fam = family_of(delta, M);
     int bm = 0;
-    Rec a = out, b = out;
     if (!t.flags[1]) {
         // Totals too large for keys (decided by the set-up kernel from the profile): every candidate
         // (s, k, m) of this state in that order with a strict-minimum update.  Slow, exact, rare.
@@ -842,14 +848,15 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
                 int mlo, mhi;
                 m_range(fam.fam, fam.units, s, r, M, t.sh.n_max, &mlo, &mhi);
                 const double cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r, cr = t.sh.Nb > 0 ? 0.0 : 4.0 * s;
-                for (int k = u + s; k <= v - r; ++k)
+                const Rec *baseA = t.rec + (t.lvl_tab[s] - dlo_of(s, M) + fam.fam_base) * trecs;
+                const Rec *baseB = t.rec + (t.lvl_tab[r] - dlo_of(r, M) + fam.fam_base + fam.units) * trecs;
+                for (int k = u + s; k <= v - r; ++k) {
+                    const Rec *atA = baseA + rec_off(u, k, t.coff, t.NB), *atB = baseB + rec_off(k, v, t.coff, t.NB);
                     for (int m = mlo; m <= mhi; ++m) {
-                        const Rec ra = t.rec[rec_index(t, s, fam.fam_base + m, u, k)];
-                        const Rec rb = t.rec[rec_index(t, r, fam.fam_base + fam.units - m, k, v)];
-                        const double T = ra.tmax >= rb.tmax ? (ra.T + cl * ra.tmax) + 2.0 * rb.T1
-                                                            : ra.T1 + (rb.T + cr * rb.tmax);
-                        if (T < best) { best = T; bs = s; bk = k; bm = m; a = ra; b = rb; }
+                        const double T = cand_total(load24(atA + m * trecs), load24(atB - m * trecs), cl, cr);
+                        if (T < best) { best = T; bs = s; bk = k; bm = m; }
                     }
+                }
             }
     } else if (best < kNone) {
         const int r = Sp - bs;
@@ -873,7 +880,7 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
             for (int q = 0; q < kSelPairs; ++q) {
                 const double T = ra[q].tmax >= rb[q].tmax ? (ra[q].T + cl * ra[q].tmax) + 2.0 * rb[q].T1
                                                           : ra[q].T1 + (rb[q].T + cr * rb[q].tmax);
-                if (bm == 0 && m0 + q <= mhi && T == best) { bm = m0 + q; a = ra[q]; b = rb[q]; }
+                if (bm == 0 && m0 + q <= mhi && T == best) bm = m0 + q;
             }
         }
     }
@@ -884,10 +891,12 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
             const int r = Sp - bs;
             const long long oa = rec_index(t, bs, fam.fam_base + bm, u, bk);
             const long long ob = rec_index(t, r, fam.fam_base + fam.units - bm, bk, v);
+            const Rec a = t.rec[oa], b = t.rec[ob];
+            const int ka = t.kstar[oa], kb = t.kstar[ob];
             out.T = best;
-            out.T1 = a.T1 + b.T1;                                                                // Eq. 1
-            if (a.tmax >= b.tmax) { out.tmax = a.tmax; ks = t.kstar[oa]; out.T3 = a.T3 + b.T1; } // Eq. 3
-            else                  { out.tmax = b.tmax; ks = bs + t.kstar[ob]; out.T3 = b.T3; }
+            out.T1 = a.T1 + b.T1;                                                     // Eq. 1
+            if (a.tmax >= b.tmax) { out.tmax = a.tmax; ks = ka; out.T3 = a.T3 + b.T1; } // Eq. 3
+            else                  { out.tmax = b.tmax; ks = bs + kb; out.T3 = b.T3; }
             ch = bs | (bk << 10) | (bm << 21);
         }
     }
@@ -918,12 +927,6 @@ __global__ void __launch_bounds__(64) k_select(Tables t, int Sp, int NT, int NAa
 // ---------------------------------------------------------------------------------------
 constexpr int kSel8Outer = 4;  // candidates of the outer splits a lane has in flight
 constexpr int kSel8M = 2;      // m a lane tests per round
-
-__device__ __forceinline__ Rec24 load24(const Rec *p) { return load24(p, 0); }
-// Eq. 1-3 for one candidate from the (T, T1, tmax) of its children.
-__device__ __forceinline__ double cand_total(const Rec24 &a, const Rec24 &b, double cl, double cr) {
-    return a.tm >= b.tm ? (a.a.x + cl * a.tm) + 2.0 * b.a.y : a.a.y + (b.a.x + cr * b.tm);
-}
 
 template <int LPS, bool FUSE>
 __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int NAall) {
