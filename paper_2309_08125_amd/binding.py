@@ -364,7 +364,7 @@ class Planner:
 
     def valu_peak(self, f64_mix: bool = False) -> float:
         """Measured lane-operations per second: 32-bit add / compare / select (oob_plan_valu_peak) or
-        the fp64 mix of a candidate (oob_plan_valu_peak_f64)."""
+        the fp64 instructions of a candidate as the keyed split kernel executes it (oob_plan_valu_peak_f64)."""
         import torch
 
         v = C.c_double()

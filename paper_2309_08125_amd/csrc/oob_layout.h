@@ -131,8 +131,9 @@ __host__ __device__ inline int tile_vmax(int L, int vb) { return vb * 8 + 7 - co
 
 // Split points k of a block of the plane at level S': kmin = 8 ub + s .. kmax = vmax - (S' - s):
 // their number does not depend on s.  The keyed split kernel cuts this range into segments, one workgroup each, of
-// whole groups of kSegUnit consecutive k (what it stages at a time; the last group may be short): as many segments as
-// the range divided by the target gives, rounded to the nearest, all of the same number of groups up to one.
+// whole groups of kSegUnit consecutive k (its up to four waves take the split points of a segment in turn: whole
+// groups of four are equally many for each; the last group may be short): as many segments as the range divided by
+// the target gives, rounded to the nearest, all of the same number of groups up to one.
 constexpr int kSegUnit = 4;
 constexpr int kSegMin = 4; // no target below this (sizes the task lists)
 constexpr int kSegTarget = 16, kSegWorkgroups = 512;

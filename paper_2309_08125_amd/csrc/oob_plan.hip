@@ -1937,9 +1937,10 @@ __global__ void __launch_bounds__(256) k_valu_peak(int *sink, int iters, int a, 
     if (r == 0x7fffffff) sink[0] = r; // keeps the chains alive; practically never taken
 }
 
-// Measurement: the instruction mix of a candidate of the split kernels in fp64, eight candidates per
-// step as there (two adds, a compare, a 64-bit select, a min against a running minimum each), plus
-// the three adds that change the step's streaming values.  51 lane-instructions per step.
+// Measurement: the step of k_split_key without LDS, keys and addresses: eight candidates by four_candidates, four
+// vector instructions each (compare, add, the other add under its mask, min), plus the three adds that change the
+// step's streaming values.  kPeakStep lane-instructions per step.
+constexpr double kPeakStep = 8 * 4 + 3;
 __global__ void __launch_bounds__(256) k_valu_peak_f64(double *sink, int iters, double a, double b) {
     double bb2[8], bbt[8], btm[8], acc[8];
 #pragma unroll
@@ -1947,14 +1948,12 @@ __global__ void __launch_bounds__(256) k_valu_peak_f64(double *sink, int iters, 
         bb2[i] = a * (threadIdx.x + i); bbt[i] = b * (threadIdx.x + 2 * i); btm[i] = a * b * (3 * i + (threadIdx.x & 7));
         acc[i] = 1e300;
     }
-    double px = a, py = b, atm = a + b;
+    double2 p = make_double2(a, b);
+    double atm = a + b;
     for (int it = 0; it < iters; ++it) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const double T = atm >= btm[i] ? px + bb2[i] : py + bbt[i];
-            acc[i] = fmin(acc[i], T);
-        }
-        px += a; py += b; atm += a;
+        four_candidates<false>(acc[0], acc[1], acc[2], acc[3], bb2, bbt, btm, p, atm);
+        four_candidates<false>(acc[4], acc[5], acc[6], acc[7], bb2 + 4, bbt + 4, btm + 4, p, atm);
+        p.x += a; p.y += b; atm += a;
     }
     double r = 0.0;
 #pragma unroll
@@ -2046,8 +2045,8 @@ extern "C" int oob_plan_export_block(oob_plan *h, int S, int delta, double *T, d
 }
 
 // Measured vector-ALU peak of this GPU in lane-operations per second, for comparison with the nominal
-// 256 CUs x 64 lanes x clock: 32-bit add / compare / select (f64_mix = 0) or the fp64 instruction mix
-// of a candidate of the split kernels (f64_mix = 1).
+// 256 CUs x 64 lanes x clock: 32-bit add / compare / select (f64_mix = 0) or the fp64 instructions of a
+// candidate of the keyed split kernel (f64_mix = 1).
 static int valu_peak(oob_plan *h, void *stream, double *lane_ops_per_s, int f64_mix) {
     if (!h || !lane_ops_per_s) return OOB_EINVAL;
     hipStream_t st = (hipStream_t)stream;
@@ -2067,7 +2066,7 @@ static int valu_peak(oob_plan *h, void *stream, double *lane_ops_per_s, int f64_
     OOB_HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    *lane_ops_per_s = (double)grid * 256 * (f64_mix ? 51.0 : 16.0 * 3) * iters / (ms * 1e-3);
+    *lane_ops_per_s = (double)grid * 256 * (f64_mix ? kPeakStep : 16.0 * 3) * iters / (ms * 1e-3);
     return OOB_OK;
 }
 extern "C" int oob_plan_valu_peak(oob_plan *h, void *stream, double *lane_ops_per_s) {
