@@ -66,7 +66,6 @@ struct Tables {
     double *partT;        // [(S'-1) * deltas * tiles * 64] per-split minima of the current level
     unsigned long long *key; // the same memory: [deltas * tiles * 64] keys of the current level (keyed kernel)
     int *partK;           // same shape: first k reaching the minimum
-    int *stack;           // backtracking stacks / coverage ring
     int2 *seg_tab;        // per level: (tile | split points << 16, ub | vb << 8 | offset of the first one << 16) of every split task
     int seg_stride;       // entries reserved per level in seg_tab (level S' starts at (S'-2) * seg_stride)
     int *flags;           // [0] 1: (total, k) keys fit a double and k_split_key runs
@@ -1339,7 +1338,7 @@ long long part_slots(int L, int M, int n_max, int Nb) {
 }
 
 struct Carve {
-    size_t lvl_tab, lvl_dir, rec, kstar, choice, partT, partK, stack, flags, seg_tab, total;
+    size_t lvl_tab, lvl_dir, rec, kstar, choice, partT, partK, flags, seg_tab, total;
     long long recs, slots;
 };
 // Byte offsets of the workspace arrays, sized for the handle's maxima.
@@ -1358,7 +1357,6 @@ Carve carve(int L, int nodes, int M) {
     // two buffers of minima: consecutive levels are evaluated side by side (see oob_plan_templates)
     c.partT = o;   o = align_up(o + 2 * sizeof(double) * (size_t)c.slots * 64);
     c.partK = o;   o = align_up(o + sizeof(int) * (size_t)c.slots * 64); // plain kernel only: one stream
-    c.stack = o;   o = align_up(o + sizeof(int) * ((size_t)nodes * (Smax + 1) * 4 + nodes + 2));
     c.flags = o;   o = align_up(o + sizeof(int) * 64);
     // the task list of a level is longest at S' = 2; every level gets that many entries
     c.seg_tab = o; o = align_up(o + sizeof(int2) * ((size_t)imax(Smax - 1, 1) * seg_count_bound(L) + 1));
@@ -1423,7 +1421,6 @@ bool plan_split(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     return true;
 }
 
-// Launch shape of k_split_key for one family of one level.
 int env_or(const char *name, int dflt) {
     const char *v = getenv(name);
     return v && *v ? atoi(v) : dflt;
@@ -1446,6 +1443,7 @@ constexpr int kSelect8From = 82, kFuseFrom = 82;
 constexpr int kSmallState = 640, kSmallLevel = 500000;
 constexpr int kOverlapFrom = 24000; // thousand candidates of a level: see enqueue_job
 constexpr int kSelLanes = 1; // lanes per state below that
+// Launch shape of k_split_key for one family of one level; waves and LDS follow per launch (key_waves, key_lds).
 bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
     target_units(fam, Sp, sh.M, sh.n_max, &t_lo, &t_hi);
@@ -1470,7 +1468,6 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     }
     p->ntab = ntab;
     p->na = imin(cnt, kKeyTargets);
-    p->lds = 0; p->pc = 0; p->waves = 0; // by launch, see launch_split_key
     return true;
 }
 
@@ -1617,7 +1614,6 @@ static Tables make_tables(const oob_plan *h, int lane, const Shape &sh, int *sta
     t.partT = (double *)(ws + h->cv.partT);
     t.key = (unsigned long long *)(ws + h->cv.partT);
     t.partK = (int *)(ws + h->cv.partK);
-    t.stack = (int *)(ws + h->cv.stack);
     t.flags = (int *)(ws + h->cv.flags);
     t.seg_tab = (int2 *)(ws + h->cv.seg_tab);
     t.seg_stride = seg_count_bound(sh.L);
