@@ -663,7 +663,7 @@ __global__ void __launch_bounds__(kFilterThreads) k_exact_filter(Args a) {
 // ---------------------------------------------------------------------------------------------
 // Exact evaluation.  Bound by chains of dependent LDS reads on the rows of the one-node tables; at 8 GPUs per node 47 % of the LDS cycles
 // are bank conflicts (neighbouring lanes read rows 64 bytes apart) and 30 registers of k_exact_eval<false, 8> are spilled: 29 MB of scratch
-// written per launch.  173 us for the first picks and 290-340 us for the rest at 98 layers x 8 GPUs (430 us with buckets of 64; the version before, without a band and
+// written per launch.  150-167 us for the first picks and 350-460 us for the rest at 98 layers x 8 GPUs (the version before, without a band and
 // evaluating everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table
 // entry: 1, or S_max + 1 (STAGED).
 // ---------------------------------------------------------------------------------------------

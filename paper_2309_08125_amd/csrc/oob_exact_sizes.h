@@ -90,7 +90,9 @@ constexpr int kBucket = 64; // entries whose bounds a workgroup holds at a time
 constexpr int kMaxCount = 64;        // templates per job that the bounds are kept for
 constexpr int kLambdas = 8, kMus = 8;
 // Least entries per bucket (more only where that would exceed kMaxBuckets).  With the lambdas alone a smaller bucket pays:
-// its bounds are tighter and the workgroups of 64 leave compute units idle (98 layers x 8 GPUs 880 -> 760 us, 16: 759 us).
+// its bounds are tighter and the workgroups of 64 leave compute units idle.  How much hangs on the instance (which
+// stages are evaluated): timed in turn, 32 against 64, 24 jobs of 34-97 layers 0.93 of the time (0.53 to 1.17), eight of 98
+// layers x 8 GPUs 0.97 (0.83 to 1.09); the bounds themselves take 212 instead of 170 us there.
 // With eight mus the bounds are a quarter of the time and it does not (48 layers, limit binding: 3.05 and 3.30 ms).
 OOB_HD inline int bucket_least(int multipliers) { return multipliers > kLambdas ? 64 : 32; }
 
