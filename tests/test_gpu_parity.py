@@ -274,6 +274,38 @@ def test_call_can_be_captured_into_a_graph_and_replayed(P, fork):
     planner.close()
 
 
+def test_capture_with_launches_beyond_64_kb_of_lds(P):
+    """Sixty nodes: launches of up to 67 KB of LDS, which the library announces to the runtime in the captured call itself.
+    Replays with eager work in between give what the plain split kernel gives."""
+    import torch
+
+    inp = inputs.random_small(67, 60, 8, 1, 60, 0, f=2)
+    planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+    planner.set_option(P.OOB_OPT_PLAIN_SPLIT, 1)
+    want = planner.plan(inp)
+    planner.set_option(P.OOB_OPT_PLAIN_SPLIT, 0)
+    planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
+    planner.set_option(P.OOB_OPT_OVERLAP_FROM, 1000)
+    prof = P.DeviceProfile(inp)
+    out = planner.new_outputs(inp)
+    planner.plan(inp)
+    flags = planner.flags()
+    assert flags[:3] == [1, 0, 0] and flags[3] > 0
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        planner.enqueue(prof, out)
+    for i in range(3):
+        say(f"replay {i}")
+        out.base.zero_()
+        torch.randn(1 << 20, device="cuda").sum().item()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.to_host()
+        for k in want:
+            assert np.array_equal(got[k], want[k]), (i, k)
+    planner.close()
+
+
 def test_device_status_reports_bad_profile_values(P):
     import torch
 
