@@ -15,10 +15,20 @@
 // (x pipelines; Cauchy-Schwarz): the closer the times, the shorter the path.
 //
 // Pipelines of one template have the same T and stay within one microbatch of each other, so the
-// state of a plan is one total per template in use (at most 16), kept in LDS with one column
-// per lane (192 bytes a lane; the templates' times are one table per workgroup); a template's
+// state of a plan is one total per template in use (at most 16); a template's
 // donor is one of its fullest pipelines, its receiver one of its emptiest.  Products reach
 // 2^124: all exact arithmetic is in 128-bit integers.
+//
+// Three forms of the same solution.  Of the plans of a node specification one in sixty has an exchange on its path at all: whether
+// there is one is decided from the templates one by one (solve_in_registers), and the others are done after one allocation.  The
+// few with a path wait until a wave is full of them; solve_general, in LDS and slow, keeps the plans of more than kFast
+// templates and the comparisons that doubles leave open.
+//
+// What bounds it: the vector ALUs (3 300 instructions a wave for 57 templates, two fifths of them for reading the counts and writing the
+// distribution) and, for plans with a path, waves of a few lanes that wait for memory.  1 343 380 plans of up to 57 templates, 512
+// microbatches: 521 us with solve_general for every plan, 172 us for the first launch and 85 us for the second here (the walkers followed
+// at the end of each wave's share 350 us; with all 57 counts of a walker read once more, and written, 172 and 170 us); 10 251 plans of
+// 29 templates 41 -> 27 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -30,9 +40,17 @@
 namespace oob_dist {
 
 typedef __int128 i128;
-constexpr int kLanes = 64; // plans per workgroup: a few thousand plans already reach every compute unit
-constexpr int kLoads = 8;  // counts of a plan in flight while its templates are listed
+constexpr int kLanes = 64;  // plans side by side in a wave
+constexpr int kLoads = 16;  // counts of a plan in flight while its templates are listed
 constexpr int kT = OOB_DIST_MAX_TEMPLATES_IN_PLAN;
+constexpr int kGeneral = 32; // lanes of a wave that solve_general uses: half of them leave room in LDS for more waves
+constexpr int kFirstThreads = 256;
+// Plans that a wave of the second launch looks through: some sixteen of them have a path.  512, 1 024, 2 048: 288, 283, 316 us
+// for the whole call with the choice (1 343 380 plans).
+constexpr int kSpanBits = 10, kSpan = 1 << kSpanBits;
+// Plans up to which one launch does it all, each wave 64 plans with their paths: as many as the GPU holds at once.  What counts
+// there is how long one wave takes (10 251 plans: 27 us, 15 + 33 us in two launches).
+constexpr long long kOnce = 3072 * 64;
 constexpr long long kMaxExchanges = 1ll << 24; // never reached (at most Q exchanges per template): every lane's loop ends
 
 struct Args {
@@ -47,24 +65,24 @@ struct Args {
     int *status;
 };
 
-// One plan's state: column `lane` of arrays [kT][kLanes].  Template k of the plan has x pipelines;
+// One plan's state: column `lane` of arrays [kT][kGeneral].  Template k of the plan has x pipelines;
 // e of them hold n + 1 microbatches, the others n (0 <= e < x): no division in the loops.
 struct Plan {
     const double *tT;              // the workgroup's copy of the templates' times per microbatch (integers: exact)
     unsigned short *j, *x, *n, *e; // template index; pipelines; see above
     int t, xs;                     // templates in use; pipelines in all
-    __device__ double Td(int k) const { return tT[j[k * kLanes]]; }
+    __device__ double Td(int k) const { return tT[j[k * kGeneral]]; }
     __device__ long long Tk(int k) const { return (long long)Td(k); }
-    __device__ int xk(int k) const { return x[k * kLanes]; }
-    __device__ int fullest(int k) const { return n[k * kLanes] + (e[k * kLanes] > 0); } // microbatches of a fullest pipeline
-    __device__ int emptiest(int k) const { return n[k * kLanes]; }
+    __device__ int xk(int k) const { return x[k * kGeneral]; }
+    __device__ int fullest(int k) const { return n[k * kGeneral] + (e[k * kGeneral] > 0); } // microbatches of a fullest pipeline
+    __device__ int emptiest(int k) const { return n[k * kGeneral]; }
     __device__ void take(int k) const { // one microbatch less for a fullest pipeline
-        if (e[k * kLanes] > 0) e[k * kLanes] -= 1;
-        else { n[k * kLanes] -= 1; e[k * kLanes] = (unsigned short)(xk(k) - 1); }
+        if (e[k * kGeneral] > 0) e[k * kGeneral] -= 1;
+        else { n[k * kGeneral] -= 1; e[k * kGeneral] = (unsigned short)(xk(k) - 1); }
     }
     __device__ void give(int k) const { // one more for an emptiest pipeline
-        if (e[k * kLanes] + 1 == xk(k)) { n[k * kLanes] += 1; e[k * kLanes] = 0; }
-        else e[k * kLanes] += 1;
+        if (e[k * kGeneral] + 1 == xk(k)) { n[k * kGeneral] += 1; e[k * kGeneral] = 0; }
+        else e[k * kGeneral] += 1;
     }
 };
 
@@ -73,6 +91,7 @@ struct Plan {
 // instruction; random times leave about one comparison in 10^8 to the exact form).  kEps bounds the rounding of a sum of
 // two products of three factors relative to the sum of their magnitudes (five roundings of 2^-53, doubled).
 constexpr double kEps = 1.0 / (1ll << 49);
+constexpr double kHuge = __builtin_huge_val();
 
 // The optimum of the fixed-level problem at the integer level mu >= 0.
 __device__ void allocate_at(const Plan &pl, long long mu, int Q) {
@@ -84,8 +103,8 @@ __device__ void allocate_at(const Plan &pl, long long mu, int Q) {
         n += (n + 1) * (2 * T) <= num;
         if (n < 1) n = 1;
         if (n > Q) n = Q;
-        pl.n[k * kLanes] = (unsigned short)n;
-        pl.e[k * kLanes] = 0;
+        pl.n[k * kGeneral] = (unsigned short)n;
+        pl.e[k * kGeneral] = 0;
         tot += n * pl.xk(k);
     }
     // cost of one microbatch more or less for a pipeline of T that counts as m (odd, its sign that of the change):
@@ -116,7 +135,7 @@ __device__ void sums(const Plan &pl, i128 *S1, i128 *S2) {
     i128 s1 = 0, s2 = 0;
     for (int k = 0; k < pl.t; ++k) {
         const i128 T = pl.Tk(k);
-        const int n = pl.n[k * kLanes], e = pl.e[k * kLanes]; // e pipelines hold n + 1, the others n
+        const int n = pl.n[k * kGeneral], e = pl.e[k * kGeneral]; // e pipelines hold n + 1, the others n
         const i128 lo = T * n, hi = T * (n + 1);
         s1 += lo * (pl.xk(k) - e) + hi * e;
         s2 += lo * lo * (pl.xk(k) - e) + hi * hi * e;
@@ -135,21 +154,17 @@ __device__ bool exact_less(const Plan &pl, int d, int r, int bd, int br) {
 }
 __device__ bool level_above(const Plan &pl, int d, int r, i128 mu) { return exchange_c(pl, d, r) > exchange_w(pl, d, r) * mu; }
 
-// What bounds it: the vector ALUs, on chains of LDS reads at three waves per SIMD; the bytes of a plan (6 p + 28) would
-// take a fifth of the time.  1 343 380 plans of up to 57 templates, 512 microbatches: 1.24 -> 0.49 ms by the shorter path,
-// comparisons in doubles, counts read eight at a time and every entry of base and extra written once.
-__global__ void __launch_bounds__(kLanes) k_dist_solve(Args a) {
-    HIP_DYNAMIC_SHARED(double, s_tT) // [p]
-    __shared__ unsigned short s_x[kT * kLanes], s_j[kT * kLanes], s_n[kT * kLanes], s_e[kT * kLanes];
-    __shared__ unsigned short s_bn[kT * kLanes], s_be[kT * kLanes]; // the best allocation met so far
-    const int lane = threadIdx.x;
-    for (int j = lane; j < a.p; j += kLanes) s_tT[j] = (double)a.tT[j]; // exact where it is used (up to 2^35)
-    __syncthreads();
-    const long long i = (long long)blockIdx.x * kLanes + lane;
-    if (i >= a.count) return;
+// The arrays of one wave's plans in LDS.
+struct General {
+    unsigned short x[kT * kGeneral], j[kT * kGeneral], n[kT * kGeneral], e[kT * kGeneral];
+    unsigned short bn[kT * kGeneral], be[kT * kGeneral]; // the best allocation met so far
+};
+
+// Plan i by one lane, whatever its templates and its path.
+__device__ void solve_general(const Args &a, const double *s_tT, General &g, long long i, int lane) {
     Plan pl;
-    pl.tT = s_tT; pl.j = s_j + lane; pl.x = s_x + lane; pl.n = s_n + lane; pl.e = s_e + lane;
-    unsigned short *bn = s_bn + lane, *be = s_be + lane, *tj = s_j + lane;
+    pl.tT = s_tT; pl.j = g.j + lane; pl.x = g.x + lane; pl.n = g.n + lane; pl.e = g.e + lane;
+    unsigned short *bn = g.bn + lane, *be = g.be + lane, *tj = g.j + lane;
 
     // the templates in use
     int t = 0, xs = 0, st = OOB_DIST_OK;
@@ -163,7 +178,7 @@ __global__ void __launch_bounds__(kLanes) k_dist_solve(Args a) {
             const double T = s_tT[j0 + q]; // a time beyond 2^53 is rounded, and refused all the same
             if (t == kT) { st = OOB_DIST_TOO_MANY_TEMPLATES; continue; }
             if (T < 1 || T > (double)OOB_DIST_MAX_T) { st = OOB_DIST_BAD_TIME; continue; }
-            pl.x[t * kLanes] = (unsigned short)c[q]; tj[t * kLanes] = (unsigned short)(j0 + q);
+            pl.x[t * kGeneral] = (unsigned short)c[q]; tj[t * kGeneral] = (unsigned short)(j0 + q);
             xs += c[q];
             ++t;
         }
@@ -210,7 +225,7 @@ __global__ void __launch_bounds__(kLanes) k_dist_solve(Args a) {
     allocate_at(pl, mu_lo, a.Q);
     sums(pl, &S1, &S2);
     i128 best = (i128)xs * S2 - S1 * S1;
-    for (int k = 0; k < t; ++k) { bn[k * kLanes] = pl.n[k * kLanes]; be[k * kLanes] = pl.e[k * kLanes]; }
+    for (int k = 0; k < t; ++k) { bn[k * kGeneral] = pl.n[k * kGeneral]; be[k * kGeneral] = pl.e[k * kGeneral]; }
     for (long long step = 0; step < kMaxExchanges; ++step) {
         // the next exchange: a microbatch of a fullest pipeline of template d (n_d of them) goes to an emptiest
         // pipeline of a slower template r (n_r): it pays from the level c / w on,
@@ -242,13 +257,13 @@ __global__ void __launch_bounds__(kLanes) k_dist_solve(Args a) {
         const i128 v = (i128)xs * S2 - S1 * S1;
         if (v < best) {
             best = v;
-            for (int k = 0; k < t; ++k) { bn[k * kLanes] = pl.n[k * kLanes]; be[k * kLanes] = pl.e[k * kLanes]; }
+            for (int k = 0; k < t; ++k) { bn[k * kGeneral] = pl.n[k * kGeneral]; be[k * kGeneral] = pl.e[k * kGeneral]; }
         }
     }
 
     long long slow = 0;
     for (int k = 0; k < t; ++k) {
-        const long long time = (long long)(bn[k * kLanes] + (be[k * kLanes] > 0)) * pl.Tk(k);
+        const long long time = (long long)(bn[k * kGeneral] + (be[k * kGeneral] > 0)) * pl.Tk(k);
         slow = time > slow ? time : slow;
     }
     if (a.base) { // every entry written once
@@ -256,9 +271,9 @@ __global__ void __launch_bounds__(kLanes) k_dist_solve(Args a) {
         for (int j = 0; j < a.p; ++j) {
             unsigned short n = 0, e = 0;
             if (j == next) {
-                n = bn[k * kLanes]; e = be[k * kLanes];
+                n = bn[k * kGeneral]; e = be[k * kGeneral];
                 ++k;
-                next = k < t ? tj[k * kLanes] : -1;
+                next = k < t ? tj[k * kGeneral] : -1;
             }
             a.base[(long long)j * a.capacity + i] = n;
             a.extra[(long long)j * a.capacity + i] = e;
@@ -267,6 +282,342 @@ __global__ void __launch_bounds__(kLanes) k_dist_solve(Args a) {
     a.vx[2 * i] = (unsigned long long)best;
     a.vx[2 * i + 1] = (unsigned long long)(best >> 64);
     a.slowest[i] = slow;
+}
+
+// Plan i by one lane with its templates in registers: the same method and the same order of comparisons as
+// solve_general, for plans of at most kFast templates.  kHard: a plan of more, one that cannot be solved, or a comparison
+// that needs the exact form; solve_general takes it.
+//
+// Mostly no exchange lies on the stretch, and then nothing has to be searched.  A distribution is the only optimum at a level mu if every
+// exchange of a microbatch between two templates costs: taking one from a fullest pipeline of d adds A = T_d^2 (1 - 2 n_d) + 2
+// T_d mu, giving it to an emptiest one of r B = T_r^2 (1 + 2 n_r) - 2 T_r mu, and A + B > 0 for all d != r (the problem is
+// separable and convex: a strict minimum among its neighbours is the minimum).  Where that holds for the distribution of the
+// stretch's middle at both ends of the stretch, the path starts with it and has no exchange on the stretch (A + B <= 0 is what makes
+// one pay).  Otherwise the path is followed with FOLLOW = true; FOLLOW = false returns kLeft.
+constexpr int kFast = 10;
+constexpr int kDone = 0, kLeft = 1, kHard = 2;
+struct Listed { unsigned jx[kFast * kLanes], best[kFast * kLanes]; }; // template | pipelines << 16; n | e << 16 (as in Plan)
+struct Walked { Listed ls; unsigned ne[kFast * kLanes]; };
+
+// FOLLOW = false hands the list of the plan's templates over where the plan stays open: rows 0 .. t-1 of its column of base and extra hold
+// them, *listed becomes t.  FOLLOW = true takes it from there if *listed is not 0.
+template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const double *s_tT, Listed &ls, unsigned *ne, long long i, int lane, int *listed) {
+    unsigned *const jx = ls.jx + lane, *const best_ne = ls.best + lane;
+    int t = 0, xs = 0;
+    if (FOLLOW && *listed) {
+        t = *listed;
+        unsigned w[kFast];
+#pragma unroll
+        for (int k = 0; k < kFast; ++k) w[k] = k < t ? (unsigned)a.base[k * a.capacity + i] | (unsigned)a.extra[k * a.capacity + i] << 16 : 0;
+#pragma unroll
+        for (int k = 0; k < kFast; ++k) {
+            jx[k * kLanes] = w[k];
+            xs += (int)(w[k] >> 16);
+        }
+    } else {
+        for (int j0 = 0; j0 < a.p; j0 += kLoads) {
+            int c[kLoads];
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) c[q] = j0 + q < a.p ? a.x[(long long)(j0 + q) * a.capacity + i] : 0;
+#pragma unroll
+            for (int q = 0; q < kLoads; ++q) {
+                if (!c[q]) continue;
+                if (t < kFast) jx[t * kLanes] = (unsigned)(j0 + q) | (unsigned)c[q] << 16;
+                xs += c[q];
+                ++t;
+            }
+        }
+        if (t == 0 || t > kFast || xs > a.Q) return kHard;
+    }
+    double T[kFast];
+    int x[kFast], n[kFast], e[kFast];
+    auto inverse = [&](int k) { return s_tT[a.p + (jx[k * kLanes] & 0xffff)]; }; // read again where it is used: registers decide how
+                                                                                 // many waves run
+    bool ok = true, twins = false;
+    double H = 0;
+#pragma unroll
+    for (int k = 0; k < kFast; ++k) {
+        T[k] = 1; x[k] = n[k] = e[k] = 0;
+        if (k < t) {
+            const unsigned w = jx[k * kLanes];
+            T[k] = s_tT[w & 0xffff]; x[k] = (int)(w >> 16);
+            ok &= T[k] >= 1 && T[k] <= (double)OOB_DIST_MAX_T;
+            H += (double)x[k] * inverse(k);
+#pragma unroll
+            for (int l = 0; l < k; ++l) twins |= T[l] == T[k];
+        }
+    }
+    if (!ok) return kHard;
+    const double mean = H / xs, L0 = (double)a.Q / H;
+    double D = 0;
+#pragma unroll
+    for (int k = 0; k < kFast; ++k)
+        if (k < t) {
+            const double r = inverse(k) - mean;
+            D += r * r * x[k];
+        }
+
+    // every exchange costs at level mu (see above)
+    auto settled = [&](double mu) {
+        const double m2 = 2.0 * mu;
+        double a1 = kHuge, a2 = kHuge, b1 = kHuge, b2 = kHuge; // smallest and second smallest A and B, less their rounding
+        int ai = -1, bi = -1;
+#pragma unroll
+        for (int k = 0; k < kFast; ++k)
+            if (k < t) {
+                const int full = n[k] + (e[k] > 0);
+                const double sq = T[k] * T[k], q = T[k] * m2, pa = sq * (2 * full - 1), pb = sq * (2 * n[k] + 1);
+                const double A = full < 2 ? kHuge : (q - pa) - (q + pa) * kEps, B = (pb - q) - (pb + q) * kEps;
+                a2 = fmin(a2, fmax(a1, A));
+                ai = A < a1 ? k : ai;
+                a1 = fmin(a1, A);
+                b2 = fmin(b2, fmax(b1, B));
+                bi = B < b1 ? k : bi;
+                b1 = fmin(b1, B);
+            }
+        return (ai != bi ? a1 + b1 : fmin(a1 + b2, a2 + b1)) > 0.0;
+    };
+    long long mu = (long long)(L0 + 0.5), mu_hi = 0;
+    long long S1; // below 2^51
+    i128 S2, best;
+    bool walk = false, open = false;
+    for (;;) { // at the middle of the stretch, then (walk) at its lower end
+#pragma unroll
+        for (int k = 0; k < kFast; ++k) asm volatile("" : "+v"(T[k])); // products of the times are formed here, not kept for the next round
+        // allocate_at
+        const double m2 = 2.0 * (double)mu;
+        int tot = 0;
+#pragma unroll
+        for (int k = 0; k < kFast; ++k)
+            if (k < t) {
+                const double num = m2 + T[k], two = 2.0 * T[k]; // integers below 2^53
+                double f = floor(num * (0.5 * inverse(k))); // nearest integer to mu / T, once corrected
+                f -= f * two > num ? 1.0 : 0.0;
+                f += (f + 1.0) * two <= num ? 1.0 : 0.0;
+                n[k] = (int)fmin(fmax(f, 1.0), (double)a.Q);
+                e[k] = 0;
+                tot += n[k] * x[k]; // mu is about Q / H at most, so n is at most Q / x + 2
+            }
+        if (tot != a.Q) {
+            const bool remove = tot > a.Q;
+            double c[kFast], most = 0; // what one microbatch less or more costs a template; what their rounding can come to
+#pragma unroll
+            for (int k = 0; k < kFast; ++k) {
+                c[k] = kHuge;
+                if (k < t) {
+                    const double sq = T[k] * T[k], q = T[k] * m2;
+                    if (remove) { if (n[k] >= 2) c[k] = q - sq * (2 * n[k] - 1); }
+                    else c[k] = sq * (2 * n[k] + 1) - q;
+                    most = fmax(most, 4.0 * kEps * (q + sq * (2 * n[k] + 1)));
+                }
+            }
+            for (;;) {
+                double c1 = kHuge, c2 = kHuge;
+#pragma unroll
+                for (int k = 0; k < kFast; ++k) {
+                    c2 = fmin(c2, fmax(c1, c[k]));
+                    c1 = fmin(c1, c[k]);
+                }
+                if (c1 >= kHuge || c2 - c1 <= most) return kHard; // (c1 is a cost: tot > Q >= pipelines, so some pipeline holds two)
+#pragma unroll
+                for (int k = 0; k < kFast; ++k) {
+                    if (c[k] != c1) continue;
+                    bool next; // the template's next pipeline starts over: another cost
+                    if (remove) { // Plan::take
+                        next = e[k] == 1 || x[k] == 1;
+                        if (e[k] > 0) --e[k];
+                        else { --n[k]; e[k] = x[k] - 1; }
+                    } else {      // Plan::give
+                        next = e[k] + 1 == x[k];
+                        if (next) { ++n[k]; e[k] = 0; }
+                        else ++e[k];
+                    }
+                    if (next) {
+                        double Tk = T[k];
+                        asm volatile("" : "+v"(Tk));
+                        c[k] = remove && n[k] < 2 ? kHuge : c[k] + 2.0 * Tk * Tk;
+                        most = fmax(most, 4.0 * kEps * (2.0 * (double)mu * Tk + Tk * Tk * (2 * n[k] + 1)));
+                    }
+                }
+                tot += remove ? -1 : 1;
+                if (tot == a.Q) break;
+            }
+        }
+        S1 = 0; S2 = 0;
+#pragma unroll
+        for (int k = 0; k < kFast; ++k)
+            if (k < t) {
+                const long long Tk = (long long)T[k];
+                const unsigned long long lo = (unsigned long long)n[k] * n[k], hi = (unsigned long long)(n[k] + 1) * (n[k] + 1);
+                S1 += Tk * ((long long)n[k] * x[k] + e[k]);
+                S2 += (i128)Tk * Tk * (long long)(lo * (x[k] - e[k]) + hi * e[k]);
+            }
+        best = (i128)xs * S2 - (i128)S1 * S1;
+        if (walk) break;
+        const double V = (double)best / (double)xs; // sum of squared deviations of a feasible allocation
+        const double narrow = twins ? 1.0 : fmin(sqrt(D) / H, 1.0);
+        const double R = sqrt(V) * (narrow * (1.0 + 1e-9) + 1e-12) + L0 * 1e-9 + 2.0;
+        mu = L0 - R > 0 ? (long long)(L0 - R) : 0;
+        mu_hi = (long long)(L0 + R) + 1;
+        bool only = true; // one end after the other: together they take more registers than the kernel has
+#pragma unroll 1
+        for (int side = 0; side < 2; ++side) only &= settled(side ? (double)mu_hi : (double)mu);
+        if (only) break;
+        if (!FOLLOW) { open = true; break; }
+        walk = true;
+    }
+#pragma unroll
+    for (int k = 0; k < kFast; ++k)
+        if (k < t) best_ne[k * kLanes] = (unsigned)n[k] | (unsigned)e[k] << 16;
+    if constexpr (FOLLOW) {
+        ne += lane; // the allocation once more in LDS, for the templates that give
+#pragma unroll
+        for (int k = 0; k < kFast; ++k)
+            if (walk && k < t) ne[k * kLanes] = (unsigned)n[k] | (unsigned)e[k] << 16;
+        while (walk && !settled((double)mu_hi)) {
+            int bd = -1, br = -1; // the next exchange, see solve_general
+            double bc = 0, be = 0, bw = 1;
+            for (int d = 0; d < t; ++d) {
+                const unsigned wd = ne[d * kLanes];
+                const int nd = (int)(wd & 0xffff) + (wd >> 16 ? 1 : 0);
+                const double Td = s_tT[jx[d * kLanes] & 0xffff], cd = Td * Td * (1 - 2 * nd);
+                if (nd < 2) continue;
+#pragma unroll
+                for (int r = 0; r < kFast; ++r) {
+                    const double Tr = T[r];
+                    if (r >= t || Tr <= Td) continue;
+                    const double cr = Tr * Tr * (1 + 2 * n[r]), c = cd + cr, w = 2.0 * (Tr - Td); // w exact
+                    const double err = (cr - cd) * kEps, diff = c * bw - bc * w;
+                    ok &= bd < 0 || fabs(diff) > 2.0 * (err * bw + be * w);
+                    if (bd < 0 || diff < 0) { bc = c; be = err; bw = w; bd = d; br = r; }
+                }
+            }
+            if (!ok) return kHard;
+            if (bd < 0) break;
+            const unsigned xd = jx[bd * kLanes], xr = jx[br * kLanes];
+            const long long Td = (long long)s_tT[xd & 0xffff], Tr = (long long)s_tT[xr & 0xffff];
+            unsigned wd = ne[bd * kLanes], wr = ne[br * kLanes];
+            const int nd = (int)(wd & 0xffff) + (wd >> 16 ? 1 : 0), nr = (int)(wr & 0xffff);
+            const i128 change = (i128)Tr * Tr * (2 * nr + 1) - (i128)Td * Td * (2 * nd - 1);
+            if (change > (i128)(2 * (Tr - Td)) * mu_hi) break; // past the stretch
+            S1 += Tr - Td;
+            S2 += change;
+            wd = wd >> 16 ? wd - 0x10000u : (wd - 1) | ((xd >> 16) - 1) << 16;   // Plan::take
+            wr = (wr >> 16) + 1 == xr >> 16 ? (wr & 0xffff) + 1 : wr + 0x10000u; // Plan::give
+            ne[bd * kLanes] = wd;
+            ne[br * kLanes] = wr;
+#pragma unroll
+            for (int k = 0; k < kFast; ++k) {
+                if (k == bd) { n[k] = (int)(wd & 0xffff); e[k] = (int)(wd >> 16); }
+                if (k == br) { n[k] = (int)(wr & 0xffff); e[k] = (int)(wr >> 16); }
+            }
+            const i128 v = (i128)xs * S2 - (i128)S1 * S1;
+            if (v < best) {
+                best = v;
+                for (int k = 0; k < t; ++k) best_ne[k * kLanes] = ne[k * kLanes];
+            }
+        }
+    }
+    long long slow = 0;
+    for (int k = 0; k < t; ++k) {
+        const unsigned w = best_ne[k * kLanes];
+        const long long time = (long long)((w & 0xffff) + (w >> 16 ? 1 : 0)) * (long long)s_tT[jx[k * kLanes] & 0xffff];
+        slow = time > slow ? time : slow;
+    }
+    if (FOLLOW && *listed) { // the other entries are zeros
+        for (int k = 0; k < t; ++k) a.base[k * a.capacity + i] = a.extra[k * a.capacity + i] = 0;
+        for (int k = 0; k < t; ++k) {
+            const unsigned w = best_ne[k * kLanes];
+            const long long at = (long long)(jx[k * kLanes] & 0xffff) * a.capacity + i;
+            a.base[at] = (unsigned short)w;
+            a.extra[at] = (unsigned short)(w >> 16);
+        }
+    } else if (a.base) { // every entry written once
+        int k = 0;
+        unsigned next = open ? 0 : jx[0] & 0xffff, have = open ? jx[0] : best_ne[0];
+        for (int j = 0; j < a.p; ++j) {
+            unsigned w = 0;
+            if ((unsigned)j == next) {
+                w = have;
+                ++k;
+                const unsigned row = k < t ? jx[k * kLanes] : 0xffffu;
+                next = open && k < t ? (unsigned)k : row & 0xffff;
+                have = open ? row : k < t ? best_ne[k * kLanes] : 0;
+            }
+            a.base[(long long)j * a.capacity + i] = (unsigned short)w;
+            a.extra[(long long)j * a.capacity + i] = (unsigned short)(w >> 16);
+        }
+    }
+    if (!FOLLOW && open) {
+        *listed = t;
+        return kLeft;
+    }
+    a.status[i] = OOB_DIST_OK;
+    a.vx[2 * i] = (unsigned long long)best;
+    a.vx[2 * i + 1] = (unsigned long long)(best >> 64);
+    a.slowest[i] = slow;
+    return kDone;
+}
+
+__device__ __forceinline__ void load_times(const Args &a, double *s_tT) { // [p], then [p] reciprocals
+    for (int j = threadIdx.x; j < a.p; j += blockDim.x) {
+        const double T = (double)a.tT[j]; // exact where it is used (up to 2^35)
+        s_tT[j] = T;
+        s_tT[a.p + j] = 1.0 / T;
+    }
+    __syncthreads();
+}
+
+// The plans without an exchange on their stretch; the others are marked in `status`.
+constexpr int kMarked = 1 << 30; // and the templates that are listed (0: none)
+__global__ void __launch_bounds__(kFirstThreads, 4) k_dist_first(Args a) {
+    HIP_DYNAMIC_SHARED(double, s_tT)
+    __shared__ Listed s_listed[kFirstThreads / kLanes];
+    load_times(a, s_tT);
+    const long long i = (long long)blockIdx.x * kFirstThreads + threadIdx.x;
+    if (i >= a.count) return;
+    int listed = 0;
+    if (solve_in_registers<false>(a, s_tT, s_listed[threadIdx.x / kLanes], nullptr, i, threadIdx.x & (kLanes - 1), &listed) != kDone)
+        a.status[i] = kMarked + listed;
+}
+
+// The marked ones of `span` consecutive plans (all of them if marked = 0), side by side: those whose path can be followed in LDS, then
+// the hard ones.
+__global__ void __launch_bounds__(kLanes, 3) k_dist_rest(Args a, int span, int marked) {
+    HIP_DYNAMIC_SHARED(double, s_tT) // the times, then twice [span] 16-bit numbers of plans
+    __shared__ union { General general; Walked walked; } s;
+    unsigned short *const left = (unsigned short *)(s_tT + 2 * a.p), *const hard = left + span;
+    const int lane = threadIdx.x;
+    load_times(a, s_tT);
+    const long long i0 = (long long)blockIdx.x * span;
+    const unsigned long long below = (1ull << lane) - 1;
+    int nleft = 0, nhard = 0;
+    for (int o0 = 0; o0 < span; o0 += kLanes * kLoads) {
+        int st[kLoads];
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            const long long i = i0 + o0 + q * kLanes + lane;
+            st[q] = o0 + q * kLanes < span && i < a.count ? marked ? a.status[i] : kMarked : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            const unsigned long long m = __ballot(st[q] >= kMarked);
+            if (st[q] >= kMarked) left[nleft + __popcll(m & below)] = (unsigned short)((o0 + q * kLanes + lane) | (st[q] - kMarked) << kSpanBits);
+            nleft += __popcll(m);
+        }
+    }
+    __syncthreads();
+    for (int q = lane; q - lane < nleft; q += kLanes) {
+        const int w = q < nleft ? left[q] : 0, o = w & ((1 << kSpanBits) - 1);
+        int got = kDone, listed = a.base ? w >> kSpanBits : 0;
+        if (q < nleft) got = solve_in_registers<true>(a, s_tT, s.walked.ls, s.walked.ne, i0 + o, lane, &listed);
+        const unsigned long long m = __ballot(got == kHard);
+        if (got == kHard) hard[nhard + __popcll(m & below)] = (unsigned short)o;
+        nhard += __popcll(m);
+    }
+    __syncthreads();
+    if (lane < kGeneral)
+        for (int q = lane; q < nhard; q += kGeneral) solve_general(a, s_tT, s.general, i0 + hard[q], lane);
 }
 
 // Plan choice: the smallest `slowest` among the solved plans of a group, the first of equals.
@@ -342,12 +693,16 @@ extern "C" int oob_dist_solve(const uint16_t *x, int64_t count, int64_t capacity
     if (!x || !template_T || !vx || !slowest || !status || (base == nullptr) != (extra == nullptr)) return OOB_EINVAL;
     if (count < 0 || capacity < count || p < 1 || p > OOB_DIST_MAX_TEMPLATES || Q < 1 || Q > OOB_DIST_MAX_Q) return OOB_EINVAL;
     if (count == 0) return OOB_OK;
-    const long long blocks = (count + kLanes - 1) / kLanes;
-    if (blocks > 0x7fffffffll) return OOB_EINVAL;
+    if ((count + kLanes - 1) / kLanes > 0x7fffffffll) return OOB_EINVAL;
     Args a;
     a.x = x; a.count = count; a.capacity = capacity; a.p = p; a.tT = (const long long *)template_T; a.Q = Q;
     a.vx = (unsigned long long *)vx; a.slowest = (long long *)slowest; a.base = base; a.extra = extra; a.status = status;
-    hipLaunchKernelGGL(k_dist_solve, dim3((unsigned)blocks), dim3(kLanes), (size_t)p * sizeof(double), (hipStream_t)stream, a);
+    const bool twice = count > kOnce;
+    const int span = twice ? kSpan : kLanes;
+    const size_t times = 2 * (size_t)p * sizeof(double);
+    if (twice) hipLaunchKernelGGL(k_dist_first, dim3((unsigned)((count + kFirstThreads - 1) / kFirstThreads)), dim3(kFirstThreads), times, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(k_dist_rest, dim3((unsigned)((count + span - 1) / span)), dim3(kLanes), times + 2 * span * sizeof(unsigned short), (hipStream_t)stream, a, span,
+                       (int)twice);
     return hipGetLastError() == hipSuccess ? OOB_OK : OOB_EHIP;
 }
 

@@ -133,6 +133,35 @@ def test_status_codes_and_limits(P):
     assert P.oob_dist_solve(fake, 0, 0, 1, fake, 1, fake, fake, 0, 0, fake, 0) == P.OOB_OK        # nothing to do
 
 
+@pytest.mark.parametrize("Q,distribution", [(17, True), (40, True), (40, False), (300, True)])
+def test_many_plans_in_two_launches(P, Q, distribution):
+    """More plans than one launch takes (196 608): plans of 1 to 16 templates (registers hold ten), many of them with exchanges on
+    their path, twins, plans that cannot be solved, a ragged end and an odd capacity; the same plans in one launch are compared
+    with the oracle."""
+    rng = random.Random(Q)
+    tT = [rng.randint(10**9, 4 * 10**9) for _ in range(19)]
+    tT[7] = tT[3]
+    vecs = []
+    for i in range(160):
+        v = [0] * 19
+        for j in rng.sample(range(19), 1 + i % 16):
+            v[j] = rng.choice([1, 1, 1, 2, 3])
+        vecs.append(v)
+    vecs += [[0] * 19, [1] * 19]
+    assert sum(sum(v) > Q for v in vecs) > (10 if Q == 17 else -1)
+    few = vecs[:160]
+    compare(P, few, tT, Q, exhaustive=False)
+    want = P.Distributor(vecs, len(vecs), tT, Q).solve()
+    pick = np.random.Generator(np.random.PCG64(Q)).integers(0, len(vecs), size=196608 + 1024 + 65)
+    got = P.Distributor(np.asarray(vecs)[pick], len(pick), tT, Q, distribution=distribution).solve()
+    assert np.array_equal(got[0], want[0][pick]) and np.array_equal(got[2], want[2][pick])
+    assert got[1] == [want[1][i] for i in pick]
+    if distribution:
+        assert np.array_equal(got[3], want[3][pick]) and np.array_equal(got[4], want[4][pick])
+    else:
+        assert got[3] is None and got[4] is None
+
+
 def test_choice_of_the_plan_against_the_oracle(P):
     """Groups of plans as the enumeration produces them (one group per cluster size); cases in which
     every minimiser of a plan has the same slowest time, so that the choice is unique."""
