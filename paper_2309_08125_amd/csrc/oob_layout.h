@@ -42,6 +42,25 @@ __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ inline int dlo_of(int S, int M) { return S <= M ? S - 1 : M - 2 + cdiv(S, M); }
 __host__ __device__ inline int dhi_of(int S, int M, int n_max) { return M - 2 + imin(S, n_max); }
 
+// floor(k / M) by a product: exact for k < 2^14 and M <= 64 (k (inv M - 2^20) < 2^20).
+__host__ __device__ inline int inverse_of(int M) { return (1 << 20) / M + 1; }
+__host__ __device__ inline int over_M(int k, int inv_M) { return (int)((unsigned)k * (unsigned)inv_M >> 20); }
+
+// Where the tables of level S' start and which unit counts they have.  The levels' tables lie one after the other, level i has dhi - dlo + 1
+// of them (at least one up to Smax).  As a sum in closed form the kernels have it without reading memory, which each of them would wait
+// for at its start (61 layers 1 350 -> 1 325 us, read from an array before).
+struct Level {
+    int base; // table of device set delta is number base + delta
+    int least; // ceil(S' / M): fewest nodes of a state
+};
+__host__ __device__ inline Level level_of(int S, int M, int n_max, int inv_M) {
+    const int k = S - 1, q = over_M(k, inv_M), rest = k - q * M;                      // levels before; ceil(i / M) summed over them:
+    const int ceils = M * (q * (q + 1) / 2) + rest * (q + 1);
+    const int m = k < M ? k : M, mins = k <= n_max ? k * (k + 1) / 2 : n_max * (n_max + 1) / 2 + (k - n_max) * n_max; // min(i, n_max)
+    const int before = m * M - m * (m + 1) / 2 + mins + k - ceils;
+    return Level{before - (S <= M ? S - 1 : M - 2 + q + 1), q + 1};
+}
+
 __host__ __device__ inline int smax_of(int L, int n_max, int M, int Nb) {
     long long s = L;
     if ((long long)n_max * M < s) s = (long long)n_max * M;

@@ -59,8 +59,7 @@ struct Tables {
     int NB;               // blocks per side of the (u, v) plane
     int coff;             // column shift of the plane: v sits in block column (v + coff) / 8
     int tab_recs;         // records per table = tri_blocks(NB) * 64
-    long long *lvl_tab;   // [Smax+2] index of the first table of level S'
-    int2 *lvl_dir;        // [Smax+2] x: table of device set delta minus delta, y: ceil(S' / M)
+    int inv_M;            // over_M()
     Rec *rec;             // [tables * tab_recs]
     int *kstar, *choice;  // [tables * tab_recs]
     double *partT;        // [(S'-1) * deltas * tiles * 64] per-split minima of the current level
@@ -75,14 +74,13 @@ struct Tables {
     int *status;
 };
 
+__device__ __forceinline__ Level level(const Tables &t, int S) { return level_of(S, t.sh.M, t.sh.n_max, t.inv_M); }
 __device__ __forceinline__ long long rec_index(const Tables &t, int S, int delta, int u, int v) {
-    const long long tab = t.lvl_tab[S] + (delta - dlo_of(S, t.sh.M));
-    return tab * t.tab_recs + rec_off(u, v, t.coff, t.NB);
+    return (long long)(level(t, S).base + delta) * t.tab_recs + rec_off(u, v, t.coff, t.NB);
 }
 // First record of block (ub, vb) of that table.
 __device__ __forceinline__ long long rec_block(const Tables &t, int S, int delta, int ub, int vb) {
-    const long long tab = t.lvl_tab[S] + (delta - dlo_of(S, t.sh.M));
-    return tab * t.tab_recs + (long long)tri_index(ub, vb, t.NB) * 64;
+    return (long long)(level(t, S).base + delta) * t.tab_recs + (long long)tri_index(ub, vb, t.NB) * 64;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -102,12 +100,15 @@ __device__ __forceinline__ unsigned long long scan_sat(unsigned long long x, uns
     }
     return x;
 }
-__device__ __forceinline__ int scan_int(int x, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
+// Inclusive scan over the lanes of a whole wave by data-parallel moves (shifts within the rows of sixteen lanes, then the row sums
+// handed on): a tenth of the time of shuffles through LDS.
+__device__ __forceinline__ int scan_int(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
     return x;
 }
 
@@ -131,7 +132,7 @@ __device__ __forceinline__ unsigned long long scan_times(const oob_profile &prof
         if (x > capT) x = capT;
         x = scan_sat(x, capT, lane) + carry;
         if (x > capT) x = capT;
-        const int c = scan_int(fb ? 1 : 0, lane) + fcarry;
+        const int c = scan_int(fb ? 1 : 0) + fcarry;
         if (PT && in) { PT[l + 1] = (long long)x; PF[l + 1] = c; }
         carry = __shfl(x, 63, 64);
         fcarry = __shfl(c, 63, 64);
@@ -192,15 +193,6 @@ __device__ void setup_body(const Tables &t, const oob_profile &prof, int how) {
         if (lane == 0) s_worst[0] = (long long)cx;
     }
     if (bad) atomicMax(&s_bad, bad);
-    if (threadIdx.x == blockDim.x - 1) { // level offsets
-        long long tab = 0;
-        for (int S = 1; S <= t.sh.Smax + 1; ++S) {
-            t.lvl_tab[S] = tab;
-            t.lvl_dir[S] = make_int2((int)tab - dlo_of(S, M), cdiv(S, M));
-            const int nd = dhi_of(S, M, t.sh.n_max) - dlo_of(S, M) + 1;
-            if (S <= t.sh.Smax && nd > 0) tab += nd;
-        }
-    }
     __syncthreads();
     if (threadIdx.x == 0) {
         int st = OOB_OK, keys = 0;
@@ -309,7 +301,7 @@ __global__ void __launch_bounds__(512) k_split(Tables t, int Sp, int fam, int NT
             s_tm[dummy * TS + e] = 0.0;
         }
         const double cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r, cr = t.sh.Nb > 0 ? 0.0 : 4.0 * s;
-        const long long tabA = t.lvl_tab[s] - dlo_of(s, M) + fam_base, tabB = t.lvl_tab[r] - dlo_of(r, M) + fam_base;
+        const long long tabA = level(t, s).base + fam_base, tabB = level(t, r).base + fam_base;
         const int fillA = nA * TS, fill = (nA + nB) * TS;
         for (int kc = (kmin / PC) * PC; kc <= kmax; kc += PC) {
             __syncthreads(); // previous pass fully consumed
@@ -535,7 +527,7 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     HIP_DYNAMIC_SHARED(unsigned long long, s_acc)
     const int Sp = ka.Sp, s = ka.s0 + blockIdx.y * ka.sstep, r = Sp - s;
     const int2 sg = t.seg_tab[(long long)(Sp - 2) * t.seg_stride + (ka.xcd ? xcd_chunked(blockIdx.x, gridDim.x) : (int)blockIdx.x)];
-    const int2 dA = t.lvl_dir[s], dB = t.lvl_dir[r];
+    const Level dA = level(t, s), dB = level(t, r);
     if (t.flags[0] == 0) return;        // keys do not fit: k_select evaluates the candidates itself
     const int L = t.sh.L, M = t.sh.M, n_max = t.sh.n_max;
     // the wave index is the same in all lanes: say so, and everything derived from it (work item,
@@ -546,7 +538,7 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     const int fam_base = fam ? M - 2 : -1;
     const int a_g0 = (fam ? ka.t_lo1 : Sp) + zg * kKeyTargets, a_g1 = imin(fam ? imin(Sp, n_max) : M, a_g0 + kKeyTargets - 1);
     const int na = a_g1 - a_g0 + 1;
-    const int A_lo = fam ? dA.y : s, A_hi = fam ? imin(s, n_max) : M - 1, B_lo = fam ? dB.y : r, B_hi = fam ? imin(r, n_max) : M - 1;
+    const int A_lo = fam ? dA.least : s, A_hi = fam ? imin(s, n_max) : M - 1, B_lo = fam ? dB.least : r, B_hi = fam ? imin(r, n_max) : M - 1;
     const int mA0 = imax(A_lo, a_g0 - B_hi), mA1 = imin(A_hi, a_g1 - B_lo);
     const int mB0 = imax(B_lo, a_g0 - A_hi), mB1 = imin(B_hi, a_g1 - A_lo);
     const int vmax = tile_vmax(L, vb); // last layer position of the block's columns (never beyond L)
@@ -565,7 +557,7 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     // distance, and only the last eight tables of a side may not all exist (streaming: the last one again, stationary:
     // "no such state").
     const double cl = uniform(t.sh.Nb > 0 ? -(double)r : 3.0 * r), cr = uniform(t.sh.Nb > 0 ? 0.0 : 4.0 * s);
-    const long long tabA = (long long)(dA.x + fam_base + mA0) * t.tab_recs, tabB = (long long)(dB.x + fam_base + mB0) * t.tab_recs;
+    const long long tabA = (long long)(dA.base + fam_base + mA0) * t.tab_recs, tabB = (long long)(dB.base + fam_base + mB0) * t.tab_recs;
     const Rec *const recY = t.rec + (y_left ? tabA : tabB), *const recS = t.rec + (y_left ? tabB : tabA);
     const int lt = lane >> 3, li = lane & 7, shY = y_left ? 3 : 0, shS = y_left ? 0 : 3;
     auto off8 = [=](int sh, int top) { // lane's record of eight tables 0..top
@@ -848,8 +840,8 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
                 int mlo, mhi;
                 m_range(fam.fam, fam.units, s, r, M, t.sh.n_max, &mlo, &mhi);
                 const double cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r, cr = t.sh.Nb > 0 ? 0.0 : 4.0 * s;
-                const Rec *baseA = t.rec + (t.lvl_tab[s] - dlo_of(s, M) + fam.fam_base) * trecs;
-                const Rec *baseB = t.rec + (t.lvl_tab[r] - dlo_of(r, M) + fam.fam_base + fam.units) * trecs;
+                const Rec *baseA = t.rec + (level(t, s).base + fam.fam_base) * trecs;
+                const Rec *baseB = t.rec + (level(t, r).base + fam.fam_base + fam.units) * trecs;
                 for (int k = u + s; k <= v - r; ++k) {
                     const Rec *atA = baseA + rec_off(u, k, t.coff, t.NB), *atB = baseB + rec_off(k, v, t.coff, t.NB);
                     for (int m = mlo; m <= mhi; ++m) {
@@ -864,9 +856,9 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
         m_range(fam.fam, fam.units, bs, r, M, t.sh.n_max, &mlo, &mhi);
         const double cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r, cr = t.sh.Nb > 0 ? 0.0 : 4.0 * bs;
         // first m whose candidate equals the minimum; kSelPairs candidates' records in flight at a time
-        const long long tabA = (t.lvl_tab[bs] - dlo_of(bs, M) + fam.fam_base) * (long long)t.tab_recs +
+        const long long tabA = (long long)(level(t, bs).base + fam.fam_base) * t.tab_recs +
                                rec_off(u, bk, t.coff, t.NB);
-        const long long tabB = (t.lvl_tab[r] - dlo_of(r, M) + fam.fam_base + fam.units) * (long long)t.tab_recs +
+        const long long tabB = (long long)(level(t, r).base + fam.fam_base + fam.units) * t.tab_recs +
                                rec_off(bk, v, t.coff, t.NB);
         for (int m0 = mlo; m0 <= mhi && bm == 0; m0 += kSelPairs) {
             Rec ra[kSelPairs], rb[kSelPairs];
@@ -953,8 +945,8 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
             int mlo, mhi;
             m_range(fam.fam, fam.units, s, r, M, t.sh.n_max, &mlo, &mhi);
             const double cl = fixed_nb ? -(double)r : 3.0 * r, cr = fixed_nb ? 0.0 : 4.0 * s;
-            const Rec *baseA = t.rec + (t.lvl_tab[s] - dlo_of(s, M) + fam.fam_base) * trecs;
-            const Rec *baseB = t.rec + (t.lvl_tab[r] - dlo_of(r, M) + fam.fam_base + fam.units) * trecs;
+            const Rec *baseA = t.rec + (level(t, s).base + fam.fam_base) * trecs;
+            const Rec *baseB = t.rec + (level(t, r).base + fam.fam_base + fam.units) * trecs;
             for (int m = mlo; m <= mhi; ++m)
                 for (int j0 = sub; j0 < nk; j0 += LPS * kSel8Outer) {
                     Rec24 ra[kSel8Outer], rb[kSel8Outer];
@@ -1001,9 +993,9 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
         int mlo, mhi;
         m_range(fam.fam, fam.units, bs, r, M, t.sh.n_max, &mlo, &mhi);
         const double cl = fixed_nb ? -(double)r : 3.0 * r, cr = fixed_nb ? 0.0 : 4.0 * bs;
-        const Rec *baseA = t.rec + (t.lvl_tab[bs] - dlo_of(bs, M) + fam.fam_base) * trecs +
+        const Rec *baseA = t.rec + (level(t, bs).base + fam.fam_base) * trecs +
                            rec_off(u, bk, t.coff, t.NB);
-        const Rec *baseB = t.rec + (t.lvl_tab[r] - dlo_of(r, M) + fam.fam_base + fam.units) * trecs +
+        const Rec *baseB = t.rec + (level(t, r).base + fam.fam_base + fam.units) * trecs +
                            rec_off(bk, v, t.coff, t.NB);
         for (int m0 = mlo + sub; m0 - sub <= mhi && bm == 0; m0 += LPS * kSel8M) {
             Rec24 ra[kSel8M], rb[kSel8M];
@@ -1050,116 +1042,117 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
 }
 
 // ---------------------------------------------------------------------------------------
-// Levels S' >= 2, small levels: grid (block of the plane, delta, row of the block); one launch does the level.
+// Levels S' >= 2, small levels: grid (block of the plane, delta, part of the block); one launch does the level.
 //
-// A level of few candidates is bound by its launches and by the round trips to memory inside them, so splits and select are
-// one kernel without keys: a workgroup evaluates the eight states (u, v) of a row of a block, candidate by candidate
-// from the child records, 32 lanes a state.  The lanes of a wave are eight columns times eight consecutive split
-// points: the left records of a load are eight neighbours, the right ones eight rows of eight neighbours.
-// The (s, m) pairs of the device set are listed in LDS first; candidate i is pair i / nk, split point i % nk of the
-// widest state of the row (a narrower one reads "no such state" beyond its own).  Smallest (T, s, k, m) by comparison,
-// so the kernel does not depend on keys fitting a double.
+// A level of few candidates is bound by its launches and the chain inside them, so splits and select are
+// one kernel without keys: a workgroup evaluates C = 2^lgC neighbouring states (u, v) of a row of a block, candidate by candidate
+// from the child records, 256 / C lanes a state.  The lanes of a wave are C columns times 64 / C consecutive split
+// points.
+// The (s, m) pairs of the device set are listed in LDS first, beside the offsets of the split points' records; candidate i is
+// pair i / nk, split point i % nk of the widest state (a narrower one reads "no such state" beyond its own).
+// Smallest (T, s, k, m) by comparison, so the kernel does not depend on keys fitting a double.
+//
+// What bounds it: the workgroup with the most candidates a lane.  With 32 lanes for every state and the records' places formed from
+// scratch for each candidate (850 cycles each) the slowest workgroup took 23 000 cycles where the others took 10 000, whatever was in
+// flight (8 or 10 candidates a lane: no change); now 13 000 and 10 000, of them 1 100 for the list of pairs, 2 000 for the
+// children of the winner.  26 layers: 9 -> 6 us a level, 232 -> 176 us a call.
 // ---------------------------------------------------------------------------------------
 constexpr int kSmallPairs = 1024;  // (s, m) pairs of a device set the kernel has room for
-constexpr int kSmallThreads = 256; // 32 lanes a state
+constexpr int kSmallThreads = 256;
 constexpr int kSmallFlight = 4;    // candidates a lane has in flight
-__global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp) {
-    __shared__ int4 s_pair[kSmallPairs]; // left table, right table (byte offsets of their first records), s, m
-    __shared__ int s_sum[kSmallThreads / 64];
-    __shared__ double s_best[kSmallThreads / 64][8];
-    __shared__ unsigned s_tag[kSmallThreads / 64][8];
+__global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp, int lgC) {
+    __shared__ int4 s_pair[kSmallPairs]; // left table, right table (byte offsets of their first records), s << 21 | m, s
+    __shared__ int2 s_off[OOB_MAX_L + 1]; // split point u + i: byte offset of left record (u, u + i), of row u + i of the right records
+    __shared__ unsigned long long s_best[8];
+    __shared__ unsigned s_tag[8];
     const int L = t.sh.L, M = t.sh.M, n_max = t.sh.n_max, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int ub, vb;
     tile_decode(L, Sp, blockIdx.x, &ub, &vb);
-    const int2 dT = t.lvl_dir[Sp];
     const int delta = dlo_of(Sp, M) + blockIdx.y;
     const Family fam = family_of(delta, M);
-    const int u = ub * 8 + blockIdx.z, v = vb * 8 + (tid & 7) - t.coff, nk = tile_vmax(L, vb) - u - Sp + 1;
+    const int row = blockIdx.z >> (3 - lgC), col0 = (blockIdx.z & ((8 >> lgC) - 1)) << lgC, C = 1 << lgC, col = tid & (C - 1);
+    const int u = ub * 8 + row, vcol = col0 + col, nk = vb * 8 + col0 + C - 1 - t.coff - u - Sp + 1;
+    const long long out_at = (long long)(level(t, Sp).base + delta) * t.tab_recs + tri_index(ub, vb, t.NB) * 64 + (row << 3) + vcol;
+    if (nk <= 0) { // no states here
+        if (tid >= C) return;
+        t.rec[out_at] = Rec{kNone, kNone, 0.0, 0.0};
+        t.kstar[out_at] = 0;
+        t.choice[out_at] = 0;
+        return;
+    }
     const unsigned tab_bytes = (unsigned)t.tab_recs * (unsigned)sizeof(Rec);
     const bool fixed_nb = t.sh.Nb > 0;
-    int np = 0;
-    if (nk > 0) {
-        for (int s0 = 1; s0 < Sp; s0 += kSmallThreads) {
-            const int s = s0 + tid, r = Sp - s;
-            int mlo = 1, mhi = 0;
-            int2 dA = {0, 0}, dB = {0, 0};
-            if (r > 0) { // unit counts of the children (child_units with the level's ceil(S / M))
-                dA = t.lvl_dir[s]; dB = t.lvl_dir[r];
-                const int alo = fam.fam ? dA.y : s, ahi = fam.fam ? imin(s, n_max) : M - 1;
-                const int blo = fam.fam ? dB.y : r, bhi = fam.fam ? imin(r, n_max) : M - 1;
-                mlo = imax(alo, fam.units - bhi);
-                mhi = imin(ahi, fam.units - blo);
-            }
-            const int cnt = imax(0, mhi - mlo + 1), incl = scan_int(cnt, lane);
-            __syncthreads(); // (s_sum of the round before is read)
-            if (lane == 63) s_sum[wave] = incl;
-            __syncthreads();
-            int at = np + incl - cnt;
-            for (int w = 0; w < kSmallThreads / 64; ++w) {
-                if (w < wave) at += s_sum[w];
-                np += s_sum[w];
-            }
-            for (int m = mlo; m <= mhi; ++m, ++at)
-                if (at < kSmallPairs) // (the host has checked that they fit)
-                    s_pair[at] = make_int4((dA.x + fam.fam_base + m) * tab_bytes, (dB.x + fam.fam_base + fam.units - m) * tab_bytes, s, m);
-        }
-        np = imin(np, kSmallPairs);
+    if (tid < 8) { s_best[tid] = kNoKey; s_tag[tid] = 0xffffffffu; }
+    for (int i = tid; i < nk + Sp; i += kSmallThreads) { // split points u + 1 .. u + nk + Sp - 2
+        const int k = u + i, kb = k >> 3;
+        s_off[i] = make_int2(((ub * t.NB - ub * (ub - 1) / 2 - ub + ((k + t.coff) >> 3)) * 64 + ((u & 7) << 3) + ((k + t.coff) & 7)) * (int)sizeof(Rec),
+                             ((kb * t.NB - kb * (kb - 1) / 2 + vb - kb) * 64 + ((k & 7) << 3)) * (int)sizeof(Rec));
     }
-    __syncthreads();
+    int np = 0;
+    for (int s0 = 1; s0 < Sp; s0 += 64) { // every wave counts the pairs of 64 splits, each writes a share of them
+        const int s = s0 + lane, r = Sp - s;
+        int mlo = 1, mhi = 0;
+        Level dA = {0, 0}, dB = {0, 0};
+        if (r > 0) { // unit counts of the children (child_units with the level's ceil(S / M))
+            dA = level(t, s); dB = level(t, r);
+            const int alo = fam.fam ? dA.least : s, ahi = fam.fam ? imin(s, n_max) : M - 1;
+            const int blo = fam.fam ? dB.least : r, bhi = fam.fam ? imin(r, n_max) : M - 1;
+            mlo = imax(alo, fam.units - bhi);
+            mhi = imin(ahi, fam.units - blo);
+        }
+        const int cnt = imax(0, mhi - mlo + 1), incl = scan_int(cnt), at = np + incl - cnt;
+        for (int m = mlo + wave; m <= mhi; m += kSmallThreads / 64)
+            if (at + m - mlo < kSmallPairs) // (the host has checked that they fit)
+                s_pair[at + m - mlo] = make_int4((dA.base + fam.fam_base + m) * tab_bytes, (dB.base + fam.fam_base + fam.units - m) * tab_bytes, s << 21 | m, s);
+        np += __builtin_amdgcn_readlane(incl, 63);
+    }
+    np = imin(np, kSmallPairs);
+    wg_sync();
     double best = kNone;
     unsigned btag = 0xffffffffu; // s << 21 | k << 10 | m
-    const int total = np * nk, g = tid >> 3;
-    if (nk > 0 && np > 0) {
-        constexpr int G = kSmallThreads / 8;
-        const int dp = G / nk, dk = G - dp * nk, c = t.coff, vcol = (v + c) & 7;
-        const int rowA = ub * t.NB - ub * (ub - 1) / 2 - ub; // block (ub, b) is number rowA + b
+    const int total = np * nk, g = tid >> lgC;
+    if (np > 0) {
+        const int G = kSmallThreads >> lgC, dp = G / nk, dk = G - dp * nk;
         const char *const rec = (const char *)t.rec;
+        const unsigned right = (unsigned)vcol * (unsigned)sizeof(Rec);
         int p = g / nk, kk = g - p * nk;
         for (int i = g; i < total; i += G * kSmallFlight) {
             Rec24 ra[kSmallFlight], rb[kSmallFlight];
             unsigned tag[kSmallFlight];
-            double cl[kSmallFlight], cr[kSmallFlight];
 #pragma unroll
             for (int q = 0; q < kSmallFlight; ++q) {
                 const int4 e = s_pair[imin(p, np - 1)]; // past the end: some candidate of the last pair again
-                const int s = e.z, r = Sp - s, k = u + s + kk, kb = k >> 3;
-                const unsigned oa = ((rowA + ((k + c) >> 3)) * 64 + ((u & 7) << 3) + ((k + c) & 7)) * (unsigned)sizeof(Rec);
-                const unsigned ob = ((kb * t.NB - kb * (kb - 1) / 2 + vb - kb) * 64 + ((k & 7) << 3) + vcol) * (unsigned)sizeof(Rec);
-                ra[q] = load24(rec, (unsigned)e.x + oa);
-                rb[q] = load24(rec, (unsigned)e.y + ob);
-                tag[q] = ((unsigned)s << 21) | ((unsigned)k << 10) | (unsigned)e.w;
-                cl[q] = fixed_nb ? -(double)r : 3.0 * r;
-                cr[q] = fixed_nb ? 0.0 : 4.0 * s;
+                const int2 o = s_off[e.w + kk];
+                ra[q] = load24(rec, (unsigned)e.x + (unsigned)o.x);
+                rb[q] = load24(rec, (unsigned)e.y + (unsigned)o.y + right);
+                tag[q] = (unsigned)e.z + ((unsigned)(u + e.w + kk) << 10);
                 p += dp; kk += dk;
                 if (kk >= nk) { kk -= nk; ++p; }
             }
 #pragma unroll
             for (int q = 0; q < kSmallFlight; ++q) {
-                const double T = cand_total(ra[q], rb[q], cl[q], cr[q]);
+                const int s = (int)(tag[q] >> 21), r = Sp - s;
+                const double T = cand_total(ra[q], rb[q], fixed_nb ? -(double)r : 3.0 * r, fixed_nb ? 0.0 : 4.0 * s);
                 if (T < best || (T == best && tag[q] < btag)) { best = T; btag = tag[q]; }
             }
         }
     }
-#pragma unroll
-    for (int d = 8; d < 64; d <<= 1) {
-        const double ob = __shfl_xor(best, d, 64);
-        const unsigned ot = (unsigned)__shfl_xor((int)btag, d, 64);
-        if (ob < best || (ob == best && ot < btag)) { best = ob; btag = ot; }
-    }
-    if (lane < 8) { s_best[wave][lane] = best; s_tag[wave][lane] = btag; }
-    __syncthreads();
-    if (tid >= 8) return;
-    for (int w = 1; w < kSmallThreads / 64; ++w) {
-        const double ob = s_best[w][tid];
-        const unsigned ot = s_tag[w][tid];
-        if (ob < best || (ob == best && ot < btag)) { best = ob; btag = ot; }
-    }
+    // the state's smallest total (as integers: non-negative doubles), then the smallest tag among those that have it; the lane
+    // that has both writes the record
+    const unsigned long long mine = (unsigned long long)__double_as_longlong(best);
+    if (best < kNone) atomicMin(&s_best[col], mine);
+    wg_sync();
+    const unsigned long long least = s_best[col];
+    if (mine == least) atomicMin(&s_tag[col], btag);
+    wg_sync();
+    if (mine != least || s_tag[col] != btag || (least == kNoKey && g > 0)) return;
     Rec out = {kNone, kNone, 0.0, 0.0};
     int ks = 0, ch = 0;
     if (best < kNone) {
         const int s = (int)(btag >> 21), k = (int)((btag >> 10) & 2047u), m = (int)(btag & 1023u), r = Sp - s;
-        const long long oa = (long long)(t.lvl_dir[s].x + fam.fam_base + m) * t.tab_recs + rec_off(u, k, t.coff, t.NB);
-        const long long ob = (long long)(t.lvl_dir[r].x + fam.fam_base + fam.units - m) * t.tab_recs + rec_off(k, v, t.coff, t.NB);
+        const int v = vb * 8 + vcol - t.coff;
+        const long long oa = (long long)(level(t, s).base + fam.fam_base + m) * t.tab_recs + rec_off(u, k, t.coff, t.NB);
+        const long long ob = (long long)(level(t, r).base + fam.fam_base + fam.units - m) * t.tab_recs + rec_off(k, v, t.coff, t.NB);
         const Rec a = t.rec[oa], b = t.rec[ob];
         const int ka = t.kstar[oa], kb = t.kstar[ob];
         out.T = best;
@@ -1168,10 +1161,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp)
         else                  { out.tmax = b.tmax; ks = s + kb; out.T3 = b.T3; }
         ch = s | (k << 10) | (m << 21);
     }
-    const long long o = (long long)(dT.x + delta) * t.tab_recs + tri_index(ub, vb, t.NB) * 64 + (blockIdx.z << 3) + tid;
-    t.rec[o] = out;
-    t.kstar[o] = ks;
-    t.choice[o] = ch;
+    t.rec[out_at] = out;
+    t.kstar[out_at] = ks;
+    t.choice[out_at] = ch;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1260,13 +1252,11 @@ __device__ void coverage_body(const Tables &t, const oob_templates &out, int len
 // side and the kernel takes as long as the deepest leaf, not as the whole tree.
 // Workgroup `count` writes the end of the offsets and the coverage.
 __global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out, int len) {
-    __shared__ long long s_lvl[OOB_MAX_L + 3];
     __shared__ int s_part[128];
     const int i = blockIdx.x, tid = threadIdx.x, cnt = t.sh.count;
     int part = 0;
     for (int q = tid; q < i && q < cnt; q += blockDim.x) part += out.S[q];
     s_part[tid] = part;
-    for (int S = tid; S <= t.sh.Smax + 1; S += blockDim.x) s_lvl[S] = t.lvl_tab[S];
     __syncthreads();
     int off = 0;
     for (int q = 0; q < (int)blockDim.x; ++q) off += s_part[q];
@@ -1279,8 +1269,7 @@ __global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out, 
     for (int p = tid; p < S; p += blockDim.x) {
         int Sq = S, delta = M - 2 + t.sh.n_min + i, u = 0, v = L, pos = p;
         while (Sq > 1) {
-            const long long o = (s_lvl[Sq] + (delta - dlo_of(Sq, M))) * t.tab_recs +
-                                rec_off(u, v, t.coff, t.NB);
+            const long long o = rec_index(t, Sq, delta, u, v);
             const int ch = t.choice[o];
             const int s = ch & 1023, k = (ch >> 10) & 2047, m = (ch >> 21) & 1023;
             const Family fam = family_of(delta, M);
@@ -1339,7 +1328,7 @@ long long part_slots(int L, int M, int n_max, int Nb) {
 }
 
 struct Carve {
-    size_t lvl_tab, lvl_dir, rec, kstar, choice, partT, partK, flags, seg_tab, total;
+    size_t rec, kstar, choice, partT, partK, flags, seg_tab, total;
     long long recs, slots;
 };
 // Byte offsets of the workspace arrays, sized for the handle's maxima.
@@ -1350,8 +1339,6 @@ Carve carve(int L, int nodes, int M) {
     const size_t E = (size_t)c.recs;
     const int Smax = smax_of(L, nodes, M, 0);
     size_t o = 0;
-    c.lvl_tab = o; o = align_up(o + sizeof(long long) * (OOB_MAX_L + 3));
-    c.lvl_dir = o; o = align_up(o + sizeof(int2) * (OOB_MAX_L + 3));
     c.rec = o;     o = align_up(o + sizeof(Rec) * E);
     c.kstar = o;   o = align_up(o + sizeof(int) * E);
     c.choice = o;  o = align_up(o + sizeof(int) * E);
@@ -1438,10 +1425,21 @@ static const int kBatchLanes = env_or("OOB_TUNE_BATCH_LANES", 8);
 constexpr int kSelect8From = 82, kFuseFrom = 82;
 // Levels that k_level_small does: as many candidates of the widest state as 32 lanes look at in five round trips, and
 // so few in all that their scattered reads are not what the launch takes (it reads 0.15 million candidates a
-// microsecond).  Measured against split and select launches: 26 layers 308 -> 232 us with the line at 640
-// (320: 274 us, 1 000: 232 us), smallest job 39 -> 27 us on the GPU; 61 layers 1 294 us either way (1 000: 1 315 us);
-// 128 lanes a state: 268 us for the 26 layers.
+// microsecond).  Measured against split and select launches, with eight columns a workgroup: 26 layers 308 -> 232 us with the line at 640
+// (320: 274 us, 1 000: 232 us), smallest job 39 -> 27 us on the GPU; 61 layers 1 294 us either way (1 000: 1 315 us).
+// A million candidates of the level instead of half a million: 48 layers x 8 GPUs x 8 nodes 497 instead of 473 us, 75 x 4 x 10 384 instead of 391.
 constexpr int kSmallState = 640, kSmallLevel = 500000;
+// Columns of a workgroup (lgC) of such a level whose widest state has `most` candidates: eight, or fewer as long as a lane then has more
+// than kSmallSerial of them one after the other and the launch no more than kSmallGroups workgroups.  A candidate is some
+// hundred cycles of a wave that is alone on its SIMD, and the workgroup of the widest state with the most of them is what a launch waits for.  26
+// layers, kSmallSerial, kSmallGroups: 4, 2 048 176 us; 4, 1 024 174; 8, 1 024 176; 2, 2 048 182; 4, 4 096 187; eight columns always 232.
+constexpr int kSmallSerial = 4, kSmallGroups = 2048;
+static int small_columns(const Shape &sh, int S, long long most) {
+    const long long groups = (long long)tile_count(sh.L, S) * (dhi_of(S, sh.M, sh.n_max) - dlo_of(S, sh.M) + 1) * 8;
+    int lgC = 3;
+    while (lgC > 0 && most > (long long)kSmallSerial * (kSmallThreads >> lgC) && groups << (4 - lgC) <= kSmallGroups) --lgC;
+    return lgC;
+}
 constexpr int kOverlapFrom = 24000; // thousand candidates of a level: see enqueue_job
 constexpr int kSelLanes = 1; // lanes per state below that
 // Launch shape of k_split_key for one family of one level; waves and LDS follow per launch (key_waves, key_lds).
@@ -1607,8 +1605,7 @@ static Tables make_tables(const oob_plan *h, int lane, const Shape &sh, int *sta
     t.NB = nblocks_of(sh.L);
     t.coff = col_shift(sh.L);
     t.tab_recs = tri_blocks(t.NB) * 64;
-    t.lvl_tab = (long long *)(ws + h->cv.lvl_tab);
-    t.lvl_dir = (int2 *)(ws + h->cv.lvl_dir);
+    t.inv_M = inverse_of(sh.M);
     t.rec = (Rec *)(ws + h->cv.rec);
     t.kstar = (int *)(ws + h->cv.kstar);
     t.choice = (int *)(ws + h->cv.choice);
@@ -1731,7 +1728,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     const Tables t = make_tables(h, ln, sh, (int *)out->status);
     // states and candidates; the levels worth an overlap (below)
     int ov_lo = sh.Smax + 1, ov_hi = 0;
-    bool small[OOB_MAX_L + 1]; // levels done by one launch
+    signed char small[OOB_MAX_L + 1]; // levels done by one launch: the columns of its workgroups (lgC), else -1
     out->states = out->candidates = 0;
     for (int S = 1; S <= sh.Smax; ++S) {
         long long states, cands;
@@ -1739,17 +1736,18 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         level_counts(sh, S, &states, &cands, &most);
         out->states += states; out->candidates += cands;
         if (S >= 4 && cands >= h->opt_overlap_from * 1000ll) { ov_lo = imin(ov_lo, S); ov_hi = S; }
-        small[S] = S >= 2 && most <= kSmallPairs && (long long)most * (L - S + 1) <= h->opt_small_state && cands <= kSmallLevel;
+        const long long widest = (long long)most * (L - S + 1);
+        small[S] = S >= 2 && most <= kSmallPairs && widest <= h->opt_small_state && cands <= kSmallLevel ? small_columns(sh, S, widest) : -1;
     }
     if (table_count(L, M, n_max, microbatches) * tri_blocks(nblocks_of(L)) * 64 * (long long)sizeof(Rec) >= 1ll << 32 || force_plain)
-        std::fill(small, small + sh.Smax + 1, false); // its offsets are 32 bits
+        std::fill(small, small + sh.Smax + 1, (signed char)-1); // its offsets are 32 bits
 
     const long long slot_stride = h->cv.slots * 64; // distance between the two buffers of per-split minima
     long long keys = 0; // of the level that has most of them
     for (int S = 2; S <= sh.Smax; ++S) keys = std::max(keys, (long long)(dhi_of(S, M, n_max) - dlo_of(S, M) + 1) * tile_count(L, S) * 64);
     bool overlap = want_overlap && !force_plain && ov_lo <= ov_hi;
     int how = force_plain;
-    for (int S = 2; S <= sh.Smax; ++S) how += small[S] ? 1 << 1 : overlap && S >= ov_lo && S <= ov_hi ? 1 << (1 + kHowBits) : 0;
+    for (int S = 2; S <= sh.Smax; ++S) how += small[S] >= 0 ? 1 << 1 : overlap && S >= ov_lo && S <= ov_hi ? 1 << (1 + kHowBits) : 0;
     const int ones = M * ((tile_count(L, 1) + 3) / 4);
     hipLaunchKernelGGL(k_prepare, dim3((unsigned)(1 + ones + imax(sh.Smax - 1, 0) + (2 * keys + kSetupThreads - 1) / kSetupThreads)),
                        dim3(kSetupThreads), 0, st, t, *profile, how, h->opt_xcd, ones, slot_stride, keys);
@@ -1782,8 +1780,8 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         const int NAall = dhi_of(S, M, n_max) - dlo_of(S, M) + 1;
         if (NAall <= 0) continue;
         const int NT = tile_count(L, S);
-        if (small[S]) {
-            hipLaunchKernelGGL(k_level_small, dim3(NT, NAall, 8), dim3(kSmallThreads), 0, st, t, S);
+        if (small[S] >= 0) {
+            hipLaunchKernelGGL(k_level_small, dim3(NT, NAall, 8 << (3 - small[S])), dim3(kSmallThreads), 0, st, t, S, (int)small[S]);
             if (overlap && S + 2 >= ov_lo && S + 2 <= ov_hi) OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S], st));
             continue;
         }
@@ -1963,6 +1961,16 @@ extern "C" int oob_plan_layout_selftest(int L) {
     if (L < 1 || L > OOB_MAX_L) return OOB_EINVAL;
     const int NB = nblocks_of(L), c = col_shift(L), recs = tri_blocks(NB) * 64;
     if ((L + c + 1) % 8 != 0 || (L + c) / 8 != NB - 1) return 1;
+    for (int M = 1; M <= OOB_MAX_GPUS; ++M) // the closed form of the levels' tables
+        for (int n_max = 1; n_max <= imin(L, OOB_MAX_NODES); n_max += 1 + n_max / 3) {
+            int tab = 0;
+            for (int S = 1; S <= imin(L, n_max * M); ++S) {
+                const Level lv = level_of(S, M, n_max, inverse_of(M));
+                const int nd = dhi_of(S, M, n_max) - dlo_of(S, M) + 1;
+                if (lv.base + dlo_of(S, M) != tab || lv.least != cdiv(S, M) || nd < 1) return 12;
+                tab += nd;
+            }
+        }
     std::vector<int> owner((size_t)(L + 1) * (L + 1));
     std::vector<char> used(recs);
     for (int u = 0; u <= L; ++u) // records of distinct (u, v) are distinct and inside the table

@@ -580,6 +580,19 @@ def test_levels_by_one_launch(P, small_state):
         planner.close()
 
 
+@pytest.mark.parametrize("job", [(26, 4, 2, 16, 32), (9, 1, 1, 9, 0), (17, 8, 1, 3, 0), (66, 2, 1, 3, 5), (7, 2, 1, 2, 0), (120, 1, 1, 2, 2)])
+def test_small_levels_with_one_to_eight_columns_a_workgroup(P, job):
+    """Levels by one launch in workgroups of one, two, four and eight states: many and few candidates a state, blocks of one state and whole
+    ones, launches at and above the most workgroups that are split further."""
+    inp = inputs.random_small(12, *job, f=1)
+    planner = P.Planner(inp.L, inp.n_max, inp.gpus_per_node)
+    for small_state in (1 << 30, 640):
+        planner.set_option(P.OOB_OPT_SMALL_STATE, small_state)
+        full_check(P, planner, inp)
+        assert planner.flags()[2] > 0
+    planner.close()
+
+
 @every_kernel
 def test_two_calls_same_answer(P, small_state):
     """Determinism: the same job twice on one handle gives identical tables."""
