@@ -1355,6 +1355,10 @@ Carve carve(int L, int nodes, int M) {
 // Structural work counts of a level: states = (u, v) with v - u >= S' per table; candidates = (s, k, m)
 // with both children valid: per (s, m) pair one per (u, k, v), u + s <= k <= v - r.
 // *most: (s, m) pairs of the target that has most of them.
+// The pairs of a split as a function of the target's units are a trapezoid, two intervals added up: its four corners go into
+// second differences, summed twice at the end of the level.  Counted target by target and split by split it took the
+// host 960 us before the first launch of the headline workload and 175 us for 61 layers, 27 and 12 us like this: a call at a time
+// 7.40 -> 6.78 ms, and 1.33 -> 1.22 ms from host to host.
 void level_counts(const Shape &sh, int S, long long *states, long long *cands, int *most) {
     const long long n = sh.L - S + 1;
     const int dlo = dlo_of(S, sh.M), dhi = dhi_of(S, sh.M, sh.n_max);
@@ -1363,13 +1367,19 @@ void level_counts(const Shape &sh, int S, long long *states, long long *cands, i
     for (int fam = S <= sh.M ? 0 : 1; fam < 2; ++fam) {
         int t_lo, t_hi;
         target_units(fam, S, sh.M, sh.n_max, &t_lo, &t_hi);
-        for (int a = t_lo; a <= t_hi; ++a) {
-            int here = 0;
-            for (int s = 1; s < S; ++s) {
-                int lo, hi;
-                m_range(fam, a, s, S - s, sh.M, sh.n_max, &lo, &hi);
-                if (hi >= lo) here += hi - lo + 1;
-            }
+        int corner[OOB_MAX_NODES + 1];
+        std::fill(corner, corner + imax(0, t_hi - t_lo + 1), 0);
+        auto add = [&](int units, int x) { if (units <= t_hi) corner[units - t_lo] += x; }; // (no child pair adds up to less than t_lo)
+        for (int s = 1; s < S; ++s) {
+            int alo, ahi, blo, bhi;
+            child_units(fam, s, sh.M, sh.n_max, &alo, &ahi);
+            child_units(fam, S - s, sh.M, sh.n_max, &blo, &bhi);
+            if (alo > ahi || blo > bhi) continue;
+            add(alo + blo, 1); add(ahi + 1 + blo, -1); add(alo + bhi + 1, -1); add(ahi + bhi + 2, 1);
+        }
+        for (int units = t_lo, slope = 0, here = 0; units <= t_hi; ++units) {
+            slope += corner[units - t_lo];
+            here += slope;
             pairs += here;
             *most = imax(*most, here);
         }
