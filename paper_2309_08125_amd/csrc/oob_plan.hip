@@ -1484,6 +1484,9 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
 
 using namespace oob;
 
+// The streams of an overlapped job beside the caller's.
+struct Pair { hipStream_t even, odd; };
+
 // The second stream and the events of a handle are borrowed from a pool that lives as long as the
 // process and are given back when the handle is destroyed: nothing is created or destroyed per
 // handle once the pool is warm (a harness that created and destroyed hundreds of handles, each
@@ -1491,19 +1494,52 @@ using namespace oob;
 struct AuxPool {
     std::mutex mu;
     std::vector<hipStream_t> streams;
+    std::vector<Pair> pairs;
+    std::vector<hipStream_t> idle;
     std::vector<hipEvent_t> events;
 };
 static AuxPool &aux_pool() {
     static AuxPool *p = new AuxPool(); // never destroyed: no order-of-destruction trouble at exit
     return *p;
 }
+// The runtime deals streams out to its hardware queues (four by default) in turn, and work of streams on one queue does not
+// overlap.  So streams are made four at a time, the third (which from the second four on gets the queue of the default stream) and
+// what a pair leaves over only keep the turns in step: a pair, or three lanes, are on different queues and not on that of the default stream.
+// Made as they were asked for, every second handle had both streams on one queue or one on the caller's: headline workload, six handles
+// alive, 6.8, 8.8, 6.8, 9.9, 6.8, 9.9 ms a call, 6.9 ms each like this; batch of 32 jobs behind such a handle 85 and 78 ms.  (Where the
+// caller makes streams in between, the turns differ, and one may still meet the caller's queue.)
+static bool make_four(AuxPool &p, hipStream_t *s) {
+    for (int i = 0; i < 4; ++i)
+        if (hipStreamCreateWithFlags(&s[i], hipStreamNonBlocking) != hipSuccess) {
+            (void)hipGetLastError();
+            p.streams.insert(p.streams.end(), s, s + i);
+            return false;
+        }
+    p.idle.push_back(s[2]);
+    return true;
+}
 static hipStream_t borrow_stream() {
     AuxPool &p = aux_pool();
     std::lock_guard<std::mutex> lk(p.mu);
-    if (!p.streams.empty()) { hipStream_t s = p.streams.back(); p.streams.pop_back(); return s; }
-    hipStream_t s = nullptr;
-    if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
-    return s;
+    hipStream_t s[4];
+    if (p.streams.empty() && make_four(p, s)) p.streams.insert(p.streams.end(), {s[3], s[1], s[0]});
+    if (p.streams.empty()) return nullptr;
+    const hipStream_t one = p.streams.back();
+    p.streams.pop_back();
+    return one;
+}
+static bool borrow_pair(Pair *pair) {
+    AuxPool &p = aux_pool();
+    std::lock_guard<std::mutex> lk(p.mu);
+    if (p.pairs.empty()) {
+        hipStream_t s[4];
+        if (!make_four(p, s)) return false;
+        p.idle.push_back(s[3]);
+        p.pairs.push_back(Pair{s[0], s[1]});
+    }
+    *pair = p.pairs.back();
+    p.pairs.pop_back();
+    return true;
 }
 static hipEvent_t borrow_event() {
     AuxPool &p = aux_pool();
@@ -1520,8 +1556,8 @@ static hipEvent_t borrow_event() {
 constexpr int kMaxLanes = 8;
 struct Lane {
     hipStream_t main = nullptr;       // lanes >= 1: borrowed; lane 0 runs on the caller's stream
-    hipStream_t aux = nullptr;        // streams for the inner splits of the even / odd levels, borrowed
-    hipStream_t aux2 = nullptr;       // (null: everything on one stream)
+    bool have_aux = false;            // (false: everything on one stream)
+    Pair aux;                         // streams for the inner splits of the even / odd levels, borrowed
     std::vector<hipEvent_t> ev_level; // [2 S'] "level S' selected", [2 S' + 1] "inner splits of level S' done",
                                       // borrowed
     hipEvent_t ev_join = nullptr;     // lanes >= 1: end of the lane's work in a batch, borrowed
@@ -1598,8 +1634,7 @@ extern "C" int oob_plan_destroy(oob_plan *h) {
         for (Lane &ln : h->lane) {
             for (hipEvent_t e : ln.ev_level) p.events.push_back(e);
             if (ln.ev_join) p.events.push_back(ln.ev_join);
-            if (ln.aux) p.streams.push_back(ln.aux);
-            if (ln.aux2) p.streams.push_back(ln.aux2);
+            if (ln.have_aux) p.pairs.push_back(ln.aux);
             if (ln.main) p.streams.push_back(ln.main);
         }
         if (h->ev_fork) p.events.push_back(h->ev_fork);
@@ -1774,16 +1809,15 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     // records, the two waits and the third launch of an overlapped one occupy the host for longer (one stream
     // throughout, against three: 26 layers 312 and 732 us, 61 layers 1.62 and 1.78 ms, headline workload 10.5 and
     // 7.5 ms; the line at 0, 20, 40, 80 million candidates: headline workload 7.47, 7.60, 7.69, 7.89 ms).
-    if (overlap && !lane.aux) lane.aux = borrow_stream();
-    if (overlap && !lane.aux2) lane.aux2 = borrow_stream();
-    if (overlap && lane.aux && lane.aux2) {
+    if (overlap && !lane.have_aux) lane.have_aux = borrow_pair(&lane.aux);
+    if (overlap && lane.have_aux) {
         while ((int)lane.ev_level.size() < 2 * sh.Smax + 2) {
             hipEvent_t e = borrow_event();
             if (!e) break;
             lane.ev_level.push_back(e);
         }
     }
-    overlap = overlap && lane.aux && lane.aux2 && (int)lane.ev_level.size() >= 2 * sh.Smax + 2;
+    overlap = overlap && lane.have_aux && (int)lane.ev_level.size() >= 2 * sh.Smax + 2;
     const bool timed = ln == 0 && h->ev_begin;
     if (timed) OOB_HIP_CHECK(hipEventRecord(h->ev_begin, st));
     for (int S = 2; S <= sh.Smax; ++S) {
@@ -1805,7 +1839,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         }
         const bool inner = overlap && S >= ov_lo && S <= ov_hi;
         if (inner) {
-            hipStream_t sx = (S & 1) ? lane.aux2 : lane.aux;
+            hipStream_t sx = (S & 1) ? lane.aux.odd : lane.aux.even;
             OOB_HIP_CHECK(hipStreamWaitEvent(sx, lane.ev_level[2 * (S - 2)], 0)); // select of level S'-2
             launch_split_keys(tl, S, have, kp, NT, h->opt_xcd, SplitRange{2, 1, S - 3}, sx);
             OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S + 1], sx));

@@ -493,6 +493,36 @@ def test_levels_on_several_streams(P, overlap_from):
         planner.close()
 
 
+def test_overlapped_jobs_of_several_handles_stay_behind_their_callers_streams(P):
+    """Three handles with overlapped levels on two caller streams, profile written before and overwritten after each call on the
+    same stream without a wait in between: the job runs between the two."""
+    import torch
+
+    inp = inputs.config(2)
+    planners = [P.Planner(inp.L, inp.n_max, inp.gpus_per_node) for _ in range(3)]
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
+    jobs, good = [], P.DeviceProfile(inp)
+    for i, planner in enumerate(planners):
+        planner.set_option(P.OOB_OPT_SMALL_STATE, 0)
+        planner.set_option(P.OOB_OPT_OVERLAP_FROM, 0)
+        jobs.append((planner, P.DeviceProfile(inp), planner.new_outputs(inp), streams[i % 2]))
+    planners[0].enqueue(good, jobs[0][2])
+    want = jobs[0][2].to_host()
+    torch.cuda.synchronize()
+    for rep in range(4):
+        for planner, prof, out, stream in jobs:
+            with torch.cuda.stream(stream):
+                prof.base.copy_(good.base)
+                out.base.zero_()
+                planner.enqueue(prof, out)
+                prof.base.fill_(rep)
+    torch.cuda.synchronize()
+    for planner, prof, out, _ in jobs:
+        got = out.to_host()
+        assert all(np.array_equal(got[k], want[k]) for k in out.t)
+        planner.close()
+
+
 def level_counts(inp):
     """Per level S' >= 2: candidates, and those of the widest state of the device set with most (s, m) pairs."""
     L, M = inp.L, inp.gpus_per_node
