@@ -69,6 +69,7 @@ struct Args {
     oob_profile prof;
     int L, M, n_min, n_max, Nb, Dmax, Smax, fast, staged, bounds;
     int sums;             // the profile without the ends of the stages (EvalLds)
+    int eval_pad, bounds_pad; // rows of the profile in LDS padded (Prof)
     int nodes;            // min(n_max, L): more nodes than layers make no pipeline
     int top, live;        // last template that can get a minimum (answered(), nodes), number of templates up to it
     long long cap;
@@ -351,24 +352,26 @@ __device__ __forceinline__ double row_below(double x) {
     return __hiloint2double(hi, lo);
 }
 
-// The profile in LDS: PT[l M + d-1] prefix sums, PX = PT plus the boundary term of a stage ending at layer l,
-// X the boundary terms, flo as in Args.  SUM: PX is not kept but added up where it is read (integers below 2^52: the same
+// The profile in LDS: PT[l ms + d-1] prefix sums, PX = PT plus the boundary term of a stage ending at layer l,
+// X the boundary terms, flo as in Args.  At eight GPUs per node a row is nine doubles where there is room (ms = M | 1, PAD): neighbouring
+// lanes read neighbouring rows, which fall on the same few banks otherwise (47-63 % of the LDS cycles were conflicts): 98 layers 780 ->
+// 662 us, 61 layers, 18 nodes 672 -> 660, 48 layers with the limit binding (in the bounds only) 3.15 -> 3.05 ms.  SUM: PX is not kept but added up where it is read (integers below 2^52: the same
 // value), for shapes whose tables leave it no room.
 struct Prof { double *PT, *PX, *X; unsigned char *flo; };
-template <bool SUM> __device__ __forceinline__ double stage_end(const Prof &s, int l, int i) { // i = l M + d-1
+template <bool SUM> __device__ __forceinline__ double stage_end(const Prof &s, int l, int i) { // i = l ms + d-1
     if constexpr (SUM) return s.PT[i] + s.X[l];
     else return s.PX[i];
 }
-template <bool SUM> __device__ __forceinline__ Prof load_prof(const Args &a, double *lds) {
+template <bool SUM> __device__ __forceinline__ Prof load_prof(const Args &a, double *lds, int ms) {
     const int W = a.L + 1, n = W * a.M;
     Prof p;
-    p.PT = lds; p.PX = p.PT + n; p.X = SUM ? p.PX : p.PX + n; p.flo = (unsigned char *)(p.X + W);
+    p.PT = lds; p.PX = p.PT + W * ms; p.X = SUM ? p.PX : p.PX + W * ms; p.flo = (unsigned char *)(p.X + W);
     const long long *bnd = (const long long *)a.prof.boundary_ns;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const int l = i / a.M;
+        const int l = i / a.M, at = ms == a.M ? i : l * ms + (i - l * a.M);
         const double pt = (double)a.PT[i];
-        p.PT[i] = pt;
-        if (!SUM) p.PX[i] = pt + (l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0);
+        p.PT[at] = pt;
+        if (!SUM) p.PX[at] = pt + (l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0);
         p.flo[i] = a.flo[i];
     }
     for (int l = threadIdx.x; l < W; l += blockDim.x) p.X[l] = l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0;
@@ -377,24 +380,24 @@ template <bool SUM> __device__ __forceinline__ Prof load_prof(const Args &a, dou
 // Reach of a stage on dd GPUs into layer p (before the slowest stage: it starts at r .. p-1; p: none) that
 // takes less than tau (STRICT) or at most tau: it only gets slower and heavier as its start goes down.
 template <bool STRICT, bool SUM>
-__device__ __forceinline__ int reach_back(const Prof &s, int M, int p, int dd, double tau) {
-    const double end = stage_end<SUM>(s, p, p * M + dd - 1);
+__device__ __forceinline__ int reach_back(const Prof &s, int M, int ms, int p, int dd, double tau) {
+    const double end = stage_end<SUM>(s, p, p * ms + dd - 1);
     int lo = s.flo[p * M + dd - 1], hi = p;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        const double t = end - s.PT[mid * M + dd - 1];
+        const double t = end - s.PT[mid * ms + dd - 1];
         if (STRICT ? t < tau : t <= tau) hi = mid; else lo = mid + 1;
     }
     return lo;
 }
 // Reach of a stage on dd GPUs out of layer p (after the slowest stage: it ends at p+1 .. r; p: none).  Impossible
 // stays impossible and the time without the boundary term only grows as the end goes up.
-__device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int p, int dd, double tau) {
-    const double start = s.PT[p * M + dd - 1];
+__device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int ms, int p, int dd, double tau) {
+    const double start = s.PT[p * ms + dd - 1];
     int lo = p, hi = L;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (s.flo[mid * M + dd - 1] <= p && s.PT[mid * M + dd - 1] - start <= tau) lo = mid; else hi = mid - 1;
+        if (s.flo[mid * M + dd - 1] <= p && s.PT[mid * ms + dd - 1] - start <= tau) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -408,7 +411,7 @@ __device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int p, int 
 // GPUs and at most S_max stages are used, whatever the prices.  The bound is the largest over the
 // multipliers.  Row after row of the two paths; a wave takes two lambdas, thirty-two lanes each share out the
 // starts of the last stage, eight GPU counts side by side.  Bound by the chain of rows (LDS read, reduction over the
-// lanes, LDS write per row) at one workgroup per bucket, 63 % of the LDS cycles bank conflicts: 212 us at 98 layers x 8 GPUs, 512 buckets (170 us with 274).
+// lanes, LDS write per row) at one workgroup per bucket: 132 us at 98 layers x 8 GPUs, 512 buckets (212 with rows of eight doubles, Prof).
 // ---------------------------------------------------------------------------------------------
 __device__ const double kLambdaGiven[kLambdas] = {0, 0.04, 0.1, 0.2, 0.4, 0.8, 1.6, 3.5}; // more nodes pay (C falls with n) ...
 __device__ const double kLambda4S[kLambdas] = {0, -0.06, -0.14, -0.25, -0.43, -0.7, -1.3, -3.5}; // ... or cost
@@ -463,9 +466,9 @@ __device__ __forceinline__ double bound_of(const Args &a, const float *lb, doubl
     for (int k = 0; k < a.nk; ++k) x = fmax(x, (double)lb[k] - lo * spent(a, k, n));
     return x;
 }
-// Six waves per SIMD asked for where M is known: 78 registers, which is also the faster schedule of the rows (170 us at 98 layers x
-// 8 GPUs, against 207 with the 94 that the compiler takes by itself; it stays at two workgroups per compute unit either way).
-template <int MT>
+// Six waves per SIMD asked for where M is known: 78 registers, which is also the faster schedule of the rows (with 274 buckets and rows of
+// eight doubles 170 us at 98 layers x 8 GPUs, 207 with the 94 that the compiler takes by itself; two workgroups per compute unit either way).
+template <int MT, bool PAD>
 __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args a, int mus) {
     constexpr int CW = MT ? MT : 8;
     HIP_DYNAMIC_SHARED(double, s_dyn)
@@ -478,8 +481,9 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
     const int L = a.L, M = MT ? MT : a.M, W = L + 1, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned c0 = b * K, c1 = min(a.head->ncand, c0 + K);
-    const Prof s = load_prof<false>(a, s_dyn);
-    unsigned char *rb = (unsigned char *)(s_dyn + prof_doubles(L, M)), *rf = rb + ((size_t)W * M + 7) / 8 * 8;
+    const int ms = PAD ? M | 1 : M;
+    const Prof s = load_prof<false>(a, s_dyn, ms);
+    unsigned char *rb = (unsigned char *)(s_dyn + prof_doubles(L, M, ms)), *rf = rb + ((size_t)W * M + 7) / 8 * 8;
     double *PS = (double *)(rf + ((size_t)W * M + 7) / 8 * 8); // [mu][lambda][side][L+1]
     float *s_lb = (float *)(PS + (size_t)mus * kLambdas * 2 * W); // [kBucket][kMaxCount]
     unsigned char *s_far = (unsigned char *)(s_lb + kBucket * kMaxCount); // [256] for fewest_nodes()
@@ -493,8 +497,8 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
     const double lo = __longlong_as_double((long long)s_lo), hi = __longlong_as_double((long long)s_hi);
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
         const int p = i / M, dd = i - p * M + 1;
-        rb[i] = (unsigned char)reach_back<false, false>(s, M, p, dd, hi);
-        rf[i] = (unsigned char)reach_on(s, L, M, p, dd, hi);
+        rb[i] = (unsigned char)reach_back<false, false>(s, M, ms, p, dd, hi);
+        rf[i] = (unsigned char)reach_on(s, L, M, ms, p, dd, hi);
     }
     const bool given = a.Nb > 0;
     if (threadIdx.x < kLambdas) s_lam[threadIdx.x] = (given ? kLambdaGiven[threadIdx.x] : kLambda4S[threadIdx.x]) * lo;
@@ -528,7 +532,7 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
 #pragma unroll
                 for (int j = 0; j < CW; ++j) {
                     const int dc = MT ? j : imin(d0 + j, M - 1), rc = reach[p * M + dc];
-                    const double e = near[p * M + dc];
+                    const double e = near[p * ms + dc];
                     lim[j] = d0 + j < M ? (side ? rc - p : p - rc) : 0;
                     most = imax(most, lim[j]);
                     cost[j] = (side ? sw + mu - 2.0 * e : pw + mu + e) + l * (dc + 1);
@@ -539,7 +543,7 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
                     const double px = P[x];
                     double f[CW], v[CW];
 #pragma unroll
-                    for (int j = 0; j < CW; ++j) f[j] = far[x * M + (MT ? j : imin(d0 + j, M - 1))];
+                    for (int j = 0; j < CW; ++j) f[j] = far[x * ms + (MT ? j : imin(d0 + j, M - 1))];
 #pragma unroll
                     for (int j = 0; j < CW; ++j) {
                         const bool ok = (k < lim[j]) & (!side | (f[j] <= edge[j]));
@@ -564,7 +568,7 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
     // path may use 255 times the GPUs of the pipeline: lowered by 1e-9 of them), and prefix sums of the GPU count in use,
     // twice over -- which hold also the layers whose time on that count no stage takes (by 1e-12 of the largest).
     double total = 0;
-    for (int d = 0; d < M; ++d) total = fmax(total, s.PT[L * M + d]);
+    for (int d = 0; d < M; ++d) total = fmax(total, s.PT[L * ms + d]);
     // bounds of the bucket's entries, kBucket at a time; the smallest of every template
     const int count = a.n_max - a.n_min + 1, nk = mus * kLambdas;
     float mine = __builtin_huge_valf();
@@ -661,9 +665,9 @@ __global__ void __launch_bounds__(kFilterThreads) k_exact_filter(Args a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact evaluation.  Bound by chains of dependent LDS reads on the rows of the one-node tables; at 8 GPUs per node 47 % of the LDS cycles
-// are bank conflicts (neighbouring lanes read rows 64 bytes apart) and 30 registers of k_exact_eval<false, 8> are spilled: 29 MB of scratch
-// written per launch.  150-167 us for the first picks and 350-460 us for the rest at 98 layers x 8 GPUs (the version before, without a band and
+// Exact evaluation.  Bound by chains of dependent LDS reads on the rows of the one-node tables; at 8 GPUs per node
+// 38 registers of k_exact_eval<false, 8> are spilled: some 30 MB of scratch
+// written per launch.  140-160 us for the first picks and 330-430 us for the rest at 98 layers x 8 GPUs (a version without a band,
 // evaluating everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table
 // entry: 1, or S_max + 1 (STAGED).
 // ---------------------------------------------------------------------------------------------
@@ -687,7 +691,7 @@ __device__ __forceinline__ int band_index(int r, int j, int len) { return (r - 1
 // counts the lanes that would share a walk out hold the counts j = 1 .. M instead.  A row takes the stages that
 // cover its last k + 1 layers on CW GPU counts side by side: the CW table entries and the CW prefix sums of a
 // step are read before any of them is used.
-template <bool MIRROR, bool STAGED, int MT, bool SUM>
+template <bool MIRROR, bool STAGED, int MT, bool SUM, bool PAD>
 __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band, double tau, double wt, double add,
                                 double *Wm, double *GU, double *G, int first, int slots, int lgxs, int gbits) {
     constexpr int CW = MT ? MT : 8;
@@ -702,7 +706,8 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
     const int g = gi + 1, rows = live ? imin(band, len - idx) : 0;
     const bool use = live && (!STAGED || j <= g);                   // this lane has an entry in every row
     const int q = live ? (MIRROR ? L - idx : idx) : 0;                           // start layer
-    auto far = [&](int l, int gc) { return MIRROR ? stage_end<SUM>(e.pr, l, l * M + gc) : e.pr.PT[l * M + gc]; };
+    const int ms = PAD ? M | 1 : M;
+    auto far = [&](int l, int gc) { return MIRROR ? stage_end<SUM>(e.pr, l, l * ms + gc) : e.pr.PT[l * ms + gc]; };
     const int top = g + 1 - (j - 1);
     const int none = 0; // row 0 holds no cover (a node's first stage is taken on its own): always impossible
     if (slot < slots && gi == 0 && xs == 0) T[none] = kNone;
@@ -713,7 +718,7 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
         const int p = on ? (MIRROR ? q - r : q + r) : 0;
         { // one stage on all g GPUs covers everything
             const int gc = imin(gi, M - 1), rc = e.reach[p * M + gc];
-            const double here = MIRROR ? e.pr.PT[p * M + gc] : stage_end<SUM>(e.pr, p, p * M + gc), all = far(q, gc);
+            const double here = MIRROR ? e.pr.PT[p * ms + gc] : stage_end<SUM>(e.pr, p, p * ms + gc), all = far(q, gc);
             const double tw = MIRROR ? all - here : here - all;
             const bool one = on & (j == 1) & (x0 == 0) & ((MIRROR ? rc - p : p - rc) >= r) & (!MIRROR | (tw <= tau));
             acc = one ? wt * tw + add : kNone;
@@ -725,8 +730,8 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
 #pragma unroll
             for (int w = 0; w < CW; ++w) {
                 const int dc = MT ? w : imin(d0 + w, M - 1), rc = e.reach[p * M + dc];
-                near[w] = wt * (MIRROR ? -e.pr.PT[p * M + dc] : stage_end<SUM>(e.pr, p, p * M + dc)) + add;
-                late[w] = MIRROR ? e.pr.PT[p * M + dc] + tau : 0.0;
+                near[w] = wt * (MIRROR ? -e.pr.PT[p * ms + dc] : stage_end<SUM>(e.pr, p, p * ms + dc)) + add;
+                late[w] = MIRROR ? e.pr.PT[p * ms + dc] + tau : 0.0;
                 lim[w] = on && d0 + w + 1 < top ? imin(MIRROR ? rc - p : p - rc, r - 1) : 0; // the other stages need a GPU each
                 most = imax(most, lim[w]);
                 const int left = g - dc - 1; // GPUs of the other stages
@@ -900,7 +905,7 @@ __device__ void combine(const Args &a, const Eval &e, int d, double tau, int nhi
 
 // One row of the tables over (layers covered, GPUs used[, stages]) of a side: T[r][D][j], r layers from the far end of the
 // side on D GPUs, node after node.  Called by nth threads (whole waves); a thread has one (D, j) and a share of the walk.
-template <bool MIRROR, bool STAGED, int MT, bool SUM>
+template <bool MIRROR, bool STAGED, int MT, bool SUM, bool PAD>
 __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, double tau, double wt, double add, double *T, int th,
                         int nth) {
     constexpr int CW = MT ? MT : 8;
@@ -909,7 +914,8 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
     int lg = 0;
     while (lg < 6 && items << (lg + 1) <= nth) ++lg;
     const int XS = 1 << lg, x0 = th & (XS - 1);
-    auto far = [&](int l, int gc) { return MIRROR ? stage_end<SUM>(e.pr, l, l * M + gc) : e.pr.PT[l * M + gc]; };
+    const int ms = PAD ? M | 1 : M;
+    auto far = [&](int l, int gc) { return MIRROR ? stage_end<SUM>(e.pr, l, l * ms + gc) : e.pr.PT[l * ms + gc]; };
     for (int i0 = 0; i0 < items; i0 += nth >> lg) {
         const int i = i0 + (th >> lg), D = i % nd, j = STAGED ? i / nd + 1 : 1;
         const bool on = i < items && D > 0 && j <= D;
@@ -921,7 +927,7 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
 #pragma unroll
             for (int w = 0; w < CW; ++w) {
                 const int dc = MT ? w : imin(d0 + w, M - 1), rc = e.reach[p * M + dc];
-                near[w] = MIRROR ? e.pr.PT[p * M + dc] : stage_end<SUM>(e.pr, p, p * M + dc);
+                near[w] = MIRROR ? e.pr.PT[p * ms + dc] : stage_end<SUM>(e.pr, p, p * ms + dc);
                 lim[w] = d0 + w < gD && (!STAGED || D - dc - 1 >= j - 1) ? imin(MIRROR ? rc - p : p - rc, r) : 0;
                 most = imax(most, lim[w]);
                 off[w] = (r - 1) * row_n + imax(D - dc - 1, 0) * jd + (STAGED ? j - 1 : 0);
@@ -953,7 +959,7 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
 
 // The cost of the best pipelines around slowest stage (u, v, d) with n <= nhi nodes, merged into s_best.
 // Returns false (the same in every thread) if the tables do not fit the workgroup's LDS (STAGED only).
-template <bool STAGED, int MT, bool SUM>
+template <bool STAGED, int MT, bool SUM, bool PAD>
 __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int nhi, unsigned long long *s_best) {
     const int L = a.L, M = MT ? MT : a.M, J = STAGED ? a.Smax + 1 : 1, nw = blockDim.x >> 6, W = L + 1;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -968,8 +974,8 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
         const int p = quot(i, inv), dd = i - p * M + 1;
         int r = p;
-        if (p >= 1 && p <= u) { r = reach_back<true, SUM>(e.pr, M, p, dd, tau); mostP = imax(mostP, (p - r) * M / dd); }
-        else if (p >= v && p < L) { r = reach_on(e.pr, L, M, p, dd, tau); mostS = imax(mostS, (r - p) * M / dd); }
+        if (p >= 1 && p <= u) { r = reach_back<true, SUM>(e.pr, M, PAD ? M | 1 : M, p, dd, tau); mostP = imax(mostP, (p - r) * M / dd); }
+        else if (p >= v && p < L) { r = reach_on(e.pr, L, M, PAD ? M | 1 : M, p, dd, tau); mostS = imax(mostS, (r - p) * M / dd); }
         e.reach[i] = (unsigned char)r;
     }
 #pragma unroll
@@ -998,8 +1004,8 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
             }
             wg_sync();
             for (int r = 1; r <= imax(lenP, lenS); ++r) {
-                if (!mir) { if (r <= lenP) gpu_row<false, STAGED, MT, SUM>(a, e, r, nd, jd, tau, 1.0, ptau * tau, e.pool, th, nth); }
-                else      { if (r <= lenS) gpu_row<true, STAGED, MT, SUM>(a, e, r, nd, jd, tau, 2.0, stau * tau, e.pool + second, th, nth); }
+                if (!mir) { if (r <= lenP) gpu_row<false, STAGED, MT, SUM, PAD>(a, e, r, nd, jd, tau, 1.0, ptau * tau, e.pool, th, nth); }
+                else      { if (r <= lenS) gpu_row<true, STAGED, MT, SUM, PAD>(a, e, r, nd, jd, tau, 2.0, stau * tau, e.pool + second, th, nth); }
                 wg_sync();
             }
             for (int i = threadIdx.x; i < (cendP + cendS) * M * J; i += blockDim.x) {
@@ -1032,6 +1038,9 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
         }
         // long walks of few tables: more lanes per walk rather than idle waves
         if (!STAGED) while (slots > 1 && slots * 4 > fit && imax(bandP, bandS) > 16) { slots >>= 1; ++lgxs; }
+        // fewer tables for every wave, or as many for fewer waves: whichever are more (57 layers x 8 GPUs, 40 nodes 592 -> 514 us)
+        const int each = imin(slots, fit / nw);
+        if (!STAGED && each * nw > imin(nw, fit / slots) * slots) slots = each;
         waves = imin(waves, imax(1, fit / slots));
         if (wave < waves) {
             double *mine = G + (size_t)wave * slots * table;
@@ -1041,8 +1050,8 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
                 int side, i;
                 if (item < both) { side = item & 1; i = item >> 1; }
                 else { side = nS > nP; i = item - (both >> 1); }
-                if (!side) one_node_tables<false, STAGED, MT, SUM>(a, e, lenP, bandP, tau, 1.0, ptau * tau, WP, e.GU, mine, i * slots, slots, lgxs, gbits);
-                else       one_node_tables<true, STAGED, MT, SUM>(a, e, lenS, bandS, tau, 2.0, stau * tau, WS, e.GU + bandP * gu, mine, i * slots, slots, lgxs, gbits);
+                if (!side) one_node_tables<false, STAGED, MT, SUM, PAD>(a, e, lenP, bandP, tau, 1.0, ptau * tau, WP, e.GU, mine, i * slots, slots, lgxs, gbits);
+                else       one_node_tables<true, STAGED, MT, SUM, PAD>(a, e, lenS, bandS, tau, 2.0, stau * tau, WS, e.GU + bandP * gu, mine, i * slots, slots, lgxs, gbits);
             }
         }
     }
@@ -1082,7 +1091,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     return true;
 }
 
-template <bool STAGED, int MT, bool SUM>
+template <bool STAGED, int MT, bool SUM, bool PAD>
 __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_exact_eval(Args a, int mode, int lds_doubles, int picks) {
     HIP_DYNAMIC_SHARED(double, s_dyn)
     __shared__ unsigned s_next;
@@ -1091,8 +1100,8 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     const int L = a.L, M = a.M, count = a.n_max - a.n_min + 1, J = STAGED ? a.Smax + 1 : 1, tid = threadIdx.x;
     if (idle) return;
     Eval e;
-    e.pr = load_prof<SUM>(a, s_dyn);
-    double *p = s_dyn + prof_doubles(L, M, SUM);
+    e.pr = load_prof<SUM>(a, s_dyn, PAD ? a.M | 1 : a.M);
+    double *p = s_dyn + prof_doubles(L, M, PAD ? M | 1 : M, SUM);
     e.reach = (unsigned char *)p; p += ((size_t)(L + 1) * M + 7) / 8;
     e.NP = p;     p += 2 * (size_t)(L + 2) * J;
     e.OUT = p; p += 2 * (size_t)a.nodes * M * J;
@@ -1173,7 +1182,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                 if (nhi == 0) continue;
             }
         }
-        if (!evaluate<STAGED, MT, SUM>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
+        if (!evaluate<STAGED, MT, SUM, PAD>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
             // (not the first picks: the filter keeps those that matter, so each entry comes here once at most)
             if (STAGED && mode != kFirst && tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
             continue;
@@ -1344,7 +1353,7 @@ static bool exact_limit_binds(int L, int n_max, int M, int Nb) { return Nb > 0 &
 
 // LDS of the fast path, 0: none for this shape.
 static oob_exact::EvalLds exact_lds(int L, int M, int n_max, int count, int Nb, bool staged) {
-    if (!staged && !oob_exact::in_doubles(L, M, n_max, count)) return {0, false};
+    if (!staged && !oob_exact::in_doubles(L, M, n_max, count)) return {0, false, false};
     const bool counts = staged && exact_limit_binds(L, n_max, M, Nb);
     return oob_exact::eval_lds(L, M, n_max, count, counts ? exact_smax(L, n_max, M, Nb) + 1 : 1, counts);
 }
@@ -1369,35 +1378,42 @@ extern "C" size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per
     return layout(L, gpus_per_node, n_max, exact_lds(L, gpus_per_node, n_max, n_max, microbatches, true).bytes != 0, mus, true).slots + slots * slot;
 }
 
-template <bool STAGED, int MT, bool SUM>
+template <bool STAGED, int MT, bool SUM, bool PAD>
 static int eval_launch_m(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
     using namespace oob_exact;
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT, SUM>,
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT, SUM, PAD>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return OOB_EHIP;
-    hipLaunchKernelGGL((k_exact_eval<STAGED, MT, SUM>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
+    hipLaunchKernelGGL((k_exact_eval<STAGED, MT, SUM, PAD>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
     return OOB_OK;
 }
 template <bool STAGED> // a kernel of its own for the usual numbers of GPUs per node, known to the compiler
 static int eval_launch(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
-    if constexpr (!STAGED) if (a.sums) return eval_launch_m<false, 0, true>(a, mode, grid, threads, lds, picks, st);
+    if constexpr (!STAGED) {
+        if (a.sums) return eval_launch_m<false, 0, true, false>(a, mode, grid, threads, lds, picks, st);
+        if (a.eval_pad) switch (a.M) {
+        case 2: return eval_launch_m<false, 2, false, true>(a, mode, grid, threads, lds, picks, st);
+        case 4: return eval_launch_m<false, 4, false, true>(a, mode, grid, threads, lds, picks, st);
+        case 8: return eval_launch_m<false, 8, false, true>(a, mode, grid, threads, lds, picks, st);
+        }
+    }
     switch (a.M) {
-    case 1: return eval_launch_m<STAGED, 1, false>(a, mode, grid, threads, lds, picks, st);
-    case 2: return eval_launch_m<STAGED, 2, false>(a, mode, grid, threads, lds, picks, st);
-    case 4: return eval_launch_m<STAGED, 4, false>(a, mode, grid, threads, lds, picks, st);
-    case 8: return eval_launch_m<STAGED, 8, false>(a, mode, grid, threads, lds, picks, st);
-    default: return eval_launch_m<STAGED, 0, false>(a, mode, grid, threads, lds, picks, st);
+    case 1: return eval_launch_m<STAGED, 1, false, false>(a, mode, grid, threads, lds, picks, st);
+    case 2: return eval_launch_m<STAGED, 2, false, false>(a, mode, grid, threads, lds, picks, st);
+    case 4: return eval_launch_m<STAGED, 4, false, false>(a, mode, grid, threads, lds, picks, st);
+    case 8: return eval_launch_m<STAGED, 8, false, false>(a, mode, grid, threads, lds, picks, st);
+    default: return eval_launch_m<STAGED, 0, false, false>(a, mode, grid, threads, lds, picks, st);
     }
 }
 
-template <int MT>
+template <int MT, bool PAD>
 static int bounds_launch(const oob_exact::Args &a, int mus, size_t lds, hipStream_t st) {
     using namespace oob_exact;
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_bounds<MT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_bounds<MT, PAD>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                (int)lds) != hipSuccess)
         return OOB_EHIP;
     const unsigned nb = (unsigned)((tri(a.L) * a.M + bucket_least(a.nk) - 1) / bucket_least(a.nk));
-    hipLaunchKernelGGL(k_exact_bounds<MT>, dim3(nb < (unsigned)kMaxBuckets ? nb : (unsigned)kMaxBuckets), dim3(kBoundThreads), lds, st, a, mus);
+    hipLaunchKernelGGL((k_exact_bounds<MT, PAD>), dim3(nb < (unsigned)kMaxBuckets ? nb : (unsigned)kMaxBuckets), dim3(kBoundThreads), lds, st, a, mus);
     return OOB_OK;
 }
 
@@ -1423,9 +1439,11 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
     const size_t lds = ev.bytes;
     a.fast = lds != 0;
     a.sums = ev.sums;
+    a.eval_pad = ev.pad && tri(L) * M > (size_t)kDirectMax; // (short models: 61 us either way, 62 padded, 15 layers)
     a.staged = staged;
     const size_t ntri = tri(L) * M;
     const int mus = bound_mus(L, M, counts);
+    a.bounds_pad = bound_pad(L, M, mus);
     a.bounds = a.fast && ntri > (size_t)kDirectMax && count <= kMaxCount && mus > 0;
     char *ws = (char *)dev_workspace;
     const Layout y = layout(L, M, n_max, a.fast, mus, staged);
@@ -1456,13 +1474,16 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
         const int threads = eval_threads(L, M, counts);
         const unsigned fill = (unsigned)(256 * imax(1, imin((int)(kLdsLimit / lds), 1024 / threads))); // workgroups the GPU holds at once
         if (a.bounds) {
-            const size_t bl = 8 * bound_doubles(L, M, mus);
-            switch (M) {
-            case 1: rc = bounds_launch<1>(a, mus, bl, st); break;
-            case 2: rc = bounds_launch<2>(a, mus, bl, st); break;
-            case 4: rc = bounds_launch<4>(a, mus, bl, st); break;
-            case 8: rc = bounds_launch<8>(a, mus, bl, st); break;
-            default: rc = bounds_launch<0>(a, mus, bl, st); break;
+            const size_t bl = 8 * bound_doubles(L, M, mus, a.bounds_pad);
+            switch (M * 2 + a.bounds_pad) {
+            case 2: rc = bounds_launch<1, false>(a, mus, bl, st); break;
+            case 4: rc = bounds_launch<2, false>(a, mus, bl, st); break;
+            case 5: rc = bounds_launch<2, true>(a, mus, bl, st); break;
+            case 8: rc = bounds_launch<4, false>(a, mus, bl, st); break;
+            case 9: rc = bounds_launch<4, true>(a, mus, bl, st); break;
+            case 16: rc = bounds_launch<8, false>(a, mus, bl, st); break;
+            case 17: rc = bounds_launch<8, true>(a, mus, bl, st); break;
+            default: rc = bounds_launch<0, false>(a, mus, bl, st); break;
             }
             if (rc != OOB_OK) return rc;
             // no more than ten: the entries of the later ranks have the slow stages that take longest to evaluate (16: 584

@@ -30,18 +30,20 @@ OOB_HD inline size_t tri(int L) { return (size_t)L * (L + 1) / 2; }
 OOB_HD inline int imin(int a, int b) { return a < b ? a : b; }
 OOB_HD inline int imax(int a, int b) { return a > b ? a : b; }
 
-// The profile in LDS (see Prof), in doubles.
-OOB_HD inline size_t prof_doubles(int L, int M, bool sums = false) {
-    return (sums ? 1 : 2) * (size_t)(L + 1) * M + (L + 1) + ((size_t)(L + 1) * M + 7) / 8;
+// Two, four and eight GPUs per node, the usual even numbers, have kernels with the rows of the profile padded to an odd number of doubles.
+OOB_HD inline bool can_pad(int M) { return M == 8; }
+// The profile in LDS (see Prof) with rows of ms doubles, in doubles.
+OOB_HD inline size_t prof_doubles(int L, int M, int ms, bool sums = false) {
+    return (sums ? 1 : 2) * (size_t)(L + 1) * ms + (L + 1) + ((size_t)(L + 1) * M + 7) / 8;
 }
 // Entries of a band matrix with rows r = 1 .. band and columns 0 .. len - r.
 OOB_HD inline size_t band_size(int band, int len) { return (size_t)band * len - (size_t)band * (band - 1) / 2; }
 
 // Tables of k_exact_eval beside its pool: profile, reach, NP, OUT (see Eval) and the minima, in doubles.  No pipeline has
 // more nodes than layers.
-OOB_HD inline size_t eval_fixed(int L, int M, int n_max, int count, int J, bool sums = false) {
+OOB_HD inline size_t eval_fixed(int L, int M, int n_max, int count, int J, bool sums = false, bool pad = false) {
     const int nodes = imin(n_max, L);
-    return prof_doubles(L, M, sums) + ((size_t)(L + 1) * M + 7) / 8 + 2 * (size_t)(L + 2) * J + 2 * (size_t)nodes * M * J + 8 +
+    return prof_doubles(L, M, pad ? M | 1 : M, sums) + ((size_t)(L + 1) * M + 7) / 8 + 2 * (size_t)(L + 2) * J + 2 * (size_t)nodes * M * J + 8 +
            imin(count, nodes);
 }
 // Its pool for any slowest stage without stage counts, in doubles: the covers next to it, both W and one one-node table,
@@ -68,18 +70,22 @@ inline bool in_doubles(int L, int M, int n_max, int count) {
 // shape takes the general path), at the latest with the ends of the stages added up where they are read; every
 // shape of in_doubles() fits.  With stage counts whatever is left for them, entries beyond that take
 // the general path one by one.
-struct EvalLds { size_t bytes; bool sums; };
+// The rows of the profile are padded where that costs no workgroup of a compute unit.
+struct EvalLds { size_t bytes; bool sums, pad; };
 inline EvalLds eval_lds(int L, int M, int n_max, int count, int J, bool staged) {
-    if (staged) return {M <= 8 && 8 * eval_fixed(L, M, n_max, count, J) + 48 * 1024 <= kLdsLimit - kLdsStatic ? kLdsLimit - kLdsStatic : 0, false};
+    if (staged) return {M <= 8 && 8 * eval_fixed(L, M, n_max, count, J) + 48 * 1024 <= kLdsLimit - kLdsStatic ? kLdsLimit - kLdsStatic : 0, false, false};
     for (const bool sums : {false, true}) {
-        const size_t all = (8 * (eval_fixed(L, M, n_max, count, 1, sums) + eval_pool(L, M)) + 15) & ~(size_t)15;
-        if (all + kLdsStatic > kLdsLimit) continue;
         // as many workgroups per compute unit as the registers allow (sixteen waves) and their tables leave room for: a share
-        // less its static arrays is never below `all`
-        const size_t most = 1024 / eval_threads(L, M, false), k = kLdsLimit / (all + kLdsStatic);
-        return {(kLdsLimit / (k < most ? k : most) - kLdsStatic) & ~(size_t)15, sums};
+        // less its static arrays is never below what they take
+        auto shares = [&](bool pad) {
+            const size_t all = (8 * (eval_fixed(L, M, n_max, count, 1, sums, pad) + eval_pool(L, M)) + 15) & ~(size_t)15;
+            const size_t most = 1024 / eval_threads(L, M, false), k = kLdsLimit / (all + kLdsStatic);
+            return k < most ? k : most;
+        };
+        const size_t k = shares(false);
+        if (k) return {(kLdsLimit / k - kLdsStatic) & ~(size_t)15, sums, !sums && can_pad(M) && shares(true) == k};
     }
-    return {0, false};
+    return {0, false, false};
 }
 
 // No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second
@@ -92,7 +98,7 @@ constexpr int kLambdas = 8, kMus = 8;
 // Least entries per bucket (more only where that would exceed kMaxBuckets).  With the lambdas alone a smaller bucket pays:
 // its bounds are tighter and the workgroups of 64 leave compute units idle.  How much hangs on the instance (which
 // stages are evaluated): timed in turn, 32 against 64, 24 jobs of 34-97 layers 0.93 of the time (0.53 to 1.17), eight of 98
-// layers x 8 GPUs 0.97 (0.83 to 1.09); the bounds themselves take 212 instead of 170 us there.
+// layers x 8 GPUs 0.97 (0.83 to 1.09); the bounds themselves took 212 instead of 170 us there, with rows of eight doubles.
 // With eight mus the bounds are a quarter of the time and it does not (48 layers, limit binding: 3.05 and 3.30 ms).
 OOB_HD inline int bucket_least(int multipliers) { return multipliers > kLambdas ? 64 : 32; }
 
@@ -103,14 +109,19 @@ struct Head {
 inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // LDS of k_exact_bounds in doubles.
-OOB_HD inline size_t bound_doubles(int L, int M, int mus) {
-    return prof_doubles(L, M) + 2 * (((size_t)(L + 1) * M + 7) / 8) + (size_t)mus * kLambdas * 2 * (L + 1) +
+OOB_HD inline size_t bound_doubles(int L, int M, int mus, bool pad = false) {
+    return prof_doubles(L, M, pad ? M | 1 : M) + 2 * (((size_t)(L + 1) * M + 7) / 8) + (size_t)mus * kLambdas * 2 * (L + 1) +
            kBucket * kMaxCount / 2 + 32;
 }
 inline int bound_mus(int L, int M, bool staged) {
     int mus = staged ? kMus : 1;
     while (mus > 1 && 8 * bound_doubles(L, M, mus) > kLdsLimit - kLdsStatic) --mus;
     return 8 * bound_doubles(L, M, mus) <= kLdsLimit - kLdsStatic ? mus : 0;
+}
+// The rows of the profile of k_exact_bounds are padded where that costs no workgroup of a compute unit (two of nine waves at most).
+inline bool bound_pad(int L, int M, int mus) {
+    auto shares = [&](bool pad) { return imin(2, (int)(kLdsLimit / (8 * bound_doubles(L, M, mus, pad) + kLdsStatic))); };
+    return can_pad(M) && shares(true) == shares(false);
 }
 struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blo, bfew, blb, barg, list, over, slots; };
 inline Layout layout(int L, int M, int n_max, bool fast, int mus, bool staged) { // mus: of the stage limit, 0: no bounds

@@ -29,7 +29,7 @@ int smallest_surplus(int L, int M) {
             const EvalLds e = eval_lds(L, M, n, count, 1, false);
             if (e.bytes == 0) { if (in_doubles(L, M, n, count)) return -2; else continue; }
             if (e.bytes > kLdsLimit - kLdsStatic) return -1;
-            const long long pool = (long long)(e.bytes / 8) - (long long)eval_fixed(L, M, n, count, 1, e.sums);
+            const long long pool = (long long)(e.bytes / 8) - (long long)eval_fixed(L, M, n, count, 1, e.sums, e.pad);
             const long long surplus = pool - (long long)tables;
             if (surplus < least) least = (int)surplus;
         }
@@ -40,6 +40,8 @@ int sums(int L, int M, int n_max) {
     const EvalLds e = eval_lds(L, M, n_max, n_max, 1, false);
     return e.bytes ? e.sums : -1;
 }
+// whether the rows of the profile of (L, M, n_max) are padded in the evaluation
+int padded(int L, int M, int n_max) { return eval_lds(L, M, n_max, n_max, 1, false).pad; }
 // offsets in the workspace of a job that takes the LDS path: times and stages of the list, its bounds, the leftovers
 void offsets(int L, int M, int n_max, int counts, int staged, size_t *at) {
     const Layout y = layout(L, M, n_max, true, bound_mus(L, M, counts), staged);

@@ -278,6 +278,20 @@ def test_shares_of_the_lds_that_just_hold_the_tables(P, shape):
         assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
 
 
+@pytest.mark.parametrize("shape,padded", [((32, 8, 1, 4, 0), 1), ((31, 8, 1, 4, 0), 1), ((59, 8, 1, 60, 0), 0), ((61, 8, 1, 60, 0), 1),
+                                          ((58, 8, 2, 18, 60), 1), ((36, 8, 1, 25, 49), 1), ((40, 4, 1, 9, 0), 0)])
+def test_padded_and_plain_rows_of_the_profile(P, sizes, shape, padded):
+    """Eight GPUs per node: rows of nine doubles, or of eight where nine would cost a workgroup of a compute unit (and in jobs
+    without bounds, up to 31 layers); one-node tables shared out evenly to the waves where they do not all fit."""
+    L, M, n_min, n_max, nb = shape
+    assert sizes.padded(L, M, n_max) == padded
+    for var in ("plain", "tight", "forbid"):
+        inp = inputs.random_small(23, L, M, n_min, n_max, nb, f=1, tight_mem=(var == "tight"), forbid_some_d=(var == "forbid"))
+        print("case", shape, var, flush=True)
+        st, got = P.ExactMinimum(inp).run()
+        assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
+
+
 @pytest.mark.parametrize("shape", [(72, 64, 1, 1, 0), (105, 32, 1, 2, 105), (142, 16, 1, 2, 0), (167, 8, 1, 3, 167), (178, 5, 1, 2, 0)])
 def test_tables_in_lds_without_the_ends_of_the_stages(P, sizes, shape):
     """The largest shapes whose times are held as doubles: their tables leave no room for the ends of the
