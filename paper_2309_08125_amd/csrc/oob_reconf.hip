@@ -3,7 +3,7 @@
 // One lane runs one failure sequence.  A trajectory's state is small (at most 64 pipeline sizes
 // and a 64-bit mask of the list positions still in use), but it is indexed by data.  Up to 16 pipelines
 // and 128 nodes the sizes are bytes in registers and every search over the list works on whole
-// words (run_in_registers); beyond that (run_in_lds) the sizes live in LDS, one column per lane (sizes[position][lane], 16 bits, as many rows as there are
+// words (run_single_losses where a step loses one node, run_in_registers for bursts); beyond that (run_in_lds) the sizes live in LDS, one column per lane (sizes[position][lane], 16 bits, as many rows as there are
 // starting pipelines), so that the lanes of a wave never share a bank row for the same position,
 // and the mask lives in a register pair.  A list position whose pipeline was absorbed keeps size
 // 0, so the two loops that run at every step (which pipeline holds the failing node; who can
@@ -163,10 +163,9 @@ __device__ void run_in_lds(const Args &a, long long t, unsigned short *mine) {
 // most kPackedNodes = 128 nodes (a running sum of sizes then fits its byte, and (128 | r) - sum neither borrows
 // nor loses its top bit) and at most 4 W starting pipelines.
 //
-// What bounds it: the vector ALUs (176 instructions a wave and step) at first, the 8 bytes a step moves next.  With the
-// sizes in LDS a step read every position twice from there and the merge, which some lane of a wave needs at almost
-// every step, walked the list position by position: 318 us for 2^20 sequences of 57 steps with 13 pipelines,
-// against 258 us here.
+// What bounds it: the vector ALUs (176 instructions a wave and loss) at first, the 8 bytes a loss moves next.  With the
+// sizes in LDS a step read every position twice from there and the merge walked the list position by position: 318 us
+// for 2^20 sequences of 57 losses of one node with 13 pipelines, against 258 us here.
 constexpr unsigned kTops = 0x80808080u;
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned pk_max(unsigned x, unsigned y) {
@@ -323,6 +322,164 @@ template <int W> __device__ void run_in_registers(const Args &a, long long t) {
     write_summary(a, t, survived, sum_reinst, sum_borrowed, sum_merges, __popc(alive), (int)total, viol, stop);
 }
 
+// Steps of one node (burst 1), in registers, W words, at most kPackedNodes nodes and 4 W starting pipelines.
+//
+// What one loss can do is narrow: every pipeline has n0 nodes or more before it.  The pipeline that is hit either keeps
+// n0, or takes one node from a lender, so that the lender is the one that loses the node, or, where all have exactly
+// n0, absorbs the first other pipeline in the list (all are equally small), once.  So nodes left, pipelines left, the
+// steps that merge (nodes left == n0 x pipelines left), the step that stops and every violation are the same for all
+// sequences: they are scalars.  A step without a merge takes one node from one list position.
+//
+// The state is the running sums of the sizes, a byte each: position i in byte i / W of word i % W, so that a size is a byte
+// of the difference of two words.  A comparison of all positions with one number is an add (the carry into a
+// byte's top bit) per word; gathered into one 32-bit mask (bit 8 (i / W) + 4 + i % W, ascending with i) its lowest set bit
+// is the first position in list order, and -bit the positions whose running sum changes.
+// The largest size needs no search: it falls by one when the last position that has it loses a node, and is 2 n0 - 1
+// after a merge.
+//
+// What bounds it: the vector ALUs (about 85 instructions a wave and step) and the 8 bytes a step moves, about equally.
+// 2^20 sequences of 57 steps with 13 pipelines: 257 us with run_in_registers (176 instructions, its merge among them:
+// all lanes merge at the same steps, but it tests lane by lane), 123 us here (4.5 TB/s).  Draws and words by ordinary
+// loads and stores 129 us, eight steps a group 139 us.
+constexpr int kGroup = 4; // steps whose draws are read, and whose trace words are stored, together
+
+template <int W> struct Sums {
+    static constexpr unsigned kOnes = 0x01010101u;
+    unsigned p[W];
+    // Bit mask of the positions whose top bit is set in word[k] + add.
+    static __device__ __forceinline__ unsigned gather(const unsigned (&word)[W], unsigned add) {
+        unsigned m = 0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) m |= ((word[k] + add) >> (3 - k)) & (kTops >> (3 - k));
+        return m;
+    }
+    __device__ __forceinline__ void sizes(unsigned (&d)[W]) const {
+        d[0] = p[0] - (p[W - 1] << 8);
+#pragma unroll
+        for (int k = 1; k < W; ++k) d[k] = p[k] - p[k - 1];
+    }
+    // One node less at the first position of `from`, a mask of that position and all behind it.
+    __device__ __forceinline__ void lose(unsigned from) {
+#pragma unroll
+        for (int k = 0; k < W; ++k) p[k] -= (from >> (4 + k)) & kOnes;
+    }
+    __device__ __forceinline__ void add(unsigned where, int nodes) {
+#pragma unroll
+        for (int k = 0; k < W; ++k) p[k] += ((where >> (4 + k)) & kOnes) * (unsigned)nodes;
+    }
+};
+
+template <int W> __device__ void run_single_losses(const Args &a, long long nodes) {
+    const unsigned n0 = (unsigned)a.n0;
+    Sums<W> sum;
+    unsigned at_most = 0, alive = 0; // largest size; list positions in use
+    {
+        unsigned run = 0;
+#pragma unroll
+        for (int k = 0; k < W; ++k) sum.p[k] = 0;
+#pragma unroll
+        for (int i = 0; i < 4 * W; ++i) {
+            const unsigned s = i < a.c0 ? (unsigned)__builtin_amdgcn_readfirstlane(a.sizes0[i]) : 0u;
+            run += s;
+            sum.p[i % W] |= run << (8 * (i / W));
+            at_most = s > at_most ? s : at_most;
+            alive |= i < a.c0 ? 1u << (8 * (i / W) + 4 + i % W) : 0u;
+        }
+    }
+    constexpr unsigned kOnes = Sums<W>::kOnes;
+    unsigned total = (unsigned)__builtin_amdgcn_readfirstlane((int)nodes); // <= 128
+    unsigned left = (unsigned)a.c0;                               // pipelines left
+    const unsigned need = (unsigned)(a.f + 1) * n0;               // fewer nodes: training stops
+    const unsigned can_lend = (127u - n0) * kOnes;                // sets the top bit of sizes above n0
+    unsigned largest = (128u - at_most) * kOnes;                  // ... of the largest size
+    unsigned borrowed = 0;
+    int stop = OOB_RECONF_STOP_NONE, survived = 0;
+
+    const long long block = (long long)blockIdx.x * kLanes;       // the same for all lanes, as every row below
+    const unsigned *draws = a.draws + block;
+    unsigned *trace = a.trace ? a.trace + block : nullptr;
+    const int lane = threadIdx.x;
+    unsigned draw[kGroup], word[kGroup];
+#pragma unroll
+    for (int e = 0; e < kGroup; ++e) draw[e] = e < a.steps ? __builtin_nontemporal_load(draws + e * a.T + lane) : 0u;
+
+    // A group's trace words are stored, and the next group's draws read, at the head of the group that follows.
+    int step = 0;
+    for (; step < a.steps && stop == OOB_RECONF_STOP_NONE; step += kGroup) {
+        draws += kGroup * a.T;
+        if (step > 0 && trace) {
+#pragma unroll
+            for (int e = 0; e < kGroup; ++e) __builtin_nontemporal_store(word[e], trace + e * a.T + lane);
+            trace += kGroup * a.T;
+        }
+        unsigned next[kGroup];
+#pragma unroll
+        for (int e = 0; e < kGroup; ++e)
+            next[e] = step + kGroup + e < a.steps ? __builtin_nontemporal_load(draws + e * a.T + lane) : 0u;
+#pragma unroll
+        for (int e = 0; e < kGroup; ++e) {
+            if (step + e < a.steps && stop == OOB_RECONF_STOP_NONE) {
+                const unsigned r = __umulhi(draw[e], total); // floor(draw * total / 2^32) < total
+                const unsigned c = 127u - r;
+                // running sums above r: the pipeline that holds node r and all behind it
+                const unsigned over = Sums<W>::gather(sum.p, __builtin_amdgcn_perm(c, c, 0u));
+                const unsigned hit = over & (0u - over);
+                if (total - 1 < need) { // stops, repairs nothing
+                    stop = OOB_RECONF_STOP_TOO_FEW_NODES;
+                    sum.lose(over);
+                    word[e] = left << 23 | (unsigned)stop << 30;
+                } else if (total == left * n0) { // nobody can lend: absorb the first other pipeline
+                    const unsigned others = alive & ~hit, other = others & (0u - others);
+                    sum.lose(over);
+                    sum.add(over ^ (0u - other), other < hit ? -(int)n0 : (int)n0);
+                    alive &= ~other;
+                    largest = (128u - (2 * n0 - 1)) * kOnes;
+                    --left;
+                    ++survived;
+                    word[e] = 1u << 16 | left << 23;
+                } else {
+                    unsigned size[W];
+                    sum.sizes(size);
+                    const bool keeps = (hit & Sums<W>::gather(size, can_lend)) != 0;
+                    const unsigned most = Sums<W>::gather(size, largest);
+                    const unsigned loser = keeps ? hit : most & (0u - most);
+                    sum.lose(0u - loser);
+                    largest += (most & ~loser) == 0 ? kOnes : 0u;
+                    borrowed += keeps ? 0u : 1u;
+                    ++survived;
+                    word[e] = (keeps ? 1u : 1u << 8) | left << 23;
+                }
+                --total;
+            } else {
+                word[e] = left << 23 | (unsigned)stop << 30;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kGroup; ++e) draw[e] = next[e];
+    }
+    // the last group's words, then those of the steps after the stop
+    if (a.trace && a.steps > 0) {
+        const int done = step - kGroup;
+#pragma unroll
+        for (int e = 0; e < kGroup; ++e)
+            if (done + e < a.steps) __builtin_nontemporal_store(word[e], trace + e * a.T + lane);
+        trace += kGroup * a.T;
+        const unsigned idle = left << 23 | (unsigned)stop << 30;
+        for (; step < a.steps; ++step, trace += a.T) __builtin_nontemporal_store(idle, trace + lane);
+    }
+
+    const long long t = block + lane;
+    unsigned size[W];
+    sum.sizes(size);
+    if (a.final_sizes)
+#pragma unroll
+        for (int i = 0; i < 4 * W; ++i)
+            if (i < a.c0) a.final_sizes[(long long)i * a.T + t] = (int)(size[i % W] >> (8 * (i / W)) & 255u);
+    const int merges = a.c0 - (int)left;
+    const int viol = (merges > 0 && 2 * a.n0 - 1 > a.n_hi ? 1 : 0) | (survived > 0 && (int)left < a.f + 1 ? 2 : 0);
+    write_summary(a, t, survived, survived - merges - (int)borrowed, (int)borrowed, merges, (int)left, (int)total, viol, stop);
+}
+
 // W: words of packed sizes, 0 for more than 16 starting pipelines.  The number of nodes is in device memory: a list of
 // more than kPackedNodes takes the sizes in LDS, the same branch for every lane.
 template <int W> __global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
@@ -334,7 +491,8 @@ template <int W> __global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
     if (!ok || t >= a.T) return;
     if constexpr (W > 0) {
         if (nodes <= kPackedNodes) {
-            run_in_registers<W>(a, t);
+            if (a.burst == 1) run_single_losses<W>(a, nodes);
+            else run_in_registers<W>(a, t);
             return;
         }
     }

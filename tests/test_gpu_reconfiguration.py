@@ -108,6 +108,17 @@ def test_numbers_of_pipelines_and_nodes(P, count, burst):
         compare(P, sizes0.tolist(), n0, int(sizes0.max()), min(f, 8), inputs.failure_draws(count, nodes // burst + 1, burst, 130))
 
 
+@pytest.mark.parametrize("sizes0, n0, n_hi, f", [([128], 1, 128, 0), ([128], 128, 128, 0), ([64, 64], 64, 64, 1),
+                                                 ([1] * 16, 1, 1, 0), ([4, 4, 4, 5, 4], 4, 6, 1), ([9] + [8] * 14, 8, 9, 0)])
+def test_single_losses_in_registers(P, sizes0, n0, n_hi, f):
+    """One node a step: a byte that holds 128, a start that merges at once, merges down to one pipeline, templates too small
+    for a merged pipeline; step counts around a group of four, before and after the stop; ragged workgroups."""
+    N = sum(sizes0)
+    stop = max(1, N - (f + 1) * n0 + 1)
+    for steps, T in [(1, 1), (3, 255), (4, 257), (5, 64), (stop, 300), (stop + 1, 5), (stop + 7, 65)]:
+        compare(P, sizes0, n0, n_hi, f, inputs.failure_draws(steps, steps, 1, T), sample=range(0, T, max(1, T // 40)))
+
+
 def test_edge_cases(P):
     # no steps at all: the starting state comes back
     st, summary, final, trace = P.FailureSimulator([3, 4], 3, 5, 0, np.zeros((0, 1, 5), dtype=np.uint32)).run()
