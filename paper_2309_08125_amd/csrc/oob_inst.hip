@@ -223,14 +223,13 @@ template <typename CT> __device__ int count_planes(const Spec &s, CT *ring, cons
     return s.p + 1;
 }
 
-// Exclusive prefix over N' = N_lo..N_hi of the filtered list lengths C(p, N', f+1), by one wave.
-template <typename CT> __device__ void write_offsets(const Spec &s, const CT *ring, long long *offsets, int *status) {
-    const int QQ = s.Q + 1, len = s.N_hi - s.N_lo + 1, lane = threadIdx.x;
-    const CT *whole = ring + (s.p & (kGroup - 1)) * (s.N_hi + 1) * QQ;
+// Exclusive prefix over N' = N_lo..N_hi of the filtered list lengths C(p, N', f+1), at whole[N' * stride], by one wave.
+template <typename CT> __device__ void write_offsets(const Spec &s, const CT *whole, int stride, long long *offsets, int *status) {
+    const int len = s.N_hi - s.N_lo + 1, lane = threadIdx.x;
     long long run = 0;
     for (int i0 = 0; i0 < len; i0 += 64) {
         const int i = i0 + lane;
-        long long v = i < len ? (long long)whole[(s.N_lo + i) * QQ + s.Q] : 0;
+        long long v = i < len ? (long long)whole[(s.N_lo + i) * stride] : 0;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const long long u = __shfl_up(v, d, 64);
@@ -246,13 +245,172 @@ template <typename CT> __device__ void write_offsets(const Spec &s, const CT *ri
     }
 }
 
-__global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long long *offsets, int *status, int keep_wide) {
+// Inclusive scan over a wave; lanes without a source add zero (the form that becomes one addition with a lane move).
+template <int CTRL, int ROWS> __device__ __forceinline__ unsigned moved(unsigned v) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ float moved(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS> __device__ __forceinline__ double moved(double v) {
+    return __hiloint2double((int)moved<CTRL, ROWS>((unsigned)__double2hiint(v)), (int)moved<CTRL, ROWS>((unsigned)__double2loint(v)));
+}
+template <int N, typename T> __device__ __forceinline__ void scan_lanes(T (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += moved<0x111, 0xf>(v[i]); // row_shr 1, 2, 4, 8
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += moved<0x112, 0xf>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += moved<0x114, 0xf>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += moved<0x118, 0xf>(v[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += moved<0x142, 0xa>(v[i]); // lane 15 of a row to the row behind it
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += moved<0x143, 0xc>(v[i]); // lane 31 to the upper half
+}
+
+// The table in 32 bits by node counts instead of by sizes.  For one (N', q) the counts of all j are the running sums of
+// C(j, N' - n_{j-1}, max(q-1, 0)), so with j along the lanes a row is one scan of a wave, and it leaves as whole lines; and as many
+// node counts as the smallest size has nodes do not depend on each other.  A wave takes a few q's (a chunk) of one node count, one
+// barrier for all of a step.  Of size n the last n node counts are needed: they are kept in LDS, with room for a step's own.  An unfiltered
+// count (q = 0) is the largest of its row; it is carried in floating point too, which tells in the end whether 32 bits held
+// everything (a hundredth of the range is left for rounding: at most p + N' additions of relative error 2^-24).
+//
+// What bounds it: the chain of N_hi / side steps, each some hundred instructions of a wave, a read of LDS and a barrier: 0.4 us where
+// a SIMD has one wave, 0.7 us where it has four; 6 us for the launch and what stands before and after the steps.  As a
+// caller sees it, planes one after the other -> here: 57 sizes 8..64, f = 8, up to 128 nodes 43 -> 19 us (25 with a wave for all q's of a
+// node count), 63 sizes 2..64, f = 8 40 -> 25 us, 29 sizes 4..32, f = 4 14.5 -> 12.2 us.
+constexpr int kScanChunk = 6;          // most q's of a wave
+constexpr float kFits = 4252017623.0f; // 0.99 * 2^32
+constexpr int kCountWaves = kCountThreads / 64;
+// A step of the scans takes about as long as a plane of count_planes; there are N_hi / side steps and p planes, and the scans take
+// longer to set up.  Planes and scans: 28 sizes 3..30, 45 nodes (15 steps) 14.5 and 12.7 us, 39 sizes 2..40, 48 nodes (24 steps)
+// 18.8 and 16.9 us; but 15 sizes 2..16, 22 nodes (11 steps) 7.7 and 11.4 us, 40 sizes 1..40, 48 nodes (48 steps) 22.0 and 28.9 us.
+constexpr int kScanFixed = 10;
+
+// Where the kept counts are.  A row: C(., N', 0) once more, C(., N', q) for the q's of all chunks, the first in floating point.
+struct Scan {
+    int chunk, chunks, side, row; // q's of a chunk; chunks; node counts of a step; words of a row (odd: neighbours in other banks)
+    int base, len;                // of this lane's size: its first row, its rows (0: a lane without a size)
+    int need, none;               // words in all; the row of zeros that a lane without a size reads, the next one it writes
+};
+// False: does not apply.  Called by whole waves, the same result in all.
+__device__ bool scan_layout(const Spec &s, const int *size, int words, Scan *sc) {
+    const int lane = threadIdx.x & 63, QQ = s.Q + 1;
+    if (s.p > 63) return false;
+    sc->chunks = (QQ + kScanChunk - 1) / kScanChunk;
+    if (sc->chunks > kCountWaves) return false;
+    sc->chunk = (QQ + sc->chunks - 1) / sc->chunks;
+    sc->row = (sc->chunk * sc->chunks + 2) | 1;
+    sc->side = kCountWaves / sc->chunks < size[0] ? kCountWaves / sc->chunks : size[0];
+    const int n = lane >= 1 && lane <= s.p ? size[lane - 1] : 0;
+    sc->len = n ? (n < s.N_hi + 1 ? n : s.N_hi + 1) + sc->side : 0;
+    unsigned upto[1] = {(unsigned)sc->len}; // at most 63 * (1215 + 16) in all
+    scan_lanes(upto);
+    const int rows = __builtin_amdgcn_readlane((int)upto[0], 63);
+    sc->none = rows * sc->row;
+    sc->base = sc->len ? ((int)upto[0] - sc->len) * sc->row : sc->none;
+    sc->need = (rows + 2) * sc->row + s.N_hi + 1;
+    return sc->need <= words && s.p >= kScanFixed + s.N_hi / sc->side;
+}
+
+// Called by the whole workgroup.
+template <int CH> __device__ float scan_steps(const Spec &s, unsigned *lds, unsigned *whole, const Scan &sc) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int QQ = s.Q + 1, mine = wave % sc.side, q0 = wave / sc.side * CH;
+    const bool works = q0 < QQ, full = q0 + CH <= QQ; // wave / side < chunks is q0 < QQ
+    // words of this lane's rows, of the row of N' and of the row of N' - n (n is len - side), and what a step adds
+    const int words = sc.len ? sc.len * sc.row : 1, step = sc.len ? sc.side * sc.row : 0;
+    int put = sc.len ? mine * sc.row : 0, get = put + step >= words ? put + step - words : put + step;
+    const unsigned *const from = lds + sc.base + q0;
+    unsigned *const to = lds + (sc.len ? sc.base : sc.none + sc.row) + q0;
+    const bool last = lane == s.p, past = lane > s.p;
+    unsigned *out = s.cnt32 + (mine * QQ + q0) * s.R; // at most 2 432 rows of 64 counts
+    float most = 0;
+    for (int N0 = 0; N0 <= s.N_hi; N0 += sc.side) {
+        const int N = N0 + mine;
+        if (works && N <= s.N_hi) {
+            unsigned v[CH];
+            float f[1] = {0};
+#pragma unroll
+            for (int i = 0; i < CH; ++i) v[i] = from[get + i];
+            if (q0 == 0) {
+                f[0] = __uint_as_float(from[get + sc.row - 1]);
+                if (N == 0) { // C(0, 0, 0) = 1
+                    v[0] = lane == 0 ? 1u : v[0];
+                    f[0] = lane == 0 ? 1.0f : f[0];
+                }
+            }
+            scan_lanes(v);
+#pragma unroll
+            for (int i = 0; i < CH; ++i) to[put + i + 1] = v[i];
+            if (q0 == 0) {
+                to[put] = v[0];
+                scan_lanes(f);
+                to[put + sc.row - 1] = __float_as_uint(f[0]);
+                most = fmaxf(most, f[0]);
+            }
+            if (q0 + CH >= QQ && last)
+#pragma unroll
+                for (int i = 0; i < CH; ++i)
+                    if (q0 + i == s.Q) whole[N] = v[i];
+            if (lane < s.R) {
+#pragma unroll
+                for (int i = 0; i < CH; ++i)
+                    if (full || q0 + i < QQ) out[(unsigned)(i * s.R + lane)] = past ? 0xFFFFFFFFu : v[i];
+            }
+        }
+        out += sc.side * QQ * s.R;
+        put = put + step >= words ? put + step - words : put + step;
+        get = get + step >= words ? get + step - words : get + step;
+        __syncthreads();
+    }
+    return most;
+}
+
+// write_offsets where no count reaches 2^32: the sums stay exact in double precision, and nothing saturates.
+__device__ void write_narrow_offsets(const Spec &s, const unsigned *whole, long long *offsets, int *status) {
+    const int len = s.N_hi - s.N_lo + 1, lane = threadIdx.x;
+    double run = 0;
+    for (int i0 = 0; i0 < len; i0 += 64) {
+        const int i = i0 + lane;
+        const double own = i < len ? (double)whole[s.N_lo + i] : 0.0;
+        double v[1] = {own};
+        scan_lanes(v);
+        if (i < len) offsets[i] = (long long)(run + (v[0] - own));
+        run += __builtin_bit_cast(double, ((unsigned long long)(unsigned)__builtin_amdgcn_readlane(__double2hiint(v[0]), 63) << 32) |
+                                              (unsigned)__builtin_amdgcn_readlane(__double2loint(v[0]), 63));
+    }
+    if (lane == 0) {
+        offsets[len] = (long long)run;
+        *status = OOB_OK;
+    }
+}
+
+// Called by the whole workgroup.  True: the 32-bit table is complete, and `whole` holds C(p, N', f+1).
+__device__ bool count_by_scan(const Spec &s, unsigned *lds, unsigned *whole, const Scan &sc, unsigned *top) {
+    for (int e = threadIdx.x; e < sc.need; e += kCountThreads) lds[e] = 0;
+    __syncthreads();
+    const float most = sc.chunk == 2   ? scan_steps<2>(s, lds, whole, sc)
+                       : sc.chunk == 3 ? scan_steps<3>(s, lds, whole, sc)
+                       : sc.chunk == 4 ? scan_steps<4>(s, lds, whole, sc)
+                       : sc.chunk == 5 ? scan_steps<5>(s, lds, whole, sc)
+                                       : scan_steps<kScanChunk>(s, lds, whole, sc);
+    atomicMax(top, __float_as_uint(most)); // not negative: ordered as integers are
+    __syncthreads();
+    return __uint_as_float(*top) < kFits;
+}
+static_assert(kScanChunk == 6, "count_by_scan names every size of a chunk; a Q of at least 1 makes chunks of two or more");
+
+// SCAN: the table may be counted by count_by_scan, if the sizes allow it (which the host does not see where they are a list).
+template <bool SCAN> __global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long long *offsets, int *status, int keep_wide, int lds_words) {
     HIP_DYNAMIC_SHARED(unsigned long long, s_ring) // [kGroup][plane]: plane j at slot j % kGroup
     __shared__ int s_size[OOB_INST_MAX_P];
     __shared__ int s_bad;
     __shared__ unsigned long long s_max;
-    __shared__ unsigned s_max32;
-    if (threadIdx.x == 0) { s_bad = 0; s_max = 0; s_max32 = 0; }
+    __shared__ unsigned s_max32, s_maxf;
+    if (threadIdx.x == 0) { s_bad = 0; s_max = 0; s_max32 = 0; s_maxf = 0; }
     for (int j = threadIdx.x; j < s.p; j += kCountThreads) s_size[j] = size_of(s, j);
     __syncthreads();
     for (int j = threadIdx.x; j < s.p; j += kCountThreads)
@@ -268,11 +426,23 @@ __global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long 
     int base = 0; // of the planes to count in 64 bits
     if (!keep_wide) {
         unsigned *ring = reinterpret_cast<unsigned *>(s_ring);
+        if constexpr (SCAN) {
+            Scan sc;
+            if (scan_layout(s, s_size, lds_words, &sc)) { // uniform
+                unsigned *whole = ring + sc.need - (s.N_hi + 1);
+                if (count_by_scan(s, ring, whole, sc, &s_maxf)) {
+                    if (threadIdx.x < 64) write_narrow_offsets(s, whole, offsets, status);
+                    if (threadIdx.x == 0) *s.narrow = 1;
+                    return;
+                }
+                __syncthreads(); // the LDS is used anew
+            }
+        }
         for (int e = threadIdx.x; e < plane; e += kCountThreads) ring[e] = e == 0 ? 1 : 0; // C(0, ., .)
         __syncthreads();
         base = count_planes(s, ring, s_size, 0, &s_max32);
         if (base > s.p) { // uniform: every count fits
-            if (threadIdx.x < 64) write_offsets(s, ring, offsets, status);
+            if (threadIdx.x < 64) write_offsets(s, ring + (s.p & (kGroup - 1)) * plane + s.Q, s.Q + 1, offsets, status);
             if (threadIdx.x == 0) *s.narrow = 1;
             return;
         }
@@ -291,7 +461,7 @@ __global__ void __launch_bounds__(kCountThreads) k_inst_count_ring(Spec s, long 
         s_ring[before * plane + e] = base > 0 ? s.cnt32[(long long)e * s.R + base - 1] : e == 0 ? 1 : 0;
     __syncthreads();
     count_planes(s, s_ring, s_size, base, &s_max);
-    if (threadIdx.x < 64) write_offsets(s, s_ring, offsets, status);
+    if (threadIdx.x < 64) write_offsets(s, s_ring + (s.p & (kGroup - 1)) * plane + s.Q, s.Q + 1, offsets, status);
     if (threadIdx.x == 0) *s.narrow = s_max < (1ull << 32) && !keep_wide;
 }
 
@@ -423,13 +593,16 @@ static int launch_count(const Spec &s, int64_t *offsets, int32_t *status, hipStr
     const size_t plane = (size_t)(s.N_hi + 1) * (s.Q + 1) * sizeof(long long);
     const size_t scan = (size_t)(s.N_hi - s.N_lo + 2) * sizeof(long long);
     if (kGroup * plane <= kRingLdsBytes) { // faster wherever it fits, see the kernel
-        const size_t lds = kGroup * plane;
+        // as many node counts a step as the smallest size, if it is known, and a wave can have at most (scan_layout)
+        const bool scan = s.p <= 63 && !keep_wide &&
+                          s.p >= kScanFixed + s.N_hi / (s.sizes || s.n0 > kCountWaves ? kCountWaves : s.n0);
+        const size_t lds = scan ? kRingLdsBytes : kGroup * plane; // one workgroup: the scans may have all there is
+        const auto kernel = scan ? k_inst_count_ring<true> : k_inst_count_ring<false>;
         if (lds > 48 * 1024 && // with the 4 KB of sizes above what a launch may ask for unannounced
-            hipFuncSetAttribute((const void *)k_inst_count_ring, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
+            hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return OOB_EHIP;
-        hipLaunchKernelGGL(k_inst_count_ring, dim3(1), dim3(kCountThreads), lds, stream, s, (long long *)offsets, status,
-                           keep_wide);
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kCountThreads), lds, stream, s, (long long *)offsets, status, keep_wide,
+                           (int)(lds / sizeof(unsigned)));
     } else if (2 * plane <= 128 * 1024) {
         const size_t lds = 2 * plane > scan ? 2 * plane : scan;
         if (lds > 64 * 1024 &&

@@ -194,3 +194,36 @@ def test_table_that_outgrows_32_bits_on_the_way(P, N_hi, p, f, first):
         n = (N_hi + 1) * (f + 2) * R
         table = inst.workspace[256: 256 + 8 * n].view(torch.int64).reshape(N_hi + 1, f + 2, R)[:, :, : p + 1]
         assert np.array_equal(table.cpu().numpy(), want), wide
+
+
+@pytest.mark.parametrize("f", [0, 1, 2, 3, 4, 5, 9, 16, 30])
+def test_count_table_by_node_counts(P, f):
+    """Every number of q's of a wave and of waves for a node count; one to sixteen node counts a step; the last lane; sizes
+    beyond N_hi; gaps; counts around 2^32, where the table is counted in 64 bits after all.  Whole tables against the recurrence."""
+    import torch
+
+    for sizes, N_hi in [(range(8, 65), 128 if f < 10 else 70), (range(2, 65), 40), (range(3, 60, 2), 50), (range(20, 83), 75), (range(40, 60), 30),
+                        (range(5, 40), 97), (range(7, 70), 230), (range(7, 70), 290)]:
+        sizes = list(sizes)
+        p, R = len(sizes), (len(sizes) + 8) // 8 * 8
+        C = np.zeros((N_hi + 1, f + 2, p + 1), dtype=np.int64)
+        C[0, 0] = 1
+        for j, n in enumerate(sizes):
+            C[:, :, j + 1] = C[:, :, j]
+            for x in range(n, N_hi + 1):
+                C[x, 1:, j + 1] += C[x - n, :-1, j + 1]
+                C[x, 0, j + 1] += C[x - n, 0, j + 1]
+        print(f"sizes {sizes[0]}..{sizes[-1]} N_hi {N_hi} f {f}: up to {C.max()}", flush=True)
+        inst = P.Instantiator(sizes, 0, N_hi, f)
+        off, st = inst.count()
+        assert st == P.OOB_OK and np.array_equal(off, np.concatenate([[0], np.cumsum(C[:, f + 1, p])]))
+        ws, n = inst.workspace.cpu(), (N_hi + 1) * (f + 2) * R
+        narrow = int(ws[:4].view(torch.int32))
+        assert narrow == int(C.max() < (1 << 32) - 1)
+        if narrow:
+            at = 256 + (8 * n + 255) // 256 * 256
+            table = ws[at: at + 4 * n].view(torch.int32).numpy().view("uint32").reshape(N_hi + 1, f + 2, R)
+            assert (table[:, :, p + 1:] == 0xFFFFFFFF).all()
+        else:
+            table = ws[256: 256 + 8 * n].view(torch.int64).numpy().reshape(N_hi + 1, f + 2, R)
+        assert np.array_equal(table[:, :, : p + 1], C)
