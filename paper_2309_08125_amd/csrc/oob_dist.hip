@@ -568,6 +568,10 @@ __device__ __forceinline__ void load_times(const Args &a, double *s_tT) { // [p]
     __syncthreads();
 }
 
+// What is left by the first launch has its list where its distribution goes, and its counts are read again if it turns out to be hard.
+// solve_general reads all counts of a plan before it writes: it takes a distribution that overwrites its counts.
+__host__ __device__ inline bool counts_apart(const Args &a) { return a.x != a.base && a.x != a.extra; }
+
 // The plans without an exchange on their stretch; the others are marked in `status`.
 constexpr int kMarked = 1 << 30; // and the templates that are listed (0: none)
 __global__ void __launch_bounds__(kFirstThreads, 4) k_dist_first(Args a) {
@@ -591,6 +595,7 @@ __global__ void __launch_bounds__(kLanes, 3) k_dist_rest(Args a, int span, int m
     load_times(a, s_tT);
     const long long i0 = (long long)blockIdx.x * span;
     const unsigned long long below = (1ull << lane) - 1;
+    const bool apart = counts_apart(a);
     int nleft = 0, nhard = 0;
     for (int o0 = 0; o0 < span; o0 += kLanes * kLoads) {
         int st[kLoads];
@@ -610,7 +615,7 @@ __global__ void __launch_bounds__(kLanes, 3) k_dist_rest(Args a, int span, int m
     for (int q = lane; q - lane < nleft; q += kLanes) {
         const int w = q < nleft ? left[q] : 0, o = w & ((1 << kSpanBits) - 1);
         int got = kDone, listed = a.base ? w >> kSpanBits : 0;
-        if (q < nleft) got = solve_in_registers<true>(a, s_tT, s.walked.ls, s.walked.ne, i0 + o, lane, &listed);
+        if (q < nleft) got = apart ? solve_in_registers<true>(a, s_tT, s.walked.ls, s.walked.ne, i0 + o, lane, &listed) : kHard;
         const unsigned long long m = __ballot(got == kHard);
         if (got == kHard) hard[nhard + __popcll(m & below)] = (unsigned short)o;
         nhard += __popcll(m);
@@ -697,7 +702,7 @@ extern "C" int oob_dist_solve(const uint16_t *x, int64_t count, int64_t capacity
     Args a;
     a.x = x; a.count = count; a.capacity = capacity; a.p = p; a.tT = (const long long *)template_T; a.Q = Q;
     a.vx = (unsigned long long *)vx; a.slowest = (long long *)slowest; a.base = base; a.extra = extra; a.status = status;
-    const bool twice = count > kOnce;
+    const bool twice = count > kOnce && counts_apart(a);
     const int span = twice ? kSpan : kLanes;
     const size_t times = 2 * (size_t)p * sizeof(double);
     if (twice) hipLaunchKernelGGL(k_dist_first, dim3((unsigned)((count + kFirstThreads - 1) / kFirstThreads)), dim3(kFirstThreads), times, (hipStream_t)stream, a);

@@ -162,6 +162,28 @@ def test_many_plans_in_two_launches(P, Q, distribution):
         assert got[3] is None and got[4] is None
 
 
+@pytest.mark.parametrize("out", ["base", "extra"])
+def test_a_distribution_may_overwrite_the_counts(P, out):
+    """base or extra in the place of x, with more plans than one launch takes, a part of them beyond what the first launch does:
+    the counts of a plan are read before its distribution is written."""
+    rng = random.Random(7)
+    tT = [10**9, 10**9 + 1, 10**9 + 2] + [rng.randint(10**9, 4 * 10**9) for _ in range(13)]
+    vecs = []
+    for i in range(200):
+        v = [0] * len(tT)
+        for j in rng.sample(range(3 if i % 4 == 0 else 16), 1 + i % (3 if i % 4 == 0 else 13)):
+            v[j] = rng.choice([1, 1, 2, 3])
+        vecs.append(v)
+    pick = np.random.Generator(np.random.PCG64(7)).integers(0, len(vecs), size=196608 + 65)
+    want = P.Distributor(vecs, len(vecs), tT, 60).solve()
+    d = P.Distributor(np.asarray(vecs)[pick], len(pick), tT, 60)
+    setattr(d, out, d.x)
+    got = d.solve()
+    assert np.array_equal(got[0], want[0][pick]) and np.array_equal(got[2], want[2][pick])
+    assert got[1] == [want[1][i] for i in pick]
+    assert np.array_equal(got[3], want[3][pick]) and np.array_equal(got[4], want[4][pick])
+
+
 def test_choice_of_the_plan_against_the_oracle(P):
     """Groups of plans as the enumeration produces them (one group per cluster size); cases in which
     every minimiser of a plan has the same slowest time, so that the choice is unique."""
