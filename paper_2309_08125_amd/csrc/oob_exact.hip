@@ -1391,11 +1391,7 @@ template <bool STAGED> // a kernel of its own for the usual numbers of GPUs per 
 static int eval_launch(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
     if constexpr (!STAGED) {
         if (a.sums) return eval_launch_m<false, 0, true, false>(a, mode, grid, threads, lds, picks, st);
-        if (a.eval_pad) switch (a.M) {
-        case 2: return eval_launch_m<false, 2, false, true>(a, mode, grid, threads, lds, picks, st);
-        case 4: return eval_launch_m<false, 4, false, true>(a, mode, grid, threads, lds, picks, st);
-        case 8: return eval_launch_m<false, 8, false, true>(a, mode, grid, threads, lds, picks, st);
-        }
+        if (a.eval_pad) return eval_launch_m<false, 8, false, true>(a, mode, grid, threads, lds, picks, st); // can_pad()
     }
     switch (a.M) {
     case 1: return eval_launch_m<STAGED, 1, false, false>(a, mode, grid, threads, lds, picks, st);
@@ -1478,9 +1474,7 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
             switch (M * 2 + a.bounds_pad) {
             case 2: rc = bounds_launch<1, false>(a, mus, bl, st); break;
             case 4: rc = bounds_launch<2, false>(a, mus, bl, st); break;
-            case 5: rc = bounds_launch<2, true>(a, mus, bl, st); break;
             case 8: rc = bounds_launch<4, false>(a, mus, bl, st); break;
-            case 9: rc = bounds_launch<4, true>(a, mus, bl, st); break;
             case 16: rc = bounds_launch<8, false>(a, mus, bl, st); break;
             case 17: rc = bounds_launch<8, true>(a, mus, bl, st); break;
             default: rc = bounds_launch<0, false>(a, mus, bl, st); break;
