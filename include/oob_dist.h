@@ -53,7 +53,9 @@ extern "C" {
  *               (low, high) 64-bit words; the minimum of Eq. 6 times x^2, exactly
  *   slowest     [count] out: max_i N_i T_i under the distribution reported
  *   base, extra [p][capacity] uint16 out, or both NULL: the distribution (see above); entries of
- *               templates not in the plan are 0
+ *               templates not in the plan are 0.  A plan's counts are read before its distribution is
+ *               written: base or extra may be x, or lie a whole number of rows (of capacity entries)
+ *               before or behind it, if the counts are not needed any more
  *   status      [count] out: OOB_DIST_*; where it is not OOB_DIST_OK the other outputs of the plan
  *               are 0
  * Returns OOB_OK once enqueued, OOB_EINVAL for arguments the host can reject. */

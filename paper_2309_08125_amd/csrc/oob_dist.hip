@@ -63,6 +63,7 @@ struct Args {
     long long *slowest;
     unsigned short *base, *extra;
     int *status;
+    int lists; // base and extra may hold what the first launch leaves to the second
 };
 
 // One plan's state: column `lane` of arrays [kT][kGeneral].  Template k of the plan has x pipelines;
@@ -568,10 +569,6 @@ __device__ __forceinline__ void load_times(const Args &a, double *s_tT) { // [p]
     __syncthreads();
 }
 
-// What is left by the first launch has its list where its distribution goes, and its counts are read again if it turns out to be hard.
-// solve_general reads all counts of a plan before it writes: it takes a distribution that overwrites its counts.
-__host__ __device__ inline bool counts_apart(const Args &a) { return a.x != a.base && a.x != a.extra; }
-
 // The plans without an exchange on their stretch; the others are marked in `status`.
 constexpr int kMarked = 1 << 30; // and the templates that are listed (0: none)
 __global__ void __launch_bounds__(kFirstThreads, 4) k_dist_first(Args a) {
@@ -595,7 +592,6 @@ __global__ void __launch_bounds__(kLanes, 3) k_dist_rest(Args a, int span, int m
     load_times(a, s_tT);
     const long long i0 = (long long)blockIdx.x * span;
     const unsigned long long below = (1ull << lane) - 1;
-    const bool apart = counts_apart(a);
     int nleft = 0, nhard = 0;
     for (int o0 = 0; o0 < span; o0 += kLanes * kLoads) {
         int st[kLoads];
@@ -615,7 +611,7 @@ __global__ void __launch_bounds__(kLanes, 3) k_dist_rest(Args a, int span, int m
     for (int q = lane; q - lane < nleft; q += kLanes) {
         const int w = q < nleft ? left[q] : 0, o = w & ((1 << kSpanBits) - 1);
         int got = kDone, listed = a.base ? w >> kSpanBits : 0;
-        if (q < nleft) got = apart ? solve_in_registers<true>(a, s_tT, s.walked.ls, s.walked.ne, i0 + o, lane, &listed) : kHard;
+        if (q < nleft) got = a.lists ? solve_in_registers<true>(a, s_tT, s.walked.ls, s.walked.ne, i0 + o, lane, &listed) : kHard;
         const unsigned long long m = __ballot(got == kHard);
         if (got == kHard) hard[nhard + __popcll(m & below)] = (unsigned short)o;
         nhard += __popcll(m);
@@ -689,6 +685,12 @@ __global__ void __launch_bounds__(kChooseThreads) k_dist_choose(const long long 
     }
 }
 
+// Whether two arrays [p][capacity] share no entry.
+static bool apart(const unsigned short *a, const unsigned short *b, int p, long long capacity) {
+    const uintptr_t bytes = (uintptr_t)p * (uintptr_t)capacity * sizeof(unsigned short), u = (uintptr_t)a, v = (uintptr_t)b;
+    return u < v ? v - u >= bytes : u - v >= bytes;
+}
+
 } // namespace oob_dist
 
 extern "C" int oob_dist_solve(const uint16_t *x, int64_t count, int64_t capacity, int p, const int64_t *template_T,
@@ -702,7 +704,10 @@ extern "C" int oob_dist_solve(const uint16_t *x, int64_t count, int64_t capacity
     Args a;
     a.x = x; a.count = count; a.capacity = capacity; a.p = p; a.tT = (const long long *)template_T; a.Q = Q;
     a.vx = (unsigned long long *)vx; a.slowest = (long long *)slowest; a.base = base; a.extra = extra; a.status = status;
-    const bool twice = count > kOnce && counts_apart(a);
+    // What is left by the first launch has its list where its distribution goes, and its counts are read again if it turns out to be hard.
+    // solve_general reads all counts of a plan before it writes: it takes arrays that share entries, whole rows apart.
+    a.lists = !base || (apart(x, base, p, capacity) && apart(x, extra, p, capacity) && apart(base, extra, p, capacity));
+    const bool twice = count > kOnce && a.lists;
     const int span = twice ? kSpan : kLanes;
     const size_t times = 2 * (size_t)p * sizeof(double);
     if (twice) hipLaunchKernelGGL(k_dist_first, dim3((unsigned)((count + kFirstThreads - 1) / kFirstThreads)), dim3(kFirstThreads), times, (hipStream_t)stream, a);

@@ -184,6 +184,51 @@ def test_a_distribution_may_overwrite_the_counts(P, out):
     assert np.array_equal(got[3], want[3][pick]) and np.array_equal(got[4], want[4][pick])
 
 
+@pytest.mark.parametrize("count", [500, 150001, 196608 + 65])
+@pytest.mark.parametrize("rows", [-3, -1, 0, 2])
+def test_a_distribution_whole_rows_from_the_counts(P, count, rows):
+    """base a number of rows before or behind x in the same buffer, in one launch and in several; plans with ties and with exchanges
+    on their path, which are read once more after the first launch."""
+    import torch
+
+    rng = random.Random(11)
+    tT = [10**9, 10**9, 2 * 10**9, 3 * 10**9, 4 * 10**9] + [rng.randint(10**9, 4 * 10**9) for _ in range(9)]
+    p = len(tT)
+    vecs = []
+    for i in range(200):
+        v = [0] * p
+        for j in rng.sample(range(5 if i % 2 else p), 1 + i % (5 if i % 2 else 12)):
+            v[j] = rng.choice([1, 1, 2, 3])
+        vecs.append(v)
+    pick = np.random.Generator(np.random.PCG64(count)).integers(0, len(vecs), size=count)
+    want = P.Distributor(vecs, len(vecs), tT, 50).solve()
+    buf = torch.full((p + abs(rows), count), -7, dtype=torch.int16, device="cuda")
+    at, out = (0, rows) if rows > 0 else (-rows, 0)
+    buf[at: at + p] = torch.from_numpy(np.ascontiguousarray(np.asarray(vecs, dtype=np.int16)[pick].T)).cuda()
+    d = P.Distributor(buf[at: at + p], count, tT, 50)
+    d.base = buf[out: out + p]
+    got = d.solve()
+    assert np.array_equal(got[0], want[0][pick]) and np.array_equal(got[2], want[2][pick])
+    assert got[1] == [want[1][i] for i in pick]
+    assert np.array_equal(got[3], want[3][pick]) and np.array_equal(got[4], want[4][pick])
+
+
+@pytest.mark.parametrize("count", [500, 196608 + 65])
+def test_one_array_for_both_parts_of_a_distribution(P, count):
+    """base and extra the same array: it holds what is written last, extra."""
+    rng = random.Random(12)
+    tT = [rng.randint(10**9, 4 * 10**9) for _ in range(14)]
+    vecs = [[rng.choice([0, 0, 1, 3]) for _ in tT] for _ in range(200)]
+    pick = np.random.Generator(np.random.PCG64(count)).integers(0, len(vecs), size=count)
+    want = P.Distributor(vecs, len(vecs), tT, 60).solve()
+    d = P.Distributor(np.asarray(vecs)[pick], count, tT, 60)
+    d.base = d.extra
+    got = d.solve()
+    assert np.array_equal(got[0], want[0][pick]) and np.array_equal(got[2], want[2][pick])
+    assert got[1] == [want[1][i] for i in pick]
+    assert np.array_equal(got[3], want[4][pick]) and np.array_equal(got[4], want[4][pick])
+
+
 def test_choice_of_the_plan_against_the_oracle(P):
     """Groups of plans as the enumeration produces them (one group per cluster size); cases in which
     every minimiser of a plan has the same slowest time, so that the choice is unique."""
