@@ -433,11 +433,12 @@ template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const do
                         if (next) { ++n[k]; e[k] = 0; }
                         else ++e[k];
                     }
-                    if (next) {
+                    if (next) { // formed anew: a sum of steps would add up their roundings, which `most` does not cover
                         double Tk = T[k];
                         asm volatile("" : "+v"(Tk));
-                        c[k] = remove && n[k] < 2 ? kHuge : c[k] + 2.0 * Tk * Tk;
-                        most = fmax(most, 4.0 * kEps * (2.0 * (double)mu * Tk + Tk * Tk * (2 * n[k] + 1)));
+                        const double sq = Tk * Tk, q = Tk * (2.0 * (double)mu);
+                        c[k] = !remove ? sq * (2 * n[k] + 1) - q : n[k] < 2 ? kHuge : q - sq * (2 * n[k] - 1);
+                        most = fmax(most, 4.0 * kEps * (q + sq * (2 * n[k] + 1)));
                     }
                 }
                 tot += remove ? -1 : 1;
