@@ -19,16 +19,25 @@
 // donor is one of its fullest pipelines, its receiver one of its emptiest.  Products reach
 // 2^124: all exact arithmetic is in 128-bit integers.
 //
-// Three forms of the same solution.  Of the plans of a node specification one in sixty has an exchange on its path at all: whether
-// there is one is decided from the templates one by one (solve_in_registers), and the others are done after one allocation.  The
-// few with a path wait until a wave is full of them; solve_general, in LDS and slow, keeps the plans of more than kFast
-// templates and the comparisons that doubles leave open.
+// How far a plan's path has to be followed depends on the templates' times.  With times that grow by a factor of two over 57 sizes one plan in
+// fifty has an exchange on its path at all, with times that fall as 1 / nodes a quarter to 40 %, and with times on a coarse grid most have,
+// and many exact ties.  So the launches share out work by the plans that have a path, wherever they are: with many plans a first launch
+// decides from the templates one by one whether there is an exchange (solve<FOLLOW = false>), finishes the others and leaves a mark, and a second
+// one takes the marked plans 64 side by side.
 //
-// What bounds it: the vector ALUs (3 300 instructions a wave for 57 templates, two fifths of them for reading the counts and writing the
-// distribution) and, for plans with a path, waves of a few lanes that wait for memory.  1 343 380 plans of up to 57 templates, 512
-// microbatches: 521 us with solve_general for every plan, 172 us for the first launch and 85 us for the second here (the walkers followed
-// at the end of each wave's share 350 us; with all 57 counts of a walker read once more, and written, 172 and 170 us); 10 251 plans of
-// 29 templates 41 -> 27 us.
+// What bounds it: the vector ALUs (3 000 instructions a wave for 57 templates in the first launch, two fifths of them for reading the
+// counts and writing the distribution) and, where few plans have a path, the chain of its longest one.  Plans of up to 57 templates, 512
+// microbatches, us a call: every plan by one lane in LDS at its place; with its path followed in stretches of 1 024 plans by one wave
+// each, ties of two costs by the form in LDS; here:
+//     1 343 380 plans, times that grow      521     261    228
+//                      that fall as 1 / n   506   1 115    430
+//                      all equal            837   4 317    510
+//                      5 .. 40 times 10^8 2 031   9 073  1 840
+//                      random, 1 to 4       695     557    380
+//       200 000 plans, times that grow      147      84     82
+//                      all equal            260   4 128    124
+//        10 251 plans, times that grow       41      27     26
+//       400 000 plans of 11..16 templates   888   8 066    500
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -40,18 +49,21 @@
 namespace oob_dist {
 
 typedef __int128 i128;
-constexpr int kLanes = 64;  // plans side by side in a wave
-constexpr int kLoads = 16;  // counts of a plan in flight while its templates are listed
+constexpr int kLanes = 64; // plans side by side in a wave
+constexpr int kLoads = 16; // counts of a plan in flight while its templates are listed
 constexpr int kT = OOB_DIST_MAX_TEMPLATES_IN_PLAN;
-constexpr int kGeneral = 32; // lanes of a wave that solve_general uses: half of them leave room in LDS for more waves
+constexpr int kFew = 10;   // templates that have registers in the first launch at four waves a SIMD
 constexpr int kFirstThreads = 256;
-// Plans that a wave of the second launch looks through: some sixteen of them have a path.  512, 1 024, 2 048: 288, 283, 316 us
-// for the whole call with the choice (1 343 380 plans).
-constexpr int kSpanBits = 10, kSpan = 1 << kSpanBits;
-// Plans up to which one launch does it all, each wave 64 plans with their paths: as many as the GPU holds at once.  What counts
-// there is how long one wave takes (10 251 plans: 27 us, 15 + 33 us in two launches).
-constexpr long long kOnce = 3072 * 64;
-constexpr long long kMaxExchanges = 1ll << 24; // never reached (at most Q exchanges per template): every lane's loop ends
+constexpr int kScan = 4, kSpanBits = 10; // marks in flight of a wave of the second launch; plans whose marks it looks through, at most
+// Up to kOnce plans one launch does it all, two waves a SIMD: what counts there is how long the wave with the longest path takes, and
+// kOnce is what the GPU holds at once (120 000 plans 54 us, in two launches 75; three waves a SIMD, which spill, 57).  Up to kFollow plans the
+// first launch, at three waves a SIMD, follows the paths as well, as many as the GPU holds, and leaves the plans of many templates (160 000
+// plans 65 us, with the paths in the second launch 76; 200 000 plans 92 and 81).
+constexpr long long kOnce = 2048 * 64, kFollow = 3072 * 64;
+// Waves of the second launch, at most a wave for every 64 plans.  3 072, 5 120, 7 168, 10 240, for 1 343 380 plans: times that grow 239, 234, 232, 233
+// us, times that fall as 1 / nodes 655, 549, 473, 434 us: the waves without a marked plan end while the others work.
+constexpr int kRestWaves = 10240;
+constexpr double kHuge = __builtin_huge_val();
 
 struct Args {
     const unsigned short *x;
@@ -66,330 +78,183 @@ struct Args {
     int lists; // base and extra may hold what the first launch leaves to the second
 };
 
-// One plan's state: column `lane` of arrays [kT][kGeneral].  Template k of the plan has x pipelines;
-// e of them hold n + 1 microbatches, the others n (0 <= e < x): no division in the loops.
-struct Plan {
-    const double *tT;              // the workgroup's copy of the templates' times per microbatch (integers: exact)
-    unsigned short *j, *x, *n, *e; // template index; pipelines; see above
-    int t, xs;                     // templates in use; pipelines in all
-    __device__ double Td(int k) const { return tT[j[k * kGeneral]]; }
-    __device__ long long Tk(int k) const { return (long long)Td(k); }
-    __device__ int xk(int k) const { return x[k * kGeneral]; }
-    __device__ int fullest(int k) const { return n[k * kGeneral] + (e[k * kGeneral] > 0); } // microbatches of a fullest pipeline
-    __device__ int emptiest(int k) const { return n[k * kGeneral]; }
-    __device__ void take(int k) const { // one microbatch less for a fullest pipeline
-        if (e[k * kGeneral] > 0) e[k * kGeneral] -= 1;
-        else { n[k * kGeneral] -= 1; e[k * kGeneral] = (unsigned short)(xk(k) - 1); }
-    }
-    __device__ void give(int k) const { // one more for an emptiest pipeline
-        if (e[k * kGeneral] + 1 == xk(k)) { n[k * kGeneral] += 1; e[k * kGeneral] = 0; }
-        else e[k * kGeneral] += 1;
-    }
-};
-
 // Comparisons of exact integers are decided in doubles where the difference exceeds the rounding of the
-// double expressions, and in 128 bits otherwise (a 128-bit product is some forty instructions, a double one
-// instruction; random times leave about one comparison in 10^8 to the exact form).  kEps bounds the rounding of a sum of
-// two products of three factors relative to the sum of their magnitudes (five roundings of 2^-53, doubled).
+// double expressions, and in 128 bits otherwise (random times leave about one comparison in 10^8 to the exact form, times on a coarse
+// grid a good part).  kEps bounds the rounding of a sum of two products of three factors relative to the sum of their magnitudes (five
+// roundings of 2^-53, doubled).  Times below kExactT need no exact form: |c| < 2^40, w < 2^12 and all sums of two products are integers
+// below 2^53 (times of 1 to 20, 1 343 380 plans: 5 170 -> 2 850 us).
 constexpr double kEps = 1.0 / (1ll << 49);
-constexpr double kHuge = __builtin_huge_val();
+constexpr double kExactT = 2048;
 
-// The optimum of the fixed-level problem at the integer level mu >= 0.
-__device__ void allocate_at(const Plan &pl, long long mu, int Q) {
-    long long tot = 0;
-    for (int k = 0; k < pl.t; ++k) {
-        const long long T = pl.Tk(k), num = 2 * mu + T; // num < 2^53
-        long long n = (long long)((double)num / (double)(2 * T)); // nearest integer to mu / T, once corrected
-        n -= n * (2 * T) > num;
-        n += (n + 1) * (2 * T) <= num;
-        if (n < 1) n = 1;
-        if (n > Q) n = Q;
-        pl.n[k * kGeneral] = (unsigned short)n;
-        pl.e[k * kGeneral] = 0;
-        tot += n * pl.xk(k);
-    }
-    // cost of one microbatch more or less for a pipeline of T that counts as m (odd, its sign that of the change):
-    // T^2 m - 2 T mu (add, m = 2 n + 1) or T^2 m + 2 T mu (remove, m = 1 - 2 n)
-    const bool remove = tot > Q;
-    const double mud = remove ? 2.0 * (double)mu : -2.0 * (double)mu;
-    while (tot != Q) {
-        int arg = -1, am = 0;
-        double bc = 0, be = 0;
-        for (int k = 0; k < pl.t; ++k) {
-            const int m = remove ? 1 - 2 * pl.fullest(k) : 2 * pl.emptiest(k) + 1;
-            if (remove && m > -3) continue; // it holds one microbatch
-            const double T = pl.Td(k), p = T * T * m, q = T * mud, c = p + q, e = (fabs(p) + fabs(q)) * kEps;
-            bool less = c < bc;
-            if (arg >= 0 && fabs(c - bc) <= e + be) {
-                const long long Ti = (long long)T, Tb = pl.Tk(arg), s = remove ? 2 * mu : -2 * mu;
-                less = (i128)Ti * Ti * m + (i128)Ti * s < (i128)Tb * Tb * am + (i128)Tb * s;
-            }
-            if (arg < 0 || less) { bc = c; be = e; arg = k; am = m; }
-        }
-        if (arg < 0) break; // cannot happen: tot > Q >= pipelines, so some pipeline holds two
-        if (remove) { pl.take(arg); --tot; } else { pl.give(arg); ++tot; }
-    }
-}
-
-// S1 = sum a_i, S2 = sum a_i^2 over the pipelines (a_i = N_i T_i).
-__device__ void sums(const Plan &pl, i128 *S1, i128 *S2) {
-    i128 s1 = 0, s2 = 0;
-    for (int k = 0; k < pl.t; ++k) {
-        const i128 T = pl.Tk(k);
-        const int n = pl.n[k * kGeneral], e = pl.e[k * kGeneral]; // e pipelines hold n + 1, the others n
-        const i128 lo = T * n, hi = T * (n + 1);
-        s1 += lo * (pl.xk(k) - e) + hi * e;
-        s2 += lo * lo * (pl.xk(k) - e) + hi * hi * e;
-    }
-    *S1 = s1; *S2 = s2;
-}
-
-// The level of the exchange d -> r as a fraction: c / w (see the loop below).
-__device__ i128 exchange_c(const Plan &pl, int d, int r) {
-    const long long Td = pl.Tk(d), Tr = pl.Tk(r);
-    return (i128)Td * Td * (1 - 2 * pl.fullest(d)) + (i128)Tr * Tr * (1 + 2 * pl.emptiest(r));
-}
-__device__ long long exchange_w(const Plan &pl, int d, int r) { return 2 * (pl.Tk(r) - pl.Tk(d)); } // below 2^37
-__device__ bool exact_less(const Plan &pl, int d, int r, int bd, int br) {
-    return exchange_c(pl, d, r) * exchange_w(pl, bd, br) < exchange_c(pl, bd, br) * exchange_w(pl, d, r);
-}
-__device__ bool level_above(const Plan &pl, int d, int r, i128 mu) { return exchange_c(pl, d, r) > exchange_w(pl, d, r) * mu; }
-
-// The arrays of one wave's plans in LDS.
-struct General {
-    unsigned short x[kT * kGeneral], j[kT * kGeneral], n[kT * kGeneral], e[kT * kGeneral];
-    unsigned short bn[kT * kGeneral], be[kT * kGeneral]; // the best allocation met so far
-};
-
-// Plan i by one lane, whatever its templates and its path.
-__device__ void solve_general(const Args &a, const double *s_tT, General &g, long long i, int lane) {
-    Plan pl;
-    pl.tT = s_tT; pl.j = g.j + lane; pl.x = g.x + lane; pl.n = g.n + lane; pl.e = g.e + lane;
-    unsigned short *bn = g.bn + lane, *be = g.be + lane, *tj = g.j + lane;
-
-    // the templates in use
-    int t = 0, xs = 0, st = OOB_DIST_OK;
+// The templates in use of plan i: jx[k * kLanes] = template | pipelines << 16, the first `rows` of them.  Returns their number.
+__device__ __forceinline__ int list_templates(const Args &a, long long i, unsigned *jx, int rows, int *pipelines) {
+    int t = 0, xs = 0;
     for (int j0 = 0; j0 < a.p; j0 += kLoads) {
         int c[kLoads];
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) c[q] = j0 + q < a.p ? a.x[(long long)(j0 + q) * a.capacity + i] : 0;
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) {
-            if (!c[q] || st != OOB_DIST_OK) continue;
-            const double T = s_tT[j0 + q]; // a time beyond 2^53 is rounded, and refused all the same
-            if (t == kT) { st = OOB_DIST_TOO_MANY_TEMPLATES; continue; }
-            if (T < 1 || T > (double)OOB_DIST_MAX_T) { st = OOB_DIST_BAD_TIME; continue; }
-            pl.x[t * kGeneral] = (unsigned short)c[q]; tj[t * kGeneral] = (unsigned short)(j0 + q);
+            if (!c[q]) continue;
+            if (t < rows) jx[t * kLanes] = (unsigned)(j0 + q) | (unsigned)c[q] << 16;
             xs += c[q];
             ++t;
         }
     }
-    if (st == OOB_DIST_OK && t == 0) st = OOB_DIST_NO_PIPELINE;
-    if (st == OOB_DIST_OK && xs > a.Q) st = OOB_DIST_TOO_FEW_MICROBATCHES;
-    a.status[i] = st;
-    if (st != OOB_DIST_OK) {
-        a.vx[2 * i] = 0; a.vx[2 * i + 1] = 0; a.slowest[i] = 0;
-        if (a.base)
-            for (int j = 0; j < a.p; ++j) {
-                a.base[(long long)j * a.capacity + i] = 0;
-                a.extra[(long long)j * a.capacity + i] = 0;
-            }
-        return;
-    }
-    pl.t = t; pl.xs = xs;
-
-    // the stretch of levels that can hold the optimum's mean
-    double H = 0;
-    bool twins = false; // two templates of the same time
-    for (int k = 0; k < t; ++k) {
-        const double T = pl.Td(k);
-        H += (double)pl.xk(k) / T;
-        for (int l = 0; l < k; ++l) twins |= pl.Td(l) == T;
-    }
-    double D = 0;
-    for (int k = 0; k < t; ++k) {
-        const double r = 1.0 / pl.Td(k) - H / xs;
-        D += r * r * pl.xk(k);
-    }
-    const double L0 = (double)a.Q / H;
-    allocate_at(pl, (long long)(L0 + 0.5), a.Q);
-    i128 S1, S2;
-    sums(pl, &S1, &S2);
-    const double V = (double)((i128)xs * S2 - S1 * S1) / (double)xs; // sum of squared deviations of a feasible allocation
-    // With twins the distribution met first among equal ones depends on where the path starts: it starts where the
-    // cruder bound, sqrt(V), puts it.
-    const double narrow = twins ? 1.0 : fmin(sqrt(D) / H, 1.0);
-    const double R = sqrt(V) * (narrow * (1.0 + 1e-9) + 1e-12) + L0 * 1e-9 + 2.0; // widened for the rounding of these few operations
-    const long long mu_lo = L0 - R > 0 ? (long long)(L0 - R) : 0;
-    const i128 mu_hi = (i128)(long long)(L0 + R) + 1;
-
-    allocate_at(pl, mu_lo, a.Q);
-    sums(pl, &S1, &S2);
-    i128 best = (i128)xs * S2 - S1 * S1;
-    for (int k = 0; k < t; ++k) { bn[k * kGeneral] = pl.n[k * kGeneral]; be[k * kGeneral] = pl.e[k * kGeneral]; }
-    for (long long step = 0; step < kMaxExchanges; ++step) {
-        // the next exchange: a microbatch of a fullest pipeline of template d (n_d of them) goes to an emptiest
-        // pipeline of a slower template r (n_r): it pays from the level c / w on,
-        // c = T_d^2 + T_r^2 - 2 T_d^2 n_d + 2 T_r^2 n_r,  w = 2 (T_r - T_d) > 0
-        int bd = -1, br = -1;
-        double bc = 0, be2 = 0, bw = 1;
-        for (int d = 0; d < t; ++d) {
-            const int nd = pl.fullest(d);
-            if (nd < 2) continue;
-            const double Td = pl.Td(d), cd = Td * Td * (1 - 2 * nd);
-            for (int r = 0; r < t; ++r) {
-                const double Tr = pl.Td(r);
-                if (Tr <= Td) continue;
-                const double cr = Tr * Tr * (1 + 2 * pl.emptiest(r)), c = cd + cr, w = 2.0 * (Tr - Td); // w exact
-                const double err = (cr - cd) * kEps; // cd < 0 < cr
-                const double diff = c * bw - bc * w;
-                bool less = diff < 0;
-                if (bd >= 0 && fabs(diff) <= 2.0 * (err * bw + be2 * w)) less = exact_less(pl, d, r, bd, br);
-                if (bd < 0 || less) { bc = c; be2 = err; bw = w; bd = d; br = r; }
-            }
-        }
-        if (bd < 0 || level_above(pl, bd, br, mu_hi)) break; // past the stretch
-        const long long Td = pl.Tk(bd), Tr = pl.Tk(br);
-        const int nd = pl.fullest(bd), nr = pl.emptiest(br);
-        S1 += Tr - Td;
-        S2 += (i128)Tr * Tr * (2 * nr + 1) - (i128)Td * Td * (2 * nd - 1);
-        pl.take(bd);
-        pl.give(br);
-        const i128 v = (i128)xs * S2 - S1 * S1;
-        if (v < best) {
-            best = v;
-            for (int k = 0; k < t; ++k) { bn[k * kGeneral] = pl.n[k * kGeneral]; be[k * kGeneral] = pl.e[k * kGeneral]; }
-        }
-    }
-
-    long long slow = 0;
-    for (int k = 0; k < t; ++k) {
-        const long long time = (long long)(bn[k * kGeneral] + (be[k * kGeneral] > 0)) * pl.Tk(k);
-        slow = time > slow ? time : slow;
-    }
-    if (a.base) { // every entry written once
-        int k = 0, next = tj[0];
-        for (int j = 0; j < a.p; ++j) {
-            unsigned short n = 0, e = 0;
-            if (j == next) {
-                n = bn[k * kGeneral]; e = be[k * kGeneral];
-                ++k;
-                next = k < t ? tj[k * kGeneral] : -1;
-            }
-            a.base[(long long)j * a.capacity + i] = n;
-            a.extra[(long long)j * a.capacity + i] = e;
-        }
-    }
-    a.vx[2 * i] = (unsigned long long)best;
-    a.vx[2 * i + 1] = (unsigned long long)(best >> 64);
-    a.slowest[i] = slow;
+    *pipelines = xs;
+    return t;
 }
 
-// Plan i by one lane with its templates in registers: the same method and the same order of comparisons as
-// solve_general, for plans of at most kFast templates.  kHard: a plan of more, one that cannot be solved, or a comparison
-// that needs the exact form; solve_general takes it.
-//
-// Mostly no exchange lies on the stretch, and then nothing has to be searched.  A distribution is the only optimum at a level mu if every
-// exchange of a microbatch between two templates costs: taking one from a fullest pipeline of d adds A = T_d^2 (1 - 2 n_d) + 2
-// T_d mu, giving it to an emptiest one of r B = T_r^2 (1 + 2 n_r) - 2 T_r mu, and A + B > 0 for all d != r (the problem is
-// separable and convex: a strict minimum among its neighbours is the minimum).  Where that holds for the distribution of the
-// stretch's middle at both ends of the stretch, the path starts with it and has no exchange on the stretch (A + B <= 0 is what makes
-// one pay).  Otherwise the path is followed with FOLLOW = true; FOLLOW = false returns kLeft.
-constexpr int kFast = 10;
-constexpr int kDone = 0, kLeft = 1, kHard = 2;
-struct Listed { unsigned jx[kFast * kLanes], best[kFast * kLanes]; }; // template | pipelines << 16; n | e << 16 (as in Plan)
-struct Walked { Listed ls; unsigned ne[kFast * kLanes]; };
+// A time beyond 2^53 is rounded, and refused all the same.
+__device__ __forceinline__ bool time_is_valid(double T) { return T >= 1 && T <= (double)OOB_DIST_MAX_T; }
 
-// FOLLOW = false hands the list of the plan's templates over where the plan stays open: rows 0 .. t-1 of its column of base and extra hold
-// them, *listed becomes t.  FOLLOW = true takes it from there if *listed is not 0.
-template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const double *s_tT, Listed &ls, unsigned *ne, long long i, int lane, int *listed) {
-    unsigned *const jx = ls.jx + lane, *const best_ne = ls.best + lane;
-    int t = 0, xs = 0;
-    if (FOLLOW && *listed) {
-        t = *listed;
-        unsigned w[kFast];
-#pragma unroll
-        for (int k = 0; k < kFast; ++k) w[k] = k < t ? (unsigned)a.base[k * a.capacity + i] | (unsigned)a.extra[k * a.capacity + i] << 16 : 0;
-#pragma unroll
-        for (int k = 0; k < kFast; ++k) {
-            jx[k * kLanes] = w[k];
-            xs += (int)(w[k] >> 16);
+__device__ __forceinline__ void refuse(const Args &a, long long i, int st) {
+    a.status[i] = st;
+    a.vx[2 * i] = 0; a.vx[2 * i + 1] = 0; a.slowest[i] = 0;
+    if (a.base)
+        for (int j = 0; j < a.p; ++j) {
+            a.base[(long long)j * a.capacity + i] = 0;
+            a.extra[(long long)j * a.capacity + i] = 0;
         }
-    } else {
-        for (int j0 = 0; j0 < a.p; j0 += kLoads) {
-            int c[kLoads];
-#pragma unroll
-            for (int q = 0; q < kLoads; ++q) c[q] = j0 + q < a.p ? a.x[(long long)(j0 + q) * a.capacity + i] : 0;
-#pragma unroll
-            for (int q = 0; q < kLoads; ++q) {
-                if (!c[q]) continue;
-                if (t < kFast) jx[t * kLanes] = (unsigned)(j0 + q) | (unsigned)c[q] << 16;
-                xs += c[q];
-                ++t;
-            }
+}
+
+// A plan of more than kT templates, the first of them listed: what the first kT or the next one are refused for.
+__device__ __forceinline__ void refuse_many(const Args &a, const double *s_tT, const unsigned *jx, long long i) {
+    bool ok = true;
+    for (int k = 0; k < kT; ++k) ok &= time_is_valid(s_tT[jx[k * kLanes] & 0xffff]);
+    refuse(a, i, ok ? OOB_DIST_TOO_MANY_TEMPLATES : OOB_DIST_BAD_TIME);
+}
+
+// The distribution `ne` of a plan of t templates, every entry of base and extra written once; or, with `open`, its list in rows 0 .. t-1.
+__device__ __forceinline__ void write_rows(const Args &a, long long i, const unsigned *jx, const unsigned *ne, int t, bool open) {
+    int k = 0;
+    unsigned next = open ? 0 : jx[0] & 0xffff, have = open ? jx[0] : ne[0];
+    for (int j = 0; j < a.p; ++j) {
+        unsigned w = 0;
+        if ((unsigned)j == next) {
+            w = have;
+            ++k;
+            const unsigned row = k < t ? jx[k * kLanes] : 0xffffu;
+            next = open && k < t ? (unsigned)k : row & 0xffff;
+            have = open ? row : k < t ? ne[k * kLanes] : 0;
         }
-        if (t == 0 || t > kFast || xs > a.Q) return kHard;
+        a.base[(long long)j * a.capacity + i] = (unsigned short)w;
+        a.extra[(long long)j * a.capacity + i] = (unsigned short)(w >> 16);
     }
-    double T[kFast];
-    int x[kFast], n[kFast], e[kFast];
+}
+
+// What one microbatch less for a fullest pipeline of n, or more for an emptiest one, costs a template at the level m2 / 2: the same double
+// wherever it is formed (nothing is left to contraction).
+__device__ __forceinline__ double cost_of_one(double T, int n, double m2, bool remove) {
+    const double q = T * m2;
+    return __builtin_fma(T * T, (double)(remove ? 1 - 2 * n : 2 * n + 1), remove ? q : -q);
+}
+
+// The template that one microbatch more or less costs least, the first of equals, among those whose cost in doubles is at most
+// `near`.  ne: K words of this lane to work in.
+template <int K>
+__device__ __forceinline__ int exact_pick(const double *s_tT, const unsigned *jx, unsigned *ne, const int (&n)[K], const int (&e)[K], int t, long long mu,
+                                          bool remove, double near) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) ne[k * kLanes] = (unsigned)(n[k] + (remove && e[k] > 0));
+    const long long s = remove ? 2 * mu : -2 * mu;
+    long long Tp = 0;
+    int mp = 0, pick = 0;
+    i128 least = 0;
+#pragma unroll 1
+    for (int k = 0; k < t; ++k) {
+        const int held = (int)ne[k * kLanes], m = remove ? 1 - 2 * held : 2 * held + 1;
+        if (remove && held < 2) continue;
+        const double T = s_tT[jx[k * kLanes] & 0xffff];
+        if (T * T * m + T * (double)s > near) continue;
+        const long long Tk = (long long)T;
+        if (Tk == Tp && m == mp) continue; // twins
+        const i128 v = (i128)Tk * (Tk * m + s); // |T m| and 2 mu are below 2^53
+        if (Tp == 0 || v < least) { least = v; Tp = Tk; mp = m; pick = k; }
+    }
+    return pick;
+}
+
+// Plan i of t <= K templates by one lane, its templates in registers.  Template k has x pipelines; e of them hold n + 1
+// microbatches, the others n (0 <= e < x): no division in the loops.  ne, best_ne: n | e << 16 of the allocation at hand and of the best.
+//
+// Mostly no exchange lies on the stretch, and then nothing has to be searched.  An exchange of a microbatch between two templates, taken from
+// a fullest pipeline of d and given to an emptiest one of r, costs A + B with A = T_d^2 (1 - 2 n_d) + 2 T_d mu and B = T_r^2 (1 + 2 n_r)
+// - 2 T_r mu.  If A + B > 0 for all T_d != T_r, the allocation is the only optimum at the level mu but for exchanges between templates of
+// the same time (the problem is separable and convex: a strict minimum among its neighbours is the minimum).  Where that holds for the allocation
+// of the stretch's middle at both ends of the stretch, the path has no exchange on the stretch (A + B <= 0 is what makes one pay) and is that
+// allocation, or with twins (templates of the same time), which share their microbatches out in an order that hangs on the level, the
+// allocation of the lower end.  Otherwise, and with twins, FOLLOW = true goes on from the lower end, and FOLLOW = false leaves the ends of
+// the stretch in vx and returns false (a second allocation in the same loop takes 40 registers more than it has).
+// mu, mu_hi: the ends of a stretch that is known (mu_hi = -1: it is not).  from_list: base and extra hold the plan's list in rows 0 .. t-1.
+template <int K, bool FOLLOW>
+__device__ __forceinline__ bool solve(const Args &a, const double *s_tT, const unsigned *jx, unsigned *best_ne, unsigned *ne, long long i, int t,
+                                      int xs, long long mu, long long mu_hi, bool from_list) {
+    double T[K];
+    int x[K], n[K], e[K];
     auto inverse = [&](int k) { return s_tT[a.p + (jx[k * kLanes] & 0xffff)]; }; // read again where it is used: registers decide how
                                                                                  // many waves run
-    bool ok = true, twins = false;
+    bool valid = true, twins = false, exact = true, walk = FOLLOW && mu_hi >= 0, open = false;
     double H = 0;
 #pragma unroll
-    for (int k = 0; k < kFast; ++k) {
+    for (int k = 0; k < K; ++k) {
         T[k] = 1; x[k] = n[k] = e[k] = 0;
         if (k < t) {
             const unsigned w = jx[k * kLanes];
             T[k] = s_tT[w & 0xffff]; x[k] = (int)(w >> 16);
-            ok &= T[k] >= 1 && T[k] <= (double)OOB_DIST_MAX_T;
-            H += (double)x[k] * inverse(k);
+            valid &= time_is_valid(T[k]);
+            exact &= T[k] < kExactT;
+            if (!walk) H += (double)x[k] * inverse(k);
 #pragma unroll
             for (int l = 0; l < k; ++l) twins |= T[l] == T[k];
         }
     }
-    if (!ok) return kHard;
+    if (!valid || t == 0 || xs > a.Q) {
+        refuse(a, i, !valid ? OOB_DIST_BAD_TIME : t == 0 ? OOB_DIST_NO_PIPELINE : OOB_DIST_TOO_FEW_MICROBATCHES);
+        return true;
+    }
     const double mean = H / xs, L0 = (double)a.Q / H;
     double D = 0;
+    if (!walk) {
 #pragma unroll
-    for (int k = 0; k < kFast; ++k)
-        if (k < t) {
-            const double r = inverse(k) - mean;
-            D += r * r * x[k];
-        }
+        for (int k = 0; k < K; ++k)
+            if (k < t) {
+                const double r = inverse(k) - mean;
+                D += r * r * x[k];
+            }
+        mu = (long long)(L0 + 0.5);
+    }
 
-    // every exchange costs at level mu (see above)
+    // every exchange between templates of different times costs at level mu (see above)
     auto settled = [&](double mu) {
         const double m2 = 2.0 * mu;
-        double a1 = kHuge, a2 = kHuge, b1 = kHuge, b2 = kHuge; // smallest and second smallest A and B, less their rounding
-        int ai = -1, bi = -1;
+        double a1 = kHuge, a2 = kHuge, b1 = kHuge, b2 = kHuge; // smallest A and B, and smallest of another time, less their rounding
+        double at = 0, bt = 0;
 #pragma unroll
-        for (int k = 0; k < kFast; ++k)
+        for (int k = 0; k < K; ++k)
             if (k < t) {
                 const int full = n[k] + (e[k] > 0);
                 const double sq = T[k] * T[k], q = T[k] * m2, pa = sq * (2 * full - 1), pb = sq * (2 * n[k] + 1);
                 const double A = full < 2 ? kHuge : (q - pa) - (q + pa) * kEps, B = (pb - q) - (pb + q) * kEps;
-                a2 = fmin(a2, fmax(a1, A));
-                ai = A < a1 ? k : ai;
+                a2 = T[k] == at ? a2 : fmin(a2, fmax(a1, A));
+                at = A < a1 ? T[k] : at;
                 a1 = fmin(a1, A);
-                b2 = fmin(b2, fmax(b1, B));
-                bi = B < b1 ? k : bi;
+                b2 = T[k] == bt ? b2 : fmin(b2, fmax(b1, B));
+                bt = B < b1 ? T[k] : bt;
                 b1 = fmin(b1, B);
             }
-        return (ai != bi ? a1 + b1 : fmin(a1 + b2, a2 + b1)) > 0.0;
+        return (at != bt ? a1 + b1 : fmin(a1 + b2, a2 + b1)) > 0.0;
     };
-    long long mu = (long long)(L0 + 0.5), mu_hi = 0;
     long long S1; // below 2^51
     i128 S2, best;
-    bool walk = false, open = false;
     for (;;) { // at the middle of the stretch, then (walk) at its lower end
 #pragma unroll
-        for (int k = 0; k < kFast; ++k) asm volatile("" : "+v"(T[k])); // products of the times are formed here, not kept for the next round
-        // allocate_at
+        for (int k = 0; k < K; ++k) asm volatile("" : "+v"(T[k])); // products of the times are formed here, not kept for the next round
+        // the optimum at the level mu: rounded, then one microbatch more or less where that is cheapest (the first of equals)
         const double m2 = 2.0 * (double)mu;
         int tot = 0;
 #pragma unroll
-        for (int k = 0; k < kFast; ++k)
+        for (int k = 0; k < K; ++k)
             if (k < t) {
                 const double num = m2 + T[k], two = 2.0 * T[k]; // integers below 2^53
                 double f = floor(num * (0.5 * inverse(k))); // nearest integer to mu / T, once corrected
@@ -401,44 +266,50 @@ template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const do
             }
         if (tot != a.Q) {
             const bool remove = tot > a.Q;
-            double c[kFast], most = 0; // what one microbatch less or more costs a template; what their rounding can come to
+            double c[K], most = 0; // what one microbatch less or more costs a template; what their rounding can come to
 #pragma unroll
-            for (int k = 0; k < kFast; ++k) {
+            for (int k = 0; k < K; ++k) {
                 c[k] = kHuge;
                 if (k < t) {
-                    const double sq = T[k] * T[k], q = T[k] * m2;
-                    if (remove) { if (n[k] >= 2) c[k] = q - sq * (2 * n[k] - 1); }
-                    else c[k] = sq * (2 * n[k] + 1) - q;
-                    most = fmax(most, 4.0 * kEps * (q + sq * (2 * n[k] + 1)));
+                    if (!remove || n[k] >= 2) c[k] = cost_of_one(T[k], n[k], m2, remove);
+                    most = fmax(most, 4.0 * kEps * (T[k] * m2 + T[k] * T[k] * (2 * n[k] + 1)));
                 }
             }
             for (;;) {
                 double c1 = kHuge, c2 = kHuge;
+                int pick = 0;
 #pragma unroll
-                for (int k = 0; k < kFast; ++k) {
+                for (int k = 0; k < K; ++k) {
                     c2 = fmin(c2, fmax(c1, c[k]));
+                    pick = c[k] < c1 ? k : pick;
                     c1 = fmin(c1, c[k]);
                 }
-                if (c1 >= kHuge || c2 - c1 <= most) return kHard; // (c1 is a cost: tot > Q >= pipelines, so some pipeline holds two)
+                if (c1 >= kHuge) break; // cannot happen: tot > Q >= pipelines, so some pipeline holds two
+                if (c2 - c1 <= most && !exact) { // templates of one time have the same double for the same cost
+                    const double Tp = s_tT[jx[pick * kLanes] & 0xffff];
+                    bool mixed = false;
 #pragma unroll
-                for (int k = 0; k < kFast; ++k) {
-                    if (c[k] != c1) continue;
+                    for (int k = 0; k < K; ++k) mixed |= c[k] - c1 <= most && T[k] != Tp;
+                    if (mixed) pick = exact_pick(s_tT, jx, best_ne, n, e, t, mu, remove, c1 + most);
+                }
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    if (k != pick) continue;
                     bool next; // the template's next pipeline starts over: another cost
-                    if (remove) { // Plan::take
+                    if (remove) { // a fullest pipeline gives one
                         next = e[k] == 1 || x[k] == 1;
                         if (e[k] > 0) --e[k];
                         else { --n[k]; e[k] = x[k] - 1; }
-                    } else {      // Plan::give
+                    } else {      // an emptiest one takes one
                         next = e[k] + 1 == x[k];
                         if (next) { ++n[k]; e[k] = 0; }
                         else ++e[k];
                     }
-                    if (next) { // formed anew: a sum of steps would add up their roundings, which `most` does not cover
+                    if (next) { // formed anew: sums of steps would add up their roundings
                         double Tk = T[k];
                         asm volatile("" : "+v"(Tk));
-                        const double sq = Tk * Tk, q = Tk * (2.0 * (double)mu);
-                        c[k] = !remove ? sq * (2 * n[k] + 1) - q : n[k] < 2 ? kHuge : q - sq * (2 * n[k] - 1);
-                        most = fmax(most, 4.0 * kEps * (q + sq * (2 * n[k] + 1)));
+                        c[k] = remove && n[k] < 2 ? kHuge : cost_of_one(Tk, n[k], 2.0 * (double)mu, remove);
+                        most = fmax(most, 4.0 * kEps * (Tk * (2.0 * (double)mu) + Tk * Tk * (2 * n[k] + 1)));
                     }
                 }
                 tot += remove ? -1 : 1;
@@ -447,7 +318,7 @@ template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const do
         }
         S1 = 0; S2 = 0;
 #pragma unroll
-        for (int k = 0; k < kFast; ++k)
+        for (int k = 0; k < K; ++k)
             if (k < t) {
                 const long long Tk = (long long)T[k];
                 const unsigned long long lo = (unsigned long long)n[k] * n[k], hi = (unsigned long long)(n[k] + 1) * (n[k] + 1);
@@ -457,44 +328,74 @@ template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const do
         best = (i128)xs * S2 - (i128)S1 * S1;
         if (walk) break;
         const double V = (double)best / (double)xs; // sum of squared deviations of a feasible allocation
+        // with twins the distribution met first among equal ones depends on where the path starts: it starts where the
+        // cruder bound, sqrt(V), puts it
         const double narrow = twins ? 1.0 : fmin(sqrt(D) / H, 1.0);
-        const double R = sqrt(V) * (narrow * (1.0 + 1e-9) + 1e-12) + L0 * 1e-9 + 2.0;
+        const double R = sqrt(V) * (narrow * (1.0 + 1e-9) + 1e-12) + L0 * 1e-9 + 2.0; // widened for the rounding of these few operations
         mu = L0 - R > 0 ? (long long)(L0 - R) : 0;
         mu_hi = (long long)(L0 + R) + 1;
         bool only = true; // one end after the other: together they take more registers than the kernel has
 #pragma unroll 1
         for (int side = 0; side < 2; ++side) only &= settled(side ? (double)mu_hi : (double)mu);
-        if (only) break;
-        if (!FOLLOW) { open = true; break; }
+        if (only && !twins) break;
+        if constexpr (!FOLLOW) { open = true; break; }
         walk = true;
     }
 #pragma unroll
-    for (int k = 0; k < kFast; ++k)
+    for (int k = 0; k < K; ++k)
         if (k < t) best_ne[k * kLanes] = (unsigned)n[k] | (unsigned)e[k] << 16;
     if constexpr (FOLLOW) {
-        ne += lane; // the allocation once more in LDS, for the templates that give
 #pragma unroll
-        for (int k = 0; k < kFast; ++k)
+        for (int k = 0; k < K; ++k) // the allocation once more in LDS, for the templates that give
             if (walk && k < t) ne[k * kLanes] = (unsigned)n[k] | (unsigned)e[k] << 16;
         while (walk && !settled((double)mu_hi)) {
-            int bd = -1, br = -1; // the next exchange, see solve_general
+            // the next exchange: a microbatch of a fullest pipeline of template d (n_d of them) goes to an emptiest
+            // pipeline of a slower template r (n_r): it pays from the level c / w on,
+            // c = T_d^2 + T_r^2 - 2 T_d^2 n_d + 2 T_r^2 n_r,  w = 2 (T_r - T_d) > 0; the first of the smallest levels
+            int bd = -1, br = -1;
             double bc = 0, be = 0, bw = 1;
+            bool near = false;
             for (int d = 0; d < t; ++d) {
                 const unsigned wd = ne[d * kLanes];
                 const int nd = (int)(wd & 0xffff) + (wd >> 16 ? 1 : 0);
                 const double Td = s_tT[jx[d * kLanes] & 0xffff], cd = Td * Td * (1 - 2 * nd);
                 if (nd < 2) continue;
 #pragma unroll
-                for (int r = 0; r < kFast; ++r) {
+                for (int r = 0; r < K; ++r) {
                     const double Tr = T[r];
                     if (r >= t || Tr <= Td) continue;
                     const double cr = Tr * Tr * (1 + 2 * n[r]), c = cd + cr, w = 2.0 * (Tr - Td); // w exact
                     const double err = (cr - cd) * kEps, diff = c * bw - bc * w;
-                    ok &= bd < 0 || fabs(diff) > 2.0 * (err * bw + be * w);
+                    near |= bd >= 0 && fabs(diff) <= 2.0 * (err * bw + be * w);
                     if (bd < 0 || diff < 0) { bc = c; be = err; bw = w; bd = d; br = r; }
                 }
             }
-            if (!ok) return kHard;
+            if (near && !exact) { // once more, exactly, among those that the rounding does not put above the smallest
+                const double mc = bc, me = be, mw = bw;
+                i128 xc = 0;
+                long long xw = 1;
+                bd = -1;
+                for (int d = 0; d < t; ++d) {
+                    const unsigned wd = ne[d * kLanes];
+                    const int nd = (int)(wd & 0xffff) + (wd >> 16 ? 1 : 0);
+                    const double Td = s_tT[jx[d * kLanes] & 0xffff], cd = Td * Td * (1 - 2 * nd);
+                    if (nd < 2) continue;
+                    unsigned hits = 0;
+#pragma unroll
+                    for (int r = 0; r < K; ++r) {
+                        const double Tr = T[r];
+                        if (r >= t || Tr <= Td) continue;
+                        const double cr = Tr * Tr * (1 + 2 * n[r]), c = cd + cr, w = 2.0 * (Tr - Td);
+                        if (c * mw - mc * w <= 2.0 * ((cr - cd) * kEps * mw + me * w)) hits |= 1u << r;
+                    }
+                    for (; hits; hits &= hits - 1) {
+                        const int r = __ffs((int)hits) - 1;
+                        const long long kd = (long long)Td, kr = (long long)s_tT[jx[r * kLanes] & 0xffff], ew = kr - kd; // below 2^36
+                        const i128 ec = (i128)kd * (kd * (1 - 2 * nd)) + (i128)kr * (kr * (1 + 2 * (int)(ne[r * kLanes] & 0xffff)));
+                        if (bd < 0 || ec * xw < xc * ew) { xc = ec; xw = ew; bd = d; br = r; }
+                    }
+                }
+            }
             if (bd < 0) break;
             const unsigned xd = jx[bd * kLanes], xr = jx[br * kLanes];
             const long long Td = (long long)s_tT[xd & 0xffff], Tr = (long long)s_tT[xr & 0xffff];
@@ -504,12 +405,12 @@ template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const do
             if (change > (i128)(2 * (Tr - Td)) * mu_hi) break; // past the stretch
             S1 += Tr - Td;
             S2 += change;
-            wd = wd >> 16 ? wd - 0x10000u : (wd - 1) | ((xd >> 16) - 1) << 16;   // Plan::take
-            wr = (wr >> 16) + 1 == xr >> 16 ? (wr & 0xffff) + 1 : wr + 0x10000u; // Plan::give
+            wd = wd >> 16 ? wd - 0x10000u : (wd - 1) | ((xd >> 16) - 1) << 16;   // a fullest pipeline gives
+            wr = (wr >> 16) + 1 == xr >> 16 ? (wr & 0xffff) + 1 : wr + 0x10000u; // an emptiest one takes
             ne[bd * kLanes] = wd;
             ne[br * kLanes] = wr;
 #pragma unroll
-            for (int k = 0; k < kFast; ++k) {
+            for (int k = 0; k < K; ++k) {
                 if (k == bd) { n[k] = (int)(wd & 0xffff); e[k] = (int)(wd >> 16); }
                 if (k == br) { n[k] = (int)(wr & 0xffff); e[k] = (int)(wr >> 16); }
             }
@@ -520,13 +421,18 @@ template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const do
             }
         }
     }
+    if (open) {
+        a.vx[2 * i] = (unsigned long long)mu;
+        a.vx[2 * i + 1] = (unsigned long long)mu_hi;
+        if (!a.lists) return false;
+    }
     long long slow = 0;
     for (int k = 0; k < t; ++k) {
         const unsigned w = best_ne[k * kLanes];
         const long long time = (long long)((w & 0xffff) + (w >> 16 ? 1 : 0)) * (long long)s_tT[jx[k * kLanes] & 0xffff];
         slow = time > slow ? time : slow;
     }
-    if (FOLLOW && *listed) { // the other entries are zeros
+    if (FOLLOW && from_list) { // the other entries are zeros
         for (int k = 0; k < t; ++k) a.base[k * a.capacity + i] = a.extra[k * a.capacity + i] = 0;
         for (int k = 0; k < t; ++k) {
             const unsigned w = best_ne[k * kLanes];
@@ -534,31 +440,15 @@ template <bool FOLLOW> __device__ int solve_in_registers(const Args &a, const do
             a.base[at] = (unsigned short)w;
             a.extra[at] = (unsigned short)(w >> 16);
         }
-    } else if (a.base) { // every entry written once
-        int k = 0;
-        unsigned next = open ? 0 : jx[0] & 0xffff, have = open ? jx[0] : best_ne[0];
-        for (int j = 0; j < a.p; ++j) {
-            unsigned w = 0;
-            if ((unsigned)j == next) {
-                w = have;
-                ++k;
-                const unsigned row = k < t ? jx[k * kLanes] : 0xffffu;
-                next = open && k < t ? (unsigned)k : row & 0xffff;
-                have = open ? row : k < t ? best_ne[k * kLanes] : 0;
-            }
-            a.base[(long long)j * a.capacity + i] = (unsigned short)w;
-            a.extra[(long long)j * a.capacity + i] = (unsigned short)(w >> 16);
-        }
+    } else if (a.base) {
+        write_rows(a, i, jx, best_ne, t, open);
     }
-    if (!FOLLOW && open) {
-        *listed = t;
-        return kLeft;
-    }
+    if (open) return false;
     a.status[i] = OOB_DIST_OK;
     a.vx[2 * i] = (unsigned long long)best;
     a.vx[2 * i + 1] = (unsigned long long)(best >> 64);
     a.slowest[i] = slow;
-    return kDone;
+    return true;
 }
 
 __device__ __forceinline__ void load_times(const Args &a, double *s_tT) { // [p], then [p] reciprocals
@@ -570,56 +460,124 @@ __device__ __forceinline__ void load_times(const Args &a, double *s_tT) { // [p]
     __syncthreads();
 }
 
-// The plans without an exchange on their stretch; the others are marked in `status`.
-constexpr int kMarked = 1 << 30; // and the templates that are listed (0: none)
-__global__ void __launch_bounds__(kFirstThreads, 4) k_dist_first(Args a) {
+// The first of two launches: the plans that cannot be solved and those of at most kFew templates, with FOLLOW = false only where no exchange
+// lies on the stretch.  The others get a mark in `status`, kMarked + templates << 8 + rank among the workgroup's plans of at most kFew
+// templates, or of more; where base and extra can hold it, their list stands there (with the counts read once more the second launch took
+// 170 us instead of 85).
+constexpr int kMarked = 1 << 30;
+template <bool FOLLOW> __global__ void __launch_bounds__(kFirstThreads, FOLLOW ? 3 : 4) k_dist_first(Args a) {
+    constexpr int W = (kT + (FOLLOW ? 2 : 1) * kFew) * kLanes;
     HIP_DYNAMIC_SHARED(double, s_tT)
-    __shared__ Listed s_listed[kFirstThreads / kLanes];
+    __shared__ unsigned s_words[kFirstThreads / kLanes * W]; // of a wave: lists, best and current allocations
+    __shared__ int s_ranks[2];
+    if (threadIdx.x < 2) s_ranks[threadIdx.x] = 0;
     load_times(a, s_tT);
     const long long i = (long long)blockIdx.x * kFirstThreads + threadIdx.x;
     if (i >= a.count) return;
-    int listed = 0;
-    if (solve_in_registers<false>(a, s_tT, s_listed[threadIdx.x / kLanes], nullptr, i, threadIdx.x & (kLanes - 1), &listed) != kDone)
-        a.status[i] = kMarked + listed;
+    const int lane = threadIdx.x & (kLanes - 1);
+    unsigned *const jx = s_words + threadIdx.x / kLanes * W + lane, *const best_ne = jx + kT * kLanes;
+    int xs;
+    const int t = list_templates(a, i, jx, kT, &xs);
+    bool left = false;
+    if (t <= kFew) {
+        left = !solve<kFew, FOLLOW>(a, s_tT, jx, best_ne, best_ne + kFew * kLanes, i, t, xs, 0, -1, false);
+    } else if (t > kT) {
+        refuse_many(a, s_tT, jx, i);
+    } else {
+        left = true;
+        if (a.lists) write_rows(a, i, jx, jx, t, true);
+    }
+#pragma unroll
+    for (int kind = 0; kind < 2; ++kind) { // a wave's places in one step
+        const bool mine = left && (t > kFew) == kind;
+        const unsigned long long m = __ballot(mine);
+        int rank = 0;
+        if (m && lane == __ffsll((long long)m) - 1) rank = atomicAdd(&s_ranks[kind], __popcll(m));
+        if (m) rank = __shfl(rank, __ffsll((long long)m) - 1) + __popcll(m & ((1ull << lane) - 1));
+        if (mine) a.status[i] = kMarked + (t << 8) + rank;
+    }
 }
 
-// The marked ones of `span` consecutive plans (all of them if marked = 0), side by side: those whose path can be followed in LDS, then
-// the hard ones.
-__global__ void __launch_bounds__(kLanes, 3) k_dist_rest(Args a, int span, int marked) {
-    HIP_DYNAMIC_SHARED(double, s_tT) // the times, then twice [span] 16-bit numbers of plans
-    __shared__ union { General general; Walked walked; } s;
-    unsigned short *const left = (unsigned short *)(s_tT + 2 * a.p), *const hard = left + span;
-    const int lane = threadIdx.x;
+// The only launch for few plans: all of them, 64 to a wave.
+__global__ void __launch_bounds__(kLanes, 2) k_dist_once(Args a) {
+    constexpr int W = kT * kLanes;
+    HIP_DYNAMIC_SHARED(double, s_tT)
+    __shared__ unsigned s_words[3 * W]; // lists, best and current allocations
     load_times(a, s_tT);
-    const long long i0 = (long long)blockIdx.x * span;
+    const int lane = threadIdx.x;
+    const long long i = (long long)blockIdx.x * kLanes + lane;
+    unsigned *const jx = s_words + lane;
+    int xs = 0, t = 0;
+    if (i < a.count) {
+        t = list_templates(a, i, jx, kT, &xs);
+        if (t > kT) refuse_many(a, s_tT, jx, i);
+        else if (t <= kFew) solve<kFew, true>(a, s_tT, jx, jx + W, jx + 2 * W, i, t, xs, 0, -1, false);
+    }
+    if (t > kFew && t <= kT) solve<kT, true>(a, s_tT, jx, jx + W, jx + 2 * W, i, t, xs, 0, -1, false);
+}
+
+// The list of t <= K templates that the first launch left for plan i, read where it is, or from the counts.  Returns the pipelines.
+template <int K> __device__ __forceinline__ int listed(const Args &a, long long i, unsigned *jx, int t) {
+    int xs = 0;
+    if (a.lists) {
+        unsigned v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = k < t ? (unsigned)a.base[k * a.capacity + i] | (unsigned)a.extra[k * a.capacity + i] << 16 : 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            jx[k * kLanes] = v[k];
+            xs += (int)(v[k] >> 16);
+        }
+    } else {
+        list_templates(a, i, jx, K, &xs);
+    }
+    return xs;
+}
+
+// The second launch: the marked ones of `span` consecutive plans, side by side, those of few templates and then the others.  `slices` waves, `spans`
+// workgroups apart, share a span: a wave has the plans whose rank / ranks is its slice modulo `slices`.  Who has a plan depends on its mark
+// alone, and nobody else writes that: the marks of others may be there or gone.
+__global__ void __launch_bounds__(kLanes, 2) k_dist_rest(Args a, int span, int spans, int slices) {
+    HIP_DYNAMIC_SHARED(double, s_tT) // the times, then [span] 16-bit numbers of plans: few templates from the front, many from the back
+    __shared__ unsigned s_words[3 * kT * kLanes]; // lists, best and current allocations
+    unsigned short *const marked = (unsigned short *)(s_tT + 2 * a.p);
+    const int lane = threadIdx.x, slice = blockIdx.x / spans, ranks = kLanes * kFirstThreads / span;
+    const long long i0 = (long long)(blockIdx.x - slice * spans) * span;
     const unsigned long long below = (1ull << lane) - 1;
-    int nleft = 0, nhard = 0;
-    for (int o0 = 0; o0 < span; o0 += kLanes * kLoads) {
-        int st[kLoads];
+    int few = 0, many = 0;
+    for (int o0 = 0; o0 < span; o0 += kLanes * kScan) {
+        int st[kScan];
 #pragma unroll
-        for (int q = 0; q < kLoads; ++q) {
+        for (int q = 0; q < kScan; ++q) {
             const long long i = i0 + o0 + q * kLanes + lane;
-            st[q] = o0 + q * kLanes < span && i < a.count ? marked ? a.status[i] : kMarked : 0;
+            st[q] = i < a.count ? a.status[i] : 0;
         }
 #pragma unroll
-        for (int q = 0; q < kLoads; ++q) {
-            const unsigned long long m = __ballot(st[q] >= kMarked);
-            if (st[q] >= kMarked) left[nleft + __popcll(m & below)] = (unsigned short)((o0 + q * kLanes + lane) | (st[q] - kMarked) << kSpanBits);
-            nleft += __popcll(m);
+        for (int q = 0; q < kScan; ++q) {
+            const int t = st[q] >> 8 & 31;
+            const bool mine = st[q] >= kMarked && (st[q] & 255) / ranks % slices == slice;
+            const unsigned long long mf = __ballot(mine && t <= kFew), mm = __ballot(mine && t > kFew);
+            const unsigned short w = (unsigned short)((o0 + q * kLanes + lane) | t << kSpanBits);
+            if (mine) marked[t <= kFew ? few + __popcll(mf & below) : span - 1 - many - __popcll(mm & below)] = w;
+            few += __popcll(mf);
+            many += __popcll(mm);
         }
     }
-    __syncthreads();
-    for (int q = lane; q - lane < nleft; q += kLanes) {
-        const int w = q < nleft ? left[q] : 0, o = w & ((1 << kSpanBits) - 1);
-        int got = kDone, listed = a.base ? w >> kSpanBits : 0;
-        if (q < nleft) got = a.lists ? solve_in_registers<true>(a, s_tT, s.walked.ls, s.walked.ne, i0 + o, lane, &listed) : kHard;
-        const unsigned long long m = __ballot(got == kHard);
-        if (got == kHard) hard[nhard + __popcll(m & below)] = (unsigned short)o;
-        nhard += __popcll(m);
+    if (few + many == 0) return; // uniform
+    load_times(a, s_tT);
+    unsigned *const jx = s_words + lane, *const best_ne = jx + kT * kLanes, *const ne = best_ne + kT * kLanes;
+    for (int q = lane; q < few; q += kLanes) {
+        const int w = marked[q], t = w >> kSpanBits;
+        const long long i = i0 + (w & ((1 << kSpanBits) - 1));
+        const int xs = listed<kFew>(a, i, jx, t);
+        solve<kFew, true>(a, s_tT, jx, best_ne, ne, i, t, xs, (long long)a.vx[2 * i], (long long)a.vx[2 * i + 1], a.lists);
     }
-    __syncthreads();
-    if (lane < kGeneral)
-        for (int q = lane; q < nhard; q += kGeneral) solve_general(a, s_tT, s.general, i0 + hard[q], lane);
+    for (int q = lane; q < many; q += kLanes) {
+        const int w = marked[span - 1 - q], t = w >> kSpanBits;
+        const long long i = i0 + (w & ((1 << kSpanBits) - 1));
+        const int xs = listed<kT>(a, i, jx, t);
+        solve<kT, true>(a, s_tT, jx, best_ne, ne, i, t, xs, 0, -1, a.lists);
+    }
 }
 
 // Plan choice: the smallest `slowest` among the solved plans of a group, the first of equals.
@@ -705,15 +663,21 @@ extern "C" int oob_dist_solve(const uint16_t *x, int64_t count, int64_t capacity
     Args a;
     a.x = x; a.count = count; a.capacity = capacity; a.p = p; a.tT = (const long long *)template_T; a.Q = Q;
     a.vx = (unsigned long long *)vx; a.slowest = (long long *)slowest; a.base = base; a.extra = extra; a.status = status;
-    // What is left by the first launch has its list where its distribution goes, and its counts are read again if it turns out to be hard.
-    // solve_general reads all counts of a plan before it writes: it takes arrays that share entries, whole rows apart.
-    a.lists = !base || (apart(x, base, p, capacity) && apart(x, extra, p, capacity) && apart(base, extra, p, capacity));
-    const bool twice = count > kOnce && a.lists;
-    const int span = twice ? kSpan : kLanes;
     const size_t times = 2 * (size_t)p * sizeof(double);
-    if (twice) hipLaunchKernelGGL(k_dist_first, dim3((unsigned)((count + kFirstThreads - 1) / kFirstThreads)), dim3(kFirstThreads), times, (hipStream_t)stream, a);
-    hipLaunchKernelGGL(k_dist_rest, dim3((unsigned)((count + span - 1) / span)), dim3(kLanes), times + 2 * span * sizeof(unsigned short), (hipStream_t)stream, a, span,
-                       (int)twice);
+    hipStream_t st = (hipStream_t)stream;
+    if (count <= kOnce) {
+        a.lists = 0;
+        hipLaunchKernelGGL(k_dist_once, dim3((unsigned)((count + kLanes - 1) / kLanes)), dim3(kLanes), times, st, a);
+    } else {
+        a.lists = base && apart(x, base, p, capacity) && apart(x, extra, p, capacity) && apart(base, extra, p, capacity);
+        const bool follow = count <= kFollow;
+        const int span = follow ? kFirstThreads : 1 << kSpanBits;
+        const long long spans = (count + span - 1) / span;
+        const int slices = (int)std::min<long long>(span / kLanes, std::max(1ll, kRestWaves / spans));
+        hipLaunchKernelGGL(follow ? k_dist_first<true> : k_dist_first<false>, dim3((unsigned)((count + kFirstThreads - 1) / kFirstThreads)),
+                           dim3(kFirstThreads), times, st, a);
+        hipLaunchKernelGGL(k_dist_rest, dim3((unsigned)(spans * slices)), dim3(kLanes), times + span * sizeof(unsigned short), st, a, span, (int)spans, slices);
+    }
     return hipGetLastError() == hipSuccess ? OOB_OK : OOB_EHIP;
 }
 

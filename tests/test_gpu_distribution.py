@@ -162,6 +162,103 @@ def test_many_plans_in_two_launches(P, Q, distribution):
         assert got[3] is None and got[4] is None
 
 
+def times_of(kind, p, rng):
+    if kind == "equal":
+        return [2 * 10**9 + 7] * p
+    if kind == "falling":
+        return [16 * 10**9 // (8 + j) for j in range(p)]
+    if kind == "plateau":
+        return [max(16 * 10**9 // (8 + j), 10**9) for j in range(p)]
+    if kind == "coarse":
+        return [rng.randint(5, 20) * 10**8 for _ in range(p)]
+    if kind == "tiny":
+        return [rng.randint(1, 12) for _ in range(p)]
+    return [rng.choice([2046, 2047, 2048, 2049, 1024, 4096, 3]) for _ in range(p)]  # around what doubles hold exactly
+
+
+@pytest.mark.parametrize("kind", ["equal", "falling", "plateau", "coarse", "tiny", "edge"])
+def test_ties_and_long_paths_in_every_launch(P, kind):
+    """Times that make exact ties of costs and of levels, twins and plans of which most have a path: up to ten templates, more, and more
+    than there may be; all plans in one launch, with paths in the first launch, in the second one, and in the place of their counts."""
+    rng = random.Random(kind)
+    p, Q = 30, 45
+    tT = times_of(kind, p, rng)
+    vecs = []
+    for i in range(96):
+        v = [0] * p
+        for j in rng.sample(range(p), 1 + i % 16):
+            v[j] = rng.choice([1, 1, 1, 2, 3])
+        vecs.append(v)
+    compare(P, vecs, tT, Q, exhaustive=False)
+    vecs += [[0] * p, [1] * 17 + [0] * 13, [2] * p, [0] * 29 + [Q + 1]]
+    want = P.Distributor(vecs, len(vecs), tT, Q).solve()
+    assert want[0][96:].tolist() == [P.OOB_DIST_NO_PIPELINE, P.OOB_DIST_TOO_MANY_TEMPLATES, P.OOB_DIST_TOO_MANY_TEMPLATES,
+                                     P.OOB_DIST_TOO_FEW_MICROBATCHES]
+    for count in (131072, 131073, 196608, 196609, 1024 * 200 + 1):
+        pick = np.random.Generator(np.random.PCG64(count)).integers(0, len(vecs), size=count)
+        for inplace in (False, True):
+            d = P.Distributor(np.asarray(vecs)[pick], count, tT, Q)
+            if inplace:
+                d.extra = d.x
+            got = d.solve()
+            assert np.array_equal(got[0], want[0][pick]) and np.array_equal(got[2], want[2][pick]), (count, inplace)
+            assert got[1] == [want[1][i] for i in pick]
+            assert np.array_equal(got[3], want[3][pick]) and np.array_equal(got[4], want[4][pick])
+
+
+@pytest.mark.parametrize("share", [0, 1, 15, 16, 17, 63, 64, 65, 255, 256])
+def test_numbers_of_plans_left_to_the_second_launch(P, share):
+    """Of every 256 plans `share` have an exchange on their path, of few templates or of many, the others do not: around the shares of a wave.
+    The plans left over are the first, the last and scattered ones."""
+    tT = [10**9 + j for j in range(12)] + [3 * 10**9]
+    few = [1] * 4 + [0] * 8 + [1]
+    many = [1] * 12 + [0]
+    plain = [0] * 12 + [5]
+    compare(P, [plain, few, many], tT, 45, exhaustive=False)
+    want = P.Distributor([plain, few, many], 3, tT, 45).solve()
+    for count in (131072 + 300, 196608 + 1024 * 3 + 300):
+        at = np.arange(count) % 256
+        left = [at < share, at >= 256 - share, np.random.Generator(np.random.PCG64(share)).permutation(256)[at] < share]
+        for where in left:
+            pick = np.where(where, 1 + (np.arange(count) // 256 % 3 == 0), 0)
+            got = P.Distributor(np.asarray([plain, few, many])[pick], count, tT, 45).solve()
+            assert np.array_equal(got[0], want[0][pick]) and np.array_equal(got[2], want[2][pick])
+            assert got[1] == [want[1][i] for i in pick]
+            assert np.array_equal(got[3], want[3][pick]) and np.array_equal(got[4], want[4][pick])
+
+
+def test_time_does_not_hang_on_the_template_times(P):
+    """200 000 plans of one to ten templates, or of eleven to sixteen: times that are all equal, fall as 1 / nodes or lie on a coarse grid make
+    ties and paths for most plans.  What a call takes may differ by a small factor (two and five here), not by forty."""
+    import torch
+
+    rng = random.Random(1)
+    p, count = 57, 200000
+
+    def us(lo, hi, kind):
+        tT = times_of(kind, p, rng) if kind else [2 * 10**9 + j * (3 * 10**7 + 12345) for j in range(p)]
+        vecs = np.zeros((512, p), dtype=np.uint16)
+        for v in vecs:
+            v[rng.sample(range(p), rng.randint(lo, hi))] = 1
+        d = P.Distributor(vecs[np.arange(count) % 512], count, tT, 512)
+        took = []
+        for _ in range(5):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            d.enqueue()
+            ev[1].record()
+            torch.cuda.synchronize()
+            took.append(ev[0].elapsed_time(ev[1]) * 1e3)
+        return sorted(took)[2]
+
+    spread = us(1, 10, None)
+    for kind, factor in (("equal", 6), ("falling", 6), ("coarse", 20)):
+        took = us(1, 10, kind)
+        print(kind, round(spread), round(took), flush=True)
+        assert took < factor * spread, kind
+    assert us(11, 16, None) < 12 * spread
+
+
 @pytest.mark.parametrize("out", ["base", "extra"])
 def test_a_distribution_may_overwrite_the_counts(P, out):
     """base or extra in the place of x, with more plans than one launch takes, a part of them beyond what the first launch does:
