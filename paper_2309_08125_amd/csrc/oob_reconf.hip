@@ -163,9 +163,9 @@ __device__ void run_in_lds(const Args &a, long long t, unsigned short *mine) {
 // most kPackedNodes = 128 nodes (a running sum of sizes then fits its byte, and (128 | r) - sum neither borrows
 // nor loses its top bit) and at most 4 W starting pipelines.
 //
-// What bounds it: the vector ALUs (176 instructions a wave and loss) at first, the 8 bytes a loss moves next.  With the
-// sizes in LDS a step read every position twice from there and the merge walked the list position by position: 318 us
-// for 2^20 sequences of 57 losses of one node with 13 pipelines, against 258 us here.
+// What bounds it: the vector ALUs (165 instructions a wave and loss: 255 of the 281 us that 2^20 sequences of 29 bursts of two nodes with 13
+// pipelines take; 12 bursts of five 312 us).  With the sizes in LDS a step read every position twice from there and the merge walked the list
+// position by position: 318 us for 57 losses one by one, which took 258 us here before run_single_losses.
 constexpr unsigned kTops = 0x80808080u;
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned pk_max(unsigned x, unsigned y) {
@@ -480,9 +480,10 @@ template <int W> __device__ void run_single_losses(const Args &a, long long node
     write_summary(a, t, survived, survived - merges - (int)borrowed, (int)borrowed, merges, (int)left, (int)total, viol, stop);
 }
 
-// W: words of packed sizes, 0 for more than 16 starting pipelines.  The number of nodes is in device memory: a list of
-// more than kPackedNodes takes the sizes in LDS, the same branch for every lane.
-template <int W> __global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
+// W: words of packed sizes, 0 for more than 16 starting pipelines.  SINGLE: steps of one node.  The number of nodes is in device memory: a
+// list of more than kPackedNodes takes the sizes in LDS, the same branch for every lane.  (One kernel for both kinds of steps: bursts of 2 to
+// 10 nodes with 4 pipelines took 2-14 % longer, 100 and 107 us for 2^20 sequences of 19 bursts of two.)
+template <int W, bool SINGLE> __global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
     HIP_DYNAMIC_SHARED(unsigned short, sizes) // [rows][kLanes], rows = c0 rounded up to kUnroll
     const long long t = (long long)blockIdx.x * kLanes + threadIdx.x;
     const long long nodes = start_nodes(a);
@@ -491,12 +492,17 @@ template <int W> __global__ void __launch_bounds__(kLanes) k_reconf(Args a) {
     if (!ok || t >= a.T) return;
     if constexpr (W > 0) {
         if (nodes <= kPackedNodes) {
-            if (a.burst == 1) run_single_losses<W>(a, nodes);
+            if constexpr (SINGLE) run_single_losses<W>(a, nodes);
             else run_in_registers<W>(a, t);
             return;
         }
     }
     run_in_lds(a, t, sizes + threadIdx.x);
+}
+
+template <bool SINGLE> static auto kernel_for(int words) {
+    return words == 1 ? k_reconf<1, SINGLE> : words == 2 ? k_reconf<2, SINGLE> : words == 3 ? k_reconf<3, SINGLE>
+         : words == kPackedWords ? k_reconf<kPackedWords, SINGLE> : k_reconf<0, false>;
 }
 
 } // namespace oob_reconf
@@ -520,8 +526,6 @@ extern "C" int oob_reconf_simulate(const int32_t *sizes0, int c0, int n0, int n_
     a.trace = trace; a.final_sizes = final_sizes; a.summary = summary; a.status = status;
     const size_t lds = (size_t)((c0 + kUnroll - 1) / kUnroll * kUnroll) * kLanes * sizeof(unsigned short); // <= 32 KB
     const int words = (c0 + 3) / 4;
-    const auto kernel = words == 1 ? k_reconf<1> : words == 2 ? k_reconf<2> : words == 3 ? k_reconf<3>
-                      : words == kPackedWords ? k_reconf<kPackedWords> : k_reconf<0>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kLanes), lds, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(burst == 1 ? kernel_for<true>(words) : kernel_for<false>(words), dim3((unsigned)blocks), dim3(kLanes), lds, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? OOB_OK : OOB_EHIP;
 }
