@@ -284,10 +284,13 @@ template <int N, typename T> __device__ __forceinline__ void scan_lanes(T (&v)[N
 constexpr int kScanChunk = 6;          // most q's of a wave
 constexpr float kFits = 4252017623.0f; // 0.99 * 2^32
 constexpr int kCountWaves = kCountThreads / 64;
-// A step of the scans takes about as long as a plane of count_planes; there are N_hi / side steps and p planes, and the scans take
-// longer to set up.  Planes and scans: 28 sizes 3..30, 45 nodes (15 steps) 14.5 and 12.7 us, 39 sizes 2..40, 48 nodes (24 steps)
+// Whether the scans are faster than the planes.  A step of the scans takes about as long as a plane of count_planes; there are N_hi / side
+// steps and p planes, and the scans take longer to set up.  Planes of fewer than 512 counts leave most threads without work and pass
+// faster.  Planes and scans: 28 sizes 3..30, 45 nodes (15 steps) 14.5 and 12.7 us, 39 sizes 2..40, 48 nodes (24 steps)
 // 18.8 and 16.9 us; but 15 sizes 2..16, 22 nodes (11 steps) 7.7 and 11.4 us, 40 sizes 1..40, 48 nodes (48 steps) 22.0 and 28.9 us.
-constexpr int kScanFixed = 10;
+// Below 512 counts, f = 0: 13 sizes 12..24, 24 nodes (2 steps) 5.9 and 7.5 us, 16 sizes 8..24 (3 steps) 7.1 and 7.7 us.  Of 1 300 specifications
+// of up to 64 sizes with f up to 20 the scans are slower for seven by this line (5 % at most; six of them outgrow 32 bits), for 115 with 10 throughout.
+__host__ __device__ inline bool scans_pay(int p, int N_hi, int QQ, int side) { return p >= ((N_hi + 1) * QQ < 512 ? 16 : 10) + N_hi / side; }
 
 // Where the kept counts are.  A row: C(., N', 0) once more, C(., N', q) for the q's of all chunks, the first in floating point.
 struct Scan {
@@ -301,9 +304,10 @@ __device__ bool scan_layout(const Spec &s, const int *size, int words, Scan *sc)
     if (s.p > 63) return false;
     sc->chunks = (QQ + kScanChunk - 1) / kScanChunk;
     if (sc->chunks > kCountWaves) return false;
+    sc->side = kCountWaves / sc->chunks < size[0] ? kCountWaves / sc->chunks : size[0];
+    if (!scans_pay(s.p, s.N_hi, QQ, sc->side)) return false;
     sc->chunk = (QQ + sc->chunks - 1) / sc->chunks;
     sc->row = (sc->chunk * sc->chunks + 2) | 1;
-    sc->side = kCountWaves / sc->chunks < size[0] ? kCountWaves / sc->chunks : size[0];
     const int n = lane >= 1 && lane <= s.p ? size[lane - 1] : 0;
     sc->len = n ? (n < s.N_hi + 1 ? n : s.N_hi + 1) + sc->side : 0;
     unsigned upto[1] = {(unsigned)sc->len}; // at most 63 * (1215 + 16) in all
@@ -312,7 +316,7 @@ __device__ bool scan_layout(const Spec &s, const int *size, int words, Scan *sc)
     sc->none = rows * sc->row;
     sc->base = sc->len ? ((int)upto[0] - sc->len) * sc->row : sc->none;
     sc->need = (rows + 2) * sc->row + s.N_hi + 1;
-    return sc->need <= words && s.p >= kScanFixed + s.N_hi / sc->side;
+    return sc->need <= words;
 }
 
 // Called by the whole workgroup.
@@ -594,10 +598,9 @@ static int launch_count(const Spec &s, int64_t *offsets, int32_t *status, hipStr
     const size_t scan = (size_t)(s.N_hi - s.N_lo + 2) * sizeof(long long);
     if (kGroup * plane <= kRingLdsBytes) { // faster wherever it fits, see the kernel
         // as many node counts a step as the smallest size, if it is known, and a wave can have at most (scan_layout)
-        const bool scan = s.p <= 63 && !keep_wide &&
-                          s.p >= kScanFixed + s.N_hi / (s.sizes || s.n0 > kCountWaves ? kCountWaves : s.n0);
-        const size_t lds = scan ? kRingLdsBytes : kGroup * plane; // one workgroup: the scans may have all there is
-        const auto kernel = scan ? k_inst_count_ring<true> : k_inst_count_ring<false>;
+        const bool by_scan = s.p <= 63 && !keep_wide && scans_pay(s.p, s.N_hi, s.Q + 1, s.sizes || s.n0 > kCountWaves ? kCountWaves : s.n0);
+        const size_t lds = by_scan ? kRingLdsBytes : kGroup * plane; // one workgroup: the scans may have all there is
+        const auto kernel = by_scan ? k_inst_count_ring<true> : k_inst_count_ring<false>;
         if (lds > 48 * 1024 && // with the 4 KB of sizes above what a launch may ask for unannounced
             hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return OOB_EHIP;

@@ -227,3 +227,29 @@ def test_count_table_by_node_counts(P, f):
         else:
             table = ws[256: 256 + 8 * n].view(torch.int64).numpy().reshape(N_hi + 1, f + 2, R)
         assert np.array_equal(table[:, :, : p + 1], C)
+
+
+@pytest.mark.parametrize("listed", [False, True])
+@pytest.mark.parametrize("N_hi,f,least", [(40, 2, 24), (126, 2, 41), (127, 2, 35), (63, 6, 22), (100, 0, 36)])
+def test_count_table_at_the_line_between_planes_and_scans(P, N_hi, f, least, listed):
+    """`least` sizes from 5 on are counted by node counts (steps of five), fewer by sizes: 10 and N_hi / 5 sizes, 16 where a plane has
+    fewer than 512 counts.  The lengths and the whole table against the recurrence, on both sides of the line."""
+    assert least == (16 if (N_hi + 1) * (f + 2) < 512 else 10) + N_hi // 5
+    for p in (least - 1, least, least + 1):
+        R = (p + 8) // 8 * 8
+        C = np.zeros((N_hi + 1, f + 2, p + 1), dtype=np.int64)
+        C[0, 0] = 1
+        for j in range(p):
+            n = 5 + j
+            C[:, :, j + 1] = C[:, :, j]
+            for x in range(n, N_hi + 1):
+                C[x, 1:, j + 1] += C[x - n, :-1, j + 1]
+                C[x, 0, j + 1] += C[x - n, 0, j + 1]
+        assert C.max() < 1 << 32
+        inst = P.Instantiator(list(range(5, 5 + p)), 0, N_hi, f) if listed else P.Instantiator(None, 0, N_hi, f, n0=5, p=p)
+        off, st = inst.count()
+        assert st == P.OOB_OK and np.array_equal(off, np.concatenate([[0], np.cumsum(C[:, f + 1, p])])), p
+        ws, n = inst.workspace.cpu().numpy(), (N_hi + 1) * (f + 2) * R
+        at = 256 + (8 * n + 255) // 256 * 256
+        table = ws[at: at + 4 * n].view("uint32").reshape(N_hi + 1, f + 2, R)
+        assert np.array_equal(table[:, :, : p + 1], C), p
