@@ -42,7 +42,8 @@ __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ inline int dlo_of(int S, int M) { return S <= M ? S - 1 : M - 2 + cdiv(S, M); }
 __host__ __device__ inline int dhi_of(int S, int M, int n_max) { return M - 2 + imin(S, n_max); }
 
-// floor(k / M) by a product: exact for k < 2^14 and M <= 64 (k (inv M - 2^20) < 2^20).
+// floor(k / M) by a product, exact for k < kOverMBelow and M <= 64: k (inv M - 2^20) < 2^20, and k inv < 2^32 also for M = 1.
+constexpr int kOverMBelow = 1 << 12;
 __host__ __device__ inline int inverse_of(int M) { return (1 << 20) / M + 1; }
 __host__ __device__ inline int over_M(int k, int inv_M) { return (int)((unsigned)k * (unsigned)inv_M >> 20); }
 

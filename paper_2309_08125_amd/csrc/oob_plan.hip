@@ -2005,6 +2005,10 @@ extern "C" int oob_plan_layout_selftest(int L) {
     if (L < 1 || L > OOB_MAX_L) return OOB_EINVAL;
     const int NB = nblocks_of(L), c = col_shift(L), recs = tri_blocks(NB) * 64;
     if ((L + c + 1) % 8 != 0 || (L + c) / 8 != NB - 1) return 1;
+    static_assert(OOB_MAX_L <= kOverMBelow && OOB_MAX_GPUS <= 64, "over_M divides numbers of levels by GPUs per node");
+    for (int M = 1; M <= OOB_MAX_GPUS; ++M)
+        for (int k = 0; k < kOverMBelow; ++k)
+            if (over_M(k, inverse_of(M)) != k / M) return 13;
     for (int M = 1; M <= OOB_MAX_GPUS; ++M) // the closed form of the levels' tables
         for (int n_max = 1; n_max <= imin(L, OOB_MAX_NODES); n_max += 1 + n_max / 3) {
             int tab = 0;
