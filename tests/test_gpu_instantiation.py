@@ -233,7 +233,7 @@ def test_count_table_by_node_counts(P, f):
 @pytest.mark.parametrize("N_hi,f,least", [(40, 2, 24), (126, 2, 41), (127, 2, 35), (63, 6, 22), (100, 0, 36)])
 def test_count_table_at_the_line_between_planes_and_scans(P, N_hi, f, least, listed):
     """`least` sizes from 5 on are counted by node counts (steps of five), fewer by sizes: 10 and N_hi / 5 sizes, 16 where a plane has
-    fewer than 512 counts.  The lengths and the whole table against the recurrence, on both sides of the line."""
+    fewer than 512 counts; lists may be counted by sizes beyond that.  The lengths and the whole table against the recurrence, on both sides of the line."""
     assert least == (16 if (N_hi + 1) * (f + 2) < 512 else 10) + N_hi // 5
     for p in (least - 1, least, least + 1):
         R = (p + 8) // 8 * 8
