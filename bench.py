@@ -297,12 +297,12 @@ def bench_distribution(P, inp, res, Q=512, reps=3, oracle_sample=40):
                         f"{Q} microbatches; time per microbatch = T1 of the template",
             "value": total / dt, "unit": "plans/s", "ms": dt * 1e3, "choose_us": t_choose * 1e6,
             "best_plan_for_all_nodes": X[int(best[-1])].nonzero()[0].tolist() if best[-1] >= 0 else None,
-            # bound by instruction issue: 3 444 vector instructions per 64 plans (SQ_INSTS_VALU of both launches
+            # bound by instruction issue: 3 613 vector instructions per 64 plans (SQ_INSTS_VALU of both launches
             # of profiles/k_dist_solve_config4.md, a constant of that profile, not measured here), each 4 cycles
             # on one of 1024 SIMDs; the algorithmic HBM bytes are kept as a secondary figure
-            "roofline": {"bound": "alu", "achieved": total / 64 * 3444 * 64 / dt / 1e12, "peak": PEAK_LANE_OPS / 1e12,
-                         "unit": "T lane-instr/s (32/64-bit integer and fp64)", "frac": total / 64 * 3444 * 64 / dt / PEAK_LANE_OPS,
-                         "traffic": None, "kernel": "k_dist_first, k_dist_rest", "valu_insts_per_wave_from_profile": 3444,
+            "roofline": {"bound": "alu", "achieved": total / 64 * 3613 * 64 / dt / 1e12, "peak": PEAK_LANE_OPS / 1e12,
+                         "unit": "T lane-instr/s (32/64-bit integer and fp64)", "frac": total / 64 * 3613 * 64 / dt / PEAK_LANE_OPS,
+                         "traffic": None, "kernel": "k_dist_first, k_dist_rest", "valu_insts_per_wave_from_profile": 3613,
                          "hbm_algorithmic": {"bytes_per_plan": 6 * p + 28, "GB_per_s": nbytes / dt / 1e9,
                                              "frac_of_hbm_peak": nbytes / dt / 8e12}},
             "cpu_baseline": {"value": cpu, "unit": "plans/s", "cores": 1, "kind": "oracle",

@@ -23,7 +23,7 @@
 //   k_exact_filter        keeps those whose bound does not exceed what was found;
 //   k_exact_eval<kRest>   evaluates these exactly, looking at the bounds again as the minima fall.
 // Small jobs (kDirectMax) skip the bounds and evaluate every stage but those too dear by their time alone.
-// Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.85 ms (1 400 of 17 524 slowest stages
+// Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.68-0.74 ms (1 400 of 17 524 slowest stages
 // evaluated); 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 69 us; 48 layers, 8 GPUs per node, N_b = 20 with
 // the limit binding 38.0 -> 2.7-4.0 ms by the instance (the evaluation of every stage in tables of the workspace before).
 //
@@ -355,7 +355,7 @@ __device__ __forceinline__ double row_below(double x) {
 // The profile in LDS: PT[l ms + d-1] prefix sums, PX = PT plus the boundary term of a stage ending at layer l,
 // X the boundary terms, flo as in Args.  At eight GPUs per node a row is nine doubles where there is room (ms = M | 1, PAD): neighbouring
 // lanes read neighbouring rows, which fall on the same few banks otherwise (47-63 % of the LDS cycles were conflicts): 98 layers 780 ->
-// 662 us, 61 layers, 18 nodes 672 -> 660, 48 layers with the limit binding (in the bounds only) 3.15 -> 3.05 ms.  SUM: PX is not kept but added up where it is read (integers below 2^52: the same
+// 662 us, 61 layers, 18 nodes 672 -> 660 us; 48 layers with the limit binding, in the bounds only: within what runs differ by.  SUM: PX is not kept but added up where it is read (integers below 2^52: the same
 // value), for shapes whose tables leave it no room.
 struct Prof { double *PT, *PX, *X; unsigned char *flo; };
 template <bool SUM> __device__ __forceinline__ double stage_end(const Prof &s, int l, int i) { // i = l ms + d-1
@@ -666,8 +666,8 @@ __global__ void __launch_bounds__(kFilterThreads) k_exact_filter(Args a) {
 
 // ---------------------------------------------------------------------------------------------
 // Exact evaluation.  Bound by chains of dependent LDS reads on the rows of the one-node tables; at 8 GPUs per node
-// 38 registers of k_exact_eval<false, 8> are spilled: some 30 MB of scratch
-// written per launch.  140-160 us for the first picks and 330-430 us for the rest at 98 layers x 8 GPUs (a version without a band,
+// 38 registers of k_exact_eval<false, 8> are spilled: 35 MB of scratch
+// written per launch.  140-160 us for the first picks and 280-420 us for the rest at 98 layers x 8 GPUs (a version without a band,
 // evaluating everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table
 // entry: 1, or S_max + 1 (STAGED).
 // ---------------------------------------------------------------------------------------------

@@ -32,6 +32,7 @@ OOB_HD inline int imax(int a, int b) { return a > b ? a : b; }
 
 // Eight GPUs per node have kernels with the rows of the profile padded to an odd number of doubles: rows of 64 bytes fall on the same
 // few banks (63 % of the LDS cycles of the bounds were conflicts, 1 % with rows of nine; 98 layers 780 -> 662 us).
+// Other numbers of GPUs have no such kernels: not measured.
 OOB_HD inline bool can_pad(int M) { return M == 8; }
 // The profile in LDS (see Prof) with rows of ms doubles, in doubles.
 OOB_HD inline size_t prof_doubles(int L, int M, int ms, bool sums = false) {
