@@ -27,9 +27,9 @@
 // evaluated); 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 69 us; 48 layers, 8 GPUs per node, N_b = 20 with
 // the limit binding 38.0 -> 2.7-4.0 ms by the instance (the evaluation of every stage in tables of the workspace before).
 //
-// k_exact_eval: one workgroup per slowest stage, everything in LDS, times as exact integers in doubles.
+// k_exact_eval: one workgroup per slowest stage, everything in LDS and registers, times as exact integers in doubles.
 // Phase 1, per wave, no workgroup barrier: the one-node table of start layer q, G_q[r][g] = least cost
-// of covering r layers from q on with stages on exactly g GPUs of one node; it yields W[r][q] =
+// of covering r layers from q on with stages on exactly g GPUs of one node (in registers, or row after row in LDS); it yields W[r][q] =
 // G_q[r][M] (a whole node) and GU[r][g] = G_{u-r}[r][g].  Phase 2: the node-level recurrence
 // NP_{a+1}[p] = min_r NP_a[p-r] + W[r][p-r], one barrier per node count.  The same for the layers after v,
 // mirrored, side by side with it; then every (template, a, g) combination.  Stages slower than tau are
@@ -377,6 +377,16 @@ template <bool SUM> __device__ __forceinline__ Prof load_prof(const Args &a, dou
     for (int l = threadIdx.x; l < W; l += blockDim.x) p.X[l] = l > 0 && l < a.L ? (double)bnd[l - 1] : 0.0;
     return p;
 }
+// Whether the ends of stages that are not the model's last ascend with the layer on every number of GPUs, as far as this thread
+// looks (the threads of the workgroup share the layers out).
+template <bool PAD> __device__ __forceinline__ bool ends_ascend(const Prof &s, int L, int M) {
+    bool up = true;
+    for (int i = threadIdx.x; i < (L - 2) * M; i += blockDim.x) {
+        const int at = (1 + i / M) * (PAD ? M | 1 : M) + i % M;
+        up = up && s.PX[at] <= s.PX[at + (PAD ? M | 1 : M)];
+    }
+    return up;
+}
 // Reach of a stage on dd GPUs into layer p (before the slowest stage: it starts at r .. p-1; p: none) that
 // takes less than tau (STRICT) or at most tau: it only gets slower and heavier as its start goes down.
 template <bool STRICT, bool SUM>
@@ -665,10 +675,10 @@ __global__ void __launch_bounds__(kFilterThreads) k_exact_filter(Args a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact evaluation.  Bound by chains of dependent LDS reads on the rows of the one-node tables; at 8 GPUs per node
-// 38 registers of k_exact_eval<false, 8> are spilled: 35 MB of scratch
-// written per launch.  140-160 us for the first picks and 280-420 us for the rest at 98 layers x 8 GPUs (a version without a band,
-// evaluating everything: 20.3 ms, 1.16 us per slowest stage against 0.44 us).  J = number of stage counts kept per table
+// Exact evaluation.  Bound by the vector instructions of the one-node tables (60 % of an entry's 69 000 cycles at 98 layers x 8
+// GPUs, two workgroups a compute unit) and the chain of nodes (25 %).  77 us for the first picks and 135-150 us for the rest there
+// (140-160 and 280-420 with the tables row after row in LDS; a version without a band,
+// evaluating everything: 20.3 ms, 1.16 us per slowest stage).  J = number of stage counts kept per table
 // entry: 1, or S_max + 1 (STAGED).
 // ---------------------------------------------------------------------------------------------
 struct Eval {
@@ -772,6 +782,84 @@ __device__ void one_node_tables(const Args &a, const Eval &e, int len, int band,
     }
 }
 
+// The value of the lane below (lane 0: its own), over the whole wave.
+__device__ __forceinline__ double lane_below(double x) {
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xF, 0xF, false));
+}
+// The same tables in registers, for 1, 2, 4 or 8 GPUs per node and bands of up to 64 layers: a lane holds row r of a start (all g, with
+// stage counts all j <= g), 64 / band starts side by side.  A cover on g' GPUs whose first layers a stage on d GPUs
+// takes makes one on g' + d: g' goes up, and every row of it is final before it is used, so what depends on what is M
+// steps long and not `band` rows.  The time of a stage is a difference of two prefix sums: the lane of the shorter
+// cover adds its share, the wave hands the sum up a lane per layer of the stage, and the lane that wants it takes the
+// minimum over as many as the stage may have layers (never past the first row of its own start).
+// No LDS but the results: with stage counts the tables in LDS left room for two or three of sixteen waves.  Cycles of an entry in
+// this phase, row after row in LDS and now: 98 layers x 8 GPUs 113 000 and 42 000 (call 711 -> 463 us), 48 layers with stage
+// counts 730 000 and 141 000 (3.35 -> 1.10 ms), 26 layers x 4 GPUs 19 000 and 7 000.
+template <bool MIRROR, bool STAGED, int MT, bool PAD>
+__device__ __forceinline__ void node_tables(const Args &a, const Eval &e, int len, int band, double tau, double wt, double add, double *Wm, double *GU, int first, int slots) {
+    constexpr int M = MT, J = STAGED ? M : 1;
+    const int L = a.L, lane = threadIdx.x & 63, ms = PAD ? M | 1 : M;
+    const int slot = lane / band, r = lane - slot * band + 1, idx = first + slot;
+    const bool on = slot < slots && idx + r <= len;
+    const int q = MIRROR ? L - idx : idx, p = on ? (MIRROR ? q - r : q + r) : 0;
+    const double *here = (MIRROR ? e.pr.PT : e.pr.PX) + p * ms, *from = (MIRROR ? e.pr.PX : e.pr.PT) + p * ms; // as the end that a stage adds, as the one it starts from
+    double T[M + 1][J + 1]; // [g][j], j = 1 without stage counts
+    int lim[M];             // layers of the longest stage on d + 1 GPUs that leaves a layer to the others
+#pragma unroll
+    for (int d = 0; d < M; ++d) {
+        const int rc = e.reach[p * M + d], n = MIRROR ? rc - p : p - rc;
+        const double tw = MIRROR ? e.pr.PX[(on ? q : 0) * ms + d] - here[d] : here[d] - e.pr.PT[(on ? q : 0) * ms + d];
+#pragma unroll
+        for (int j = 1; j <= J; ++j) T[d + 1][j] = kNone;
+        if (on & (n >= r) & (!MIRROR | (tw <= tau))) T[d + 1][1] = fma(wt, tw, add); // one stage on all of them
+        lim[d] = on ? imin(n, r - 1) : 0;
+    }
+    if (MIRROR) // (the ends of the stages ascend: where the longest is not too slow with its boundary term, no shorter one is)
+        for (bool more = true; __any(more);) {
+            more = false;
+#pragma unroll
+            for (int d = 0; d < M; ++d) {
+                const bool slow = lim[d] > 0 && e.pr.PX[(p + lim[d]) * ms + d] - here[d] > tau;
+                lim[d] -= slow;
+                more = more || slow;
+            }
+        }
+#pragma unroll
+    for (int g = 1; g < M; ++g)
+#pragma unroll
+        for (int d = 0; d + 1 + g <= M; ++d) {
+            const double share = MIRROR ? wt * from[d] : -from[d], rest = (MIRROR ? -wt * here[d] : here[d]) + add;
+            double h[J + 1], acc[J + 1];
+#pragma unroll
+            for (int j = 1; j <= J; ++j) if (j <= g) { h[j] = T[g][j] + share; acc[j] = kNone; }
+            for (int k = 0; __any(k < lim[d]); ++k) {
+#pragma unroll
+                for (int j = 1; j <= J; ++j) if (j <= g) h[j] = lane_below(h[j]);
+                if (k < lim[d])
+#pragma unroll
+                    for (int j = 1; j <= J; ++j) if (j <= g) acc[j] = fmin(acc[j], h[j]);
+            }
+#pragma unroll
+            for (int j = 1; j <= J; ++j)
+                if (j <= g) {
+                    double &t = T[g + d + 1][STAGED ? imin(j + 1, J) : 1]; // (j <= g < M)
+                    t = fmin(t, acc[j] + rest);
+                }
+        }
+    if (!on) return;
+#pragma unroll
+    for (int j = 1; j <= J; ++j) Wm[(size_t)band_index(r, idx, len) * J + j - 1] = T[M][j];
+    if (idx + r == len)
+#pragma unroll
+        for (int g = 1; g <= M; ++g)
+#pragma unroll
+            for (int j = 1; j <= J; ++j) {
+                if (STAGED) { if (j <= g) GU[(r - 1) * staged_row(M) + staged_col(g, j)] = T[g][j]; }
+                else if (g < M) GU[(r - 1) * M + g] = T[g][1];
+            }
+}
+
 // c -> c + 1 whole nodes: nxt[p] = min over r of cur[p - r] + W[r][p - r] for this side, by nth threads (whole waves).
 template <bool STAGED>
 __device__ void node_step(const Args &a, int len, int band, int c, const double *Wm, const double *cur, double *nxt, int th,
@@ -833,12 +921,20 @@ __device__ void node_out(const Args &a, int len, int band, int c, const double *
 // what the last node's partial covers need.  No LDS read and no barrier on the chain of up to n_max steps.
 template <int B, bool TWO>
 __device__ __forceinline__ void node_chain(int len, int band, int cend, const double *Wm, double *HIST) {
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane)); // (or the places of W are formed once for all variants and kept in scratch memory: 5 000 cycles)
     double w0[B], w1[TWO ? B : 1];
+    int at = lane - 1; // of W[r][lane - r]
 #pragma unroll
     for (int r = 1; r <= B; ++r) {
-        w0[r - 1] = r <= band && lane >= r && lane <= len ? Wm[band_index(r, lane - r, len)] : kNone;
-        if (TWO) w1[r - 1] = r <= band && lane + 64 <= len ? Wm[band_index(r, lane + 64 - r, len)] : kNone;
+        const bool in0 = (r <= band) & (lane >= r) & (lane <= len), in1 = (r <= band) & (lane + 64 <= len);
+        w0[r - 1] = Wm[in0 ? at : 0];
+        if (!in0) w0[r - 1] = kNone;
+        if (TWO) {
+            w1[r - 1] = Wm[in1 ? at + 64 : 0];
+            if (!in1) w1[r - 1] = kNone;
+        }
+        at += len - r;
     }
     double c0 = lane == 0 ? 0.0 : kNone, c1 = kNone;
     for (int c = 0; c < cend; ++c) {
@@ -847,16 +943,19 @@ __device__ __forceinline__ void node_chain(int len, int band, int cend, const do
         double n0 = kNone, n1 = kNone, s0 = c0, s1 = c1;
 #pragma unroll
         for (int r = 1; r <= B; ++r) {
-            if (TWO) {
-                const int blo = __builtin_amdgcn_readlane(__double2loint(s0), 63), bhi = __builtin_amdgcn_readlane(__double2hiint(s0), 63);
-                const int lo = __builtin_amdgcn_update_dpp(blo, __double2loint(s1), 0x138, 0xF, 0xF, false);
-                const int hi = __builtin_amdgcn_update_dpp(bhi, __double2hiint(s1), 0x138, 0xF, 0xF, false);
+            if (TWO) { // lane 0 of the upper half takes the lower half's last
+                int lo = __builtin_amdgcn_update_dpp(0, __double2loint(s0), 0x13C, 0xF, 0xF, false);
+                int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(s0), 0x13C, 0xF, 0xF, false);
+                s0 = __hiloint2double(lane == 0 ? 0x7FF00000 : hi, lane == 0 ? 0 : lo);
+                lo = __builtin_amdgcn_update_dpp(lo, __double2loint(s1), 0x138, 0xF, 0xF, false);
+                hi = __builtin_amdgcn_update_dpp(hi, __double2hiint(s1), 0x138, 0xF, 0xF, false);
                 s1 = __hiloint2double(hi, lo);
                 n1 = fmin(n1, s1 + w1[r - 1]);
+            } else {
+                const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(s0), 0x138, 0xF, 0xF, false);
+                const int hi = __builtin_amdgcn_update_dpp(0x7FF00000, __double2hiint(s0), 0x138, 0xF, 0xF, false);
+                s0 = __hiloint2double(hi, lo);
             }
-            const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(s0), 0x138, 0xF, 0xF, false);
-            const int hi = __builtin_amdgcn_update_dpp(0x7FF00000, __double2hiint(s0), 0x138, 0xF, 0xF, false);
-            s0 = __hiloint2double(hi, lo);
             n0 = fmin(n0, s0 + w0[r - 1]);
         }
         c0 = n0;
@@ -868,9 +967,11 @@ __device__ __forceinline__ void node_chain_any(int len, int band, int cend, cons
     if (len < 64) {
         if (band <= 4) node_chain<4, false>(len, band, cend, Wm, HIST);
         else if (band <= 8) node_chain<8, false>(len, band, cend, Wm, HIST);
+        else if (band <= 12) node_chain<12, false>(len, band, cend, Wm, HIST);
         else node_chain<kChainBand, false>(len, band, cend, Wm, HIST);
     } else {
         if (band <= 8) node_chain<8, true>(len, band, cend, Wm, HIST);
+        else if (band <= 12) node_chain<12, true>(len, band, cend, Wm, HIST);
         else node_chain<kChainBand, true>(len, band, cend, Wm, HIST);
     }
 }
@@ -990,9 +1091,17 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     const int cendP = imin(nhi, lenP + 1), cendS = imin(nhi, lenS + 1); // a node covers at least one layer
     const int nwp = (nw + 1) >> 1, mir = wave >= nwp; // half of the waves per side
     const int th = mir ? (int)threadIdx.x - nwp * 64 : (int)threadIdx.x, nth = (mir ? nw - nwp : nwp) * 64;
-    // ---- few nodes, each of many layers: tables over (layers covered, GPUs used) are smaller work than a table per
-    // start layer (nodes against layers per node), and the covers next to the slowest stage are their last rows
-    {
+    // ---- layout of the pool: the two GU, the two W, then one-node tables
+    const int mult = STAGED ? M : 1, row_n = STAGED ? staged_row(M) : M + 1;
+    const size_t gu = STAGED ? row_n : M;
+    e.GU = e.pool;
+    double *WP = e.GU + (bandP + bandS) * gu, *WS = WP + band_size(bandP, lenP) * mult, *G = WS + band_size(bandS, lenS) * mult;
+    const unsigned used = (unsigned)(G - e.pool);
+    const bool in_regs = MT && e.ints[2] && imax(bandP, bandS) <= 64 && used <= e.pool_n; // node_tables()
+    const unsigned table = in_regs ? 0u : (unsigned)(imax(bandP, bandS) + 1) * row_n;
+    // ---- few nodes, each of many layers: where node_tables() does not serve, tables over (layers covered, GPUs used) are smaller work than a table per
+    // start layer in LDS (nodes against layers per node), and the covers next to the slowest stage are their last rows
+    if (!in_regs) {
         const int nd = imax(cendP, cendS) * M, jd = STAGED ? imin(J, nd + 1) : 1;
         const unsigned need = ((unsigned)lenP + 1 + lenS + 1) * nd * jd; // below 2^29
         if (nhi * 4 <= imax(bandP, bandS) && need <= e.pool_n) {
@@ -1019,16 +1128,22 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
             return true;
         }
     }
-    // ---- layout of the pool: the two GU, the two W, then one-node tables
-    const int mult = STAGED ? M : 1, row_n = STAGED ? staged_row(M) : M + 1;
-    const size_t gu = STAGED ? row_n : M;
-    e.GU = e.pool;
-    double *WP = e.GU + (bandP + bandS) * gu, *WS = WP + band_size(bandP, lenP) * mult, *G = WS + band_size(bandS, lenS) * mult;
-    const unsigned used = (unsigned)(G - e.pool), table = (unsigned)(imax(bandP, bandS) + 1) * row_n;
     if (used + table > e.pool_n) return false; // (without stage counts they fit: eval_pool())
-    const int fit = (int)((e.pool_n - used) / table); // one-node tables side by side
     // ---- phase 1
-    {
+    if constexpr (MT != 0) if (in_regs) {
+        const int sP = 64 / imax(bandP, 1), sS = 64 / imax(bandS, 1); // start layers a wave takes at a time
+        // (with a single node in all there is only the start at the far end)
+        const int nP = nhi == 1 ? lenP > 0 : (lenP + sP - 1) / sP, nS = nhi == 1 ? lenS > 0 : (lenS + sS - 1) / sS, both = 2 * imin(nP, nS);
+        for (int item = wave; item < nP + nS; item += nw) { // the two sides in turn
+            int side, i;
+            if (item < both) { side = item & 1; i = item >> 1; }
+            else { side = nS > nP; i = item - (both >> 1); }
+            if (!side) node_tables<false, STAGED, MT, PAD>(a, e, lenP, bandP, tau, 1.0, ptau * tau, WP, e.GU, i * sP, sP);
+            else       node_tables<true, STAGED, MT, PAD>(a, e, lenS, bandS, tau, 2.0, stau * tau, WS, e.GU + bandP * gu, i * sS, sS);
+        }
+    }
+    if (!in_regs) {
+        const int fit = (int)((e.pool_n - used) / table); // one-node tables side by side
         int gbits = 0;
         while (1 << gbits < M) ++gbits;
         int lgxs = STAGED ? gbits : 0, slots = 64 >> (gbits + lgxs), waves = nw;
@@ -1110,6 +1225,11 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     e.ints = s_ints;
     for (int i = tid; i < a.live; i += blockDim.x) s_best[i] = kNoneBits;
     const unsigned total = mode == kRest ? a.head->alive : a.head->ncand;
+    if constexpr (MT != 0) {
+        if (tid == 0) s_ints[2] = 1; // ends_ascend(), for node_tables()
+        wg_sync();
+        if (!ends_ascend<PAD>(e.pr, L, M)) s_ints[2] = 0;
+    }
     for (int turn = 0;; ++turn) {
         wg_sync(); // the previous entry is done with LDS (and s_next has been read)
         unsigned c;

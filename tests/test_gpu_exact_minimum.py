@@ -322,6 +322,44 @@ def test_shapes_beyond_doubles_take_times_beyond_them(P, sizes, shape):
             assert st == P.OOB_OK and got == want, (shape, add, staged)
 
 
+# (layers, GPUs per node, templates, N_b): a node covers up to 64 layers, one more, few; starts that fill a wave and do not
+@pytest.mark.parametrize("ends", ["ascending", "mixed"])
+@pytest.mark.parametrize("shape", [(64, 1, 1, 4, 64), (65, 1, 1, 3, 0), (64, 2, 1, 2, 0), (66, 2, 1, 3, 70), (67, 4, 1, 2, 70), (65, 8, 1, 1, 70),
+                                   (66, 8, 1, 3, 0), (33, 4, 1, 5, 33), (17, 8, 2, 4, 20), (31, 8, 4, 12, 0)])
+def test_tables_of_a_node_in_registers_and_in_lds(P, shape, ends):
+    """Ends of stages that ascend with the layer (tables in registers where a node covers at most 64) and boundary terms
+    that outweigh layers."""
+    import dataclasses
+
+    import numpy as np
+
+    L, M, n_min, n_max, nb = shape
+    for var in ("plain", "tight", "forbid"):
+        inp = inputs.random_small(41, L, M, n_min, n_max, nb, f=1, t_lo=60, t_hi=99, tight_mem=(var == "tight"), forbid_some_d=(var == "forbid"))
+        if ends == "mixed":
+            inp = dataclasses.replace(inp, boundary_ns=np.random.default_rng(L).integers(0, 400, L))
+        print("case", shape, ends, var, flush=True)
+        st, got = P.ExactMinimum(inp).run()
+        assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, ends, var)
+
+
+@pytest.mark.parametrize("ends", ["ascending", "mixed"])
+@pytest.mark.parametrize("shape", [(20, 8, 1, 4, 9), (33, 4, 1, 4, 12), (40, 2, 1, 6, 11), (30, 1, 1, 24, 10), (66, 2, 1, 2, 3)])
+def test_tables_of_a_node_with_stage_counts(P, shape, ends):
+    import dataclasses
+
+    import numpy as np
+
+    L, M, n_min, n_max, nb = shape
+    for var in ("plain", "tight"):
+        inp = inputs.random_small(43, L, M, n_min, n_max, nb, f=1, t_lo=60, t_hi=99, tight_mem=(var == "tight"))
+        if ends == "mixed":
+            inp = dataclasses.replace(inp, boundary_ns=np.random.default_rng(L).integers(0, 400, L))
+        print("case", shape, ends, var, flush=True)
+        st, got = P.ExactMinimum(inp, staged=True).run()
+        assert st == P.OOB_OK and got == E.exact_minimum_staged(inp), (shape, ends, var)
+
+
 def test_leftovers_with_stage_counts_are_listed_once(P, sizes):
     """Slowest stages whose tables exceed LDS are left to the general path: each at most once, whatever the
     number of templates that pick it first."""
