@@ -419,9 +419,13 @@ __device__ __forceinline__ int reach_on(const Prof &s, int L, int M, int ms, int
 // P[u] / S[v] = least sum over the stages of [0, u) / [v, L) of (weighted time + lambda GPUs + mu), stage times
 // at most hi, tau's share in a weight taken from the end of the bucket that makes it smaller: exactly n M
 // GPUs and at most S_max stages are used, whatever the prices.  The bound is the largest over the
-// multipliers.  Row after row of the two paths; a wave takes two lambdas, thirty-two lanes each share out the
-// starts of the last stage, eight GPU counts side by side.  Bound by the chain of rows (LDS read, reduction over the
-// lanes, LDS write per row) at one workgroup per bucket: 132 us at 98 layers x 8 GPUs, 512 buckets (212 with rows of eight doubles, Prof).
+// multipliers.  Row after row of the two paths.  With prices of stages, and where stages of more than kRing layers are
+// fast enough: a wave takes two or four lambdas, thirty-two or sixteen lanes each share out the starts of the last stage, and the
+// cost of a stage, which does not hang on mu, serves every mu of the wave; what hangs on the row alone is read once for the wave.  Else
+// path_rows().  Bound by the chain of rows (LDS reads, the GPU counts one after the other, reduction over the lanes) at one
+// workgroup per bucket: 120 us at 98 layers x 8 GPUs, 512 buckets, and 79 us at 48 layers with 64 pairs of multipliers (348 with
+// a path per pair, the prices formed again for every entry and template at the end).  The ends of stages count with
+// their boundary term (less so before: 2 400 instead of 2 000 evaluations at 98 layers).
 // ---------------------------------------------------------------------------------------------
 __device__ const double kLambdaGiven[kLambdas] = {0, 0.04, 0.1, 0.2, 0.4, 0.8, 1.6, 3.5}; // more nodes pay (C falls with n) ...
 __device__ const double kLambda4S[kLambdas] = {0, -0.06, -0.14, -0.25, -0.43, -0.7, -1.3, -3.5}; // ... or cost
@@ -476,15 +480,57 @@ __device__ __forceinline__ double bound_of(const Args &a, const float *lb, doubl
     for (int k = 0; k < a.nk; ++k) x = fmax(x, (double)lb[k] - lo * spent(a, k, n));
     return x;
 }
-// Six waves per SIMD asked for where M is known: 78 registers, which is also the faster schedule of the rows (with 274 buckets and rows of
-// eight doubles 170 us at 98 layers x 8 GPUs, 207 with the 94 that the compiler takes by itself; two workgroups per compute unit either way).
-template <int MT, bool PAD>
-__global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args a, int mus) {
-    constexpr int CW = MT ? MT : 8;
+// Five waves per SIMD asked for, two workgroups per compute unit; with prices of stages three: a workgroup has most of the LDS there.
+// The rows of one side's path without prices of stages where no stage has more than K layers, one wave: lane = (lambda, GPU
+// count).  A lane keeps, per layer x so far, the path up to x plus what x adds to the time of a stage on its GPUs, and takes
+// the least over as many x as such a stage may have layers.  The last K of them are in LDS, no lane reads another's, and all
+// but the newest two are read a row ahead.  One wave does for a side what four do with the starts shared out: 64 000 cycles
+// instead of 90 000-130 000 for stages of up to 8 layers, 95 000 instead of 140 000 up to 16 (98 layers x 8 GPUs).
+constexpr int kRing = 16;
+template <int MT, bool PAD, bool SIDE, int K>
+__device__ __forceinline__ void path_rows(const Prof &s, int L, const unsigned char *reach, double price, double extra, double *P, double *ring) {
+    constexpr int M = MT, ms = PAD ? M | 1 : M;
+    const int lane = threadIdx.x & 63, d = lane & (M - 1);
+    const double *near = (SIDE ? s.PT : s.PX) + d, *far = (SIDE ? s.PX : s.PT) + d;
+    const double sign = SIDE ? 2.0 : -1.0;
+    double *const mine = ring + lane;
+    double last = 0.0, g1 = kNone, old[K]; // the path up to the layer before; what the one before that adds, and those before it (k = 2 ..)
+#pragma unroll
+    for (int k = 2; k < K; ++k) old[k] = kNone;
+    auto of = [=](int row) { return SIDE ? L - row : row; };
+    int rc = reach[of(1) * M + d];
+    double here = near[of(1) * ms], there = far[of(0) * ms];
+    for (int row = 1; row <= L; ++row) {
+        // stages [x, p) before, [p, x) after the slowest stage
+        const int p = of(row), lim = SIDE ? rc - p : p - rc, pn = of(imin(row + 1, L));
+        double acc = 1 < lim ? g1 : kNone;
+#pragma unroll
+        for (int k = 2; k < K; ++k) if (k < lim) acc = fmin(acc, old[k]);
+        const double g0 = fma(sign, there, last), h = here;
+        rc = reach[pn * M + d];
+        here = near[pn * ms];
+        there = far[p * ms];
+        mine[(row & (kRing - 1)) * 64] = g1;
+#pragma unroll
+        for (int k = 2; k < K; ++k) old[k] = mine[((row + 2 - k) & (kRing - 1)) * 64]; // of the next row (before the first: not used)
+        if (lim > 0) acc = fmin(acc, g0);
+        g1 = g0;
+        acc = fma(-sign, h, acc) + price;
+        if (M >= 2) acc = fmin(acc, dpp_f64<0xB1>(acc));
+        if (M >= 4) acc = fmin(acc, dpp_f64<0x4E>(acc));
+        if (M >= 8) acc = fmin(acc, dpp_f64<0x141>(acc));
+        last = acc + extra;
+        if (d == 0 && lane < kLambdas * M) P[p] = last;
+    }
+    wave_sync();
+}
+template <int MT, bool PAD, bool MUS>
+__global__ void __launch_bounds__(kBoundThreads, MUS ? 3 : 5) k_exact_bounds(Args a, int mus) {
+    constexpr int CW = MT ? MT : 8, KL = MUS ? 16 : 32, LL = 64 / KL, MH = MUS ? kMus / 2 : 1; // lanes of a lambda, lambdas and mus of a wave
     HIP_DYNAMIC_SHARED(double, s_dyn)
     __shared__ unsigned long long s_lo, s_hi;
     __shared__ double s_lam[kLambdas], s_mu[kMus];
-    __shared__ int s_fewest;
+    __shared__ int s_fewest, s_up, s_most[2];
     if (*a.status != OOB_OK || !a.head->narrow) return;
     const unsigned b = blockIdx.x, K = a.head->bucket;
     if (b >= a.head->nbuckets) return;
@@ -496,82 +542,127 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
     unsigned char *rb = (unsigned char *)(s_dyn + prof_doubles(L, M, ms)), *rf = rb + ((size_t)W * M + 7) / 8 * 8;
     double *PS = (double *)(rf + ((size_t)W * M + 7) / 8 * 8); // [mu][lambda][side][L+1]
     float *s_lb = (float *)(PS + (size_t)mus * kLambdas * 2 * W); // [kBucket][kMaxCount]
+    double *s_ring = (double *)s_lb;                              // [2][kRing][64] for path_rows(), before that
     unsigned char *s_far = (unsigned char *)(s_lb + kBucket * kMaxCount); // [256] for fewest_nodes()
-    if (threadIdx.x == 0) { s_lo = kNoneBits; s_hi = 0; s_fewest = 0; }
+    static_assert(2 * kRing * 64 * sizeof(double) <= kBucket * kMaxCount * sizeof(float), "");
+    if (threadIdx.x == 0) { s_lo = kNoneBits; s_hi = 0; s_fewest = 0; s_up = 1; s_most[0] = s_most[1] = 0; }
     wg_sync();
+    if (!ends_ascend<PAD>(s, L, M)) s_up = 0;
     for (unsigned c = c0 + threadIdx.x; c < c1; c += blockDim.x) {
         atomicMin(&s_lo, (unsigned long long)__double_as_longlong(a.ctau[c]));
         atomicMax(&s_hi, (unsigned long long)__double_as_longlong(a.ctau[c]));
     }
     wg_sync();
     const double lo = __longlong_as_double((long long)s_lo), hi = __longlong_as_double((long long)s_hi);
+    int mostP = 0, mostS = 0; // layers of the longest stage
     for (int i = threadIdx.x; i < W * M; i += blockDim.x) {
         const int p = i / M, dd = i - p * M + 1;
-        rb[i] = (unsigned char)reach_back<false, false>(s, M, ms, p, dd, hi);
-        rf[i] = (unsigned char)reach_on(s, L, M, ms, p, dd, hi);
+        const int back = reach_back<false, false>(s, M, ms, p, dd, hi);
+        rb[i] = (unsigned char)back;
+        int on = reach_on(s, L, M, ms, p, dd, hi);
+        // no end of a stage beyond this is fast enough (where they are, but for the model's end, ascending: else more are let through)
+        if (on < L && s_up) while (on > p && s.PX[on * ms + dd - 1] - s.PT[p * ms + dd - 1] > hi) --on;
+        rf[i] = (unsigned char)on;
+        mostP = imax(mostP, p - back);
+        mostS = imax(mostS, on - p);
     }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) { mostP = imax(mostP, __shfl_xor(mostP, m, 64)); mostS = imax(mostS, __shfl_xor(mostS, m, 64)); }
+    if (lane == 0) { atomicMax(&s_most[0], mostP); atomicMax(&s_most[1], mostS); }
     const bool given = a.Nb > 0;
     if (threadIdx.x < kLambdas) s_lam[threadIdx.x] = (given ? kLambdaGiven[threadIdx.x] : kLambda4S[threadIdx.x]) * lo;
     else if (threadIdx.x - kLambdas < kMus) s_mu[threadIdx.x - kLambdas] = kMuStep[threadIdx.x - kLambdas] * lo;
     wg_sync();
     const double pw = given ? 0.0 : 4.0 * lo, sw = given ? -hi : 3.0 * lo, mid = given ? (double)a.Nb : 4.0;
-    const int sub = lane & 31, nt = nw - 1; // the last wave: fewest nodes
+    const int nt = nw - 1; // the last wave: fewest nodes
     if (wave == nt && M <= kCoverGpus) {
         const int n = fewest_nodes(L, M, rf, s_far);
         if (lane == 0) s_fewest = n;
     }
-    for (int task = wave; wave < nt && task < mus * kLambdas; task += nt) { // two lambdas, one side
-        const int side = task & 1, lg = (task >> 1) % (kLambdas / 2), mi = (task >> 1) / (kLambdas / 2);
-        const int li = lg * 2 + (lane >> 5);
-        const double l = s_lam[li], mu = s_mu[mi];
-        double *P = PS + ((size_t)(mi * kLambdas + li) * 2 + side) * W;
-        for (int x = sub; x <= L; x += 32) P[x] = x == (side ? L : 0) ? 0.0 : kNone;
+    bool done = false; // the rows, one wave a side
+    if constexpr (MT != 0 && !MUS) {
+        const int most = imax(s_most[0], s_most[1]), li = imin(lane / MT, kLambdas - 1);
+        done = most <= kRing;
+        if (done && wave < 2) {
+            double *P = PS + ((size_t)li * 2 + wave) * W;
+            const double price = s_lam[li] * (lane % MT + 1);
+            if (lane % MT == 0 && lane < kLambdas * MT) P[wave ? L : 0] = 0.0;
+            if (wave == 0) {
+                if (most <= 8) path_rows<MT, PAD, false, 8>(s, L, rb, price, pw + s_mu[0], P, s_ring);
+                else path_rows<MT, PAD, false, kRing>(s, L, rb, price, pw + s_mu[0], P, s_ring);
+            } else {
+                if (most <= 8) path_rows<MT, PAD, true, 8>(s, L, rf, price, sw + s_mu[0], P, s_ring + kRing * 64);
+                else path_rows<MT, PAD, true, kRing>(s, L, rf, price, sw + s_mu[0], P, s_ring + kRing * 64);
+            }
+        }
+    }
+    if (!done) {
+    const int kp = lane & (KL - 1), each = MUS ? (mus + 1) / 2 : 1; // mus of a task
+    for (int task = wave; wave < nt && task < 2 * (kLambdas / LL) * (MUS ? 2 : 1); task += nt) { // one side
+        const int side = task & 1, li = (task >> 1) % (kLambdas / LL) * LL + lane / KL, m0 = (task >> 1) / (kLambdas / LL) * each, mn = MUS ? imin(each, mus - m0) : 1;
+        const double l = s_lam[li];
+        double *P = PS + ((size_t)(m0 * kLambdas + li) * 2 + side) * W; // of the task's first mu
+        const int next_mu = kLambdas * 2 * W;
+        for (int i = 0; i < mn; ++i)
+            for (int x = kp; x <= L; x += KL) P[i * next_mu + x] = x == (side ? L : 0) ? 0.0 : kNone;
+        double ld[CW];
+#pragma unroll
+        for (int j = 0; j < CW; ++j) ld[j] = l * (j + 1);
+        double extra[MH];
+#pragma unroll
+        for (int i = 0; i < MH; ++i) extra[i] = (side ? sw : pw) + s_mu[imin(m0 + i, kMus - 1)];
         wave_sync();
         auto rows = [&](auto side_c) {
         constexpr bool side = decltype(side_c)::value;
+        const double *near = side ? s.PT : s.PX, *far = side ? s.PX : s.PT;
+        const unsigned char *reach = side ? rf : rb;
         for (int row = 1; row <= L; ++row) {
-            // stages [x, row) before, [p, x) after the slowest stage; a lane's share of the x, eight GPU counts side by side
+            // stages [x, row) before, [p, x) after the slowest stage; what hangs on p alone is the same in all lanes
             const int p = side ? L - row : row;
-            const double *near = side ? s.PT : s.PX, *far = side ? s.PX : s.PT;
-            const unsigned char *reach = side ? rf : rb;
-            const double per = side ? 2.0 : -1.0;
-            double acc = kNone;
+            double acc[MH];
+#pragma unroll
+            for (int i = 0; i < MH; ++i) acc[i] = kNone;
             for (int d0 = 0; d0 < M; d0 += CW) {
-                double cost[CW], edge[CW];
                 int lim[CW], most = 0; // layers of the longest stage per GPU count
+                double e[CW];
 #pragma unroll
                 for (int j = 0; j < CW; ++j) {
-                    const int dc = MT ? j : imin(d0 + j, M - 1), rc = reach[p * M + dc];
-                    const double e = near[p * ms + dc];
+                    const int dc = MT ? j : imin(d0 + j, M - 1), rc = __builtin_amdgcn_readfirstlane(reach[p * M + dc]);
+                    e[j] = near[p * ms + dc];
                     lim[j] = d0 + j < M ? (side ? rc - p : p - rc) : 0;
                     most = imax(most, lim[j]);
-                    cost[j] = (side ? sw + mu - 2.0 * e : pw + mu + e) + l * (dc + 1);
-                    edge[j] = side ? e + hi : kNone; // a later end than this is too slow by its boundary term
                 }
-                for (int k = sub; __any(k < most); k += 32) { // stage of k + 1 layers
-                    const int x = k < most ? (side ? p + 1 + k : p - 1 - k) : p;
-                    const double px = P[x];
-                    double f[CW], v[CW];
+                const double shift = MT ? 0.0 : l * d0;
+                for (int k0 = 0; k0 < most; k0 += KL) { // stages of k + 1 layers
+                    const int k = k0 + kp, x = side ? imin(p + 1 + k, L) : imax(p - 1 - k, 0);
+                    double f[CW], v = kNone;
 #pragma unroll
                     for (int j = 0; j < CW; ++j) f[j] = far[x * ms + (MT ? j : imin(d0 + j, M - 1))];
+                    double px[MH];
+#pragma unroll
+                    for (int i = 0; i < MH; ++i) if (i < mn) px[i] = P[i * next_mu + x];
 #pragma unroll
                     for (int j = 0; j < CW; ++j) {
-                        const bool ok = (k < lim[j]) & (!side | (f[j] <= edge[j]));
-                        const double c = fma(f[j], per, cost[j]);
-                        v[j] = ok ? c : kNone;
+                        const double c = side ? fma(2.0, f[j] - e[j], ld[j]) : (e[j] - f[j]) + ld[j];
+                        if (k < lim[j]) v = fmin(v, c);
                     }
+                    if (!MT) v += shift;
 #pragma unroll
-                    for (int j = 1; j < CW; ++j) v[0] = fmin(v[0], v[j]);
-                    acc = fmin(acc, px + v[0]);
+                    for (int i = 0; i < MH; ++i) if (i < mn) acc[i] = fmin(acc[i], px[i] + v);
                 }
             }
-            acc = min16(acc);
-            acc = fmin(acc, row_below(acc)); // the upper row of each half wave now holds the minimum of both
-            if (sub == 31) P[p] = acc;
+#pragma unroll
+            for (int i = 0; i < MH; ++i)
+                if (i < mn) {
+                    double x = min16(acc[i]);
+                    if (KL == 32) x = fmin(x, row_below(x)); // (the upper row of either half: the minimum of both)
+                    if (kp == KL - 1) P[i * next_mu + p] = x + extra[i];
+                }
             wave_sync();
         }
         };
         if (side) rows(std::true_type{}); else rows(std::false_type{});
+    }
     }
     wg_sync();
     // Roundings: at most six per stage, so 6 L 2^-53 < 2e-13 of what is added up.  That is prices and stage times (a
@@ -581,6 +672,12 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
     for (int d = 0; d < M; ++d) total = fmax(total, s.PT[L * ms + d]);
     // bounds of the bucket's entries, kBucket at a time; the smallest of every template
     const int count = a.n_max - a.n_min + 1, nk = mus * kLambdas;
+    int lg = 0; // lanes per entry: the templates, rounded up to a power of two
+    while (1 << lg < a.live) ++lg;
+    const int E = 64 >> lg, ni = lane & ((1 << lg) - 1), n = a.n_min + ni;
+    double lam[kLambdas]; // what the prices of n nodes' GPUs take off
+#pragma unroll
+    for (int i = 0; i < kLambdas; ++i) lam[i] = s_lam[i] * (n * M);
     float mine = __builtin_huge_valf();
     unsigned arg = c0;
     for (unsigned m0 = c0; m0 < c1; m0 += kBucket) {
@@ -597,15 +694,30 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
             a.lb[(size_t)m0 * nk + i] = s_lb[i];
         }
         wg_sync();
-        // lanes: templates; the entries shared out among the waves
-        for (int ni = lane; ni < a.live; ni += 64)
-            for (int q = wave; q < m; q += nw) {
-                const double x = bound_of(a, s_lb + q * nk, lo, s_fewest, a.n_min + ni);
-                if (x < (double)mine) { mine = __double2float_rd(x); arg = m0 + q; }
+        // lanes: as many entries as have lanes for their templates; the entries shared out among the waves
+        for (int q0 = wave * E; q0 < m; q0 += nw * E) {
+            const int q = imin(q0 + (lane >> lg), m - 1);
+            double x = -kNone;
+            for (int mi = 0; mi < mus; ++mi) {
+                const float2 *f = (const float2 *)(s_lb + (q * mus + mi) * kLambdas);
+                double y = -kNone;
+#pragma unroll
+                for (int i = 0; i < kLambdas; i += 2) y = fmax(y, fmax((double)f[i / 2].x - lam[i], (double)f[i / 2].y - lam[i + 1]));
+                x = fmax(x, y - s_mu[mi] * a.Smax);
             }
+            if (n < s_fewest || ni >= a.live) x = kNone;
+            if (x < (double)mine) { mine = __double2float_rd(x); arg = m0 + q; }
+        }
         wg_sync();
     }
-    // (count <= kMaxCount = 64: a lane has one template)
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) // the entries side by side: smallest bound, then first entry
+        if (d >= 1 << lg) {
+            const float f = __shfl_xor(mine, d, 64);
+            const unsigned g = (unsigned)__shfl_xor((int)arg, d, 64);
+            if (f < mine || (f == mine && g < arg)) { mine = f; arg = g; }
+        }
+    // (count <= kMaxCount = 64: a lane of the first wave has one template; those beyond the live ones have no bound)
     s_lb[threadIdx.x] = mine;
     ((unsigned *)s_lb)[kBoundThreads + threadIdx.x] = arg;
     wg_sync();
@@ -614,6 +726,7 @@ __global__ void __launch_bounds__(kBoundThreads, MT ? 6 : 5) k_exact_bounds(Args
             const float f = s_lb[w * 64 + threadIdx.x];
             if (f < mine) { mine = f; arg = ((unsigned *)s_lb)[kBoundThreads + w * 64 + threadIdx.x]; }
         }
+        if ((int)threadIdx.x >= a.live) { mine = __builtin_huge_valf(); arg = c0; }
         a.blb[(size_t)b * count + threadIdx.x] = mine;
         a.barg[(size_t)b * count + threadIdx.x] = (unsigned short)(arg - c0);
     }
@@ -1522,15 +1635,19 @@ static int eval_launch(const oob_exact::Args &a, int mode, unsigned grid, int th
     }
 }
 
-template <int MT, bool PAD>
-static int bounds_launch(const oob_exact::Args &a, int mus, size_t lds, hipStream_t st) {
+template <int MT, bool PAD, bool MUS>
+static int bounds_launch_m(const oob_exact::Args &a, int mus, size_t lds, hipStream_t st) {
     using namespace oob_exact;
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_bounds<MT, PAD>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_bounds<MT, PAD, MUS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                (int)lds) != hipSuccess)
         return OOB_EHIP;
     const unsigned nb = (unsigned)((tri(a.L) * a.M + bucket_least(a.nk) - 1) / bucket_least(a.nk));
-    hipLaunchKernelGGL((k_exact_bounds<MT, PAD>), dim3(nb < (unsigned)kMaxBuckets ? nb : (unsigned)kMaxBuckets), dim3(kBoundThreads), lds, st, a, mus);
+    hipLaunchKernelGGL((k_exact_bounds<MT, PAD, MUS>), dim3(nb < (unsigned)kMaxBuckets ? nb : (unsigned)kMaxBuckets), dim3(kBoundThreads), lds, st, a, mus);
     return OOB_OK;
+}
+template <int MT, bool PAD>
+static int bounds_launch(const oob_exact::Args &a, int mus, size_t lds, hipStream_t st) {
+    return mus > 1 ? bounds_launch_m<MT, PAD, true>(a, mus, lds, st) : bounds_launch_m<MT, PAD, false>(a, mus, lds, st);
 }
 
 static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max, int M, int microbatches, int64_t mem_cap,

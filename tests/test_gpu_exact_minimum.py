@@ -441,6 +441,20 @@ def test_lower_bounds_are_below_what_they_bound(P, sizes, never):
     assert (~finite).any() and np.isposinf(lb[~finite]).all()
 
 
+@pytest.mark.parametrize("L,M,n_max", [(92, 1, 60), (92, 1, 4), (65, 2, 20), (66, 2, 2), (48, 4, 10), (47, 4, 1), (34, 8, 6), (34, 8, 1)])
+def test_lower_bounds_whatever_the_longest_stage(P, sizes, L, M, n_max):
+    """The same for every number of GPUs that has kernels of its own: buckets whose longest stage has a few layers (eight, sixteen and more of
+    them are different paths), up to the whole model."""
+    import numpy as np
+
+    inp = inputs.random_small(5, L, M, 1, n_max, L, f=1, t_lo=60, t_hi=99)
+    lb, want, err = bounds_of_a_job(P, sizes, inp)
+    finite = np.isfinite(want)
+    assert finite.any() and (lb <= want + err)[finite].all(), float((lb - want)[finite].max())
+    # and not below by more than what is taken off for the rounding, where no end of a stage is let through that is too slow
+    assert (lb[finite] >= want[finite] * (1 - 1e-5) - 1).mean() > 0.9
+
+
 def test_stages_that_leave_a_layer_uncovered_are_ruled_out(P):
     """One layer that dwarfs the others, more GPUs per node than the count of the fewest nodes takes: what is
     faster than that layer on all its GPUs is the slowest stage of no pipeline and is not evaluated."""
