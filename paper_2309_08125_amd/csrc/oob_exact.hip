@@ -62,6 +62,7 @@ constexpr double kNone = __builtin_huge_val();
 constexpr unsigned long long kNoneBits = 0x7FF0000000000000ull;
 
 constexpr int kPrepThreads = 1024, kBins = 4096;
+constexpr size_t kPrepStatic = kBins * sizeof(int) + 1024; // its static arrays
 constexpr int kBoundThreads = 576;   // eight waves for the paths, one for the fewest nodes
 constexpr int kFirst = 1, kRest = 2, kAll = 0;
 
@@ -131,7 +132,9 @@ __device__ bool last_workgroup(const Args &a) {
 // of all stage times of any pipeline), mult = N_b + 2 (4 S_max + 2 when N_b = 4 S).  status =
 // OOB_EOVERFLOW unless that stays below the limit of the path; OOB_EINVAL for a negative entry.
 // One launch in place of four (62 + 13 + 4 + 4 us at 98 layers x 8 GPUs): prefix sums instead of a table of all stage
-// times, 45 us there and 14 us at 26 x 4, most of it the two walks over the layer pairs with LDS atomics.
+// times, 37 us there and 12 us at 26 x 4, most of it the two walks over the layer pairs with LDS atomics.  (45 and 14 us with the
+// list scattered to memory, the sums as integers that every stage turned into a double, and a lane per single layer at
+// one LDS word for the fastest.)
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ unsigned long long scan_add(unsigned long long x, int lane) {
 #pragma unroll
@@ -160,8 +163,8 @@ __device__ __forceinline__ void triple(int i, int M, int *u, int *v, int *d) {
     *u = p - w * (w - 1) / 2;
 }
 
-__global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
-    HIP_DYNAMIC_SHARED(long long, s_prep) // [(L+1)] bytes, [(L+1) M] times where the fast path needs them, then bytes
+__global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a, int room) {
+    HIP_DYNAMIC_SHARED(long long, s_prep) // [(L+1)] bytes, [(L+1) M] times where the fast path needs them, then bytes, [room] entries of the list
     __shared__ int s_hist[kBins];
     __shared__ int s_bad, s_wave[kPrepThreads / 64];
     __shared__ unsigned long long s_sum[kPrepThreads / 64], s_min;
@@ -169,8 +172,9 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
     const long long *fwd = (const long long *)a.prof.fwd_ns, *bwd = (const long long *)a.prof.bwd_ns;
     const long long *mem = (const long long *)a.prof.mem_bytes, *bnd = (const long long *)a.prof.boundary_ns;
     unsigned long long *s_pm = (unsigned long long *)s_prep;
-    long long *s_pt = s_prep + W;
+    double *s_pt = (double *)(s_prep + W); // (read only where every one is an exact integer)
     unsigned char *s_lf = (unsigned char *)(s_pt + (a.fast ? (size_t)W * M : 0));
+    unsigned *s_list = (unsigned *)(s_lf + ((size_t)W * M + 3) / 4 * 4);
     const int count = a.n_max - a.n_min + 1;
     for (int i = tid; i < count; i += blockDim.x) a.best[i] = kNoneBits; // +inf as a double, huge as an integer
     for (int i = tid; i < kBins; i += blockDim.x) s_hist[i] = 0;
@@ -214,7 +218,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
             const int lf = imax(scan_max(forb ? l + 1 : 0, lane), last);
             if (l < L) {
                 a.PT[(size_t)(l + 1) * M + d] = (long long)x;
-                if (a.fast) s_pt[(size_t)(l + 1) * M + d] = (long long)x;
+                if (a.fast) s_pt[(size_t)(l + 1) * M + d] = (double)(long long)x;
                 s_lf[(size_t)(l + 1) * M + d] = (unsigned char)lf;
             }
             carry = __shfl(x, 63, 64);
@@ -250,12 +254,17 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
         a.flo[i] = (unsigned char)lo;
         s_lf[i] = (unsigned char)lo; // (only this thread reads entry i before the barrier)
     }
-    if (st == OOB_OK && narrow) // the fastest stage is one of a single layer
+    if (st == OOB_OK && narrow) { // the fastest stage is one of a single layer
+        double least = kNone;
         for (int i = tid; i < L * M; i += blockDim.x) {
             const int l = i / M, d = i - l * M;
-            const long long t = s_pt[(size_t)(l + 1) * M + d] - s_pt[(size_t)l * M + d] + (l + 1 < L ? bnd[l] : 0);
-            if (t > 0) atomicMin(&s_min, (unsigned long long)__double_as_longlong((double)t));
+            const double t = s_pt[(l + 1) * M + d] - s_pt[l * M + d] + (l + 1 < L ? (double)bnd[l] : 0.0);
+            if (t > 0) least = fmin(least, t);
         }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) least = fmin(least, __shfl_xor(least, d, 64));
+        if (lane == 0) atomicMin(&s_min, (unsigned long long)__double_as_longlong(least));
+    }
     wg_sync();
     int total = 0;
     if (st == OOB_OK && narrow) { // list the possible slowest stages by time
@@ -263,7 +272,7 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
         const unsigned inv = recip(M);
         for (int pass = 0; pass < 2; ++pass) {
             for (int v = 1 + wave; v <= L; v += nw) { // a wave takes the stages that end at layer v
-                const long long x = v < L ? bnd[v - 1] : 0;
+                const double x = v < L ? (double)bnd[v - 1] : 0.0;
                 for (int i0 = lane; i0 < v * M; i0 += 256) { // four entries of a lane in flight
                     double tau[4];
                     int pos[4], ud[4];
@@ -272,20 +281,33 @@ __global__ void __launch_bounds__(kPrepThreads) k_exact_prep(Args a) {
                         const int i = i0 + 64 * q, ic = i < v * M ? i : 0;
                         const int u = quot(ic, inv), d = ic - u * M;
                         const bool ok = (i < v * M) & (u >= s_lf[v * M + d]);
-                        tau[q] = (double)(s_pt[v * M + d] - s_pt[ic] + x);
+                        tau[q] = s_pt[v * M + d] - s_pt[ic] + x;
                         ud[q] = u | (d + 1) << 16;
-                        pos[q] = ok ? imax(0, imin((int)((unsigned long long)__double_as_longlong(tau[q]) >> 44) - kmin, kBins - 1)) : -1;
+                        pos[q] = ok ? imax(0, imin((__double2hiint(tau[q]) >> 12) - kmin, kBins - 1)) : -1;
                     }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) if (pos[q] >= 0) pos[q] = atomicAdd(&s_hist[pos[q]], 1);
                     if (pass)
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
-                            if (pos[q] >= 0) { a.ctau[pos[q]] = tau[q]; a.cuvd[pos[q]] = (unsigned)(ud[q] | v << 8); }
+                            if (pos[q] >= 0) {
+                                if (total <= room) s_list[pos[q]] = (unsigned)(ud[q] | v << 8);
+                                else { a.ctau[pos[q]] = tau[q]; a.cuvd[pos[q]] = (unsigned)(ud[q] | v << 8); }
+                            }
                 }
             }
             wg_sync();
-            if (pass) break;
+            if (pass) {
+                // lists that fit are put in order in LDS and written out in a row
+                if (total <= room)
+                    for (int i = tid; i < total; i += blockDim.x) {
+                        const unsigned uvd = s_list[i];
+                        const int u = uvd & 255, v = uvd >> 8 & 255, d = (int)(uvd >> 16) - 1;
+                        a.ctau[i] = s_pt[v * M + d] - s_pt[u * M + d] + (v < L ? (double)bnd[v - 1] : 0.0);
+                        a.cuvd[i] = uvd;
+                    }
+                break;
+            }
             // exclusive scan of the bins: kBins / kPrepThreads each
             constexpr int per = kBins / kPrepThreads;
             int h[per], sum = 0;
@@ -1697,11 +1719,14 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
         if (slots > (size_t)kFlatSlots) slots = kFlatSlots;
     } else if (workspace_bytes < y.slots) return OOB_ECAPACITY;
     a.limit = general ? kInf : kDoubleExact;
-    const size_t prep = 8 * ((size_t)(L + 1) + (a.fast ? (size_t)(L + 1) * M : 0)) + (size_t)(L + 1) * M;
+    size_t prep = 8 * ((size_t)(L + 1) + (a.fast ? (size_t)(L + 1) * M : 0)) + ((size_t)(L + 1) * M + 3) / 4 * 4;
+    const size_t left = kLdsLimit - kPrepStatic - prep; // to order the list in
+    const int room = a.fast ? (int)(4 * ntri < left ? ntri : left / 4) : 0;
+    prep += 4 * (size_t)room;
     if (prep > 48 * 1024 && hipFuncSetAttribute((const void *)k_exact_prep, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                 (int)prep) != hipSuccess)
         return OOB_EHIP;
-    hipLaunchKernelGGL(k_exact_prep, dim3(1), dim3(kPrepThreads), prep, st, a);
+    hipLaunchKernelGGL(k_exact_prep, dim3(1), dim3(kPrepThreads), prep, st, a, room);
     int rc = OOB_OK;
     if (a.fast) {
         const int threads = eval_threads(L, M, counts);

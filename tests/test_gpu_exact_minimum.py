@@ -360,6 +360,31 @@ def test_tables_of_a_node_with_stage_counts(P, shape, ends):
         assert st == P.OOB_OK and got == E.exact_minimum_staged(inp), (shape, ends, var)
 
 
+@pytest.mark.parametrize("L,M", [(92, 1), (60, 8), (150, 8), (66, 33)])
+def test_list_of_the_possible_slowest_stages(P, sizes, L, M):
+    """Every stage that fits once, with its time, ascending by the leading bits -- lists put in order in LDS and longer ones."""
+    import numpy as np
+    import torch
+
+    inp = inputs.random_small(17, L, M, 1, 1, L, f=1, t_lo=200, t_hi=3000, tight_mem=True)
+    e = P.ExactMinimum(inp)
+    st, _ = e.run()
+    assert st == P.OOB_OK
+    h, at = exact_sizes.head(e.workspace), exact_sizes.offsets(sizes, L, M, inp.n_max)
+    n = h["ncand"]
+    tau = e.workspace[at["ctau"]: at["ctau"] + 8 * n].view(torch.float64).cpu().numpy()
+    uvd = e.workspace[at["cuvd"]: at["cuvd"] + 4 * n].view(torch.int32).cpu().numpy()
+    PT = np.concatenate([np.zeros((1, M), dtype=np.int64), np.cumsum(inp.fwd_ns + inp.bwd_ns, axis=0)])
+    X = np.concatenate([[0], inp.boundary_ns[:-1], [0]])
+    mem = np.concatenate([[0], np.cumsum(inp.mem_bytes)])
+    want = {(u, v, d): int(PT[v, d - 1] - PT[u, d - 1] + X[v]) for v in range(1, L + 1) for u in range(v) for d in range(1, M + 1)
+            if -(-int(mem[v] - mem[u]) // d) <= inp.mem_cap}
+    got = list(zip((uvd & 255).tolist(), (uvd >> 8 & 255).tolist(), (uvd >> 16).tolist()))
+    assert len(set(got)) == n == len(want) and all(want[k] == t for k, t in zip(got, tau.tolist()))
+    lead = tau.view(np.int64) >> 44
+    assert (np.diff(lead - lead.min()).clip(max=1)[: int((lead - lead.min() < 4095).sum()) - 1] >= 0).all()
+
+
 def test_leftovers_with_stage_counts_are_listed_once(P, sizes):
     """Slowest stages whose tables exceed LDS are left to the general path: each at most once, whatever the
     number of templates that pick it first."""
