@@ -23,9 +23,9 @@
 //   k_exact_filter        keeps those whose bound does not exceed what was found;
 //   k_exact_eval<kRest>   evaluates these exactly, looking at the bounds again as the minima fall.
 // Small jobs (kDirectMax) skip the bounds and evaluate every stage but those too dear by their time alone.
-// Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.68-0.74 ms (1 400 of 17 524 slowest stages
-// evaluated); 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 69 us; 48 layers, 8 GPUs per node, N_b = 20 with
-// the limit binding 38.0 -> 2.7-4.0 ms by the instance (the evaluation of every stage in tables of the workspace before).
+// Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.39 ms (2 000 evaluations of 17 524 slowest stages);
+// 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 56 us; 48 layers, 8 GPUs per node, N_b = 20 with
+// the limit binding 38.0 -> 0.57 ms (the evaluation of every stage in tables of the workspace before).
 //
 // k_exact_eval: one workgroup per slowest stage, everything in LDS and registers, times as exact integers in doubles.
 // Phase 1, per wave, no workgroup barrier: the one-node table of start layer q, G_q[r][g] = least cost
@@ -996,57 +996,105 @@ __device__ __forceinline__ void node_tables(const Args &a, const Eval &e, int le
 }
 
 // c -> c + 1 whole nodes: nxt[p] = min over r of cur[p - r] + W[r][p - r] for this side, by nth threads (whole waves).
-template <bool STAGED>
-__device__ void node_step(const Args &a, int len, int band, int c, const double *Wm, const double *cur, double *nxt, int th,
-                          int nth) {
-    const int lo = c + 1, hi = (int)imin(len, (c + 1) * band), np = hi - lo + 1;
-    if (!STAGED) {
-        const int h4 = th & 3;
-        for (int i = th; i < ((np * 4 + 63) & ~63); i += nth) { // whole waves, four threads per position
-            const int p = lo + (i >> 2), most = imin(band, p - c); // c nodes cover at least c layers
-            double m = kNone;
-            if (p <= hi)
-                for (int r = 1 + h4; r <= most; r += 4) m = fmin(m, cur[p - r] + Wm[band_index(r, p - r, len)]);
-            m = min4(m);
-            if (h4 == 0 && p <= hi) nxt[p] = m;
-        }
-    } else {
-        const int J = a.Smax + 1, M = a.M;
-        for (int i = th; i < np * J; i += nth) {
-            const int p = lo + i / J, s = i % J, most = imin(band, p - c);
-            double m = kNone;
-            for (int r = 1; r <= most; ++r)
-                for (int j = 1; j <= imin(imin(M, r), s - c); ++j)
-                    m = fmin(m, cur[(size_t)(p - r) * J + s - j] + Wm[(size_t)band_index(r, p - r, len) * M + j - 1]);
-            nxt[(size_t)p * J + s] = m;
-        }
+__device__ void node_step(int len, int band, int c, const double *Wm, const double *cur, double *nxt, int th, int nth) {
+    const int lo = c + 1, hi = imin(len, (c + 1) * band), np = hi - lo + 1, h4 = th & 3;
+    for (int i = th; i < ((np * 4 + 63) & ~63); i += nth) { // whole waves, four threads per position
+        const int p = lo + (i >> 2), most = imin(band, p - c); // c nodes cover at least c layers
+        double m = kNone;
+        if (p <= hi)
+            for (int r = 1 + h4; r <= most; r += 4) m = fmin(m, cur[p - r] + Wm[band_index(r, p - r, len)]);
+        m = min4(m);
+        if (h4 == 0 && p <= hi) nxt[p] = m;
     }
 }
 // OUT[c][g]: c whole nodes and g more GPUs next to the slowest stage cover the side.
-template <bool STAGED>
-__device__ void node_out(const Args &a, int len, int band, int c, const double *cur, const double *GU, double *OUT, int th, int nth) {
-    const int M = a.M, from = imax(1, len - c * band), to = imin(band, len - c); // distances left for the last node
+__device__ void node_out(int M, int len, int band, int c, const double *cur, const double *GU, double *OUT, int th, int nth) {
+    const int from = imax(1, len - c * band), to = imin(band, len - c); // distances left for the last node
     const bool whole = len >= c && len <= c * band;
-    if (!STAGED) {
-        for (int i = th; i < ((M * 4 + 63) & ~63); i += nth) { // four threads per g
-            const int g = i >> 2, h4 = i & 3;
-            double m = kNone;
-            if (g == 0) { if (h4 == 0 && whole) m = cur[len]; }
-            else if (g < M) for (int r = from + h4; r <= to; r += 4) m = fmin(m, cur[len - r] + GU[(r - 1) * M + g]);
-            m = min4(m);
-            if (h4 == 0 && g < M) OUT[c * M + g] = m;
+    for (int i = th; i < ((M * 4 + 63) & ~63); i += nth) { // four threads per g
+        const int g = i >> 2, h4 = i & 3;
+        double m = kNone;
+        if (g == 0) { if (h4 == 0 && whole) m = cur[len]; }
+        else if (g < M) for (int r = from + h4; r <= to; r += 4) m = fmin(m, cur[len - r] + GU[(r - 1) * M + g]);
+        m = min4(m);
+        if (h4 == 0 && g < M) OUT[c * M + g] = m;
+    }
+}
+
+// The same with stage counts: a thread takes kCounts neighbouring counts s of a cover by r layers and j stages more, so that of
+// what it reads -- the M entries of the last node, the counts s - M .. s + kCounts - 2 of the cover before it -- each serves
+// several sums (one count a thread, every sum two reads: 217 000 cycles an entry at 48 layers, 8 GPUs,
+// 8 nodes; 80 000 now, with the waves of a side without layers put to the other's work; call 0.85 -> 0.56 ms).
+// No count is below that of the nodes, so entry 0 of a row is impossible from one node on and stands for the counts below 0.
+constexpr int kCounts = 4;
+template <int MT>
+__device__ __forceinline__ void add_node(const double *before, const double *node, int M, int s0, double *m) {
+    constexpr int JM = MT ? MT : 8;
+    double w[JM], x[JM + kCounts - 1];
+#pragma unroll
+    for (int j = 0; j < JM; ++j) w[j] = MT || j < M ? node[j] : kNone;
+#pragma unroll
+    for (int i = 0; i < JM + kCounts - 1; ++i) x[i] = before[imax(s0 - JM + i, 0)];
+#pragma unroll
+    for (int i = 0; i < kCounts; ++i)
+#pragma unroll
+        for (int j = 1; j <= JM; ++j) m[i] = fmin(m[i], x[JM + i - j] + w[j - 1]);
+}
+template <int MT>
+__device__ void node_step_staged(const Args &a, int len, int band, int c, const double *Wm, const double *cur, double *nxt, int th, int nth) {
+    const int J = a.Smax + 1, M = MT ? MT : a.M, lo = c + 1, hi = imin(len, (c + 1) * band), np = hi - lo + 1;
+    if (c == 0) { // a single node
+        for (int i = th; i < np * J; i += nth) {
+            const int p = 1 + i / J, s = i % J;
+            nxt[p * J + s] = s >= 1 && s <= M ? Wm[(size_t)band_index(p, 0, len) * M + s - 1] : kNone;
         }
-    } else {
-        const int J = a.Smax + 1, row_n = staged_row(M);
+        return;
+    }
+    const int groups = (J + kCounts - 1) / kCounts, items = np * groups, h4 = th & 3;
+    for (int i = th; i < ((items * 4 + 63) & ~63); i += nth) { // whole waves, four threads per item
+        const int it = imin(i >> 2, items - 1), p = lo + it / groups, s0 = it % groups * kCounts;
+        const int least = imax(1, p - c * band), most = imin(band, p - c); // c nodes cover c layers at least and c band at most
+        double m[kCounts];
+#pragma unroll
+        for (int q = 0; q < kCounts; ++q) m[q] = kNone;
+        for (int r = least + h4; r <= most; r += 4) add_node<MT>(cur + (p - r) * J, Wm + (size_t)band_index(r, p - r, len) * M, M, s0, m);
+#pragma unroll
+        for (int q = 0; q < kCounts; ++q) {
+            m[q] = min4(m[q]);
+            if (h4 == q && i >> 2 < items && s0 + q < J) nxt[p * J + s0 + q] = m[q];
+        }
+    }
+}
+template <int MT>
+__device__ void node_out_staged(const Args &a, int len, int band, int c, const double *cur, const double *GU, double *OUT, int th, int nth) {
+    const int J = a.Smax + 1, M = MT ? MT : a.M, row_n = staged_row(M);
+    const int from = imax(1, len - c * band), to = imin(band, len - c); // distances left for the last node
+    double *const out = OUT + (size_t)c * M * J;
+    if (c == 0) { // (a side of no layers: nothing is a cover)
         for (int i = th; i < M * J; i += nth) {
             const int g = i / J, s = i % J;
-            double m = kNone;
-            if (g == 0) { if (whole) m = cur[(size_t)len * J + s]; }
-            else
-                for (int r = from; r <= to; ++r)
-                    for (int j = 1; j <= imin(imin(g, r), s); ++j)
-                        m = fmin(m, cur[(size_t)(len - r) * J + s - j] + GU[(size_t)(r - 1) * row_n + staged_col(g, j)]);
-            OUT[((size_t)c * M + g) * J + s] = m;
+            out[i] = len == 0 ? (i == 0 ? 0.0 : kNone) : s >= 1 && s <= g && len <= band ? GU[(size_t)(len - 1) * row_n + staged_col(g, s)] : kNone;
+        }
+        return;
+    }
+    const bool whole = len >= c && len <= c * band;
+    for (int s = th; s < J; s += nth) out[s] = whole ? cur[(size_t)len * J + s] : kNone; // g = 0
+    const int groups = (J + kCounts - 1) / kCounts, items = (M - 1) * groups, h = th & 15;
+    for (int i = th; i < ((items * 16 + 63) & ~63); i += nth) { // sixteen threads per item
+        const int it = imin(i >> 4, items - 1), g = 1 + it / groups, s0 = it % groups * kCounts;
+        double m[kCounts];
+#pragma unroll
+        for (int q = 0; q < kCounts; ++q) m[q] = kNone;
+        for (int r = from + h; r <= to; r += 16) {
+            const double *before = cur + (size_t)(len - r) * J, *node = GU + (size_t)(r - 1) * row_n + staged_col(g, 1);
+            for (int j = 1; j <= g; ++j)
+#pragma unroll
+                for (int q = 0; q < kCounts; ++q) m[q] = fmin(m[q], before[imax(s0 + q - j, 0)] + node[j - 1]);
+        }
+#pragma unroll
+        for (int q = 0; q < kCounts; ++q) {
+            m[q] = min16(m[q]);
+            if (h == q && i >> 4 < items && s0 + q < J) out[g * J + s0 + q] = m[q];
         }
     }
 }
@@ -1323,15 +1371,29 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
         }
         wg_sync();
     } else {
-    // wide ones: half of the waves each, a barrier per node count
-    double *cur = e.NP + (mir ? (size_t)(lenP + 1) * J : 0), *nxt = cur + (size_t)(L + 2) * J;
-    const int len = mir ? lenS : lenP, band = mir ? bandS : bandP, cend = mir ? cendS : cendP;
-    for (int i = th; i < (len + 1) * J; i += nth) { cur[i] = i == 0 ? 0.0 : kNone; nxt[i] = kNone; }
-    wg_sync();
+    // wide ones: half of the waves each (one side alone: all), a barrier per node count
+    const bool alone = STAGED && (!lenP || !lenS), after = alone ? !lenP : (bool)mir;
+    const int t0 = alone ? (int)threadIdx.x : th, tn = alone ? (int)blockDim.x : nth;
+    double *cur = e.NP + (after ? (size_t)(lenP + 1) * J : 0), *nxt = cur + (size_t)(L + 2) * J;
+    double *const out = e.OUT + (after ? (size_t)a.nodes * M * J : 0);
+    const double *const W1 = WP + (after ? WS - WP : 0), *const GU1 = e.GU + (after ? bandP * gu : 0);
+    const int len = after ? lenS : lenP, band = after ? bandS : bandP, cend = after ? cendS : cendP;
+    if constexpr (STAGED) {
+        if (alone) node_out_staged<MT>(a, 0, 0, 0, cur, GU1, e.OUT + (after ? 0 : (size_t)a.nodes * M * J), t0, tn);
+        wg_sync(); // W and GU are written
+    } else {
+        for (int i = th; i < len + 1; i += nth) { cur[i] = i == 0 ? 0.0 : kNone; nxt[i] = kNone; }
+        wg_sync();
+    }
     for (int c = 0; c < imax(cendP, cendS); ++c) {
         if (c < cend) {
-            node_out<STAGED>(a, len, band, c, cur, e.GU + (mir ? bandP * gu : 0), e.OUT + (mir ? (size_t)a.nodes * M * J : 0), th, nth);
-            if (c + 1 < cend) node_step<STAGED>(a, len, band, c, WP + (mir ? WS - WP : 0), cur, nxt, th, nth);
+            if constexpr (STAGED) {
+                node_out_staged<MT>(a, len, band, c, cur, GU1, out, t0, tn);
+                if (c + 1 < cend) node_step_staged<MT>(a, len, band, c, W1, cur, nxt, t0, tn);
+            } else {
+                node_out(M, len, band, c, cur, GU1, out, t0, tn);
+                if (c + 1 < cend) node_step(len, band, c, W1, cur, nxt, t0, tn);
+            }
         }
         wg_sync();
         double *t = cur; cur = nxt; nxt = t;

@@ -385,6 +385,16 @@ def test_list_of_the_possible_slowest_stages(P, sizes, L, M):
     assert (np.diff(lead - lead.min()).clip(max=1)[: int((lead - lead.min() < 4095).sum()) - 1] >= 0).all()
 
 
+@pytest.mark.parametrize("M", [1, 3, 4, 8])
+@pytest.mark.parametrize("nb", [2, 7, 8, 9, 10])
+def test_stage_counts_around_whole_groups(P, M, nb):
+    """Counts 0 .. N_b in groups of four: one short group, and every remainder; one side without layers and two."""
+    for L, n_max in ((18, 3), (26, 6)):
+        inp = inputs.random_small(nb, L, M, 1, n_max, nb, f=1, t_lo=60, t_hi=99)
+        st, got = P.ExactMinimum(inp, staged=True).run()
+        assert st == P.OOB_OK and got == E.exact_minimum_staged(inp), (L, M, nb)
+
+
 def test_leftovers_with_stage_counts_are_listed_once(P, sizes):
     """Slowest stages whose tables exceed LDS are left to the general path: each at most once, whatever the
     number of templates that pick it first."""
