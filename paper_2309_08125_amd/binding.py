@@ -251,19 +251,31 @@ def oob_exact_minimum_staged(profile, L, n_min, n_max, gpus_per_node, microbatch
 
 
 # ---- convenience layer over torch device memory ------------------------------------------
+def _to_device(parts, device):
+    """Host integers (a list of flat sequences) as one int64 device tensor.  By way of pinned memory: the copy is only enqueued on the
+    current stream (torch keeps the pinned block until it is done), where one from pageable memory holds the host up."""
+    import numpy as np
+    import torch
+
+    host = torch.empty(sum(len(p) for p in parts), dtype=torch.int64, pin_memory=True)
+    np.concatenate([np.asarray(p, dtype=np.int64) for p in parts], out=host.numpy())
+    return host.to(device, non_blocking=True)
+
+
 class DeviceProfile:
-    """A PlanInput's arrays resident in HBM: one device buffer, one host-to-device copy."""
+    """A PlanInput's arrays resident in HBM: one device buffer, one host-to-device copy, which is done on return
+    (wait=False: only enqueued on the current stream)."""
 
     KEYS = ("fwd_ns", "bwd_ns", "mem_bytes", "boundary_ns")
 
-    def __init__(self, inp, device="cuda:0"):
+    def __init__(self, inp, device="cuda:0", wait: bool = True):
         import numpy as np
         import torch
 
         self.inp = inp
         parts = [np.ascontiguousarray(a, dtype=np.int64).reshape(-1)
                  for a in (inp.fwd_ns, inp.bwd_ns, inp.mem_bytes, inp.boundary_ns)]
-        self.base = torch.from_numpy(np.concatenate(parts)).to(device)
+        self.base = torch.from_numpy(np.concatenate(parts)).to(device) if wait else _to_device(parts, device)
         self.t, o = {}, 0
         for k, a in zip(self.KEYS, parts):
             self.t[k] = self.base[o: o + a.size]
@@ -392,7 +404,7 @@ class Planner:
         """Independent jobs through oob_plan_templates_batch (one after the other on the stream)."""
         import torch
 
-        profs = [DeviceProfile(inp, self.device) for inp in inps]
+        profs = [DeviceProfile(inp, self.device, wait=False) for inp in inps]
         outs = [self.new_outputs(inp) for inp in inps]
         s = torch.cuda.current_stream(self.device)
         rc = oob_plan_templates_batch(self.h, [p.c for p in profs], [i.L for i in inps],
@@ -406,7 +418,7 @@ class Planner:
         return [o.to_host() for o in outs]
 
     def plan(self, inp) -> Dict[str, "object"]:
-        prof = DeviceProfile(inp, self.device)
+        prof = DeviceProfile(inp, self.device, wait=False)
         out = self.new_outputs(inp)
         self.enqueue(prof, out)
         return out.to_host()
@@ -460,8 +472,9 @@ class Instantiator:
         if nbytes == 0:
             raise ValueError("oob_inst_workspace_size: arguments out of range")
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        self.offsets = torch.zeros(N_hi - N_lo + 2, dtype=torch.int64, device=self.device)
-        self.status = torch.zeros(1, dtype=torch.int32, device=self.device)
+        # offsets and status side by side: count() brings both to the host with one copy
+        self._counts = torch.zeros(N_hi - N_lo + 3, dtype=torch.int64, device=self.device)
+        self.offsets, self.status = self._counts[:-1], self._counts[-1:].view(torch.int32)[:1]
 
     def _spec(self):
         return (self.sizes.data_ptr() if self.sizes is not None else 0, self.p, self.n0, self.N_lo, self.N_hi,
@@ -474,8 +487,8 @@ class Instantiator:
         s = torch.cuda.current_stream(self.device)
         check(oob_inst_count(*self._spec(), self.offsets.data_ptr(), self.status.data_ptr(), s.cuda_stream),
               "oob_inst_count")
-        torch.cuda.synchronize(self.device)
-        return self.offsets.cpu().numpy(), int(self.status.item())
+        got = self._counts.cpu().numpy()  # waits for the stream's work, then one copy
+        return got[:-1], int(got[-1:].view("int32")[0])
 
     def enqueue(self, x, capacity: int) -> None:
         """oob_inst_enumerate into the 16-bit tensor x ([p, capacity], read as uint16) on the current stream;
@@ -592,13 +605,13 @@ class Distributor:
             x = torch.from_numpy(np.ascontiguousarray(np.asarray(x, dtype=np.uint16).T).view(np.int16)).to(self.device)
         self.x, self.count, self.Q = x, count, Q
         self.p, self.capacity = int(x.shape[0]), int(x.shape[1])
-        self.template_T = torch.tensor([int(v) for v in template_T], dtype=torch.int64, device=self.device)
+        self.template_T = _to_device([[int(v) for v in template_T]], self.device)
         n = max(count, 1)
-        self.vx = torch.zeros((n, 2), dtype=torch.int64, device=self.device)
-        self.slowest = torch.zeros(n, dtype=torch.int64, device=self.device)
+        # results out of one zeroed buffer: a small set of plans pays per launch
+        results = torch.zeros(3 * n, dtype=torch.int64, device=self.device)
+        self.vx, self.slowest = results[: 2 * n].view(n, 2), results[2 * n:]
         self.status = torch.full((n,), -99, dtype=torch.int32, device=self.device)
-        self.base = torch.zeros_like(x) if distribution else None
-        self.extra = torch.zeros_like(x) if distribution else None
+        self.base, self.extra = torch.zeros((2, *x.shape), dtype=x.dtype, device=x.device) if distribution else (None, None)
 
     def enqueue(self) -> None:
         import torch
@@ -624,15 +637,13 @@ class Distributor:
 
     def choose(self, offsets):
         """Index of the best plan of every group offsets[g] .. offsets[g+1]-1 (host array in, host array out)."""
-        import numpy as np
         import torch
 
-        off = torch.from_numpy(np.asarray(offsets, dtype=np.int64)).to(self.device)
-        best = torch.full((len(offsets) - 1,), -99, dtype=torch.int64, device=self.device)
+        off = _to_device([offsets], self.device)
+        best = torch.empty(len(offsets) - 1, dtype=torch.int64, device=self.device)
         s = torch.cuda.current_stream(self.device)
         check(oob_dist_choose(off.data_ptr(), len(offsets) - 1, self.count, self.slowest.data_ptr(),
                               self.status.data_ptr(), best.data_ptr(), s.cuda_stream), "oob_dist_choose")
-        torch.cuda.synchronize(self.device)
         return best.cpu().numpy()
 
     def time_choose(self, offsets, reps: int = 20) -> float:

@@ -409,3 +409,34 @@ def test_headline_node_specification_at_full_size(P):
     for g in range(len(off) - 1):
         seg = slow[off[g]:off[g + 1]]
         assert best[g] == off[g] + int(np.argmin(seg))
+
+
+def test_times_and_groups_handed_over_on_a_stream_of_the_callers(P):
+    """The times and the groups travel on the current stream: everything on one that is not the default, behind work
+    of its own, and the arrays that come back are the caller's."""
+    import torch
+
+    n0, p, N, f = 2, 5, 20, 2
+    inst = P.Instantiator(None, (f + 1) * n0, N, f, n0=n0, p=p)
+    off, x, st = inst.enumerate()
+    assert st == P.OOB_OK
+    times = [7, 11, 13, 17, 19]
+    want = P.Distributor(x, len(x), times, 40)
+    want.solve()
+    best = want.choose(off)
+    s = torch.cuda.Stream()
+    busy = torch.empty(1 << 26, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        for _ in range(20):
+            busy.zero_()
+        again, st = inst.count()
+        xd = torch.empty((p, int(again[-1])), dtype=torch.int16, device="cuda")
+        inst.enqueue(xd, int(again[-1]))
+        d = P.Distributor(xd, int(again[-1]), times, 40)
+        d.enqueue()
+        got = d.choose(again)
+    assert st == P.OOB_OK and (again == off).all() and again is not off and (got == best).all()
+    inst.offsets.zero_()
+    torch.cuda.synchronize()
+    assert (again == off).all() and torch.equal(d.slowest, want.slowest) and torch.equal(d.vx, want.vx)
