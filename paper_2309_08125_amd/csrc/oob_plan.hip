@@ -436,8 +436,12 @@ __device__ __forceinline__ int xcd_chunked(int x, int n) {
 
 struct Rec24 { double2 a; double tm; }; // (T, T1), tmax: the 24 bytes of a record the splits need
 
-// Which child streams: the one that leaves less padding when the other one is cut into blocks of eight.
-__host__ __device__ __forceinline__ bool left_streams(int nA, int nB) { return nA * ((nB + 7) & ~7) <= nB * ((nA + 7) & ~7); }
+// Which child streams: the one that leaves less padding when the other one is cut into blocks of eight, but none of
+// more than `cap` tables.
+__host__ __device__ __forceinline__ bool left_streams(int nA, int nB, int cap) {
+    const bool left = nA * ((nB + 7) & ~7) <= nB * ((nA + 7) & ~7);
+    return left == ((left ? nA : nB) <= cap);
+}
 __device__ __forceinline__ int log2_up(int x) { return 32 - __clz(x - 1); } // smallest b with 2^b >= x, x >= 1
 
 // Four candidates of a step: streaming record (p, atm) against four stationary ones, into the minima a0..a3
@@ -487,6 +491,7 @@ struct KeyArgs {
     int NT;
     int s0, sstep;       // a launch covers the splits s0, s0 + sstep, ...
     int na;              // rows of the key table: targets of the largest group
+    int cap;             // most streaming tables of a split point
     int t_lo1, dlo;      // smallest target of the whole-node family; first device set of the level
     int pack, xcd;       // several items per wave near the range ends; XCD-chunked task order
 };
@@ -544,7 +549,7 @@ __global__ void __launch_bounds__(256, kWavesPerSimd) k_split_key(Tables t, KeyA
     const int vmax = tile_vmax(L, vb); // last layer position of the block's columns (never beyond L)
     const int kmin = ub * 8 + s + kofs, kmax = imin(vmax - r, kmin + klen - 1); // this workgroup's segment of the block's split points
     if (!(mA0 <= mA1 && mB0 <= mB1 && kmin <= kmax)) return; // nothing to merge
-    const bool y_left = left_streams(mA1 - mA0 + 1, mB1 - mB0 + 1);
+    const bool y_left = left_streams(mA1 - mA0 + 1, mB1 - mB0 + 1, ka.cap);
     const int yM0 = y_left ? mA0 : mB0, yM1 = y_left ? mA1 : mB1; // streaming unit counts
     const int qM0 = y_left ? mB0 : mA0, qM1 = y_left ? mB1 : mA1; // stationary unit counts
     const int nY = yM1 - yM0 + 1, nS = qM1 - qM0 + 1, nyb = (nY + 7) >> 3, nmb = (nS + 7) >> 3;
@@ -1392,7 +1397,7 @@ constexpr size_t kLdsLimit = 160 * 1024; // gfx950: 160 KB of LDS per workgroup
 constexpr size_t kLdsPrefer = 64 * 1024; // at least two workgroups per compute unit
 
 // Launch shape of k_split for one family of one level.
-struct SplitPlan { int waves, groups, pc, ntab, na; size_t lds; };
+struct SplitPlan { int waves, groups, pc, ntab, na, cap, full; size_t lds; }; // (cap, full: k_split_key)
 bool plan_split(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
     target_units(fam, Sp, sh.M, sh.n_max, &t_lo, &t_hi);
@@ -1454,6 +1459,18 @@ static int small_columns(const Shape &sh, int S, long long most) {
 }
 constexpr int kOverlapFrom = 24000; // thousand candidates of a level: see enqueue_job
 constexpr int kSelLanes = 1; // lanes per state below that
+// Waves of k_split_key on a compute unit in workgroups of w of them, which share the key table.
+static int key_waves_on(int na, int ntab, int w) {
+    return imin((int)(kLdsLimit / ((size_t)na * 512 + (size_t)w * ntab * 192)) * w, 4 * kWavesPerSimd);
+}
+// Waves per workgroup of a keyed launch: as many as put the most waves on a compute unit, four
+// at most; of equal numbers the larger, which has fewer split points to do one after the other (61 layers 1.31 -> 1.19 ms).
+static int key_waves(int na, int ntab) {
+    int waves = 1;
+    for (int w = 2; w <= kKeyWaves; ++w)
+        if (key_waves_on(na, ntab, w) >= key_waves_on(na, ntab, waves)) waves = w;
+    return waves;
+}
 // Launch shape of k_split_key for one family of one level; waves and LDS follow per launch (key_waves, key_lds).
 bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
@@ -1462,7 +1479,7 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     if (t_hi < t_lo) return false;
     const int cnt = t_hi - t_lo + 1;
     p->groups = cdiv(cnt, kKeyTargets);
-    int ntab = 1;
+    int most = 0, least = 0; // streaming tables of the split that has most of them, by padding and where the shorter side streams
     for (int s = 1; s < Sp; ++s) {
         int A_lo, A_hi, B_lo, B_hi;
         child_units(fam, s, sh.M, sh.n_max, &A_lo, &A_hi);
@@ -1473,12 +1490,25 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
             const int mB0 = imax(B_lo, a0 - A_hi), mB1 = imin(B_hi, a1 - A_lo);
             if (mA0 <= mA1 && mB0 <= mB1) {
                 const int nA = mA1 - mA0 + 1, nB = mB1 - mB0 + 1;
-                ntab = imax(ntab, (left_streams(nA, nB) ? nA : nB) + 8); // streaming side, one block of the stationary side
+                most = imax(most, left_streams(nA, nB, 1 << 20) ? nA : nB);
+                least = imax(least, imin(nA, nB));
             }
         }
     }
-    p->ntab = ntab;
     p->na = imin(cnt, kKeyTargets);
+    p->full = most ? most + 8 : 1; // streaming side, one block of the stationary side
+    // The LDS of a launch is that of its split with the most streaming tables.  Where the splits of a short and a long side keep
+    // one workgroup of four waves (or more) off the compute unit, their shorter side streams: as many tables as leave room for it.
+    // Headline workload, time of the levels 36-43 (12 -> 16 waves) 775 -> 637 us, 55-61 (8 -> 12) 837 -> 743 us, call 6.70 ->
+    // 6.53 ms.  Not for a wave more in workgroups of three (levels 62-67, 8 -> 9 waves 542 -> 653 us; 48-54, 9 -> 12 waves
+    // 848 -> 918 us): the padding of the longer side costs more.
+    p->cap = most;
+    auto on = [&](int cap) { return key_waves_on(p->na, cap + 8, key_waves(p->na, cap + 8)); };
+    if (most) {
+        const int goal = on(least), had = on(most);
+        if (had >= 8 && goal >= had + 4) while (on(p->cap) < goal) --p->cap;
+    }
+    p->ntab = most ? p->cap + 8 : 1;
     return true;
 }
 
@@ -1678,27 +1708,16 @@ struct SplitRange { int s0, sstep, scount; };
 // A keyed launch: the target groups of family `fam` (gz of them) and, in a launch for both families
 // of a low level, those of the whole-node family behind them (`groups` in all); at most ntab tables
 // staged per split point, na targets per group.
-struct KeyLaunch { int fam, gz, groups, ntab, na; };
+struct KeyLaunch { int fam, gz, groups, ntab, na, cap; };
 // Most tables per split point the keyed kernel serves: with a full group of targets four waves then still fit a
 // compute unit, in a workgroup of 140 KB.  Measured against the plain kernel, most tables, layers x nodes x GPUs per node:
 // 76, 150 x 150 x 8: 109 and 329 ms; 82, 140 x 140 x 64: 137 and 452 ms; 99, 176 x 176 x 8: 313 and 833 ms; 120, 200 x 200 x 8:
 // 747 and 1 790 ms; 136, 240 x 200 x 8: 2.67 and 5.50 s.
 constexpr int kKeyTables = 144;
-// Waves per workgroup of a keyed launch: as many as put the most waves on a compute unit (they share the key table), four
-// at most; of equal numbers the larger, which has fewer split points to do one after the other (61 layers 1.31 -> 1.19 ms).
-static int key_waves(int na, int ntab) {
-    const size_t keys = (size_t)na * 512, per = (size_t)ntab * 192;
-    int waves = 1, most = 0;
-    for (int w = 1; w <= kKeyWaves; ++w) {
-        const int on = imin((int)(kLdsLimit / (keys + w * per)) * w, 4 * kWavesPerSimd);
-        if (on >= most) { most = on; waves = w; }
-    }
-    return waves;
-}
 static size_t key_lds(int na, int ntab) { return (size_t)na * 512 + (size_t)key_waves(na, ntab) * ntab * 192; }
 static void launch_split_key(const Tables &t, int S, const KeyLaunch &kl, int NT, int xcd, SplitRange sr, hipStream_t st) {
     KeyArgs ka;
-    ka.na = kl.na;
+    ka.na = kl.na; ka.cap = kl.cap;
     ka.Sp = S; ka.fam0 = kl.fam; ka.gz = kl.gz; ka.NT = NT; ka.s0 = sr.s0; ka.sstep = sr.sstep;
     ka.t_lo1 = imax(2, cdiv(S, t.sh.M)); ka.dlo = dlo_of(S, t.sh.M); ka.pack = kKeyPack; ka.xcd = xcd;
     hipLaunchKernelGGL(k_split_key, dim3(seg_count(t.sh.L, S), sr.scount, kl.groups), dim3(key_waves(kl.na, kl.ntab) * 64), key_lds(kl.na, kl.ntab), st, t, ka);
@@ -1710,10 +1729,10 @@ static void launch_split_keys(const Tables &t, int S, const bool *have, const Sp
     KeyLaunch kl[2];
     for (int fam = 0; fam < 2; ++fam)
         if (have[fam])
-            kl[fam] = KeyLaunch{fam, kp[fam].groups, kp[fam].groups, kp[fam].ntab, kp[fam].na};
+            kl[fam] = KeyLaunch{fam, kp[fam].groups, kp[fam].groups, kp[fam].ntab, kp[fam].na, kp[fam].cap};
     if (have[0] && have[1]) {
         const KeyLaunch both{0, kl[0].groups, kl[0].groups + kl[1].groups, imax(kl[0].ntab, kl[1].ntab),
-                             imax(kl[0].na, kl[1].na)};
+                             imax(kl[0].na, kl[1].na), imax(kl[0].cap, kl[1].cap)};
         launch_split_key(t, S, both, NT, xcd, sr, st);
         return;
     }
@@ -1756,12 +1775,12 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
     int force_plain = h->opt_plain != 0;
     size_t lds = 0; // of the largest keyed launch
     for (int S = 2; S <= sh.Smax; ++S) {
-        int ntab = 0, na = 0;
+        int ntab = 0, na = 0, full = 0;
         for (int fam = 0; fam < 2; ++fam) {
             SplitPlan sp;
-            if (plan_split_key(sh, S, fam, &sp)) { ntab = imax(ntab, sp.ntab); na = imax(na, sp.na); }
+            if (plan_split_key(sh, S, fam, &sp)) { ntab = imax(ntab, sp.ntab); na = imax(na, sp.na); full = imax(full, sp.full); }
         }
-        if (ntab > kKeyTables) force_plain = 1;
+        if (full > kKeyTables) force_plain = 1;
         else if (ntab) lds = std::max(lds, key_lds(na, ntab));
     }
     if (!force_plain && lds > kLdsPrefer) // beyond the default dynamic-LDS limit of a launch

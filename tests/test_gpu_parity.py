@@ -422,6 +422,16 @@ def test_split_kernel_of_the_most_nodes_it_serves(P, shape):
     planner.close()
 
 
+@pytest.mark.parametrize("shape", [(44, 1, 36, 8, 0), (47, 4, 44, 8, 50), (62, 6, 60, 8, 0), (76, 5, 37, 2, 100)])
+def test_splits_of_a_short_and_a_long_side(P, shape):
+    """Levels whose launch has the shorter side of such splits stream (36 to 61 targets across nodes), every state."""
+    L, n_min, n_max, M, nb = shape
+    inp = inputs.random_small(67, L, M, n_min, n_max, nb, f=2, t_lo=20)
+    planner = P.Planner(L, n_max, M)
+    full_check(P, planner, inp)
+    planner.close()
+
+
 def test_xcd_chunked_task_order(P):
     """The other order of the workgroup tasks (block row by block row, each XCD walking one
     contiguous stretch of the list) computes the same tables."""
