@@ -156,7 +156,7 @@ __host__ __device__ inline int tile_vmax(int L, int vb) { return vb * 8 + 7 - co
 // the target gives, rounded to the nearest, all of the same number of groups up to one.
 constexpr int kSegUnit = 4;
 constexpr int kSegMin = 4; // no target below this (sizes the task lists)
-constexpr int kSegTarget = 16, kSegWorkgroups = 512;
+constexpr int kSegTarget = 16, kSegWorkgroups = 512, kSegLong = 32, kSegLongWorkgroups = 1280;
 // Split points of all blocks of the level, for one split.
 __host__ __device__ inline int level_krange(int L, int S) {
     const int NB = nblocks_of(L), ubmax = (L - S) / 8;
@@ -164,12 +164,15 @@ __host__ __device__ inline int level_krange(int L, int S) {
     for (int d = NB - 1; d >= tile_dmin(L, S); --d) c += (imin(ubmax, NB - 1 - d) + 1) * (8 * d + 8 - col_shift(L) - S);
     return c;
 }
-// The longest segments (16, 8 or 4 split points) that still make kSegWorkgroups workgroups of the level: a longer segment
+// The longest segments (32, 16, 8 or 4 split points) that still make kSegWorkgroups workgroups of the level: a longer segment
 // pays the set-up and the merge of its keys less often, a shorter one fills the machine and shortens the level.
 // Measured with 256, 512, 768 workgroups wanted: headline workload 6.93, 6.82, 6.89 ms; 61 layers 1.35, 1.19, 1.26 ms;
 // batch of 32 jobs 78.5, 79.1, 79.4 ms.  8 or 32 split points at most: 7.27, 7.10 ms; 1.19, 1.27 ms; 86.7, 77.1 ms.
+// Hence 32 where that makes kSegLongWorkgroups: batch 77.7 -> 75.5 ms, headline workload 6.53 -> 6.52 ms.  With 600, 768, 1 024, 1 536,
+// 3 072 of them wanted: batch 75.6, 75.6, 75.5, 75.7, 77.6 ms; headline workload 6.78, 6.73, 6.57, 6.50-6.57, 6.52 ms.
 __host__ __device__ inline int seg_target(int L, int S) {
     const long long passes = (long long)level_krange(L, S) * (S - 1);
+    if (passes >= (long long)kSegLong * kSegLongWorkgroups) return kSegLong;
     return passes >= (long long)kSegTarget * kSegWorkgroups ? kSegTarget : passes >= (long long)kSegTarget / 2 * kSegWorkgroups ? kSegTarget / 2 : kSegMin;
 }
 __host__ __device__ inline int tile_krange(int L, int S, int ub, int vb) {
