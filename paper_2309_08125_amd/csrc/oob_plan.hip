@@ -16,7 +16,7 @@
 // where X.T is the child's own total under its own stage count, and (cl, cr) = (-r, 0) when
 // N_b is the caller's microbatch count or (3r, 4s) when N_b = 4 S' per state.  So the hot
 // loop needs only (T, T1, tmax) per child: 2 adds (the second under a mask), 1 compare, 1 min per candidate.
-// T3 and k* are carried per state for the output only.
+// T3 and k* follow from the stages of a template and are formed for the templates alone (k_backtrack).
 //
 // One level S' = split kernels, then a select kernel.
 //   k_split_key  per (block of the (u,v) plane, segment of its split points k, split s, group of
@@ -51,7 +51,7 @@ constexpr double kNone = __builtin_huge_val(); // total of a state that does not
 constexpr long long kExactBound = 1LL << 52;
 constexpr int kInternalError = -5;             // status: a state's minimum was not re-found
 
-struct Rec { double T, T1, tmax, T3; };        // 32 bytes, one per (table, u, v)
+struct Rec { double T, T1, tmax; long long choice; }; // 32 bytes, one per (table, u, v); the split that gives T: s | k << 10 | m << 21
 
 // Device view of the workspace.
 struct Tables {
@@ -61,7 +61,6 @@ struct Tables {
     int tab_recs;         // records per table = tri_blocks(NB) * 64
     int inv_M;            // over_M()
     Rec *rec;             // [tables * tab_recs]
-    int *kstar, *choice;  // [tables * tab_recs]
     double *partT;        // [(S'-1) * deltas * tiles * 64] per-split minima of the current level
     unsigned long long *key; // the same memory: [deltas * tiles * 64] keys of the current level (keyed kernel)
     int *partK;           // same shape: first k reaching the minimum
@@ -238,19 +237,17 @@ __device__ void level1_body(const Tables &t, const oob_profile &prof, int wg) {
     int ub, vb;
     tile_decode(L, 1, tile, &ub, &vb);
     const int u = ub * 8 + (lane >> 3), v = vb * 8 + (lane & 7) - t.coff;
-    Rec r = {kNone, kNone, 0.0, 0.0};
+    Rec r = {kNone, kNone, 0.0, 0};
     if (u < L && v <= L && v - u >= 1 && s_PF[v] == s_PF[u]) { // (v < 0 in the first block column: no state)
         const long long bytes = s_PM[v] - s_PM[u];
         if ((bytes + d - 1) / d <= t.sh.cap) {
             const double nb = t.sh.Nb > 0 ? (double)t.sh.Nb : 4.0;
-            r.T1 = r.tmax = r.T3 = (double)(s_PT[v] - s_PT[u] + (v < L ? prof.boundary_ns[v - 1] : 0));
-            r.T = r.T1 + (nb - 2.0) * r.tmax + r.T3; // Eq. 2 with S' = 1, k* = 0
+            r.T1 = r.tmax = (double)(s_PT[v] - s_PT[u] + (v < L ? prof.boundary_ns[v - 1] : 0));
+            r.T = r.T1 + (nb - 2.0) * r.tmax + r.T1; // Eq. 2 with S' = 1, k* = 0, T3 = T1
         }
     }
     const long long o = (long long)delta * t.tab_recs + tri_index(ub, vb, t.NB) * 64 + lane; // level 1 has the first tables
     t.rec[o] = r;
-    t.kstar[o] = 0;
-    t.choice[o] = 0;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -814,6 +811,11 @@ __device__ __forceinline__ double cand_total(const Rec24 &a, const Rec24 &b, dou
     return a.tm >= b.tm ? (a.a.x + cl * a.tm) + 2.0 * b.a.y : a.a.y + (b.a.x + cr * b.tm);
 }
 
+// A state's record: from the candidate that gives it (Eq. 1, 3), or "no such state".
+__device__ __forceinline__ void write_state(const Tables &t, long long at, bool exists, double T, double T1, double tmax, int choice) {
+    t.rec[at] = exists ? Rec{T, T1, tmax, choice} : Rec{kNone, kNone, 0.0, 0};
+}
+
 // Without the keys of k_split_key: the per-split minima of k_split (flags[1]), or every candidate.
 constexpr int kSelPairs = 2; // pairs of child records a lane has in flight while it looks for the first m
 __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall) {
@@ -823,7 +825,7 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
     tile_decode(L, Sp, blockIdx.x, &ub, &vb);
     const int aidx = blockIdx.y, delta = dlo_of(Sp, M) + aidx;
     const int u = ub * 8 + (lane >> 3), v = vb * 8 + (lane & 7) - t.coff;
-    double best = kNone;
+    double best = kNone, T1 = kNone, tmax = 0.0;
     int bs = 0, bk = 0;
     if (t.flags[1]) {
         for (int s = 1; s < Sp; ++s) { // first s with the smallest minimum
@@ -832,8 +834,6 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
             if (T < best) { best = T; bs = s; bk = t.partK[o]; }
         }
     }
-    Rec out = {kNone, kNone, 0.0, 0.0};
-    int ks = 0, ch = 0;
     const Family fam = family_of(delta, M);
     int bm = 0;
     if (!t.flags[1]) {
@@ -850,8 +850,9 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
                 for (int k = u + s; k <= v - r; ++k) {
                     const Rec *atA = baseA + rec_off(u, k, t.coff, t.NB), *atB = baseB + rec_off(k, v, t.coff, t.NB);
                     for (int m = mlo; m <= mhi; ++m) {
-                        const double T = cand_total(load24(atA + m * trecs), load24(atB - m * trecs), cl, cr);
-                        if (T < best) { best = T; bs = s; bk = k; bm = m; }
+                        const Rec24 a = load24(atA + m * trecs), b = load24(atB - m * trecs);
+                        const double T = cand_total(a, b, cl, cr);
+                        if (T < best) { best = T; bs = s; bk = k; bm = m; T1 = a.a.y + b.a.y; tmax = fmax(a.tm, b.tm); }
                     }
                 }
             }
@@ -861,46 +862,25 @@ __device__ void select_lane_per_state(const Tables &t, int Sp, int NT, int NAall
         m_range(fam.fam, fam.units, bs, r, M, t.sh.n_max, &mlo, &mhi);
         const double cl = t.sh.Nb > 0 ? -(double)r : 3.0 * r, cr = t.sh.Nb > 0 ? 0.0 : 4.0 * bs;
         // first m whose candidate equals the minimum; kSelPairs candidates' records in flight at a time
-        const long long tabA = (long long)(level(t, bs).base + fam.fam_base) * t.tab_recs +
-                               rec_off(u, bk, t.coff, t.NB);
-        const long long tabB = (long long)(level(t, r).base + fam.fam_base + fam.units) * t.tab_recs +
-                               rec_off(bk, v, t.coff, t.NB);
+        const Rec *atA = t.rec + (long long)(level(t, bs).base + fam.fam_base) * trecs + rec_off(u, bk, t.coff, t.NB);
+        const Rec *atB = t.rec + (long long)(level(t, r).base + fam.fam_base + fam.units) * trecs + rec_off(bk, v, t.coff, t.NB);
         for (int m0 = mlo; m0 <= mhi && bm == 0; m0 += kSelPairs) {
-            Rec ra[kSelPairs], rb[kSelPairs];
+            Rec24 ra[kSelPairs], rb[kSelPairs];
 #pragma unroll
             for (int q = 0; q < kSelPairs; ++q) {
                 const int m = imin(m0 + q, mhi);
-                ra[q] = t.rec[tabA + (long long)m * t.tab_recs];
-                rb[q] = t.rec[tabB - (long long)m * t.tab_recs];
+                ra[q] = load24(atA + m * trecs);
+                rb[q] = load24(atB - m * trecs);
             }
 #pragma unroll
-            for (int q = 0; q < kSelPairs; ++q) {
-                const double T = ra[q].tmax >= rb[q].tmax ? (ra[q].T + cl * ra[q].tmax) + 2.0 * rb[q].T1
-                                                          : ra[q].T1 + (rb[q].T + cr * rb[q].tmax);
-                if (bm == 0 && m0 + q <= mhi && T == best) bm = m0 + q;
-            }
+            for (int q = 0; q < kSelPairs; ++q)
+                if (bm == 0 && m0 + q <= mhi && cand_total(ra[q], rb[q], cl, cr) == best) {
+                    bm = m0 + q; T1 = ra[q].a.y + rb[q].a.y; tmax = fmax(ra[q].tm, rb[q].tm);
+                }
         }
     }
-    if (best < kNone) {
-        if (bm == 0) {
-            *t.status = kInternalError;
-        } else {
-            const int r = Sp - bs;
-            const long long oa = rec_index(t, bs, fam.fam_base + bm, u, bk);
-            const long long ob = rec_index(t, r, fam.fam_base + fam.units - bm, bk, v);
-            const Rec a = t.rec[oa], b = t.rec[ob];
-            const int ka = t.kstar[oa], kb = t.kstar[ob];
-            out.T = best;
-            out.T1 = a.T1 + b.T1;                                                     // Eq. 1
-            if (a.tmax >= b.tmax) { out.tmax = a.tmax; ks = ka; out.T3 = a.T3 + b.T1; } // Eq. 3
-            else                  { out.tmax = b.tmax; ks = bs + kb; out.T3 = b.T3; }
-            ch = bs | (bk << 10) | (bm << 21);
-        }
-    }
-    const long long o = rec_block(t, Sp, delta, ub, vb) + lane;
-    t.rec[o] = out;
-    t.kstar[o] = ks;
-    t.choice[o] = ch;
+    if (best < kNone && bm == 0) *t.status = kInternalError;
+    write_state(t, rec_block(t, Sp, delta, ub, vb) + lane, best < kNone && bm, best, T1, tmax, bs | bk << 10 | bm << 21);
 }
 __global__ void __launch_bounds__(64) k_select(Tables t, int Sp, int NT, int NAall) {
     select_lane_per_state(t, Sp, NT, NAall);
@@ -919,7 +899,7 @@ __global__ void __launch_bounds__(64) k_select(Tables t, int Sp, int NT, int NAa
 //   2. The key of the (other) splits holds the smallest (T, s, k).
 //   3. FUSE only: the lanes' partial minima are merged in the order (T, s, k, m).
 //   4. A winner that came from a key does not know its m yet: the lanes test LPS m at a time.
-//   5. Lane 0 of the state forms the record from the two child records.
+//   5. The lane that has seen the winner forms the record from the two child records it has read.
 // Without keys (flags[0] = 0) the wave of part 0 evaluates the block one lane per state as k_select does.
 // ---------------------------------------------------------------------------------------
 constexpr int kSel8Outer = 4;  // candidates of the outer splits a lane has in flight
@@ -940,7 +920,7 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
     const Family fam = family_of(delta, M);
     const bool fixed_nb = t.sh.Nb > 0;
     const long long trecs = t.tab_recs;
-    double best = kNone;
+    double best = kNone, T1 = kNone, tmax = 0.0; // (of the candidate this lane has seen for it)
     unsigned btag = 0xffffffffu; // s << 21 | k << 10 | m (m = 0: not known yet)
 
     if (FUSE && valid) {
@@ -967,7 +947,9 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
                     for (int q = 0; q < kSel8Outer; ++q) {
                         const double T = cand_total(ra[q], rb[q], cl, cr);
                         const unsigned tag = ((unsigned)s << 21) | ((unsigned)kk[q] << 10) | (unsigned)m;
-                        if (T < best || (T == best && tag < btag)) { best = T; btag = tag; }
+                        if (T < best || (T == best && tag < btag)) {
+                            best = T; btag = tag; T1 = ra[q].a.y + rb[q].a.y; tmax = fmax(ra[q].tm, rb[q].tm);
+                        }
                     }
                 }
         }
@@ -983,13 +965,16 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
             if (sub == 0) *at = kNoKey;
         }
     }
+    bool mine = sub == 0; // the lane that writes the state's record
     if (FUSE) { // the lanes of a state: smallest (T, s, k, m)
+        const unsigned own = btag;
 #pragma unroll
         for (int d = 1; d < LPS; d <<= 1) {
             const double ob = __shfl_xor(best, d, 64);
             const unsigned ot = (unsigned)__shfl_xor((int)btag, d, 64);
             if (ob < best || (ob == best && ot < btag)) { best = ob; btag = ot; }
         }
+        if ((btag & 1023u) && best < kNone) mine = own == btag; // an outer split: the lane that has seen it (tags are unique)
     }
     const int bs = (int)(btag >> 21), bk = (int)((btag >> 10) & 2047u);
     int bm = (int)(btag & 1023u);
@@ -1014,36 +999,17 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
 #pragma unroll
             for (int q = kSel8M - 1; q >= 0; --q) {
                 const int m = m0 + LPS * q;
-                if (m <= mhi && cand_total(ra[q], rb[q], cl, cr) == best) found = m;
+                if (m <= mhi && cand_total(ra[q], rb[q], cl, cr) == best) { found = m; T1 = ra[q].a.y + rb[q].a.y; tmax = fmax(ra[q].tm, rb[q].tm); }
             }
+            int first = found;
 #pragma unroll
-            for (int d = 1; d < LPS; d <<= 1) found = imin(found, __shfl_xor(found, d, 64));
-            if (found != 0x7fffffff) bm = found;
+            for (int d = 1; d < LPS; d <<= 1) first = imin(first, __shfl_xor(first, d, 64));
+            if (first != 0x7fffffff) { bm = first; mine = found == first; }
         }
     }
-    if (sub != 0) return;
-    Rec out = {kNone, kNone, 0.0, 0.0};
-    int ks = 0, ch = 0;
-    if (best < kNone) {
-        if (bm == 0) {
-            *t.status = kInternalError;
-        } else {
-            const int r = Sp - bs;
-            const long long oa = rec_index(t, bs, fam.fam_base + bm, u, bk);
-            const long long ob = rec_index(t, r, fam.fam_base + fam.units - bm, bk, v);
-            const Rec a = t.rec[oa], b = t.rec[ob];
-            const int ka = t.kstar[oa], kb = t.kstar[ob];
-            out.T = best;
-            out.T1 = a.T1 + b.T1;                                                     // Eq. 1
-            if (a.tmax >= b.tmax) { out.tmax = a.tmax; ks = ka; out.T3 = a.T3 + b.T1; } // Eq. 3
-            else                  { out.tmax = b.tmax; ks = bs + kb; out.T3 = b.T3; }
-            ch = bs | (bk << 10) | (bm << 21);
-        }
-    }
-    const long long o = rec_block(t, Sp, delta, ub, vb) + tl;
-    t.rec[o] = out;
-    t.kstar[o] = ks;
-    t.choice[o] = ch;
+    if (!mine) return;
+    if (best < kNone && bm == 0) *t.status = kInternalError;
+    write_state(t, rec_block(t, Sp, delta, ub, vb) + tl, best < kNone && bm, best, T1, tmax, bs | bk << 10 | bm << 21);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1080,9 +1046,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp,
     const long long out_at = (long long)(level(t, Sp).base + delta) * t.tab_recs + tri_index(ub, vb, t.NB) * 64 + (row << 3) + vcol;
     if (nk <= 0) { // no states here
         if (tid >= C) return;
-        t.rec[out_at] = Rec{kNone, kNone, 0.0, 0.0};
-        t.kstar[out_at] = 0;
-        t.choice[out_at] = 0;
+        write_state(t, out_at, false, kNone, kNone, 0.0, 0);
         return;
     }
     const unsigned tab_bytes = (unsigned)t.tab_recs * (unsigned)sizeof(Rec);
@@ -1113,7 +1077,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp,
     }
     np = imin(np, kSmallPairs);
     wg_sync();
-    double best = kNone;
+    double best = kNone, T1 = kNone, tmax = 0.0;
     unsigned btag = 0xffffffffu; // s << 21 | k << 10 | m
     const int total = np * nk, g = tid >> lgC;
     if (np > 0) {
@@ -1138,7 +1102,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp,
             for (int q = 0; q < kSmallFlight; ++q) {
                 const int s = (int)(tag[q] >> 21), r = Sp - s;
                 const double T = cand_total(ra[q], rb[q], fixed_nb ? -(double)r : 3.0 * r, fixed_nb ? 0.0 : 4.0 * s);
-                if (T < best || (T == best && tag[q] < btag)) { best = T; btag = tag[q]; }
+                if (T < best || (T == best && tag[q] < btag)) { best = T; btag = tag[q]; T1 = ra[q].a.y + rb[q].a.y; tmax = fmax(ra[q].tm, rb[q].tm); }
             }
         }
     }
@@ -1151,24 +1115,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_level_small(Tables t, int Sp,
     if (mine == least) atomicMin(&s_tag[col], btag);
     wg_sync();
     if (mine != least || s_tag[col] != btag || (least == kNoKey && g > 0)) return;
-    Rec out = {kNone, kNone, 0.0, 0.0};
-    int ks = 0, ch = 0;
-    if (best < kNone) {
-        const int s = (int)(btag >> 21), k = (int)((btag >> 10) & 2047u), m = (int)(btag & 1023u), r = Sp - s;
-        const int v = vb * 8 + vcol - t.coff;
-        const long long oa = (long long)(level(t, s).base + fam.fam_base + m) * t.tab_recs + rec_off(u, k, t.coff, t.NB);
-        const long long ob = (long long)(level(t, r).base + fam.fam_base + fam.units - m) * t.tab_recs + rec_off(k, v, t.coff, t.NB);
-        const Rec a = t.rec[oa], b = t.rec[ob];
-        const int ka = t.kstar[oa], kb = t.kstar[ob];
-        out.T = best;
-        out.T1 = a.T1 + b.T1;                                                     // Eq. 1
-        if (a.tmax >= b.tmax) { out.tmax = a.tmax; ks = ka; out.T3 = a.T3 + b.T1; } // Eq. 3
-        else                  { out.tmax = b.tmax; ks = s + kb; out.T3 = b.T3; }
-        ch = s | (k << 10) | (m << 21);
-    }
-    t.rec[out_at] = out;
-    t.kstar[out_at] = ks;
-    t.choice[out_at] = ch;
+    const int s = (int)(btag >> 21), k = (int)((btag >> 10) & 2047u), m = (int)(btag & 1023u);
+    write_state(t, out_at, best < kNone, best, T1, tmax, s | (k << 10) | (m << 21));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1196,17 +1144,13 @@ __global__ void __launch_bounds__(64) k_pick(Tables t, oob_templates out) {
     if (!(best < kNone)) bestS = 0;
     out.feasible[i] = bestS > 0;
     out.S[i] = bestS;
-    long long T = 0, T1 = 0, T2 = 0, T3 = 0, tm = 0;
-    int ks = 0;
+    long long T = 0, T1 = 0, tm = 0;
     if (bestS > 0) {
-        const long long o = rec_index(t, bestS, delta, 0, L);
-        const Rec r = t.rec[o];
-        T = (long long)best; T1 = (long long)r.T1; T3 = (long long)r.T3; tm = (long long)r.tmax;
-        ks = t.kstar[o];
-        const long long nb = t.sh.Nb > 0 ? t.sh.Nb : 4LL * bestS;
-        T2 = (nb - bestS + ks - 1) * tm; // Eq. 2
+        const Rec r = t.rec[rec_index(t, bestS, delta, 0, L)];
+        T = (long long)best; T1 = (long long)r.T1; tm = (long long)r.tmax;
     }
-    out.T[i] = T; out.T1[i] = T1; out.T2[i] = T2; out.T3[i] = T3; out.tmax[i] = tm; out.kstar[i] = ks;
+    out.T[i] = T; out.T1[i] = T1; out.tmax[i] = tm;
+    out.T2[i] = out.T3[i] = out.kstar[i] = 0; // k_backtrack, where there is a pipeline
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1255,9 +1199,13 @@ __device__ void coverage_body(const Tables &t, const oob_templates &out, int len
 // per stage.  Thread p walks from the root to the p-th leaf (left subtree if p is below the left
 // child's stage count, else right with p reduced by it), so the walks of a template run side by
 // side and the kernel takes as long as the deepest leaf, not as the whole tree.
+// The first slowest stage is k*, the stages from it on make T3 (Eq. 3), k* and tmax make T2 (Eq. 2).
 // Workgroup `count` writes the end of the offsets and the coverage.
 __global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out, int len) {
     __shared__ int s_part[128];
+    __shared__ long long s_time[OOB_MAX_L];
+    __shared__ unsigned long long s_T3;
+    __shared__ int s_kstar;
     const int i = blockIdx.x, tid = threadIdx.x, cnt = t.sh.count;
     int part = 0;
     for (int q = tid; q < i && q < cnt; q += blockDim.x) part += out.S[q];
@@ -1274,8 +1222,7 @@ __global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out, 
     for (int p = tid; p < S; p += blockDim.x) {
         int Sq = S, delta = M - 2 + t.sh.n_min + i, u = 0, v = L, pos = p;
         while (Sq > 1) {
-            const long long o = rec_index(t, Sq, delta, u, v);
-            const int ch = t.choice[o];
+            const int ch = (int)t.rec[rec_index(t, Sq, delta, u, v)].choice;
             const int s = ch & 1023, k = (ch >> 10) & 2047, m = (ch >> 21) & 1023;
             const Family fam = family_of(delta, M);
             if (s < 1 || s >= Sq) { *t.status = kInternalError; break; }
@@ -1284,24 +1231,54 @@ __global__ void __launch_bounds__(128) k_backtrack(Tables t, oob_templates out, 
         }
         begin[p] = u;
         gpus[p] = delta < M - 1 ? delta + 1 : M;
+        s_time[p] = (long long)t.rec[rec_index(t, Sq, delta, u, v)].T1;
     }
-    if (tid == 0) begin[S] = L;
+    if (tid == 0) { begin[S] = L; s_kstar = S; s_T3 = 0; }
+    __syncthreads();
+    const long long tmax = out.tmax[i];
+    for (int p = tid; p < S; p += blockDim.x) if (s_time[p] == tmax) { atomicMin(&s_kstar, p); break; } // (a thread's ascend)
+    __syncthreads();
+    const int ks = s_kstar;
+    unsigned long long part3 = 0;
+    for (int p = tid; p < S; p += blockDim.x) if (p >= ks) part3 += (unsigned long long)s_time[p];
+    if (part3) atomicAdd(&s_T3, part3);
+    __syncthreads();
+    if (tid == 0) {
+        if (ks == S) *t.status = kInternalError;
+        const long long nb = t.sh.Nb > 0 ? t.sh.Nb : 4LL * S;
+        out.T3[i] = (long long)s_T3;
+        out.kstar[i] = ks;
+        out.T2[i] = (nb - S + ks - 1) * tmax;
+    }
 }
 
-// Copies one table into dense n x n arrays, n = L-S'+1, entry [u][v - S'] (tests only).
+// Copies one table into dense n x n arrays, n = L-S'+1, entry [u][v - S'] (tests only).  T3 and k* of a state: down the tree to its
+// first slowest stage (Eq. 3).
 __global__ void k_export(Tables t, int S, int delta, double *T, double *T1, double *tmax, double *T3,
                          int *kstar, int *choice) {
     const int n = t.sh.L - S + 1;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= n * n) return;
     const int u = idx / n, j = idx % n, v = j + S;
-    Rec r = {kNone, kNone, 0.0, 0.0};
-    int ks = 0, ch = 0;
-    if (j >= u) {
-        const long long o = rec_index(t, S, delta, u, v);
-        r = t.rec[o]; ks = t.kstar[o]; ch = t.choice[o];
+    Rec r = {kNone, kNone, 0.0, 0};
+    if (j >= u) r = t.rec[rec_index(t, S, delta, u, v)];
+    double after = 0.0; // T3
+    int ks = 0;
+    T[idx] = r.T; T1[idx] = r.T1; tmax[idx] = r.tmax; choice[idx] = (int)r.choice;
+    if (r.T < kNone) {
+        int Sq = S, d = delta, a = u, b = v;
+        Rec x = r;
+        while (Sq > 1) {
+            const int s = (int)x.choice & 1023, k = ((int)x.choice >> 10) & 2047, m = ((int)x.choice >> 21) & 1023;
+            const Family fam = family_of(d, t.sh.M);
+            if (s < 1 || s >= Sq) break; // (never: a state's split has stages on both sides)
+            const Rec left = t.rec[rec_index(t, s, fam.fam_base + m, a, k)], right = t.rec[rec_index(t, Sq - s, fam.fam_base + fam.units - m, k, b)];
+            if (left.tmax >= right.tmax) { after += right.T1; Sq = s; d = fam.fam_base + m; b = k; x = left; }
+            else { ks += s; Sq -= s; d = fam.fam_base + fam.units - m; a = k; x = right; }
+        }
+        after += x.T1;
     }
-    T[idx] = r.T; T1[idx] = r.T1; tmax[idx] = r.tmax; T3[idx] = r.T3; kstar[idx] = ks; choice[idx] = ch;
+    T3[idx] = after; kstar[idx] = ks;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1333,7 +1310,7 @@ long long part_slots(int L, int M, int n_max, int Nb) {
 }
 
 struct Carve {
-    size_t rec, kstar, choice, partT, partK, flags, seg_tab, total;
+    size_t rec, partT, partK, flags, seg_tab, total;
     long long recs, slots;
 };
 // Byte offsets of the workspace arrays, sized for the handle's maxima.
@@ -1345,8 +1322,6 @@ Carve carve(int L, int nodes, int M) {
     const int Smax = smax_of(L, nodes, M, 0);
     size_t o = 0;
     c.rec = o;     o = align_up(o + sizeof(Rec) * E);
-    c.kstar = o;   o = align_up(o + sizeof(int) * E);
-    c.choice = o;  o = align_up(o + sizeof(int) * E);
     // two buffers of minima: consecutive levels are evaluated side by side (see oob_plan_templates)
     c.partT = o;   o = align_up(o + 2 * sizeof(double) * (size_t)c.slots * 64);
     c.partK = o;   o = align_up(o + sizeof(int) * (size_t)c.slots * 64); // plain kernel only: one stream
@@ -1684,8 +1659,6 @@ static Tables make_tables(const oob_plan *h, int lane, const Shape &sh, int *sta
     t.tab_recs = tri_blocks(t.NB) * 64;
     t.inv_M = inverse_of(sh.M);
     t.rec = (Rec *)(ws + h->cv.rec);
-    t.kstar = (int *)(ws + h->cv.kstar);
-    t.choice = (int *)(ws + h->cv.choice);
     t.partT = (double *)(ws + h->cv.partT);
     t.key = (unsigned long long *)(ws + h->cv.partT);
     t.partK = (int *)(ws + h->cv.partK);
