@@ -1372,7 +1372,7 @@ constexpr size_t kLdsLimit = 160 * 1024; // gfx950: 160 KB of LDS per workgroup
 constexpr size_t kLdsPrefer = 64 * 1024; // at least two workgroups per compute unit
 
 // Launch shape of k_split for one family of one level.
-struct SplitPlan { int waves, groups, pc, ntab, na, cap, full; size_t lds; }; // (cap, full: k_split_key)
+struct SplitPlan { int waves, groups, pc, ntab, na, cap, full, range; size_t lds; }; // (cap, full, range: k_split_key)
 bool plan_split(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     int t_lo, t_hi;
     target_units(fam, Sp, sh.M, sh.n_max, &t_lo, &t_hi);
@@ -1432,6 +1432,10 @@ static int small_columns(const Shape &sh, int S, long long most) {
     while (lgC > 0 && most > (long long)kSmallSerial * (kSmallThreads >> lgC) && groups << (4 - lgC) <= kSmallGroups) --lgC;
     return lgC;
 }
+// So do levels on one stream of a job that has the GPU to itself, where a state has more than kSel8Range m to look through for some split and
+// eight lanes a state still find a place at once: 61 layers 1 181 -> 1 124 us with it from level 20 on, 1 144 from level 8 on (short ranges); beside the
+// other jobs of a batch or the inner splits of the next level the waves wait for a place instead (batch of 32 jobs 74.8 -> 80 ms).
+constexpr int kSel8Range = 8, kSel8Waves = 8192;
 constexpr int kOverlapFrom = 24000; // thousand candidates of a level: see enqueue_job
 constexpr int kSelLanes = 1; // lanes per state below that
 // Waves of k_split_key on a compute unit in workgroups of w of them, which share the key table.
@@ -1472,6 +1476,7 @@ bool plan_split_key(const Shape &sh, int Sp, int fam, SplitPlan *p) {
     }
     p->na = imin(cnt, kKeyTargets);
     p->full = most ? most + 8 : 1; // streaming side, one block of the stationary side
+    p->range = least;              // most m of a target and split
     // The LDS of a launch is that of its split with the most streaming tables.  Where the splits of a short and a long side keep
     // one workgroup of four waves (or more) off the compute unit, their shorter side streams: as many tables as leave room for it.
     // Headline workload, time of the levels 36-43 (12 -> 16 waves) 775 -> 637 us, 55-61 (8 -> 12) 837 -> 743 us, call 6.70 ->
@@ -1832,6 +1837,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
             have[fam] = plan_split(sh, S, fam, &sp[fam]) && plan_split_key(sh, S, fam, &kp[fam]);
         }
         const bool inner = overlap && S >= ov_lo && S <= ov_hi;
+        const bool many = want_overlap && !inner && have[1] && kp[1].range > kSel8Range && NT * NAall * 8 <= kSel8Waves;
         if (inner) {
             hipStream_t sx = (S & 1) ? lane.aux.odd : lane.aux.even;
             OOB_HIP_CHECK(hipStreamWaitEvent(sx, lane.ev_level[2 * (S - 2)], 0)); // select of level S'-2
@@ -1854,7 +1860,7 @@ static int enqueue_job(oob_plan *h, int ln, bool want_overlap, const oob_profile
         if (inner) OOB_HIP_CHECK(hipStreamWaitEvent(st, lane.ev_level[2 * S + 1], 0));
         if (force_plain) hipLaunchKernelGGL(k_select, dim3(NT, NAall), dim3(64), 0, st, tl, S, NT, NAall);
         else if (fuse) hipLaunchKernelGGL((k_select_key<8, true>), dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
-        else if (S >= h->opt_select8_from) hipLaunchKernelGGL((k_select_key<8, false>), dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
+        else if (S >= h->opt_select8_from || many) hipLaunchKernelGGL((k_select_key<8, false>), dim3(NT, NAall, 8), dim3(64), 0, st, tl, S, NT, NAall);
         else hipLaunchKernelGGL((k_select_key<kSelLanes, false>), dim3(NT, NAall, kSelLanes), dim3(64), 0, st, tl, S, NT, NAall);
         if (overlap && S + 2 >= ov_lo && S + 2 <= ov_hi) OOB_HIP_CHECK(hipEventRecord(lane.ev_level[2 * S], st));
     }
