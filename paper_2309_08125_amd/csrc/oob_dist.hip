@@ -25,19 +25,19 @@
 // decides from the templates one by one whether there is an exchange (solve<FOLLOW = false>), finishes the others and leaves a mark, and a second
 // one takes the marked plans 64 side by side.
 //
-// What bounds it: the vector ALUs (3 000 instructions a wave for 57 templates in the first launch, two fifths of them for reading the
-// counts and writing the distribution) and, where few plans have a path, the chain of its longest one.  Plans of up to 57 templates, 512
+// What bounds it: the vector ALUs (2 650 instructions a wave for 57 templates in the first launch, 97 us of its 150 for 1 343 380 plans), next to
+// them the memory (92 us for the same loads and stores alone) and, where few plans have a path, the chain of its longest one.  Plans of up to 57 templates, 512
 // microbatches, us a call: every plan by one lane in LDS at its place; with its path followed in stretches of 1 024 plans by one wave
-// each, ties of two costs by the form in LDS; here:
-//     1 343 380 plans, times that grow      521     261    228
-//                      that fall as 1 / n   506   1 115    430
-//                      all equal            837   4 317    510
-//                      5 .. 40 times 10^8 2 031   9 073  1 840
-//                      random, 1 to 4       695     557    380
-//       200 000 plans, times that grow      147      84     82
-//                      all equal            260   4 128    124
-//        10 251 plans, times that grow       41      27     26
-//       400 000 plans of 11..16 templates   888   8 066    500
+// each, ties of two costs by the form in LDS; by marks, with the counts and the distribution two bytes a lane, sums in 128-bit integers and
+// microbatches moved one by one; here:
+//     1 343 380 plans, times that grow      521     261    221    200
+//                      that fall as 1 / n   506   1 115    433    409
+//                      all equal            837   4 317    514    368
+//       200 000 plans, times that grow      147      84     70     62
+//                      all equal            260   4 128    114     84
+//        10 251 plans, times that grow       41      27     30     27
+//                      all equal                             40     25
+//       300 000 plans of 1 000 templates                  1 214    672
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -56,9 +56,10 @@ constexpr int kFew = 10;   // templates that have registers in the first launch 
 constexpr int kFirstThreads = 256;
 constexpr int kScan = 4, kSpanBits = 10; // marks in flight of a wave of the second launch; plans whose marks it looks through, at most
 // Up to kOnce plans one launch does it all, two waves a SIMD: what counts there is how long the wave with the longest path takes, and
-// kOnce is what the GPU holds at once (120 000 plans 54 us, in two launches 75; three waves a SIMD, which spill, 57).  Up to kFollow plans the
+// kOnce is what the GPU holds at once (120 000 plans 54 us, in two launches 75; three waves a SIMD, which spill, 57; all three before the counts went
+// through memory four rows at a time, now 44).  Up to kFollow plans the
 // first launch, at three waves a SIMD, follows the paths as well, as many as the GPU holds, and leaves the plans of many templates (160 000
-// plans 65 us, with the paths in the second launch 76; 200 000 plans 92 and 81).
+// plans 65 us, with the paths in the second launch 76; 200 000 plans 92 and 81; now 150 000 plans 48 and 200 000 plans 62).
 constexpr long long kOnce = 2048 * 64, kFollow = 3072 * 64;
 // Waves of the second launch, at most a wave for every 64 plans.  3 072, 5 120, 7 168, 10 240, for 1 343 380 plans: times that grow 239, 234, 232, 233
 // us, times that fall as 1 / nodes 655, 549, 473, 434 us: the waves without a marked plan end while the others work.
@@ -105,17 +106,68 @@ __device__ __forceinline__ int list_templates(const Args &a, long long i, unsign
     return t;
 }
 
+// A wave's 64 plans i0 .. i0 + 63, all of them below `count`, go through memory together: lane 16 r + g has the plans 4 g .. 4 g + 3 of the
+// rows j = r modulo 4, so one load or store of eight bytes a lane moves four whole rows of the wave (the element's alignment, two bytes, is all that
+// is asked of the arrays), and `area`, kRows rows of 64 words of the wave, turns them into a plan to a lane and back.  A row at a time, a lane its
+// plan's two bytes, is twelve instructions a row for the counts and eighteen for the distribution, here four and seven; 1 343 380 plans of 57
+// templates take 12 us less.  The same loads and stores without the plans' solution take 92 us there; stores that pass by the caches
+// (non-temporal) cost 65 us more, since a wave's part of a row is one line of 128 bytes.
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2), may_alias));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4), may_alias));
+constexpr int kRows = 8, kLoad = 16, kStage = 8; // loads in flight; of them in `area` at a time, 4 kStage rows of 16-bit counts: 2 kRows of words
+
+// What the lanes of a wave have put into LDS so far is there for all of them.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// As list_templates, for a wave; row kT of jx is overwritten.
+__device__ __forceinline__ int list_wave(const Args &a, long long i0, unsigned *jx, unsigned *area, int *pipelines) {
+    const int lane = threadIdx.x & (kLanes - 1), r = lane >> 4;
+    const unsigned short *from = a.x + r * a.capacity + i0 + 4 * (lane & 15);
+    int t = 0, xs = 0;
+    for (int j0 = 0; j0 < a.p; j0 += 4 * kLoad) {
+        u16x4 c[kLoad];
+#pragma unroll
+        for (int q = 0; q < kLoad; ++q) {
+            c[q] = (u16x4)0;
+            if (j0 + 4 * q + r < a.p) c[q] = *(const u16x4 *)(from + (j0 + 4 * q) * a.capacity);
+        }
+#pragma unroll
+        for (int s = 0; s < kLoad; s += kStage) {
+            unsigned long long any[kStage]; // 16 bits a row: who has plans with the template
+#pragma unroll
+            for (int q = 0; q < kStage; ++q) {
+                const u32x2 w = __builtin_bit_cast(u32x2, c[s + q]);
+                ((u32x2 *)area)[q * kLanes + lane] = w;
+                any[q] = __ballot((w.x | w.y) != 0);
+            }
+            wave_sync();
+#pragma unroll
+            for (int q = 0; q < kStage; ++q)
+#pragma unroll
+                for (int row = 0; row < 4; ++row) {
+                    if (!(any[q] >> 16 * row & 0xffff)) continue; // uniform
+                    const unsigned n = ((const unsigned short *)area)[(4 * q + row) * kLanes + lane];
+                    jx[std::min(t, kT) * kLanes] = (unsigned)(j0 + 4 * (s + q) + row) | n << 16; // overwritten by the next one if there are none
+                    xs += (int)n;
+                    t += n != 0;
+                }
+            wave_sync();
+        }
+    }
+    *pipelines = xs;
+    return t;
+}
+
 // A time beyond 2^53 is rounded, and refused all the same.
 __device__ __forceinline__ bool time_is_valid(double T) { return T >= 1 && T <= (double)OOB_DIST_MAX_T; }
 
 __device__ __forceinline__ void refuse(const Args &a, long long i, int st) {
     a.status[i] = st;
     a.vx[2 * i] = 0; a.vx[2 * i + 1] = 0; a.slowest[i] = 0;
-    if (a.base)
-        for (int j = 0; j < a.p; ++j) {
-            a.base[(long long)j * a.capacity + i] = 0;
-            a.extra[(long long)j * a.capacity + i] = 0;
-        }
 }
 
 // A plan of more than kT templates, the first of them listed: what the first kT or the next one are refused for.
@@ -125,10 +177,11 @@ __device__ __forceinline__ void refuse_many(const Args &a, const double *s_tT, c
     refuse(a, i, ok ? OOB_DIST_TOO_MANY_TEMPLATES : OOB_DIST_BAD_TIME);
 }
 
-// The distribution `ne` of a plan of t templates, every entry of base and extra written once; or, with `open`, its list in rows 0 .. t-1.
+// The distribution `ne` of a plan of t templates (none: it was refused), every entry of base and extra written once; or, with `open`, its list
+// in rows 0 .. t-1.
 __device__ __forceinline__ void write_rows(const Args &a, long long i, const unsigned *jx, const unsigned *ne, int t, bool open) {
     int k = 0;
-    unsigned next = open ? 0 : jx[0] & 0xffff, have = open ? jx[0] : ne[0];
+    unsigned next = t == 0 ? a.p : open ? 0 : jx[0] & 0xffff, have = open ? jx[0] : ne[0];
     for (int j = 0; j < a.p; ++j) {
         unsigned w = 0;
         if ((unsigned)j == next) {
@@ -143,11 +196,57 @@ __device__ __forceinline__ void write_rows(const Args &a, long long i, const uns
     }
 }
 
+// As write_rows, for a wave.
+__device__ __forceinline__ void write_wave(const Args &a, long long i0, const unsigned *jx, const unsigned *ne, int t, bool open, unsigned *area) {
+    const int lane = threadIdx.x & (kLanes - 1), r = lane >> 4;
+    const long long at = r * a.capacity + i0 + 4 * (lane & 15);
+    unsigned short *base = a.base + at, *extra = a.extra + at;
+    u32x4 *const wide = (u32x4 *)area;
+    int k = 0, next = t == 0 ? a.p : open ? 0 : (int)(jx[0] & 0xffff);
+    unsigned have = open ? jx[0] : ne[0];
+    for (int j0 = 0; j0 < a.p; j0 += kRows) {
+#pragma unroll
+        for (int h = 0; h < kRows / 4; ++h) wide[h * kLanes + lane] = (u32x4)0;
+        wave_sync();
+        while (next < std::min(j0 + kRows, a.p)) {
+            area[(next - j0) * kLanes + lane] = have;
+            ++k;
+            const unsigned row = k < t ? jx[k * kLanes] : (unsigned)a.p;
+            next = open && k < t ? k : (int)(row & 0xffff);
+            have = open ? row : k < t ? ne[k * kLanes] : 0;
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < kRows / 4; ++h) {
+            const u32x4 w = wide[h * kLanes + lane];
+            if (j0 + 4 * h + r < a.p) {
+                u32x2 lo, hi;
+                lo.x = __builtin_amdgcn_perm(w.y, w.x, 0x05040100); hi.x = __builtin_amdgcn_perm(w.y, w.x, 0x07060302);
+                lo.y = __builtin_amdgcn_perm(w.w, w.z, 0x05040100); hi.y = __builtin_amdgcn_perm(w.w, w.z, 0x07060302);
+                *(u16x4 *)base = __builtin_bit_cast(u16x4, lo);
+                *(u16x4 *)extra = __builtin_bit_cast(u16x4, hi);
+            }
+            base += 4 * a.capacity;
+            extra += 4 * a.capacity;
+        }
+        wave_sync();
+    }
+}
+
 // What one microbatch less for a fullest pipeline of n, or more for an emptiest one, costs a template at the level m2 / 2: the same double
 // wherever it is formed (nothing is left to contraction).
 __device__ __forceinline__ double cost_of_one(double T, int n, double m2, bool remove) {
     const double q = T * m2;
     return __builtin_fma(T * T, (double)(remove ? 1 - 2 * n : 2 * n + 1), remove ? q : -q);
+}
+
+// v >= 0, rounded to nearest: the highest 64 bits and whether anything is below them.
+__device__ __forceinline__ double nearest(i128 v) {
+    const unsigned long long hi = (unsigned long long)(v >> 64), lo = (unsigned long long)v;
+    const int up = hi ? __clzll((long long)hi) : 64;
+    unsigned long long top = lo;
+    if (up < 64) top = (unsigned long long)(v >> (64 - up)) | (unsigned long long)(lo << up != 0);
+    return ldexp((double)top, 64 - up);
 }
 
 // The template that one microbatch more or less costs least, the first of equals, among those whose cost in doubles is at most
@@ -185,45 +284,52 @@ __device__ __forceinline__ int exact_pick(const double *s_tT, const unsigned *jx
 // of the stretch's middle at both ends of the stretch, the path has no exchange on the stretch (A + B <= 0 is what makes one pay) and is that
 // allocation, or with twins (templates of the same time), which share their microbatches out in an order that hangs on the level, the
 // allocation of the lower end.  Otherwise, and with twins, FOLLOW = true goes on from the lower end, and FOLLOW = false leaves the ends of
-// the stretch in vx and returns false (a second allocation in the same loop takes 40 registers more than it has).
-// mu, mu_hi: the ends of a stretch that is known (mu_hi = -1: it is not).  from_list: base and extra hold the plan's list in rows 0 .. t-1.
+// the stretch in vx (a second allocation in the same loop takes 40 registers more than it has).
+// mu, mu_hi: the ends of a stretch that is known (mu_hi = -1: it is not).  base and extra are the caller's.
+enum { kRefused, kSolved, kOpen };
 template <int K, bool FOLLOW>
-__device__ __forceinline__ bool solve(const Args &a, const double *s_tT, const unsigned *jx, unsigned *best_ne, unsigned *ne, long long i, int t,
-                                      int xs, long long mu, long long mu_hi, bool from_list) {
-    double T[K];
+__device__ __forceinline__ int solve(const Args &a, const double *s_tT, const unsigned *jx, unsigned *best_ne, unsigned *ne, long long i, int t,
+                                     int xs, long long mu, long long mu_hi) {
+    double T[K], inv[K];
     int x[K], n[K], e[K];
-    auto inverse = [&](int k) { return s_tT[a.p + (jx[k * kLanes] & 0xffff)]; }; // read again where it is used: registers decide how
-                                                                                 // many waves run
+    int again = 0;
+    auto inverse = [&](int k) { return s_tT[a.p + (jx[k * kLanes + again] & 0xffff)]; };
     bool valid = true, twins = false, exact = true, walk = FOLLOW && mu_hi >= 0, open = false;
     double H = 0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        T[k] = 1; x[k] = n[k] = e[k] = 0;
+    for (int k = 0; k < K; ++k) { // no branch: the reads of all templates are in flight together
+        const unsigned w = k < t ? jx[k * kLanes] : 0;
+        T[k] = s_tT[w & 0xffff];
+        inv[k] = s_tT[a.p + (w & 0xffff)];
+        x[k] = (int)(w >> 16);
+        n[k] = e[k] = 0;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
         if (k < t) {
-            const unsigned w = jx[k * kLanes];
-            T[k] = s_tT[w & 0xffff]; x[k] = (int)(w >> 16);
             valid &= time_is_valid(T[k]);
             exact &= T[k] < kExactT;
-            if (!walk) H += (double)x[k] * inverse(k);
+            H += (double)x[k] * inv[k];
 #pragma unroll
             for (int l = 0; l < k; ++l) twins |= T[l] == T[k];
         }
-    }
     if (!valid || t == 0 || xs > a.Q) {
         refuse(a, i, !valid ? OOB_DIST_BAD_TIME : t == 0 ? OOB_DIST_NO_PIPELINE : OOB_DIST_TOO_FEW_MICROBATCHES);
-        return true;
+        return kRefused;
     }
     const double mean = H / xs, L0 = (double)a.Q / H;
     double D = 0;
-    if (!walk) {
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (k < t) {
-                const double r = inverse(k) - mean;
-                D += r * r * x[k];
-            }
-        mu = (long long)(L0 + 0.5);
-    }
+    for (int k = 0; k < K; ++k)
+        if (k < t) {
+            const double r = inv[k] - mean;
+            D += r * r * x[k];
+        }
+    if (!walk) mu = (long long)(L0 + 0.5);
+    // D is formed here, the reciprocals are read again and x converted again where they are used: registers decide how many waves run
+    asm volatile("" : "+v"(D), "+v"(again));
+#pragma unroll
+    for (int k = 0; k < K; ++k) asm volatile("" : "+v"(x[k]));
 
     // every exchange between templates of different times costs at level mu (see above)
     auto settled = [&](double mu) {
@@ -295,15 +401,22 @@ __device__ __forceinline__ bool solve(const Args &a, const double *s_tT, const u
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     if (k != pick) continue;
-                    bool next; // the template's next pipeline starts over: another cost
-                    if (remove) { // a fullest pipeline gives one
-                        next = e[k] == 1 || x[k] == 1;
-                        if (e[k] > 0) --e[k];
-                        else { --n[k]; e[k] = x[k] - 1; }
-                    } else {      // an emptiest one takes one
-                        next = e[k] + 1 == x[k];
+                    // its pipelines that are alike cost alike: all of them, as far as there are microbatches to move, in one step (one by one
+                    // 3 500 cycles more of a wave's 11 300)
+                    int move;
+                    bool next; // the template's pipelines start over: another cost
+                    if (remove) { // the fullest ones give one each
+                        if (e[k] == 0) { --n[k]; e[k] = x[k]; }
+                        move = std::min(tot - a.Q, e[k]);
+                        e[k] -= move;
+                        next = e[k] == 0;
+                        tot -= move;
+                    } else {      // the emptiest ones take one each
+                        move = std::min(a.Q - tot, x[k] - e[k]);
+                        e[k] += move;
+                        next = e[k] == x[k];
                         if (next) { ++n[k]; e[k] = 0; }
-                        else ++e[k];
+                        tot += move;
                     }
                     if (next) { // formed anew: sums of steps would add up their roundings
                         double Tk = T[k];
@@ -312,22 +425,35 @@ __device__ __forceinline__ bool solve(const Args &a, const double *s_tT, const u
                         most = fmax(most, 4.0 * kEps * (Tk * (2.0 * (double)mu) + Tk * Tk * (2 * n[k] + 1)));
                     }
                 }
-                tot += remove ? -1 : 1;
                 if (tot == a.Q) break;
             }
         }
-        S1 = 0; S2 = 0;
+        {
+            // S1 = sum_i N_i T_i and S2 = sum_i (N_i T_i)^2, exactly: all of it is integers in doubles.  sum_i N_i = Q < 2^16, so S1 < 2^51, w = sum N_i^2 of
+            // a template and their sum are at most 2^32 and S2 at most 2^102.  A product and what its rounding left out are two instructions, a sum and
+            // what its rounding left out six; a part left out of T^2 is below 2^16, of T^2 w or of a sum at most 2^48, so that all of
+            // them together, at most 16 templates, come to 2^53 at most.  In 128-bit integers a template takes 60 instructions, a third of them
+            // products at a quarter of the rate, here 25.
+#pragma clang fp contract(off)
+            double sum = 0, rest = 0, s1 = 0;
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (k < t) {
-                const long long Tk = (long long)T[k];
-                const unsigned long long lo = (unsigned long long)n[k] * n[k], hi = (unsigned long long)(n[k] + 1) * (n[k] + 1);
-                S1 += Tk * ((long long)n[k] * x[k] + e[k]);
-                S2 += (i128)Tk * Tk * (long long)(lo * (x[k] - e[k]) + hi * e[k]);
-            }
+            for (int k = 0; k < K; ++k)
+                if (k < t) {
+                    const double N = (double)n[k], E = (double)e[k], X = (double)x[k];
+                    const double w = __builtin_fma(N * N, X, __builtin_fma(2.0, N, 1.0) * E);
+                    s1 = __builtin_fma(T[k], __builtin_fma(N, X, E), s1);
+                    const double sq = T[k] * T[k], v = sq * w, to = sum + v, part = to - sum;
+                    rest += __builtin_fma(__builtin_fma(T[k], T[k], -sq), w, __builtin_fma(sq, w, -v));
+                    rest += (sum - (to - part)) + (v - part);
+                    sum = to;
+                }
+            const double high = floor(sum * 0x1p-52);
+            S1 = (long long)s1;
+            S2 = ((i128)(long long)high << 52) + (long long)__builtin_fma(-0x1p52, high, sum) + (long long)rest;
+        }
         best = (i128)xs * S2 - (i128)S1 * S1;
         if (walk) break;
-        const double V = (double)best / (double)xs; // sum of squared deviations of a feasible allocation
+        const double V = nearest(best) / (double)xs; // sum of squared deviations of a feasible allocation
         // with twins the distribution met first among equal ones depends on where the path starts: it starts where the
         // cruder bound, sqrt(V), puts it
         const double narrow = twins ? 1.0 : fmin(sqrt(D) / H, 1.0);
@@ -341,9 +467,13 @@ __device__ __forceinline__ bool solve(const Args &a, const double *s_tT, const u
         if constexpr (!FOLLOW) { open = true; break; }
         walk = true;
     }
+    double slow = 0; // a pipeline's time is below 2^51
 #pragma unroll
     for (int k = 0; k < K; ++k)
-        if (k < t) best_ne[k * kLanes] = (unsigned)n[k] | (unsigned)e[k] << 16;
+        if (k < t) {
+            best_ne[k * kLanes] = (unsigned)n[k] | (unsigned)e[k] << 16;
+            slow = fmax(slow, T[k] * (double)(n[k] + (e[k] > 0)));
+        }
     if constexpr (FOLLOW) {
 #pragma unroll
         for (int k = 0; k < K; ++k) // the allocation once more in LDS, for the templates that give
@@ -417,43 +547,31 @@ __device__ __forceinline__ bool solve(const Args &a, const double *s_tT, const u
             const i128 v = (i128)xs * S2 - (i128)S1 * S1;
             if (v < best) {
                 best = v;
-                for (int k = 0; k < t; ++k) best_ne[k * kLanes] = ne[k * kLanes];
+                slow = 0;
+                for (int k = 0; k < t; ++k) {
+                    const unsigned w = ne[k * kLanes];
+                    best_ne[k * kLanes] = w;
+                    slow = fmax(slow, s_tT[jx[k * kLanes] & 0xffff] * (double)((w & 0xffff) + (w >> 16 ? 1 : 0)));
+                }
             }
         }
     }
     if (open) {
         a.vx[2 * i] = (unsigned long long)mu;
         a.vx[2 * i + 1] = (unsigned long long)mu_hi;
-        if (!a.lists) return false;
+        return kOpen;
     }
-    long long slow = 0;
-    for (int k = 0; k < t; ++k) {
-        const unsigned w = best_ne[k * kLanes];
-        const long long time = (long long)((w & 0xffff) + (w >> 16 ? 1 : 0)) * (long long)s_tT[jx[k * kLanes] & 0xffff];
-        slow = time > slow ? time : slow;
-    }
-    if (FOLLOW && from_list) { // the other entries are zeros
-        for (int k = 0; k < t; ++k) a.base[k * a.capacity + i] = a.extra[k * a.capacity + i] = 0;
-        for (int k = 0; k < t; ++k) {
-            const unsigned w = best_ne[k * kLanes];
-            const long long at = (long long)(jx[k * kLanes] & 0xffff) * a.capacity + i;
-            a.base[at] = (unsigned short)w;
-            a.extra[at] = (unsigned short)(w >> 16);
-        }
-    } else if (a.base) {
-        write_rows(a, i, jx, best_ne, t, open);
-    }
-    if (open) return false;
     a.status[i] = OOB_DIST_OK;
     a.vx[2 * i] = (unsigned long long)best;
     a.vx[2 * i + 1] = (unsigned long long)(best >> 64);
-    a.slowest[i] = slow;
-    return true;
+    a.slowest[i] = (long long)slow;
+    return kSolved;
 }
 
-__device__ __forceinline__ void load_times(const Args &a, double *s_tT) { // [p], then [p] reciprocals
+// The times, [p], then [p] reciprocals; first: that of the thread's number.
+__device__ __forceinline__ void load_times(const Args &a, double *s_tT, long long first) {
     for (int j = threadIdx.x; j < a.p; j += blockDim.x) {
-        const double T = (double)a.tT[j]; // exact where it is used (up to 2^35)
+        const double T = (double)(j < (int)blockDim.x ? first : a.tT[j]); // exact where it is used (up to 2^35)
         s_tT[j] = T;
         s_tT[a.p + j] = 1.0 / T;
     }
@@ -466,27 +584,28 @@ __device__ __forceinline__ void load_times(const Args &a, double *s_tT) { // [p]
 // 170 us instead of 85).
 constexpr int kMarked = 1 << 30;
 template <bool FOLLOW> __global__ void __launch_bounds__(kFirstThreads, FOLLOW ? 3 : 4) k_dist_first(Args a) {
-    constexpr int W = (kT + (FOLLOW ? 2 : 1) * kFew) * kLanes;
+    constexpr int W = (kT + kFew + (FOLLOW ? kFew : kRows)) * kLanes;
+    static_assert(kFew >= kRows, "rows of the wave where its allocations were");
     HIP_DYNAMIC_SHARED(double, s_tT)
-    __shared__ unsigned s_words[kFirstThreads / kLanes * W]; // of a wave: lists, best and current allocations
+    __shared__ __attribute__((aligned(16))) unsigned s_words[kFirstThreads / kLanes * W]; // of a wave: lists, best and current allocations
     __shared__ int s_ranks[2];
     if (threadIdx.x < 2) s_ranks[threadIdx.x] = 0;
-    load_times(a, s_tT);
     const long long i = (long long)blockIdx.x * kFirstThreads + threadIdx.x;
-    if (i >= a.count) return;
     const int lane = threadIdx.x & (kLanes - 1);
-    unsigned *const jx = s_words + threadIdx.x / kLanes * W + lane, *const best_ne = jx + kT * kLanes;
-    int xs;
-    const int t = list_templates(a, i, jx, kT, &xs);
-    bool left = false;
-    if (t <= kFew) {
-        left = !solve<kFew, FOLLOW>(a, s_tT, jx, best_ne, best_ne + kFew * kLanes, i, t, xs, 0, -1, false);
-    } else if (t > kT) {
-        refuse_many(a, s_tT, jx, i);
-    } else {
-        left = true;
-        if (a.lists) write_rows(a, i, jx, jx, t, true);
-    }
+    const bool whole = i - lane + kLanes <= a.count; // the same for a wave
+    unsigned *const words = s_words + threadIdx.x / kLanes * W, *const area = words + (kT + kFew) * kLanes, *const jx = words + lane, *const best_ne = jx + kT * kLanes;
+    int xs = 0, t = 0, got = kRefused;
+    const long long first = threadIdx.x < a.p ? a.tT[threadIdx.x] : 0; // on its way while the templates are listed
+    if (whole) t = list_wave(a, i - lane, jx, words + (kT + 1) * kLanes, &xs);
+    else if (i < a.count) t = list_templates(a, i, jx, kT, &xs);
+    load_times(a, s_tT, first);
+    if (i >= a.count) return;
+    if (t <= kFew) got = solve<kFew, FOLLOW>(a, s_tT, jx, best_ne, area + lane, i, t, xs, 0, -1);
+    else if (t > kT) refuse_many(a, s_tT, jx, i);
+    else got = kOpen;
+    const bool left = got == kOpen;
+    if (a.lists && whole) write_wave(a, i - lane, jx, left ? jx : best_ne, got == kRefused ? 0 : t, left, area);
+    else if (a.base && (a.lists || !left)) write_rows(a, i, jx, left ? jx : best_ne, got == kRefused ? 0 : t, left);
 #pragma unroll
     for (int kind = 0; kind < 2; ++kind) { // a wave's places in one step
         const bool mine = left && (t > kFew) == kind;
@@ -502,18 +621,22 @@ template <bool FOLLOW> __global__ void __launch_bounds__(kFirstThreads, FOLLOW ?
 __global__ void __launch_bounds__(kLanes, 2) k_dist_once(Args a) {
     constexpr int W = kT * kLanes;
     HIP_DYNAMIC_SHARED(double, s_tT)
-    __shared__ unsigned s_words[3 * W]; // lists, best and current allocations
-    load_times(a, s_tT);
+    __shared__ __attribute__((aligned(16))) unsigned s_words[3 * W]; // lists, best and current allocations
     const int lane = threadIdx.x;
     const long long i = (long long)blockIdx.x * kLanes + lane;
     unsigned *const jx = s_words + lane;
-    int xs = 0, t = 0;
-    if (i < a.count) {
-        t = list_templates(a, i, jx, kT, &xs);
-        if (t > kT) refuse_many(a, s_tT, jx, i);
-        else if (t <= kFew) solve<kFew, true>(a, s_tT, jx, jx + W, jx + 2 * W, i, t, xs, 0, -1, false);
-    }
-    if (t > kFew && t <= kT) solve<kT, true>(a, s_tT, jx, jx + W, jx + 2 * W, i, t, xs, 0, -1, false);
+    const bool whole = i - lane + kLanes <= a.count;
+    int xs = 0, t = 0, got = kRefused;
+    const long long first = lane < a.p ? a.tT[lane] : 0; // on its way while the templates are listed
+    if (whole) t = list_wave(a, i - lane, jx, s_words + 2 * W, &xs);
+    else if (i < a.count) t = list_templates(a, i, jx, kT, &xs);
+    load_times(a, s_tT, first);
+    if (i >= a.count) return;
+    if (t > kT) refuse_many(a, s_tT, jx, i);
+    else if (t <= kFew) got = solve<kFew, true>(a, s_tT, jx, jx + W, jx + 2 * W, i, t, xs, 0, -1);
+    if (t > kFew && t <= kT) got = solve<kT, true>(a, s_tT, jx, jx + W, jx + 2 * W, i, t, xs, 0, -1);
+    if (a.base && whole) write_wave(a, i - lane, jx, jx + W, got == kRefused ? 0 : t, false, s_words + 2 * W);
+    else if (a.base) write_rows(a, i, jx, jx + W, got == kRefused ? 0 : t, false);
 }
 
 // The list of t <= K templates that the first launch left for plan i, read where it is, or from the counts.  Returns the pipelines.
@@ -534,6 +657,24 @@ template <int K> __device__ __forceinline__ int listed(const Args &a, long long 
     return xs;
 }
 
+// A marked plan whose list has been read: solved, its distribution written.  From a list the entries that hold none of it are zeros.
+template <int K>
+__device__ __forceinline__ void solve_listed(const Args &a, const double *s_tT, const unsigned *jx, unsigned *best_ne, unsigned *ne, long long i, int t,
+                                             int xs, long long mu, long long mu_hi) {
+    const int got = solve<K, true>(a, s_tT, jx, best_ne, ne, i, t, xs, mu, mu_hi);
+    if (a.lists && got != kRefused) {
+        for (int k = 0; k < t; ++k) a.base[k * a.capacity + i] = a.extra[k * a.capacity + i] = 0;
+        for (int k = 0; k < t; ++k) {
+            const unsigned w = best_ne[k * kLanes];
+            const long long at = (long long)(jx[k * kLanes] & 0xffff) * a.capacity + i;
+            a.base[at] = (unsigned short)w;
+            a.extra[at] = (unsigned short)(w >> 16);
+        }
+    } else if (a.base) {
+        write_rows(a, i, jx, best_ne, got == kRefused ? 0 : t, false);
+    }
+}
+
 // The second launch: the marked ones of `span` consecutive plans, side by side, those of few templates and then the others.  `slices` waves, `spans`
 // workgroups apart, share a span: a wave has the plans whose rank / ranks is its slice modulo `slices`.  Who has a plan depends on its mark
 // alone, and nobody else writes that: the marks of others may be there or gone.
@@ -544,6 +685,7 @@ __global__ void __launch_bounds__(kLanes, 2) k_dist_rest(Args a, int span, int s
     const int lane = threadIdx.x, slice = blockIdx.x / spans, ranks = kLanes * kFirstThreads / span;
     const long long i0 = (long long)(blockIdx.x - slice * spans) * span;
     const unsigned long long below = (1ull << lane) - 1;
+    const long long first = lane < a.p ? a.tT[lane] : 0;
     int few = 0, many = 0;
     for (int o0 = 0; o0 < span; o0 += kLanes * kScan) {
         int st[kScan];
@@ -564,19 +706,19 @@ __global__ void __launch_bounds__(kLanes, 2) k_dist_rest(Args a, int span, int s
         }
     }
     if (few + many == 0) return; // uniform
-    load_times(a, s_tT);
+    load_times(a, s_tT, first);
     unsigned *const jx = s_words + lane, *const best_ne = jx + kT * kLanes, *const ne = best_ne + kT * kLanes;
     for (int q = lane; q < few; q += kLanes) {
         const int w = marked[q], t = w >> kSpanBits;
         const long long i = i0 + (w & ((1 << kSpanBits) - 1));
         const int xs = listed<kFew>(a, i, jx, t);
-        solve<kFew, true>(a, s_tT, jx, best_ne, ne, i, t, xs, (long long)a.vx[2 * i], (long long)a.vx[2 * i + 1], a.lists);
+        solve_listed<kFew>(a, s_tT, jx, best_ne, ne, i, t, xs, (long long)a.vx[2 * i], (long long)a.vx[2 * i + 1]);
     }
     for (int q = lane; q < many; q += kLanes) {
         const int w = marked[span - 1 - q], t = w >> kSpanBits;
         const long long i = i0 + (w & ((1 << kSpanBits) - 1));
         const int xs = listed<kT>(a, i, jx, t);
-        solve<kT, true>(a, s_tT, jx, best_ne, ne, i, t, xs, 0, -1, a.lists);
+        solve_listed<kT>(a, s_tT, jx, best_ne, ne, i, t, xs, 0, -1);
     }
 }
 

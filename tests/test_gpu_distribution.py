@@ -162,6 +162,34 @@ def test_many_plans_in_two_launches(P, Q, distribution):
         assert got[3] is None and got[4] is None
 
 
+@pytest.mark.parametrize("p,count,spare", [(1, 64, 0), (3, 128, 1), (7, 65, 2), (8, 64, 3), (9, 191, 0), (63, 64, 1), (64, 130, 5), (65, 64, 2), (130, 257, 7),
+                                           (65, 131072 + 192, 1), (9, 196608 + 320, 3)])
+def test_plans_read_and_written_by_whole_waves(P, p, count, spare):
+    """A full wave moves its counts and its distribution four rows at a time, the plans of a last one that is not full a row at a time: the
+    same 63 plans (none of them in a full wave) give the same; entries past the plans are left alone.  Row counts around the tile's and rows
+    that start at any multiple of two bytes."""
+    import torch
+
+    rng = np.random.Generator(np.random.PCG64(p * 1000 + count))
+    T = rng.integers(10**6, 3 * 10**6, size=p).tolist()
+    vecs = np.zeros((63, p), dtype=np.int64)
+    for i, v in enumerate(vecs):
+        used = rng.choice(p, size=min(p, [1, 2, 5, 10, 11, 16, 17][i % 7]), replace=False)
+        v[used] = rng.integers(1, 4, size=len(used))
+    vecs[17] = 0
+    want = P.Distributor(vecs, 63, T, 60).solve()
+    pick = rng.integers(0, 63, size=count)
+    x = torch.full((p, count + spare), 9, dtype=torch.int16)
+    x[:, :count] = torch.from_numpy(vecs[pick].T.astype(np.int16))
+    d = P.Distributor(x.to("cuda:0"), count, T, 60)
+    d.base.fill_(77), d.extra.fill_(78)
+    got = d.solve()
+    assert got[1] == [want[1][i] for i in pick]
+    for k in (0, 2, 3, 4):
+        assert np.array_equal(got[k], want[k][pick])
+    assert (d.base[:, count:] == 77).all() and (d.extra[:, count:] == 78).all()
+
+
 def times_of(kind, p, rng):
     if kind == "equal":
         return [2 * 10**9 + 7] * p
