@@ -469,6 +469,24 @@ template <bool SCAN> __global__ void __launch_bounds__(kCountThreads) k_inst_cou
     if (threadIdx.x == 0) *s.narrow = s_max < (1ull << 32) && !keep_wide;
 }
 
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4), aligned(2))); // rows of the output start at any entry
+template <int CTRL> __device__ __forceinline__ unsigned quad(unsigned v) { return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true); }
+// The 16-bit counts of four templates of the lane's vector, those of the first in the lowest bits, for those of template lane / 16 of the four
+// vectors of lanes 4 (lane % 16) ..: turned in a quad, then sixteen lanes a template, so that a store of the wave is four runs of 128 bytes (with the
+// lanes of a template four apart 1 343 380 vectors take 63 us, not 51).
+__device__ __forceinline__ u16x4 transposed(unsigned long long v) {
+    const int lane = threadIdx.x & 63;
+    const unsigned sel = lane & 1 ? 0x03020706u : 0x05040100u;
+    unsigned d0 = (unsigned)v, d1 = (unsigned)(v >> 32);
+    d0 = __builtin_amdgcn_perm(quad<0xB1>(d0), d0, sel); // templates 0 and 1 of a pair of lanes: the even one has 0 of both, the odd one 1
+    d1 = __builtin_amdgcn_perm(quad<0xB1>(d1), d1, sel);
+    const bool up = lane & 2;
+    const unsigned got = quad<0x4E>(up ? d0 : d1);
+    const int from = 4 * (4 * (lane & 15) + (lane >> 4));
+    const unsigned lo = __builtin_amdgcn_ds_bpermute(from, (int)(up ? got : d0)), hi = __builtin_amdgcn_ds_bpermute(from, (int)(up ? d1 : got));
+    return __builtin_bit_cast(u16x4, (unsigned long long)hi << 32 | lo);
+}
+
 // One lane per output vector (grid-stride).  A vector at position rho of the list of (N', q)
 // over the first j sizes has its highest non-zero count at the largest i < j with
 // C(i, N', q) <= rho (the lists over fewer sizes are prefixes of the list over more); it then
@@ -476,22 +494,37 @@ template <bool SCAN> __global__ void __launch_bounds__(kCountThreads) k_inst_cou
 // sizes are visited in groups of kGroup from the top: all lanes take the same trip through
 // the groups, so the kGroup counts of a group are stored by whole waves (128 contiguous bytes
 // per template), and one read of kGroup counts fetches every count a lane must compare with in
-// that group.  C is non-decreasing along a row, so the number of entries <= rho locates i without
-// a search, and a group whose first count exceeds rho holds no pipeline of this vector.
+// that group.  C is non-decreasing along a row, so halving locates i (no indexed registers), and a
+// group whose first count exceeds rho holds no pipeline of this vector.
+//
+// What bounds it: the chain of a vector's pipelines, a read of a row and some 50 instructions each; 1 343 380 vectors take 41 us
+// without the stores and 25 with nothing else.  With the list of N' searched lane by lane, the entries of a row counted, its address
+// multiplied out and two bytes a lane and store 56.5 us, here 51.  Group 0 of all rows in LDS (where most pipelines are): 65; four
+// consecutive vectors a lane, which go their common way once: 76, some lane of a wave parts early.
 template <typename CT> // long long, or unsigned when the counting kernel could narrow the table
 __device__ __forceinline__ void unrank_all(const Spec &s, const long long *offsets, unsigned short *x,
                                            long long capacity, long long total) {
     const int len = s.N_hi - s.N_lo + 1, QQ = s.Q + 1;
+    const unsigned step = (unsigned)QQ * (unsigned)s.R; // entries a node count takes: below 2^19, all below 2^30
     const long long stride = (long long)gridDim.x * blockDim.x;
     const CT *tab = sizeof(CT) == 4 ? (const CT *)s.cnt32 : (const CT *)s.cnt;
     for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += stride) {
-        int lo = 0, hi = len - 1; // last N' whose list starts at or before idx
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (offsets[mid] <= idx) lo = mid; else hi = mid - 1;
+        // Last N' whose list starts at or before idx: 64 lists a read, up to that of the wave's first vector; mostly it is the others' too.
+        const int lane = threadIdx.x & 63;
+        const long long idx0 = idx - lane;
+        const bool whole = idx0 + 64 <= total; // of the wave
+        unsigned short *to = x + ((s.p - 1) / kGroup * kGroup + (lane >> 4)) * capacity + (idx0 + 4 * (lane & 15));
+        int lo = 0;
+        for (int l0 = 0; l0 < len; l0 += 64) {
+            const int l = l0 + (threadIdx.x & 63);
+            const unsigned long long at = __ballot(l < len && offsets[l] <= idx0);
+            if (!at) break;
+            lo = l0 + 63 - __clzll((long long)at);
         }
+        while (lo < len - 1 && offsets[lo + 1] <= idx) ++lo;
         int N = s.N_lo + lo, q = s.Q;
         CT rho = (CT)(idx - offsets[lo]);
+        unsigned at = (unsigned)N * step + (unsigned)q * (unsigned)s.R; // of (N, q) in the table
         // A group can hold a pipeline only if its first count is <= rho.  The first counts of up to
         // eight groups are read in one go (independent reads), so that the many empty groups of the
         // large sizes cost one round trip together instead of one each.
@@ -500,7 +533,7 @@ __device__ __forceinline__ void unrank_all(const Spec &s, const long long *offse
         for (int g = (s.p - 1) / kGroup; g >= 0; --g) {
             const int base = g * kGroup;
             if (g < gcov) {
-                const CT *r0 = tab + ((long long)N * QQ + q) * s.R;
+                const CT *r0 = tab + at;
                 CT f[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) f[i] = r0[(g - i > 0 ? g - i : 0) * kGroup];
@@ -513,29 +546,44 @@ __device__ __forceinline__ void unrank_all(const Spec &s, const long long *offse
             int kcap = s.p - 1 - base < kGroup - 1 ? s.p - 1 - base : kGroup - 1; // sizes base..base+kcap may get a pipeline
             unsigned long long xlo = 0, xhi = 0; // kGroup 16-bit counts
             while (g == gnext) {
-                const CT *row = tab + ((long long)N * QQ + q) * s.R + base;
+                const CT *row = tab + at + base;
                 CT c[kGroup];
 #pragma unroll
                 for (int k = 0; k < kGroup; ++k) c[k] = row[k];
+#pragma unroll
+                for (int k = 0; k < kGroup; ++k) asm volatile("" : "+v"(c[k])); // read whole: not one entry after the choice of the one before
                 gcov = g;              // whatever follows changes (N, q, rho): the groups below are probed again
                 if (c[0] > rho) break; // nothing (more) in this group
-                int m = 0;             // entries <= rho: a prefix of the row
-#pragma unroll
-                for (int k = 0; k < kGroup; ++k) m += c[k] <= rho ? 1 : 0;
-                const int ks = m - 1 < kcap ? m - 1 : kcap;
-                // c[ks] by halving (no indexed registers)
-                const bool b0 = ks & 1, b1 = ks & 2, b2 = ks & 4;
-                const CT c01 = b0 ? c[1] : c[0], c23 = b0 ? c[3] : c[2], c45 = b0 ? c[5] : c[4], c67 = b0 ? c[7] : c[6];
-                const CT c03 = b1 ? c23 : c01, c47 = b1 ? c67 : c45;
-                const CT ck = b2 ? c47 : c03;
+                // The last entry <= rho up to kcap: they are a prefix of the row, so by halving (no indexed registers).
+                const bool b2 = c[4] <= rho && kcap >= 4;
+                int ks = b2 ? 4 : 0;
+                CT ck = b2 ? c[4] : c[0];
+                const CT c26 = b2 ? c[6] : c[2];
+                const bool b1 = c26 <= rho && kcap >= (ks | 2);
+                ks = b1 ? ks | 2 : ks;
+                ck = b1 ? c26 : ck;
+                const CT c15 = b2 ? c[5] : c[1], c37 = b2 ? c[7] : c[3], codd = b1 ? c37 : c15;
+                const bool b0 = codd <= rho && kcap >= (ks | 1);
+                ks = b0 ? ks | 1 : ks;
+                ck = b0 ? codd : ck;
                 const int nk = size_of(s, base + ks); // consecutive sizes: arithmetic; a list: one cached read
                 if (nk > N) break; // cannot happen with a consistent table; keeps the loop finite
                 rho -= ck;
                 N -= nk;
+                at -= __umul24((unsigned)nk, step) + (q > 0 ? (unsigned)s.R : 0u);
                 q = q > 0 ? q - 1 : 0;
                 kcap = ks;
                 const unsigned long long one = 1ull << (16 * (ks & 3));
                 if (b2) xhi += one; else xlo += one;
+            }
+            if (whole) {
+#pragma unroll
+                for (int h = 0; h < kGroup; h += 4) {
+                    const u16x4 w = transposed(h ? xhi : xlo);
+                    if (base + h + (lane >> 4) < s.p) *(u16x4 *)(to + h * capacity) = w;
+                }
+                to -= kGroup * capacity;
+                continue;
             }
             unsigned short *xr = x + (long long)base * capacity + idx; // row `base` of the output, this lane's column
             if (base + kGroup <= s.p) { // whole group: no per-template test

@@ -70,6 +70,23 @@ def test_node_specifications_of_the_planning_workloads(P, n0, n_hi, f):
         assert total == 1343380
 
 
+@pytest.mark.parametrize("p,N_lo,N_hi,f,spare", [(1, 0, 130, 0, 1), (3, 0, 40, 0, 3), (7, 10, 40, 1, 1), (8, 0, 36, 2, 2), (9, 0, 36, 1, 5),
+                                                 (16, 0, 40, 1, 1), (17, 3, 40, 1, 0), (4, 0, 63, 3, 1), (4, 0, 64, 3, 2), (4, 100, 229, 30, 3)])
+def test_rows_written_by_whole_waves(P, p, N_lo, N_hi, f, spare):
+    """Full waves store four rows at a time, the last one row by row; rows that start at any multiple of two bytes, templates around a
+    group's and a store's number, more lists than a wave has lanes, empty lists in front; entries past the total are left alone."""
+    import torch
+
+    inst = P.Instantiator(None, N_lo, N_hi, f, n0=1, p=p)
+    off, st = inst.count()
+    want_off, want = I.instantiations_range(list(range(1, p + 1)), N_lo, N_hi, f)
+    assert st == P.OOB_OK and np.array_equal(off, want_off) and (len(want) > 64 or p == 1)
+    x = torch.full((p, len(want) + spare), 9, dtype=torch.int16, device="cuda:0")
+    inst.enqueue(x, len(want) + spare)
+    got = x.cpu().numpy()
+    assert np.array_equal(got[:, : len(want)].T, want) and (got[:, len(want):] == 9).all()
+
+
 def test_large_cluster_sizes_take_the_table_from_global_memory(P):
     """Two planes of the count table exceed the LDS here: the counting kernel's other path."""
     print("sizes 500,700,900", flush=True)
