@@ -593,7 +593,8 @@ template <bool FOLLOW> __global__ void __launch_bounds__(kFirstThreads, FOLLOW ?
     const long long i = (long long)blockIdx.x * kFirstThreads + threadIdx.x;
     const int lane = threadIdx.x & (kLanes - 1);
     const bool whole = i - lane + kLanes <= a.count; // the same for a wave
-    unsigned *const words = s_words + threadIdx.x / kLanes * W, *const area = words + (kT + kFew) * kLanes, *const jx = words + lane, *const best_ne = jx + kT * kLanes;
+    unsigned *const words = s_words + threadIdx.x / kLanes * W, *const area = words + (kT + kFew) * kLanes;
+    unsigned *const jx = words + lane, *const best_ne = jx + kT * kLanes;
     int xs = 0, t = 0, got = kRefused;
     const long long first = threadIdx.x < a.p ? a.tT[threadIdx.x] : 0; // on its way while the templates are listed
     if (whole) t = list_wave(a, i - lane, jx, words + (kT + 1) * kLanes, &xs);

@@ -1025,8 +1025,9 @@ __global__ void __launch_bounds__(64) k_select_key(Tables t, int Sp, int NT, int
 //
 // What bounds it: the workgroup with the most candidates a lane.  With 32 lanes for every state and the records' places formed from
 // scratch for each candidate (850 cycles each) the slowest workgroup took 23 000 cycles where the others took 10 000, whatever was in
-// flight (8 or 10 candidates a lane: no change); now 13 000 and 10 000, of them 1 100 for the list of pairs, 2 000 for the
-// children of the winner.  26 layers: 9 -> 6 us a level, 232 -> 176 us a call.
+// flight (8 or 10 candidates a lane: no change); then 13 000 and 10 000, of them 1 100 for the list of pairs and 2 000 for a second look
+// at the winner's children, which a state without T3 and k* does not take.  26 layers: 9 -> 6 us a level, 232 -> 176 us a call, without the
+// second look 155.
 // ---------------------------------------------------------------------------------------
 constexpr int kSmallPairs = 1024;  // (s, m) pairs of a device set the kernel has room for
 constexpr int kSmallThreads = 256;
@@ -1421,8 +1422,8 @@ constexpr int kSelect8From = 82, kFuseFrom = 82;
 constexpr int kSmallState = 640, kSmallLevel = 500000;
 // Columns of a workgroup (lgC) of such a level whose widest state has `most` candidates: eight, or fewer as long as a lane then has more
 // than kSmallSerial of them one after the other and the launch no more than kSmallGroups workgroups.  A candidate is some
-// hundred cycles of a wave that is alone on its SIMD, and the workgroup of the widest state with the most of them is what a launch waits for.  26
-// layers, kSmallSerial, kSmallGroups: 4, 2 048 176 us; 4, 1 024 174; 8, 1 024 176; 2, 2 048 182; 4, 4 096 187; eight columns always 232.
+// hundred cycles of a wave that is alone on its SIMD, and the workgroup of the widest state with the most of them is what a launch waits for.  (All
+// with the second look at the winner's children, which is the same for every line.)  26 layers, kSmallSerial, kSmallGroups: 4, 2 048 176 us; 4, 1 024 174; 8, 1 024 176; 2, 2 048 182; 4, 4 096 187; eight columns always 232.
 // 31 jobs of 12 to 98 layers drawn at random, against 4, 2 048 (geometric mean, best, worst): 4, 1 024 1.01, 0.94, 1.05; 8, 2 048 1.03, 0.92, 1.11; 2, 2 048
 // 1.03, 0.95, 1.13; 4, 4 096 1.03, 0.94, 1.25; eight columns always 1.05, 0.93, 1.20.
 constexpr int kSmallSerial = 4, kSmallGroups = 2048;
