@@ -40,8 +40,8 @@ INT64_OPS_PER_CANDIDATE = 30
 # counter reads for one 256 MiB device-to-device copy), and vector-ALU wave-instructions per call
 # (SQ_INSTS_VALU of k_split_key + k_select_key + k_level_small).
 PROFILE_CONFIG4 = {"source": "profiles/k_split_key_config4.md",
-                   "hbm_read_bytes_per_call": 16.15e9, "hbm_written_bytes_per_call": 2.29e9,
-                   "valu_wave_insts_per_call": 2.02e9 + 0.04e9,
+                   "hbm_read_bytes_per_call": 16.16e9, "hbm_written_bytes_per_call": 2.26e9,
+                   "valu_wave_insts_per_call": 2.03e9 + 0.04e9,
                    "kernel_launches_per_call": 268}  # 168 k_split_key + 97 k_select_key + 3 others (kernel trace)
 
 
@@ -138,8 +138,8 @@ def bench_instantiation(P, inp, res, reps=20):
             "roofline": {"bound": "hbm", "achieved": nbytes / t_enum / 1e9, "peak": 8000.0, "unit": "GB/s",
                          "frac": nbytes / t_enum / 8e12,
                          # rocprofv3 --pmc of this kernel on configuration 4's node specification, scaled as
-                         # above: 149 557 KiB written + 694 KiB read per launch (profiles/k_inst_unrank_config4.md)
-                         "traffic": (149557 + 694) * 1024 if (n0, n_hi, inp.f) == (8, 64, 8) else None,
+                         # above: 154 500 KiB written + 981 KiB read per launch (profiles/k_inst_unrank_config4.md)
+                         "traffic": (154500 + 981) * 1024 if (n0, n_hi, inp.f) == (8, 64, 8) else None,
                          "kernel": "k_inst_unrank", "bytes_per_vector": 2 * p}}
 
 
@@ -297,12 +297,12 @@ def bench_distribution(P, inp, res, Q=512, reps=3, oracle_sample=40):
                         f"{Q} microbatches; time per microbatch = T1 of the template",
             "value": total / dt, "unit": "plans/s", "ms": dt * 1e3, "choose_us": t_choose * 1e6,
             "best_plan_for_all_nodes": X[int(best[-1])].nonzero()[0].tolist() if best[-1] >= 0 else None,
-            # bound by instruction issue: 3 613 vector instructions per 64 plans (SQ_INSTS_VALU of both launches
+            # bound by instruction issue: 3 053 vector instructions per 64 plans (SQ_INSTS_VALU of both launches
             # of profiles/k_dist_solve_config4.md, a constant of that profile, not measured here), each 4 cycles
             # on one of 1024 SIMDs; the algorithmic HBM bytes are kept as a secondary figure
-            "roofline": {"bound": "alu", "achieved": total / 64 * 3613 * 64 / dt / 1e12, "peak": PEAK_LANE_OPS / 1e12,
-                         "unit": "T lane-instr/s (32/64-bit integer and fp64)", "frac": total / 64 * 3613 * 64 / dt / PEAK_LANE_OPS,
-                         "traffic": None, "kernel": "k_dist_first, k_dist_rest", "valu_insts_per_wave_from_profile": 3613,
+            "roofline": {"bound": "alu", "achieved": total / 64 * 3053 * 64 / dt / 1e12, "peak": PEAK_LANE_OPS / 1e12,
+                         "unit": "T lane-instr/s (32/64-bit integer and fp64)", "frac": total / 64 * 3053 * 64 / dt / PEAK_LANE_OPS,
+                         "traffic": None, "kernel": "k_dist_first, k_dist_rest", "valu_insts_per_wave_from_profile": 3053,
                          "hbm_algorithmic": {"bytes_per_plan": 6 * p + 28, "GB_per_s": nbytes / dt / 1e9,
                                              "frac_of_hbm_peak": nbytes / dt / 8e12}},
             "cpu_baseline": {"value": cpu, "unit": "plans/s", "cores": 1, "kind": "oracle",

@@ -25,7 +25,7 @@
 // decides from the templates one by one whether there is an exchange (solve<FOLLOW = false>), finishes the others and leaves a mark, and a second
 // one takes the marked plans 64 side by side.
 //
-// What bounds it: the vector ALUs (2 650 instructions a wave for 57 templates in the first launch, 97 us of its 150 for 1 343 380 plans), next to
+// What bounds it: the vector ALUs (2 650 instructions a wave for 57 templates in the first launch, 90 us of its 150 for 1 343 380 plans), next to
 // them the memory (92 us for the same loads and stores alone) and, where few plans have a path, the chain of its longest one.  Plans of up to 57 templates, 512
 // microbatches, us a call: every plan by one lane in LDS at its place; with its path followed in stretches of 1 024 plans by one wave
 // each, ties of two costs by the form in LDS; by marks, with the counts and the distribution two bytes a lane, sums in 128-bit integers and
