@@ -509,19 +509,27 @@ __device__ __forceinline__ void unrank_all(const Spec &s, const long long *offse
     const long long stride = (long long)gridDim.x * blockDim.x;
     const CT *tab = sizeof(CT) == 4 ? (const CT *)s.cnt32 : (const CT *)s.cnt;
     for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += stride) {
-        // Last N' whose list starts at or before idx: 64 lists a read, up to that of the wave's first vector; mostly it is the others' too.
+        // Last N' whose list starts at or before idx.  For the wave's first vector by 64 of the offsets a read, evenly spread over those still
+        // in question (one read up to 64 lists, two up to 4 096); mostly it is the others' too, and the lanes past its end halve what is behind it.
         const int lane = threadIdx.x & 63;
         const long long idx0 = idx - lane;
         const bool whole = idx0 + 64 <= total; // of the wave
         unsigned short *to = x + ((s.p - 1) / kGroup * kGroup + (lane >> 4)) * capacity + (idx0 + 4 * (lane & 15));
         int lo = 0;
-        for (int l0 = 0; l0 < len; l0 += 64) {
-            const int l = l0 + (threadIdx.x & 63);
-            const unsigned long long at = __ballot(l < len && offsets[l] <= idx0);
-            if (!at) break;
-            lo = l0 + 63 - __clzll((long long)at);
+        if (whole) // (a ballot of all lanes)
+            for (int n = len; n > 1;) { // lo .. lo + n - 1
+                const int each = (n + 63) >> 6, l = lane * each;
+                const int k = 63 - __clzll((long long)__ballot(l < n && offsets[lo + l] <= idx0)); // (the first one does)
+                lo += k * each;
+                n = each < n - k * each ? each : n - k * each;
+            }
+        if (lo < len - 1 && offsets[lo + 1] <= idx) {
+            int hi = len - 1;
+            for (++lo; lo < hi;) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (offsets[mid] <= idx) lo = mid; else hi = mid - 1;
+            }
         }
-        while (lo < len - 1 && offsets[lo + 1] <= idx) ++lo;
         int N = s.N_lo + lo, q = s.Q;
         CT rho = (CT)(idx - offsets[lo]);
         unsigned at = (unsigned)N * step + (unsigned)q * (unsigned)s.R; // of (N, q) in the table

@@ -87,6 +87,43 @@ def test_rows_written_by_whole_waves(P, p, N_lo, N_hi, f, spare):
     assert np.array_equal(got[:, : len(want)].T, want) and (got[:, len(want):] == 9).all()
 
 
+@pytest.mark.parametrize("sizes,N_lo,N_hi,f", [([64], 0, 4095, 0), ([64, 128], 0, 4095, 0), ([64, 128, 192], 1, 4095, 1), ([500, 700, 900], 0, 4095, 0),
+                                               ([31, 57], 0, 2047, 1), ([5, 9], 7, 70, 0), ([5, 9], 7, 71, 0), ([1, 2], 100, 100, 0),
+                                               ([1], 0, 4094, 0), ([1, 90], 4031, 4095, 0)])
+def test_many_cluster_sizes_and_gaps_between_their_lists(P, sizes, N_lo, N_hi, f):
+    """Lists of one vector, of none for tens of cluster sizes between two and of more than a wave, from one to 4 096 of them: where a
+    vector's list is found by two reads, and by halving for the lanes behind the wave's first list."""
+    print(sizes, N_lo, N_hi, f, flush=True)
+    assert compare(P, sizes, N_lo, N_hi, f) >= 40
+
+
+def test_gaps_between_the_lists_take_no_walk(P):
+    """63 vectors of up to 63 pipelines, in 4 096 lists of which 63 are not empty, against 64 such vectors in 65 lists: the search for a
+    vector's list grows with the logarithm of their number (1.2 times the time; past one empty list after the other it was 19 times)."""
+    import torch
+
+    def us(sizes, N_hi):
+        inst = P.Instantiator(sizes, 1, N_hi, 0)
+        off, st = inst.count()
+        assert st == P.OOB_OK and off[-1] in (63, 64)
+        x = torch.empty((1, int(off[-1])), dtype=torch.int16, device="cuda:0")
+        best = float("inf")
+        for _ in range(5):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            inst.enqueue(x, int(off[-1]))
+            ev[0].record()
+            for _ in range(20):
+                inst.enqueue(x, int(off[-1]))
+            ev[1].record()
+            torch.cuda.synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) / 20 * 1e3)
+        return best
+
+    sparse, dense = us([64], 4095), us([1], 64)
+    print(f"{sparse:.1f} and {dense:.1f} us", flush=True)
+    assert sparse < 4 * dense
+
+
 def test_large_cluster_sizes_take_the_table_from_global_memory(P):
     """Two planes of the count table exceed the LDS here: the counting kernel's other path."""
     print("sizes 500,700,900", flush=True)
