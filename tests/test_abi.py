@@ -174,3 +174,31 @@ def test_table_layout_and_task_lists_for_every_depth():
     # a workspace sized for a depth serves every smaller depth: sizes grow with every maximum
     sizes = [P.oob_plan_workspace_size(L, 16, 4) for L in range(8, 140)]
     assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+def test_kernels_read_and_write_lds_as_lds(tmp_path):
+    """No kernel has a flat access.  All memory is either LDS or a kernel's argument, so one means that the compiler has lost sight of which
+    (as it does of a pointer into LDS that is subtracted from another), and an access of LDS then goes by the vector memory path: slower by a
+    third where it was in the inner loop of the exact minimum."""
+    import shutil
+    import subprocess
+
+    from paper_2309_08125_amd import build
+
+    lib = shutil.copy(build.LIB, tmp_path / "lib.so")
+    objdump = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+    subprocess.run([objdump, "--offloading", lib], check=True, capture_output=True, cwd=tmp_path)
+    kernels, found = set(), {}
+    for name in sorted(os.listdir(tmp_path)):
+        if not name.endswith("gfx950"):
+            continue
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(tmp_path / name)], check=True, capture_output=True, text=True).stdout
+        where = None
+        for line in text.splitlines():
+            m = re.match(r"[0-9a-f]+ <(\w+)>:", line)
+            if m:
+                where = m[1]
+                kernels.add(where)
+            elif re.match(r"\s+flat_(load|store|atomic)", line):
+                found[where] = found.get(where, 0) + 1
+    assert len(kernels) > 40 and not found, found
