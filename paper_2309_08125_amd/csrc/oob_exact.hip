@@ -1282,12 +1282,18 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     double *WP = e.pool + atP, *WS = WP + sizeP, *G = e.pool + used;
     const bool in_regs = MT && e.ints[2] && imax(bandP, bandS) <= 64 && used <= e.pool_n; // node_tables()
     const unsigned table = in_regs ? 0u : (unsigned)(imax(bandP, bandS) + 1) * row_n;
-    // ---- few nodes, each of many layers: where node_tables() does not serve, tables over (layers covered, GPUs used) are smaller work than a table per
-    // start layer in LDS (nodes against layers per node), and the covers next to the slowest stage are their last rows
-    if (!in_regs) {
+    // ---- few nodes, each of many layers: tables over (layers covered, GPUs used) are smaller work than a table per start layer (nodes against
+    // layers per node), and the covers next to the slowest stage are their last rows.  Against tables in LDS from four layers a node on.  Against
+    // node_tables() from eight on, if bands are so wide that a wave holds one start or two: 64 layers x 8 GPUs, up to 2 nodes 581 -> 354 us (396 with LDS alone);
+    // from bands of 16 on 40 layers x 4 GPUs, 2 nodes 94 -> 115 us; beyond 32 for eight GPUs too 48 layers, 2 nodes 344 -> 394 us; from twelve layers a
+    // node on 52 layers x 8 GPUs, 3 nodes 393 -> 601 us.  Never with one or two GPUs per node, where node_tables() has hardly anything to add up, for a
+    // single node, which has one start a side, or with stage counts, where rows over (GPUs, stages) are longer (34 layers x 8 GPUs, 3 nodes 247 -> 510 us).
+    const int wide = imax(bandP, bandS);
+    const bool by_gpus = !STAGED && M > 2 && nhi > 1 && nhi * 8 <= wide && wide > (M == 8 ? 24 : 32);
+    if (!in_regs || by_gpus) {
         const int nd = imax(cendP, cendS) * M, jd = STAGED ? imin(J, nd + 1) : 1;
         const unsigned need = ((unsigned)lenP + 1 + lenS + 1) * nd * jd; // below 2^29
-        if (nhi * 4 <= imax(bandP, bandS) && need <= e.pool_n) {
+        if (nhi * 4 <= wide && need <= e.pool_n) {
             const int row_n = nd * jd;
             const int second = (lenP + 1) * row_n; // the other side's table
             for (int i = threadIdx.x; i < 2 * row_n; i += blockDim.x) {

@@ -343,6 +343,46 @@ def test_tables_of_a_node_in_registers_and_in_lds(P, shape, ends):
         assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, ends, var)
 
 
+# (layers, GPUs per node, templates, N_b) whose bands are a layer or two off the lines between the tables of a node and those over all GPUs
+@pytest.mark.parametrize("shape", [(26, 8, 1, 2, 40), (28, 8, 1, 3, 0), (35, 4, 1, 2, 50), (36, 4, 2, 4, 0), (43, 4, 1, 5, 45), (34, 8, 1, 4, 34)])
+def test_few_nodes_of_many_layers(P, shape):
+    L, M, n_min, n_max, nb = shape
+    for var in ("plain", "tight", "uniform"):
+        inp = inputs.random_small(47, L, M, n_min, n_max, nb, f=1, t_lo=60, t_hi=99, tight_mem=(var == "tight"), uniform_layers=(var == "uniform"))
+        print("case", shape, var, flush=True)
+        st, got = P.ExactMinimum(inp).run()
+        assert st == P.OOB_OK and got == E.exact_minimum(inp, allow_bound=True), (shape, var)
+
+
+def call_us(exact):
+    """Time of a call, the best of five."""
+    import torch
+
+    best = float("inf")
+    for _ in range(5):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        exact.enqueue()
+        ev[0].record()
+        for _ in range(10):
+            exact.enqueue()
+        ev[1].record()
+        torch.cuda.synchronize()
+        best = min(best, ev[0].elapsed_time(ev[1]) / 10 * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("job", [226, 171])
+def test_two_nodes_of_many_layers_take_little_longer_than_one(P, job):
+    """61 and 66 ragged layers, 8 GPUs per node: where a node may cover most of the model a table per start layer is the longer way for
+    two nodes (1.8 and 1.6 times the time of one node, 1.3 with the tables over all GPUs)."""
+    import dataclasses
+
+    inp = inputs.config(5)[job]
+    one, two = (call_us(P.ExactMinimum(dataclasses.replace(inp, n_min=1, n_max=n, microbatches=0))) for n in (1, 2))
+    print(f"{one:.0f} and {two:.0f} us", flush=True)
+    assert two < 1.7 * one
+
+
 @pytest.mark.parametrize("ends", ["ascending", "mixed"])
 @pytest.mark.parametrize("shape", [(20, 8, 1, 4, 9), (33, 4, 1, 4, 12), (40, 2, 1, 6, 11), (30, 1, 1, 24, 10), (66, 2, 1, 2, 3)])
 def test_tables_of_a_node_with_stage_counts(P, shape, ends):
