@@ -71,6 +71,7 @@ struct Args {
     int L, M, n_min, n_max, Nb, Dmax, Smax, fast, staged, bounds;
     int sums;             // the profile without the ends of the stages (EvalLds)
     int eval_pad, bounds_pad; // rows of the profile in LDS padded (Prof)
+    int regs;                 // k_exact_eval holds the tables of a node in registers where it can
     int nodes;            // min(n_max, L): more nodes than layers make no pipeline
     int top, live;        // last template that can get a minimum (answered(), nodes), number of templates up to it
     long long cap;
@@ -1243,7 +1244,7 @@ __device__ void gpu_row(const Args &a, const Eval &e, int r, int nd, int jd, dou
 
 // The cost of the best pipelines around slowest stage (u, v, d) with n <= nhi nodes, merged into s_best.
 // Returns false (the same in every thread) if the tables do not fit the workgroup's LDS (STAGED only).
-template <bool STAGED, int MT, bool SUM, bool PAD>
+template <bool STAGED, int MT, bool SUM, bool PAD, bool REGS>
 __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int nhi, unsigned long long *s_best) {
     const int L = a.L, M = MT ? MT : a.M, J = STAGED ? a.Smax + 1 : 1, nw = blockDim.x >> 6, W = L + 1;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1280,7 +1281,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     e.GU = e.pool;
     const unsigned atP = (unsigned)((bandP + bandS) * gu), sizeP = (unsigned)(band_size(bandP, lenP) * mult), used = atP + sizeP + (unsigned)(band_size(bandS, lenS) * mult);
     double *WP = e.pool + atP, *WS = WP + sizeP, *G = e.pool + used;
-    const bool in_regs = MT && e.ints[2] && imax(bandP, bandS) <= 64 && used <= e.pool_n; // node_tables()
+    const bool in_regs = REGS && e.ints[2] && imax(bandP, bandS) <= 64 && used <= e.pool_n; // node_tables()
     const unsigned table = in_regs ? 0u : (unsigned)(imax(bandP, bandS) + 1) * row_n;
     // ---- few nodes, each of many layers: tables over (layers covered, GPUs used) are smaller work than a table per start layer (nodes against
     // layers per node), and the covers next to the slowest stage are their last rows.  Against tables in LDS from four layers a node on.  Against
@@ -1319,7 +1320,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     }
     if (used + table > e.pool_n) return false; // (without stage counts they fit: eval_pool())
     // ---- phase 1
-    if constexpr (MT != 0) if (in_regs) {
+    if constexpr (REGS) if (in_regs) {
         const int sP = 64 / imax(bandP, 1), sS = 64 / imax(bandS, 1); // start layers a wave takes at a time
         // (with a single node in all there is only the start at the far end)
         const int nP = nhi == 1 ? lenP > 0 : (lenP + sP - 1) / sP, nS = nhi == 1 ? lenS > 0 : (lenS + sS - 1) / sS, both = 2 * imin(nP, nS);
@@ -1409,7 +1410,7 @@ __device__ bool evaluate(const Args &a, Eval &e, unsigned uvd, double tau, int n
     return true;
 }
 
-template <bool STAGED, int MT, bool SUM, bool PAD>
+template <bool STAGED, int MT, bool SUM, bool PAD, bool REGS>
 __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_exact_eval(Args a, int mode, int lds_doubles, int picks) {
     HIP_DYNAMIC_SHARED(double, s_dyn)
     __shared__ unsigned s_next;
@@ -1430,7 +1431,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     e.ints = s_ints;
     for (int i = tid; i < a.live; i += blockDim.x) s_best[i] = kNoneBits;
     const unsigned total = mode == kRest ? a.head->alive : a.head->ncand;
-    if constexpr (MT != 0) {
+    if constexpr (REGS) {
         if (tid == 0) s_ints[2] = 1; // ends_ascend(), for node_tables()
         wg_sync();
         if (!ends_ascend<PAD>(e.pr, L, M)) s_ints[2] = 0;
@@ -1507,7 +1508,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
                 if (nhi == 0) continue;
             }
         }
-        if (!evaluate<STAGED, MT, SUM, PAD>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
+        if (!evaluate<STAGED, MT, SUM, PAD, REGS>(a, e, a.cuvd[c], a.ctau[c], nhi, s_best)) {
             // (not the first picks: the filter keeps those that matter, so each entry comes here once at most)
             if (STAGED && mode != kFirst && tid == 0) a.over[__hip_atomic_fetch_add(&a.head->over, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = c;
             continue;
@@ -1703,13 +1704,13 @@ extern "C" size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per
     return layout(L, gpus_per_node, n_max, exact_lds(L, gpus_per_node, n_max, n_max, microbatches, true).bytes != 0, mus, true).slots + slots * slot;
 }
 
-template <bool STAGED, int MT, bool SUM, bool PAD>
+template <bool STAGED, int MT, bool SUM, bool PAD, bool REGS = MT != 0>
 static int eval_launch_m(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
     using namespace oob_exact;
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT, SUM, PAD>,
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT, SUM, PAD, REGS>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return OOB_EHIP;
-    hipLaunchKernelGGL((k_exact_eval<STAGED, MT, SUM, PAD>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
+    hipLaunchKernelGGL((k_exact_eval<STAGED, MT, SUM, PAD, REGS>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
     return OOB_OK;
 }
 template <bool STAGED> // a kernel of its own for the usual numbers of GPUs per node, known to the compiler
@@ -1717,6 +1718,9 @@ static int eval_launch(const oob_exact::Args &a, int mode, unsigned grid, int th
     if constexpr (!STAGED) {
         if (a.sums) return eval_launch_m<false, 0, true, false>(a, mode, grid, threads, lds, picks, st);
         if (a.eval_pad) return eval_launch_m<false, 8, false, true>(a, mode, grid, threads, lds, picks, st); // can_pad()
+    }
+    if constexpr (STAGED) {
+        if (!a.regs) return eval_launch_m<true, 8, false, false, false>(a, mode, grid, threads, lds, picks, st); // eval_tables_in_lds()
     }
     switch (a.M) {
     case 1: return eval_launch_m<STAGED, 1, false, false>(a, mode, grid, threads, lds, picks, st);
@@ -1766,6 +1770,7 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
     a.sums = ev.sums;
     a.eval_pad = ev.pad && tri(L) * M > (size_t)kDirectMax; // (short models: 61 us either way, 62 padded, 15 layers)
     a.staged = staged;
+    a.regs = !(counts && eval_tables_in_lds(L, M, n_max, J));
     const size_t ntri = tri(L) * M;
     const int mus = bound_mus(L, M, counts);
     a.bounds_pad = bound_pad(L, M, mus);

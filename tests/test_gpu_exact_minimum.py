@@ -400,6 +400,26 @@ def test_tables_of_a_node_with_stage_counts(P, shape, ends):
         assert st == P.OOB_OK and got == E.exact_minimum_staged(inp), (shape, ends, var)
 
 
+@pytest.mark.parametrize("shape", [(2, 8, 1, 2, 1), (17, 8, 1, 4, 9), (18, 8, 1, 4, 9), (20, 8, 1, 3, 12), (23, 8, 2, 3, 11), (20, 8, 1, 4, 8)])
+def test_stage_counts_with_tables_in_lds_and_in_registers(P, shape):
+    """As many start layers as waves and one more, and few nodes up to the layers whose tables still fit LDS."""
+    L, M, n_min, n_max, nb = shape
+    for var in ("plain", "tight"):
+        inp = inputs.random_small(53, L, M, n_min, n_max, nb, f=1, t_lo=60, t_hi=99, tight_mem=(var == "tight"))
+        print("case", shape, var, flush=True)
+        st, got = P.ExactMinimum(inp, staged=True).run()
+        assert st == P.OOB_OK and got == E.exact_minimum_staged(inp), (shape, var)
+
+
+def test_stage_counts_of_a_short_model_take_little_longer(P):
+    """Ten layers, 8 GPUs per node: where every start layer has a wave and a table in LDS, the tables in registers are the longer way (1.9 times
+    the time of the call without stage counts, 1.4 with those in LDS)."""
+    with_counts = call_us(P.ExactMinimum(inputs.random_small(5, 10, 8, 1, 2, 3, f=1, t_lo=60, t_hi=99), staged=True))
+    without = call_us(P.ExactMinimum(inputs.random_small(5, 10, 8, 1, 2, 10, f=1, t_lo=60, t_hi=99)))
+    print(f"{with_counts:.0f} and {without:.0f} us", flush=True)
+    assert with_counts < 1.6 * without
+
+
 @pytest.mark.parametrize("L,M", [(92, 1), (60, 8), (150, 8), (66, 33)])
 def test_list_of_the_possible_slowest_stages(P, sizes, L, M):
     """Every stage that fits once, with its time, ascending by the leading bits -- lists put in order in LDS and longer ones."""
