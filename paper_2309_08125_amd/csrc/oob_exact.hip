@@ -61,8 +61,7 @@ constexpr long long kDoubleExact = 1ll << 52;
 constexpr double kNone = __builtin_huge_val();
 constexpr unsigned long long kNoneBits = 0x7FF0000000000000ull;
 
-constexpr int kPrepThreads = 1024, kBins = 4096;
-constexpr size_t kPrepStatic = kBins * sizeof(int) + 1024; // its static arrays
+constexpr int kPrepThreads = 1024;
 constexpr int kBoundThreads = 576;   // eight waves for the paths, one for the fewest nodes
 constexpr int kFirst = 1, kRest = 2, kAll = 0;
 
@@ -1707,7 +1706,7 @@ extern "C" size_t oob_exact_staged_workspace_size(int L, int n_max, int gpus_per
 template <bool STAGED, int MT, bool SUM, bool PAD, bool REGS = MT != 0>
 static int eval_launch_m(const oob_exact::Args &a, int mode, unsigned grid, int threads, size_t lds, int picks, hipStream_t st) {
     using namespace oob_exact;
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT, SUM, PAD, REGS>,
+    if (beyond_default(lds, kLdsStatic) && hipFuncSetAttribute((const void *)k_exact_eval<STAGED, MT, SUM, PAD, REGS>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return OOB_EHIP;
     hipLaunchKernelGGL((k_exact_eval<STAGED, MT, SUM, PAD, REGS>), dim3(grid), dim3(threads), lds, st, a, mode, (int)(lds / 8), picks);
@@ -1734,7 +1733,7 @@ static int eval_launch(const oob_exact::Args &a, int mode, unsigned grid, int th
 template <int MT, bool PAD, bool MUS>
 static int bounds_launch_m(const oob_exact::Args &a, int mus, size_t lds, hipStream_t st) {
     using namespace oob_exact;
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)k_exact_bounds<MT, PAD, MUS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (beyond_default(lds, kLdsStatic) && hipFuncSetAttribute((const void *)k_exact_bounds<MT, PAD, MUS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                (int)lds) != hipSuccess)
         return OOB_EHIP;
     const unsigned nb = (unsigned)((tri(a.L) * a.M + bucket_least(a.nk) - 1) / bucket_least(a.nk));
@@ -1794,14 +1793,11 @@ static int exact_launch(const oob_profile *profile, int L, int n_min, int n_max,
         if (slots > (size_t)kFlatSlots) slots = kFlatSlots;
     } else if (workspace_bytes < y.slots) return OOB_ECAPACITY;
     a.limit = general ? kInf : kDoubleExact;
-    size_t prep = 8 * ((size_t)(L + 1) + (a.fast ? (size_t)(L + 1) * M : 0)) + ((size_t)(L + 1) * M + 3) / 4 * 4;
-    const size_t left = kLdsLimit - kPrepStatic - prep; // to order the list in
-    const int room = a.fast ? (int)(4 * ntri < left ? ntri : left / 4) : 0;
-    prep += 4 * (size_t)room;
-    if (prep > 48 * 1024 && hipFuncSetAttribute((const void *)k_exact_prep, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                (int)prep) != hipSuccess)
+    const PrepLds prep = prep_lds(L, M, a.fast);
+    if (beyond_default(prep.bytes, kPrepStatic) && hipFuncSetAttribute((const void *)k_exact_prep, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                                       (int)prep.bytes) != hipSuccess)
         return OOB_EHIP;
-    hipLaunchKernelGGL(k_exact_prep, dim3(1), dim3(kPrepThreads), prep, st, a, room);
+    hipLaunchKernelGGL(k_exact_prep, dim3(1), dim3(kPrepThreads), prep.bytes, st, a, prep.room);
     int rc = OOB_OK;
     if (a.fast) {
         const int threads = eval_threads(L, M, counts);

@@ -23,6 +23,10 @@ OOB_HD inline int quot(int i, unsigned recip_M) { return (int)((unsigned)i * rec
 
 constexpr size_t kLdsLimit = 160 * 1024;
 constexpr size_t kLdsStatic = 512;   // left to the kernels' own static arrays
+constexpr int kBins = 4096;          // of the order of the list of slowest stages
+constexpr size_t kPrepStatic = kBins * sizeof(int) + 1024; // static arrays of k_exact_prep
+// Whether a launch with so much dynamic LDS beside static arrays has to be announced (hipFuncAttributeMaxDynamicSharedMemorySize).
+inline bool beyond_default(size_t dynamic, size_t fixed) { return dynamic + fixed > 64 * 1024; }
 constexpr int kEvalThreads = 512;    // two workgroups per compute unit where LDS allows
 constexpr int kStagedThreads = 1024; // with stage counts: one, it needs all the LDS
 
@@ -134,6 +138,14 @@ inline int bound_mus(int L, int M, bool staged) {
 inline bool bound_pad(int L, int M, int mus) {
     auto shares = [&](bool pad) { return imin(2, (int)(kLdsLimit / (8 * bound_doubles(L, M, mus, pad) + kLdsStatic))); };
     return can_pad(M) && shares(true) == shares(false);
+}
+// LDS of k_exact_prep beside its static arrays: bytes, times where the fast path needs them, first layers, and `room` entries of the list.
+struct PrepLds { size_t bytes; int room; };
+inline PrepLds prep_lds(int L, int M, bool fast) {
+    const size_t row = (size_t)(L + 1) * M, tables = 8 * ((size_t)(L + 1) + (fast ? row : 0)) + (row + 3) / 4 * 4;
+    const size_t left = kLdsLimit - kPrepStatic - tables, list = 4 * tri(L) * M;
+    const int room = fast ? (int)((list < left ? list : left) / 4) : 0;
+    return {tables + 4 * (size_t)room, room};
 }
 struct Layout { size_t head, PT, flo, ctau, cuvd, lb, blo, bfew, blb, barg, list, over, slots; };
 inline Layout layout(int L, int M, int n_max, bool fast, int mus, bool staged) { // mus: of the stage limit, 0: no bounds

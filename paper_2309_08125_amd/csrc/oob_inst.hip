@@ -668,7 +668,7 @@ static int launch_count(const Spec &s, int64_t *offsets, int32_t *status, hipStr
                            (int)(lds / sizeof(unsigned)));
     } else if (2 * plane <= 128 * 1024) {
         const size_t lds = 2 * plane > scan ? 2 * plane : scan;
-        if (lds > 64 * 1024 &&
+        if (lds > 48 * 1024 && // (as above)
             hipFuncSetAttribute((const void *)k_inst_count<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) != hipSuccess)
             return OOB_EHIP;

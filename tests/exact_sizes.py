@@ -42,6 +42,16 @@ int sums(int L, int M, int n_max) {
 }
 // whether the rows of the profile of (L, M, n_max) are padded in the evaluation
 int padded(int L, int M, int n_max) { return eval_lds(L, M, n_max, n_max, 1, false).pad; }
+// LDS of a launch: what it asks for, whether that is announced.  kernel 0: k_exact_prep of the fast path, 1: k_exact_bounds, 2: k_exact_eval
+// (one template, without stage counts); 0: no such launch
+size_t launch(int kernel, int L, int M, int counts, int *announced) {
+    size_t n = 0;
+    if (kernel == 0) n = prep_lds(L, M, in_doubles(L, M, 1, 1)).bytes;
+    if (kernel == 1) { const int mus = bound_mus(L, M, counts); n = mus ? 8 * bound_doubles(L, M, mus, bound_pad(L, M, mus)) : 0; }
+    if (kernel == 2) n = eval_lds(L, M, 1, 1, 1, false).bytes;
+    *announced = beyond_default(n, kernel ? kLdsStatic : kPrepStatic);
+    return n;
+}
 // offsets in the workspace of a job that takes the LDS path: times and stages of the list, its bounds, the leftovers
 void offsets(int L, int M, int n_max, int counts, int staged, size_t *at) {
     const Layout y = layout(L, M, n_max, true, bound_mus(L, M, counts), staged);
@@ -70,3 +80,25 @@ def head(workspace):
     import torch
 
     return dict(zip(HEAD, workspace[:32].view(torch.int32).tolist()))
+
+
+def static_lds():
+    """Static LDS of the kernels of the exact minimum, the largest of every template, from the metadata of the library that is built."""
+    import re
+    import shutil
+    import tempfile
+
+    from paper_2309_08125_amd import build
+
+    tools, sizes = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin"), {}
+    with tempfile.TemporaryDirectory() as d:
+        lib = shutil.copy(build.LIB, os.path.join(d, "lib.so"))
+        subprocess.run([os.path.join(tools, "llvm-objdump"), "--offloading", lib], check=True, capture_output=True, cwd=d)
+        for name in os.listdir(d):
+            if name.endswith("gfx950"):
+                text = subprocess.run([os.path.join(tools, "llvm-readelf"), "--notes", os.path.join(d, name)], check=True, capture_output=True, text=True).stdout
+                for n, symbol in re.findall(r"\.group_segment_fixed_size: (\d+)(?:(?!\.group_segment).)*?\.symbol: +(\S+)\.kd", text, re.S):
+                    m = re.search(r"k_exact_(prep|bounds|eval)", symbol)
+                    if m:
+                        sizes[m[0]] = max(sizes.get(m[0], 0), int(n))
+    return sizes

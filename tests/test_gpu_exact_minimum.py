@@ -445,6 +445,12 @@ def test_list_of_the_possible_slowest_stages(P, sizes, L, M):
     assert (np.diff(lead - lead.min()).clip(max=1)[: int((lead - lead.min() < 4095).sum()) - 1] >= 0).all()
 
 
+@pytest.mark.parametrize("L,M", [(87, 3), (107, 2), (23, 37)])
+def test_list_that_ends_at_the_default_limit_of_lds(P, sizes, L, M):
+    """The list fits beside its tables in 48 KB, but not in 64 KB with the static arrays of the kernel."""
+    test_list_of_the_possible_slowest_stages(P, sizes, L, M)
+
+
 @pytest.mark.parametrize("M", [1, 3, 4, 8])
 @pytest.mark.parametrize("nb", [2, 7, 8, 9, 10])
 def test_stage_counts_around_whole_groups(P, M, nb):
