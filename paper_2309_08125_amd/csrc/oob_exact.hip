@@ -1420,7 +1420,7 @@ __global__ void __launch_bounds__(STAGED ? kStagedThreads : kEvalThreads, 4) k_e
     Eval e;
     e.pr = load_prof<SUM>(a, s_dyn, PAD ? a.M | 1 : a.M);
     // Places as whole numbers: a difference of pointers into LDS made every access of the pool a flat one (64 layers, 16 GPUs per node, one entry
-    // 145 -> 194 us).
+    // 160 -> 194 us).
     unsigned at = (unsigned)prof_doubles(L, M, PAD ? M | 1 : M, SUM);
     e.reach = (unsigned char *)(s_dyn + at); at += (unsigned)(((size_t)(L + 1) * M + 7) / 8);
     e.NP = s_dyn + at;  at += 2 * (unsigned)(L + 2) * J;

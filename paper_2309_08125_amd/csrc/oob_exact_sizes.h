@@ -97,11 +97,12 @@ inline EvalLds eval_lds(int L, int M, int n_max, int count, int J, bool staged) 
 // With stage counts: whether the one-node tables are taken in LDS throughout.  Those in registers are more steps one after the other, and
 // k_exact_eval<true, 8> spills 200 registers for them, so with eight GPUs per node they lose where LDS has room for a table of every start layer
 // beside the covers and both W of any slowest stage, and no wave has two of them to do: 10 layers, 2 nodes 53 and 72 us, 16 layers 109 and 134
-// us.  With more start layers than waves only few nodes still gain (20 layers, 2 nodes, N_b = 8 182 and 198 us; 4 nodes, N_b = 18 303 and 248 us).
+// us.  With more start layers than waves only few nodes with few stage counts still gain, whose rows over (GPUs, stages) are short (20 layers, 2 nodes:
+// N_b = 8 182 and 198 us, N_b = 11 207 and 198 us; 4 nodes, N_b = 18 303 and 248 us).
 // With four GPUs registers are faster at any depth (10 layers 35 and 30 us).
 inline bool eval_tables_in_lds(int L, int M, int n_max, int J) {
     const size_t row = (size_t)M * (M + 1) / 2 + 1, tables = (size_t)(L - 1) * row + tri(L - 1) * M + (size_t)(L - 1) * L * row;
-    return M == 8 && (L - 1 <= kStagedThreads / 64 || n_max <= 3) && 8 * (eval_fixed(L, M, n_max, n_max, J) + tables) <= kLdsLimit - kLdsStatic;
+    return M == 8 && (L - 1 <= kStagedThreads / 64 || (n_max <= 3 && J <= 10)) && 8 * (eval_fixed(L, M, n_max, n_max, J) + tables) <= kLdsLimit - kLdsStatic;
 }
 
 // No bounds for jobs with at most this many (layer pair, GPU count) triples: the bounds, their filter and the second

@@ -400,7 +400,8 @@ def test_tables_of_a_node_with_stage_counts(P, shape, ends):
         assert st == P.OOB_OK and got == E.exact_minimum_staged(inp), (shape, ends, var)
 
 
-@pytest.mark.parametrize("shape", [(2, 8, 1, 2, 1), (17, 8, 1, 4, 9), (18, 8, 1, 4, 9), (20, 8, 1, 3, 12), (23, 8, 2, 3, 11), (20, 8, 1, 4, 8)])
+@pytest.mark.parametrize("shape", [(2, 8, 1, 2, 1), (17, 8, 1, 4, 9), (18, 8, 1, 4, 9), (20, 8, 1, 3, 12), (23, 8, 2, 3, 11), (20, 8, 1, 4, 8),
+                                   (20, 8, 1, 3, 9), (20, 8, 1, 3, 10), (23, 8, 2, 3, 9)])
 def test_stage_counts_with_tables_in_lds_and_in_registers(P, shape):
     """As many start layers as waves and one more, and few nodes up to the layers whose tables still fit LDS."""
     L, M, n_min, n_max, nb = shape
