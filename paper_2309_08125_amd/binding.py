@@ -591,8 +591,17 @@ class ExactMinimum:
         return int(self.status.item()), [None if v == -1 else int(v) for v in self.best.cpu().numpy()]
 
 
+def _capturing(stream) -> bool:
+    import torch
+
+    with torch.cuda.stream(stream):
+        return torch.cuda.is_current_stream_capturing()
+
+
 class Distributor:
-    """Device buffers for oob_dist_solve / oob_dist_choose over `count` plans of p templates."""
+    """Device buffers for oob_dist_solve / oob_dist_choose over `count` plans of p templates.  The times are copied and the results
+    cleared on the current stream, and neither is waited for: enqueue() on another stream goes behind that one.  A capture into a graph cannot,
+    it has to begin behind it (as torch.cuda.graph does, which waits for the device)."""
 
     def __init__(self, x, count: int, template_T, Q: int, distribution: bool = True, device="cuda:0"):
         """x: int16 device tensor [p, capacity] (uint16 bits, as Instantiator.enqueue fills it) or a host
@@ -603,6 +612,7 @@ class Distributor:
         self.device = torch.device(device)
         if not torch.is_tensor(x):
             x = torch.from_numpy(np.ascontiguousarray(np.asarray(x, dtype=np.uint16).T).view(np.int16)).to(self.device)
+        self._stream = torch.cuda.current_stream(self.device)
         self.x, self.count, self.Q = x, count, Q
         self.p, self.capacity = int(x.shape[0]), int(x.shape[1])
         self.template_T = _to_device([[int(v) for v in template_T]], self.device)
@@ -617,6 +627,8 @@ class Distributor:
         import torch
 
         s = torch.cuda.current_stream(self.device)
+        if s != self._stream and not _capturing(s) and not _capturing(self._stream):
+            s.wait_stream(self._stream)
         check(oob_dist_solve(self.x.data_ptr(), self.count, self.capacity, self.p, self.template_T.data_ptr(), self.Q,
                              self.vx.data_ptr(), self.slowest.data_ptr(),
                              self.base.data_ptr() if self.base is not None else 0,

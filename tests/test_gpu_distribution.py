@@ -468,3 +468,37 @@ def test_times_and_groups_handed_over_on_a_stream_of_the_callers(P):
     inst.offsets.zero_()
     torch.cuda.synchronize()
     assert (again == off).all() and torch.equal(d.slowest, want.slowest) and torch.equal(d.vx, want.vx)
+
+
+def test_solved_on_another_stream_than_it_was_made_on(P):
+    """Counts, times and cleared results are still on their way on a busy stream when another one is asked to solve; then the same from a graph."""
+    import torch
+
+    n0, p, N, f = 2, 5, 20, 2
+    inst = P.Instantiator(None, (f + 1) * n0, N, f, n0=n0, p=p)
+    off, x, st = inst.enumerate()
+    assert st == P.OOB_OK
+    times = [7, 11, 13, 17, 19]
+    want = P.Distributor(x, len(x), times, 40)
+    want.solve()
+    same = lambda: all(torch.equal(getattr(d, k), getattr(want, k)) for k in ("status", "vx", "slowest", "base", "extra"))
+    s = torch.cuda.Stream()
+    busy = torch.empty(1 << 26, dtype=torch.int32, device="cuda")
+    xd = torch.zeros((p, len(x)), dtype=torch.int16, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        for _ in range(20):
+            busy.zero_()
+        inst.enqueue(xd, len(x))
+        d = P.Distributor(xd, len(x), times, 40)
+    d.enqueue()
+    assert same()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        d.enqueue()
+    for _ in range(3):
+        for t in (d.status, d.vx, d.slowest, d.base, d.extra):
+            t.fill_(9)
+        g.replay()
+        torch.cuda.synchronize()
+        assert same()
