@@ -138,8 +138,8 @@ def bench_instantiation(P, inp, res, reps=20):
             "roofline": {"bound": "hbm", "achieved": nbytes / t_enum / 1e9, "peak": 8000.0, "unit": "GB/s",
                          "frac": nbytes / t_enum / 8e12,
                          # rocprofv3 --pmc of this kernel on configuration 4's node specification, scaled as
-                         # above: 154 500 KiB written + 981 KiB read per launch (profiles/k_inst_unrank_config4.md)
-                         "traffic": (154500 + 981) * 1024 if (n0, n_hi, inp.f) == (8, 64, 8) else None,
+                         # above: 157 100 KiB written + 883 KiB read per launch (profiles/k_inst_unrank_config4.md)
+                         "traffic": (157100 + 883) * 1024 if (n0, n_hi, inp.f) == (8, 64, 8) else None,
                          "kernel": "k_inst_unrank", "bytes_per_vector": 2 * p}}
 
 
@@ -239,10 +239,11 @@ def bench_exact(P, planner, inp, res, reps=3):
                     f"({relax_node_tables:.4g} in one-node tables, {relax_node_level:.4g} node-level) for all of them, "
                     "counted on the host",
         "ms": dt_given * 1e3, "value": len(got_given) / dt_given, "unit": "templates/s",
-        "roofline": {"bound": "lds latency", "achieved": None, "peak": None, "unit": None, "frac": None, "traffic": None,
+        "roofline": {"bound": "latency", "achieved": None, "peak": None, "unit": None, "frac": None, "traffic": None,
                      "kernel": "k_exact_eval",
                      "note": "branch and bound: most slowest stages are never evaluated; the evaluation and the bounds "
-                             "are chains of dependent LDS reads, not bound by the vector ALUs or memory"},
+                             "are chains of dependent steps (two thirds of the wave cycles are waits), not bound by LDS or memory; "
+                             "vector instructions are 47 of the evaluation's 104 us a launch"},
         "cpu_baseline": {"seconds": t_cpu, "cores": capi.lib().oob_oracle_threads(), "kind": "oracle",
                          "sample": f"templates for {small.n_min}..{small.n_max} nodes, N_b = {inp.microbatches}"}})
     return out

@@ -160,9 +160,10 @@ int oob_plan_destroy(oob_plan *h);
  *                        default 0: the inner splits of the larger levels run on two streams of the
  *                        library beside the caller's, which carries the outer splits and the selects
  *   OOB_OPT_SELECT8_FROM value = first level S' whose select kernel works with eight lanes per
- *                        state (below it: one lane per state, eight where a level on one stream has few
- *                        states of many candidates); default 82 (the top levels, where
- *                        the select kernel's own latency is what a level waits for)
+ *                        state (below it: one lane per state; eight where a job that may use the library's
+ *                        streams leaves a level of few states with many candidates to the caller's
+ *                        alone); default 82 (the top levels, where the select kernel's own latency is
+ *                        what a level waits for)
  *   OOB_OPT_FUSE_FROM    value = first level S' whose two outer splits (s = 1 and s = S'-1) are
  *                        evaluated inside that select kernel instead of by split launches of
  *                        their own; default 82.  A value of 2 covers every level, one above the

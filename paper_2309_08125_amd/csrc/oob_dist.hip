@@ -430,8 +430,8 @@ __device__ __forceinline__ int solve(const Args &a, const double *s_tT, const un
         }
         {
             // S1 = sum_i N_i T_i and S2 = sum_i (N_i T_i)^2, exactly: all of it is integers in doubles.  sum_i N_i = Q < 2^16, so S1 < 2^51, w = sum N_i^2 of
-            // a template and their sum are at most 2^32 and S2 at most 2^102.  A product and what its rounding left out are two instructions, a sum and
-            // what its rounding left out six; a part left out of T^2 is below 2^16, of T^2 w or of a sum at most 2^48, so that all of
+            // a template and their sum are at most 2^32 and S2 at most 2^102.  A product and what its rounding left out (by fma) are two instructions, a sum and
+            // what its rounding left out (two-sum) six; a part left out of T^2 is below 2^16, of T^2 w or of a sum at most 2^48, so that all of
             // them together, at most 16 templates, come to 2^53 at most.  In 128-bit integers a template takes 60 instructions, a third of them
             // products at a quarter of the rate, here 25.
 #pragma clang fp contract(off)

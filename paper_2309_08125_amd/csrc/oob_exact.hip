@@ -24,8 +24,8 @@
 //   k_exact_eval<kRest>   evaluates these exactly, looking at the bounds again as the minima fall.
 // Small jobs (kDirectMax) skip the bounds and evaluate every stage but those too dear by their time alone.
 // Measured, one call: 98 layers, 8 GPUs per node, 57 templates 20.4 -> 0.39 ms (2 000 evaluations of 17 524 slowest stages);
-// 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 56 us; 48 layers, 8 GPUs per node, N_b = 20 with
-// the limit binding 38.0 -> 0.57 ms (the evaluation of every stage in tables of the workspace before).
+// 26 layers, 4 GPUs per node, N_b = 4 S 171 -> 54 us; 48 layers, 8 GPUs per node, N_b = 20 with
+// the limit binding 38.0 -> 0.54 ms (the evaluation of every stage in tables of the workspace before).
 //
 // k_exact_eval: one workgroup per slowest stage, everything in LDS and registers, times as exact integers in doubles.
 // Phase 1, per wave, no workgroup barrier: the one-node table of start layer q, G_q[r][g] = least cost
@@ -502,7 +502,6 @@ __device__ __forceinline__ double bound_of(const Args &a, const float *lb, doubl
     for (int k = 0; k < a.nk; ++k) x = fmax(x, (double)lb[k] - lo * spent(a, k, n));
     return x;
 }
-// Five waves per SIMD asked for, two workgroups per compute unit; with prices of stages three: a workgroup has most of the LDS there.
 // The rows of one side's path without prices of stages where no stage has more than K layers, one wave: lane = (lambda, GPU
 // count).  A lane keeps, per layer x so far, the path up to x plus what x adds to the time of a stage on its GPUs, and takes
 // the least over as many x as such a stage may have layers.  The last K of them are in LDS, no lane reads another's, and all
@@ -546,6 +545,7 @@ __device__ __forceinline__ void path_rows(const Prof &s, int L, const unsigned c
     }
     wave_sync();
 }
+// Five waves per SIMD asked for, two workgroups per compute unit; with prices of stages three: a workgroup has most of the LDS there.
 template <int MT, bool PAD, bool MUS>
 __global__ void __launch_bounds__(kBoundThreads, MUS ? 3 : 5) k_exact_bounds(Args a, int mus) {
     constexpr int CW = MT ? MT : 8, KL = MUS ? 16 : 32, LL = 64 / KL, MH = MUS ? kMus / 2 : 1; // lanes of a lambda, lambdas and mus of a wave
@@ -810,8 +810,9 @@ __global__ void __launch_bounds__(kFilterThreads) k_exact_filter(Args a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Exact evaluation.  Bound by the vector instructions of the one-node tables (60 % of an entry's 69 000 cycles at 98 layers x 8
-// GPUs, two workgroups a compute unit) and the chain of nodes (25 %).  77 us for the first picks and 135-150 us for the rest there
+// Exact evaluation.  Bound by the steps of an entry, one after the other: at 98 layers x 8 GPUs the one-node tables are 60 % of its
+// 69 000 cycles and the chain of nodes 25 %; the vector instructions of a launch are 47 us of its 104, two thirds of the wave cycles are waits, LDS and
+// memory are far from busy.  81 us for the first picks and 124-130 us for the rest there
 // (140-160 and 280-420 with the tables row after row in LDS; a version without a band,
 // evaluating everything: 20.3 ms, 1.16 us per slowest stage).  J = number of stage counts kept per table
 // entry: 1, or S_max + 1 (STAGED).

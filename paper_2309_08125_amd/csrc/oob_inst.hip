@@ -499,7 +499,7 @@ __device__ __forceinline__ u16x4 transposed(unsigned long long v) {
 //
 // What bounds it: the chain of a vector's pipelines, a read of a row and some 50 instructions each; 1 343 380 vectors take 41 us
 // without the stores and 25 with nothing else.  With the list of N' searched lane by lane, the entries of a row counted, its address
-// multiplied out and two bytes a lane and store 56.5 us, here 51.  Group 0 of all rows in LDS (where most pipelines are): 65; four
+// multiplied out and two bytes a lane and store 56.5 us, here 51 (both for a list of 56 of the sizes; 46 for all 57 by arithmetic).  Group 0 of all rows in LDS (where most pipelines are): 65; four
 // consecutive vectors a lane, which go their common way once: 76, some lane of a wave parts early.
 template <typename CT> // long long, or unsigned when the counting kernel could narrow the table
 __device__ __forceinline__ void unrank_all(const Spec &s, const long long *offsets, unsigned short *x,
